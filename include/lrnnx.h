@@ -288,7 +288,7 @@ typedef struct lrnnx_ss_bwd_args {
     float *dD;                                                     /* [D] out or NULL */
     float *dbias;                                                  /* [D] out or NULL */
     float *dx0;                                                    /* [B,D,N] out or NULL */
-    void *workspace;    size_t workspace_bytes;                    /* LRNNX_WS_BWD, or LRNNX_WS_BWD_CARRY with ckpt */
+    void *workspace;    size_t workspace_bytes;                    /* LRNNX_WS_BWD, or LRNNX_WS_BWD_CARRY with ckpt; plus LRNNX_WS_BWD_SUMS */
     void *stream;
 } lrnnx_ss_bwd_args;
 
@@ -492,7 +492,10 @@ int lrnnx_lti_step(const lrnnx_lti_step_args *args);
 typedef enum { LRNNX_WS_FWD = 0, LRNNX_WS_BWD = 1, LRNNX_WS_LTI = 2, LRNNX_WS_LTI_BWD = 3, LRNNX_WS_DIAG = 4,
                LRNNX_WS_DIAG_BWD = 5, LRNNX_WS_BWD_COMPLEX = 6,
                LRNNX_WS_BWD_CARRY = 7,  /* the chunk aggregates of lrnnx_selective_scan_bwd alone (ckpt supplied) */
-               LRNNX_WS_FWD_COMPLEX = 8
+               LRNNX_WS_FWD_COMPLEX = 8,
+               LRNNX_WS_BWD_SUMS = 9    /* optional, in addition to LRNNX_WS_BWD or LRNNX_WS_BWD_CARRY: partial sums of dBm
+                                         * and dCm.  With it they are added up by a second launch, in a fixed order;
+                                         * without it by float atomics, which is slower */
              } lrnnx_ws_kind;
 
 /* Bytes of device scratch the call may need (the largest over its paths).  bc_groups as in the call's struct (0 or 1:

@@ -20,7 +20,7 @@ LIB_PATH = os.path.join(_HERE, "liblrnnx.so")
 F32, BF16, C64 = 0, 1, 2
 DISC = {"zoh_s6": 0, "zoh": 1, "bilinear": 2, "dirac": 3}
 PATH = {"auto": 0, "single_pass": 1, "chunk_carry": 2}
-WS_FWD, WS_BWD, WS_LTI, WS_LTI_BWD, WS_DIAG, WS_DIAG_BWD, WS_BWD_COMPLEX, WS_BWD_CARRY, WS_FWD_COMPLEX = 0, 1, 2, 3, 4, 5, 6, 7, 8
+WS_FWD, WS_BWD, WS_LTI, WS_LTI_BWD, WS_DIAG, WS_DIAG_BWD, WS_BWD_COMPLEX, WS_BWD_CARRY, WS_FWD_COMPLEX, WS_BWD_SUMS = 0, 1, 2, 3, 4, 5, 6, 7, 8, 9
 STATUS = {0: "ok", 1: "invalid argument", 2: "unsupported", 3: "workspace", 4: "launch"}
 
 _vp, _i32, _i64, _sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
@@ -618,7 +618,8 @@ def lrnnx_selective_scan_bwd(u, delta, A, Bm, Cm, dy, Dskip=None, delta_bias=Non
         a.dx0 = new("dx0", (Bsz, D, N), torch.float32).data_ptr()
     if workspace is None:
         kind = WS_BWD if ckpt is None else WS_BWD_CARRY
-        nbytes = lrnnx_workspace_bytes(kind, Bsz, D, N, L, a.io_dtype, a.bc_groups, packed)
+        nbytes = (lrnnx_workspace_bytes(kind, Bsz, D, N, L, a.io_dtype, a.bc_groups, packed) +
+                  lrnnx_workspace_bytes(WS_BWD_SUMS, Bsz, D, N, L, a.io_dtype, a.bc_groups, packed))
         if nbytes:
             workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
     if workspace is not None:

@@ -144,6 +144,23 @@ void fit_chunks(BwdPlan &pl, size_t nfit) {
     pl.nchunks = (int)nfit;
 }
 
+// Scratch for the tile sums of dBm and dCm of a real backward call (LRNNX_WS_BWD_SUMS): what the widest launch the host may choose
+// for this shape takes, capped for packed batches, whose channels per workgroup depend on the longest sequence.
+size_t bwd_sums_bytes(int64_t B, int64_t D, int64_t N, int64_t L, int64_t bcg, bool packed) {
+    const int64_t dpg = D / bcg;
+    if (packed) {
+        const int64_t G = dpg < kBwdPackedSumG ? dpg : kBwdPackedSumG;
+        return bwd_part_bytes((int)N, lrnnx_packed_ckpt_slots(L, B), bcg * cdiv(dpg, G));
+    }
+    size_t most = 0;
+    for (int path = LRNNX_PATH_AUTO; path <= LRNNX_PATH_CHUNK_CARRY; ++path) {
+        const BwdPlan pl = bwd_plan((int)(B * bcg), (int)dpg, (int)N, L, path, true);
+        const size_t n = bwd_part_bytes((int)N, B * cdiv(L, kBwdTileSteps), bcg * cdiv(dpg, pl.G));
+        if (n > most) most = n;
+    }
+    return most;
+}
+
 // The real and the complex backward entry points take the same per-row tensors (same field names in both argument
 // structs and both parameter blocks): checks and marshalling are written once.
 template <typename Args>
@@ -220,11 +237,12 @@ size_t lrnnx_workspace_bytes(int which, int64_t B, int64_t D, int64_t N, int64_t
     if (B < 1 || D < 1 || L < 1 || bc_groups < 0 || B > 65535 || D > INT32_MAX) return 0;
     const int64_t bcg = bc_groups > 1 ? bc_groups : 1;
     const bool selective = which == LRNNX_WS_FWD || which == LRNNX_WS_BWD || which == LRNNX_WS_BWD_CARRY ||
-                           which == LRNNX_WS_FWD_COMPLEX || which == LRNNX_WS_BWD_COMPLEX;
+                           which == LRNNX_WS_FWD_COMPLEX || which == LRNNX_WS_BWD_COMPLEX || which == LRNNX_WS_BWD_SUMS;
     if (selective) {
         const bool cplx = which == LRNNX_WS_FWD_COMPLEX || which == LRNNX_WS_BWD_COMPLEX;
         if (!(cplx ? supported_n_complex((int)N) : supported_n((int)N)) || D % bcg) return 0;
         const size_t es = cplx ? sizeof(float2) : sizeof(float);
+        if (which == LRNNX_WS_BWD_SUMS) return bwd_sums_bytes(B, D, N, L, bcg, packed != 0) + 512;
         if (which == LRNNX_WS_FWD) return packed ? 0 : (size_t)2 * B * D * fwd_chunks(B, D, L, io_dtype, true) * N * es;
         if (which == LRNNX_WS_FWD_COMPLEX)
             return packed ? 0 : (size_t)2 * B * D * cfwd_chunks(B * bcg * cdiv(D / bcg, 8), L, true) * N * es;
@@ -558,8 +576,10 @@ int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
     p.tiles_per_chunk = pl.tiles_per_chunk;
     if (cu && pl.nchunks == 1)
         bwd_packed_shape(a->B, a->D, a->L, a->max_seqlen, bwd_channels_per_group(a->B * bcg, a->D / bcg, a->N, a->L, true),
-                         2048 / bwd_waves_per_workgroup(a->N), &p.G, &p.wcap, &p.gmin);
+                         bwd_places(a->N), &p.G, &p.wcap, &p.gmin);
+    size_t used = carry_off;                          // bytes of the workspace taken so far
     if (pl.nchunks > 1) {
+        used += (size_t)2 * a->B * a->D * p.nchunks * a->N * sizeof(float);
         p.ws_P = reinterpret_cast<float *>(static_cast<char *>(a->workspace) + carry_off);
         p.ws_Q = p.ws_P + (size_t)a->B * a->D * p.nchunks * a->N;
         p.hc = p.ws_Q;
@@ -573,13 +593,23 @@ int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
         int *order = reinterpret_cast<int *>(static_cast<char *>(a->workspace) + carry_off);
         if (launch_seq_order(cu, a->B, a->L, order, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
         p.order = order;
+        used = carry_off + sizeof(int) * (size_t)a->B;
     }
+    // room behind that for the tile sums of dBm and dCm 
+    const int64_t slots = cu ? nslots : a->B * nck;
+    p.part_tiles = nck;
+    const uintptr_t part = align256(reinterpret_cast<uintptr_t>(a->workspace) + used);
+    if (a->workspace && part + bwd_part_bytes(a->N, slots, bwd_grid_x(p)) <= reinterpret_cast<uintptr_t>(a->workspace) + a->workspace_bytes)
+        p.part = reinterpret_cast<float *>(part);
 
-    // reduced outputs are accumulated with atomics: clear them on the stream first
+    // reduced outputs that are accumulated with atomics: clear them on the stream first (dBm and dCm of a packed batch in
+    // any case: rows outside every sequence are zero)
     const int64_t nbc = (cu ? 1 : (int64_t)a->B) * bcg * a->L * a->N;   // packed mode: one time axis for all sequences
     FillList z{};
-    z.ptr[0] = a->dBm; z.count[0] = nbc;
-    z.ptr[1] = a->dCm; z.count[1] = nbc;
+    if (!p.part || cu) {
+        z.ptr[0] = a->dBm; z.count[0] = nbc;
+        z.ptr[1] = a->dCm; z.count[1] = nbc;
+    }
     z.ptr[2] = a->dA; z.count[2] = (int64_t)a->D * a->N;
     z.ptr[3] = a->dD; z.count[3] = a->D;
     z.ptr[4] = a->dbias; z.count[4] = a->D;

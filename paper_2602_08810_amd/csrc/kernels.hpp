@@ -107,9 +107,15 @@ struct BwdParams {
     // workgroup of a long sequence then takes wcap / tiles channels, between gmin and G, and the workgroups of the
     // launch that its sequence does not need leave at once.
     int wcap, gmin;
+    // Workspace of the tile sums of dBm and dCm, one slot per (256-step tile, workgroup of grid.x, map), added up by a second
+    // launch; null: the kernel adds them to dBm and dCm with float atomics.  part_tiles: tiles of a batch entry
+    // (a packed batch counts its tiles like its checkpoint slots).
+    float *part;
+    int64_t part_tiles;
 };
 constexpr int kBwdTileSteps = 256;
 constexpr int kBwdMinG = 4;
+constexpr int kBwdPackedSumG = 8;    // channels per workgroup that the tile sums of a packed batch are sized for
 // launch shape of a packed batch of B sequences on L steps, D channels, whose longest has max_seqlen steps (0: not
 // known, nothing changes): *G comes in as the channels per workgroup of a batch of unknown lengths and may be raised
 // to Gbal, those of a batch [B,D,L] of equal lengths; else cap and fewest channels as in BwdParams.  `places` =
@@ -271,6 +277,8 @@ int lti_chunk_group();                       // chunks (wavefronts) of one workg
 int lti_onepass_anchor();                    // every how many groups the single-launch LTI scan publishes a true state
 int fwd_tile_steps(int io_dtype);            // time steps one workgroup covers per tile
 int bwd_channels_per_group(int B, int D, int N, int64_t L, bool balanced);
-int bwd_waves_per_workgroup(int N);
+int bwd_places(int N);                       // workgroups of the backward kernel the chip holds at once
+int bwd_grid_x(const BwdParams &p);
+size_t bwd_part_bytes(int N, int64_t tile_slots, int64_t grid_x);
 
 }  // namespace lrnnx

@@ -8,82 +8,180 @@
 //     du_l     += H_l g_l Bm_{l,n}      da_l = H_l x_{l-1}          dg_l = H_l Bm_{l,n} u_l
 //     dDelta_l += da_l da/dDelta + dg_l dg/dDelta                    dA_n += da_l da/dA + dg_l dg/dA
 //
-// Mapping.  Time runs along the lanes as in the forward kernel (lane i owns T consecutive steps of
-// the tile), but the N states are split over the W = N/NK wavefronts of the workgroup, which all
-// work on the same channel at the same time.  A wavefront therefore keeps its NK columns of Bm/Cm
-// for the tile, and the running sums of dBm/dCm over channels, in registers while the workgroup
-// loops over G channels: the reduction of dBm/dCm over channels costs no memory traffic and no
-// per-element atomics inside the loop (LDS float atomics are very slow on this chip when every lane
-// takes part; only the few lanes that own a per-channel sum use them).  What is summed over n
-// (du, dDelta, ypre for dz) is exchanged through LDS once per (channel, tile): each wavefront
-// writes its partial sums, and after a barrier the threads share the epilogue of the 64*T steps
-// in flat order, so u/delta/dy/z are each read once and du/ddelta/dz written once, coalesced.
-// At the end of a tile the dBm/dCm sums are transposed through LDS and added to global memory
-// with fully coalesced float atomics (other workgroups hold other channel groups).
+// Mapping.  A workgroup of W = N/4 wavefronts works on one tile of 256 steps at a time, last tile first, and on two
+// channels at a time: the halves of a wavefront are the two channels, and lane i of a half owns T = 8 consecutive steps
+// of the tile.  A wavefront holds four states, one after the other in the same registers, so a prefix over the tile is
+// a scan of 32 lanes shared by 8 steps.  The workgroup loops over G channels; a lane keeps its columns of Bm and Cm (4
+// states x 8 steps) and the running sums of dBm and dCm over channels in registers, so the reduction over channels costs
+// no traffic inside the loop.  What is summed over states (ypre for dz, du, dDelta) is added over the wavefront's
+// states in registers and over wavefronts through LDS: after a barrier every thread finishes a few consecutive steps
+// of one channel (epilogue) and prepares the same steps of the next pair of channels (prologue).
+//
+// What bounds it: vector-ALU issue.  With exponentials and DPP instructions in the stream a SIMD issues one vector
+// instruction every four cycles, whatever its kind and however many wavefronts it holds (an exponential takes two such
+// slots), so the time is the number of instructions: 22.6 slots per state update in the main part (15 multiply-adds
+// and products, 3 for the exponential and its argument, 3.6 for the two scans and the fold's product) and about 5 for
+// prologue, epilogue and the work per tile.  Time on 64 lanes with 4 steps each and all four states of a wavefront
+// scanned together took 34.8.  Mamba-block shape (B=8, D=1536, N=16, L=2048, bf16): 440 -> 358 us + 25 us for the
+// sums of dBm and dCm; B=16, D=2560, L=4096: 2630 -> 2190 us.  Also tried: four channels per wavefront on rows of 16
+// lanes with 16 steps each (19.7 slots, but twice the LDS traffic and one workgroup per compute unit: 560 us), halves
+// holding different states at three wavefronts per SIMD (25.4 slots and a swap-and-add per sum: 431 us).
 #include "kernels.hpp"
 #include "scan_common.hpp"
+#include <type_traits>
 
 namespace lrnnx {
 
-constexpr int kMaxG = 128;
+constexpr int kMaxG = 128;                           // channels of a workgroup (sizes the tables in LDS)
 
-template <typename IO, int N, int NK, int T, int DISC, bool DZ>
-__global__ __launch_bounds__((N / NK) * 64, 2) void k_ss_bwd(const BwdParams p) {
-    constexpr int W = N / NK;
-    constexpr int NT = W * 64;
-    constexpr int TILE = 64 * T;
-    constexpr int TPW = TILE / NT > 0 ? TILE / NT : 1;   // flat steps per thread in prologue / epilogue
-    constexpr int NA = TILE / TPW;                   // threads that take part in them: all, or (N = 32) the first 256
-    constexpr int TQ = T / 4;
-    constexpr int CK_PER_TILE = TILE / (int)kCkptInterval;
-    // states whose scans advance together: all of the wavefront's, or two for the schemes that also keep the gains
-    // g of every step (more registers)
-    constexpr int JSW = (DISC == DISC_ZOH || DISC == DISC_BILINEAR) ? 2 : 4;
-    constexpr int JS = NK < JSW ? NK : JSW;
-    static_assert(T % 4 == 0 && (T % W == 0 || W % T == 0) && TPW <= 8 && NA % 64 == 0 && NA <= NT, "tile shape");
-    static_assert(TILE % kCkptInterval == 0, "tiles must start on checkpoints");
-    static_assert(TILE == kBwdTileSteps, "the chunked launch counts its chunks in tiles of this kernel");
+// Both scans of one state over the 32 lanes of each half-wavefront: on return S is the inclusive prefix (lane 0 of the
+// half first) and Q the inclusive suffix (lane 31 first) of the pairs (P, S) and (P, Q), xin the prefix of the lane
+// before (lane 0 keeps what it came with) and Gin the suffix of the lane after (lane 31 keeps it).  The two scans
+// alternate, so that a DPP read of a register comes at least two instructions after its last write.  The suffix of a
+// half's upper row reaches the last lane of the lower row by a shift of the whole wavefront, and the row's other lanes
+// from there.
+__device__ __forceinline__ void half_scans(float P, float &S, float &Q, float &xin, float &Gin) {
+    float Pr = P;
+    asm("s_nop 1\n\t"
+        LRNNX_FR_STATE(0, 1, 2, 3, "row_shr:1" LRNNX_ALLROWS, "row_shl:1" LRNNX_ALLROWS)
+        LRNNX_FR_STATE(0, 1, 2, 3, "row_shr:2" LRNNX_ALLROWS, "row_shl:2" LRNNX_ALLROWS)
+        LRNNX_FR_STATE(0, 1, 2, 3, "row_shr:4" LRNNX_ALLROWS, "row_shl:4" LRNNX_ALLROWS)
+        LRNNX_FR_STATE(0, 1, 2, 3, "row_shr:8" LRNNX_ALLROWS, "row_shl:8" LRNNX_ALLROWS)
+        : "+v"(S), "+v"(P), "+v"(Q), "+v"(Pr));
+    float Qn;                                        // lane 15 of rows 0 and 2: the first lane of the row after
+    asm("s_nop 0\n\t"
+        "v_fmac_f32_dpp %0, %0, %5 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "v_mov_b32_dpp %4, %1 wave_shl:1 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_mov_b32_dpp %2, %0 wave_shr:1 row_mask:0xa bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %4, %6 row_newbcast:15 row_mask:0x5 bank_mask:0xf\n\t"
+        "v_mov_b32_dpp %2, %0 row_shr:1 row_mask:0x5 bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_mov_b32_dpp %3, %1 wave_shl:1 row_mask:0x5 bank_mask:0xf\n\t"
+        "v_mov_b32_dpp %3, %1 row_shl:1 row_mask:0xa bank_mask:0xf"
+        : "+v"(S), "+v"(Q), "+v"(xin), "+v"(Gin), "=&v"(Qn) : "v"(P), "v"(Pr));
+}
 
-    __shared__ __attribute__((aligned(16))) float sIn[3 * TILE];          // delta, u, dypre   [q][lane][4]
-    __shared__ __attribute__((aligned(16))) float sPart[W * 3 * TILE];    // per wave: ypre, du, ddelta partials
-    __shared__ __attribute__((aligned(16))) float sBt[N * TILE];          // Bm columns of the tile, fp32: [n][q][lane][4], wave-private slices
-    __shared__ float sH[kMaxG * N];       // a_{l0} H_{l0} carried to the earlier tile, per (channel, n)
-    __shared__ float sdA[2][kMaxG * N];   // per half-wavefront partial sums of dA (added up when they are flushed)
-    __shared__ float sdD[2 * W * kMaxG];  // dD and dbias partial sums per (half-wavefront, wavefront, channel)
-    __shared__ float sdb[2 * W * kMaxG];
+// CNT consecutive steps of a tile of 256 in LDS: laid out [step % 8 / 4][step / 8][step % 4], so that a lane's 8 steps
+// are two conflict-free 16-byte accesses, the second half rotated by half the banks, so that consecutive threads of
+// the prologue and epilogue (a few steps each) touch every bank once as well.  f is a multiple of CNT.
+__device__ __forceinline__ int step_slot(int f) { return ((f & 4) << 5) + (((f >> 3) << 2) ^ ((f & 4) << 3)) + (f & 3); }
+template <int CNT>
+__device__ __forceinline__ void lds_steps_read(const float *plane, int slot, float *out) {
+    const float *p = plane + slot;
+    if constexpr (CNT == 1) out[0] = p[0];
+    else if constexpr (CNT == 2) { const float2 v = *reinterpret_cast<const float2 *>(p); out[0] = v.x; out[1] = v.y; }
+    else {
+#pragma unroll
+        for (int q = 0; q < CNT / 4; ++q) {
+            const float4 v = *reinterpret_cast<const float4 *>(plane + (q ? (slot ^ 32) + 128 : slot));
+            out[4 * q] = v.x; out[4 * q + 1] = v.y; out[4 * q + 2] = v.z; out[4 * q + 3] = v.w;
+        }
+    }
+}
+template <int CNT>
+__device__ __forceinline__ void lds_steps_write(float *plane, int slot, const float *v) {
+    float *p = plane + slot;
+    if constexpr (CNT == 1) p[0] = v[0];
+    else if constexpr (CNT == 2) *reinterpret_cast<float2 *>(p) = make_float2(v[0], v[1]);
+    else {
+#pragma unroll
+        for (int q = 0; q < CNT / 4; ++q)
+            *reinterpret_cast<float4 *>(plane + (q ? (slot ^ 32) + 128 : slot)) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    }
+}
+
+// CNT consecutive elements of a row, wholly inside it: wave-uniform base plus a lane's 32-bit offset
+template <typename IO, int CNT>
+__device__ __forceinline__ void load_at(const IO *row, unsigned f, RawFew<IO, CNT> &r) {
+    load_few_raw<IO, CNT>(reinterpret_cast<const IO *>(reinterpret_cast<const char *>(row) + f * (unsigned)sizeof(IO)), 0, CNT, true, r);
+}
+template <typename IO, int CNT>
+__device__ __forceinline__ void store_at(IO *row, unsigned f, const float *v) {
+    store_few<IO, CNT>(reinterpret_cast<IO *>(reinterpret_cast<char *>(row) + f * (unsigned)sizeof(IO)), 0, CNT, true, v);
+}
+
+template <int CNT>
+__device__ __forceinline__ void lds_few(const float *p, float *out) {       // CNT = 1, 2 or 4, p aligned to as many floats
+    if constexpr (CNT == 4) { const float4 v = *reinterpret_cast<const float4 *>(p); out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w; }
+    else if constexpr (CNT == 2) { const float2 v = *reinterpret_cast<const float2 *>(p); out[0] = v.x; out[1] = v.y; }
+    else out[0] = p[0];
+}
+
+// Geometry of a workgroup for N states.
+template <int N> struct BwdGeom {
+    static constexpr int W = N == 4 ? 2 : (N >= 4 ? N / 4 : 1);      // wavefronts
+    static constexpr int NS = N / W;                 // states of a wavefront, one after the other
+    static constexpr int NT = W * 64;
+    static constexpr int CP = 2;                     // channels per pass
+    static constexpr int TPT = CP * kBwdTileSteps / NT;       // steps of a thread in prologue and epilogue
+    static constexpr int NTC = kBwdTileSteps / TPT;           // threads that share a channel there
+    // one wavefront: a lane's steps of the main part are its own of the prologue and epilogue, nothing goes through LDS;
+    // two: two barriers per pass, single buffers (the LDS of a compute unit then holds eight wavefronts); more: one
+    // barrier per pass, double buffers
+    static constexpr bool OWN = W == 1;
+    static constexpr int NB = W >= 4 ? 2 : 1;        // buffers
+};
+
+// `sequence bounds of batch entry b`: packed variable-length mode (cu != nullptr): batch entry b is the sequence of
+// steps cu[b] .. cu[b+1]-1 of ONE packed time axis of Lp steps.  The bounds are clamped to the packed axis, so no
+// content of cu can send an access out of the buffers.
+__device__ __forceinline__ void seq_bounds(const int64_t *cu, int b, int64_t Lp, int64_t &toff, int64_t &L) {
+    int64_t o = cu[b], e = cu[b + 1];
+    o = o < 0 ? 0 : (o > Lp ? Lp : o);
+    e = e < o ? o : (e > Lp ? Lp : e);
+    toff = o; L = e - o;
+}
+// channels per workgroup for a sequence of ntiles tiles: fewer than G in a packed batch with a work cap
+__device__ __forceinline__ int channels_of(const BwdParams &p, int64_t ntiles) {
+    if (p.wcap <= 0) return p.G;
+    const int64_t fit = p.wcap / (ntiles > 0 ? ntiles : 1);
+    return fit < p.gmin ? p.gmin : (fit < p.G ? (int)fit : p.G);
+}
+
+template <typename IO, int N, int DISC, bool HAS_Z>
+__global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p) {
+    using GE = BwdGeom<N>;
+    constexpr int W = GE::W, NS = GE::NS, NT = GE::NT, CP = GE::CP, TPT = GE::TPT, NTC = GE::NTC;
+    constexpr int T = 8, TILE = kBwdTileSteps;
+    static_assert(TILE == kCkptInterval && TILE == 32 * T, "a tile is one checkpoint interval and one half-wavefront");
+
+    constexpr bool OWN = GE::OWN;
+    constexpr int NB = GE::NB;
+    __shared__ __attribute__((aligned(16))) float sIn[NB][CP][3][OWN ? 4 : TILE];       // delta, u, dypre of a pair of channels
+    __shared__ __attribute__((aligned(16))) float sPart[NB][CP][W][3][OWN ? 4 : TILE];  // per wavefront: ypre, du, ddelta partials
+    __shared__ __attribute__((aligned(16))) float sH[kMaxG * N];   // a_{l0} H_{l0} carried to the earlier tile, per (channel, n)
+    __shared__ __attribute__((aligned(16))) float sAC[NB][2][CP][N];   // A and the state entering the tile, of a pair
+    __shared__ float sdA[kMaxG * N];
+    __shared__ float sdD[kMaxG], sdb[kMaxG];
+    __shared__ float sDskip[kMaxG], sBias[kMaxG];
 
     // Two workgroups share a compute unit, so each SIMD holds one wavefront of each.  The issue arbiter prefers the
-    // older wavefront, the older workgroup finishes some 17 % earlier and the younger one then runs alone, badly
-    // hiding its latencies (measured: 474 us against 570 us on the Mamba-block shape).  With four wavefronts per
-    // workgroup the two wavefronts of a SIMD therefore take turns at the higher issue priority, one channel each
-    // (told apart by the lowest bit of the hardware wavefront slot): 5-7 % faster on every shape tried.  Not with
-    // eight wavefronts per workgroup (both wavefronts of a SIMD then belong to one workgroup and meet at its
-    // barriers: 7 % slower), and of no effect with two.
-    constexpr bool ALT_PRIO = (N / NK == 4);
+    // older wavefront, the older workgroup finishes earlier and the younger one then runs alone, badly hiding its
+    // latencies.  With four wavefronts per workgroup the two wavefronts of a SIMD therefore take turns at the higher issue
+    // priority, one pass each (told apart by the lowest bit of the hardware wavefront slot).
+    constexpr bool ALT_PRIO = W == 4;
     [[maybe_unused]] const unsigned hw_slot = ALT_PRIO ? (__builtin_amdgcn_s_getreg(6148) & 1u) : 0u;   // HW_ID.WAVE_ID, bit 0
     const int tid = threadIdx.x;
-    const int lane = tid & 63;
+    const int lane = tid & 63, li = lane & 31, half = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n0 = w * NS;                           // this wavefront's first state
     // packed batches: workgroups start in launch order, so the longest sequences go first and the short ones fill the
     // end of the launch instead of a long one running on alone
     const int b = p.order ? p.order[blockIdx.y] : blockIdx.y;
-    // Packed variable-length mode (p.cu != nullptr): batch entry b is the sequence of steps cu[b] .. cu[b+1]-1 of ONE
-    // packed time axis of p.L steps; I/O rows have no batch stride, the maps are [G, p.L, N].  The bounds are
-    // clamped to the packed axis, so no content of cu can send an access out of the buffers.
     int64_t L = p.L, toff = 0, bs = b;
-    if (p.cu) {
-        int64_t o = p.cu[b], e = p.cu[b + 1];
-        o = o < 0 ? 0 : (o > p.L ? p.L : o);
-        e = e < o ? o : (e > p.L ? p.L : e);
-        toff = o; L = e - o; bs = 0;
-    }
+    if (p.cu) { seq_bounds(p.cu, b, p.L, toff, L); bs = 0; }
+    const int64_t slot0 = p.cu ? toff / TILE + b : (int64_t)b * p.part_tiles;    // first tile of this entry among all tiles
     // Chunked launch: this workgroup walks chunk blockIdx.z of its rows only, i.e. the steps toff .. toff + L - 1 of
     // the time axis, starting from that chunk's carried adjoint.  Chunks are counted from the start of the sequence;
     // the last one takes whatever is left (see chunk_span in selective_bwd_carry.hip), and the workgroups of a packed
     // sequence that ends before their chunk leave here, all threads together and before any barrier (chunk 0 stays
     // even for an empty sequence: it writes that sequence's dx0).
     const int chunk = blockIdx.z;
+    const int64_t ntiles_seq = (L + TILE - 1) / TILE;
+    int64_t tile_first = 0;                          // first tile of the chunk within its sequence
     if (p.nchunks > 1) {
+        tile_first = chunk * p.tiles_per_chunk;
         const int64_t span = p.tiles_per_chunk * TILE;
         const int64_t left = L - chunk * span;
         if (chunk > 0 && left <= 0) return;
@@ -94,561 +192,552 @@ __global__ __launch_bounds__((N / NK) * 64, 2) void k_ss_bwd(const BwdParams p) 
     // a workgroup takes up to G consecutive channels of ONE Bm/Cm group; in a packed batch with a work cap fewer when
     // its sequence is long, and the workgroups of the launch that its sequence then does not need leave here, all
     // threads together and before any barrier
-    int G = p.G;
-    if (p.wcap > 0) {
-        const int64_t fit = p.wcap / (ntiles > 0 ? ntiles : 1);
-        G = fit < p.gmin ? p.gmin : (fit < G ? (int)fit : G);
-    }
-    const int chunks_per_grp = (p.dpg + G - 1) / G;
-    if ((int)blockIdx.x >= p.bcg * chunks_per_grp) return;
-    const int grp = blockIdx.x / chunks_per_grp;
-    const int din0 = (blockIdx.x % chunks_per_grp) * G;
+    const int G = channels_of(p, ntiles_seq);
+    const int blocks_per_grp = (p.dpg + G - 1) / G;
+    if ((int)blockIdx.x >= p.bcg * blocks_per_grp) return;
+    const int grp = blockIdx.x / blocks_per_grp;
+    const int din0 = (blockIdx.x % blocks_per_grp) * G;
     const int d0 = grp * p.dpg + din0;
     const int Gact = (p.dpg - din0 < G) ? p.dpg - din0 : G;
-    const int bcrow = b * p.bcg + grp;                               // row of Bm, Cm, dBm, dCm (unpacked)
     // checkpoints of this workgroup's rows: [B,D,nck,N], or packed [D,nslots,N] with sequence b at slot toff/interval + b
     const int64_t nck = p.cu ? p.nslots : (p.L + kCkptInterval - 1) / kCkptInterval;
     const int64_t ck0 = p.cu ? toff / kCkptInterval + b : toff / kCkptInterval;
+    const float *ckrow = p.ckpt + (((p.cu ? (int64_t)d0 : (int64_t)b * p.D + d0) * nck) + ck0) * N;
     const bool vec = p.vec != 0;
-    const bool has_z = p.z != nullptr;
 
-    for (int i = tid; i < kMaxG * N; i += NT) {
+    for (int i = tid; i < Gact * N; i += NT) {
         float h = 0.0f;
-        if (p.nchunks > 1 && i < Gact * N)
-            h = p.hc[(((int64_t)b * p.D + d0 + i / N) * p.nchunks + chunk) * N + i % N];
-        sH[i] = h; sdA[0][i] = 0.0f; sdA[1][i] = 0.0f;
+        if (p.nchunks > 1) h = p.hc[(((int64_t)b * p.D + d0 + i / N) * p.nchunks + chunk) * N + i % N];
+        sH[i] = h; sdA[i] = 0.0f;
     }
-    for (int i = tid; i < 2 * W * kMaxG; i += NT) { sdD[i] = 0.0f; sdb[i] = 0.0f; }
+    for (int i = tid; i < Gact; i += NT) {
+        sdD[i] = 0.0f; sdb[i] = 0.0f;
+        sDskip[i] = p.Dskip ? p.Dskip[d0 + i] : 0.0f;
+        sBias[i] = p.bias ? p.bias[d0 + i] : 0.0f;
+    }
 
-    const int64_t bc0 = ((p.cu ? (int64_t)grp : (int64_t)bcrow) * p.L + toff) * N;   // first element of the maps of this sequence
+    const int64_t bc0 = ((p.cu ? (int64_t)grp : (int64_t)b * p.bcg + grp) * p.L + toff) * N;   // first element of the maps of this sequence
     const IO *Bm = reinterpret_cast<const IO *>(p.Bm) + bc0;
     const IO *Cm = reinterpret_cast<const IO *>(p.Cm) + bc0;
 
-    // flat position of this thread in prologue / epilogue, and its slot in the [q][lane][4] layout
-    const int f0 = tid * TPW;
-    const bool io_thread = NA == NT || tid < NA;                     // wave-uniform: NA is a multiple of 64
-    auto fslot = [](int f) { return (((f % T) / 4) * 64 + f / T) * 4 + (f % 4); };
+    // this thread's channel of a pair and its steps in prologue / epilogue
+    int c_own = tid / NTC;
+    if constexpr (NTC >= 64) c_own = __builtin_amdgcn_readfirstlane(c_own);
+    // The addresses that follow from the thread's number are formed where they are needed: hoisted out of the loops by the
+    // compiler they would sit in registers all through the main pass, which has none to spare.
+    auto fresh = [](unsigned v) { asm volatile("" : "+v"(v)); return v; };
+    const unsigned first_lane = li == 0 ? ~0u : 0u, last_lane = li == 31 ? ~0u : 0u;
 
-    // ---- The dBm/dCm sums of a tile (over the workgroup's channels) are added to global memory one tile late: after
-    // the next tile's loads have been issued, so that those round trips run while the flush goes through LDS, and so
-    // that nothing has to wait for the atomics (the memory counter is in order: a load issued after them cannot be
-    // claimed before they are done, and all workgroups flush at about the same time).  The sums are transposed
-    // through LDS so that consecutive threads hit consecutive addresses: two rounds of 32 lanes each, in the area of
-    // the Bm columns (the tile they belonged to is finished, the next tile stages its own after the flush).
-    // `mid` runs after the first round's trip through LDS, before the first atomic.
-    float dBacc[NK][T], dCacc[NK][T];
-    int64_t fl_l0 = 0;                                               // first step of the tile the sums belong to
-    int fl_rem = 0;                                                  // its valid steps; 0: nothing to flush
-    auto flush = [&](auto &&mid) {
-        constexpr int FL = 32;                                           // lanes per round
-        float *fbB = sBt, *fbC = sBt + FL * T * N;
-        static_assert(2 * FL * T * N <= N * TILE, "flush buffer must fit in the Bm area");
-#pragma unroll
-        for (int j = 0; j < 64 / FL; ++j) {
-            __syncthreads();
-            // A lane's values of one step are NK consecutive floats of that step's row.  With NK = 4 they go out as one
-            // 16-byte write; lanes are T * N floats apart, which would put all of them on the same banks (measured:
-            // the 32-way conflicts of the plain layout made the flush 11 % of the kernel), so the 16-byte chunk index
-            // is XORed with the lane's low bits: eight consecutive lanes then cover all banks, and a reader's 64
-            // consecutive floats stay a permutation of whole chunks within the same 8-chunk block.
-            constexpr bool SWZ = NK == 4;
-            constexpr int CPL = T * N / 4;                               // 16-byte chunks per lane
-            if (lane / FL == j) {
-                // (the addresses are formed here and now: hoisted out of the tile loop they would sit in registers
-                // all through the channel loop, which has none to spare)
-                int lr = lane % FL;
-                asm volatile("" : "+v"(lr));
-#pragma unroll
-                for (int t = 0; t < T; ++t) {
-                    if constexpr (SWZ) {
-                        const int c4 = ((lr * T + t) * (N / 4) + w) ^ (lr & 7);
-                        *reinterpret_cast<float4 *>(&fbB[c4 * 4]) = make_float4(dBacc[0][t], dBacc[1][t], dBacc[2][t], dBacc[3][t]);
-                        *reinterpret_cast<float4 *>(&fbC[c4 * 4]) = make_float4(dCacc[0][t], dCacc[1][t], dCacc[2][t], dCacc[3][t]);
-                    } else {
-#pragma unroll
-                        for (int k = 0; k < NK; ++k) {
-                            fbB[(lr * T + t) * N + w * NK + k] = dBacc[k][t];
-                            fbC[(lr * T + t) * N + w * NK + k] = dCacc[k][t];
-                        }
-                    }
-                }
-            }
-            __syncthreads();
-            const int step0 = j * FL * T;                                // within the tile
-            float *gB = p.dBm + bc0 + (fl_l0 + step0) * N, *gC = p.dCm + bc0 + (fl_l0 + step0) * N;
-            // each thread's values are read from LDS in one batch, then added (one round trip instead of one per value)
-            constexpr int PER = FL * T * N / NT;                         // = T * NK / 2
-            static_assert(PER * NT == FL * T * N, "the flush buffer is a whole number of values per thread");
-            float vB[PER], vC[PER];
-            int tf = tid;
-            asm volatile("" : "+v"(tf));
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                const int idx = tf + i * NT;
-                const int at = SWZ ? ((((idx >> 2) ^ (((idx >> 2) / CPL) & 7)) << 2) | (idx & 3)) : idx;
-                vB[i] = fbB[at]; vC[i] = fbC[at];
-            }
-            if (j == 0) mid();
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                const int idx = tid + i * NT;
-                if (step0 + idx / N < fl_rem) {
-                    unsafeAtomicAdd(gB + (unsigned)idx, vB[i]);
-                    unsafeAtomicAdd(gC + (unsigned)idx, vC[i]);
-                }
-            }
-        }
-        __syncthreads();
-    };
-
-    for (int64_t tile = ntiles - 1; tile >= 0; --tile) {
+    // One tile.  FULL: all of its steps are valid and every row takes vector accesses, nothing to check per element (a
+    // taken branch costs a wavefront about a hundred cycles).
+    auto do_tile = [&](int64_t tile, auto full) {
+        constexpr bool FULL = decltype(full)::value;
         const int64_t l0 = tile * TILE;
-        const int rem = (L - l0 < TILE) ? (int)(L - l0) : TILE;      // valid steps of this tile
-        // all global addresses below are a wave-uniform base plus a small unsigned per-lane offset, so that
-        // they need one 32-bit register per lane instead of a 64-bit induction variable each
-        const IO *BmT = Bm + l0 * N + w * NK, *CmT = Cm + l0 * N + w * NK;
+        const int rem = FULL ? TILE : ((L - l0 < TILE) ? (int)(L - l0) : TILE);      // valid steps of this tile (at least one)
 
-        // ---- this wavefront's NK columns of Bm/Cm for the tile: fetched here (raw), used after the flush of the
-        // tile before (below), so that the round trip runs while that flush goes through LDS.  Every row is loaded
-        // without a branch (past the end of the tile the last valid row is read again and then discarded), so that
-        // all 2 T loads of a lane are in flight together instead of one round trip per step.
-        RawFew<IO, NK> rB[T], rC[T];
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const int step = lane * T + t;
-            const int row = step < rem ? step : rem - 1;                  // rem >= 1: a tile has at least one step
-            load_few_raw<IO, NK>(BmT + (unsigned)(row * N), 0, NK, true, rB[t]);
-            load_few_raw<IO, NK>(CmT + (unsigned)(row * N), 0, NK, true, rC[t]);
-        }
-
-        // Per-channel inputs are fetched one channel ahead, so that their latency hides behind the main pass.  Every
-        // memory access of the channel loop is unconditional straight-line code (rows past the end of the tile, absent
-        // optional inputs and the channel past the last one read a valid address again and the value is discarded).
-        // (Fetching two channels ahead into two register sets was tried: the doubled loop body costs more than the
-        // longer distance gains.)
-        struct Pref { RawFew<IO, TPW> u, dl, dy, z; float A[NK], ck[NK], Dsk, bias; };
-        Pref S0;
-        // Row pointers (wave-uniform) of the channel the next prefetch reads and of the channel the next epilogue
-        // writes: set once per tile and stepped by one channel stride each time, so that the channel loop carries no
-        // 64-bit multiplications.
-        const int64_t tl = toff + l0;
-        const IO *n_u = reinterpret_cast<const IO *>(p.u) + bs * p.u_sb + d0 * p.u_sd + tl;
-        const IO *n_dl = reinterpret_cast<const IO *>(p.delta) + bs * p.dl_sb + d0 * p.dl_sd + tl;
-        const IO *n_dy = reinterpret_cast<const IO *>(p.dy) + bs * p.dy_sb + d0 * p.dy_sd + tl;
-        const IO *n_z = has_z ? reinterpret_cast<const IO *>(p.z) + bs * p.z_sb + d0 * p.z_sd + tl : n_dy;
-        const int64_t z_step = has_z ? p.z_sd : p.dy_sd;
-        IO *o_du_row = reinterpret_cast<IO *>(p.du) + bs * p.du_sb + d0 * p.du_sd + tl;
-        IO *o_dd_row = reinterpret_cast<IO *>(p.ddelta) + bs * p.dd_sb + d0 * p.dd_sd + tl;
-        IO *o_dz_row = DZ ? reinterpret_cast<IO *>(p.dz) + bs * p.dz_sb + d0 * p.dz_sd + tl : nullptr;
-        const float *n_A = p.A + (int64_t)d0 * N + w * NK;
-        const int64_t ck_stride = nck * N;                              // floats between the checkpoints of two channels
-        const float *n_ck = p.ckpt + ((p.cu ? (int64_t)d0 : (int64_t)b * p.D + d0) * nck + ck0 + tile * CK_PER_TILE) * N + w * NK;
-        const bool has_D = p.Dskip != nullptr, has_bias = p.bias != nullptr;
-        const float *n_Dsk = has_D ? p.Dskip + d0 : p.A, *n_bias = has_bias ? p.bias + d0 : p.A;
-        int n_left = Gact - 1;                                           // channels after the one the pointers are on
-        auto prefetch = [&](Pref &s) {
-            if (io_thread) {
-                if constexpr (TPW == 1) {
-                    // steps past the end of the tile read the last valid one again; the prologue discards them
-                    load_one_raw_clamped<IO>(n_u, f0, rem, s.u);
-                    load_one_raw_clamped<IO>(n_dl, f0, rem, s.dl);
-                    load_one_raw_clamped<IO>(n_dy, f0, rem, s.dy);
-                    load_one_raw_clamped<IO>(n_z, f0, rem, s.z);
-                } else {
-                    load_few_raw<IO, TPW>(n_u, f0, rem, vec, s.u);
-                    load_few_raw<IO, TPW>(n_dl, f0, rem, vec, s.dl);
-                    load_few_raw<IO, TPW>(n_dy, f0, rem, vec, s.dy);
-                    load_few_raw<IO, TPW>(n_z, f0, rem, vec, s.z);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < NK; ++k) { s.A[k] = n_A[k]; s.ck[k] = n_ck[k]; }
-            s.Dsk = *n_Dsk;
-            s.bias = *n_bias;
-            const bool more = n_left > 0;                                // else stay on the last channel
-            n_left -= more ? 1 : 0;
-            n_u += more ? p.u_sd : 0; n_dl += more ? p.dl_sd : 0; n_dy += more ? p.dy_sd : 0; n_z += more ? z_step : 0;
-            n_A += more ? N : 0; n_ck += more ? ck_stride : 0;
-            n_Dsk += (more && has_D) ? 1 : 0; n_bias += (more && has_bias) ? 1 : 0;
-        };
-        // The prefetched registers are claimed ("settled") at a point of the program where their loads have long
-        // arrived and no store is in flight behind them: the memory counter is in order, so a wait for a load that
-        // comes after younger stores (the epilogue's, issued under a branch) would wait for those stores as well.
-        auto settle = [&](Pref &s) {
-#pragma unroll
-            for (int i = 0; i < RawFew<IO, TPW>::WORDS; ++i)
-                asm volatile("" : "+v"(s.u.w[i]), "+v"(s.dl.w[i]), "+v"(s.dy.w[i]), "+v"(s.z.w[i]) : : "memory");
-#pragma unroll
-            for (int k = 0; k < NK; ++k) asm volatile("" : "+v"(s.A[k]), "+v"(s.ck[k]) : : "memory");
-            asm volatile("" : "+v"(s.Dsk), "+v"(s.bias) : : "memory");
-        };
-        prefetch(S0);
-        // The loads above are claimed before the first atomic of the flush is issued (the memory counter is in
-        // order and the atomics sit under a branch: a wait placed after them would wait for them as well), i.e. after
-        // the flush's first trip through LDS.
-        auto settle_tile = [&]() {
-            settle(S0);
-#pragma unroll
-            for (int t = 0; t < T; ++t)
-#pragma unroll
-                for (int i = 0; i < RawFew<IO, NK>::WORDS; ++i)
-                    asm volatile("" : "+v"(rB[t].w[i]), "+v"(rC[t].w[i]) : : "memory");
-        };
-        if (fl_rem > 0) flush(settle_tile);          // the sums of the tile before (later in time); same branch for the whole workgroup
-        settle_tile();
-        // Cm and both sums stay in registers; the Bm columns go to this wavefront's own slice of LDS (read back as
-        // ds_read_b128 in each pass)
-        float Cv[NK][T];
+        // ---- this lane's columns of Bm and Cm: every row is loaded without a branch (past the end of the tile the last
+        // valid row is read again and then discarded), so that all loads of a lane are in flight together
+        RawFew<IO, NS> rB[T], rC[T];
         {
-        float Bv[NK][T];
+            const IO *BmT = Bm + l0 * N, *CmT = Cm + l0 * N;
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int step = li * T + t;
+                const int row = step < rem ? step : rem - 1;
+                load_few_raw<IO, NS>(BmT + (unsigned)(row * N + n0), 0, NS, true, rB[t]);
+                load_few_raw<IO, NS>(CmT + (unsigned)(row * N + n0), 0, NS, true, rC[t]);
+            }
+        }
+
+        // ---- per-step inputs of a pair of channels are fetched one pair ahead.  Row pointers: this thread's channel of
+        // the pair the next fetch reads and the next epilogue writes (past the last channel they stay on a valid one).
+        RawFew<IO, TPT> r_u, r_dl, r_dy, r_z;
+        const int64_t tl = toff + l0;
+        const int c_first = c_own < Gact ? c_own : Gact - 1;
+        const int64_t dch = d0 + c_first;
+        const IO *n_u = reinterpret_cast<const IO *>(p.u) + bs * p.u_sb + dch * p.u_sd + tl;
+        const IO *n_dl = reinterpret_cast<const IO *>(p.delta) + bs * p.dl_sb + dch * p.dl_sd + tl;
+        const IO *n_dy = reinterpret_cast<const IO *>(p.dy) + bs * p.dy_sb + dch * p.dy_sd + tl;
+        const IO *n_z = HAS_Z ? reinterpret_cast<const IO *>(p.z) + bs * p.z_sb + dch * p.z_sd + tl : n_dy;
+        const int64_t z_sd = HAS_Z ? p.z_sd : p.dy_sd;
+        IO *o_du = reinterpret_cast<IO *>(p.du) + bs * p.du_sb + dch * p.du_sd + tl;
+        IO *o_dd = reinterpret_cast<IO *>(p.ddelta) + bs * p.dd_sb + dch * p.dd_sd + tl;
+        IO *o_dz = HAS_Z && p.dz ? reinterpret_cast<IO *>(p.dz) + bs * p.dz_sb + dch * p.dz_sd + tl : nullptr;
+        int n_g = 0;                                                 // first channel of the pair of the next fetch
+        // A and the checkpointed state of the pair: one value each for the first 2 * CP * N threads
+        const float *n_A = p.A + (int64_t)d0 * N, *n_ck = ckrow + tile * N;
+        const unsigned ck_sd = (unsigned)(nck * N);                  // floats between the checkpoints of two channels
+        float r_ac = 0.0f;
+        auto fetch = [&](unsigned t0) {
+            const unsigned f0 = (t0 % NTC) * TPT;
+            if (FULL) {
+                load_at<IO, TPT>(n_u, f0, r_u);
+                load_at<IO, TPT>(n_dl, f0, r_dl);
+                load_at<IO, TPT>(n_dy, f0, r_dy);
+                if constexpr (HAS_Z) load_at<IO, TPT>(n_z, f0, r_z);
+            } else {
+                load_few_raw<IO, TPT>(n_u, (int)f0, rem, vec, r_u);
+                load_few_raw<IO, TPT>(n_dl, (int)f0, rem, vec, r_dl);
+                load_few_raw<IO, TPT>(n_dy, (int)f0, rem, vec, r_dy);
+                if constexpr (HAS_Z) load_few_raw<IO, TPT>(n_z, (int)f0, rem, vec, r_z);
+            }
+            if (t0 < 2 * CP * N) {
+                const bool second = (t0 / N) % CP && n_g + 1 < Gact;     // else the first channel of the pair again
+                const float *q = t0 < CP * N ? n_A : n_ck;
+                r_ac = q[t0 % N + (second ? (t0 < CP * N ? (unsigned)N : ck_sd) : 0u)];
+            }
+            n_g += CP;
+            if (n_g < Gact) { n_A += CP * N; n_ck += (int64_t)CP * ck_sd; }
+            if (n_g + c_own < Gact) { n_u += CP * p.u_sd; n_dl += CP * p.dl_sd; n_dy += CP * p.dy_sd; n_z += CP * z_sd; }
+        };
+        fetch(tid);
+
+        // ---- Bm, Cm columns and the sums of dBm, dCm over channels stay in registers
+        float Bv[NS][T], Cv[NS][T], dB[NS][T], dC[NS][T];
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-            float tb[NK], tc[NK];
-            unpack_few<IO, NK>(rB[t], tb);
-            unpack_few<IO, NK>(rC[t], tc);
-            const int step = lane * T + t;
+            float tb[NS], tc[NS];
+            unpack_few<IO, NS>(rB[t], tb);
+            unpack_few<IO, NS>(rC[t], tc);
+            const bool ok = li * T + t < rem;
 #pragma unroll
-            for (int k = 0; k < NK; ++k) {
-                Bv[k][t] = step < rem ? tb[k] : 0.0f; Cv[k][t] = step < rem ? tc[k] : 0.0f;
-                dBacc[k][t] = 0.0f; dCacc[k][t] = 0.0f;
+            for (int s = 0; s < NS; ++s) {
+                Bv[s][t] = ok ? tb[s] : 0.0f; Cv[s][t] = ok ? tc[s] : 0.0f;
+                dB[s][t] = 0.0f; dC[s][t] = 0.0f;
             }
         }
-#pragma unroll
-        for (int k = 0; k < NK; ++k)
-#pragma unroll
-            for (int q = 0; q < TQ; ++q)
-                *reinterpret_cast<float4 *>(&sBt[(((w * NK + k) * TQ + q) * 64 + lane) * 4]) =
-                    make_float4(Bv[k][4 * q], Bv[k][4 * q + 1], Bv[k][4 * q + 2], Bv[k][4 * q + 3]);
-        }
 
-        // Order of a channel's work between the workgroup's two barriers per channel.  After the first barrier (the
-        // step inputs of channel g are in LDS): the main pass, which leaves the wavefronts' partial sums in LDS.
-        // After the second: the LDS reads of the epilogue of channel g are issued, the prologue of channel g+1 runs
-        // while they are in flight (softplus, gate, staging of the step inputs; its inputs were fetched during the
-        // main pass), then the epilogue's arithmetic and stores.  Kept in registers from a channel's prologue to its
-        // epilogue: d softplus / ds, the factor that turns ypre into dz, and Dskip (n_*: of the channel after).
-        float e_sg[TPW], e_zf[TPW], n_sg[TPW], n_zf[TPW];
-        float Dsk = 0.0f, nDsk = 0.0f;
-        float cA[NK], cck[NK];                       // A and the checkpointed state of the main pass's channel
-
-        // ---- prologue of the channel whose inputs S0 holds: each thread prepares TPW flat steps for everybody
-        auto prologue = [&]() {
-            const float bias = has_bias ? S0.bias : 0.0f;
-            // The values are moved out of S0 here and now (real moves, which the compiler may not turn into a renaming):
-            // the fetch that follows then loads into the very registers S0 has at the top of the loop.  Left to the
-            // compiler, the fetch gets fresh registers and the copies land at the end of the loop body, where they
-            // wait for the loads that have just been issued.
-            nDsk = has_D ? S0.Dsk : 0.0f;
-            asm volatile("" : "+v"(nDsk));
+        // kept in registers from a pair's prologue to its epilogue: d softplus / ds and the factor that turns ypre
+        // into dz (n_*: of the pair after)
+        float e_sg[TPT], e_zf[TPT], n_sg[TPT], n_zf[TPT];
+        // ---- prologue of the pair whose inputs have been fetched: each thread prepares TPT steps of its channel
+        auto step_inputs = [&](int ch, unsigned t0, float (&u)[TPT], float (&dl)[TPT], float (&dy)[TPT]) {
+            const float bias = sBias[ch < Gact ? ch : Gact - 1];
+            float z[TPT];
+            unpack_few<IO, TPT>(r_u, u);
+            unpack_few<IO, TPT>(r_dl, dl);
+            unpack_few<IO, TPT>(r_dy, dy);
+            if constexpr (HAS_Z) unpack_few<IO, TPT>(r_z, z);
 #pragma unroll
-            for (int k = 0; k < NK; ++k) {
-                asm volatile("v_mov_b32 %0, %1" : "=v"(cA[k]) : "v"(S0.A[k]));
-                asm volatile("v_mov_b32 %0, %1" : "=v"(cck[k]) : "v"(S0.ck[k]));
+            for (int i = 0; i < TPT; ++i) {
+                const float v = dl[i] + bias;
+                float sp, sg;
+                softplus_sigmoid<sizeof(IO) == 4>(v, sp, sg);
+                dl[i] = p.softplus ? sp : v;
+                n_sg[i] = p.softplus ? sg : 1.0f;
+                if constexpr (HAS_Z) gate_bwd(z[i], dy[i], n_zf[i]);
             }
-            if (io_thread) {
-                float e_u[TPW], r_d[TPW], e_dy[TPW], e_z[TPW];
-                unpack_few<IO, TPW>(S0.u, e_u);
-                unpack_few<IO, TPW>(S0.dl, r_d);
-                unpack_few<IO, TPW>(S0.dy, e_dy);
-                unpack_few<IO, TPW>(S0.z, e_z);
+            if (!FULL || ch >= Gact) {                   // steps past the end: Delta = 0 (a = 1), no input, no gradient
+                const int f0 = (t0 % NTC) * TPT;
 #pragma unroll
-                for (int i = 0; i < TPW; ++i) {
-                    float sp, dyp;
-                    bwd_step_inputs<sizeof(IO) == 4>(r_d[i] + bias, e_dy[i], has_z ? e_z[i] : 0.0f, p.softplus != 0, has_z, sp, n_sg[i], dyp, n_zf[i]);
-                    const bool valid = f0 + i < rem;     // steps past the end: Delta = 0 (a = 1), no input, no gradient
-                    sIn[0 * TILE + fslot(f0 + i)] = valid ? sp : 0.0f;
-                    sIn[1 * TILE + fslot(f0 + i)] = valid ? e_u[i] : 0.0f;
-                    sIn[2 * TILE + fslot(f0 + i)] = valid ? dyp : 0.0f;
-                }
+                for (int i = 0; i < TPT; ++i)
+                    if (f0 + i >= rem || ch >= Gact) { dl[i] = 0.0f; u[i] = 0.0f; dy[i] = 0.0f; }
             }
+        };
+        auto prologue = [&](int ch, unsigned t0, int slot, int buf) {
+            float u[TPT], dl[TPT], dy[TPT];
+            step_inputs(ch, t0, u, dl, dy);
+            lds_steps_write<TPT>(sIn[buf][c_own][0], slot, dl);
+            lds_steps_write<TPT>(sIn[buf][c_own][1], slot, u);
+            lds_steps_write<TPT>(sIn[buf][c_own][2], slot, dy);
+            if (t0 < 2 * CP * N) (&sAC[buf][0][0][0])[t0] = r_ac;
         };
         auto rotate = [&]() {
 #pragma unroll
-            for (int i = 0; i < TPW; ++i) { e_sg[i] = n_sg[i]; e_zf[i] = n_zf[i]; }
-            Dsk = nDsk;
+            for (int i = 0; i < TPT; ++i) { e_sg[i] = n_sg[i]; if constexpr (HAS_Z) e_zf[i] = n_zf[i]; }
         };
-        prologue();                                  // channel 0
-        rotate();
-        prefetch(S0);                                // channel 1 (where there is none, the last channel again)
-
-        auto channel = [&](const int g) {
-            if constexpr (ALT_PRIO) {
-                if ((unsigned)(g & 1) == hw_slot) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
+        // ---- epilogue: du, ddelta, dz of this thread's steps from the sums over states
+        auto finish = [&](const int g, unsigned t0, unsigned f0, const float (&e_dl)[TPT], const float (&e_u)[TPT], const float (&e_dy)[TPT],
+                          const float (&s_yp)[TPT], const float (&s_du)[TPT], const float (&s_dd)[TPT]) {
+            const int ch = g + c_own;
+            const bool live = ch < Gact;
+            const float Dsk = sDskip[live ? ch : Gact - 1];
+            float o_u[TPT], o_d[TPT], o_z[TPT];
+            float dD_part = 0.0f, db_part = 0.0f;
+#pragma unroll
+            for (int i = 0; i < TPT; ++i) {
+                const float ed = e_dl[i], eu = e_u[i], ey = e_dy[i];
+                float su = s_du[i], sd = s_dd[i];
+                if constexpr (DISC == DISC_ZOH_S6) {
+                    // the wavefronts' sums are sum_n H B: dDelta += u sum_n H B, du = Delta sum_n H B
+                    sd = __builtin_fmaf(eu, su, sd);
+                    su *= ed;
+                }
+                o_u[i] = __builtin_fmaf(ey, Dsk, su);
+                o_d[i] = sd * e_sg[i];
+                if constexpr (HAS_Z) o_z[i] = __builtin_fmaf(Dsk, eu, s_yp[i]) * e_zf[i];
+                dD_part = __builtin_fmaf(ey, eu, dD_part);
+                db_part += (FULL || (int)f0 + i < rem) ? o_d[i] : 0.0f;
             }
-            __syncthreads();
-
-            // ---- main: this lane's T steps, this wavefront's NK states
-            float dl[T], dyp[T], dlu[T], ypre[T], pdu[T], pdd[T];
-#pragma unroll
-            for (int q = 0; q < TQ; ++q) {
-                const float4 v0 = *reinterpret_cast<const float4 *>(&sIn[0 * TILE + (q * 64 + lane) * 4]);
-                const float4 v1 = *reinterpret_cast<const float4 *>(&sIn[1 * TILE + (q * 64 + lane) * 4]);
-                const float4 v2 = *reinterpret_cast<const float4 *>(&sIn[2 * TILE + (q * 64 + lane) * 4]);
-                dl[4 * q] = v0.x; dl[4 * q + 1] = v0.y; dl[4 * q + 2] = v0.z; dl[4 * q + 3] = v0.w;
-                dlu[4 * q] = v1.x; dlu[4 * q + 1] = v1.y; dlu[4 * q + 2] = v1.z; dlu[4 * q + 3] = v1.w;   // u for now
-                dyp[4 * q] = v2.x; dyp[4 * q + 1] = v2.y; dyp[4 * q + 2] = v2.z; dyp[4 * q + 3] = v2.w;
-            }
-#pragma unroll
-            for (int t = 0; t < T; ++t)
-                if constexpr (DISC == DISC_ZOH_S6) dlu[t] *= dl[t];   // S6 only ever needs Delta*u; the others keep u
-
-            float dA4[NK];
-#pragma unroll
-            for (int k0 = 0; k0 < NK; k0 += JS) {
-            // ---- phase 1: forward fold (states) and backward fold (adjoint) of this lane's T steps, JS states at a time
-            float a[NK][T + 1], gg[NK][T], x[NK][T], cdy[NK][T];
-            float P[NK], S[NK], Pr[NK], Sr[NK], hcv[NK];
-            ACoef acs[NK];
-            // The Bm columns of all JS states are read from LDS in one batch (one round trip instead of one per state;
-            // the scheduler is kept from moving the reads down to their uses)
-            float Bk[NK][T];
-            auto read_Bk = [&]() {
-#pragma unroll
-                for (int k = k0; k < k0 + JS; ++k)
-#pragma unroll
-                    for (int q = 0; q < TQ; ++q) {
-                        const float4 vb = *reinterpret_cast<const float4 *>(&sBt[(((w * NK + k) * TQ + q) * 64 + lane) * 4]);
-                        Bk[k][4 * q] = vb.x; Bk[k][4 * q + 1] = vb.y; Bk[k][4 * q + 2] = vb.z; Bk[k][4 * q + 3] = vb.w;
-                    }
-            };
-            read_Bk();
-#pragma unroll
-            for (int k = k0; k < k0 + JS; ++k) hcv[k] = sH[g * N + w * NK + k];
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int k = k0; k < k0 + JS; ++k) {
-                const ACoef ac = make_acoef<DISC>(cA[k]);
-                acs[k] = ac;
-                const float xck = cck[k];
-                const float hc = hcv[k];
-                float sx = 0.0f;
-#pragma unroll
-                for (int t = 0; t < T; ++t) {
-                    disc_ag<DISC>(dl[t], ac, a[k][t], gg[k][t]);
-                    if constexpr (DISC == DISC_ZOH_S6) x[k][t] = dlu[t] * Bk[k][t];
-                    else if constexpr (DISC == DISC_DIRAC) x[k][t] = dlu[t] * Bk[k][t];
-                    else x[k][t] = gg[k][t] * dlu[t] * Bk[k][t];
-                    sx = (t == 0) ? x[k][0] : __builtin_fmaf(a[k][t], sx, x[k][t]);   // the fold starts from zero
-                }
-                // products of the multipliers of this lane's steps (state prefix) and of the same steps shifted by one
-                // (adjoint suffix: H_l = c_l + a_{l+1} H_{l+1}; the multiplier after the tile's last step is 1 because
-                // the carried value is already a_{l1} H_{l1}).  The inner factors are shared.
-                a[k][T] = dpp<DPP_WAVE_SHL1>(1.0f, a[k][0]);
-                float inner = a[k][1];
-#pragma unroll
-                for (int t = 2; t < T; ++t) inner *= a[k][t];
-                const float p = a[k][0] * inner, pr = inner * a[k][T];
-                if (lane == 0) sx = __builtin_fmaf(p, xck, sx);             // the checkpointed state enters through lane 0
-                P[k] = p; S[k] = sx;
-
-                float sr = 0.0f;
-#pragma unroll
-                for (int t = T - 1; t >= 0; --t) {
-                    cdy[k][t] = Cv[k][t] * dyp[t];
-                    sr = (t == T - 1) ? cdy[k][t] : __builtin_fmaf(a[k][t + 1], sr, cdy[k][t]);
-                }
-                if (lane == 63) sr = __builtin_fmaf(pr, hc, sr);            // the carried adjoint enters through lane 63
-                Pr[k] = pr; Sr[k] = sr;
-            }
-            // ---- phase 2: state prefixes (forward in time) and adjoint suffixes (backward in time) of these JS states;
-            // the Bm columns are read again meanwhile (the fold has consumed the first copy)
-            __builtin_amdgcn_sched_barrier(0);
-            read_Bk();
-            __builtin_amdgcn_sched_barrier(0);
-            wave_scan_fwd_rev_multi<JS>(P + k0, S + k0, Pr + k0, Sr + k0, lane);
-            // ---- phase 3: replay of the states and of the adjoint, gradients
-#pragma unroll
-            for (int k = k0; k < k0 + JS; ++k) {
-                const int n = w * NK + k;
-                const ACoef ac = acs[k];
-                const float xin = dpp<DPP_WAVE_SHR1>(cck[k], S[k]);         // x entering this lane's first step
-                {
-                    float xp = xin;
-#pragma unroll
-                    for (int t = 0; t < T; ++t) { xp = __builtin_fmaf(a[k][t], xp, x[k][t]); x[k][t] = xp; }
-                }
-                const float H0 = Sr[k];                                     // H of this lane's first step
-                float R = dpp<DPP_WAVE_SHL1>(hcv[k], Sr[k]);                // H of the next lane's first step (the carry itself past lane 63)
-                if (lane == 0) sH[g * N + n] = a[k][0] * H0;                // carried to the earlier tile
-
-                float dA_part = 0.0f;                                       // this lane's share of dA[d, n]
-#pragma unroll
-                for (int t = T - 1; t >= 0; --t) {
-                    R = __builtin_fmaf(a[k][t + 1], R, cdy[k][t]);            // H_t
-                    const float xprev = (t > 0) ? x[k][t - 1] : xin;
-                    dCacc[k][t] = __builtin_fmaf(dyp[t], x[k][t], dCacc[k][t]);
-                    if constexpr (DZ) ypre[t] = (k == 0) ? Cv[k][t] * x[k][t] : __builtin_fmaf(Cv[k][t], x[k][t], ypre[t]);
-                    // the first state of the wavefront starts the sums over n (pdu, pdd), the others add to them
-                    auto acc = [&](float &sum, float m1, float m2) { sum = (k == 0) ? m1 * m2 : __builtin_fmaf(m1, m2, sum); };
-                    if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) {
-                        // S6: g = Delta (du and dDelta share sum_n H B, scaled in the epilogue); dirac: g = 1, and only
-                        // a = e^{Delta A} depends on Delta and A
-                        acc(pdu[t], R, Bk[k][t]);
-                        dBacc[k][t] = __builtin_fmaf(R, dlu[t], dBacc[k][t]);
-                        const float q = R * xprev * a[k][t];
-                        acc(pdd[t], q, ac.A);
-                        dA_part = __builtin_fmaf(q, dl[t], dA_part);
-                    } else if constexpr (DISC == DISC_ZOH) {
-                        // da/dDelta = A a, da/dA = Delta a, dg/dDelta = a: the common factor a is taken out
-                        float a_t, a_A, g_t, g_A;
-                        disc_partials<DISC>(dl[t], ac, a[k][t], gg[k][t], a_t, a_A, g_t, g_A);
-                        const float hb = R * Bk[k][t];
-                        const float dg = hb * dlu[t];
-                        const float dax = R * a[k][t] * xprev;               // H x_{l-1} a
-                        acc(pdu[t], hb, gg[k][t]);
-                        dBacc[k][t] = __builtin_fmaf(R * gg[k][t], dlu[t], dBacc[k][t]);
-                        if (k == 0) pdd[t] = __builtin_fmaf(dax, ac.A, dg * a[k][t]);
-                        else pdd[t] = __builtin_fmaf(dax, ac.A, __builtin_fmaf(dg, a[k][t], pdd[t]));
-                        dA_part = __builtin_fmaf(dax, dl[t], __builtin_fmaf(dg, g_A, dA_part));
-                    } else {
-                        // bilinear: with q = 1 / (1 - Delta A / 2) all four partials are multiples of q^2, and
-                        // a = (1 + Delta A / 2) q gives q = (a + 1) / 2 without a second reciprocal
-                        const float q = __builtin_fmaf(a[k][t], 0.5f, 0.5f);
-                        const float q2 = q * q;
-                        const float da = R * xprev;
-                        const float hb = R * Bk[k][t];
-                        const float dg = hb * dlu[t];
-                        acc(pdu[t], hb, gg[k][t]);
-                        dBacc[k][t] = __builtin_fmaf(R * gg[k][t], dlu[t], dBacc[k][t]);
-                        acc(pdd[t], __builtin_fmaf(da, ac.A, dg), q2);                                            // A q^2 da + q^2 dg
-                        dA_part = __builtin_fmaf(__builtin_fmaf(0.5f * dl[t], dg, da) * dl[t], q2, dA_part);     // Delta q^2 da + Delta^2 q^2 dg / 2
-                    }
-                }
-                if constexpr (NK == 4 || NK == 2) {
-                    dA4[k] = dA_part;
+            if (live) {
+                if (FULL) {
+                    store_at<IO, TPT>(o_du, f0, o_u);
+                    store_at<IO, TPT>(o_dd, f0, o_d);
+                    if constexpr (HAS_Z) { if (o_dz) store_at<IO, TPT>(o_dz, f0, o_z); }
                 } else {
-                    const float dA_tot = wave_sum(dA_part);
-                    if (lane == 0) lds_add(&sdA[0][g * N + n], dA_tot);
+                    store_few<IO, TPT>(o_du, (int)f0, rem, vec, o_u);
+                    store_few<IO, TPT>(o_dd, (int)f0, rem, vec, o_d);
+                    if constexpr (HAS_Z) { if (o_dz) store_few<IO, TPT>(o_dz, (int)f0, rem, vec, o_z); }
                 }
             }
-            }   // groups of JS states
-            if constexpr (NK == 4) {
-                // The four per-lane partial sums are reduced together: two exchange steps leave each lane of a quad
-                // with the quad's sum of ONE state (lane%4 = 0,1,2,3 -> state 0,2,1,3), two rotations sum the quads of
-                // a row, one row-pair swap sums the two rows of a half-wavefront; lanes 0-3 and 32-35 own the results.
-                const bool b0 = lane & 1, b1 = lane & 2;
-                float kA = b0 ? dA4[2] : dA4[0], kB = b0 ? dA4[3] : dA4[1];
-                const float sA = b0 ? dA4[0] : dA4[2], sB = b0 ? dA4[1] : dA4[3];
-                kA += dpp<0xB1>(0.0f, sA);                                  // quad_perm [1,0,3,2]
-                kB += dpp<0xB1>(0.0f, sB);
-                float v = b1 ? kB : kA;
-                v += dpp<0x4E>(0.0f, b1 ? kA : kB);                         // quad_perm [2,3,0,1]
-                v += dpp<0x124>(0.0f, v);                                   // row_ror:4
-                v += dpp<0x128>(0.0f, v);                                   // row_ror:8
-                v = sum_xor16(v);
-                if ((lane & 0x1C) == 0) lds_add(&sdA[lane >> 5][g * N + w * NK + ((lane & 1) << 1) + ((lane >> 1) & 1)], v);
-            } else if constexpr (NK == 2) {
-                // the same with two partial sums: even lanes end up with state 0, odd lanes with state 1
-                const bool odd = lane & 1;
-                float v = odd ? dA4[1] : dA4[0];
-                v += dpp<0xB1>(0.0f, odd ? dA4[0] : dA4[1]);               // quad_perm [1,0,3,2]
-                v += dpp<0x4E>(0.0f, v);                                    // quad_perm [2,3,0,1]
-                v += dpp<0x124>(0.0f, v);                                   // row_ror:4
-                v += dpp<0x128>(0.0f, v);                                   // row_ror:8
-                v = sum_xor16(v);
-                if ((lane & 0x1E) == 0) lds_add(&sdA[lane >> 5][g * N + w * NK + (lane & 1)], v);
-            }
-#pragma unroll
-            for (int q = 0; q < TQ; ++q) {
-                float *base = &sPart[(w * 3) * TILE + (q * 64 + lane) * 4];
-                if constexpr (DZ) *reinterpret_cast<float4 *>(base) = make_float4(ypre[4 * q], ypre[4 * q + 1], ypre[4 * q + 2], ypre[4 * q + 3]);
-                *reinterpret_cast<float4 *>(base + TILE) = make_float4(pdu[4 * q], pdu[4 * q + 1], pdu[4 * q + 2], pdu[4 * q + 3]);
-                *reinterpret_cast<float4 *>(base + 2 * TILE) = make_float4(pdd[4 * q], pdd[4 * q + 1], pdd[4 * q + 2], pdd[4 * q + 3]);
-            }
-            __syncthreads();
-            // ---- epilogue of this channel, with the prologue of the next one in its shadow
-            float e_in[TPW][3], e_part[TPW][W][3];
-            if (io_thread) {
-                // every LDS value of the epilogue is read up front, in one round trip (left alone, the compiler moves
-                // the reads that only feed the stores into the stores' own branch, one round trip after the other)
-#pragma unroll
-                for (int i = 0; i < TPW; ++i) {
-#pragma unroll
-                    for (int j = 0; j < 3; ++j) e_in[i][j] = sIn[j * TILE + fslot(f0 + i)];
-#pragma unroll
-                    for (int ww = 0; ww < W; ++ww)
-#pragma unroll
-                        for (int j = DZ ? 0 : 1; j < 3; ++j) e_part[i][ww][j] = sPart[(ww * 3 + j) * TILE + fslot(f0 + i)];
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            settle(S0);                              // the next channel's inputs: claimed before this channel's stores
-            prologue();                              // (past the last channel: the last one again, unused)
-            prefetch(S0);                            // the channel after the next
-            __builtin_amdgcn_sched_barrier(0);
-            if (io_thread) {
-                float o_du[TPW], o_dd[TPW], o_dz[TPW];
-                float dD_part = 0.0f, db_part = 0.0f;
-#pragma unroll
-                for (int i = 0; i < TPW; ++i) {
-                    const float e_u = e_in[i][1], e_dyp = e_in[i][2];
-                    float yp = Dsk * e_u, s_du = 0.0f, s_dd = 0.0f;
-#pragma unroll
-                    for (int ww = 0; ww < W; ++ww) {
-                        if constexpr (DZ) yp += e_part[i][ww][0];
-                        s_du += e_part[i][ww][1];
-                        s_dd += e_part[i][ww][2];
-                    }
-                    if constexpr (DISC == DISC_ZOH_S6) {
-                        // the wavefronts' sums are sum_n H B: dDelta += u sum_n H B, du = Delta sum_n H B
-                        s_dd = __builtin_fmaf(e_u, s_du, s_dd);
-                        s_du *= e_in[i][0];
-                    }
-                    o_du[i] = __builtin_fmaf(e_dyp, Dsk, s_du);
-                    o_dd[i] = s_dd * e_sg[i];
-                    o_dz[i] = yp * e_zf[i];
-                    dD_part = __builtin_fmaf(e_dyp, e_u, dD_part);
-                    db_part += (f0 + i < rem) ? o_dd[i] : 0.0f;
-                    asm volatile("" : "+v"(o_du[i]), "+v"(o_dd[i]), "+v"(o_dz[i]));   // computed here, not inside the stores' branch
-                }
-                store_few<IO, TPW>(o_du_row, f0, rem, vec, o_du);
-                store_few<IO, TPW>(o_dd_row, f0, rem, vec, o_dd);
-                if constexpr (DZ) store_few<IO, TPW>(o_dz_row, f0, rem, vec, o_dz);
-                // joint reduction of the two per-lane sums: one exchange leaves even lanes with dD and odd lanes with
-                // dbias pair sums, then lanes of equal parity are summed over the half-wavefront (lanes 0,1 / 32,33)
-                const bool odd = lane & 1;
+            {
+                // joint reduction of the two per-lane sums over a row of lanes, as for dA
+                const bool odd = t0 & 1;
                 float v = odd ? db_part : dD_part;
-                v += dpp<0xB1>(0.0f, odd ? dD_part : db_part);             // quad_perm [1,0,3,2]
-                v += dpp<0x4E>(0.0f, v);                                    // quad_perm [2,3,0,1]
-                v += dpp<0x124>(0.0f, v);                                   // row_ror:4
-                v += dpp<0x128>(0.0f, v);                                   // row_ror:8
-                v = sum_xor16(v);
-                if ((lane & 0x1E) == 0) lds_add(&(odd ? sdb : sdD)[((lane >> 5) * W + w) * kMaxG + g], v);
+                v += dpp<0xB1>(0.0f, odd ? dD_part : db_part);           // quad_perm [1,0,3,2]
+                v += dpp<0x4E>(0.0f, v);                                  // quad_perm [2,3,0,1]
+                v += dpp<0x124>(0.0f, v);                                 // row_ror:4
+                v += dpp<0x128>(0.0f, v);                                 // row_ror:8
+                if ((t0 & 15) < 2 && live) lds_add(&(odd ? sdb : sdD)[ch], v);
             }
-            rotate();
-            o_du_row += p.du_sd; o_dd_row += p.dd_sd;
-            if constexpr (DZ) o_dz_row += p.dz_sd;
+            o_du += CP * p.du_sd; o_dd += CP * p.dd_sd;
+            if constexpr (HAS_Z) { if (o_dz) o_dz += CP * p.dz_sd; }
         };
-        for (int g = 0; g < Gact; ++g) channel(g);
-        fl_l0 = l0; fl_rem = rem;                    // flushed while the next tile's maps are on their way
+        auto epilogue = [&](const int g, const int buf) {
+            const unsigned t0 = fresh(tid), f0 = (t0 % NTC) * TPT;
+            const int slot = step_slot((int)f0);
+            float e_in[3][TPT], s_yp[TPT], s_du[TPT], s_dd[TPT];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) lds_steps_read<TPT>(sIn[buf][c_own][j], slot, e_in[j]);
+#pragma unroll
+            for (int i = 0; i < TPT; ++i) { s_yp[i] = 0.0f; s_du[i] = 0.0f; s_dd[i] = 0.0f; }
+#pragma unroll
+            for (int ww = 0; ww < W; ++ww) {
+                float v[TPT];
+                if constexpr (HAS_Z) {
+                    lds_steps_read<TPT>(sPart[buf][c_own][ww][0], slot, v);
+#pragma unroll
+                    for (int i = 0; i < TPT; ++i) s_yp[i] = ww ? s_yp[i] + v[i] : v[i];
+                }
+                lds_steps_read<TPT>(sPart[buf][c_own][ww][1], slot, v);
+#pragma unroll
+                for (int i = 0; i < TPT; ++i) s_du[i] = ww ? s_du[i] + v[i] : v[i];
+                lds_steps_read<TPT>(sPart[buf][c_own][ww][2], slot, v);
+#pragma unroll
+                for (int i = 0; i < TPT; ++i) s_dd[i] = ww ? s_dd[i] + v[i] : v[i];
+            }
+            finish(g, t0, f0, e_in[0], e_in[1], e_in[2], s_yp, s_du, s_dd);
+        };
+        // ---- main: this lane's 8 steps of its channel, one state after the other
+        auto states = [&](const int g, const int buf, const unsigned ln, const float (&dl)[T], float (&du)[T], const float (&dy)[T],
+                          float (&yp)[T], float (&pu)[T], float (&pd)[T]) {
+                const unsigned c = ln >> 5;
+                const int ch = g + (int)c < Gact ? g + (int)c : g;             // (the half past the last channel repeats the first, unused)
+                const bool own = g + (int)c < Gact;
+                const int at = ch * N + n0;
+                float Ak[NS], ck[NS], hc[NS];
+                lds_few<NS>(&sAC[buf][0][c][n0], Ak);
+                lds_few<NS>(&sAC[buf][1][c][n0], ck);
+                lds_few<NS>(&sH[at], hc);
+                if constexpr (DISC == DISC_ZOH_S6) {
+#pragma unroll
+                    for (int t = 0; t < T; ++t) du[t] *= dl[t];      // S6 only ever needs Delta*u; the others keep u
+                }
+                float sum_dl = dl[0];
+#pragma unroll
+                for (int t = 1; t < T; ++t) sum_dl += dl[t];
+                float dA[NS];
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+                    const ACoef ac = make_acoef<DISC>(Ak[s]);
+                    // the checkpointed state enters through the half's first lane, the carried adjoint through its last
+                    float xin = i2f(f2i(ck[s]) & (int)first_lane), Gin = i2f(f2i(hc[s]) & (int)last_lane);
+                    float a[T], x[T], gg[T];
+#pragma unroll
+                    for (int t = 0; t < T; ++t) {
+                        disc_ag<DISC>(dl[t], ac, a[t], gg[t]);
+                        if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) x[t] = du[t] * Bv[s][t];
+                        else x[t] = gg[t] * du[t] * Bv[s][t];
+                    }
+                    // folds of the lane's steps: S the end state, Q = a_0 (c_0 + a_1 (c_1 + ...)) the adjoint handed on,
+                    // both with multiplier P
+                    float S = __builtin_fmaf(a[0], xin, x[0]), Q = Gin, P;
+#pragma unroll
+                    for (int t = 1; t < T; ++t) S = __builtin_fmaf(a[t], S, x[t]);
+#pragma unroll
+                    for (int t = T - 1; t >= 0; --t) Q = a[t] * __builtin_fmaf(Cv[s][t], dy[t], Q);
+                    if constexpr (DISC == DISC_BILINEAR) P = ((a[0] * a[1]) * (a[2] * a[3])) * ((a[4] * a[5]) * (a[6] * a[7]));
+                    else P = exp2_fast(sum_dl * ac.A2);
+                    half_scans(P, S, Q, xin, Gin);
+                    if (own && (ln & 31) == 0) sH[at + s] = Q;       // carried to the earlier tile
+                    // replay of the states (earliest step first) and of the adjoint (last step first), side by side: two chains
+                    // whose instructions fill each other's result latencies
+                    float R[T], G[T];
+                    {
+                        float xp = xin;
+#pragma unroll
+                        for (int t = 0; t < T; ++t) {
+                            const int r = T - 1 - t;
+                            R[r] = __builtin_fmaf(Cv[s][r], dy[r], Gin);                 // H_r
+                            xp = __builtin_fmaf(a[t], xp, x[t]); x[t] = xp;
+                            Gin = a[r] * R[r];                                           // a_r H_r
+                            G[r] = Gin;
+                        }
+                    }
+                    auto acc = [&](float &sum, float m1, float m2) { sum = (s == 0) ? m1 * m2 : __builtin_fmaf(m1, m2, sum); };
+                    float dAp = 0.0f;
+#pragma unroll
+                    for (int t = T - 1; t >= 0; --t) {
+                        const float xprev = t > 0 ? x[t - 1] : xin;
+                        dC[s][t] = __builtin_fmaf(dy[t], x[t], dC[s][t]);
+                        if constexpr (HAS_Z) acc(yp[t], Cv[s][t], x[t]);
+                        if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) {
+                            // S6: g = Delta (du and dDelta share sum_n H B, scaled in the epilogue); dirac: g = 1, and
+                            // only a = e^{Delta A} depends on Delta and A
+                            acc(pu[t], R[t], Bv[s][t]);
+                            dB[s][t] = __builtin_fmaf(R[t], du[t], dB[s][t]);
+                            const float q = G[t] * xprev;
+                            acc(pd[t], q, ac.A);
+                            dAp = __builtin_fmaf(q, dl[t], dAp);
+                        } else if constexpr (DISC == DISC_ZOH) {
+                            // da/dDelta = A a, da/dA = Delta a, dg/dDelta = a: the common factor a is taken out
+                            float a_t, a_A, g_t, g_A;
+                            disc_partials<DISC>(dl[t], ac, a[t], gg[t], a_t, a_A, g_t, g_A);
+                            const float hb = R[t] * Bv[s][t];
+                            const float dg = hb * du[t];
+                            const float q = G[t] * xprev;
+                            acc(pu[t], hb, gg[t]);
+                            dB[s][t] = __builtin_fmaf(R[t] * gg[t], du[t], dB[s][t]);
+                            if (s == 0) pd[t] = __builtin_fmaf(q, ac.A, dg * a[t]);
+                            else pd[t] = __builtin_fmaf(q, ac.A, __builtin_fmaf(dg, a[t], pd[t]));
+                            dAp = __builtin_fmaf(q, dl[t], __builtin_fmaf(dg, g_A, dAp));
+                        } else {
+                            // bilinear: with q = 1 / (1 - Delta A / 2) all four partials are multiples of q^2, and
+                            // a = (1 + Delta A / 2) q gives q = (a + 1) / 2 without a second reciprocal
+                            const float q = __builtin_fmaf(a[t], 0.5f, 0.5f);
+                            const float q2 = q * q, gt = dl[t] * q;
+                            const float da = R[t] * xprev;
+                            const float hb = R[t] * Bv[s][t];
+                            const float dg = hb * du[t];
+                            acc(pu[t], hb, gt);
+                            dB[s][t] = __builtin_fmaf(R[t] * gt, du[t], dB[s][t]);
+                            acc(pd[t], __builtin_fmaf(da, ac.A, dg), q2);                                    // A q^2 da + q^2 dg
+                            dAp = __builtin_fmaf(__builtin_fmaf(0.5f * dl[t], dg, da) * dl[t], q2, dAp);     // Delta q^2 da + Delta^2 q^2 dg / 2
+                        }
+                        // computed here: left to itself the compiler moves the products of one state down to the sums of the
+                        // next one's, and spills what it then has to keep
+                        if constexpr (HAS_Z) asm volatile("" : "+v"(yp[t]));
+                        asm volatile("" : "+v"(dC[s][t]), "+v"(dB[s][t]), "+v"(pu[t]), "+v"(pd[t]), "+v"(dAp));
+                    }
+                    dA[s] = dAp;
+                }
+                // dA: over the 16 lanes of a row.  With four states two exchange steps leave each lane of a quad with the
+                // quad's sum of ONE state (lane % 4 = 0, 1, 2, 3: state 0, 2, 1, 3), two rotations sum the quads
+                if constexpr (NS == 4) {
+                    const bool b0 = ln & 1, b1 = ln & 2;
+                    float kA = b0 ? dA[2] : dA[0], kB = b0 ? dA[3] : dA[1];
+                    kA += dpp<0xB1>(0.0f, b0 ? dA[0] : dA[2]);           // quad_perm [1,0,3,2]
+                    kB += dpp<0xB1>(0.0f, b0 ? dA[1] : dA[3]);
+                    float v = b1 ? kB : kA;
+                    v += dpp<0x4E>(0.0f, b1 ? kA : kB);                  // quad_perm [2,3,0,1]
+                    v += dpp<0x124>(0.0f, v);                            // row_ror:4
+                    v += dpp<0x128>(0.0f, v);                            // row_ror:8
+                    if (own && (ln & 15) < 4) lds_add(&sdA[at + ((ln & 1) << 1) + ((ln >> 1) & 1)], v);
+                } else {
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) {
+                        float v = dA[s];
+                        v += dpp<0xB1>(0.0f, v);
+                        v += dpp<0x4E>(0.0f, v);
+                        v += dpp<0x124>(0.0f, v);
+                        v += dpp<0x128>(0.0f, v);
+                        if (own && (ln & 15) == 0) lds_add(&sdA[at + s], v);
+                    }
+                }
+        };
+        __syncthreads();                                 // the tables (first tile) are in place; the tile before is done
+        auto take_turn = [&](int g) {
+            if constexpr (ALT_PRIO) {
+                if (((unsigned)(g / CP) & 1u) == hw_slot) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
+            }
+        };
+        if constexpr (OWN) {
+            for (int g = 0; g < Gact; g += CP) {
+                const unsigned t0 = fresh(tid);
+                float u[T], dl[T], dy[T], du[T], yp[T], pu[T], pd[T];
+                step_inputs(g + c_own, t0, u, dl, dy);
+                rotate();
+                if (t0 < 2 * CP * N) (&sAC[0][0][0][0])[t0] = r_ac;
+                fetch(t0);
+#pragma unroll
+                for (int t = 0; t < T; ++t) du[t] = u[t];
+                __syncthreads();                         // (one wavefront: orders the LDS accesses only)
+                states(g, 0, t0, dl, du, dy, yp, pu, pd);
+                finish(g, t0, (t0 % NTC) * TPT, dl, u, dy, yp, pu, pd);
+                __syncthreads();
+            }
+        } else {
+            auto main_part = [&](const int g, const int buf) {
+                const unsigned ln = fresh(lane), c = ln >> 5;
+                const int l4 = (ln & 31) * 4;
+                float dl[T], du[T], dy[T], yp[T], pu[T], pd[T];
+                lds_steps_read<T>(sIn[buf][c][0], l4, dl);
+                lds_steps_read<T>(sIn[buf][c][1], l4, du);
+                lds_steps_read<T>(sIn[buf][c][2], l4, dy);
+                states(g, buf, ln, dl, du, dy, yp, pu, pd);
+                if constexpr (HAS_Z) lds_steps_write<T>(sPart[buf][c][w][0], l4, yp);
+                lds_steps_write<T>(sPart[buf][c][w][1], l4, pu);
+                lds_steps_write<T>(sPart[buf][c][w][2], l4, pd);
+            };
+            auto next_inputs = [&](const int g, const int buf) {          // (past the last pair: unused)
+                const unsigned t0 = fresh(tid);
+                prologue(g + c_own, t0, step_slot((int)((t0 % NTC) * TPT)), buf);
+                fetch(t0);
+            };
+            next_inputs(0, 0);
+            if constexpr (NB == 2) {
+                // Between two barriers a wavefront finishes the pair before (its partial sums are complete), runs the main
+                // part of this pair and prepares the next one: nobody waits in between.  (Two barriers per pair cost 4 %.)
+                int g = 0, buf = 0;
+                for (; g < Gact; g += CP, buf ^= 1) {
+                    take_turn(g);
+                    __syncthreads();
+                    if (g > 0) epilogue(g - CP, buf ^ 1);
+                    rotate();
+                    main_part(g, buf);
+                    next_inputs(g + CP, buf ^ 1);
+                }
+                __syncthreads();
+                epilogue(g - CP, buf ^ 1);
+            } else {
+                for (int g = 0; g < Gact; g += CP) {
+                    take_turn(g);
+                    __syncthreads();
+                    rotate();
+                    main_part(g, 0);
+                    __syncthreads();
+                    epilogue(g, 0);
+                    next_inputs(g + CP, 0);
+                }
+            }
+        }
+
+        // ---- the tile's sums of dBm and dCm over this workgroup's channels
+        // (the two halves hold different channels: summed by a swap that leaves the lower half with steps 0-3 of a lane, the
+        // upper half with steps 4-7)
+        float oB[NS][4], oC[NS][4];
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const auto r = __builtin_amdgcn_permlane32_swap((unsigned)f2i(dB[s][t]), (unsigned)f2i(dB[s][t + 4]), false, false);
+                const auto q = __builtin_amdgcn_permlane32_swap((unsigned)f2i(dC[s][t]), (unsigned)f2i(dC[s][t + 4]), false, false);
+                oB[s][t] = i2f((int)r[0]) + i2f((int)r[1]);
+                oC[s][t] = i2f((int)q[0]) + i2f((int)q[1]);
+            }
+        if (p.part) {
+            // to this workgroup's own slot of the workspace, as 16-byte pieces in the order the lanes hold them (the sum
+            // over workgroups and the transposition to [L,N] are k_ss_bwd_maps's)
+            float *pt = p.part + (((slot0 + tile_first + tile) * gridDim.x + blockIdx.x) * 2 * N + n0) * TILE + lane * 4;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                *reinterpret_cast<float4 *>(pt + s * TILE) = make_float4(oB[s][0], oB[s][1], oB[s][2], oB[s][3]);
+                *reinterpret_cast<float4 *>(pt + (N + s) * TILE) = make_float4(oC[s][0], oC[s][1], oC[s][2], oC[s][3]);
+            }
+        } else {
+            // without a workspace: float atomics
+            float *gB = p.dBm + bc0 + l0 * N + n0, *gC = p.dCm + bc0 + l0 * N + n0;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int st = li * T + half * 4 + t;
+                if (st < rem) {
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) {
+                        unsafeAtomicAdd(gB + st * N + s, oB[s][t]);
+                        unsafeAtomicAdd(gC + st * N + s, oC[s][t]);
+                    }
+                }
+            }
+        }
+    };
+    for (int64_t tile = ntiles - 1; tile >= 0; --tile) {
+        if (vec && (tile + 1) * TILE <= L) do_tile(tile, std::true_type{}); else do_tile(tile, std::false_type{});
     }
-    if (fl_rem > 0) flush([]() {});
+    __syncthreads();
     // ---- per-channel results of this workgroup
     for (int i = tid; i < Gact * N; i += NT) {
-        const int g = i / N, n = i % N;
-        unsafeAtomicAdd(p.dA + (int64_t)(d0 + g) * N + n, sdA[0][g * N + n] + sdA[1][g * N + n]);
-        if (p.dx0 && chunk == 0) p.dx0[((int64_t)b * p.D + d0 + g) * N + n] = sH[g * N + n];
+        unsafeAtomicAdd(p.dA + (int64_t)d0 * N + i, sdA[i]);
+        if (p.dx0 && chunk == 0) p.dx0[((int64_t)b * p.D + d0) * N + i] = sH[i];
     }
     for (int g = tid; g < Gact; g += NT) {
-        float sD = 0.0f, sb = 0.0f;
-#pragma unroll
-        for (int ww = 0; ww < 2 * W; ++ww) { sD += sdD[ww * kMaxG + g]; sb += sdb[ww * kMaxG + g]; }
-        if (p.dD) unsafeAtomicAdd(p.dD + d0 + g, sD);
-        if (p.dbias) unsafeAtomicAdd(p.dbias + d0 + g, sb);
+        if (p.dD) unsafeAtomicAdd(p.dD + d0 + g, sdD[g]);
+        if (p.dbias) unsafeAtomicAdd(p.dbias + d0 + g, sdb[g]);
+    }
+}
+
+// dBm, dCm [.., L, N] from the tile sums the workgroups of k_ss_bwd left in the workspace: a workgroup adds one piece of a
+// tile (blockIdx.x) of one of the two maps (blockIdx.y) of one group (blockIdx.z) over the channel blocks, always in the same order, and
+// transposes it through LDS.  Bound by the reads of the workspace.
+template <int N>
+__global__ __launch_bounds__(256) void k_ss_bwd_maps(const BwdParams p, int gx) {
+    constexpr int PT = N * kBwdTileSteps;            // floats of one map's sums of one tile
+    constexpr int PIECES = N >= 8 ? N / 4 : 1;
+    constexpr int LP = 32 / PIECES;                  // lanes (of 8 steps) of a piece
+    constexpr int SP = LP * 8;                       // its steps
+    __shared__ float sT[SP * (N + 1)];
+    const int piece = blockIdx.x % PIECES;
+    const int64_t slot = blockIdx.x / PIECES;
+    int64_t b, tile, toff = 0, L = p.L;
+    if (p.cu) {
+        // the sequence whose tiles start last at or before this slot: sequence b's start at cu[b] / 256 + b
+        int lo = 0, hi = p.B - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            int64_t o = p.cu[mid];
+            o = o < 0 ? 0 : (o > p.L ? p.L : o);
+            if (o / kBwdTileSteps + mid <= slot) lo = mid; else hi = mid - 1;
+        }
+        b = lo;
+        seq_bounds(p.cu, lo, p.L, toff, L);
+        tile = slot - (toff / kBwdTileSteps + b);
+    } else {
+        b = slot / p.part_tiles;
+        tile = slot % p.part_tiles;
+    }
+    const int64_t l0 = tile * kBwdTileSteps + piece * SP;
+    if (tile < 0 || l0 >= L) return;
+    const int G = channels_of(p, (L + kBwdTileSteps - 1) / kBwdTileSteps);
+    const int nblk = (p.dpg + G - 1) / G;
+    const int grp = blockIdx.z;
+
+    const int tid = threadIdx.x;
+    if (tid < N * LP * 2) {
+        // this thread's four steps: of lane li of the piece (8 steps each), the first or the second four
+        const int li = tid % LP, q = (tid / LP) & 1, n = tid / (2 * LP);
+        const int at = n * kBwdTileSteps + q * 128 + (piece * LP + li) * 4;
+        const float *src = p.part + ((slot * gx + (int64_t)grp * nblk) * 2 + blockIdx.y) * PT + at;
+        float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll 8
+        for (int k = 0; k < nblk; ++k) {
+            const float4 v = *reinterpret_cast<const float4 *>(src + (int64_t)k * 2 * PT);
+            a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
+        }
+        float *t = sT + (li * 8 + q * 4) * (N + 1) + n;
+        t[0] = a.x; t[N + 1] = a.y; t[2 * (N + 1)] = a.z; t[3 * (N + 1)] = a.w;
+    }
+    __syncthreads();
+    float *out = (blockIdx.y ? p.dCm : p.dBm) + ((p.cu ? (int64_t)grp : b * p.bcg + grp) * p.L + toff + l0) * N;
+    const int rows = L - l0 < SP ? (int)(L - l0) : SP;
+    if constexpr (N >= 4) {
+        const int r = tid / (N / 4), n = (tid % (N / 4)) * 4;        // SP * N / 4 is the number of threads
+        static_assert(SP * N / 4 == 256, "one 16-byte piece per thread");
+        if (r < rows) {
+            const float *t = sT + r * (N + 1) + n;
+            *reinterpret_cast<float4 *>(out + r * N + n) = make_float4(t[0], t[1], t[2], t[3]);
+        }
+    } else {
+        for (int i = tid; i < rows * N; i += 256) out[i] = sT[(i / N) * (N + 1) + i % N];
     }
 }
 
 // ---------------------------------------------------------------- launchers
+// Workgroups the chip holds at once: two wavefronts per SIMD are what the registers allow.
+int bwd_places(int N) { return 2048 / (N == 4 ? 2 : (N >= 4 ? N / 4 : 1)); }
+
 // channels per workgroup: D here is the number of channels that share one pair of Bm/Cm maps.  `balanced` says
 // that all batch entries have the same length; otherwise (packed variable-length batches) four times as many,
 // smaller, workgroups let the dispatcher even out sequences of different lengths.
-int bwd_waves_per_workgroup(int N) { return N >= 8 ? N / 4 : (N == 4 ? 2 : 1); }   // as dispatched in launch_bwd_disc
-
-int bwd_channels_per_group(int B, int D, int N, int64_t, bool balanced) {
-    // aim at eight wavefronts per CU (two per SIMD, what the register budget allows): a workgroup has 8, 4, 2, 2, 1, 1
-    // of them for N = 32, 16, 8, 4, 2, 1, so 256, 512, 1024, 1024, 2048, 2048 workgroups
-    const int waves = bwd_waves_per_workgroup(N);
-    const int64_t full = 2048 / waves;                 // workgroups the chip holds at once
+static int channels_for(int B, int D, int64_t full, bool balanced) {
     int64_t G = ((int64_t)B * D) / (balanced ? full : 2048);
     // All workgroups of a balanced launch take equally long: a few more than the chip holds would run as a second,
     // almost empty round (518 instead of 512 workgroups: 40 % slower).  So as many channel blocks per row group as
@@ -663,8 +752,14 @@ int bwd_channels_per_group(int B, int D, int N, int64_t, bool balanced) {
     if (G > kMaxG) G = kMaxG;
     if (G > D) G = D;
     const int64_t groups = (D + G - 1) / G;
-    G = (D + groups - 1) / groups;                     // even split
-    return (int)G;
+    return (int)((D + groups - 1) / groups);           // even split
+}
+// a workgroup walks its channels in pairs
+static int whole_passes(int G) {
+    return (G + 1) / 2 * 2;
+}
+int bwd_channels_per_group(int B, int D, int N, int64_t, bool balanced) {
+    return whole_passes(channels_for(B, D, bwd_places(N), balanced));
 }
 
 void bwd_packed_shape(int B, int D, int64_t L, int64_t max_seqlen, int Gbal, int places, int *G, int *wcap, int *gmin) {
@@ -686,32 +781,43 @@ void bwd_packed_shape(int B, int D, int64_t L, int64_t max_seqlen, int Gbal, int
 
 // launch shape incl. the chunked path for few rows and long sequences (selective_bwd_carry.hip)
 BwdPlan bwd_plan(int rowsg, int dpg, int N, int64_t L, int mode, bool balanced) {
-    const int G = bwd_channels_per_group(rowsg, dpg, N, L, balanced);
-    // two wavefronts per SIMD are what the chip holds of this kernel: 2048 wavefronts
-    return plan_time_chunks(rowsg, dpg, L, balanced ? mode : 1, G, 2048 / bwd_waves_per_workgroup(N), kMaxG);
+    BwdPlan pl = plan_time_chunks(rowsg, dpg, L, balanced ? mode : 1, channels_for(rowsg, dpg, bwd_places(N), balanced), bwd_places(N), kMaxG);
+    pl.G = whole_passes(pl.G);
+    return pl;
 }
 
-// DZ (the caller wants dz) is a template parameter: without it the kernel does not rebuild ypre = sum_n C x
-template <typename IO, int N, int NK, int DISC, int T = 8>
-static hipError_t launch_bwd_n(const BwdParams &p, hipStream_t s) {
+// grid.x of a backward launch and the workspace its tile sums of dBm and dCm take
+int bwd_grid_x(const BwdParams &p) {
     const int gmin = p.wcap > 0 ? p.gmin : p.G;                       // fewest channels a workgroup may take
-    dim3 grid(p.bcg * ((p.dpg + gmin - 1) / gmin), p.B, p.nchunks > 1 ? p.nchunks : 1);
-    if (p.dz) hipLaunchKernelGGL((k_ss_bwd<IO, N, NK, T, DISC, true>), grid, dim3((N / NK) * 64), 0, s, p);
-    else hipLaunchKernelGGL((k_ss_bwd<IO, N, NK, T, DISC, false>), grid, dim3((N / NK) * 64), 0, s, p);
+    return p.bcg * ((p.dpg + gmin - 1) / gmin);
+}
+size_t bwd_part_bytes(int N, int64_t tile_slots, int64_t grid_x) {
+    return (size_t)tile_slots * grid_x * 2 * N * kBwdTileSteps * sizeof(float);
+}
+
+// HAS_Z (gated) is a template parameter: without it the kernel does not rebuild ypre = sum_n C x for dz
+template <typename IO, int N, int DISC>
+static hipError_t launch_bwd_n(const BwdParams &p, hipStream_t s) {
+    dim3 grid(bwd_grid_x(p), p.B, p.nchunks > 1 ? p.nchunks : 1);
+    if (p.z) hipLaunchKernelGGL((k_ss_bwd<IO, N, DISC, true>), grid, dim3(BwdGeom<N>::NT), 0, s, p);
+    else hipLaunchKernelGGL((k_ss_bwd<IO, N, DISC, false>), grid, dim3(BwdGeom<N>::NT), 0, s, p);
+    if (p.part) {
+        const int64_t slots = p.cu ? p.nslots : (int64_t)p.B * p.part_tiles;
+        dim3 g2((unsigned)(slots * (N >= 8 ? N / 4 : 1)), 2, p.bcg);
+        hipLaunchKernelGGL((k_ss_bwd_maps<N>), g2, dim3(256), 0, s, p, (int)grid.x);
+    }
     return hipGetLastError();
 }
 
 template <typename IO, int DISC>
 static hipError_t launch_bwd_disc(const BwdParams &p, hipStream_t s) {
     switch (p.N) {
-        // T = 4 steps per lane: with T = 8 the compiler spills to scratch, which costs far more than the
-        // longer scans (measured 2.4x slower on the Mamba-block shape)
-        case 1: return launch_bwd_n<IO, 1, 1, DISC, 4>(p, s);
-        case 2: return launch_bwd_n<IO, 2, 2, DISC, 4>(p, s);
-        case 4: return launch_bwd_n<IO, 4, 2, DISC, 4>(p, s);
-        case 8: return launch_bwd_n<IO, 8, 4, DISC, 4>(p, s);
-        case 16: return launch_bwd_n<IO, 16, 4, DISC, 4>(p, s);
-        case 32: return launch_bwd_n<IO, 32, 4, DISC, 4>(p, s);    // eight wavefronts: one workgroup per compute unit
+        case 1: return launch_bwd_n<IO, 1, DISC>(p, s);
+        case 2: return launch_bwd_n<IO, 2, DISC>(p, s);
+        case 4: return launch_bwd_n<IO, 4, DISC>(p, s);
+        case 8: return launch_bwd_n<IO, 8, DISC>(p, s);
+        case 16: return launch_bwd_n<IO, 16, DISC>(p, s);
+        case 32: return launch_bwd_n<IO, 32, DISC>(p, s);
     }
     return hipErrorInvalidValue;
 }
