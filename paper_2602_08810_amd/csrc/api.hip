@@ -9,7 +9,6 @@ using namespace lrnnx;
 
 namespace {
 
-constexpr int kNumCU = 256;              // MI355X
 
 inline bool supported_n(int n) { return n == 1 || n == 2 || n == 4 || n == 8 || n == 16 || n == 32; }
 inline bool supported_n_complex(int n) { return n <= 16 && supported_n(n); }   // complex-A entry points
@@ -24,9 +23,9 @@ inline bool row_vec_ok(const void *p, int64_t, int64_t, size_t es) {
 }
 
 // Number of time chunks of the chunk-carry forward path.
-int fwd_chunks(int64_t B, int64_t D, int64_t L, int io, bool forced) {
+int fwd_chunks(int64_t B, int64_t D, int64_t L, bool forced) {
     const int64_t wgs = B * cdiv(D, fwd_channels_per_workgroup());
-    const int64_t ntiles = cdiv(L, fwd_tile_steps(io));
+    const int64_t ntiles = cdiv(L, fwd_tile_steps());
     // eight workgroups per compute unit in all: measured on 256-1024 rows x 8k-64k steps, many short chunks beat the
     // two per compute unit an earlier rule aimed at by 5-10 % (the launch evens out better)
     int64_t n = cdiv(8 * kNumCU, wgs);
@@ -34,6 +33,14 @@ int fwd_chunks(int64_t B, int64_t D, int64_t L, int io, bool forced) {
     if (n > ntiles) n = ntiles;
     if (n < 1) n = 1;
     return (int)n;
+}
+
+// Whether the chunk-carry path is faster than a single pass: it walks the sequence twice, at 60 % and 100 % of a
+// pass's work, but on a full chip, where the single pass takes as long for few rows as for 2048.  N = 16, bf16: 512 rows of
+// 8192 steps 52 us against 89, 1024 rows 83 against 90, 1536 rows 110 against 97; 512 rows of 4096 steps 31 against 46,
+// of 2048 steps 31 against 26 (three launches are not free).
+bool fwd_chunks_pay(int64_t B, int64_t D, int64_t N, int64_t L) {
+    return L * N >= 65536 && B * D + ((int64_t)5 << 23) / (L * N) <= 1344;
 }
 
 // the complex forward kernel: 8 channels per workgroup, tiles of 512 steps for both I/O types
@@ -243,7 +250,7 @@ size_t lrnnx_workspace_bytes(int which, int64_t B, int64_t D, int64_t N, int64_t
         if (!(cplx ? supported_n_complex((int)N) : supported_n((int)N)) || D % bcg) return 0;
         const size_t es = cplx ? sizeof(float2) : sizeof(float);
         if (which == LRNNX_WS_BWD_SUMS) return bwd_sums_bytes(B, D, N, L, bcg, packed != 0) + 512;
-        if (which == LRNNX_WS_FWD) return packed ? 0 : (size_t)2 * B * D * fwd_chunks(B, D, L, io_dtype, true) * N * es;
+        if (which == LRNNX_WS_FWD) return packed ? 0 : (size_t)2 * B * D * fwd_chunks(B, D, L, true) * N * es;
         if (which == LRNNX_WS_FWD_COMPLEX)
             return packed ? 0 : (size_t)2 * B * D * cfwd_chunks(B * bcg * cdiv(D / bcg, 8), L, true) * N * es;
         // backward: the checkpoints of the recompute sweep (not LRNNX_WS_BWD_CARRY: the caller has the forward's), then
@@ -306,17 +313,16 @@ int lrnnx_selective_scan_fwd(const lrnnx_ss_fwd_args *a) {
     p.vec = row_vec_ok(a->u, p.u_sb, p.u_sd, es) && row_vec_ok(a->delta, p.dl_sb, p.dl_sd, es) &&
             row_vec_ok(a->y, p.y_sb, p.y_sd, es) && (!a->z || row_vec_ok(a->z, p.z_sb, p.z_sd, es));
 
-    const int64_t ntiles = cdiv(a->L, fwd_tile_steps(a->io_dtype));
-    const int64_t wgs = (int64_t)a->B * cdiv(a->D, fwd_channels_per_workgroup());
+    const int64_t ntiles = cdiv(a->L, fwd_tile_steps());
     bool chunked = false;
     int nch = 1;
     if (a->path == LRNNX_PATH_CHUNK_CARRY) {
-        nch = fwd_chunks(a->B, a->D, a->L, a->io_dtype, true);
+        nch = fwd_chunks(a->B, a->D, a->L, true);
         const size_t need = (size_t)2 * a->B * a->D * nch * a->N * sizeof(float);
         if (!a->workspace || a->workspace_bytes < need) return LRNNX_ERR_WORKSPACE;
         chunked = true;
-    } else if (a->path == LRNNX_PATH_AUTO && !cu && wgs <= kNumCU / 2 && ntiles >= 4) {
-        nch = fwd_chunks(a->B, a->D, a->L, a->io_dtype, false);
+    } else if (a->path == LRNNX_PATH_AUTO && !cu && fwd_chunks_pay(a->B, a->D, a->N, a->L)) {
+        nch = fwd_chunks(a->B, a->D, a->L, false);
         const size_t need = (size_t)2 * a->B * a->D * nch * a->N * sizeof(float);
         chunked = nch > 1 && a->workspace && a->workspace_bytes >= need;
         if (!chunked) nch = 1;
@@ -560,7 +566,7 @@ int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
         f.A = a->A; f.bias = a->delta_bias; f.x0 = a->x0; f.Bm = a->Bm; f.Cm = a->Cm;
         f.ckpt = reinterpret_cast<float *>(a->workspace);
         f.vec = row_vec_ok(a->u, f.u_sb, f.u_sd, es) && row_vec_ok(a->delta, f.dl_sb, f.dl_sd, es);
-        f.mode = MODE_CKPT_ONLY; f.nchunks = 1; f.tiles_per_chunk = cdiv(a->L, fwd_tile_steps(a->io_dtype));
+        f.mode = MODE_CKPT_ONLY; f.nchunks = 1; f.tiles_per_chunk = cdiv(a->L, fwd_tile_steps());
         if (launch_ss_fwd(f, a->io_dtype, a->disc, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
         ckpt = f.ckpt;
     }

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 namespace lrnnx {
+constexpr int kNumCU = 256;              // MI355X
 
 constexpr int64_t kCkptInterval = 256;   // steps between state checkpoints (public: lrnnx_ckpt_interval)
 
@@ -272,10 +273,10 @@ struct FillList {
 hipError_t launch_fill(const FillList &z, hipStream_t s);
 
 // Tile geometry the host needs for grids, workspaces and the choice of path (each constant lives beside its kernel).
-int fwd_channels_per_workgroup();            // wavefronts (= channels) of one forward workgroup
+int fwd_channels_per_workgroup();            // of the chunk-carry forward path
 int lti_chunk_group();                       // chunks (wavefronts) of one workgroup of the two-launch LTI path
 int lti_onepass_anchor();                    // every how many groups the single-launch LTI scan publishes a true state
-int fwd_tile_steps(int io_dtype);            // time steps one workgroup covers per tile
+int fwd_tile_steps();                        // time steps one of its workgroups covers per tile
 int bwd_channels_per_group(int B, int D, int N, int64_t L, bool balanced);
 int bwd_places(int N);                       // workgroups of the backward kernel the chip holds at once
 int bwd_grid_x(const BwdParams &p);

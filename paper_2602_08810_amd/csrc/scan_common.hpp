@@ -74,6 +74,19 @@ __device__ __forceinline__ void softplus_sigmoid(float s, float &sp, float &sg) 
     sp = fmaxf(v, s);
     sg = w * rcp_fast(1.0f + w);
 }
+// softplus alone, as max(s, 0) + log(1 + e^-|s|)
+template <bool PRECISE = true>
+__device__ __forceinline__ float softplus(float s) {
+    const float w = exp2_fast(__builtin_fabsf(s) * -kLog2e);
+    const float v = log2_fast(1.0f + w);
+    float r;                                     // (fmaxf would first spend an instruction on quieting s)
+    asm("v_max_f32 %0, 0, %1" : "=v"(r) : "v"(s));
+    if constexpr (PRECISE) {
+        const float series = w * (1.0f - w * (0.5f - w * (0.33333334f - w * 0.25f)));
+        return r + (w < 0.015625f ? series : v * kLn2);
+    }
+    return __builtin_fmaf(v, kLn2, r);
+}
 __device__ __forceinline__ float sigmoid_fast(float zz) { return rcp_fast(1.0f + exp2_fast(-zz * kLog2e)); }
 
 // Input gain of the exact zero-order hold, g = (e^{dt A} - 1) / A, given a = e^{dt A} and rA = 1/A (0 for A = 0).
@@ -81,8 +94,9 @@ __device__ __forceinline__ float sigmoid_fast(float zz) { return rcp_fast(1.0f +
 // A = 0, g = dt (1 + x/2 + x^2/6) with x = dt A, whose first omitted term x^3/24 is below 2e-7.
 __device__ __forceinline__ float zoh_gain(float dt, float A, float rA, float a) {
     const float x = dt * A;
-    const float small = dt * __builtin_fmaf(x, __builtin_fmaf(x, 0.16666667f, 0.5f), 1.0f);
-    return fabsf(x) < 0.015625f ? small : (a - 1.0f) * rA;
+    float small = dt * __builtin_fmaf(x, __builtin_fmaf(x, 0.16666667f, 0.5f), 1.0f), closed = (a - 1.0f) * rA;
+    asm("" : "+v"(small), "+v"(closed));             // a select of two values: the compiler makes branches around the four
+    return fabsf(x) < 0.015625f ? small : closed;    // instructions otherwise, which cost more than both sides together
 }
 
 // ---------------------------------------------------------------- fused discretisation (Sec. 3 schemes)
@@ -138,8 +152,10 @@ __device__ __forceinline__ void disc_partials(float dt, const ACoef &c, float a,
             // rounding error e in a reaches the difference dt a - g as e / A, i.e. 2 eps / x^2 relative to it: the
             // closed form is used from |x| = 1/8 on (1e-5), the series below (first omitted term x^4/144 < 4e-6)
             const float x = dt * c.A;
-            const float small = dt * dt * __builtin_fmaf(x, __builtin_fmaf(x, __builtin_fmaf(x, 0.033333335f, 0.125f), 0.33333334f), 0.5f);
-            g_A = (fabsf(x) < 0.125f) ? small : __builtin_fmaf(dt, a, -g) * c.rA;
+            float small = dt * dt * __builtin_fmaf(x, __builtin_fmaf(x, __builtin_fmaf(x, 0.033333335f, 0.125f), 0.33333334f), 0.5f);
+            float closed = __builtin_fmaf(dt, a, -g) * c.rA;
+            asm("" : "+v"(small), "+v"(closed));     // (no branches, as in zoh_gain)
+            g_A = fabsf(x) < 0.125f ? small : closed;
         }
     }
 }
@@ -550,14 +566,20 @@ __device__ __forceinline__ void load_few_raw(const IO *row, IDX l, IDX L, bool v
             r.w[0] = *reinterpret_cast<const unsigned short *>(row + l);
         }
     } else {
-#pragma unroll
-        for (int i = 0; i < WORDS; ++i) r.w[i] = 0u;
+        // all of them without a branch, so that they are under way together (one after the other, each waited for, the end
+        // of a sequence cost a wavefront ten microseconds); past the end the last element, dropped (L >= 1)
+        uint32_t v[CNT];
 #pragma unroll
         for (int i = 0; i < CNT; ++i) {
-            if (l + i < L) {
-                if constexpr (sizeof(IO) == 4) r.w[i] = *reinterpret_cast<const uint32_t *>(row + l + i);
-                else r.w[i / 2] |= (uint32_t)(*reinterpret_cast<const unsigned short *>(row + l + i)) << (16 * (i % 2));
-            }
+            const IDX lc = l + i < L ? l + i : L - 1;
+            if constexpr (sizeof(IO) == 4) v[i] = *reinterpret_cast<const uint32_t *>(row + lc);
+            else v[i] = *reinterpret_cast<const unsigned short *>(row + lc);
+        }
+#pragma unroll
+        for (int i = 0; i < CNT; ++i) {
+            v[i] = l + i < L ? v[i] : 0u;
+            if constexpr (sizeof(IO) == 4) r.w[i] = v[i];
+            else r.w[i / 2] = i % 2 ? r.w[i / 2] | v[i] << 16 : v[i];
         }
     }
 }

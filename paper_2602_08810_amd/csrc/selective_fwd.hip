@@ -1,51 +1,104 @@
 // Forward selective scan for gfx950 (Eq. 2 of the paper with diagonal, input-dependent
 // A(k), B(k), C(k); S6 row of Table 1; discretisation fused in, Sec. 3).
 //
-// Mapping.  Time runs along the lanes: lane i of a wavefront owns T consecutive steps
-// of one (b,d) row, so the [B,D,L] tensors are read and written with 16-byte accesses
-// that are contiguous across the wavefront.  One wavefront = one channel; the W
-// wavefronts of a workgroup are W channels of the same batch entry walking the same
-// time tile (64*T steps), so the tile of Bm/Cm (shared by all channels) is staged once
-// per workgroup into LDS as fp32, in an order that makes every later read a
-// conflict-free ds_read_b128.  States never leave registers (Sec. 3: no hidden-state
-// materialisation): for each n the lane folds its T steps into one affine pair, the
-// wavefront takes an inclusive prefix over the 64 pairs with DPP moves, and the lane
-// replays its steps from the carried-in state, accumulating y = sum_n C x on the fly.
-// The state after the tile is lane 63's, broadcast through a scalar register to the
-// next tile of the same row.
+// Mapping.  Time runs along the lanes: a channel takes LPC lanes (16 or 64), each of which owns T consecutive steps (4, 8
+// or 16), so the [B,D,L] tensors are read and written with 16-byte accesses that are contiguous across the lanes of a
+// channel.  The W wavefronts of a workgroup (each with 64/LPC channels) walk the same time tile of LPC T steps, so the
+// tile of Bm/Cm (shared by all channels) is staged once per workgroup into LDS as fp32, 16 states at a time, in an order
+// that makes every access conflict-free.  States never leave registers (Sec. 3: no hidden-state materialisation): for
+// each n the lane folds its steps into one affine pair, the channel's lanes take an inclusive prefix over their pairs
+// with DPP moves, and the lane replays its steps from the carried-in state, accumulating y = sum_n C x on the fly.  The
+// state after the tile is the last lane's; it waits in LDS for the next tile of the same row.
+//
+// What bounds it: vector-ALU issue, one instruction per SIMD every four cycles whatever its kind (an exponential takes
+// two of these slots); with three wavefronts a SIMD the ALU is busy all the time.  Per state update: 7 slots for the
+// multiplier (a product and an exponential), the input, the fold, the replay and the projection, and 1/T of the rest:
+// 13 to 16 for the prefix, its start and its end, and of 26 a step (softplus, gate, conversions) shared by the N states.
+// Hence 16 steps per lane, one LDS address for all of Bm and Cm, and tiles known to be whole without any check.
+// The next tile's inputs are fetched before the state loop where the registers allow, else after it.
+// Mamba-block training shape (B = 8, D = 1536, N = 16, L = 2048, bf16, with gate and checkpoints): 112 us, 137 us with 64
+// lanes of 8 steps and 13 slots an update; B = 16, D = 2560, L = 4096 without gate: 640 us, before 823.
+// See fwd_shape() for the choice of LPC and T.
 //
 // The same kernel serves the three launches of the chunk-carry path for long L / few
 // rows (blockIdx.z = chunk): MODE_AGG returns each chunk's affine aggregate,
 // k_ss_carry chains them, MODE_APPLY reruns the chunk from its true carry-in.
 #include "kernels.hpp"
 #include "scan_common.hpp"
+#include <type_traits>
 
 namespace lrnnx {
 
-// Two workgroups share a compute unit only if a wavefront stays within 128 vector registers, and with short rows
-// (many workgroups per CU, one after the other) the second one is worth 20-25 %: it covers the other's start-up
-// and drain (measured with a variant that needed 146 registers).  The compiler is therefore held to 128 (the exact-ZOH
-// variant otherwise takes 133).  With float32 I/O the rows of Bm/Cm fetched one tile ahead would alone cost 2 N
-// registers, so that prefetch is for bfloat16 only (float32: 196 -> 171 us on the Mamba-block shape).  N = 32 fills
-// the LDS of a CU with one workgroup's tile and is left alone.
-template <typename IO, int N, int T, int W, int DISC, bool WANT_Y, bool CKPT>
-__global__ __launch_bounds__(W * 64, (N <= 16) ? 4 : 2) void k_ss_fwd(const FwdParams p) {
-    constexpr int TQ = T / 4;
-    constexpr int QS = 256 + (TQ > 1 ? 32 / TQ : 0);   // floats per quarter-plane, padded against bank conflicts on staging
-    constexpr int PLANE = TQ * QS;                     // floats per state index n
-    constexpr int TILE = 64 * T;
-    __shared__ __attribute__((aligned(16))) float sB[N * PLANE];
-    __shared__ __attribute__((aligned(16))) float sC[N * PLANE];
+// Inclusive prefix over the LPC lanes of each channel, first lane first; on return S holds it and xin the prefix of the
+// lane before (a channel's first lane keeps what it came with).  A DPP read needs two wait states after the write of its
+// register: the s_nop cost the wavefront a cycle each and the other wavefronts of the SIMD nothing.  With KEEP_P the
+// product is complete as well.
+template <int LPC, bool KEEP_P>
+__device__ __forceinline__ void channel_scan(float &P, float &S, float &xin) {
+    static_assert(LPC == 16 || (LPC == 64 && !KEEP_P), "lanes of a channel");
+#define LRNNX_S(CTRL) "v_fmac_f32_dpp %0, %0, %1 " CTRL "\n\ts_nop 1\n\t"
+#define LRNNX_PS(CTRL) LRNNX_F_STATE(0, 1, CTRL) "s_nop 0\n\t"
+#define LRNNX_SCAN(LAST, MOVES)                                                                                          \
+    asm("s_nop 1\n\t" LRNNX_PS("row_shr:1" LRNNX_ALLROWS) LRNNX_PS("row_shr:2" LRNNX_ALLROWS)                            \
+        LRNNX_PS("row_shr:4" LRNNX_ALLROWS) LAST MOVES                                                                   \
+        : "+v"(S), "+v"(P), "+v"(xin))
+#define LRNNX_SHR8(KIND) LRNNX_##KIND("row_shr:8" LRNNX_ALLROWS)
+#define LRNNX_BC15(KIND) LRNNX_##KIND("row_bcast:15 row_mask:0xa bank_mask:0xf")   /* lane 15 of rows 0, 2 -> rows 1, 3 */
+#define LRNNX_BC31(KIND) LRNNX_##KIND("row_bcast:31 row_mask:0xc bank_mask:0xf")   /* lane 31 -> rows 2, 3 */
+#define LRNNX_MV(CTRL) "v_mov_b32_dpp %2, %0 " CTRL "\n\t"
+    if constexpr (LPC == 16) {
+        if constexpr (KEEP_P) LRNNX_SCAN(LRNNX_SHR8(PS), LRNNX_MV("row_shr:1" LRNNX_ALLROWS));
+        else LRNNX_SCAN(LRNNX_SHR8(S), LRNNX_MV("row_shr:1" LRNNX_ALLROWS));
+    } else {
+        LRNNX_SCAN(LRNNX_SHR8(PS) LRNNX_BC15(PS) LRNNX_BC31(S), LRNNX_MV("wave_shr:1" LRNNX_ALLROWS));
+    }
+#undef LRNNX_MV
+#undef LRNNX_BC31
+#undef LRNNX_BC15
+#undef LRNNX_SHR8
+#undef LRNNX_SCAN
+#undef LRNNX_PS
+#undef LRNNX_S
+}
 
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+template <int LPC, int T> struct FwdGeom {
+    static constexpr int W = LPC * T / 64 < 8 ? LPC * T / 64 : 8;      // wavefronts of a workgroup
+    static constexpr int CPW = 64 / LPC;             // channels of a wavefront
+    static constexpr int CH = W * CPW;               // channels of a workgroup
+    static constexpr int TILE = LPC * T;
+    static constexpr int Q = 4 * LPC + 256 / T;      // a quarter (T = 16), half (T = 8) or all (T = 4) of a staged row, see below
+    static constexpr int ROW = Q * (T / 4);
+};
+
+// Three workgroups of four wavefronts share a compute unit with 16 lanes per channel (168 registers), one of eight
+// otherwise (its staged tile fills the LDS).
+template <typename IO, int N, int DISC, bool WANT_Y, bool CKPT, int LPC, int T>
+__global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 3 : 2) : 4)) void k_ss_fwd(const FwdParams p) {
+    using GE = FwdGeom<LPC, T>;
+    constexpr int W = GE::W, CPW = GE::CPW, CH = GE::CH, TILE = GE::TILE, NT = W * 64;
+    constexpr int RPT = TILE / NT;                   // rows of the maps a thread stages
+    constexpr int NS = N > 16 ? 16 : N, NH = N / NS; // states staged at a time, and how often
+    constexpr bool EARLY = sizeof(IO) == 2 ? LPC > 16 || N <= 8 : LPC > 16 && N <= 8;
+    constexpr bool LATE_Z = sizeof(IO) == 4 && T == 16 && LPC == 16;
+    constexpr bool AGG = !WANT_Y && !CKPT;           // the aggregate launch of the chunk-carry path
+    static_assert(TILE % kCkptInterval == 0 && RPT * NT == TILE, "tile shape");
+    __shared__ __attribute__((aligned(16))) float sBC[WANT_Y ? 2 * NS : NS + 1][GE::ROW];   // Bm, Cm
+    __shared__ __attribute__((aligned(16))) float sA[CH + 1][N], sX[CH + 2][N];    // A; the state entering the next tile, and zeros
+    __shared__ float sP[AGG ? CH : 1][N];            // aggregate: product of the multipliers so far
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, li = lane % LPC;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = blockIdx.y;
-    // a workgroup takes W consecutive channels of ONE Bm/Cm group (it stages that group's maps in LDS)
-    const int blk_per_grp = (p.dpg + W - 1) / W;
+    // a workgroup takes CH consecutive channels of ONE Bm/Cm group (it stages that group's maps in LDS)
+    const int blk_per_grp = (p.dpg + CH - 1) / CH;
     const int grp = blockIdx.x / blk_per_grp;
-    const int d_in = (blockIdx.x % blk_per_grp) * W + w;
-    const bool active = d_in < p.dpg;
-    const int d = grp * p.dpg + (active ? d_in : p.dpg - 1);
+    const int din0 = (blockIdx.x % blk_per_grp) * CH;
+    const int ch = w * CPW + lane / LPC;             // this lane's channel of the workgroup
+    const bool live = din0 + ch < p.dpg;
+    const bool busy = din0 + w * CPW < p.dpg;        // wave-uniform: the wavefront has a channel at all
+    const int d0 = grp * p.dpg + din0;
+    const int d = grp * p.dpg + (live ? din0 + ch : p.dpg - 1);
     const int chunk = blockIdx.z;
     // Packed variable-length mode (p.cu != nullptr): batch entry b is the sequence of steps cu[b] .. cu[b+1]-1 of ONE
     // packed time axis of p.L steps; I/O rows have no batch stride, the maps are [G, p.L, N].  The bounds are
@@ -60,288 +113,372 @@ __global__ __launch_bounds__(W * 64, (N <= 16) ? 4 : 2) void k_ss_fwd(const FwdP
     const int64_t ntiles = (L + TILE - 1) / TILE;
     const int64_t tile0 = (int64_t)chunk * p.tiles_per_chunk;
     const int64_t tile1 = (tile0 + p.tiles_per_chunk < ntiles) ? tile0 + p.tiles_per_chunk : ntiles;
-    const int64_t row = (int64_t)b * p.D + d;
     const bool vec = p.vec != 0;
     const int mode = p.mode;
 
-    const IO *urow = reinterpret_cast<const IO *>(p.u) + bs * p.u_sb + d * p.u_sd + toff;
-    const IO *drow = reinterpret_cast<const IO *>(p.delta) + bs * p.dl_sb + d * p.dl_sd + toff;
-    const IO *zrow = p.z ? reinterpret_cast<const IO *>(p.z) + bs * p.z_sb + d * p.z_sd + toff : nullptr;
-    IO *yrow = p.y ? reinterpret_cast<IO *>(p.y) + bs * p.y_sb + d * p.y_sd + toff : nullptr;
+    // Rows and lanes are worked out again where they are used: an opaque copy of the thread's number keeps the compiler
+    // from holding a register for each address throughout.
+    auto fresh = [&]() { unsigned t = tid; asm volatile("" : "+v"(t)); return t; };
+    auto row = [&](const void *base, int64_t sb, int64_t sd, int64_t l) {
+        int c = din0 + w * CPW + (fresh() & 63) / LPC;
+        c = c < p.dpg ? c : p.dpg - 1;
+        return reinterpret_cast<const IO *>(base) + (bs * sb + (int64_t)(grp * p.dpg + c) * sd + toff + l);
+    };
     const int64_t bc0 = ((bs * p.bcg + grp) * p.L + toff) * N;       // first element of the maps of this sequence
     const IO *Bm = reinterpret_cast<const IO *>(p.Bm) + bc0;
     const IO *Cm = reinterpret_cast<const IO *>(p.Cm) + bc0;
-
-    // Per-state uniform values live one per lane (lane n holds state n) and are read with
-    // v_readlane, so the loop over n stays rolled and nothing is indexed dynamically.
-    float xcv = 0.0f, pcv = 1.0f;
-    if (lane < N) {
-        if (mode == MODE_APPLY) xcv = p.ws_S[(row * p.nchunks + chunk) * N + lane];
-        else if (mode != MODE_AGG && p.x0) xcv = p.x0[row * N + lane];
-    }
-    const float Av = (lane < N) ? p.A[d * N + lane] : 0.0f;
     const float Dsk = p.Dskip ? p.Dskip[d] : 0.0f;
     const float bias = p.bias ? p.bias[d] : 0.0f;
-    // checkpoints of this row: [B,D,nck,N], or packed [D,nslots,N] with sequence b starting at slot toff/interval + b
-    const int64_t ck0 = p.cu ? (int64_t)d * p.nslots + toff / kCkptInterval + b
-                             : row * ((L + kCkptInterval - 1) / kCkptInterval);
+    // checkpoints: [B,D,nck,N], or packed [D,nslots,N] with sequence b starting at slot toff/interval + b
+    const int64_t nck = p.cu ? p.nslots : (L + kCkptInterval - 1) / kCkptInterval;
+    const int64_t ck_first = p.cu ? toff / kCkptInterval + b : 0;
 
-    // this lane's T steps of u, Delta and z are fetched one tile ahead (raw, converted when their tile starts), so
-    // that their latency hides behind the previous tile's state loop
-    RawFew<IO, T> r_u, r_dl, r_z;
-    auto fetch = [&](int64_t tile) {
-        const int64_t lf = tile * TILE + lane * T;
-        if (vec && (tile + 1) * TILE <= L) {
-            // a tile wholly inside the sequence (wave-uniform): plain vector loads, nothing to check per element
-            load_few_raw<IO, T>(urow + lf, 0, T, true, r_u);
-            load_few_raw<IO, T>(drow + lf, 0, T, true, r_dl);
-            if constexpr (WANT_Y) { if (zrow) load_few_raw<IO, T>(zrow + lf, 0, T, true, r_z); }
-        } else {
-            load_few_raw<IO, T>(urow, lf, L, vec, r_u);
-            load_few_raw<IO, T>(drow, lf, L, vec, r_dl);
-            if constexpr (WANT_Y) { if (zrow) load_few_raw<IO, T>(zrow, lf, L, vec, r_z); }
-        }
-    };
-    if (active && tile0 < tile1) fetch(tile0);
-    // likewise the row of Bm and Cm this thread stages (one step of the tile per thread when the tile has as many
-    // steps as the workgroup has threads); rows past the sequence read as zero
-    constexpr bool PREFETCH_MAPS = TILE == W * 64 && sizeof(IO) == 2;   // float32 rows would cost 2 N registers
-    RawFew<IO, PREFETCH_MAPS ? N : 1> r_B, r_C;
-    auto fetch_maps = [&](int64_t tile) {
-        const int64_t l = tile * TILE + threadIdx.x;
-        if constexpr (PREFETCH_MAPS) {
-            load_few_raw<IO, N>(Bm + l * N, (int64_t)0, l < L ? (int64_t)N : (int64_t)0, true, r_B);
-            load_few_raw<IO, N>(Cm + l * N, (int64_t)0, l < L ? (int64_t)N : (int64_t)0, true, r_C);
-        }
-    };
-    if constexpr (PREFETCH_MAPS) { if (tile0 < tile1) fetch_maps(tile0); }
+    for (int i = lane; i < CPW * N; i += 64) {       // a wavefront's channels are its own: no barrier between it and these
+        const int c = w * CPW + i / N, n = i % N;
+        const int dc = d0 + (din0 + c < p.dpg ? c : 0);
+        const int64_t r = (int64_t)b * p.D + dc;
+        sA[c][n] = p.A[(int64_t)dc * N + n];
+        float x = 0.0f;
+        if (mode == MODE_APPLY) x = p.ws_S[(r * p.nchunks + chunk) * N + n];
+        else if (mode != MODE_AGG && p.x0) x = p.x0[r * N + n];
+        sX[c][n] = x;
+        if constexpr (AGG) sP[c][n] = 1.0f;
+    }
+    if (lane < N) sX[CH][lane] = 0.0f;               // (every wavefront: the same value)
 
-    for (int64_t tile = tile0; tile < tile1; ++tile) {
+    // A staged row of Bm or Cm: step 4 q + i of lane l (of T) at q Q + 4 l + i.  The reads, 16 bytes from each lane,
+    // are contiguous over the lanes and all share one address; Q leaves a gap of 256 / T so that the 64 consecutive steps
+    // which a wavefront stages at once fall into 64 banks.
+    // ---- the inputs of a tile, raw.  Those of a whole tile (FULL: nothing to check per element) are fetched ahead, once
+    // the state loop of the tile before is done, and used after its epilogue.
+    RawFew<IO, T> r_u, r_dl;
+    RawFew<IO, NS> r_B[RPT], r_C[WANT_Y ? RPT : 1];
+    auto fetch_rows = [&](int64_t tile, auto FULL) {
         const int64_t l0 = tile * TILE;
-        const int64_t ll = l0 + lane * T;
-        static_assert(TILE % kCkptInterval == 0 && kCkptInterval % T == 0, "checkpoints fall on lane boundaries");
-        const bool ck_lane = (lane % ((int)kCkptInterval / T)) == 0;     // ll is a multiple of the checkpoint interval
-
-        // ---- stage the Bm/Cm tile (all wavefronts), fp32, layout [n][t/4][lane][t%4]; the rows were fetched (raw) one
-        // tile ahead
-        __syncthreads();
-        if constexpr (PREFETCH_MAPS) {
-            const int r = threadIdx.x;
-            float bv[N], cv[N];
-            unpack_few<IO, PREFETCH_MAPS ? N : 1>(r_B, bv);
-            unpack_few<IO, PREFETCH_MAPS ? N : 1>(r_C, cv);
-            const int off = ((r % T) / 4) * QS + (r / T) * 4 + (r % 4);
-#pragma unroll
-            for (int k = 0; k < N; ++k) { sB[k * PLANE + off] = bv[k]; sC[k * PLANE + off] = cv[k]; }
-            if (tile + 1 < tile1) fetch_maps(tile + 1);
+        const IO *u = row(p.u, p.u_sb, p.u_sd, l0), *dl = row(p.delta, p.dl_sb, p.dl_sd, l0);
+        const int r = (fresh() % LPC) * T;
+        if constexpr (FULL) {
+            load_few_raw<IO, T>(u + r, 0, T, true, r_u);
+            load_few_raw<IO, T>(dl + r, 0, T, true, r_dl);
         } else {
-            for (int r = threadIdx.x; r < TILE; r += W * 64) {
-                float bv[N], cv[N];
-                const int64_t l = l0 + r;
-                if (l < L) {
-                    load_row<IO, N>(Bm + l * N, bv);
-                    load_row<IO, N>(Cm + l * N, cv);
-                } else {
-#pragma unroll
-                    for (int k = 0; k < N; ++k) { bv[k] = 0.0f; cv[k] = 0.0f; }
-                }
-                const int off = ((r % T) / 4) * QS + (r / T) * 4 + (r % 4);
-#pragma unroll
-                for (int k = 0; k < N; ++k) { sB[k * PLANE + off] = bv[k]; sC[k * PLANE + off] = cv[k]; }
-            }
+            const int n = L - l0 < TILE ? (int)(L - l0) : TILE;
+            load_few_raw<IO, T>(u, r, n, vec, r_u);
+            load_few_raw<IO, T>(dl, r, n, vec, r_dl);
         }
-        __syncthreads();
-        if (!active) continue;
-
-        // ---- this lane's T steps of u and Delta
-        float uv[T], dl[T], du[T], yv[T];
-        unpack_few<IO, T>(r_u, uv);
-        unpack_few<IO, T>(r_dl, dl);
-        const RawFew<IO, T> c_z = r_z;                // this tile's gate values, needed after the state loop
-        if (tile + 1 < tile1) fetch(tile + 1);
-        float sum_dl = 0.0f;
-        const int rem = (L - l0 < TILE) ? (int)(L - l0) : TILE;   // valid steps of this tile (wave-uniform)
+    };
+    auto fetch_maps = [&](int64_t tile, int h, auto FULL) {
+        const int64_t l0 = tile * TILE;
 #pragma unroll
-        for (int t = 0; t < T; ++t) {
-            float s = dl[t] + bias, sp, sg;
-            if (p.softplus) softplus_sigmoid<sizeof(IO) == 4>(s, sp, sg); else sp = s;
-            dl[t] = sp;
+        for (int k = 0; k < RPT; ++k) {
+            int64_t l = l0 + (int)(fresh() + k * NT);
+            if constexpr (!FULL) l = l < L ? l : L - 1;  // rows past the sequence: the last one again, discarded below
+            load_few_raw<IO, NS>(Bm + (l * N + h * NS), 0, NS, true, r_B[k]);
+            if constexpr (WANT_Y) load_few_raw<IO, NS>(Cm + (l * N + h * NS), 0, NS, true, r_C[k]);
         }
-        if (rem < TILE) {                             // steps past the end are the identity map (a = 1, b = 0)
+    };
+    // after the last tile: these registers hold nothing any more (without it they would stay occupied throughout)
+    auto forget = [](auto &r) {
 #pragma unroll
-            for (int t = 0; t < T; ++t) dl[t] = (lane * T + t < rem) ? dl[t] : 0.0f;
-        }
+        for (uint32_t &x : r.w) asm volatile("" : "=v"(x));
+    };
+    auto forget_maps = [&]() {
 #pragma unroll
-        for (int t = 0; t < T; ++t) {
-            sum_dl += dl[t];
-            du[t] = dl[t] * uv[t];
-            yv[t] = Dsk * uv[t];
-        }
-
-        // One state: fold the lane's T steps, wavefront prefix, replay.  Bc holds this state's Bm for the lane; Bn
-        // receives the next state's while this one computes (ping-pong, no copies).  Cm is only needed by the
-        // replay, so it is read from LDS after the fold and its latency hides behind the prefix.
-        auto one_state = [&](int n, const float4 (&Bc)[TQ], float4 (&Bn)[TQ]) {
-            if (n + 1 < N) {
-#pragma unroll
-                for (int q = 0; q < TQ; ++q)
-                    Bn[q] = *reinterpret_cast<const float4 *>(&sB[(n + 1) * PLANE + q * QS + lane * 4]);
-            }
-            float Bv[T], a[T], bb[T];
-#pragma unroll
-            for (int q = 0; q < TQ; ++q) {
-                Bv[4 * q] = Bc[q].x; Bv[4 * q + 1] = Bc[q].y; Bv[4 * q + 2] = Bc[q].z; Bv[4 * q + 3] = Bc[q].w;
-            }
-            const ACoef ac = make_acoef<DISC>(readlane(Av, n));
-            const float xc = readlane(xcv, n);
-            float P = 1.0f, S = 0.0f;
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                float g;
-                disc_ag<DISC>(dl[t], ac, a[t], g);
-                if constexpr (DISC == DISC_ZOH_S6) bb[t] = du[t] * Bv[t];
-                else if constexpr (DISC == DISC_DIRAC) bb[t] = uv[t] * Bv[t];
-                else bb[t] = g * uv[t] * Bv[t];
-                S = (t == 0) ? bb[0] : __builtin_fmaf(a[t], S, bb[t]);   // the fold starts from zero
-                if constexpr (DISC == DISC_BILINEAR) P *= a[t];
-            }
-            float4 Cc[TQ];
+        for (int k = 0; k < RPT; ++k) { forget(r_B[k]); if constexpr (WANT_Y) forget(r_C[k]); }
+    };
+    auto do_tile = [&](int64_t tile, auto FULL, bool ahead) {
+        const int64_t l0 = tile * TILE;
+        const int rem = FULL ? TILE : (L - l0 < TILE ? (int)(L - l0) : TILE);
+        float dl[T], du[T], yv[T], sum_dl = 0.0f;    // du: Delta*u for S6, u for the other schemes
+        RawFew<IO, T> r_z;
+        auto fetch_z = [&]() {
             if constexpr (WANT_Y) {
-#pragma unroll
-                for (int q = 0; q < TQ; ++q)
-                    Cc[q] = *reinterpret_cast<const float4 *>(&sC[n * PLANE + q * QS + lane * 4]);
+                if (!p.z) return;
+                const IO *z = row(p.z, p.z_sb, p.z_sd, l0);
+                const int r = (fresh() % LPC) * T;
+                if constexpr (FULL) load_few_raw<IO, T>(z + r, 0, T, true, r_z);
+                else load_few_raw<IO, T>(z, r, rem, vec, r_z);
             }
-            if constexpr (DISC != DISC_BILINEAR) P = exp2_fast(sum_dl * ac.A2);   // product of the T multipliers
-            if (lane == 0) S = __builtin_fmaf(P, xc, S);             // the carried state enters through lane 0
-            wave_scan_fwd(P, S);
-            float x = dpp<DPP_WAVE_SHR1>(xc, S);                     // state entering this lane's first step
-            if constexpr (CKPT) {
-                if (ck_lane && ll < L) p.ckpt[(ck0 + ll / kCkptInterval) * N + n] = x;
-            }
-            if constexpr (!WANT_Y) {
-                xcv = writelane(xcv, readlane(S, 63), n);            // inclusive prefix at lane 63 = state after the tile
-                pcv = writelane(pcv, readlane(pcv, n) * readlane(P, 63), n);
-            } else {
-                float Cv[T];
+        };
 #pragma unroll
-                for (int q = 0; q < TQ; ++q) {
-                    Cv[4 * q] = Cc[q].x; Cv[4 * q + 1] = Cc[q].y; Cv[4 * q + 2] = Cc[q].z; Cv[4 * q + 3] = Cc[q].w;
+        for (int h = 0; h < NH; ++h) {
+            // ---- stage the maps of NS states (all wavefronts) as fp32
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < RPT; ++k) {
+                const unsigned r = fresh() + k * NT, q = (r % T) / 4;
+                const unsigned off = q * GE::Q + (r / T) * 4 + (r % 4);
+                float v[NS];
+                unpack_few<IO, NS>(r_B[k], v);
+#pragma unroll
+                for (int n = 0; n < NS; ++n) sBC[n][off] = FULL || (int)r < rem ? v[n] : 0.0f;
+                if constexpr (WANT_Y) {
+                    unpack_few<IO, NS>(r_C[k], v);
+#pragma unroll
+                    for (int n = 0; n < NS; ++n) sBC[NS + n][off] = FULL || (int)r < rem ? v[n] : 0.0f;
+                }
+            }
+            if constexpr (CKPT && TILE == kCkptInterval) {           // the state entering the tile is the carried one
+                if (busy && h == 0)
+                    for (int i = fresh() & 63; i < CPW * N; i += 64) {
+                        const int c = w * CPW + i / N;
+                        const int64_t r = p.cu ? (int64_t)(d0 + c) : (int64_t)b * p.D + d0 + c;
+                        if (din0 + c < p.dpg) p.ckpt[(r * nck + ck_first + tile) * N + i % N] = sX[c][i % N];
+                    }
+            }
+            __syncthreads();
+            if (busy && h == 0) {
+                // ---- this lane's steps of Delta, Delta u and D u
+                unpack_few<IO, T>(r_u, du);
+                unpack_few<IO, T>(r_dl, dl);
+#pragma unroll
+                for (int t = 0; t < T; ++t) asm volatile("" : "+v"(du[t]), "+v"(dl[t]));
+                if constexpr (!LATE_Z) fetch_z();
+#pragma unroll
+                for (int t = 0; t < T; ++t) { dl[t] += bias; asm volatile("" : "+v"(dl[t])); }
+                if (p.softplus) {
+#pragma unroll
+                    for (int t = 0; t < T; ++t) dl[t] = softplus<sizeof(IO) == 4>(dl[t]);
+                }
+                if constexpr (!FULL) {                   // steps past the end are the identity map (a = 1, b = 0)
+                    const int r0 = (fresh() % LPC) * T;
+#pragma unroll
+                    for (int t = 0; t < T; ++t) { dl[t] = (r0 + t < rem) ? dl[t] : 0.0f; du[t] = (r0 + t < rem) ? du[t] : 0.0f; }
                 }
 #pragma unroll
                 for (int t = 0; t < T; ++t) {
-                    x = __builtin_fmaf(a[t], x, bb[t]);
-                    yv[t] = __builtin_fmaf(Cv[t], x, yv[t]);
+                    sum_dl += dl[t];
+                    if constexpr (WANT_Y) yv[t] = Dsk * du[t];
+                    if constexpr (DISC == DISC_ZOH_S6) du[t] *= dl[t];
                 }
-                xcv = writelane(xcv, readlane(x, 63), n);            // lane 63 ends on the tile's last step
+
             }
-        };
-        // Two states at a time (every supported N > 1 is even): their folds and replays are independent chains and
-        // their prefix scans are interleaved step by step, which fills the issue gaps a single dependent chain leaves.
-        auto two_states = [&](int n) {
-            float4 B0[TQ], B1[TQ];
+            auto fetch_next = [&](auto ROWS) {
+                if (h + 1 < NH) { fetch_maps(tile, h + 1, FULL); return; }
+                if (FULL && ahead) {
+                    fetch_maps(tile + 1, 0, FULL);
+                    if constexpr (ROWS) fetch_rows(tile + 1, FULL);
+                } else { forget_maps(); forget(r_u); forget(r_dl); }
+            };
+            if (busy) {
+                if constexpr (EARLY) fetch_next(std::true_type{});
+                // The LDS reads run ahead of their use: Bm, A and the carried state of the next n during this one, Cm from the
+                // top of the pass to its end.
+                auto read = [&](const float *m, float *v) {
 #pragma unroll
-            for (int q = 0; q < TQ; ++q) {
-                B0[q] = *reinterpret_cast<const float4 *>(&sB[n * PLANE + q * QS + lane * 4]);
-                B1[q] = *reinterpret_cast<const float4 *>(&sB[(n + 1) * PLANE + q * QS + lane * 4]);
-            }
-            const ACoef ac0 = make_acoef<DISC>(readlane(Av, n)), ac1 = make_acoef<DISC>(readlane(Av, n + 1));
-            const float xc0 = readlane(xcv, n), xc1 = readlane(xcv, n + 1);
-            float a0[T], b0[T], a1[T], b1[T];
-            float P0 = 1.0f, S0 = 0.0f, P1 = 1.0f, S1 = 0.0f;
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const float Bt0 = reinterpret_cast<const float *>(&B0[t / 4])[t % 4];
-                const float Bt1 = reinterpret_cast<const float *>(&B1[t / 4])[t % 4];
-                float g0, g1;
-                disc_ag<DISC>(dl[t], ac0, a0[t], g0);
-                disc_ag<DISC>(dl[t], ac1, a1[t], g1);
-                if constexpr (DISC == DISC_ZOH_S6) { b0[t] = du[t] * Bt0; b1[t] = du[t] * Bt1; }
-                else if constexpr (DISC == DISC_DIRAC) { b0[t] = uv[t] * Bt0; b1[t] = uv[t] * Bt1; }
-                else { b0[t] = g0 * uv[t] * Bt0; b1[t] = g1 * uv[t] * Bt1; }
-                S0 = (t == 0) ? b0[0] : __builtin_fmaf(a0[t], S0, b0[t]);   // the folds start from zero
-                S1 = (t == 0) ? b1[0] : __builtin_fmaf(a1[t], S1, b1[t]);
-                if constexpr (DISC == DISC_BILINEAR) { P0 *= a0[t]; P1 *= a1[t]; }
-            }
-            float4 C0[TQ], C1[TQ];
-            if constexpr (WANT_Y) {
-#pragma unroll
-                for (int q = 0; q < TQ; ++q) {
-                    C0[q] = *reinterpret_cast<const float4 *>(&sC[n * PLANE + q * QS + lane * 4]);
-                    C1[q] = *reinterpret_cast<const float4 *>(&sC[(n + 1) * PLANE + q * QS + lane * 4]);
-                }
-            }
-            if constexpr (DISC != DISC_BILINEAR) {                   // product of the T multipliers
-                P0 = exp2_fast(sum_dl * ac0.A2);
-                P1 = exp2_fast(sum_dl * ac1.A2);
-            }
-            if (lane == 0) {                                         // the carried states enter through lane 0
-                S0 = __builtin_fmaf(P0, xc0, S0);
-                S1 = __builtin_fmaf(P1, xc1, S1);
-            }
-            wave_scan_fwd2(P0, S0, P1, S1);
-            float x0 = dpp<DPP_WAVE_SHR1>(xc0, S0);                  // states entering this lane's first step
-            float x1 = dpp<DPP_WAVE_SHR1>(xc1, S1);
-            if constexpr (CKPT) {
-                if (ck_lane && ll < L) {
-                    float *ck = p.ckpt + (ck0 + ll / kCkptInterval) * N + n;
-                    ck[0] = x0; ck[1] = x1;
-                }
-            }
-            if constexpr (!WANT_Y) {
-                xcv = writelane(xcv, readlane(S0, 63), n);           // inclusive prefix at lane 63 = state after the tile
-                xcv = writelane(xcv, readlane(S1, 63), n + 1);
-                pcv = writelane(pcv, readlane(pcv, n) * readlane(P0, 63), n);
-                pcv = writelane(pcv, readlane(pcv, n + 1) * readlane(P1, 63), n + 1);
-            } else {
-#pragma unroll
-                for (int t = 0; t < T; ++t) {
-                    const float Ct0 = reinterpret_cast<const float *>(&C0[t / 4])[t % 4];
-                    const float Ct1 = reinterpret_cast<const float *>(&C1[t / 4])[t % 4];
-                    x0 = __builtin_fmaf(a0[t], x0, b0[t]);
-                    x1 = __builtin_fmaf(a1[t], x1, b1[t]);
-                    yv[t] = __builtin_fmaf(Ct0, x0, yv[t]);
-                    yv[t] = __builtin_fmaf(Ct1, x1, yv[t]);
-                }
-                xcv = writelane(xcv, readlane(x0, 63), n);           // lane 63 ends on the tile's last step
-                xcv = writelane(xcv, readlane(x1, 63), n + 1);
-            }
-        };
-        if constexpr (N == 1) {
-            float4 Bq0[TQ], Bq1[TQ];
-#pragma unroll
-            for (int q = 0; q < TQ; ++q) Bq0[q] = *reinterpret_cast<const float4 *>(&sB[q * QS + lane * 4]);
-            one_state(0, Bq0, Bq1);
-        } else {
-            static_assert(N == 1 || N % 2 == 0, "states are processed in pairs");
+                    for (int q = 0; q < T / 4; ++q) {
+                        const float4 f = *reinterpret_cast<const float4 *>(m + q * GE::Q);
+                        v[4 * q] = f.x; v[4 * q + 1] = f.y; v[4 * q + 2] = f.z; v[4 * q + 3] = f.w;
+                    }
+                };
+                const float *lB = &sBC[0][li * 4], *lA = &sA[ch][h * NS];
+                const float *lX = &sX[li == 0 ? ch : CH][h * NS];    // the carried state enters through the channel's first lane
+                float Bt[T], Ct[T], An = lA[0], xn = lX[0];
+                read(lB, Bt);
 #pragma unroll 1
-            for (int n = 0; n < N; n += 2) two_states(n);
-        }
-
-        if constexpr (WANT_Y) {
-            if (zrow) {
-                float zv[T];
-                unpack_few<IO, T>(c_z, zv);
+                for (int n = 0; n < NS; ++n) {
+                    const ACoef ac = make_acoef<DISC>(An);
+                    float xin = xn;
+                    auto next_n = [&]() {                // (after the last n: one row further, not used)
+                        An = lA[n + 1]; xn = lX[n + 1]; read(lB + (n + 1) * GE::ROW, Bt);
+                    };
+                    float a[T], x[T], P, S;
+                    if constexpr (WANT_Y) read(lB + (NS + n) * GE::ROW, Ct);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int t = 0; t < T; ++t) yv[t] *= zv[t] * sigmoid_fast(zv[t]);
-            }
-            if constexpr (T % io_traits<IO>::EPC == 0) {
-                if (vec && rem == TILE) store_seg<IO, T>(yrow + ll, 0, T, true, yv);   // whole tile inside the sequence
-                else store_seg<IO, T>(yrow, ll, L, vec, yv);
-            } else {                                                             // less than a 16-byte chunk per lane
-                store_few<IO, T>(yrow, ll, L, vec, yv);
+                    for (int t = 0; t < T; ++t) {
+                        if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) x[t] = du[t] * Bt[t];
+                        else x[t] = Bt[t];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) next_n();
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int t = 0; t < T; ++t) {
+                        float g;
+                        disc_ag<DISC>(dl[t], ac, a[t], g);
+                        if constexpr (DISC != DISC_ZOH_S6 && DISC != DISC_DIRAC) x[t] *= g * du[t];
+                    }
+                    if constexpr (DISC != DISC_ZOH_S6 && DISC != DISC_DIRAC) next_n();
+                    S = __builtin_fmaf(a[0], xin, x[0]);
+#pragma unroll
+                    for (int t = 1; t < T; ++t) S = __builtin_fmaf(a[t], S, x[t]);
+                    if constexpr (DISC == DISC_BILINEAR) {
+                        P = a[0];
+#pragma unroll
+                        for (int t = 1; t < T; ++t) P *= a[t];
+                    } else P = exp2_fast(sum_dl * ac.A2);            // product of the T multipliers
+                    channel_scan<LPC, AGG>(P, S, xin);
+                    if constexpr (CKPT && TILE != kCkptInterval) {
+                        const int64_t ll = l0 + li * T;
+                        if (li % ((int)kCkptInterval / T) == 0 && live && ll < L) {
+                            const int64_t r = p.cu ? (int64_t)d : (int64_t)b * p.D + d;
+                            p.ckpt[(r * nck + ck_first + ll / kCkptInterval) * N + h * NS + n] = xin;
+                        }
+                    }
+                    if constexpr (WANT_Y) {
+#pragma unroll
+                        for (int t = 0; t < T; ++t) {
+                            xin = __builtin_fmaf(a[t], xin, x[t]);
+                            yv[t] = __builtin_fmaf(Ct[t], xin, yv[t]);
+                        }
+                    }
+                    if (li == LPC - 1) {                 // the channel's last lane ends on the tile's last step
+                        sX[ch][h * NS + n] = WANT_Y ? xin : S;
+                        if constexpr (AGG) sP[ch][h * NS + n] *= P;
+                    }
+                }
+                if (LATE_Z && h + 1 == NH) fetch_z();
+                if constexpr (!EARLY) fetch_next(std::true_type{});
+            } else fetch_next(std::false_type{});
+        }
+        if constexpr (WANT_Y) {
+            if (busy) {
+                if (p.z) {
+                    float zv[T];
+                    unpack_few<IO, T>(r_z, zv);
+#pragma unroll
+                    for (int t = 0; t < T; ++t) yv[t] *= zv[t] * sigmoid_fast(zv[t]);
+                }
+                if (live) {
+                    IO *y = const_cast<IO *>(row(p.y, p.y_sb, p.y_sd, l0));
+                    const int r = (fresh() % LPC) * T;
+                    if constexpr (T == 4) store_few<IO, T>(y, r, rem, FULL || vec, yv);
+                    else if constexpr (FULL) store_seg<IO, T>(y + r, 0, T, true, yv);
+                    else store_seg<IO, T>(y, r, rem, vec, yv);
+                }
             }
         }
+    };
+    const int64_t whole = vec ? L / TILE : 0, tilef = whole < tile0 ? tile0 : (whole < tile1 ? whole : tile1);
+    int64_t tile = tile0;
+    if (tile < tilef) {
+        fetch_maps(tile, 0, std::true_type{});
+        if (busy) fetch_rows(tile, std::true_type{});
+        for (; tile < tilef; ++tile) do_tile(tile, std::true_type{}, tile + 1 < tilef);
+    }
+    for (; tile < tile1; ++tile) {                   // the rest of the sequence (all of it without vector access)
+        fetch_maps(tile, 0, std::false_type{});
+        if (busy) fetch_rows(tile, std::false_type{});
+        do_tile(tile, std::false_type{}, false);
     }
 
-    if (active && lane < N) {
-        if (mode == MODE_AGG) {
-            p.ws_P[(row * p.nchunks + chunk) * N + lane] = pcv;
-            p.ws_S[(row * p.nchunks + chunk) * N + lane] = xcv;
-        } else if (p.x_last && tile1 == ntiles) {
-            p.x_last[row * N + lane] = xcv;
+    // every wavefront wrote the end states of its own channels
+    if (busy)
+        for (int i = lane; i < CPW * N; i += 64) {
+            const int c = w * CPW + i / N, n = i % N;
+            if (din0 + c >= p.dpg) continue;
+            const int64_t r = (int64_t)b * p.D + d0 + c;
+            if constexpr (AGG) {
+                p.ws_P[(r * p.nchunks + chunk) * N + n] = sP[c][n];
+                p.ws_S[(r * p.nchunks + chunk) * N + n] = sX[c][n];
+            } else if (p.x_last && tile1 == ntiles) {
+                p.x_last[r * N + n] = sX[c][n];
+            }
         }
-    }
 }
+
+// ---------------------------------------------------------------- launchers
+// The shape of a single pass, by the time each would take (in tenths of a microsecond, N = 16; other N scale all three
+// alike).  A tile costs its fixed part (staging, barriers, the latency of a wavefront that is alone on its SIMD) and a
+// part for each workgroup that shares the compute unit; measured over 64 to 40960 rows of 256 to 65536 steps.
+//   16 lanes: the fewest instructions, the finest tiles; needs about 8000 rows for three workgroups a compute unit.
+//             (8 x 1536 rows, L = 2048, N = 16, bf16: 112 us; 64 x 8: 125, 64 x 16: 144)
+//   64 x 8:   four times the wavefronts from as many rows (3 x 1000 rows, L = 2048: 46 us; 16 lanes: 57)
+//   64 x 16:  one workgroup a compute unit (its tile takes the LDS), so at most 2048 rows at once, but fewer instructions
+//             than 64 x 8 (2048 rows, L = 65536: 645 to 670 us; 64 x 8: 730)
+// For float32 and N <= 4 memory is the bound, and 16 lanes, which fetch later, do not keep enough of it in flight
+// (16 x 2048 rows, L = 1024, N = 4: 106 us; 64 x 8: 87).
+enum class FwdShape { l16, l64x4, l64x8, l64x16 };
+static FwdShape fwd_shape(const FwdParams &p, bool memory_bound) {
+    auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    const int64_t L = p.L, maps = (int64_t)p.B * p.bcg;
+    const int64_t cu16 = up(maps * up(p.dpg, 16), kNumCU), cu8 = up(maps * up(p.dpg, 8), kNumCU);   // workgroups of a compute unit
+    const int64_t t16 = up(L, 256) * (33 + 36 * cu16) * (memory_bound ? 4 : 3) / 3;
+    const int64_t t8 = up(L, 512) * (15 + 50 * cu8);
+    const int64_t t64 = up(L, 1024) * 120 * cu8;
+    if (t16 <= t8 && t16 <= t64) return FwdShape::l16;
+    return t64 < t8 ? FwdShape::l64x16 : FwdShape::l64x8;
+}
+// The shape for a packed batch, whose lengths only the device knows: as a rule 64 lanes of 4 steps, whose tiles of 256
+// steps spend little past the ends of short sequences while a long one does not run on alone for long (31 sequences of 705
+// steps on average, 522 channels, N = 8, bf16: 95 us; 16 lanes 122, 64 x 8 102).  With so many rows that the chip
+// stays full, 16 lanes, which take fewer instructions: from 24576 rows (24 sequences, 1536 channels, N = 16, bf16: 141 us,
+// 64 x 4: 195), of sequences of hardly a tile from 12288 (17 of 206 steps on average, 1068 channels: 38 us, 54), in
+// float32 from 8192 (6 sequences, 1616 channels, N = 32: 75 us, 110).  Long sequences take the longer tiles: 64 x 8 (5 of 3056 steps
+// on average, 1724 channels: 173 us, 64 x 4: 188), very few rows of very long ones 64 x 16 (2 sequences of up to
+// 23848 steps, 363 channels: 152 us, 64 x 4: 186).
+static FwdShape packed_shape(const FwdParams &p, bool f32) {
+    const int64_t rows = (int64_t)p.B * p.D, mean = p.L / p.B;
+    if (rows >= (f32 ? 8192 : mean <= 256 ? 12288 : 24576)) return FwdShape::l16;
+    if (rows <= 1024 && mean >= 4096) return FwdShape::l64x16;
+    return rows >= 2048 && mean >= 2048 ? FwdShape::l64x8 : FwdShape::l64x4;
+}
+
+template <typename IO, int N, int DISC, int LPC, int T>
+static hipError_t launch_fwd_lanes(FwdParams p, hipStream_t s) {
+    using GE = FwdGeom<LPC, T>;
+    // tiles_per_chunk counts tiles of 256 steps; a single pass is one chunk whatever the tile
+    if (p.nchunks == 1) p.tiles_per_chunk = (p.L + GE::TILE - 1) / GE::TILE;
+    dim3 grid(p.bcg * ((p.dpg + GE::CH - 1) / GE::CH), p.B, p.mode == MODE_AGG ? p.nchunks - 1 : p.nchunks);
+    const bool want_y = (p.mode == MODE_FULL || p.mode == MODE_APPLY);
+    const dim3 block(GE::W * 64);
+    if (want_y && p.ckpt) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, true, true, LPC, T>), grid, block, 0, s, p);
+    else if (want_y) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, true, false, LPC, T>), grid, block, 0, s, p);
+    else if (p.ckpt) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, false, true, LPC, T>), grid, block, 0, s, p);
+    else if constexpr (LPC == 16) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, false, false, LPC, T>), grid, block, 0, s, p);
+    else return hipErrorInvalidValue;                    // the chunk-carry path takes 16 lanes per channel
+    return hipGetLastError();
+}
+
+template <typename IO, int N, int DISC>
+static hipError_t launch_fwd_n(const FwdParams &p, hipStream_t s) {
+    // the aggregate launch skips the last chunk: nobody needs its pair
+    if (p.mode == MODE_AGG && p.nchunks < 2) return hipSuccess;
+    switch (p.cu ? packed_shape(p, sizeof(IO) == 4) : p.nchunks == 1 ? fwd_shape(p, sizeof(IO) == 4 && N <= 4) : FwdShape::l16) {
+        case FwdShape::l64x4: return launch_fwd_lanes<IO, N, DISC, 64, 4>(p, s);
+        case FwdShape::l64x8: return launch_fwd_lanes<IO, N, DISC, 64, 8>(p, s);
+        case FwdShape::l64x16: return launch_fwd_lanes<IO, N, DISC, 64, 16>(p, s);
+        default: break;
+    }
+    return launch_fwd_lanes<IO, N, DISC, 16, 16>(p, s);
+}
+
+template <typename IO, int DISC>
+static hipError_t launch_fwd_disc(const FwdParams &p, hipStream_t s) {
+    switch (p.N) {
+        case 1: return launch_fwd_n<IO, 1, DISC>(p, s);
+        case 2: return launch_fwd_n<IO, 2, DISC>(p, s);
+        case 4: return launch_fwd_n<IO, 4, DISC>(p, s);
+        case 8: return launch_fwd_n<IO, 8, DISC>(p, s);
+        case 16: return launch_fwd_n<IO, 16, DISC>(p, s);
+        case 32: return launch_fwd_n<IO, 32, DISC>(p, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <typename IO>
+static hipError_t launch_fwd_io(const FwdParams &p, int disc, hipStream_t s) {
+    switch (disc) {
+        case DISC_ZOH_S6: return launch_fwd_disc<IO, DISC_ZOH_S6>(p, s);
+        case DISC_ZOH: return launch_fwd_disc<IO, DISC_ZOH>(p, s);
+        case DISC_BILINEAR: return launch_fwd_disc<IO, DISC_BILINEAR>(p, s);
+        case DISC_DIRAC: return launch_fwd_disc<IO, DISC_DIRAC>(p, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+// float32 and bfloat16 are compiled side by side: selective_fwd_f32.hip includes this file for the former.
+hipError_t launch_ss_fwd_f32(const FwdParams &p, int disc, hipStream_t s);
+#ifdef LRNNX_FWD_F32
+hipError_t launch_ss_fwd_f32(const FwdParams &p, int disc, hipStream_t s) { return launch_fwd_io<float>(p, disc, s); }
+#else
+hipError_t launch_ss_fwd(const FwdParams &p, int io_dtype, int disc, hipStream_t s) {
+    return io_dtype == 1 ? launch_fwd_io<bf16_t>(p, disc, s) : launch_ss_fwd_f32(p, disc, s);
+}
+
+int fwd_channels_per_workgroup() { return FwdGeom<16, 16>::CH; }
+int fwd_tile_steps() { return FwdGeom<16, 16>::TILE; }
+
 
 // Chains the chunk aggregates of one (b,d,n): carry-in of chunk c+1 = P_c * carry-in of chunk c + S_c.
 // ws_S[c] is replaced by the carry-in of chunk c.
@@ -374,84 +511,6 @@ __global__ void k_fill(const FillList z) {
     }
 }
 
-// ---------------------------------------------------------------- launchers
-constexpr int kFwdT = 8;
-constexpr int kFwdW = 8;
-
-int fwd_tile_steps(int) { return 64 * kFwdT; }
-int fwd_channels_per_workgroup() { return kFwdW; }
-
-// Short tiles: the single pass can also run with 4 steps per lane and 4 channels per workgroup (tiles of 256 steps).
-// A tile is walked whole whether its steps are real or past the end of the sequence, so short rows and packed
-// batches of short sequences waste fewer steps on the smaller tile, which costs about 25 % more per real step (the
-// 64-lane prefix is shared by 4 steps instead of 8, the staged maps by 4 channels instead of 8; measured 2.6e12
-// against 3.3e12 elements/s on full tiles).  Batch [B,D,L]: taken when the steps walked shrink by more than that
-// (L <= 256: twice the rate; 512 < L <= 768: 9 % faster); packed batch: the lengths are on the device, so by the
-// mean length (a sequence wastes half a tile on average: the smaller tile pays below about 360 steps per sequence).
-constexpr int kFwdShortT = 4;
-constexpr int kFwdShortW = 4;
-static bool fwd_short_tiles(const FwdParams &p) {
-    if (p.nchunks != 1 || (p.mode != MODE_FULL && p.mode != MODE_CKPT_ONLY)) return false;
-    if (p.cu) return p.L < (int64_t)360 * p.B;
-    const int64_t s8 = 64 * kFwdT, s4 = 64 * kFwdShortT;
-    const int64_t walked8 = (p.L + s8 - 1) / s8 * s8, walked4 = (p.L + s4 - 1) / s4 * s4;
-    return walked4 * 125 < walked8 * 100;
-}
-
-template <typename IO, int N, int DISC>
-static hipError_t launch_fwd_short(FwdParams p, hipStream_t s) {
-    p.tiles_per_chunk = (p.L + 64 * kFwdShortT - 1) / (64 * kFwdShortT);          // one chunk: every tile of the row
-    dim3 grid(p.bcg * ((p.dpg + kFwdShortW - 1) / kFwdShortW), p.B, 1);
-    const dim3 block(kFwdShortW * 64);
-    if (p.mode == MODE_CKPT_ONLY) hipLaunchKernelGGL((k_ss_fwd<IO, N, kFwdShortT, kFwdShortW, DISC, false, true>), grid, block, 0, s, p);
-    else if (p.ckpt) hipLaunchKernelGGL((k_ss_fwd<IO, N, kFwdShortT, kFwdShortW, DISC, true, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((k_ss_fwd<IO, N, kFwdShortT, kFwdShortW, DISC, true, false>), grid, block, 0, s, p);
-    return hipGetLastError();
-}
-
-template <typename IO, int N, int DISC>
-static hipError_t launch_fwd_n(const FwdParams &p, hipStream_t s) {
-    // the aggregate launch skips the last chunk: nobody needs its pair
-    if (p.mode == MODE_AGG && p.nchunks < 2) return hipSuccess;
-    if (fwd_short_tiles(p)) return launch_fwd_short<IO, N, DISC>(p, s);
-    dim3 grid(p.bcg * ((p.dpg + kFwdW - 1) / kFwdW), p.B, p.mode == MODE_AGG ? p.nchunks - 1 : p.nchunks);
-    const bool want_y = (p.mode == MODE_FULL || p.mode == MODE_APPLY);
-    const dim3 block(kFwdW * 64);
-    if (want_y && p.ckpt) hipLaunchKernelGGL((k_ss_fwd<IO, N, kFwdT, kFwdW, DISC, true, true>), grid, block, 0, s, p);
-    else if (want_y) hipLaunchKernelGGL((k_ss_fwd<IO, N, kFwdT, kFwdW, DISC, true, false>), grid, block, 0, s, p);
-    else if (p.ckpt) hipLaunchKernelGGL((k_ss_fwd<IO, N, kFwdT, kFwdW, DISC, false, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((k_ss_fwd<IO, N, kFwdT, kFwdW, DISC, false, false>), grid, block, 0, s, p);
-    return hipGetLastError();
-}
-
-template <typename IO, int DISC>
-static hipError_t launch_fwd_disc(const FwdParams &p, hipStream_t s) {
-    switch (p.N) {
-        case 1: return launch_fwd_n<IO, 1, DISC>(p, s);
-        case 2: return launch_fwd_n<IO, 2, DISC>(p, s);
-        case 4: return launch_fwd_n<IO, 4, DISC>(p, s);
-        case 8: return launch_fwd_n<IO, 8, DISC>(p, s);
-        case 16: return launch_fwd_n<IO, 16, DISC>(p, s);
-        case 32: return launch_fwd_n<IO, 32, DISC>(p, s);
-    }
-    return hipErrorInvalidValue;
-}
-
-template <typename IO>
-static hipError_t launch_fwd_io(const FwdParams &p, int disc, hipStream_t s) {
-    switch (disc) {
-        case DISC_ZOH_S6: return launch_fwd_disc<IO, DISC_ZOH_S6>(p, s);
-        case DISC_ZOH: return launch_fwd_disc<IO, DISC_ZOH>(p, s);
-        case DISC_BILINEAR: return launch_fwd_disc<IO, DISC_BILINEAR>(p, s);
-        case DISC_DIRAC: return launch_fwd_disc<IO, DISC_DIRAC>(p, s);
-    }
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_ss_fwd(const FwdParams &p, int io_dtype, int disc, hipStream_t s) {
-    return io_dtype == 1 ? launch_fwd_io<bf16_t>(p, disc, s) : launch_fwd_io<float>(p, disc, s);
-}
-
 hipError_t launch_ss_carry(const FwdParams &p, hipStream_t s) {
     const int64_t total = (int64_t)p.B * p.D * p.N;
     hipLaunchKernelGGL(k_ss_carry, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, p);
@@ -467,5 +526,6 @@ hipError_t launch_fill(const FillList &z, hipStream_t s) {
     hipLaunchKernelGGL(k_fill, dim3((unsigned)blocks), dim3(256), 0, s, z);
     return hipGetLastError();
 }
+#endif
 
 }  // namespace lrnnx
