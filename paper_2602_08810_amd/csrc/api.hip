@@ -152,12 +152,13 @@ void fit_chunks(BwdPlan &pl, size_t nfit) {
 }
 
 // Scratch for the tile sums of dBm and dCm of a real backward call (LRNNX_WS_BWD_SUMS): what the widest launch the host may choose
-// for this shape takes, capped for packed batches, whose channels per workgroup depend on the longest sequence.
+// for this shape takes.  For packed batches, whose channels per workgroup depend on the longest sequence, that is the fewest
+// a workgroup may take, or kBwdPackedSumG if this would pass half a GiB (the launch then takes no fewer).
 size_t bwd_sums_bytes(int64_t B, int64_t D, int64_t N, int64_t L, int64_t bcg, bool packed) {
     const int64_t dpg = D / bcg;
     if (packed) {
-        const int64_t G = dpg < kBwdPackedSumG ? dpg : kBwdPackedSumG;
-        return bwd_part_bytes((int)N, lrnnx_packed_ckpt_slots(L, B), bcg * cdiv(dpg, G));
+        auto bytes = [&](int64_t G) { return bwd_part_bytes((int)N, lrnnx_packed_ckpt_slots(L, B), bcg * cdiv(dpg, dpg < G ? dpg : G)); };
+        return bytes(kBwdMinG) <= (size_t)512 << 20 ? bytes(kBwdMinG) : bytes(kBwdPackedSumG);
     }
     size_t most = 0;
     for (int path = LRNNX_PATH_AUTO; path <= LRNNX_PATH_CHUNK_CARRY; ++path) {
@@ -601,12 +602,19 @@ int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
         p.order = order;
         used = carry_off + sizeof(int) * (size_t)a->B;
     }
-    // room behind that for the tile sums of dBm and dCm 
+    // room behind that for the tile sums of dBm and dCm (with fewer workgroups to a long packed sequence if need be)
     const int64_t slots = cu ? nslots : a->B * nck;
     p.part_tiles = nck;
     const uintptr_t part = align256(reinterpret_cast<uintptr_t>(a->workspace) + used);
-    if (a->workspace && part + bwd_part_bytes(a->N, slots, bwd_grid_x(p)) <= reinterpret_cast<uintptr_t>(a->workspace) + a->workspace_bytes)
-        p.part = reinterpret_cast<float *>(part);
+    const uintptr_t end = reinterpret_cast<uintptr_t>(a->workspace) + a->workspace_bytes;
+    auto fits = [&]() { return part + bwd_part_bytes(a->N, slots, bwd_grid_x(p)) <= end; };
+    if (a->workspace) {
+        const int gmin = p.gmin;
+        if (cu && p.wcap > 0)
+            while (!fits() && p.gmin < p.G) p.gmin = p.gmin + 2 < p.G ? p.gmin + 2 : p.G;
+        if (fits()) p.part = reinterpret_cast<float *>(part);
+        else p.gmin = gmin;
+    }
 
     // reduced outputs that are accumulated with atomics: clear them on the stream first (dBm and dCm of a packed batch in
     // any case: rows outside every sequence are zero)

@@ -136,10 +136,10 @@ __device__ __forceinline__ void seq_bounds(const int64_t *cu, int b, int64_t Lp,
 __device__ __forceinline__ int channels_of(const BwdParams &p, int64_t ntiles) {
     if (p.wcap <= 0) return p.G;
     const int64_t fit = p.wcap / (ntiles > 0 ? ntiles : 1);
-    return fit < p.gmin ? p.gmin : (fit < p.G ? (int)fit : p.G);
+    return fit < p.gmin ? p.gmin : (fit < p.G ? (int)fit & ~1 : p.G);      // (channels are walked in pairs)
 }
 
-template <typename IO, int N, int DISC, bool HAS_Z>
+template <typename IO, int N, int DISC, bool HAS_Z, bool PART>
 __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p) {
     using GE = BwdGeom<N>;
     constexpr int W = GE::W, NS = GE::NS, NT = GE::NT, CP = GE::CP, TPT = GE::TPT, NTC = GE::NTC;
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
             finish(g, t0, f0, e_in[0], e_in[1], e_in[2], s_yp, s_du, s_dd);
         };
         // ---- main: this lane's 8 steps of its channel, one state after the other
-        auto states = [&](const int g, const int buf, const unsigned ln, const float (&dl)[T], float (&du)[T], const float (&dy)[T],
+        auto states = [&](const int g, const int buf, const unsigned ln, float (&dl)[T], float (&du)[T], const float (&dy)[T],
                           float (&yp)[T], float (&pu)[T], float (&pd)[T]) {
                 const unsigned c = ln >> 5;
                 const int ch = g + (int)c < Gact ? g + (int)c : g;             // (the half past the last channel repeats the first, unused)
@@ -445,6 +445,8 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                     float a[T], x[T], gg[T];
 #pragma unroll
                     for (int t = 0; t < T; ++t) {
+                        // (an own copy for each state: multiples and powers of Delta are not kept in registers for the next)
+                        if constexpr (DISC == DISC_ZOH || DISC == DISC_BILINEAR) asm volatile("" : "+v"(dl[t]));
                         disc_ag<DISC>(dl[t], ac, a[t], gg[t]);
                         if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) x[t] = du[t] * Bv[s][t];
                         else x[t] = gg[t] * du[t] * Bv[s][t];
@@ -461,17 +463,22 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                     half_scans(P, S, Q, xin, Gin);
                     if (own && (ln & 31) == 0) sH[at + s] = Q;       // carried to the earlier tile
                     // replay of the states (earliest step first) and of the adjoint (last step first), side by side: two chains
-                    // whose instructions fill each other's result latencies
+                    // whose instructions fill each other's result latencies.  zoh and bilinear, which need more registers and
+                    // have more instructions a step to fill them with, take the adjoint step by step below instead (side by
+                    // side zoh spilled 50 registers).
+                    constexpr bool APART = DISC == DISC_ZOH || DISC == DISC_BILINEAR;
                     float R[T], G[T];
                     {
                         float xp = xin;
 #pragma unroll
                         for (int t = 0; t < T; ++t) {
                             const int r = T - 1 - t;
-                            R[r] = __builtin_fmaf(Cv[s][r], dy[r], Gin);                 // H_r
+                            if constexpr (!APART) R[r] = __builtin_fmaf(Cv[s][r], dy[r], Gin);                 // H_r
                             xp = __builtin_fmaf(a[t], xp, x[t]); x[t] = xp;
-                            Gin = a[r] * R[r];                                           // a_r H_r
-                            G[r] = Gin;
+                            if constexpr (!APART) {
+                                Gin = a[r] * R[r];                                       // a_r H_r
+                                G[r] = Gin;
+                            }
                         }
                     }
                     auto acc = [&](float &sum, float m1, float m2) { sum = (s == 0) ? m1 * m2 : __builtin_fmaf(m1, m2, sum); };
@@ -479,6 +486,11 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
 #pragma unroll
                     for (int t = T - 1; t >= 0; --t) {
                         const float xprev = t > 0 ? x[t - 1] : xin;
+                        if constexpr (APART) {
+                            asm volatile("" : "+v"(dl[t]));
+                            R[t] = __builtin_fmaf(Cv[s][t], dy[t], Gin);
+                            Gin = a[t] * R[t];
+                        }
                         dC[s][t] = __builtin_fmaf(dy[t], x[t], dC[s][t]);
                         if constexpr (HAS_Z) acc(yp[t], Cv[s][t], x[t]);
                         if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) {
@@ -495,7 +507,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                             disc_partials<DISC>(dl[t], ac, a[t], gg[t], a_t, a_A, g_t, g_A);
                             const float hb = R[t] * Bv[s][t];
                             const float dg = hb * du[t];
-                            const float q = G[t] * xprev;
+                            const float q = Gin * xprev;
                             acc(pu[t], hb, gg[t]);
                             dB[s][t] = __builtin_fmaf(R[t] * gg[t], du[t], dB[s][t]);
                             if (s == 0) pd[t] = __builtin_fmaf(q, ac.A, dg * a[t]);
@@ -625,7 +637,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 oB[s][t] = i2f((int)r[0]) + i2f((int)r[1]);
                 oC[s][t] = i2f((int)q[0]) + i2f((int)q[1]);
             }
-        if (p.part) {
+        if constexpr (PART) {
             // to this workgroup's own slot of the workspace, as 16-byte pieces in the order the lanes hold them (the sum
             // over workgroups and the transposition to [L,N] are k_ss_bwd_maps's)
             float *pt = p.part + (((slot0 + tile_first + tile) * gridDim.x + blockIdx.x) * 2 * N + n0) * TILE + lane * 4;
@@ -635,18 +647,34 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 *reinterpret_cast<float4 *>(pt + (N + s) * TILE) = make_float4(oC[s][0], oC[s][1], oC[s][2], oC[s][3]);
             }
         } else {
-            // without a workspace: float atomics
-            float *gB = p.dBm + bc0 + l0 * N + n0, *gC = p.dCm + bc0 + l0 * N + n0;
+            // without a workspace: float atomics, on consecutive addresses (the sums change their order in LDS: lanes that add
+            // 8 steps apart take a transaction each, 8 times as long)
+            const unsigned t0 = fresh(tid), st0 = (t0 & 31) * T + (t0 >> 5 & 1) * 4;
+            if constexpr (OWN) {
+                float *gB = p.dBm + bc0 + l0 * N, *gC = p.dCm + bc0 + l0 * N;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int st = li * T + half * 4 + t;
-                if (st < rem) {
+                for (int t = 0; t < 4; ++t)
+                    if ((int)st0 + t < rem) {
 #pragma unroll
-                    for (int s = 0; s < NS; ++s) {
-                        unsafeAtomicAdd(gB + st * N + s, oB[s][t]);
-                        unsafeAtomicAdd(gC + st * N + s, oC[s][t]);
+                        for (int s = 0; s < NS; ++s) {
+                            unsafeAtomicAdd(gB + (st0 + t) * N + s, oB[s][t]);
+                            unsafeAtomicAdd(gC + (st0 + t) * N + s, oC[s][t]);
+                        }
                     }
-                }
+            } else {
+                static_assert(OWN || N <= NB * CP * W * 3, "one map's sums in the partial sums' place");
+                float *buf = &sPart[0][0][0][0][0];
+                auto flush = [&](float (&o)[NS][4], float *g) {
+                    __syncthreads();
+#pragma unroll
+                    for (int s = 0; s < NS; ++s)
+                        *reinterpret_cast<float4 *>(buf + (n0 + s) * TILE + st0) = make_float4(o[s][0], o[s][1], o[s][2], o[s][3]);
+                    __syncthreads();
+#pragma unroll 1
+                    for (int i = t0; i < rem * N; i += NT) unsafeAtomicAdd(g + bc0 + l0 * N + i, buf[(i % N) * TILE + i / N]);
+                };
+                flush(oB, p.dBm);
+                flush(oC, p.dCm);
             }
         }
     };
@@ -731,6 +759,57 @@ __global__ __launch_bounds__(256) void k_ss_bwd_maps(const BwdParams p, int gx) 
 }
 
 // ---------------------------------------------------------------- launchers
+// HAS_Z (gated) is a template parameter: without it the kernel does not rebuild ypre = sum_n C x for dz.  So is whether the
+// tile sums go to the workspace: the code that adds them with atomics instead would cost the other kernel registers.
+template <typename IO, int N, int DISC>
+static hipError_t launch_bwd_n(const BwdParams &p, hipStream_t s) {
+    dim3 grid(bwd_grid_x(p), p.B, p.nchunks > 1 ? p.nchunks : 1);
+    const dim3 block(BwdGeom<N>::NT);
+    if (p.part && p.z) hipLaunchKernelGGL((k_ss_bwd<IO, N, DISC, true, true>), grid, block, 0, s, p);
+    else if (p.part) hipLaunchKernelGGL((k_ss_bwd<IO, N, DISC, false, true>), grid, block, 0, s, p);
+    else if (p.z) hipLaunchKernelGGL((k_ss_bwd<IO, N, DISC, true, false>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((k_ss_bwd<IO, N, DISC, false, false>), grid, block, 0, s, p);
+    if (p.part) {
+        const int64_t slots = p.cu ? p.nslots : (int64_t)p.B * p.part_tiles;
+        dim3 g2((unsigned)(slots * (N >= 8 ? N / 4 : 1)), 2, p.bcg);
+        hipLaunchKernelGGL((k_ss_bwd_maps<N>), g2, dim3(256), 0, s, p, (int)grid.x);
+    }
+    return hipGetLastError();
+}
+
+template <typename IO, int DISC>
+static hipError_t launch_bwd_disc(const BwdParams &p, hipStream_t s) {
+    switch (p.N) {
+        case 1: return launch_bwd_n<IO, 1, DISC>(p, s);
+        case 2: return launch_bwd_n<IO, 2, DISC>(p, s);
+        case 4: return launch_bwd_n<IO, 4, DISC>(p, s);
+        case 8: return launch_bwd_n<IO, 8, DISC>(p, s);
+        case 16: return launch_bwd_n<IO, 16, DISC>(p, s);
+        case 32: return launch_bwd_n<IO, 32, DISC>(p, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <typename IO>
+static hipError_t launch_bwd_io(const BwdParams &p, int disc, hipStream_t s) {
+    switch (disc) {
+        case DISC_ZOH_S6: return launch_bwd_disc<IO, DISC_ZOH_S6>(p, s);
+        case DISC_ZOH: return launch_bwd_disc<IO, DISC_ZOH>(p, s);
+        case DISC_BILINEAR: return launch_bwd_disc<IO, DISC_BILINEAR>(p, s);
+        case DISC_DIRAC: return launch_bwd_disc<IO, DISC_DIRAC>(p, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+// float32 and bfloat16 are compiled side by side: selective_bwd_f32.hip includes this file for the former.
+hipError_t launch_ss_bwd_f32(const BwdParams &p, int disc, hipStream_t s);
+#ifdef LRNNX_BWD_F32
+hipError_t launch_ss_bwd_f32(const BwdParams &p, int disc, hipStream_t s) { return launch_bwd_io<float>(p, disc, s); }
+#else
+hipError_t launch_ss_bwd(const BwdParams &p, int io_dtype, int disc, hipStream_t s) {
+    return io_dtype == 1 ? launch_bwd_io<bf16_t>(p, disc, s) : launch_ss_bwd_f32(p, disc, s);
+}
+
 // Workgroups the chip holds at once: two wavefronts per SIMD are what the registers allow.
 int bwd_places(int N) { return 2048 / (N == 4 ? 2 : (N >= 4 ? N / 4 : 1)); }
 
@@ -776,7 +855,7 @@ void bwd_packed_shape(int B, int D, int64_t L, int64_t max_seqlen, int Gbal, int
     if (Gbal > *G && (double)Gbal <= 1.1 * fit) { *G = *gmin = Gbal; return; }
     if (fit >= (double)*G || *G <= kBwdMinG) return;    // the longest sequence is no longer than a fair share: no cap
     *wcap = cap < 1.0 ? 1 : (cap > 1e9 ? 1000000000 : (int)cap);
-    *gmin = fit < (double)kBwdMinG ? kBwdMinG : (int)fit;
+    *gmin = fit < (double)kBwdMinG ? kBwdMinG : (int)fit & ~1;
 }
 
 // launch shape incl. the chunked path for few rows and long sequences (selective_bwd_carry.hip)
@@ -794,47 +873,6 @@ int bwd_grid_x(const BwdParams &p) {
 size_t bwd_part_bytes(int N, int64_t tile_slots, int64_t grid_x) {
     return (size_t)tile_slots * grid_x * 2 * N * kBwdTileSteps * sizeof(float);
 }
-
-// HAS_Z (gated) is a template parameter: without it the kernel does not rebuild ypre = sum_n C x for dz
-template <typename IO, int N, int DISC>
-static hipError_t launch_bwd_n(const BwdParams &p, hipStream_t s) {
-    dim3 grid(bwd_grid_x(p), p.B, p.nchunks > 1 ? p.nchunks : 1);
-    if (p.z) hipLaunchKernelGGL((k_ss_bwd<IO, N, DISC, true>), grid, dim3(BwdGeom<N>::NT), 0, s, p);
-    else hipLaunchKernelGGL((k_ss_bwd<IO, N, DISC, false>), grid, dim3(BwdGeom<N>::NT), 0, s, p);
-    if (p.part) {
-        const int64_t slots = p.cu ? p.nslots : (int64_t)p.B * p.part_tiles;
-        dim3 g2((unsigned)(slots * (N >= 8 ? N / 4 : 1)), 2, p.bcg);
-        hipLaunchKernelGGL((k_ss_bwd_maps<N>), g2, dim3(256), 0, s, p, (int)grid.x);
-    }
-    return hipGetLastError();
-}
-
-template <typename IO, int DISC>
-static hipError_t launch_bwd_disc(const BwdParams &p, hipStream_t s) {
-    switch (p.N) {
-        case 1: return launch_bwd_n<IO, 1, DISC>(p, s);
-        case 2: return launch_bwd_n<IO, 2, DISC>(p, s);
-        case 4: return launch_bwd_n<IO, 4, DISC>(p, s);
-        case 8: return launch_bwd_n<IO, 8, DISC>(p, s);
-        case 16: return launch_bwd_n<IO, 16, DISC>(p, s);
-        case 32: return launch_bwd_n<IO, 32, DISC>(p, s);
-    }
-    return hipErrorInvalidValue;
-}
-
-template <typename IO>
-static hipError_t launch_bwd_io(const BwdParams &p, int disc, hipStream_t s) {
-    switch (disc) {
-        case DISC_ZOH_S6: return launch_bwd_disc<IO, DISC_ZOH_S6>(p, s);
-        case DISC_ZOH: return launch_bwd_disc<IO, DISC_ZOH>(p, s);
-        case DISC_BILINEAR: return launch_bwd_disc<IO, DISC_BILINEAR>(p, s);
-        case DISC_DIRAC: return launch_bwd_disc<IO, DISC_DIRAC>(p, s);
-    }
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_ss_bwd(const BwdParams &p, int io_dtype, int disc, hipStream_t s) {
-    return io_dtype == 1 ? launch_bwd_io<bf16_t>(p, disc, s) : launch_bwd_io<float>(p, disc, s);
-}
+#endif
 
 }  // namespace lrnnx
