@@ -9,7 +9,6 @@ using namespace lrnnx;
 
 namespace {
 
-
 inline bool supported_n(int n) { return n == 1 || n == 2 || n == 4 || n == 8 || n == 16 || n == 32; }
 inline bool supported_n_complex(int n) { return n <= 16 && supported_n(n); }   // complex-A entry points
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }

@@ -13,7 +13,6 @@
 
 namespace lrnnx {
 
-constexpr int kWave = 64;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -28,7 +27,6 @@ template <int CTRL, int ROW_MASK = 0xF>
 __device__ __forceinline__ float dpp(float old, float src) {
     return i2f(__builtin_amdgcn_update_dpp(f2i(old), f2i(src), CTRL, ROW_MASK, 0xF, false));
 }
-constexpr int DPP_ROW_SHL1 = 0x101, DPP_ROW_SHR1 = 0x111;
 constexpr int DPP_WAVE_SHL1 = 0x130, DPP_WAVE_SHR1 = 0x138;
 constexpr int DPP_ROW_BCAST15 = 0x142, DPP_ROW_BCAST31 = 0x143;
 
@@ -191,16 +189,6 @@ __device__ __forceinline__ void bwd_step_inputs(float s, float dy, float z, bool
         "v_mul_f32_dpp %1, %1, %1 " CTRL                                              \
         : "+v"(S), "+v"(P))
 
-// The same step on two independent pairs at once.  Each pair's instructions give the other pair the wait states its
-// next DPP read needs, so only the first step of a sequence carries the s_nop; the two dependent chains also fill
-// each other's issue gaps.
-#define LRNNX_PAIR_STEP2(NOP, P, S, CTRL, Q, R, CTRL2)                                \
-    asm(NOP "v_fmac_f32_dpp %0, %0, %1 " CTRL "\n\t"                                  \
-            "v_mul_f32_dpp %1, %1, %1 " CTRL "\n\t"                                   \
-            "v_fmac_f32_dpp %2, %2, %3 " CTRL2 "\n\t"                                 \
-            "v_mul_f32_dpp %3, %3, %3 " CTRL2                                         \
-        : "+v"(S), "+v"(P), "+v"(R), "+v"(Q))
-
 // Inclusive prefix over the 64 lanes, lane 0 first:  (P,S)_i <- (P,S)_i o ... o (P,S)_0.
 __device__ __forceinline__ void wave_scan_fwd(float &P, float &S) {
     LRNNX_PAIR_STEP(P, S, "row_shr:1 row_mask:0xf bank_mask:0xf");
@@ -211,180 +199,14 @@ __device__ __forceinline__ void wave_scan_fwd(float &P, float &S) {
     LRNNX_PAIR_STEP(P, S, "row_bcast:31 row_mask:0xc bank_mask:0xf");   // lane 31 -> rows 2,3
 }
 
-// Inclusive prefixes of two independent pairs at once (two states of one channel): see LRNNX_PAIR_STEP2.
-__device__ __forceinline__ void wave_scan_fwd2(float &P, float &S, float &Q, float &R) {
-    LRNNX_PAIR_STEP2("s_nop 1\n\t", P, S, "row_shr:1 row_mask:0xf bank_mask:0xf", Q, R, "row_shr:1 row_mask:0xf bank_mask:0xf");
-    LRNNX_PAIR_STEP2("", P, S, "row_shr:2 row_mask:0xf bank_mask:0xf", Q, R, "row_shr:2 row_mask:0xf bank_mask:0xf");
-    LRNNX_PAIR_STEP2("", P, S, "row_shr:4 row_mask:0xf bank_mask:0xf", Q, R, "row_shr:4 row_mask:0xf bank_mask:0xf");
-    LRNNX_PAIR_STEP2("", P, S, "row_shr:8 row_mask:0xf bank_mask:0xf", Q, R, "row_shr:8 row_mask:0xf bank_mask:0xf");
-    LRNNX_PAIR_STEP2("", P, S, "row_bcast:15 row_mask:0xa bank_mask:0xf", Q, R, "row_bcast:15 row_mask:0xa bank_mask:0xf");
-    LRNNX_PAIR_STEP2("", P, S, "row_bcast:31 row_mask:0xc bank_mask:0xf", Q, R, "row_bcast:31 row_mask:0xc bank_mask:0xf");
-}
-
-// ---------------------------------------------------------------- both scans of the backward pass, NK states at once
-// The state prefix (P,S) and the adjoint suffix (Pr,Sr) of each of NK states advance together, one Hillis-Steele
-// step of all 2 NK pairs per block of instructions.  The chains of different states are independent, so each fills
-// the others' wait states (no s_nop between DPP steps) and, above all, the one LDS round trip of the suffix scan
-// (the hand-over between rows: no DPP control moves data towards lower rows) is paid once per call instead of once
-// per state: all 2 NK lane permutes are in flight while the prefix scans take their two broadcast steps.
-// Hazards inside the blocks are kept by construction (a DPP read of a register comes at least three instructions
-// after its last write); every block starts with s_nop 1 in case the compiler placed a copy right before it.
-#define LRNNX_FR_STATE(s, p, r, q, CF, CR)                                             \
-    "v_fmac_f32_dpp %" #s ", %" #s ", %" #p " " CF "\n\t"                               \
-    "v_mul_f32_dpp %" #p ", %" #p ", %" #p " " CF "\n\t"                                \
-    "v_fmac_f32_dpp %" #r ", %" #r ", %" #q " " CR "\n\t"                               \
-    "v_mul_f32_dpp %" #q ", %" #q ", %" #q " " CR "\n\t"
+// Parts of a kernel's own blocks: one Hillis-Steele step of a prefix pair (s, p), and of a prefix pair together with a suffix
+// pair (r, q).  The numbers are operands of the block.  Whoever strings them together keeps two instructions between a
+// register's write and its next DPP read, and begins the block with s_nop 1, in case the compiler placed a copy right before.
 #define LRNNX_F_STATE(s, p, CF)                                                        \
     "v_fmac_f32_dpp %" #s ", %" #s ", %" #p " " CF "\n\t"                               \
     "v_mul_f32_dpp %" #p ", %" #p ", %" #p " " CF "\n\t"
+#define LRNNX_FR_STATE(s, p, r, q, CF, CR) LRNNX_F_STATE(s, p, CF) LRNNX_F_STATE(r, q, CR)
 #define LRNNX_ALLROWS " row_mask:0xf bank_mask:0xf"
-
-// One state only (NK = 1): the four in-row steps of its prefix and of its suffix in one block (four instructions per
-// step, so a DPP read comes at least two instructions after the last write of its register) ...
-__device__ __forceinline__ void scan_fr_rows_one(float &P, float &S, float &Pr, float &Sr) {
-    asm("s_nop 1\n\t"
-        LRNNX_FR_STATE(0, 1, 2, 3, "row_shr:1" LRNNX_ALLROWS, "row_shl:1" LRNNX_ALLROWS)
-        LRNNX_FR_STATE(0, 1, 2, 3, "row_shr:2" LRNNX_ALLROWS, "row_shl:2" LRNNX_ALLROWS)
-        LRNNX_FR_STATE(0, 1, 2, 3, "row_shr:4" LRNNX_ALLROWS, "row_shl:4" LRNNX_ALLROWS)
-        LRNNX_FR_STATE(0, 1, 2, 3, "row_shr:8" LRNNX_ALLROWS, "row_shl:8" LRNNX_ALLROWS)
-        : "+v"(S), "+v"(P), "+v"(Sr), "+v"(Pr));
-}
-// ... and the two steps of its prefix that cross rows (lane 15 of rows 0,2 -> rows 1,3; lane 31 -> rows 2,3; the
-// last one leaves the product alone, nobody needs it afterwards)
-__device__ __forceinline__ void scan_f_cross_one(float &P, float &S) {
-    asm("s_nop 1\n\t" LRNNX_F_STATE(0, 1, "row_bcast:15 row_mask:0xa bank_mask:0xf")
-        "s_nop 0\n\t"
-        "v_fmac_f32_dpp %0, %0, %1 row_bcast:31 row_mask:0xc bank_mask:0xf"
-        : "+v"(S), "+v"(P));
-}
-
-// All steps of the NK suffix scans inside their rows, and all steps of the NK prefix scans, as one block of
-// instructions each (NK = 2 or 4).  Every leading s_nop and every boundary between blocks costs the wavefront an issue
-// slot of its own, and a wavefront of the backward kernel is bound by the length of its own instruction stream.
-// A step touches every state once, so a DPP read of a register comes at least two instructions after its last write.
-#define LRNNX_STEP2(CTRL) LRNNX_F_STATE(0, 1, CTRL) LRNNX_F_STATE(2, 3, CTRL)
-#define LRNNX_STEP4(CTRL) LRNNX_STEP2(CTRL) LRNNX_F_STATE(4, 5, CTRL) LRNNX_F_STATE(6, 7, CTRL)
-#define LRNNX_S_ONLY(s, p, CTRL) "v_fmac_f32_dpp %" #s ", %" #s ", %" #p " " CTRL "\n\t"
-template <int NK>
-__device__ __forceinline__ void scan_r_rows(float *Pr, float *Sr) {
-    static_assert(NK == 2 || NK == 4, "states per block");
-    if constexpr (NK == 2) {
-        asm("s_nop 1\n\t" LRNNX_STEP2("row_shl:1" LRNNX_ALLROWS) LRNNX_STEP2("row_shl:2" LRNNX_ALLROWS)
-            LRNNX_STEP2("row_shl:4" LRNNX_ALLROWS) LRNNX_STEP2("row_shl:8" LRNNX_ALLROWS)
-            : "+v"(Sr[0]), "+v"(Pr[0]), "+v"(Sr[1]), "+v"(Pr[1]));
-    } else {
-        asm("s_nop 1\n\t" LRNNX_STEP4("row_shl:1" LRNNX_ALLROWS) LRNNX_STEP4("row_shl:2" LRNNX_ALLROWS)
-            LRNNX_STEP4("row_shl:4" LRNNX_ALLROWS) LRNNX_STEP4("row_shl:8" LRNNX_ALLROWS)
-            : "+v"(Sr[0]), "+v"(Pr[0]), "+v"(Sr[1]), "+v"(Pr[1]), "+v"(Sr[2]), "+v"(Pr[2]), "+v"(Sr[3]), "+v"(Pr[3]));
-    }
-}
-// inclusive prefixes of NK states, complete (lane 15 of rows 0,2 -> rows 1,3, then lane 31 -> rows 2,3; the last
-// step leaves the products alone, nobody needs them afterwards)
-template <int NK>
-__device__ __forceinline__ void scan_f_all(float *P, float *S) {
-    static_assert(NK == 2 || NK == 4, "states per block");
-    if constexpr (NK == 2) {
-        asm("s_nop 1\n\t" LRNNX_STEP2("row_shr:1" LRNNX_ALLROWS) LRNNX_STEP2("row_shr:2" LRNNX_ALLROWS)
-            LRNNX_STEP2("row_shr:4" LRNNX_ALLROWS) LRNNX_STEP2("row_shr:8" LRNNX_ALLROWS)
-            LRNNX_STEP2("row_bcast:15 row_mask:0xa bank_mask:0xf")
-            LRNNX_S_ONLY(0, 1, "row_bcast:31 row_mask:0xc bank_mask:0xf") LRNNX_S_ONLY(2, 3, "row_bcast:31 row_mask:0xc bank_mask:0xf")
-            : "+v"(S[0]), "+v"(P[0]), "+v"(S[1]), "+v"(P[1]));
-    } else {
-        asm("s_nop 1\n\t" LRNNX_STEP4("row_shr:1" LRNNX_ALLROWS) LRNNX_STEP4("row_shr:2" LRNNX_ALLROWS)
-            LRNNX_STEP4("row_shr:4" LRNNX_ALLROWS) LRNNX_STEP4("row_shr:8" LRNNX_ALLROWS)
-            LRNNX_STEP4("row_bcast:15 row_mask:0xa bank_mask:0xf")
-            LRNNX_S_ONLY(0, 1, "row_bcast:31 row_mask:0xc bank_mask:0xf") LRNNX_S_ONLY(2, 3, "row_bcast:31 row_mask:0xc bank_mask:0xf")
-            LRNNX_S_ONLY(4, 5, "row_bcast:31 row_mask:0xc bank_mask:0xf") LRNNX_S_ONLY(6, 7, "row_bcast:31 row_mask:0xc bank_mask:0xf")
-            : "+v"(S[0]), "+v"(P[0]), "+v"(S[1]), "+v"(P[1]), "+v"(S[2]), "+v"(P[2]), "+v"(S[3]), "+v"(P[3]));
-    }
-}
-
-// On return S holds the inclusive prefix (lane 0 first) and Sr the inclusive suffix (lane 63 first) of every state;
-// P and Pr are left in an unspecified state.
-template <int NK>
-__device__ __forceinline__ void wave_scan_fwd_rev_multi(float *P, float *S, float *Pr, float *Sr, int lane) {
-    // suffixes: rows 0 and 2 take the pair held by the first lane of the next row
-    const int src = ((lane & 0x30) + 16) & 63;
-    float Pp[NK], Sp[NK];
-    if constexpr (NK == 1) {
-        scan_fr_rows_one(P[0], S[0], Pr[0], Sr[0]);
-        Pp[0] = bpermute(src, Pr[0]); Sp[0] = bpermute(src, Sr[0]);
-        scan_f_cross_one(P[0], S[0]);
-    } else {
-        // the suffixes go first, so that the lane permutes of their hand-over between rows (one round trip through
-        // the LDS crossbar) are in flight during all of the prefix scans
-        scan_r_rows<NK>(Pr, Sr);
-#pragma unroll
-        for (int k = 0; k < NK; ++k) { Pp[k] = bpermute(src, Pr[k]); Sp[k] = bpermute(src, Sr[k]); }
-        scan_f_all<NK>(P, S);
-    }
-    // rows 0, 2 only (row_mask 0x5); the other rows keep their pair
-    if constexpr (NK == 4) {
-        asm("s_nop 1\n\t"
-            "v_fmac_f32_dpp %0, %8, %4 quad_perm:[0,1,2,3] row_mask:0x5 bank_mask:0xf\n\t"
-            "v_fmac_f32_dpp %1, %9, %5 quad_perm:[0,1,2,3] row_mask:0x5 bank_mask:0xf\n\t"
-            "v_fmac_f32_dpp %2, %10, %6 quad_perm:[0,1,2,3] row_mask:0x5 bank_mask:0xf\n\t"
-            "v_fmac_f32_dpp %3, %11, %7 quad_perm:[0,1,2,3] row_mask:0x5 bank_mask:0xf\n\t"
-            "v_mul_f32_dpp %4, %12, %4 quad_perm:[0,1,2,3] row_mask:0x5 bank_mask:0xf\n\t"
-            "v_mul_f32_dpp %5, %13, %5 quad_perm:[0,1,2,3] row_mask:0x5 bank_mask:0xf\n\t"
-            "v_mul_f32_dpp %6, %14, %6 quad_perm:[0,1,2,3] row_mask:0x5 bank_mask:0xf\n\t"
-            "v_mul_f32_dpp %7, %15, %7 quad_perm:[0,1,2,3] row_mask:0x5 bank_mask:0xf"
-            : "+v"(Sr[0]), "+v"(Sr[1]), "+v"(Sr[2]), "+v"(Sr[3]), "+v"(Pr[0]), "+v"(Pr[1]), "+v"(Pr[2]), "+v"(Pr[3])
-            : "v"(Sp[0]), "v"(Sp[1]), "v"(Sp[2]), "v"(Sp[3]), "v"(Pp[0]), "v"(Pp[1]), "v"(Pp[2]), "v"(Pp[3]));
-    } else {
-#pragma unroll
-        for (int k = 0; k < NK; ++k)
-            asm("s_nop 1\n\t"
-                "v_fmac_f32_dpp %0, %2, %1 quad_perm:[0,1,2,3] row_mask:0x5 bank_mask:0xf\n\t"
-                "v_mul_f32_dpp %1, %3, %1 quad_perm:[0,1,2,3] row_mask:0x5 bank_mask:0xf"
-                : "+v"(Sr[k]), "+v"(Pr[k]) : "v"(Sp[k]), "v"(Pp[k]));
-    }
-    // rows 0 and 1 take the suffix now held by lane 32: Sr += Pr * Sr[32] (the product of the multipliers is not
-    // needed any more).  The value travels through a scalar register; the update runs with the upper half of the
-    // wavefront switched off.  Wait states: one between the VALU write of Sr and its v_readlane, two between the
-    // v_readlane and the VALU read of its scalar result.
-    if constexpr (NK == 4) {
-        unsigned save;
-        float t0, t1, t2, t3;
-        asm("s_nop 1\n\t"
-            "v_readlane_b32 %4, %0, 32\n\t"
-            "v_readlane_b32 %5, %1, 32\n\t"
-            "v_readlane_b32 %6, %2, 32\n\t"
-            "v_readlane_b32 %7, %3, 32\n\t"
-            "s_mov_b32 %8, exec_hi\n\t"
-            "s_mov_b32 exec_hi, 0\n\t"
-            "v_fmac_f32 %0, %4, %9\n\t"
-            "v_fmac_f32 %1, %5, %10\n\t"
-            "v_fmac_f32 %2, %6, %11\n\t"
-            "v_fmac_f32 %3, %7, %12\n\t"
-            "s_mov_b32 exec_hi, %8"
-            : "+v"(Sr[0]), "+v"(Sr[1]), "+v"(Sr[2]), "+v"(Sr[3]), "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3), "=&s"(save)
-            : "v"(Pr[0]), "v"(Pr[1]), "v"(Pr[2]), "v"(Pr[3]));
-    } else {
-#pragma unroll
-        for (int k = 0; k < NK; ++k) {
-            unsigned save;
-            float t0;
-            asm("s_nop 1\n\t"
-                "v_readlane_b32 %1, %0, 32\n\t"
-                "s_mov_b32 %2, exec_hi\n\t"
-                "s_mov_b32 exec_hi, 0\n\t"
-                "v_fmac_f32 %0, %1, %3\n\t"
-                "s_mov_b32 exec_hi, %2"
-                : "+v"(Sr[k]), "=&s"(t0), "=&s"(save) : "v"(Pr[k]));
-        }
-    }
-}
-
-__device__ __forceinline__ float wave_sum(float v) {
-    v += dpp<0x111>(0.0f, v);
-    v += dpp<0x112>(0.0f, v);
-    v += dpp<0x114>(0.0f, v);
-    v += dpp<0x118>(0.0f, v);
-    v += dpp<DPP_ROW_BCAST15, 0xA>(0.0f, v);
-    v += dpp<DPP_ROW_BCAST31, 0xC>(0.0f, v);
-    return readlane(v, 63);
-}
 
 // ---------------------------------------------------------------- I/O element access
 template <typename IO> struct io_traits;
@@ -531,14 +353,6 @@ struct RawFew {
     static constexpr int WORDS = (CNT * (16 / io_traits<IO>::EPC) + 3) / 4;
     uint32_t w[WORDS];
 };
-// One element, read without a branch and without touching the loaded register afterwards (so nothing waits for the
-// load before its real use): past the end the last element is read again (L >= 1) and the CALLER discards it.
-template <typename IO, typename IDX>
-__device__ __forceinline__ void load_one_raw_clamped(const IO *row, IDX l, IDX L, RawFew<IO, 1> &r) {
-    const IDX lc = l < L ? l : L - 1;
-    if constexpr (sizeof(IO) == 4) r.w[0] = *reinterpret_cast<const uint32_t *>(row + lc);
-    else r.w[0] = *reinterpret_cast<const unsigned short *>(row + lc);
-}
 template <typename IO, int CNT, typename IDX>
 __device__ __forceinline__ void load_few_raw(const IO *row, IDX l, IDX L, bool vec, RawFew<IO, CNT> &r) {
     constexpr int BYTES = CNT * (16 / io_traits<IO>::EPC);

@@ -479,7 +479,6 @@ hipError_t launch_ss_fwd(const FwdParams &p, int io_dtype, int disc, hipStream_t
 int fwd_channels_per_workgroup() { return FwdGeom<16, 16>::CH; }
 int fwd_tile_steps() { return FwdGeom<16, 16>::TILE; }
 
-
 // Chains the chunk aggregates of one (b,d,n): carry-in of chunk c+1 = P_c * carry-in of chunk c + S_c.
 // ws_S[c] is replaced by the carry-in of chunk c.
 __global__ void k_ss_carry(const FwdParams p) {
