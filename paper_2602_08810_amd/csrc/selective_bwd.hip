@@ -39,7 +39,8 @@ constexpr int kMaxG = 128;                           // channels of a workgroup 
 // before (lane 0 keeps what it came with) and Gin the suffix of the lane after (lane 31 keeps it).  The two scans
 // alternate, so that a DPP read of a register comes at least two instructions after its last write.  The suffix of a
 // half's upper row reaches the last lane of the lower row by a shift of the whole wavefront, and the row's other lanes
-// from there.
+// from there.  Two blocks, each with its own wait states at its head: as one block the compiler can place nothing between
+// them, and the backward pass of B=16, D=2560, L=4096 took 1 % longer (2707 us with recompute, 2679).
 __device__ __forceinline__ void half_scans(float P, float &S, float &Q, float &xin, float &Gin) {
     float Pr = P;
     asm("s_nop 1\n\t"
@@ -49,7 +50,7 @@ __device__ __forceinline__ void half_scans(float P, float &S, float &Q, float &x
         LRNNX_FR_STATE(0, 1, 2, 3, "row_shr:8" LRNNX_ALLROWS, "row_shl:8" LRNNX_ALLROWS)
         : "+v"(S), "+v"(P), "+v"(Q), "+v"(Pr));
     float Qn;                                        // lane 15 of rows 0 and 2: the first lane of the row after
-    asm("s_nop 0\n\t"
+    asm("s_nop 1\n\t"
         "v_fmac_f32_dpp %0, %0, %5 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
         "v_mov_b32_dpp %4, %1 wave_shl:1 row_mask:0xf bank_mask:0xf\n\t"
         "s_nop 1\n\t"
