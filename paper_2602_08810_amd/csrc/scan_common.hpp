@@ -406,4 +406,28 @@ __device__ __forceinline__ void unpack_few(const RawFew<IO, CNT> &r, float *out)
     }
 }
 
+// The end of a sequence, without a branch: a lane whose CNT elements row[l .. l+CNT) reach past the last valid one, row[n-1],
+// reads the last CNT valid ones instead (tail_window; they must exist, n may be less than CNT if the row has steps before
+// row[0]) and moves them down once they are needed (tail_shift).  What then stands for elements past the end is some valid
+// element: the CALLER discards it.  Element by element, a lane at the end sent its wavefront through CNT loads more, and in a
+// packed batch every sequence has such a tile (24 sequences of 8192 steps in all, 2560 channels, N = 4, bf16: backward
+// 306 us, so 235; 24 of 16384 steps, 1536 channels, N = 16: forward and backward 683 us, so 634).
+template <int CNT>
+__device__ __forceinline__ int tail_window(int l, int n) { return l + CNT <= n ? l : n - CNT; }
+template <typename IO, int CNT>
+__device__ __forceinline__ void tail_shift(RawFew<IO, CNT> &r, int by) {         // by = l - tail_window(l, n)
+    constexpr int W = RawFew<IO, CNT>::WORDS, PER = sizeof(IO) == 2 ? 2 : 1;
+    if constexpr (PER == 2 && CNT > 1) {
+        const unsigned s = (by & 1) * 16;
+#pragma unroll
+        for (int i = 0; i < W; ++i) r.w[i] = __builtin_amdgcn_alignbit(i + 1 < W ? r.w[i + 1] : 0u, r.w[i], s);
+    }
+#pragma unroll
+    for (int b = 1; b < W; b <<= 1) {
+        const uint32_t move = by & (b * PER) ? ~0u : 0u;     // (a select of the two would become one of their addresses)
+#pragma unroll
+        for (int i = 0; i + b < W; ++i) r.w[i] = (move & r.w[i + b]) | (~move & r.w[i]);
+    }
+}
+
 }  // namespace lrnnx

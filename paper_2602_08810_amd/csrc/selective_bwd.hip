@@ -269,6 +269,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         const float *n_A = p.A + (int64_t)d0 * N, *n_ck = ckrow + tile * N;
         const unsigned ck_sd = (unsigned)(nck * N);                  // floats between the checkpoints of two channels
         float r_ac = 0.0f;
+        const bool window = TPT > 1 && vec && L >= TPT;              // the last steps of the sequence: see tail_window
         auto fetch = [&](unsigned t0) {
             const unsigned f0 = (t0 % NTC) * TPT;
             if (FULL) {
@@ -276,6 +277,12 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 load_at<IO, TPT>(n_dl, f0, r_dl);
                 load_at<IO, TPT>(n_dy, f0, r_dy);
                 if constexpr (HAS_Z) load_at<IO, TPT>(n_z, f0, r_z);
+            } else if (window) {
+                const int o = tail_window<TPT>((int)f0, rem);
+                load_few_raw<IO, TPT>(n_u + o, 0, TPT, true, r_u);
+                load_few_raw<IO, TPT>(n_dl + o, 0, TPT, true, r_dl);
+                load_few_raw<IO, TPT>(n_dy + o, 0, TPT, true, r_dy);
+                if constexpr (HAS_Z) load_few_raw<IO, TPT>(n_z + o, 0, TPT, true, r_z);
             } else {
                 load_few_raw<IO, TPT>(n_u, (int)f0, rem, vec, r_u);
                 load_few_raw<IO, TPT>(n_dl, (int)f0, rem, vec, r_dl);
@@ -315,6 +322,13 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         auto step_inputs = [&](int ch, unsigned t0, float (&u)[TPT], float (&dl)[TPT], float (&dy)[TPT]) {
             const float bias = sBias[ch < Gact ? ch : Gact - 1];
             float z[TPT];
+            if (!FULL && window) {
+                const int f0 = (int)((t0 % NTC) * TPT), by = f0 - tail_window<TPT>(f0, rem);
+                tail_shift<IO, TPT>(r_u, by);
+                tail_shift<IO, TPT>(r_dl, by);
+                tail_shift<IO, TPT>(r_dy, by);
+                if constexpr (HAS_Z) tail_shift<IO, TPT>(r_z, by);
+            }
             unpack_few<IO, TPT>(r_u, u);
             unpack_few<IO, TPT>(r_dl, dl);
             unpack_few<IO, TPT>(r_dy, dy);

@@ -151,6 +151,9 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
     // which a wavefront stages at once fall into 64 banks.
     // ---- the inputs of a tile, raw.  Those of a whole tile (FULL: nothing to check per element) are fetched ahead, once
     // the state loop of the tile before is done, and used after its epilogue.
+    // the last steps of the sequence: see tail_window (64 x 16 is for long rows, which have one such tile: left out there,
+    // where the mere presence of that code cost the main loop 2 %)
+    const bool window = GE::TILE <= 512 && vec && L >= T;
     RawFew<IO, T> r_u, r_dl;
     RawFew<IO, NS> r_B[RPT], r_C[WANT_Y ? RPT : 1];
     auto fetch_rows = [&](int64_t tile, auto FULL) {
@@ -162,8 +165,14 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
             load_few_raw<IO, T>(dl + r, 0, T, true, r_dl);
         } else {
             const int n = L - l0 < TILE ? (int)(L - l0) : TILE;
-            load_few_raw<IO, T>(u, r, n, vec, r_u);
-            load_few_raw<IO, T>(dl, r, n, vec, r_dl);
+            if (window) {
+                const int o = tail_window<T>(r, n);
+                load_few_raw<IO, T>(u + o, 0, T, true, r_u);
+                load_few_raw<IO, T>(dl + o, 0, T, true, r_dl);
+            } else {
+                load_few_raw<IO, T>(u, r, n, vec, r_u);
+                load_few_raw<IO, T>(dl, r, n, vec, r_dl);
+            }
         }
     };
     auto fetch_maps = [&](int64_t tile, int h, auto FULL) {
@@ -196,6 +205,7 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
                 const IO *z = row(p.z, p.z_sb, p.z_sd, l0);
                 const int r = (fresh() % LPC) * T;
                 if constexpr (FULL) load_few_raw<IO, T>(z + r, 0, T, true, r_z);
+                else if (window) load_few_raw<IO, T>(z + tail_window<T>(r, rem), 0, T, true, r_z);
                 else load_few_raw<IO, T>(z, r, rem, vec, r_z);
             }
         };
@@ -228,6 +238,11 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
             __syncthreads();
             if (busy && h == 0) {
                 // ---- this lane's steps of Delta, Delta u and D u
+                if (!FULL && window) {
+                    const int r = (fresh() % LPC) * T, by = r - tail_window<T>(r, rem);
+                    tail_shift<IO, T>(r_u, by);
+                    tail_shift<IO, T>(r_dl, by);
+                }
                 unpack_few<IO, T>(r_u, du);
                 unpack_few<IO, T>(r_dl, dl);
 #pragma unroll
@@ -335,6 +350,10 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
             if (busy) {
                 if (p.z) {
                     float zv[T];
+                    if (!FULL && window) {
+                        const int r = (fresh() % LPC) * T;
+                        tail_shift<IO, T>(r_z, r - tail_window<T>(r, rem));
+                    }
                     unpack_few<IO, T>(r_z, zv);
 #pragma unroll
                     for (int t = 0; t < T; ++t) yv[t] *= zv[t] * sigmoid_fast(zv[t]);
