@@ -288,11 +288,18 @@ typedef struct lrnnx_ss_bwd_args {
     float *dD;                                                     /* [D] out or NULL */
     float *dbias;                                                  /* [D] out or NULL */
     float *dx0;                                                    /* [B,D,N] out or NULL */
-    void *workspace;    size_t workspace_bytes;                    /* LRNNX_WS_BWD, or LRNNX_WS_BWD_CARRY with ckpt; plus LRNNX_WS_BWD_SUMS */
+    void *workspace;    size_t workspace_bytes;                    /* LRNNX_WS_BWD, or LRNNX_WS_BWD_CARRY with ckpt; plus LRNNX_WS_BWD_SUMS;
+                                                                      or lrnnx_selective_scan_bwd_workspace_bytes(args) */
     void *stream;
 } lrnnx_ss_bwd_args;
 
 int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *args);
+
+/* Bytes of workspace with which this very call runs at full speed: the sizes, bc_groups, path and max_seqlen of *args, and
+ * whether cu_seqlens and ckpt are given, decide; other pointers and the strides are not looked at (host only, no GPU
+ * needed).  Never more than lrnnx_workspace_bytes() names for the two or three kinds together.  0 for invalid sizes and
+ * for calls that need none. */
+size_t lrnnx_selective_scan_bwd_workspace_bytes(const lrnnx_ss_bwd_args *args);
 
 /* ------------------------------------------------------------------ LTI complex-diagonal scan
  *     x[b,k,p] = lambda[p] * x[b,k-1,p] + v[b,k,p]        (Eq. 2 with constant diagonal A; Sec. 2.2.1)
@@ -494,8 +501,9 @@ typedef enum { LRNNX_WS_FWD = 0, LRNNX_WS_BWD = 1, LRNNX_WS_LTI = 2, LRNNX_WS_LT
                LRNNX_WS_BWD_CARRY = 7,  /* the chunk aggregates of lrnnx_selective_scan_bwd alone (ckpt supplied) */
                LRNNX_WS_FWD_COMPLEX = 8,
                LRNNX_WS_BWD_SUMS = 9    /* optional, in addition to LRNNX_WS_BWD or LRNNX_WS_BWD_CARRY: partial sums of dBm
-                                         * and dCm.  With it they are added up by a second launch, in a fixed order;
-                                         * without it by float atomics, which is slower */
+                                         * and dCm, at most 512 MiB.  With room for all of them they are added up by a
+                                         * second launch, in a fixed order; else by float atomics, which is the slower way
+                                         * for launches that need no more than that */
              } lrnnx_ws_kind;
 
 /* Bytes of device scratch the call may need (the largest over its paths).  bc_groups as in the call's struct (0 or 1:

@@ -129,6 +129,8 @@ def lib():
         L = ctypes.CDLL(LIB_PATH)
         L.lrnnx_selective_scan_fwd.argtypes = [ctypes.POINTER(FwdArgs)]
         L.lrnnx_selective_scan_bwd.argtypes = [ctypes.POINTER(BwdArgs)]
+        L.lrnnx_selective_scan_bwd_workspace_bytes.argtypes = [ctypes.POINTER(BwdArgs)]
+        L.lrnnx_selective_scan_bwd_workspace_bytes.restype = _sz
         L.lrnnx_selective_scan_fwd_complex.argtypes = [ctypes.POINTER(FwdComplexArgs)]
         L.lrnnx_selective_scan_fwd_complex.restype = ctypes.c_int
         L.lrnnx_selective_scan_bwd_complex.argtypes = [ctypes.POINTER(BwdComplexArgs)]
@@ -617,9 +619,7 @@ def lrnnx_selective_scan_bwd(u, delta, A, Bm, Cm, dy, Dskip=None, delta_bias=Non
     if want_dx0:
         a.dx0 = new("dx0", (Bsz, D, N), torch.float32).data_ptr()
     if workspace is None:
-        kind = WS_BWD if ckpt is None else WS_BWD_CARRY
-        nbytes = (lrnnx_workspace_bytes(kind, Bsz, D, N, L, a.io_dtype, a.bc_groups, packed) +
-                  lrnnx_workspace_bytes(WS_BWD_SUMS, Bsz, D, N, L, a.io_dtype, a.bc_groups, packed))
+        nbytes = lib().lrnnx_selective_scan_bwd_workspace_bytes(ctypes.byref(a))
         if nbytes:
             workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
     if workspace is not None:

@@ -150,22 +150,56 @@ void fit_chunks(BwdPlan &pl, size_t nfit) {
     pl.nchunks = (int)nfit;
 }
 
-// Scratch for the tile sums of dBm and dCm of a real backward call (LRNNX_WS_BWD_SUMS): what the widest launch the host may choose
-// for this shape takes.  For packed batches, whose channels per workgroup depend on the longest sequence, that is the fewest
-// a workgroup may take, or kBwdPackedSumG if this would pass half a GiB (the launch then takes no fewer).
+// Scratch for the tile sums of dBm and dCm of a real backward call (LRNNX_WS_BWD_SUMS): what the widest launch takes among those the
+// host may choose for this shape (by path, and for a packed batch by its longest sequence) that need no more than
+// kBwdSumsCap.
 size_t bwd_sums_bytes(int64_t B, int64_t D, int64_t N, int64_t L, int64_t bcg, bool packed) {
     const int64_t dpg = D / bcg;
-    if (packed) {
-        auto bytes = [&](int64_t G) { return bwd_part_bytes((int)N, lrnnx_packed_ckpt_slots(L, B), bcg * cdiv(dpg, dpg < G ? dpg : G)); };
-        return bytes(kBwdMinG) <= (size_t)512 << 20 ? bytes(kBwdMinG) : bytes(kBwdPackedSumG);
-    }
     size_t most = 0;
-    for (int path = LRNNX_PATH_AUTO; path <= LRNNX_PATH_CHUNK_CARRY; ++path) {
-        const BwdPlan pl = bwd_plan((int)(B * bcg), (int)dpg, (int)N, L, path, true);
-        const size_t n = bwd_part_bytes((int)N, B * cdiv(L, kBwdTileSteps), bcg * cdiv(dpg, pl.G));
-        if (n > most) most = n;
-    }
+    auto widest = [&](int64_t G) {
+        const size_t n = bwd_part_bytes((int)N, packed ? lrnnx_packed_ckpt_slots(L, B) : B * cdiv(L, kBwdTileSteps), bcg * cdiv(dpg, G));
+        if (n <= kBwdSumsCap && n > most) most = n;
+    };
+    if (packed)
+        for (int64_t G = kBwdMinG; !most && G < dpg + 2; G += 2) widest(G);
+    else
+        for (int path = LRNNX_PATH_AUTO; path <= LRNNX_PATH_CHUNK_CARRY; ++path)
+            widest(bwd_plan((int)(B * bcg), (int)dpg, (int)N, L, path, true).G);
     return most;
+}
+
+// What a real backward call launches when its workspace has room for everything: the plan, and the shape of a packed
+// launch, in the parameter block (bwd_grid_x reads it from there).
+BwdPlan plan_bwd(BwdParams &p, const lrnnx_ss_bwd_args *a, int bcg) {
+    p.bcg = bcg; p.dpg = a->D / bcg;
+    return packed_bwd_plan(bwd_plan, a->B * bcg, a->D / bcg, a->N, a->L, a->path, a->cu_seqlens != nullptr, a->max_seqlen);
+}
+// tiles of 256 steps of the whole call (a packed batch counts them like its checkpoint slots)
+int64_t bwd_tile_slots(const lrnnx_ss_bwd_args *a) {
+    return a->cu_seqlens ? lrnnx_packed_ckpt_slots(a->L, a->B) : a->B * cdiv(a->L, kBwdTileSteps);
+}
+void set_bwd_shape(BwdParams &p, const lrnnx_ss_bwd_args *a, const BwdPlan &pl) {
+    p.G = pl.G;
+    p.nchunks = pl.nchunks;
+    p.tiles_per_chunk = pl.tiles_per_chunk;
+    if (!a->cu_seqlens || pl.nchunks > 1) return;
+    bwd_packed_shape(a->B, a->D, a->L, a->max_seqlen, bwd_channels_per_group(a->B * p.bcg, p.dpg, a->N, a->L, true),
+                     bwd_places(a->N), &p.G, &p.wcap, &p.gmin);
+    // tile sums a little over their scratch: up to half as many channels again, if that makes them fit (see kBwdSumsCap)
+    int &least = p.wcap > 0 ? p.gmin : p.G;
+    const int planned = least, most = planned + planned / 2 < kBwdMaxG ? planned + planned / 2 : kBwdMaxG;
+    auto fits = [&]() { return bwd_part_bytes(a->N, bwd_tile_slots(a), bwd_grid_x(p)) <= kBwdSumsCap; };
+    while (!fits() && least + 2 <= most) least += 2;
+    if (!fits()) least = planned;
+    if (p.G < least) p.G = least;
+}
+// bytes of the checkpoints of the recompute sweep, and of the launch order of a packed batch
+size_t bwd_ckpt_bytes(const lrnnx_ss_bwd_args *a) {
+    const int64_t rows = a->cu_seqlens ? (int64_t)a->D * lrnnx_packed_ckpt_slots(a->L, a->B) : (int64_t)a->B * a->D * cdiv(a->L, kCkptInterval);
+    return (size_t)rows * a->N * sizeof(float);
+}
+size_t bwd_order_bytes(const lrnnx_ss_bwd_args *a, int nchunks) {
+    return a->cu_seqlens && nchunks == 1 && a->B > 1 && a->B <= kMaxOrdered ? sizeof(int) * (size_t)a->B : 0;
 }
 
 // The real and the complex backward entry points take the same per-row tensors (same field names in both argument
@@ -515,6 +549,22 @@ int lrnnx_selective_scan_bwd_complex(const lrnnx_ss_bwd_complex_args *a) {
     return launch_ss_cbwd(p, a->io_dtype, a->disc, s) == hipSuccess ? LRNNX_OK : LRNNX_ERR_LAUNCH;
 }
 
+size_t lrnnx_selective_scan_bwd_workspace_bytes(const lrnnx_ss_bwd_args *a) {
+    if (!a || a->struct_size != sizeof(lrnnx_ss_bwd_args)) return 0;
+    if (a->B < 1 || a->B > 65535 || a->D < 1 || a->L < 1 || !supported_n(a->N) || a->bc_groups < 0 || a->max_seqlen < 0) return 0;
+    if (a->path < LRNNX_PATH_AUTO || a->path > LRNNX_PATH_CHUNK_CARRY) return 0;
+    const int bcg = a->bc_groups > 1 ? a->bc_groups : 1;
+    if (a->D % bcg) return 0;
+    BwdParams p{};
+    const BwdPlan pl = plan_bwd(p, a, bcg);
+    set_bwd_shape(p, a, pl);
+    size_t n = a->ckpt ? 0 : align256(bwd_ckpt_bytes(a));
+    if (pl.nchunks > 1) n += (size_t)2 * a->B * a->D * pl.nchunks * a->N * sizeof(float);
+    n += bwd_order_bytes(a, pl.nchunks);
+    const size_t sums = bwd_part_bytes(a->N, bwd_tile_slots(a), bwd_grid_x(p));
+    return sums <= kBwdSumsCap ? n + 256 + sums : n;          // (256: the sums start on such a boundary)
+}
+
 int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
     if (!a || a->struct_size != sizeof(lrnnx_ss_bwd_args)) return LRNNX_ERR_INVALID_ARG;
     const int64_t *cu = a->cu_seqlens;
@@ -535,14 +585,14 @@ int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
     const size_t es = elem_size(a->io_dtype);
     const int64_t nck = cdiv(a->L, kCkptInterval);
     const int64_t nslots = lrnnx_packed_ckpt_slots(a->L, a->B);
-    const size_t ck_bytes = cu ? (size_t)a->D * nslots * a->N * sizeof(float)
-                               : (size_t)a->B * a->D * nck * a->N * sizeof(float);
+    const size_t ck_bytes = bwd_ckpt_bytes(a);
     if (!a->ckpt && (!a->workspace || a->workspace_bytes < ck_bytes)) return LRNNX_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(a->workspace) & 3u) return LRNNX_ERR_INVALID_ARG;
     hipStream_t s = reinterpret_cast<hipStream_t>(a->stream);
 
     // chunked path: the aggregates live in the workspace, after the checkpoints of the recompute sweep if there are any
-    BwdPlan pl = packed_bwd_plan(bwd_plan, a->B * bcg, a->D / bcg, a->N, a->L, path, cu != nullptr, a->max_seqlen);
+    BwdParams p{};
+    BwdPlan pl = plan_bwd(p, a, bcg);
     const size_t carry_off = a->ckpt ? 0 : align256(ck_bytes);
     if (pl.nchunks > 1) {
         const size_t per_chunk = (size_t)2 * a->B * a->D * a->N * sizeof(float);
@@ -571,18 +621,11 @@ int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
         ckpt = f.ckpt;
     }
 
-    BwdParams p{};
     set_bwd_rows(p, a);
-    p.bcg = bcg; p.dpg = a->D / bcg;
-    p.cu = cu; p.nslots = lrnnx_packed_ckpt_slots(a->L, a->B);
+    p.cu = cu; p.nslots = nslots;
     p.A = a->A; p.x0 = a->x0; p.ckpt = ckpt;
     p.dA = a->dA; p.dBm = a->dBm; p.dCm = a->dCm; p.dx0 = a->dx0;
-    p.G = pl.G;
-    p.nchunks = pl.nchunks;
-    p.tiles_per_chunk = pl.tiles_per_chunk;
-    if (cu && pl.nchunks == 1)
-        bwd_packed_shape(a->B, a->D, a->L, a->max_seqlen, bwd_channels_per_group(a->B * bcg, a->D / bcg, a->N, a->L, true),
-                         bwd_places(a->N), &p.G, &p.wcap, &p.gmin);
+    set_bwd_shape(p, a, pl);
     size_t used = carry_off;                          // bytes of the workspace taken so far
     if (pl.nchunks > 1) {
         used += (size_t)2 * a->B * a->D * p.nchunks * a->N * sizeof(float);
@@ -594,26 +637,19 @@ int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
     }
     // packed batches: longest sequences first, if the workspace has room for the order (B ints, after the checkpoints
     // of the recompute sweep if there are any)
-    if (cu && pl.nchunks == 1 && a->B > 1 && a->B <= kMaxOrdered && a->workspace &&
-        a->workspace_bytes >= carry_off + sizeof(int) * (size_t)a->B) {
+    const size_t order_bytes = bwd_order_bytes(a, pl.nchunks);
+    if (order_bytes && a->workspace && a->workspace_bytes >= carry_off + order_bytes) {
         int *order = reinterpret_cast<int *>(static_cast<char *>(a->workspace) + carry_off);
         if (launch_seq_order(cu, a->B, a->L, order, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
         p.order = order;
-        used = carry_off + sizeof(int) * (size_t)a->B;
+        used = carry_off + order_bytes;
     }
-    // room behind that for the tile sums of dBm and dCm (with fewer workgroups to a long packed sequence if need be)
-    const int64_t slots = cu ? nslots : a->B * nck;
+    // room behind that for the tile sums of dBm and dCm
     p.part_tiles = nck;
     const uintptr_t part = align256(reinterpret_cast<uintptr_t>(a->workspace) + used);
     const uintptr_t end = reinterpret_cast<uintptr_t>(a->workspace) + a->workspace_bytes;
-    auto fits = [&]() { return part + bwd_part_bytes(a->N, slots, bwd_grid_x(p)) <= end; };
-    if (a->workspace) {
-        const int gmin = p.gmin;
-        if (cu && p.wcap > 0)
-            while (!fits() && p.gmin < p.G) p.gmin = p.gmin + 2 < p.G ? p.gmin + 2 : p.G;
-        if (fits()) p.part = reinterpret_cast<float *>(part);
-        else p.gmin = gmin;
-    }
+    if (a->workspace && part <= end && bwd_part_bytes(a->N, bwd_tile_slots(a), bwd_grid_x(p)) <= end - part)
+        p.part = reinterpret_cast<float *>(part);
 
     // reduced outputs that are accumulated with atomics: clear them on the stream first (dBm and dCm of a packed batch in
     // any case: rows outside every sequence are zero)

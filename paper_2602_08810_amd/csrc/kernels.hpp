@@ -115,8 +115,15 @@ struct BwdParams {
     int64_t part_tiles;
 };
 constexpr int kBwdTileSteps = 256;
-constexpr int kBwdMinG = 4;
-constexpr int kBwdPackedSumG = 8;    // channels per workgroup that the tile sums of a packed batch are sized for
+constexpr int kBwdMinG = 4, kBwdMaxG = 128;   // channels of a workgroup (the most: it sizes the tables in LDS)
+// The most scratch that the tile sums of dBm and dCm are given; a launch that would need more adds to dBm and dCm with
+// atomics.  At that size they cost little or nothing: a workgroup then takes many channels or many tiles, and what it adds is
+// little beside its other work (N = 16, bf16: B = 64, D = 2560, L = 4096, 768 MiB: 8644 us with the workspace, 8641 with atomics;
+// 24 packed sequences of 32768 steps, 5120 channels, 0.9 GiB: 2737 and 2713; smaller: B = 8, D = 1536, L = 2048, 128 MiB:
+// 380 and 392).  Launches of few channels a workgroup meet at the same addresses more often: a batch is then cut into
+// chunks of the time axis instead (plan_time_chunks), and a packed launch that needs a little more than this takes up to
+// half as many channels again (24 sequences, 32768 steps, 128 channels, N = 32: 400 us, with atomics 759).
+constexpr size_t kBwdSumsCap = (size_t)512 << 20;
 // launch shape of a packed batch of B sequences on L steps, D channels, whose longest has max_seqlen steps (0: not
 // known, nothing changes): *G comes in as the channels per workgroup of a batch of unknown lengths and may be raised
 // to Gbal, those of a batch [B,D,L] of equal lengths; else cap and fewest channels as in BwdParams.  `places` =
@@ -210,7 +217,10 @@ hipError_t launch_ss_cbwd_carry(const CBwdParams &p, hipStream_t s);
 // full: a second, half-empty round, 20-30 % slower), with as many channels each as that allows (staging of the maps
 // and flush of dBm/dCm are paid per workgroup and tile: G = 8 -> 64 is 25 % faster at equal workgroup count).  So:
 // the largest G <= maxG for which some chunk count fills the chip without exceeding it; baseG is the single pass's G.
-inline BwdPlan plan_time_chunks(int rowsg, int dpg, int64_t L, int mode, int baseG, int64_t full, int maxG) {
+// `roomy`: the tile sums of the single pass fit their scratch.  If not, and its workgroups take few channels, chunks of more
+// channels are the better plan (B * D = 4096, N = 16, bf16: L = 8192 670 us, chunked 584, L = 16384 1311 and 1148, and a
+// sixteenth of the sums; L = 4096, where they still fit: 342 and 367).
+inline BwdPlan plan_time_chunks(int rowsg, int dpg, int64_t L, int mode, int baseG, int64_t full, int maxG, bool roomy = true) {
     BwdPlan pl;
     pl.G = baseG;
     pl.nchunks = 1;
@@ -219,7 +229,7 @@ inline BwdPlan plan_time_chunks(int rowsg, int dpg, int64_t L, int mode, int bas
     const int64_t ntiles = pl.tiles_per_chunk;
     const int64_t single = (int64_t)rowsg * ((dpg + pl.G - 1) / pl.G);
     // enough rows already, unless they come as many small workgroups (G at its minimum) that leave room on the chip
-    if (mode == 0 && single * 4 >= full * 3 && (pl.G >= 16 || single >= full)) return pl;
+    if (mode == 0 && single * 4 >= full * 3 && (pl.G >= 16 || (single >= full && roomy))) return pl;
     int64_t cmax = ntiles;                                                     // asked for: down to one tile per chunk
     if (mode == 0) {                                                           // automatic: four tiles or more per chunk,
         cmax = ntiles / 4;                                                     // two when the sequence is short
@@ -244,7 +254,7 @@ inline BwdPlan plan_time_chunks(int rowsg, int dpg, int64_t L, int mode, int bas
     if (bestC < 2) {
         if (mode != 2 || ntiles < 2) return pl;
         bestC = 2; bestG = pl.G;                                               // asked for: two chunks at least
-    } else if (mode == 0 && bestW <= single) {
+    } else if (mode == 0 && (roomy ? bestW <= single : bestW * 4 < full * 3)) {
         return pl;                                                             // chunking would not fill the chip better
     }
     pl.G = bestG;

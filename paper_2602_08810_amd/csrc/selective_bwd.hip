@@ -32,7 +32,6 @@
 
 namespace lrnnx {
 
-constexpr int kMaxG = 128;                           // channels of a workgroup (sizes the tables in LDS)
 
 // Both scans of one state over the 32 lanes of each half-wavefront: on return S is the inclusive prefix (lane 0 of the
 // half first) and Q the inclusive suffix (lane 31 first) of the pairs (P, S) and (P, Q), xin the prefix of the lane
@@ -151,11 +150,11 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
     constexpr int NB = GE::NB;
     __shared__ __attribute__((aligned(16))) float sIn[NB][CP][3][OWN ? 4 : TILE];       // delta, u, dypre of a pair of channels
     __shared__ __attribute__((aligned(16))) float sPart[NB][CP][W][3][OWN ? 4 : TILE];  // per wavefront: ypre, du, ddelta partials
-    __shared__ __attribute__((aligned(16))) float sH[kMaxG * N];   // a_{l0} H_{l0} carried to the earlier tile, per (channel, n)
+    __shared__ __attribute__((aligned(16))) float sH[kBwdMaxG * N];   // a_{l0} H_{l0} carried to the earlier tile, per (channel, n)
     __shared__ __attribute__((aligned(16))) float sAC[NB][2][CP][N];   // A and the state entering the tile, of a pair
-    __shared__ float sdA[kMaxG * N];
-    __shared__ float sdD[kMaxG], sdb[kMaxG];
-    __shared__ float sDskip[kMaxG], sBias[kMaxG];
+    __shared__ float sdA[kBwdMaxG * N];
+    __shared__ float sdD[kBwdMaxG], sdb[kBwdMaxG];
+    __shared__ float sDskip[kBwdMaxG], sBias[kBwdMaxG];
 
     // Two workgroups share a compute unit, so each SIMD holds one wavefront of each.  The issue arbiter prefers the
     // older wavefront, the older workgroup finishes earlier and the younger one then runs alone, badly hiding its
@@ -838,12 +837,12 @@ static int channels_for(int B, int D, int64_t full, bool balanced) {
     // fit into a whole number of rounds, not one more (several rounds only when a block cannot hold more channels).
     if (balanced) {
         int64_t rounds = 1;
-        while ((int64_t)B * ((D + kMaxG - 1) / kMaxG) > rounds * full && rounds < 64) ++rounds;
+        while ((int64_t)B * ((D + kBwdMaxG - 1) / kBwdMaxG) > rounds * full && rounds < 64) ++rounds;
         const int64_t nb = rounds * full / B;          // channel blocks per row group
         if (nb >= 1) G = (D + nb - 1) / nb;
     }
     if (G < 8) G = 8;
-    if (G > kMaxG) G = kMaxG;
+    if (G > kBwdMaxG) G = kBwdMaxG;
     if (G > D) G = D;
     const int64_t groups = (D + G - 1) / G;
     return (int)((D + groups - 1) / groups);           // even split
@@ -875,7 +874,9 @@ void bwd_packed_shape(int B, int D, int64_t L, int64_t max_seqlen, int Gbal, int
 
 // launch shape incl. the chunked path for few rows and long sequences (selective_bwd_carry.hip)
 BwdPlan bwd_plan(int rowsg, int dpg, int N, int64_t L, int mode, bool balanced) {
-    BwdPlan pl = plan_time_chunks(rowsg, dpg, L, balanced ? mode : 1, channels_for(rowsg, dpg, bwd_places(N), balanced), bwd_places(N), kMaxG);
+    const int G = channels_for(rowsg, dpg, bwd_places(N), balanced), pairs = whole_passes(G);
+    const bool roomy = bwd_part_bytes(N, (L + kBwdTileSteps - 1) / kBwdTileSteps, (int64_t)rowsg * ((dpg + pairs - 1) / pairs)) <= kBwdSumsCap;
+    BwdPlan pl = plan_time_chunks(rowsg, dpg, L, balanced ? mode : 1, G, bwd_places(N), kBwdMaxG, roomy);
     pl.G = whole_passes(pl.G);
     return pl;
 }
