@@ -561,6 +561,11 @@ size_t lrnnx_selective_scan_bwd_workspace_bytes(const lrnnx_ss_bwd_args *a) {
     size_t n = a->ckpt ? 0 : align256(bwd_ckpt_bytes(a));
     if (pl.nchunks > 1) n += (size_t)2 * a->B * a->D * pl.nchunks * a->N * sizeof(float);
     n += bwd_order_bytes(a, pl.nchunks);
+    // A batch of one tile and many blocks of channels: a workgroup adds to dBm and dCm once, and atomics are done before a second
+    // launch could start (L = 256, bf16: 1024 rows, N = 16 27 us, with the workspace 32, N = 4 19 and 20; 4096 rows 44 and
+    // 49, 27 and 29).  Few blocks of many states take as long either way or longer (256 rows, N = 32: 33 and 32 us), and
+    // with N <= 2 the additions collide within a wavefront (4096 rows, N = 1: 37 and 27).
+    if (!a->cu_seqlens && a->L <= kBwdTileSteps && a->N >= 4 && bwd_grid_x(p) >= (a->N > 8 ? 2 * a->N : 16) * bcg) return n;
     const size_t sums = bwd_part_bytes(a->N, bwd_tile_slots(a), bwd_grid_x(p));
     return sums <= kBwdSumsCap ? n + 256 + sums : n;          // (256: the sums start on such a boundary)
 }

@@ -709,16 +709,30 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
 
 // dBm, dCm [.., L, N] from the tile sums the workgroups of k_ss_bwd left in the workspace: a workgroup adds one piece of a
 // tile (blockIdx.x) of one of the two maps (blockIdx.y) of one group (blockIdx.z) over the channel blocks, always in the same order, and
-// transposes it through LDS.  Bound by the reads of the workspace.
-template <int N>
+// transposes it through LDS.  With many tiles it is bound by the reads of the workspace.  With few tiles of many channel blocks a
+// chain of reads is what it waits for: KS threads then share an element, each a quarter of the blocks, and a
+// workgroup takes a quarter of the piece (whole call, bf16, L = 512: 1024 rows, N = 16 49 us, so 41; 4096 rows 73 and 57, N = 4
+// 57 and 42).
+template <int N> struct BwdMaps {
+    static constexpr int PIECES = N >= 8 ? N / 4 : 1;                // pieces of a tile, of one thread an element
+};
+template <int N, int KS>
 __global__ __launch_bounds__(256) void k_ss_bwd_maps(const BwdParams p, int gx) {
     constexpr int PT = N * kBwdTileSteps;            // floats of one map's sums of one tile
-    constexpr int PIECES = N >= 8 ? N / 4 : 1;
+    // the quarter of a piece is one of time as long as what is read of a state stays whole lines of 128 bytes, and one of the
+    // states beyond that (cut to 32 bytes, the sums of 4096 rows of 2048 steps, N = 16, took 40 us longer)
+    constexpr int LS = KS == 1 || N >= 16 ? 1 : KS * 4 / N, NP = KS / LS;
+    constexpr int PIECES = BwdMaps<N>::PIECES * LS;
     constexpr int LP = 32 / PIECES;                  // lanes (of 8 steps) of a piece
     constexpr int SP = LP * 8;                       // its steps
-    __shared__ float sT[SP * (N + 1)];
-    const int piece = blockIdx.x % PIECES;
-    const int64_t slot = blockIdx.x / PIECES;
+    constexpr int NW = N / NP;                       // its states
+    constexpr int NE = NW * LP * 2;                  // its elements of four steps
+    static_assert(LP * PIECES == 32 && (KS == 1 ? NE <= 256 : NE == 64 && KS == 4), "a thread for each element, a wavefront for each share of the blocks");
+    __shared__ float sT[SP * (NW + 1)];
+    __shared__ float4 sK[KS > 1 ? KS * NE : 1];
+    const int n0 = (blockIdx.x % NP) * NW;
+    const int piece = (blockIdx.x / NP) % PIECES;
+    const int64_t slot = blockIdx.x / (NP * PIECES);
     int64_t b, tile, toff = 0, L = p.L;
     if (p.cu) {
         // the sequence whose tiles start last at or before this slot: sequence b's start at cu[b] / 256 + b
@@ -742,30 +756,41 @@ __global__ __launch_bounds__(256) void k_ss_bwd_maps(const BwdParams p, int gx) 
     const int nblk = (p.dpg + G - 1) / G;
     const int grp = blockIdx.z;
 
-    const int tid = threadIdx.x;
-    if (tid < N * LP * 2) {
-        // this thread's four steps: of lane li of the piece (8 steps each), the first or the second four
-        const int li = tid % LP, q = (tid / LP) & 1, n = tid / (2 * LP);
-        const int at = n * kBwdTileSteps + q * 128 + (piece * LP + li) * 4;
+    const int tid = threadIdx.x, el = tid % NE;
+    // (wave-uniform, and with it the number of reads: a loop that lanes leave one by one reads one value at a time)
+    const int ks = KS > 1 ? __builtin_amdgcn_readfirstlane(tid / NE) : 0;
+    // this thread's four steps: of lane li of the piece (8 steps each), the first or the second four
+    const int li = el % LP, q = (el / LP) & 1, n = el / (2 * LP);
+    float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    auto add = [&](const float4 v) { a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w; };
+    if (KS > 1 || tid < NE) {
+        const int at = (n0 + n) * kBwdTileSteps + q * 128 + (piece * LP + li) * 4;
         const float *src = p.part + ((slot * gx + (int64_t)grp * nblk) * 2 + blockIdx.y) * PT + at;
-        float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        const int k0 = nblk * ks / KS, k1 = nblk * (ks + 1) / KS;
 #pragma unroll 8
-        for (int k = 0; k < nblk; ++k) {
-            const float4 v = *reinterpret_cast<const float4 *>(src + (int64_t)k * 2 * PT);
-            a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
+        for (int k = k0; k < k1; ++k) add(*reinterpret_cast<const float4 *>(src + (int64_t)k * 2 * PT));
+        if constexpr (KS > 1) sK[ks * NE + el] = a;
+    }
+    if constexpr (KS > 1) {
+        __syncthreads();
+        if (ks == 0) {
+#pragma unroll
+            for (int k = 1; k < KS; ++k) add(sK[k * NE + el]);
         }
-        float *t = sT + (li * 8 + q * 4) * (N + 1) + n;
-        t[0] = a.x; t[N + 1] = a.y; t[2 * (N + 1)] = a.z; t[3 * (N + 1)] = a.w;
+    }
+    if (ks == 0 && tid < NE) {
+        float *t = sT + (li * 8 + q * 4) * (NW + 1) + n;
+        t[0] = a.x; t[NW + 1] = a.y; t[2 * (NW + 1)] = a.z; t[3 * (NW + 1)] = a.w;
     }
     __syncthreads();
     float *out = (blockIdx.y ? p.dCm : p.dBm) + ((p.cu ? (int64_t)grp : b * p.bcg + grp) * p.L + toff + l0) * N;
     const int rows = L - l0 < SP ? (int)(L - l0) : SP;
     if constexpr (N >= 4) {
-        const int r = tid / (N / 4), n = (tid % (N / 4)) * 4;        // SP * N / 4 is the number of threads
-        static_assert(SP * N / 4 == 256, "one 16-byte piece per thread");
+        const int r = tid / (NW / 4), m = (tid % (NW / 4)) * 4;
+        static_assert(SP * NW / 4 <= 256, "one 16-byte piece per thread");
         if (r < rows) {
-            const float *t = sT + r * (N + 1) + n;
-            *reinterpret_cast<float4 *>(out + r * N + n) = make_float4(t[0], t[1], t[2], t[3]);
+            const float *t = sT + r * (NW + 1) + m;
+            *reinterpret_cast<float4 *>(out + r * N + n0 + m) = make_float4(t[0], t[1], t[2], t[3]);
         }
     } else {
         for (int i = tid; i < rows * N; i += 256) out[i] = sT[(i / N) * (N + 1) + i % N];
@@ -784,9 +809,13 @@ static hipError_t launch_bwd_n(const BwdParams &p, hipStream_t s) {
     else if (p.z) hipLaunchKernelGGL((k_ss_bwd<IO, N, DISC, true, false>), grid, block, 0, s, p);
     else hipLaunchKernelGGL((k_ss_bwd<IO, N, DISC, false, false>), grid, block, 0, s, p);
     if (p.part) {
-        const int64_t slots = p.cu ? p.nslots : (int64_t)p.B * p.part_tiles;
-        dim3 g2((unsigned)(slots * (N >= 8 ? N / 4 : 1)), 2, p.bcg);
-        hipLaunchKernelGGL((k_ss_bwd_maps<N>), g2, dim3(256), 0, s, p, (int)grid.x);
+        const int64_t slots = p.cu ? p.nslots : (int64_t)p.B * p.part_tiles, pieces = slots * BwdMaps<N>::PIECES;
+        // fewer workgroups than the chip holds four times over, and more blocks than a thread has reads under way at once
+        constexpr int KS = N >= 4 ? 4 : 1;
+        const bool split = KS > 1 && pieces * 2 * p.bcg < 4 * kNumCU && (int)grid.x / p.bcg > 8;
+        dim3 g2((unsigned)(split ? pieces * KS : pieces), 2, p.bcg);
+        if (split) hipLaunchKernelGGL((k_ss_bwd_maps<N, KS>), g2, dim3(256), 0, s, p, (int)grid.x);
+        else hipLaunchKernelGGL((k_ss_bwd_maps<N, 1>), g2, dim3(256), 0, s, p, (int)grid.x);
     }
     return hipGetLastError();
 }
