@@ -904,7 +904,7 @@ void bwd_packed_shape(int B, int D, int64_t L, int64_t max_seqlen, int Gbal, int
 // launch shape incl. the chunked path for few rows and long sequences (selective_bwd_carry.hip)
 BwdPlan bwd_plan(int rowsg, int dpg, int N, int64_t L, int mode, bool balanced) {
     const int G = channels_for(rowsg, dpg, bwd_places(N), balanced), pairs = whole_passes(G);
-    const bool roomy = bwd_part_bytes(N, (L + kBwdTileSteps - 1) / kBwdTileSteps, (int64_t)rowsg * ((dpg + pairs - 1) / pairs)) <= kBwdSumsCap;
+    const bool roomy = bwd_part_bytes(N, (L + kBwdTileSteps - 1) / kBwdTileSteps, (int64_t)rowsg * ((dpg + pairs - 1) / pairs)) < kBwdSumsCap;
     BwdPlan pl = plan_time_chunks(rowsg, dpg, L, balanced ? mode : 1, G, bwd_places(N), kBwdMaxG, roomy);
     pl.G = whole_passes(pl.G);
     return pl;
