@@ -499,20 +499,52 @@ int fwd_channels_per_workgroup() { return FwdGeom<16, 16>::CH; }
 int fwd_tile_steps() { return FwdGeom<16, 16>::TILE; }
 
 // Chains the chunk aggregates of one (b,d,n): carry-in of chunk c+1 = P_c * carry-in of chunk c + S_c.
-// ws_S[c] is replaced by the carry-in of chunk c.
-__global__ void k_ss_carry(const FwdParams p) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t total = (int64_t)p.B * p.D * p.N;
-    if (i >= total) return;
-    const int64_t row = i / p.N;
-    const int n = (int)(i % p.N);
+// ws_S[c] is replaced by the carry-in of chunk c.  A workgroup takes 16 such chains and up to 256 chunks at a time: 16 threads
+// of a chain fold up to 16 consecutive pairs each, all read at once, and replay them from the state that the threads before
+// hand on through LDS.  One after the other the reads cost 0.2 us a chunk, half of the time of few long rows (16 rows of
+// 65536 steps, N = 16, float32, 256 chunks: call 83 us, so 24).
+constexpr int kCarryLen = 16;
+__global__ __launch_bounds__(256) void k_ss_carry(const FwdParams p) {
+    __shared__ float sP[kCarryLen][17], sS[kCarryLen][17];
+    const int chain = threadIdx.x % 16, seg = threadIdx.x / 16;
+    const int64_t total = (int64_t)p.B * p.D * p.N, id = blockIdx.x * (int64_t)16 + chain;
+    const int64_t i = id < total ? id : total - 1;       // (past the end: the last one again, nothing is written)
+    const int64_t first = i / p.N * p.nchunks * p.N + i % p.N;
     float x = p.x0 ? p.x0[i] : 0.0f;
-    for (int c = 0; c < p.nchunks; ++c) {
-        const int64_t j = (row * p.nchunks + c) * p.N + n;
-        if (c + 1 == p.nchunks) { p.ws_S[j] = x; break; }     // nothing follows the last chunk: its pair was not computed
-        const float P = p.ws_P[j], S = p.ws_S[j];
-        p.ws_S[j] = x;
-        x = __builtin_fmaf(P, x, S);
+    for (int c0 = 0; c0 < p.nchunks; c0 += 16 * kCarryLen) {
+        const int left = p.nchunks - c0, most = left < 16 * kCarryLen ? left : 16 * kCarryLen;
+        const int len = (most + 15) / 16, c1 = c0 + seg * len;
+        float P[kCarryLen], S[kCarryLen], fP = 1.0f, fS = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kCarryLen; ++k) {
+            P[k] = 1.0f; S[k] = 0.0f;
+            if (k < len) {
+                const int c = c1 + k < p.nchunks ? c1 + k : p.nchunks - 1;
+                P[k] = p.ws_P[first + (int64_t)c * p.N];
+                S[k] = p.ws_S[first + (int64_t)c * p.N];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kCarryLen; ++k) {
+            const bool pair = k < len && c1 + k + 1 < p.nchunks;      // nothing follows the last chunk: its pair was not computed
+            P[k] = pair ? P[k] : 1.0f; S[k] = pair ? S[k] : 0.0f;
+            fS = __builtin_fmaf(P[k], fS, S[k]);
+            fP *= P[k];
+        }
+        sP[seg][chain] = fP; sS[seg][chain] = fS;
+        __syncthreads();
+        float mine = x;
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            if (s == seg) mine = x;
+            x = __builtin_fmaf(sP[s][chain], x, sS[s][chain]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kCarryLen; ++k) {
+            if (k < len && c1 + k < p.nchunks && id < total) p.ws_S[first + (int64_t)(c1 + k) * p.N] = mine;
+            mine = __builtin_fmaf(P[k], mine, S[k]);
+        }
     }
 }
 
@@ -531,7 +563,7 @@ __global__ void k_fill(const FillList z) {
 
 hipError_t launch_ss_carry(const FwdParams &p, hipStream_t s) {
     const int64_t total = (int64_t)p.B * p.D * p.N;
-    hipLaunchKernelGGL(k_ss_carry, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(k_ss_carry, dim3((unsigned)((total + 15) / 16)), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
