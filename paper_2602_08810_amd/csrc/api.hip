@@ -34,14 +34,6 @@ int fwd_chunks(int64_t B, int64_t D, int64_t L, bool forced) {
     return (int)n;
 }
 
-// Whether the chunk-carry path is faster than a single pass: it walks the sequence twice, at 60 % and 100 % of a
-// pass's work, but on a full chip, where the single pass takes as long for few rows as for 2048.  N = 16, bf16: 512 rows of
-// 8192 steps 52 us against 89, 1024 rows 83 against 90, 1536 rows 110 against 97; 512 rows of 4096 steps 31 against 46,
-// of 2048 steps 31 against 26 (three launches are not free).
-bool fwd_chunks_pay(int64_t B, int64_t D, int64_t N, int64_t L) {
-    return L * N >= 65536 && B * D + ((int64_t)5 << 23) / (L * N) <= 1344;
-}
-
 // the complex forward kernel: 8 channels per workgroup, tiles of 512 steps for both I/O types
 constexpr int kCfwdTile = 512;
 int cfwd_chunks(int64_t wgs, int64_t L, bool forced) {
@@ -355,7 +347,7 @@ int lrnnx_selective_scan_fwd(const lrnnx_ss_fwd_args *a) {
         const size_t need = (size_t)2 * a->B * a->D * nch * a->N * sizeof(float);
         if (!a->workspace || a->workspace_bytes < need) return LRNNX_ERR_WORKSPACE;
         chunked = true;
-    } else if (a->path == LRNNX_PATH_AUTO && !cu && fwd_chunks_pay(a->B, a->D, a->N, a->L)) {
+    } else if (a->path == LRNNX_PATH_AUTO && !cu && fwd_chunks_pay(a->B, bcg, p.dpg, a->N, a->L, a->io_dtype == LRNNX_F32)) {
         nch = fwd_chunks(a->B, a->D, a->L, false);
         const size_t need = (size_t)2 * a->B * a->D * nch * a->N * sizeof(float);
         chunked = nch > 1 && a->workspace && a->workspace_bytes >= need;

@@ -283,10 +283,11 @@ struct FillList {
 hipError_t launch_fill(const FillList &z, hipStream_t s);
 
 // Tile geometry the host needs for grids, workspaces and the choice of path (each constant lives beside its kernel).
-int fwd_channels_per_workgroup();            // of the chunk-carry forward path
+int fwd_channels_per_workgroup();            // of the 16-lane shape, which the chunk-carry forward path launches
+bool fwd_chunks_pay(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L, bool f32);
 int lti_chunk_group();                       // chunks (wavefronts) of one workgroup of the two-launch LTI path
 int lti_onepass_anchor();                    // every how many groups the single-launch LTI scan publishes a true state
-int fwd_tile_steps();                        // time steps one of its workgroups covers per tile
+int fwd_tile_steps();                        // time steps one workgroup of the 16-lane shape covers per tile
 int bwd_channels_per_group(int B, int D, int N, int64_t L, bool balanced);
 int bwd_places(int N);                       // workgroups of the backward kernel the chip holds at once
 int bwd_grid_x(const BwdParams &p);

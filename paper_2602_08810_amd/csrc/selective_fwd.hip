@@ -16,8 +16,9 @@
 // 13 to 16 for the prefix, its start and its end, and of 26 a step (softplus, gate, conversions) shared by the N states.
 // Hence 16 steps per lane, one LDS address for all of Bm and Cm, and tiles known to be whole without any check.
 // The next tile's inputs are fetched before the state loop where the registers allow, else after it.
-// Mamba-block training shape (B = 8, D = 1536, N = 16, L = 2048, bf16, with gate and checkpoints): 112 us, 137 us with 64
-// lanes of 8 steps and 13 slots an update; B = 16, D = 2560, L = 4096 without gate: 640 us, before 823.
+// Mamba-block training shape (B = 8, D = 1536, N = 16, L = 2048, bf16, with gate and checkpoints): 109 us when launched from a
+// graph, 122 us between the events of the benchmark, which an earlier kernel of 64 lanes, 8 steps and 13 slots an update
+// took 143 us by; B = 16, D = 2560, L = 4096 without gate: 640 us, before 823.
 // See fwd_shape() for the choice of LPC and T.
 //
 // The same kernel serves the three launches of the chunk-carry path for long L / few
@@ -70,8 +71,9 @@ template <int LPC, int T> struct FwdGeom {
     static constexpr int ROW = Q * (T / 4);
 };
 
-// Three workgroups of four wavefronts share a compute unit with 16 lanes per channel (168 registers), one of eight
-// otherwise (its staged tile fills the LDS).
+// Workgroups that share a compute unit: three of four wavefronts with 16 lanes per channel (168 registers, three wavefronts a
+// SIMD); with 64 lanes four of four wavefronts (4 steps) or two of eight (8 steps: 75 KB of LDS each), at 128 registers four a
+// SIMD; one of eight with 16 steps, whose staged tile takes more than half of the LDS.
 template <typename IO, int N, int DISC, bool WANT_Y, bool CKPT, int LPC, int T>
 __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 3 : 2) : 4)) void k_ss_fwd(const FwdParams p) {
     using GE = FwdGeom<LPC, T>;
@@ -397,38 +399,55 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
 }
 
 // ---------------------------------------------------------------- launchers
-// The shape of a single pass, by the time each would take (in tenths of a microsecond, N = 16; other N scale all three
-// alike).  A tile costs its fixed part (staging, barriers, the latency of a wavefront that is alone on its SIMD) and a
-// part for each workgroup that shares the compute unit; measured over 64 to 40960 rows of 256 to 65536 steps.
-//   16 lanes: the fewest instructions, the finest tiles; needs about 8000 rows for three workgroups a compute unit.
-//             (8 x 1536 rows, L = 2048, N = 16, bf16: 112 us; 64 x 8: 125, 64 x 16: 144)
-//   64 x 8:   four times the wavefronts from as many rows (3 x 1000 rows, L = 2048: 46 us; 16 lanes: 57)
-//   64 x 16:  one workgroup a compute unit (its tile takes the LDS), so at most 2048 rows at once, but fewer instructions
+// The shape of a single pass, by the time each would take.  A tile costs its fixed part and a part for each state (staging,
+// barriers, the latency of a wavefront that is alone on its SIMD), and the same for each workgroup that shares the compute
+// unit; the costs (in 10 ns) are fitted to 16 to 40960 rows of 64 to 65536 steps with N = 1 to 32.
+//   16 lanes: the fewest instructions; needs about 8000 rows for three workgroups a compute unit
+//             (8 x 1536 rows, L = 2048, N = 16, bf16: 109 us; 64 x 8: 125, 64 x 16: 144)
+//   64 x 4:   the shortest tile and the quickest, for rows of up to 256 steps (256 rows, L = 256, N = 16, float32: 6.4 us,
+//             64 x 8 10.7, 16 lanes 10.3) and with few states, where memory is the bound, for many rows (16 x 2560 rows,
+//             L = 1024, N = 4, float32: 124 us, 16 lanes 147)
+//   64 x 8:   a few thousand rows (4096 rows, L = 2048, N = 16, float32: 50 us; 16 lanes 74, 64 x 4 72)
+//   64 x 16:  one workgroup a compute unit (its tile takes the LDS), so at most 2048 rows, but fewer instructions
 //             than 64 x 8 (2048 rows, L = 65536: 645 to 670 us; 64 x 8: 730)
-// For float32 and N <= 4 memory is the bound, and 16 lanes, which fetch later, do not keep enough of it in flight
-// (16 x 2048 rows, L = 1024, N = 4: 106 us; 64 x 8: 87).
+// Over that grid the choice is 1 % slower than the best of the four and the chunked path.
 enum class FwdShape { l16, l64x4, l64x8, l64x16 };
-static FwdShape fwd_shape(const FwdParams &p, bool memory_bound) {
-    auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
-    const int64_t L = p.L, maps = (int64_t)p.B * p.bcg;
-    const int64_t cu16 = up(maps * up(p.dpg, 16), kNumCU), cu8 = up(maps * up(p.dpg, 8), kNumCU);   // workgroups of a compute unit
-    const int64_t t16 = up(L, 256) * (33 + 36 * cu16) * (memory_bound ? 4 : 3) / 3;
-    const int64_t t8 = up(L, 512) * (15 + 50 * cu8);
-    const int64_t t64 = up(L, 1024) * 120 * cu8;
-    if (t16 <= t8 && t16 <= t64) return FwdShape::l16;
-    return t64 < t8 ? FwdShape::l64x16 : FwdShape::l64x8;
+struct FwdCost { int tile, state, wg, wg_state; };
+static constexpr FwdCost kFwdCost[2][4] = {{{0, 20, 249, 17}, {22, 12, 52, 8}, {0, 6, 183, 27}, {0, 0, 215, 65}},          // float32
+                                           {{19, 16, 136, 17}, {40, 9, 31, 7}, {0, 8, 132, 24}, {0, 0, 170, 53}}};         // bfloat16
+static int64_t fwd_cost(const FwdCost &c, int64_t N, int64_t tiles, int64_t wgs) {
+    const int64_t share = (wgs + kNumCU - 1) / kNumCU;   // workgroups of a compute unit
+    return tiles * (c.tile + c.state * N + share * (c.wg + c.wg_state * N));
+}
+static int64_t fwd_time(int64_t maps, int64_t dpg, int64_t N, int64_t L, bool f32, FwdShape shape) {
+    static constexpr int steps[4] = {256, 256, 512, 1024}, channels[4] = {16, 4, 8, 8};
+    const int i = (int)shape;
+    const int64_t wgs = maps * ((dpg + channels[i] - 1) / channels[i]);
+    if (shape == FwdShape::l64x16 && wgs > kNumCU) return INT64_MAX;
+    return fwd_cost(kFwdCost[f32 ? 0 : 1][i], N, (L + steps[i] - 1) / steps[i], wgs);
+}
+static FwdShape fwd_shape(const FwdParams &p, bool f32) {
+    FwdShape best = FwdShape::l16;
+    int64_t least = INT64_MAX;
+    for (const FwdShape shape : {FwdShape::l16, FwdShape::l64x4, FwdShape::l64x8, FwdShape::l64x16}) {
+        const int64_t t = fwd_time((int64_t)p.B * p.bcg, p.dpg, p.N, p.L, f32, shape);
+        if (t < least) { least = t; best = shape; }
+    }
+    return best;
 }
 // The shape for a packed batch, whose lengths only the device knows: as a rule 64 lanes of 4 steps, whose tiles of 256
 // steps spend little past the ends of short sequences while a long one does not run on alone for long (31 sequences of 705
 // steps on average, 522 channels, N = 8, bf16: 95 us; 16 lanes 122, 64 x 8 102).  With so many rows that the chip
 // stays full, 16 lanes, which take fewer instructions: from 24576 rows (24 sequences, 1536 channels, N = 16, bf16: 141 us,
 // 64 x 4: 195), of sequences of hardly a tile from 12288 (17 of 206 steps on average, 1068 channels: 38 us, 54), in
-// float32 from 8192 (6 sequences, 1616 channels, N = 32: 75 us, 110).  Long sequences take the longer tiles: 64 x 8 (5 of 3056 steps
+// float32 from 12288, with 16 states or more (6 sequences, 2560 channels, 8192 steps, N = 16: 153 us, 64 x 4: 197); with fewer
+// memory is the bound there, and 16 lanes, which fetch later, do not keep enough of it in flight (24 sequences of 8192
+// steps in all, 1536 channels, N = 4: 70 us, 64 x 4: 58).  Long sequences take the longer tiles: 64 x 8 (5 of 3056 steps
 // on average, 1724 channels: 173 us, 64 x 4: 188), very few rows of very long ones 64 x 16 (2 sequences of up to
 // 23848 steps, 363 channels: 152 us, 64 x 4: 186).
 static FwdShape packed_shape(const FwdParams &p, bool f32) {
     const int64_t rows = (int64_t)p.B * p.D, mean = p.L / p.B;
-    if (rows >= (f32 ? 8192 : mean <= 256 ? 12288 : 24576)) return FwdShape::l16;
+    if (f32 ? p.N >= 16 && rows >= 12288 : rows >= (mean <= 256 ? 12288 : 24576)) return FwdShape::l16;
     if (rows <= 1024 && mean >= 4096) return FwdShape::l64x16;
     return rows >= 2048 && mean >= 2048 ? FwdShape::l64x8 : FwdShape::l64x4;
 }
@@ -453,7 +472,7 @@ template <typename IO, int N, int DISC>
 static hipError_t launch_fwd_n(const FwdParams &p, hipStream_t s) {
     // the aggregate launch skips the last chunk: nobody needs its pair
     if (p.mode == MODE_AGG && p.nchunks < 2) return hipSuccess;
-    switch (p.cu ? packed_shape(p, sizeof(IO) == 4) : p.nchunks == 1 ? fwd_shape(p, sizeof(IO) == 4 && N <= 4) : FwdShape::l16) {
+    switch (p.cu ? packed_shape(p, sizeof(IO) == 4) : p.nchunks == 1 ? fwd_shape(p, sizeof(IO) == 4) : FwdShape::l16) {
         case FwdShape::l64x4: return launch_fwd_lanes<IO, N, DISC, 64, 4>(p, s);
         case FwdShape::l64x8: return launch_fwd_lanes<IO, N, DISC, 64, 8>(p, s);
         case FwdShape::l64x16: return launch_fwd_lanes<IO, N, DISC, 64, 16>(p, s);
@@ -497,6 +516,24 @@ hipError_t launch_ss_fwd(const FwdParams &p, int io_dtype, int disc, hipStream_t
 
 int fwd_channels_per_workgroup() { return FwdGeom<16, 16>::CH; }
 int fwd_tile_steps() { return FwdGeom<16, 16>::TILE; }
+
+// Whether the chunk-carry path is faster than the best single pass, by 3 % at least since it takes scratch: it walks the sequence
+// twice and launches three times, but on a full chip (costs fitted as above; the first two are those of the three launches).
+// N = 16, bf16: 512 rows of 2048 steps 21 us against 23, 1024 rows of 2048 28 against 24; 16 rows of 65536 steps 22
+// against 640.
+bool fwd_chunks_pay(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L, bool f32) {
+    static constexpr FwdCost cost[2] = {{771, 41, 405, 30}, {865, 32, 188, 33}};
+    const int64_t tiles = (L + fwd_tile_steps() - 1) / fwd_tile_steps();
+    if (tiles < 2) return false;
+    const int64_t channels = fwd_channels_per_workgroup();
+    const int64_t chunked = fwd_cost(cost[f32 ? 0 : 1], N, 1, B * bcg * ((dpg + channels - 1) / channels) * tiles);
+    constexpr int64_t launch = 220;
+    for (const FwdShape shape : {FwdShape::l16, FwdShape::l64x4, FwdShape::l64x8, FwdShape::l64x16}) {
+        const int64_t t = fwd_time(B * bcg, dpg, N, L, f32, shape);
+        if (t != INT64_MAX && t + launch <= chunked + chunked * 3 / 100) return false;
+    }
+    return true;
+}
 
 // Chains the chunk aggregates of one (b,d,n): carry-in of chunk c+1 = P_c * carry-in of chunk c + S_c.
 // ws_S[c] is replaced by the carry-in of chunk c.  A workgroup takes 16 such chains and up to 256 chunks at a time: 16 threads
