@@ -1,5 +1,5 @@
-"""GPU parity of the forward kernel's three shapes (16 lanes per channel; 64 lanes of 8 and of 16 steps) and of the chunked
-path at the edges of a lane, a checkpoint interval and a tile: outputs, last state and every checkpoint."""
+"""GPU parity of the forward pass at the edges of a lane, a checkpoint interval and a tile, with outputs, last state and every
+checkpoint, whatever shape the launch rule takes; the shapes over several tiles are in test_gpu_fwd_tiles.py."""
 import numpy as np
 import pytest
 
@@ -18,8 +18,7 @@ def api():
     return _api
 
 
-# B*D rows and L choose the shape: many rows 16 lanes; few rows 64 lanes, of 16 steps from 513 steps on.  Odd channel
-# counts leave lanes and wavefronts of the last workgroup without a channel; N = 32 stages its maps twice.
+# Odd channel counts leave lanes and wavefronts of the last workgroup without a channel; N = 32 stages its maps twice.
 @pytest.mark.parametrize("io", ["f32", "bf16"])
 @pytest.mark.parametrize("N,B,D,L", [
     (16, 1, 2501, 17), (32, 1, 2301, 255), (1, 1, 3001, 256), (2, 1, 2601, 100), (8, 2, 4201, 257), (16, 2, 4501, 511),
@@ -35,6 +34,7 @@ def test_forward_shapes(api, oracle, io, N, B, D, L):
     check_outputs({"y": (host(y), yr, TOL[io]), "x_last": (host(x), xr, 1e-4), "ckpt": (host(ckpt), before, 1e-4)}, disc)
 
 
+# chunks of one tile each
 @pytest.mark.parametrize("N,L", [(16, 255), (16, 257), (32, 1025), (4, 2000), (1, 513)])
 def test_forward_chunks(api, oracle, N, L):
     p = workloads.make_selective(B=2, D=21, N=N, L=L, io="f32", gate=True, with_x0=True, seed=L, bias=("uniform", -4.0, -2.0))
@@ -43,7 +43,8 @@ def test_forward_chunks(api, oracle, N, L):
     check_outputs({"y": (host(y), yr, 1e-4), "x_last": (host(x), xr, 1e-4)})
 
 
-# packed batches: many rows of short sequences 16 lanes; else 64 lanes, of 4 steps, of 8 or of 16 as the sequences get longer
+# packed batches: many rows of short sequences 16 lanes (bfloat16); else 64 lanes, of 4 steps, of 8 or of 16 as the sequences get
+# longer
 @pytest.mark.parametrize("io", ["f32", "bf16"])
 @pytest.mark.parametrize("N,D,lengths", [
     (4, 2101, (1, 255, 256, 257, 7, 300)), (16, 11, (1, 3, 256, 257, 1030, 515)), (2, 1025, (2047, 2100)), (8, 9, (4097, 5121))])
