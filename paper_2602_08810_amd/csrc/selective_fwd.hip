@@ -440,14 +440,18 @@ static FwdShape fwd_shape(const FwdParams &p, bool f32) {
 // steps on average, 522 channels, N = 8, bf16: 95 us; 16 lanes 122, 64 x 8 102).  With so many rows that the chip
 // stays full, 16 lanes, which take fewer instructions: from 24576 rows (24 sequences, 1536 channels, N = 16, bf16: 141 us,
 // 64 x 4: 195), of sequences of hardly a tile from 12288 (17 of 206 steps on average, 1068 channels: 38 us, 54), in
-// float32 from 12288, with 16 states or more (6 sequences, 2560 channels, 8192 steps, N = 16: 153 us, 64 x 4: 197); with fewer
-// memory is the bound there, and 16 lanes, which fetch later, do not keep enough of it in flight (24 sequences of 8192
-// steps in all, 1536 channels, N = 4: 70 us, 64 x 4: 58).  Long sequences take the longer tiles: 64 x 8 (5 of 3056 steps
+// float32 with 16 states or more from 14336 (6 sequences, 2560 channels, 8192 steps, N = 16: 153 us, 64 x 4: 197; 24
+// sequences, 512 channels, 32768 steps: 289, 218), of sequences of hardly a tile from 8192 (24 of 85 steps, 512 channels: 29,
+// 32).  With fewer states memory is the bound in float32, and 16 lanes, which fetch later, do not keep enough of it in flight
+// (24 sequences of 8192 steps in all, 1536 channels, N = 4: 70 us, 64 x 4: 58) except on very many rows of short sequences (24
+// of 85 steps, 2560 channels: 50, 58).  Long sequences take the longer tiles: 64 x 8 (5 of 3056 steps
 // on average, 1724 channels: 173 us, 64 x 4: 188), very few rows of very long ones 64 x 16 (2 sequences of up to
 // 23848 steps, 363 channels: 152 us, 64 x 4: 186).
 static FwdShape packed_shape(const FwdParams &p, bool f32) {
     const int64_t rows = (int64_t)p.B * p.D, mean = p.L / p.B;
-    if (f32 ? p.N >= 16 && rows >= 12288 : rows >= (mean <= 256 ? 12288 : 24576)) return FwdShape::l16;
+    const bool brief = mean <= 256;
+    const int64_t full = !f32 ? (brief ? 12288 : 24576) : p.N >= 16 ? (brief ? 8192 : 14336) : brief ? 32768 : INT64_MAX;
+    if (rows >= full) return FwdShape::l16;
     if (rows <= 1024 && mean >= 4096) return FwdShape::l64x16;
     return rows >= 2048 && mean >= 2048 ? FwdShape::l64x8 : FwdShape::l64x4;
 }
