@@ -533,7 +533,8 @@ def lrnnx_selective_scan_bwd_complex(u, delta, A, Bm, Cm, dy, Dskip=None, delta_
     if want_dx0:
         a.dx0 = new("dx0", (Bsz, D, N), c64).data_ptr()
     if workspace is None:
-        # with the forward's checkpoints only the chunk aggregates (or the launch order of a packed batch) are needed
+        # with the forward's checkpoints only the chunk aggregates (or the launch order of a packed batch) and the sums of
+        # dBm and dCm are needed
         nbytes = lrnnx_workspace_bytes(WS_BWD_COMPLEX, Bsz, D, N, L, a.io_dtype, G, packed)
         if ckpt is not None:
             nbytes -= (ckpt.numel() * 8 + 255) // 256 * 256

@@ -142,21 +142,22 @@ void fit_chunks(BwdPlan &pl, size_t nfit) {
     pl.nchunks = (int)nfit;
 }
 
-// Scratch for the tile sums of dBm and dCm of a real backward call (LRNNX_WS_BWD_SUMS): what the widest launch takes among those the
-// host may choose for this shape (by path, and for a packed batch by its longest sequence) that need no more than
-// kBwdSumsCap.
-size_t bwd_sums_bytes(int64_t B, int64_t D, int64_t N, int64_t L, int64_t bcg, bool packed) {
+// Scratch for the tile sums of dBm and dCm of a backward call, real (LRNNX_WS_BWD_SUMS) or complex (`plan` is its bwd_plan resp.
+// cbwd_plan, `floats` the floats of a state): what the widest launch takes among those the host may choose for this shape (by
+// path, and for a packed batch by its longest sequence) that need no more than kBwdSumsCap.
+template <typename Plan>
+size_t bwd_sums_bytes(Plan plan, int floats, int64_t B, int64_t D, int64_t N, int64_t L, int64_t bcg, bool packed) {
     const int64_t dpg = D / bcg;
     size_t most = 0;
     auto widest = [&](int64_t G) {
-        const size_t n = bwd_part_bytes((int)N, packed ? lrnnx_packed_ckpt_slots(L, B) : B * cdiv(L, kBwdTileSteps), bcg * cdiv(dpg, G));
+        const size_t n = bwd_part_bytes((int)N * floats, packed ? lrnnx_packed_ckpt_slots(L, B) : B * cdiv(L, kBwdTileSteps), bcg * cdiv(dpg, G));
         if (n <= kBwdSumsCap && n > most) most = n;
     };
     if (packed)
         for (int64_t G = kBwdMinG; !most && G < dpg + 2; G += 2) widest(G);
     else
         for (int path = LRNNX_PATH_AUTO; path <= LRNNX_PATH_CHUNK_CARRY; ++path)
-            widest(bwd_plan((int)(B * bcg), (int)dpg, (int)N, L, path, true).G);
+            widest(plan((int)(B * bcg), (int)dpg, (int)N, L, path, true).G);
     return most;
 }
 
@@ -275,7 +276,7 @@ size_t lrnnx_workspace_bytes(int which, int64_t B, int64_t D, int64_t N, int64_t
         const bool cplx = which == LRNNX_WS_FWD_COMPLEX || which == LRNNX_WS_BWD_COMPLEX;
         if (!(cplx ? supported_n_complex((int)N) : supported_n((int)N)) || D % bcg) return 0;
         const size_t es = cplx ? sizeof(float2) : sizeof(float);
-        if (which == LRNNX_WS_BWD_SUMS) return bwd_sums_bytes(B, D, N, L, bcg, packed != 0) + 512;
+        if (which == LRNNX_WS_BWD_SUMS) return bwd_sums_bytes(bwd_plan, 1, B, D, N, L, bcg, packed != 0) + 512;
         if (which == LRNNX_WS_FWD) return packed ? 0 : (size_t)2 * B * D * fwd_chunks(B, D, L, true) * N * es;
         if (which == LRNNX_WS_FWD_COMPLEX)
             return packed ? 0 : (size_t)2 * B * D * cfwd_chunks(B * bcg * cdiv(D / bcg, 8), L, true) * N * es;
@@ -286,7 +287,10 @@ size_t lrnnx_workspace_bytes(int which, int64_t B, int64_t D, int64_t N, int64_t
             ck = align256((size_t)(packed ? D * lrnnx_packed_ckpt_slots(L, B) : B * D * cdiv(L, kCkptInterval)) * N * es);
         const size_t carry = cplx ? cbwd_carry_bytes(B * bcg, D / bcg, N, L) : bwd_carry_bytes(B * bcg, D / bcg, N, L);
         const size_t order = packed ? sizeof(int) * (size_t)B : 0;
-        return ck + (carry > order ? carry : order);
+        const size_t base = ck + (carry > order ? carry : order);
+        if (!cplx) return base;
+        const size_t sums = bwd_sums_bytes(cbwd_plan, 2, B, D, N, L, bcg, packed != 0);
+        return cbwd_sums_pay((int)N, cdiv(L, kBwdTileSteps), packed != 0, sums) ? base + sums + 512 : base;
     }
     if (which == LRNNX_WS_LTI) {
         const int nch = lti_chunks(B, D, L);
@@ -512,13 +516,15 @@ int lrnnx_selective_scan_bwd_complex(const lrnnx_ss_bwd_complex_args *a) {
     p.G = pl.G;
     p.nchunks = pl.nchunks;
     p.tiles_per_chunk = pl.tiles_per_chunk;
+    size_t used = carry_off;                       // bytes of the workspace taken so far
     if (cu && pl.nchunks == 1)
         bwd_packed_shape(a->B, a->D, a->L, a->max_seqlen, cbwd_channels_per_group(a->B * bcg, a->D / bcg, a->N, true),
-                         a->N >= 16 ? 256 : 512, &p.G, &p.wcap, &p.gmin);
+                         cbwd_places(a->N), &p.G, &p.wcap, &p.gmin);
     if (pl.nchunks > 1) {
         p.ws_P = reinterpret_cast<float2 *>(static_cast<char *>(a->workspace) + carry_off);
         p.ws_Q = p.ws_P + (size_t)a->B * a->D * p.nchunks * a->N;
         p.hc = p.ws_Q;
+        used += (size_t)2 * a->B * a->D * p.nchunks * a->N * sizeof(float2);
         if (launch_ss_cbwd_agg(p, a->io_dtype, a->disc, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
         if (launch_ss_cbwd_carry(p, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
     }
@@ -528,12 +534,22 @@ int lrnnx_selective_scan_bwd_complex(const lrnnx_ss_bwd_complex_args *a) {
         int *order = reinterpret_cast<int *>(static_cast<char *>(a->workspace) + carry_off);
         if (launch_seq_order(cu, a->B, a->L, order, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
         p.order = order;
+        used = carry_off + sizeof(int) * (size_t)a->B;
     }
+    // room behind that for the tile sums of dBm and dCm
+    p.part_tiles = cdiv(a->L, kBwdTileSteps);
+    const uintptr_t part = align256(reinterpret_cast<uintptr_t>(a->workspace) + used);
+    const uintptr_t end = reinterpret_cast<uintptr_t>(a->workspace) + a->workspace_bytes;
+    const size_t part_need = bwd_part_bytes(2 * a->N, cu ? nslots : a->B * p.part_tiles, cbwd_grid_x(p));
+    if (cbwd_sums_pay(a->N, p.part_tiles, cu != nullptr, part_need) && a->workspace && part <= end && part_need <= end - part)
+        p.part = reinterpret_cast<float *>(part);
 
     const int64_t nbc = (cu ? 1 : (int64_t)a->B) * bcg * a->L * a->N * 2;   // floats; packed mode: one time axis for all sequences
     FillList z{};
-    z.ptr[0] = reinterpret_cast<float *>(a->dBm); z.count[0] = nbc;
-    z.ptr[1] = reinterpret_cast<float *>(a->dCm); z.count[1] = nbc;
+    if (!p.part || cu) {                           // (rows of a packed batch outside every sequence are zero in any case)
+        z.ptr[0] = reinterpret_cast<float *>(a->dBm); z.count[0] = nbc;
+        z.ptr[1] = reinterpret_cast<float *>(a->dCm); z.count[1] = nbc;
+    }
     z.ptr[2] = reinterpret_cast<float *>(a->dA); z.count[2] = (int64_t)a->D * a->N * 2;
     z.ptr[3] = a->dD; z.count[3] = a->D;
     z.ptr[4] = a->dbias; z.count[4] = a->D;

@@ -77,6 +77,8 @@ struct CBwdParams {
     const float2 *hc;
     const int *order;        // packed mode: sequences in the order the launch should start them, or null
     int wcap, gmin;          // packed mode with a known longest sequence: as in BwdParams
+    float *part;             // workspace of the tile sums of dBm and dCm, as in BwdParams (two floats a state), or null
+    int64_t part_tiles;
 };
 
 struct BwdParams {
@@ -199,7 +201,11 @@ hipError_t launch_ss_carry(const FwdParams &p, hipStream_t s);
 hipError_t launch_ss_cfwd(const CFwdParams &p, int io_dtype, int disc, hipStream_t s);
 hipError_t launch_ss_cbwd(const CBwdParams &p, int io_dtype, int disc, hipStream_t s);
 int cbwd_channels_per_group(int B, int D, int N, bool balanced);
+int cbwd_grid_x(const CBwdParams &p);
+bool cbwd_sums_pay(int N, int64_t tiles, bool packed, size_t bytes);   // tile sums through the workspace, not with atomics
+int cbwd_places(int N);                      // workgroups of the complex backward kernel the chip holds at once
 hipError_t launch_ss_bwd(const BwdParams &p, int io_dtype, int disc, hipStream_t s);
+hipError_t launch_bwd_maps(const BwdParams &p, int grid_x, hipStream_t s);   // sums the tiles of p.part, of p.N states, over the channel blocks
 hipError_t launch_ss_bwd_agg(const BwdParams &p, int io_dtype, int disc, hipStream_t s);   // chunk aggregates -> ws_P, ws_Q
 hipError_t launch_ss_bwd_carry(const BwdParams &p, hipStream_t s);                         // ws_Q -> carries, in place
 // Launch shape of the backward pass: channels per workgroup, and (chunks > 1) the chunked path's cut of the time axis

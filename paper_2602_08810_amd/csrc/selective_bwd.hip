@@ -808,16 +808,7 @@ static hipError_t launch_bwd_n(const BwdParams &p, hipStream_t s) {
     else if (p.part) hipLaunchKernelGGL((k_ss_bwd<IO, N, DISC, false, true>), grid, block, 0, s, p);
     else if (p.z) hipLaunchKernelGGL((k_ss_bwd<IO, N, DISC, true, false>), grid, block, 0, s, p);
     else hipLaunchKernelGGL((k_ss_bwd<IO, N, DISC, false, false>), grid, block, 0, s, p);
-    if (p.part) {
-        const int64_t slots = p.cu ? p.nslots : (int64_t)p.B * p.part_tiles, pieces = slots * BwdMaps<N>::PIECES;
-        // fewer workgroups than the chip holds four times over, and more blocks than a thread has reads under way at once
-        constexpr int KS = N >= 4 ? 4 : 1;
-        const bool split = KS > 1 && pieces * 2 * p.bcg < 4 * kNumCU && (int)grid.x / p.bcg > 8;
-        dim3 g2((unsigned)(split ? pieces * KS : pieces), 2, p.bcg);
-        if (split) hipLaunchKernelGGL((k_ss_bwd_maps<N, KS>), g2, dim3(256), 0, s, p, (int)grid.x);
-        else hipLaunchKernelGGL((k_ss_bwd_maps<N, 1>), g2, dim3(256), 0, s, p, (int)grid.x);
-    }
-    return hipGetLastError();
+    return p.part ? launch_bwd_maps(p, (int)grid.x, s) : hipGetLastError();
 }
 
 template <typename IO, int DISC>
@@ -851,6 +842,29 @@ hipError_t launch_ss_bwd_f32(const BwdParams &p, int disc, hipStream_t s) { retu
 #else
 hipError_t launch_ss_bwd(const BwdParams &p, int io_dtype, int disc, hipStream_t s) {
     return io_dtype == 1 ? launch_bwd_io<bf16_t>(p, disc, s) : launch_ss_bwd_f32(p, disc, s);
+}
+
+template <int N>
+static hipError_t launch_bwd_maps_n(const BwdParams &p, int gx, hipStream_t s) {
+    const int64_t slots = p.cu ? p.nslots : (int64_t)p.B * p.part_tiles, pieces = slots * BwdMaps<N>::PIECES;
+    // fewer workgroups than the chip holds four times over, and more blocks than a thread has reads under way at once
+    constexpr int KS = N >= 4 ? 4 : 1;
+    const bool split = KS > 1 && pieces * 2 * p.bcg < 4 * kNumCU && gx / p.bcg > 8;
+    dim3 g2((unsigned)(split ? pieces * KS : pieces), 2, p.bcg);
+    if (split) hipLaunchKernelGGL((k_ss_bwd_maps<N, KS>), g2, dim3(256), 0, s, p, gx);
+    else hipLaunchKernelGGL((k_ss_bwd_maps<N, 1>), g2, dim3(256), 0, s, p, gx);
+    return hipGetLastError();
+}
+hipError_t launch_bwd_maps(const BwdParams &p, int gx, hipStream_t s) {
+    switch (p.N) {
+        case 1: return launch_bwd_maps_n<1>(p, gx, s);
+        case 2: return launch_bwd_maps_n<2>(p, gx, s);
+        case 4: return launch_bwd_maps_n<4>(p, gx, s);
+        case 8: return launch_bwd_maps_n<8>(p, gx, s);
+        case 16: return launch_bwd_maps_n<16>(p, gx, s);
+        case 32: return launch_bwd_maps_n<32>(p, gx, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 // Workgroups the chip holds at once: two wavefronts per SIMD are what the registers allow.

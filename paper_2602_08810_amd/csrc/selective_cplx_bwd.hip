@@ -4,84 +4,167 @@
 // (Eq. 2 of the paper with a complex diagonal A as in the layers of Sec. 2.2.1, states recomputed from checkpoints
 // as Sec. 3 prescribes for the real scan).
 //
-// The gradient of the real loss with respect to a complex quantity q is dLoss/dRe q + i dLoss/dIm q.  With it, for
-// one (b,d) row and one state n, H_l = grad x_l:
-//     H_l       = dypre_l conj(Cm_l) + conj(a_{l+1}) H_{l+1}        (the same affine scan, time reversed)
-//     dCm_l    += dypre_l conj(x_l)            dBm_l += H_l conj(g_l) u_l
-//     du_l     += Re(H_l conj(g_l Bm_l))       grad a_l = H_l conj(x_{l-1})     grad g_l = H_l conj(Bm_l) u_l
-//     dDelta_l += Re(grad a_l conj(da/dDelta) + grad g_l conj(dg/dDelta))
-//     dA_n     += grad a_l conj(da/dA) + grad g_l conj(dg/dA)
+// The gradient of the real loss with respect to a complex quantity q is dLoss/dRe q + i dLoss/dIm q.  The kernel carries
+// the conjugates of all of them: with K_l the conjugate of grad x_l every conjugation of the chain rule drops out (a and g
+// are holomorphic in A), and it is put back where a gradient leaves the kernel.  For one (b,d) row and one state n:
+//     K_l       = Cm_l dypre_l + a_{l+1} K_{l+1}                    (the same affine scan, time reversed)
+//     dCm_l*   += dypre_l x_l              dBm_l* += K_l g_l u_l
+//     du_l     += Re(K_l g_l Bm_l)         grad a_l* = K_l x_{l-1}        grad g_l* = K_l Bm_l u_l
+//     dDelta_l += Re(grad a_l* da/dDelta + grad g_l* dg/dDelta)
+//     dA_n*    += grad a_l* da/dA + grad g_l* dg/dA
 //
-// Mapping: that of the real backward kernel.  Time runs along the lanes (a lane owns T consecutive steps of a tile),
-// the N states are split over the W = N/NK wavefronts of a workgroup, which work on the same channel at the same
-// time and loop over G channels, so the sums of dBm/dCm over channels stay in registers.  Both complex maps of the
-// tile live in LDS as fp32 pairs (converted once per tile), in slices private to the wavefront that owns
-// the states.  What is summed over n (du, dDelta, ypre) goes through LDS once per (channel, tile).
+// Mapping: that of the real backward kernel (selective_bwd.hip).  A workgroup of W = N/2 wavefronts works on one tile of 256
+// steps at a time, last tile first, and on two channels at a time: the halves of a wavefront are the two channels, a lane of
+// a half owns T = 8 consecutive steps.  A wavefront holds two states.  The two rows of 16 lanes of a half hold alternate
+// pieces of the tile: lane i of row r has the steps 16 i + 8 r .. 16 i + 8 r + 7.  After the lanes' folds a row swap then
+// gives the lanes of row 0 both pieces of state 0 and those of row 1 both pieces of state 1, so that one scan over the 16
+// lanes of a row serves both states (piece_scans): 92 vector instructions for both scans of two states, 174 with a scan over
+// 32 lanes for each.  A lane's sums of dBm and dCm over the channels of the workgroup stay in registers; both maps of the tile
+// sit in LDS as fp32 pairs, and what is summed over states (ypre, du, dDelta) goes through LDS once per pair of channels.
+//
+// What bounds it: vector-ALU issue, 65 instructions per state update (57.6 of them in the main part, among them 18 folds and
+// replays with two multiply-adds a component, 9 for the multiplier, 6 for the scans), 81 % of the issue slots in use; the rest is
+// lost where a wavefront waits for LDS or at the one barrier of a pass and the other of its SIMD cannot fill in alone.
+// B=8, D=1536, N=16, L=2048, bf16: 1505 us with time on 64 lanes of 4 steps and a scan of 64 lanes for each state (116
+// instructions an update), now 935; B=4, D=2560, L=2048: call 1288 us, now 811; N = 4: 686, now 265.
 #include "kernels.hpp"
 #include "scan_common.hpp"
 #include "cplx_common.hpp"
+#include <type_traits>
 
 namespace lrnnx {
 
 constexpr int kMaxGc = 64;
 
-namespace {
+// Geometry of a workgroup for N states.
+template <int N> struct CBwdGeom {
+    static constexpr int NS = N >= 2 ? 2 : 1;        // states of a wavefront
+    static constexpr int W = N / NS;                 // wavefronts
+    static constexpr int NT = W * 64;
+    static constexpr int CP = 2;                     // channels per pass
+    static constexpr bool OWN = W == 1;              // a lane's steps of the main part are its own of prologue and epilogue
+    // eight wavefronts: the first four prepare the next pair while the last four finish the one before (two steps a thread:
+    // with one step a thread the fixed part of both would be paid twice)
+    static constexpr bool SPLIT = W == 8;
+    static constexpr int NA = SPLIT ? NT / 2 : NT;   // threads of a prologue or an epilogue
+    static constexpr int TPT = CP * kBwdTileSteps / NA;       // steps of a thread there
+    static constexpr int NTC = kBwdTileSteps / TPT;           // threads that share a channel there
+    static constexpr int NB = W >= 4 ? 2 : 1;        // buffers of the inputs
+    // planes of the inputs: Delta, u, dypre (eight wavefronts: and d softplus, dz factor; one wavefront: u and the latter two,
+    // which it needs again only after its main part)
+    static constexpr int IN = SPLIT ? 5 : 3;
+};
 
-// Sum over the 32 lanes of each half-wavefront of four per-lane values at once: two exchange steps leave each lane
-// of a quad with the quad's sum of ONE value (lane%4 = 0,1,2,3 -> value 0,2,1,3), two rotations sum the quads of a
-// row, one row-pair swap sums the two rows.  Lanes 0-3 and 32-35 own the results.
-__device__ __forceinline__ float half_sum4(const float *v4, int lane) {
-    const bool b0 = lane & 1, b1 = lane & 2;
-    float kA = b0 ? v4[2] : v4[0], kB = b0 ? v4[3] : v4[1];
-    const float sA = b0 ? v4[0] : v4[2], sB = b0 ? v4[1] : v4[3];
-    kA += dpp<0xB1>(0.0f, sA);                                  // quad_perm [1,0,3,2]
-    kB += dpp<0xB1>(0.0f, sB);
-    float v = b1 ? kB : kA;
-    v += dpp<0x4E>(0.0f, b1 ? kA : kB);                         // quad_perm [2,3,0,1]
-    v += dpp<0x124>(0.0f, v);                                   // row_ror:4
-    v += dpp<0x128>(0.0f, v);                                   // row_ror:8
-    return sum_xor16(v);
+// The lane of a half that owns piece q of the tile (8 steps each), and the place of step f in a plane of 256 floats in LDS:
+// [step % 8 / 4][lane][step % 4], the second half rotated by half the banks (see step_slot in selective_bwd.hip).
+__device__ __forceinline__ int piece_lane(int q) { return ((q & 1) << 4) + (q >> 1); }
+__device__ __forceinline__ int cstep_slot(int f) {
+    return ((f & 4) << 5) + ((piece_lane(f >> 3) << 2) ^ ((f & 4) << 3)) + (f & 3);
 }
-__device__ __forceinline__ float half_sum(float v) {
-    v += dpp<0xB1>(0.0f, v);
-    v += dpp<0x4E>(0.0f, v);
-    v += dpp<0x124>(0.0f, v);
-    v += dpp<0x128>(0.0f, v);
-    return sum_xor16(v);
+template <int CNT>
+__device__ __forceinline__ void csteps_read(const float *plane, int slot, float *out) {
+    if constexpr (CNT == 2) { const float2 v = *reinterpret_cast<const float2 *>(plane + slot); out[0] = v.x; out[1] = v.y; }
+    else {
+#pragma unroll
+        for (int q = 0; q < CNT / 4; ++q) {
+            const float4 v = *reinterpret_cast<const float4 *>(plane + (q ? (slot ^ 32) + 128 : slot));
+            out[4 * q] = v.x; out[4 * q + 1] = v.y; out[4 * q + 2] = v.z; out[4 * q + 3] = v.w;
+        }
+    }
+}
+template <int CNT>
+__device__ __forceinline__ void csteps_write(float *plane, int slot, const float *v) {
+    if constexpr (CNT == 2) *reinterpret_cast<float2 *>(plane + slot) = make_float2(v[0], v[1]);
+    else {
+#pragma unroll
+        for (int q = 0; q < CNT / 4; ++q)
+            *reinterpret_cast<float4 *>(plane + (q ? (slot ^ 32) + 128 : slot)) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    }
 }
 
-}  // namespace
+// Over the 16 lanes of each row: S becomes the inclusive prefix (lane 0 first) of the pairs (P, S), Q the inclusive suffix
+// (lane 15 first) of the pairs (P, Q); X the prefix of the lane before, Y the suffix of the lane after (lane 0 resp. 15
+// keeps what it came with).  A step needs the product over the lanes up to its own for S and from its own on for Q: the
+// latter is the former of a lane further on.  Lanes whose source does not exist are left unchanged (the products are then
+// not complete, and not used).  A DPP read comes two instructions or more after the write of its register.
+__device__ __forceinline__ void crow_scans(float2 P, float2 &S, float2 &Q, float2 &X, float2 &Y) {
+    float t, u, nx, ny, rx, ry;
+#define LRNNX_ROW " row_mask:0xf bank_mask:0xf\n\t"
+    // S += shr(S) P, Q += shl(Q) R of distance D; (NX, NY): the product over twice the distance
+#define LRNNX_CS(D, PX, PY, RX, RY, M1, M2, M3, M4)                                                                       \
+    "v_mov_b32 %4, %0\n\tv_mov_b32 %5, %2\n\t" M1                                                                          \
+    "v_fmac_f32_dpp %0, %0, " PX " row_shr:" #D LRNNX_ROW "v_fmac_f32_dpp %2, %2, " RX " row_shl:" #D LRNNX_ROW M2         \
+    "v_fmac_f32_dpp %0, -%1, " PY " row_shr:" #D LRNNX_ROW "v_fmac_f32_dpp %2, -%3, " RY " row_shl:" #D LRNNX_ROW M3       \
+    "v_fmac_f32_dpp %1, %1, " PX " row_shr:" #D LRNNX_ROW "v_fmac_f32_dpp %3, %3, " RX " row_shl:" #D LRNNX_ROW            \
+    "v_fmac_f32_dpp %1, %4, " PY " row_shr:" #D LRNNX_ROW "v_fmac_f32_dpp %3, %5, " RY " row_shl:" #D LRNNX_ROW M4
+#define LRNNX_CSP(D, E, PX, PY, RX, RY, NX, NY)                                                                           \
+    LRNNX_CS(D, PX, PY, RX, RY, "v_mul_f32_dpp " NX ", " PX ", " PX " row_shr:" #D LRNNX_ROW,                              \
+             "v_fmac_f32_dpp " NX ", -" PY ", " PY " row_shr:" #D LRNNX_ROW "v_mul_f32_dpp " NY ", " PX ", " PY " row_shr:" #D LRNNX_ROW, \
+             "v_fmac_f32_dpp " NY ", " PY ", " PX " row_shr:" #D LRNNX_ROW,                                                \
+             "v_mov_b32_dpp %8, " NX " row_shl:" #E LRNNX_ROW "v_mov_b32_dpp %9, " NY " row_shl:" #E LRNNX_ROW)
+    asm("s_nop 1\n\t"
+        LRNNX_CSP(1, 1, "%10", "%11", "%10", "%11", "%6", "%7")
+        LRNNX_CSP(2, 3, "%6", "%7", "%8", "%9", "%10", "%11")
+        LRNNX_CSP(4, 7, "%10", "%11", "%8", "%9", "%6", "%7")
+        LRNNX_CS(8, "%6", "%7", "%8", "%9", "", "", "",
+                 "v_mov_b32_dpp %12, %0 row_shr:1" LRNNX_ROW "v_mov_b32_dpp %14, %2 row_shl:1" LRNNX_ROW
+                 "v_mov_b32_dpp %13, %1 row_shr:1" LRNNX_ROW "v_mov_b32_dpp %15, %3 row_shl:1 row_mask:0xf bank_mask:0xf")
+        : "+v"(S.x), "+v"(S.y), "+v"(Q.x), "+v"(Q.y), "=&v"(t), "=&v"(u), "=&v"(nx), "=&v"(ny), "=&v"(rx), "=&v"(ry),
+          "+v"(P.x), "+v"(P.y), "+v"(X.x), "+v"(X.y), "+v"(Y.x), "+v"(Y.y));
+#undef LRNNX_CSP
+#undef LRNNX_CS
+#undef LRNNX_ROW
+}
 
-template <typename IO, int N, int NK, int T, int DISC>
-__global__ __launch_bounds__((N / NK) * 64, 2) void k_ss_cbwd(const CBwdParams p) {
+// rows of two registers: on return a holds the even rows of both (a's first), b the odd rows
+__device__ __forceinline__ void swap_rows(float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)f2i(a), (unsigned)f2i(b), false, false);
+    a = i2f((int)r[0]); b = i2f((int)r[1]);
+}
+__device__ __forceinline__ void swap_rows(float2 &a, float2 &b) { swap_rows(a.x, b.x); swap_rows(a.y, b.y); }
+
+// Both scans of a state over the tile, in a row of lanes that holds its even pieces (E) and its odd ones (O): xc is the
+// state entering the tile (lane 0 of the row, zero elsewhere), hc the adjoint entering it from the later side (lane 15).
+// On return xE, xO are the states entering the pieces, gE, gO the adjoints entering them from the later side; the result is
+// the adjoint leaving the tile on the earlier side (lane 0).
+__device__ __forceinline__ float2 piece_scans(float2 PE, float2 SE, float2 QE, float2 PO, float2 SO, float2 QO, float2 xc,
+                                              float2 hc, float2 &xE, float2 &xO, float2 &gE, float2 &gO) {
+    const float2 P = cxmul(PE, PO);
+    float2 S = cxfma(PO, SE, SO), Q = cxfma(PE, QO, QE);
+    S = cxfma(P, xc, S);
+    Q = cxfma(P, hc, Q);
+    crow_scans(P, S, Q, xc, hc);
+    xE = xc; gO = hc;
+    xO = cxfma(PE, xE, SE);
+    gE = cxfma(PO, gO, QO);
+    return Q;
+}
+
+template <typename IO, int N, int DISC, bool HAS_Z>
+__global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams p) {
     using CW = typename cword<IO>::type;
-    constexpr int W = N / NK;
-    constexpr int NT = W * 64;
-    constexpr int TILE = 64 * T;
-    constexpr int TPW = TILE / NT > 0 ? TILE / NT : 1;   // flat steps per thread in prologue / epilogue
-    constexpr int NA = TILE / TPW;                   // threads that take part in them (all, or the first wavefronts)
-    constexpr int TQ = T / 4;
-    constexpr int CK_PER_TILE = TILE / (int)kCkptInterval;
-    constexpr int FL = 16;                           // lanes whose dBm/dCm sums are flushed together
-    static_assert(T % 4 == 0 && (T % W == 0 || W % T == 0) && TPW <= 8 && NA % 64 == 0 && NA <= NT, "tile shape");
-    static_assert(TILE % kCkptInterval == 0, "tiles must start on checkpoints");
-    static_assert(TILE == kBwdTileSteps, "the chunked launch counts its chunks in tiles of this kernel");
-    static_assert(W * 3 * TILE >= 2 * FL * T * N * 2, "flush buffer must fit in the partials area");
+    using GE = CBwdGeom<N>;
+    constexpr int W = GE::W, NS = GE::NS, NT = GE::NT, CP = GE::CP, TPT = GE::TPT, NTC = GE::NTC, NA = GE::NA, NB = GE::NB;
+    constexpr bool OWN = GE::OWN, SPLIT = GE::SPLIT;
+    constexpr int T = 8, TILE = kBwdTileSteps;
+    // two states side by side; the exact zero-order hold takes one after the other, since it also keeps the gains
+    constexpr bool PAIR = NS == 2 && DISC != DISC_ZOH;
+    static_assert(TILE == kCkptInterval && TILE == 32 * T, "a tile is one checkpoint interval and one half-wavefront");
 
-    __shared__ __attribute__((aligned(16))) float sIn[2][5 * TILE];       // two channels in flight: delta, u, dypre, d softplus, dz factor; [q][lane][4]
-    __shared__ __attribute__((aligned(16))) float sPart[W * 3 * TILE];    // per wave: ypre, du, ddelta partials
-    // maps of the tile as fp32 pairs: [n][t/2][lane][t%2], wave-private slices (converted once per tile; every channel
-    // of the workgroup then reads them five times)
-    __shared__ __attribute__((aligned(16))) float2 sB[N * TILE];
-    __shared__ __attribute__((aligned(16))) float2 sC[N * TILE];
-    __shared__ float2 sH[kMaxGc * N];     // conj(a_{l0}) H_{l0} carried to the earlier tile, per (channel, n)
-    __shared__ float sdA[2][kMaxGc * N * 2];   // per half-wavefront partial sums of dA, (re, im) pairs
-    __shared__ float sdD[2 * W * kMaxGc]; // dD and dbias partial sums per (half-wavefront, wavefront, channel)
-    __shared__ float sdb[2 * W * kMaxGc];
+    __shared__ __attribute__((aligned(16))) float sIn[NB][CP][GE::IN][TILE];
+    __shared__ __attribute__((aligned(16))) float sPart[CP][W][3][OWN ? 4 : TILE];      // per wavefront: ypre, du, ddelta partials
+    __shared__ __attribute__((aligned(16))) float2 sB[N * TILE], sC[N * TILE];          // maps of the tile, see map_at
+    __shared__ __attribute__((aligned(16))) float2 sH[kMaxGc * N];      // a_{l0} K_{l0} carried to the earlier tile, per (channel, n)
+    __shared__ __attribute__((aligned(16))) float2 sAC[NB][2][CP][N];   // A and the state entering the tile, of a pair
+    __shared__ float2 sdA[kMaxGc * N];
+    __shared__ float sdD[kMaxGc], sdb[kMaxGc], sDskip[kMaxGc], sBias[kMaxGc];
+    __shared__ __attribute__((aligned(8))) float2 sZero;
+    __shared__ int sDone;                            // wavefronts that have finished with the partial sums of a pass, all passes
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n0 = w * NS;                           // this wavefront's first state
     const int b = p.order ? p.order[blockIdx.y] : blockIdx.y;   // packed batches: the longest sequences start first
     // Packed variable-length mode (p.cu != nullptr): batch entry b is the sequence of steps cu[b] .. cu[b+1]-1 of ONE
     // packed time axis of p.L steps; I/O rows have no batch stride, the maps and their gradients are [G, p.L, N].
@@ -99,7 +182,10 @@ __global__ __launch_bounds__((N / NK) * 64, 2) void k_ss_cbwd(const CBwdParams p
     // sequence that ends before their chunk leave here, all threads together and before any barrier (chunk 0 stays
     // even for an empty sequence: it writes that sequence's dx0).
     const int chunk = blockIdx.z;
+    const int64_t slot0 = p.cu ? toff / TILE + b : (int64_t)b * p.part_tiles;    // first tile of this entry among all tiles
+    int64_t tile_first = 0;                          // first tile of the chunk within its sequence
     if (p.nchunks > 1) {
+        tile_first = chunk * p.tiles_per_chunk;
         const int64_t span = p.tiles_per_chunk * TILE;
         const int64_t left = L - chunk * span;
         if (chunk > 0 && left <= 0) return;
@@ -113,475 +199,607 @@ __global__ __launch_bounds__((N / NK) * 64, 2) void k_ss_cbwd(const CBwdParams p
     int G = p.G;
     if (p.wcap > 0) {
         const int64_t fit = p.wcap / (ntiles > 0 ? ntiles : 1);
-        G = fit < p.gmin ? p.gmin : (fit < G ? (int)fit : G);
+        G = fit < p.gmin ? p.gmin : (fit < G ? (int)fit & ~1 : G);       // (channels are walked in pairs)
     }
-    const int chunks_per_grp = (p.dpg + G - 1) / G;
-    if ((int)blockIdx.x >= p.bcg * chunks_per_grp) return;
-    const int grp = blockIdx.x / chunks_per_grp;
-    const int din0 = (blockIdx.x % chunks_per_grp) * G;
+    const int blocks_per_grp = (p.dpg + G - 1) / G;
+    if ((int)blockIdx.x >= p.bcg * blocks_per_grp) return;
+    const int grp = blockIdx.x / blocks_per_grp;
+    const int din0 = (blockIdx.x % blocks_per_grp) * G;
     const int d0 = grp * p.dpg + din0;
     const int Gact = (p.dpg - din0 < G) ? p.dpg - din0 : G;
     // checkpoints of this workgroup's rows: [B,D,nck,N], or packed [D,nslots,N] with sequence b at slot toff/interval + b
     const int64_t nck = p.cu ? p.nslots : (p.L + kCkptInterval - 1) / kCkptInterval;
     const int64_t ck0 = p.cu ? toff / kCkptInterval + b : toff / kCkptInterval;
+    const float2 *ckrow = p.ckpt + (((p.cu ? (int64_t)d0 : (int64_t)b * p.D + d0) * nck) + ck0) * N;
     const bool vec = p.vec != 0;
-    const bool has_z = p.z != nullptr;
 
-    for (int i = tid; i < kMaxGc * N; i += NT) {
+    for (int i = tid; i < Gact * N; i += NT) {
         float2 h = make_float2(0.0f, 0.0f);
-        if (p.nchunks > 1 && i < Gact * N)
-            h = p.hc[(((int64_t)b * p.D + d0 + i / N) * p.nchunks + chunk) * N + i % N];
-        sH[i] = h;
-        sdA[0][2 * i] = 0.0f; sdA[0][2 * i + 1] = 0.0f; sdA[1][2 * i] = 0.0f; sdA[1][2 * i + 1] = 0.0f;
+        if (p.nchunks > 1) { h = p.hc[(((int64_t)b * p.D + d0 + i / N) * p.nchunks + chunk) * N + i % N]; h.y = -h.y; }
+        sH[i] = h; sdA[i] = make_float2(0.0f, 0.0f);
     }
-    for (int i = tid; i < 2 * W * kMaxGc; i += NT) { sdD[i] = 0.0f; sdb[i] = 0.0f; }
+    for (int i = tid; i < Gact; i += NT) {
+        sdD[i] = 0.0f; sdb[i] = 0.0f;
+        sDskip[i] = p.Dskip ? p.Dskip[d0 + i] : 0.0f;
+        sBias[i] = p.bias ? p.bias[d0 + i] : 0.0f;
+    }
+    if (tid == 0) { sZero = make_float2(0.0f, 0.0f); sDone = 0; }
+    [[maybe_unused]] int done = 0;                   // what sDone has to reach before the partial sums may be written again
 
     const int64_t bc0 = ((bs * p.bcg + grp) * p.L + toff) * N;       // first complex element of the maps of this sequence and group
     const CW *Bm = reinterpret_cast<const CW *>(p.Bm) + bc0;
     const CW *Cm = reinterpret_cast<const CW *>(p.Cm) + bc0;
 
-    // The flat prologue (inputs of a channel -> LDS) and epilogue (partials -> outputs) need NA threads each.  A
-    // workgroup of 2 NA threads gives the prologue to its first half and the epilogue to its second half, which then
-    // run side by side (epilogue of channel g, prologue of channel g + 1); otherwise the same threads do both.
-    constexpr bool SPLIT = NT == 2 * NA;
-    const bool pro_thread = NA == NT || tid < NA;                     // wave-uniform: NA is a multiple of 64
-    const bool epi_thread = SPLIT ? tid >= NA : pro_thread;
-    const int f0 = tid * TPW;                                         // first flat step of a prologue thread
-    const int f0e = (SPLIT ? tid - NA : tid) * TPW;                   // ... of an epilogue thread
-    auto fslot = [](int f) { return (((f % T) / 4) * 64 + f / T) * 4 + (f % 4); };
+    // prologue and epilogue: this thread's channel of a pair (wave-uniform where a channel takes whole wavefronts)
+    const bool pro = !SPLIT || w < W / 2, epi = !SPLIT || w >= W / 2;
+    int c_own = tid % NA / NTC;
+    if constexpr (NTC >= 64) c_own = __builtin_amdgcn_readfirstlane(c_own);
+    // The addresses that follow from the thread's number are formed where they are needed: hoisted out of the loops by the
+    // compiler they would sit in registers all through the main pass, which has none to spare.
+    auto fresh = [](unsigned v) { asm volatile("" : "+v"(v)); return v; };
+    // first step of a thread in prologue and epilogue (a wavefront alone: the lane's own steps)
+    auto first_step = [](unsigned t) {
+        if constexpr (OWN) return (int)(((t & 15) * 2 + ((t >> 4) & 1)) * T);
+        else return (int)(t % NTC) * TPT;
+    };
+    // two steps of a map in LDS: [n][step % 8 / 2][lane][step % 2], lanes permuted per block of four states against the
+    // conflicts of the staging writes
+    auto map_at = [](int n, int k, int l) { return ((n * 4 + k) * 32 + (l ^ ((n >> 2 & 3) << 1))) * 2; };
 
     for (int64_t tile = ntiles - 1; tile >= 0; --tile) {
         const int64_t l0 = tile * TILE;
-        const int rem = (L - l0 < TILE) ? (int)(L - l0) : TILE;      // valid steps of this tile
+        const int rem = (L - l0 < TILE) ? (int)(L - l0) : TILE;      // valid steps of this tile (at least one)
+        const bool full = rem == TILE;
+        __syncthreads();                             // the tables (first tile) are in place; the tile before is done with LDS
 
-        // ---- this wavefront's NK columns of both maps into its own slices of LDS; zeroed dBm/dCm sums
-        float2 dBacc[NK][T], dCacc[NK][T];
+        // ---- both maps into LDS as fp32 pairs: two steps of up to four states a thread
         {
-            const CW *BmT = Bm + l0 * N + w * NK, *CmT = Cm + l0 * N + w * NK;
-            CW tb[T][NK], tc[T][NK];
+            constexpr int QN = N < 4 ? N : 4, PER = N / QN;
+            const CW *BmT = Bm + l0 * N, *CmT = Cm + l0 * N;
 #pragma unroll
-            for (int t = 0; t < T; ++t) {
-                if (lane * T + t < rem) {
-                    load_cwords<CW, NK>(BmT + (unsigned)((lane * T + t) * N), tb[t]);
-                    load_cwords<CW, NK>(CmT + (unsigned)((lane * T + t) * N), tc[t]);
-                } else {
+            for (int it = 0; it < 128 * PER / NT; ++it) {
+                const int t0 = (int)fresh(tid) + it * NT, pr = t0 / PER, q = t0 % PER;
+                CW rB[2][QN], rC[2][QN];
 #pragma unroll
-                    for (int k = 0; k < NK; ++k) { tb[t][k] = CW{}; tc[t][k] = CW{}; }
+                for (int j = 0; j < 2; ++j) {
+                    const int row = pr * 2 + j < rem ? pr * 2 + j : rem - 1;
+                    load_cwords<CW, QN>(BmT + (unsigned)(row * N + q * QN), rB[j]);
+                    load_cwords<CW, QN>(CmT + (unsigned)(row * N + q * QN), rC[j]);
                 }
+                const bool ok0 = pr * 2 < rem, ok1 = pr * 2 + 1 < rem;
 #pragma unroll
-                for (int k = 0; k < NK; ++k) { dBacc[k][t] = make_float2(0.0f, 0.0f); dCacc[k][t] = make_float2(0.0f, 0.0f); }
+                for (int s = 0; s < QN; ++s) {
+                    const int at = map_at(q * QN + s, pr & 3, piece_lane(pr >> 2));
+                    auto put = [&](float2 *m, CW w0, CW w1) {
+                        const float2 v0 = cword<IO>::unpack(w0), v1 = cword<IO>::unpack(w1);
+                        *reinterpret_cast<float4 *>(&m[at]) = make_float4(ok0 ? v0.x : 0.0f, ok0 ? v0.y : 0.0f, ok1 ? v1.x : 0.0f, ok1 ? v1.y : 0.0f);
+                    };
+                    put(sB, rB[0][s], rB[1][s]);
+                    put(sC, rC[0][s], rC[1][s]);
+                }
             }
-#pragma unroll
-            for (int k = 0; k < NK; ++k)
-#pragma unroll
-                for (int t = 0; t < T; ++t) {
-                    sB[(((w * NK + k) * (T / 2) + t / 2) * 64 + lane) * 2 + (t % 2)] = cword<IO>::unpack(tb[t][k]);
-                    sC[(((w * NK + k) * (T / 2) + t / 2) * 64 + lane) * 2 + (t % 2)] = cword<IO>::unpack(tc[t][k]);
-                }
         }
 
-        // per-channel inputs are fetched one channel ahead
-        RawFew<IO, TPW> r_u, r_dl, r_dy, r_z;
-        float2 pA[NK], pck[NK];
-        float pDsk, pbias;
-        auto prefetch = [&](int g) {
-            const int d = d0 + g;
-            const int64_t row = (int64_t)b * p.D + d;
-            if (pro_thread) {
-                load_few_raw<IO, TPW>(reinterpret_cast<const IO *>(p.u) + bs * p.u_sb + d * p.u_sd + toff + l0, f0, rem, vec, r_u);
-                load_few_raw<IO, TPW>(reinterpret_cast<const IO *>(p.delta) + bs * p.dl_sb + d * p.dl_sd + toff + l0, f0, rem, vec, r_dl);
-                load_few_raw<IO, TPW>(reinterpret_cast<const IO *>(p.dy) + bs * p.dy_sb + d * p.dy_sd + toff + l0, f0, rem, vec, r_dy);
-                if (has_z) load_few_raw<IO, TPW>(reinterpret_cast<const IO *>(p.z) + bs * p.z_sb + d * p.z_sd + toff + l0, f0, rem, vec, r_z);
+        // ---- per-step inputs of a pair of channels are fetched one pair ahead.  Row pointers: this thread's channel of
+        // the pair the next fetch reads and the next epilogue writes (past the last channel they stay on a valid one).
+        RawFew<IO, TPT> r_u, r_dl, r_dy, r_z;
+        const int64_t tl = toff + l0;
+        const int c_first = c_own < Gact ? c_own : Gact - 1;
+        const int64_t dch = d0 + c_first;
+        const IO *n_u = reinterpret_cast<const IO *>(p.u) + bs * p.u_sb + dch * p.u_sd + tl;
+        const IO *n_dl = reinterpret_cast<const IO *>(p.delta) + bs * p.dl_sb + dch * p.dl_sd + tl;
+        const IO *n_dy = reinterpret_cast<const IO *>(p.dy) + bs * p.dy_sb + dch * p.dy_sd + tl;
+        const IO *n_z = HAS_Z ? reinterpret_cast<const IO *>(p.z) + bs * p.z_sb + dch * p.z_sd + tl : n_dy;
+        const int64_t z_sd = HAS_Z ? p.z_sd : p.dy_sd;
+        IO *o_du = reinterpret_cast<IO *>(p.du) + bs * p.du_sb + dch * p.du_sd + tl;
+        IO *o_dd = reinterpret_cast<IO *>(p.ddelta) + bs * p.dd_sb + dch * p.dd_sd + tl;
+        IO *o_dz = HAS_Z && p.dz ? reinterpret_cast<IO *>(p.dz) + bs * p.dz_sb + dch * p.dz_sd + tl : nullptr;
+        int n_g = 0;                                                 // first channel of the pair of the next fetch
+        // A and the checkpointed state of the pair: one value each for the first 2 * CP * N threads
+        const float2 *n_A = p.A + (int64_t)d0 * N, *n_ck = ckrow + tile * N;
+        const unsigned ck_sd = (unsigned)(nck * N);                  // elements between the checkpoints of two channels
+        float2 r_ac = make_float2(0.0f, 0.0f);
+        const bool window = vec && L >= TPT;                         // the last steps of the sequence: see tail_window
+        auto fetch = [&](unsigned t0) {
+            const int f0 = first_step(t0);
+            if (window) {
+                const int o = f0 < rem - TPT ? f0 : rem - TPT;       // (tail_window)
+                load_few_raw<IO, TPT>(n_u + o, 0, TPT, true, r_u);
+                load_few_raw<IO, TPT>(n_dl + o, 0, TPT, true, r_dl);
+                load_few_raw<IO, TPT>(n_dy + o, 0, TPT, true, r_dy);
+                if constexpr (HAS_Z) load_few_raw<IO, TPT>(n_z + o, 0, TPT, true, r_z);
+            } else {
+                load_few_raw<IO, TPT>(n_u, f0, rem, vec, r_u);
+                load_few_raw<IO, TPT>(n_dl, f0, rem, vec, r_dl);
+                load_few_raw<IO, TPT>(n_dy, f0, rem, vec, r_dy);
+                if constexpr (HAS_Z) load_few_raw<IO, TPT>(n_z, f0, rem, vec, r_z);
             }
-#pragma unroll
-            for (int k = 0; k < NK; ++k) {
-                pA[k] = p.A[d * N + w * NK + k];
-                pck[k] = p.ckpt[((p.cu ? (int64_t)d : row) * nck + ck0 + tile * CK_PER_TILE) * N + w * NK + k];
+            if (t0 < 2 * CP * N) {
+                const bool second = (t0 / N) % CP && n_g + 1 < Gact;     // else the first channel of the pair again
+                const float2 *q = t0 < CP * N ? n_A : n_ck;
+                r_ac = q[t0 % N + (second ? (t0 < CP * N ? (unsigned)N : ck_sd) : 0u)];
             }
-            pDsk = p.Dskip ? p.Dskip[d] : 0.0f;
-            pbias = p.bias ? p.bias[d] : 0.0f;
+            n_g += CP;
+            if (n_g < Gact) { n_A += CP * N; n_ck += (int64_t)CP * ck_sd; }
+            if (n_g + c_own < Gact) { n_u += CP * p.u_sd; n_dl += CP * p.dl_sd; n_dy += CP * p.dy_sd; n_z += CP * z_sd; }
         };
-        prefetch(0);
+        if (pro) fetch(tid);
 
-        // ---- prologue of channel g: each prologue thread prepares TPW flat steps for everybody
-        auto prologue = [&](int g) {
-            float *in = sIn[g & 1];
-            const float bias = pbias;
-            float e_u[TPW], r_d[TPW], e_dy[TPW], e_z[TPW];
-            unpack_few<IO, TPW>(r_u, e_u);
-            unpack_few<IO, TPW>(r_dl, r_d);
-            unpack_few<IO, TPW>(r_dy, e_dy);
-            if (has_z) unpack_few<IO, TPW>(r_z, e_z);
+        float2 dB[NS][T], dC[NS][T];                 // this lane's sums of dBm* and dCm* over channels
 #pragma unroll
-            for (int i = 0; i < TPW; ++i) {
-                float sp, sg, dyp, zf;
-                bwd_step_inputs<sizeof(IO) == 4>(r_d[i] + bias, e_dy[i], has_z ? e_z[i] : 0.0f, p.softplus != 0, has_z, sp, sg, dyp, zf);
-                in[0 * TILE + fslot(f0 + i)] = (f0 + i < rem) ? sp : 0.0f;
-                in[1 * TILE + fslot(f0 + i)] = e_u[i];
-                in[2 * TILE + fslot(f0 + i)] = dyp;
-                in[3 * TILE + fslot(f0 + i)] = sg;
-                in[4 * TILE + fslot(f0 + i)] = zf;
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int t = 0; t < T; ++t) { dB[s][t] = make_float2(0.0f, 0.0f); dC[s][t] = make_float2(0.0f, 0.0f); }
+
+        // kept from a pair's prologue to its epilogue: d softplus / ds and the factor that turns ypre into dz (in registers
+        // where the same threads do both)
+        float e_sg[TPT], e_zf[TPT], n_sg[TPT], n_zf[TPT];
+        // ---- prologue of the pair whose inputs have been fetched: each thread prepares TPT steps of its channel
+        auto step_inputs = [&](int ch, unsigned t0, float (&u)[TPT], float (&dl)[TPT], float (&dy)[TPT]) {
+            const float bias = sBias[ch < Gact ? ch : Gact - 1];
+            const int f0 = first_step(t0);
+            float z[TPT];
+            if (!full && window) {
+                const int by = f0 - (f0 < rem - TPT ? f0 : rem - TPT);
+                tail_shift<IO, TPT>(r_u, by);
+                tail_shift<IO, TPT>(r_dl, by);
+                tail_shift<IO, TPT>(r_dy, by);
+                if constexpr (HAS_Z) tail_shift<IO, TPT>(r_z, by);
+            }
+            unpack_few<IO, TPT>(r_u, u);
+            unpack_few<IO, TPT>(r_dl, dl);
+            unpack_few<IO, TPT>(r_dy, dy);
+            if constexpr (HAS_Z) unpack_few<IO, TPT>(r_z, z);
+#pragma unroll
+            for (int i = 0; i < TPT; ++i) {
+                const float v = dl[i] + bias;
+                float sp, sg;
+                softplus_sigmoid<sizeof(IO) == 4>(v, sp, sg);
+                dl[i] = p.softplus ? sp : v;
+                n_sg[i] = p.softplus ? sg : 1.0f;
+                if constexpr (HAS_Z) gate_bwd(z[i], dy[i], n_zf[i]);
+            }
+            if (!full || ch >= Gact) {                   // steps past the end: Delta = 0 (a = 1), no input, no gradient
+#pragma unroll
+                for (int i = 0; i < TPT; ++i)
+                    if (f0 + i >= rem || ch >= Gact) { dl[i] = 0.0f; u[i] = 0.0f; dy[i] = 0.0f; }
             }
         };
-        if (pro_thread) prologue(0);
-
-        for (int g = 0; g < Gact; ++g) {
-            const int d = d0 + g;
-            const float Dsk = pDsk;
-            const float *in = sIn[g & 1];
-            float2 cA[NK], cck[NK];
-#pragma unroll
-            for (int k = 0; k < NK; ++k) { cA[k] = pA[k]; cck[k] = pck[k]; }
-
-            __syncthreads();
-            if (g + 1 < Gact) prefetch(g + 1);
-
-            // ---- main: this lane's T steps, this wavefront's NK states
-            float dl[T], dyp[T], uv[T], ypre[T], pdu[T], pdd[T];
-#pragma unroll
-            for (int q = 0; q < TQ; ++q) {
-                const float4 v0 = *reinterpret_cast<const float4 *>(&in[0 * TILE + (q * 64 + lane) * 4]);
-                const float4 v1 = *reinterpret_cast<const float4 *>(&in[1 * TILE + (q * 64 + lane) * 4]);
-                const float4 v2 = *reinterpret_cast<const float4 *>(&in[2 * TILE + (q * 64 + lane) * 4]);
-                dl[4 * q] = v0.x; dl[4 * q + 1] = v0.y; dl[4 * q + 2] = v0.z; dl[4 * q + 3] = v0.w;
-                uv[4 * q] = v1.x; uv[4 * q + 1] = v1.y; uv[4 * q + 2] = v1.z; uv[4 * q + 3] = v1.w;
-                dyp[4 * q] = v2.x; dyp[4 * q + 1] = v2.y; dyp[4 * q + 2] = v2.z; dyp[4 * q + 3] = v2.w;
+        auto prologue = [&](int ch, unsigned t0, int buf) {
+            float u[TPT], dl[TPT], dy[TPT];
+            step_inputs(ch, t0, u, dl, dy);
+            const int slot = cstep_slot(first_step(t0));
+            csteps_write<TPT>(sIn[buf][c_own][0], slot, dl);
+            csteps_write<TPT>(sIn[buf][c_own][1], slot, u);
+            csteps_write<TPT>(sIn[buf][c_own][2], slot, dy);
+            if constexpr (SPLIT) {
+                csteps_write<TPT>(sIn[buf][c_own][3], slot, n_sg);
+                if constexpr (HAS_Z) csteps_write<TPT>(sIn[buf][c_own][4], slot, n_zf);
             }
-            float sum_dl = 0.0f;
+            if (t0 < 2 * CP * N) (&sAC[buf][0][0][0])[t0] = r_ac;
+        };
+        auto rotate = [&]() {
+            if constexpr (!SPLIT && !OWN) {
 #pragma unroll
-            for (int t = 0; t < T; ++t) { sum_dl += dl[t]; ypre[t] = 0.0f; pdu[t] = 0.0f; pdd[t] = 0.0f; }
-            const float dl_next0 = dpp<DPP_WAVE_SHL1>(0.0f, dl[0]);        // first Delta of the next lane (0 past lane 63)
-            const float sum_shift = sum_dl - dl[0] + dl_next0;
-
-            float dAr4[NK], dAi4[NK];
+                for (int i = 0; i < TPT; ++i) { e_sg[i] = n_sg[i]; if constexpr (HAS_Z) e_zf[i] = n_zf[i]; }
+            }
+        };
+        // ---- epilogue: du, ddelta, dz of this thread's steps from the sums over states
+        auto finish = [&](const int g, unsigned t0, const float (&e_dl)[TPT], const float (&e_u)[TPT], const float (&e_dy)[TPT],
+                          const float (&s_yp)[TPT], const float (&s_du)[TPT], const float (&s_dd)[TPT]) {
+            const int ch = g + c_own, f0 = first_step(t0);
+            const bool live = ch < Gact;
+            const float Dsk = sDskip[live ? ch : Gact - 1];
+            float o_u[TPT], o_d[TPT], o_z[TPT];
+            float dD_part = 0.0f, db_part = 0.0f;
 #pragma unroll
-            for (int k = 0; k < NK; ++k) {
-                const int n = w * NK + k;
-                const CCoef cc = make_ccoef(cA[k].x, cA[k].y);
-                const float2 xck = cck[k];
-                const float2 hc = sH[g * N + n];
-                // [n][t/2][lane][t%2]: two steps of a lane are one 16-byte chunk and neighbouring lanes neighbouring
-                // chunks, so a ds_read_b128 touches every bank once (with the lane's four steps side by side, 32 bytes
-                // per lane, each such read hit half the banks twice: a quarter of this kernel's LDS cycles)
-                const float2 *sBn = &sB[(n * (T / 2) * 64 + lane) * 2], *sCn = &sC[(n * (T / 2) * 64 + lane) * 2];
-                auto mapB = [&](int t) { return sBn[(t / 2) * 128 + (t % 2)]; };
-                auto mapC = [&](int t) { return sCn[(t / 2) * 128 + (t % 2)]; };
+            for (int i = 0; i < TPT; ++i) {
+                const float ed = e_dl[i], eu = e_u[i], ey = e_dy[i];
+                float su = s_du[i], sd = s_dd[i];
+                if constexpr (DISC == DISC_ZOH_S6) {
+                    // the wavefronts' sums are sum_n Re(K B): dDelta += u times it, du = Delta times it
+                    sd = __builtin_fmaf(eu, su, sd);
+                    su *= ed;
+                }
+                o_u[i] = __builtin_fmaf(ey, Dsk, su);
+                o_d[i] = sd * e_sg[i];
+                if constexpr (HAS_Z) o_z[i] = __builtin_fmaf(Dsk, eu, s_yp[i]) * e_zf[i];
+                dD_part = __builtin_fmaf(ey, eu, dD_part);
+                db_part += (full || f0 + i < rem) ? o_d[i] : 0.0f;
+            }
+            if (live) {
+                store_few<IO, TPT>(o_du, f0, rem, vec, o_u);
+                store_few<IO, TPT>(o_dd, f0, rem, vec, o_d);
+                if constexpr (HAS_Z) { if (o_dz) store_few<IO, TPT>(o_dz, f0, rem, vec, o_z); }
+            }
+            {
+                // joint reduction of the two per-lane sums over a row of lanes
+                const bool odd = t0 & 1;
+                float v = odd ? db_part : dD_part;
+                v += dpp<0xB1>(0.0f, odd ? dD_part : db_part);           // quad_perm [1,0,3,2]
+                v += dpp<0x4E>(0.0f, v);                                  // quad_perm [2,3,0,1]
+                v += dpp<0x124>(0.0f, v);                                 // row_ror:4
+                v += dpp<0x128>(0.0f, v);                                 // row_ror:8
+                if ((t0 & 15) < 2 && live) lds_add(&(odd ? sdb : sdD)[ch], v);
+            }
+            o_du += CP * p.du_sd; o_dd += CP * p.dd_sd;
+            if constexpr (HAS_Z) { if (o_dz) o_dz += CP * p.dz_sd; }
+        };
+        auto epilogue = [&](const int g, const int buf) {
+            const unsigned t0 = fresh(tid % NA);
+            const int slot = cstep_slot(first_step(t0));
+            float e_in[3][TPT], s_yp[TPT], s_du[TPT], s_dd[TPT];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) csteps_read<TPT>(sIn[buf][c_own][j], slot, e_in[j]);
+            if constexpr (SPLIT) {
+                csteps_read<TPT>(sIn[buf][c_own][3], slot, e_sg);
+                if constexpr (HAS_Z) csteps_read<TPT>(sIn[buf][c_own][4], slot, e_zf);
+            }
+#pragma unroll
+            for (int i = 0; i < TPT; ++i) { s_yp[i] = 0.0f; s_du[i] = 0.0f; s_dd[i] = 0.0f; }
+#pragma unroll
+            for (int ww = 0; ww < W; ++ww) {
+                float v[TPT];
+                if constexpr (HAS_Z) {
+                    csteps_read<TPT>(sPart[c_own][ww][0], slot, v);
+#pragma unroll
+                    for (int i = 0; i < TPT; ++i) s_yp[i] = ww ? s_yp[i] + v[i] : v[i];
+                }
+                csteps_read<TPT>(sPart[c_own][ww][1], slot, v);
+#pragma unroll
+                for (int i = 0; i < TPT; ++i) s_du[i] = ww ? s_du[i] + v[i] : v[i];
+                csteps_read<TPT>(sPart[c_own][ww][2], slot, v);
+#pragma unroll
+                for (int i = 0; i < TPT; ++i) s_dd[i] = ww ? s_dd[i] + v[i] : v[i];
+            }
+            finish(g, t0, e_in[0], e_in[1], e_in[2], s_yp, s_du, s_dd);
+        };
 
-                // forward recompute of the states of this tile
-                float2 a[T + 1], gg[T], x[T];
-                float2 P = make_float2(1.0f, 0.0f), S = make_float2(0.0f, 0.0f);
+        // ---- main: this lane's 8 steps of its channel for the wavefront's states
+        auto states = [&](const int g, const int buf, const unsigned ln, const float (&dl)[T], float (&du)[T], const float (&dy)[T],
+                          float (&yp)[T], float (&pu)[T], float (&pd)[T]) {
+            const unsigned c = ln >> 5, li = ln & 15, row = ln >> 4 & 1;
+            const int ch = g + (int)c < Gact ? g + (int)c : g;             // (the half past the last channel repeats the first, unused)
+            const bool own = g + (int)c < Gact;
+            const int at = ch * N + n0;
+            if constexpr (DISC == DISC_ZOH_S6) {
+#pragma unroll
+                for (int t = 0; t < T; ++t) du[t] *= dl[t];      // S6 only ever needs Delta*u; the others keep u
+            }
+            float sum_dl = dl[0];
+#pragma unroll
+            for (int t = 1; t < T; ++t) sum_dl += dl[t];
+            auto maps = [&](const float2 *m, int s, float2 (&v)[T]) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float4 f = *reinterpret_cast<const float4 *>(m + map_at(n0 + s, k, ln & 31));
+                    v[2 * k] = make_float2(f.x, f.y); v[2 * k + 1] = make_float2(f.z, f.w);
+                }
+            };
+            // the lane's steps as one affine pair each way: S the end state from zero, Q = a_0 (c_0 + a_1 (c_1 + ...)) the
+            // adjoint handed on, both with multiplier P
+            auto fold = [&](int s, float2 (&a)[T], float2 (&x)[T], float2 (&gg)[T], float2 &P, float2 &S, float2 &Q) {
+                const float2 Av = sAC[buf][0][c][n0 + s];
+                const CCoef cc = make_ccoef(Av.x, Av.y);
+                float2 Bv[T], Cv[T];
+                maps(sB, s, Bv);
+                maps(sC, s, Cv);
 #pragma unroll
                 for (int t = 0; t < T; ++t) {
                     cdisc_ag<DISC>(dl[t], cc, a[t], gg[t]);
-                    const float2 Bv = mapB(t);
-                    if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) {
-                        const float gu = gg[t].x * uv[t];                  // the gain is real
-                        x[t] = make_float2(gu * Bv.x, gu * Bv.y);
-                    } else {
-                        x[t] = cxmul(make_float2(gg[t].x * uv[t], gg[t].y * uv[t]), Bv);
-                    }
-                    S = (t == 0) ? x[0] : cxfma(a[t], S, x[t]);           // the fold starts from zero
-                    if constexpr (DISC == DISC_BILINEAR) P = cxmul(P, a[t]);
+                    if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) x[t] = make_float2(du[t] * Bv[t].x, du[t] * Bv[t].y);
+                    else x[t] = cxmul(make_float2(gg[t].x * du[t], gg[t].y * du[t]), Bv[t]);
                 }
-                if constexpr (DISC != DISC_BILINEAR) P = cexp_dt(sum_dl, cc.A2r, cc.Arev);
-                if (lane == 0) S = cxfma(P, xck, S);                       // the checkpointed state enters through lane 0
-
-                // lane aggregate of the adjoint H_l = c_l + conj(a_{l+1}) H_{l+1}; the multiplier of the tile's last
-                // step is 1 because the carried value is already conj(a_{l1}) H_{l1}
-                a[T] = make_float2(dpp<DPP_WAVE_SHL1>(1.0f, a[0].x), dpp<DPP_WAVE_SHL1>(0.0f, a[0].y));
-                float2 Pr = make_float2(1.0f, 0.0f), Sr = make_float2(0.0f, 0.0f);
+                S = x[0];
 #pragma unroll
-                for (int t = T - 1; t >= 0; --t) {
-                    const float2 Cv = mapC(t);
-                    const float2 c = make_float2(Cv.x * dyp[t], -Cv.y * dyp[t]);
-                    Sr = (t == T - 1) ? c : cxcfma(a[t + 1], Sr, c);
-                    if constexpr (DISC == DISC_BILINEAR) Pr = cxmulc(Pr, a[t + 1]);
-                }
-                if constexpr (DISC != DISC_BILINEAR) {
-                    const float2 e = cexp_dt(sum_shift, cc.A2r, cc.Arev);
-                    Pr = make_float2(e.x, -e.y);
-                }
-                if (lane == 63) Sr = cxfma(Pr, hc, Sr);                    // the carried adjoint enters through lane 63
-
-                cwave_scan_fwd_rev(P, S, Pr, Sr, lane);
-                const float2 xin = make_float2(dpp<DPP_WAVE_SHR1>(xck.x, S.x), dpp<DPP_WAVE_SHR1>(xck.y, S.y));
+                for (int t = 1; t < T; ++t) S = cxfma(a[t], S, x[t]);
+                Q = cxmul(a[T - 1], make_float2(Cv[T - 1].x * dy[T - 1], Cv[T - 1].y * dy[T - 1]));
+#pragma unroll
+                for (int t = T - 2; t >= 0; --t)
+                    Q = cxmul(a[t], make_float2(__builtin_fmaf(Cv[t].x, dy[t], Q.x), __builtin_fmaf(Cv[t].y, dy[t], Q.y)));
+                if constexpr (DISC == DISC_BILINEAR)
+                    P = cxmul(cxmul(cxmul(a[0], a[1]), cxmul(a[2], a[3])), cxmul(cxmul(a[4], a[5]), cxmul(a[6], a[7])));
+                else P = cexp_dt(sum_dl, cc.A2r, cc.Arev);       // product of the T multipliers
+            };
+            float2 dA[NS];
+            // the states (earliest step first), then the adjoint (last step first) with all that is summed over it
+            auto replay = [&](int s, const float2 (&a)[T], float2 (&x)[T], const float2 (&gg)[T], const float2 xin, float2 Gin) {
+                const float2 Av = sAC[buf][0][c][n0 + s];
+                float2 Bv[T], Cv[T];
+                maps(sC, s, Cv);
+                maps(sB, s, Bv);
                 {
                     float2 xp = xin;
 #pragma unroll
                     for (int t = 0; t < T; ++t) { xp = cxfma(a[t], xp, x[t]); x[t] = xp; }
                 }
-                const float2 H0 = Sr;                                       // H of this lane's first step
-                float2 R = make_float2(dpp<DPP_WAVE_SHL1>(hc.x, Sr.x), dpp<DPP_WAVE_SHL1>(hc.y, Sr.y));   // H of the next lane's first step
-                if (lane == 0) sH[g * N + n] = cxcfma(a[0], H0, make_float2(0.0f, 0.0f));   // carried to the earlier tile
-
-                float2 dA_part = make_float2(0.0f, 0.0f);
+                float2 dAp = make_float2(0.0f, 0.0f);
+                auto acc = [&](float &sum, float m1, float m2) { sum = (s == 0) ? m1 * m2 : __builtin_fmaf(m1, m2, sum); };
 #pragma unroll
                 for (int t = T - 1; t >= 0; --t) {
-                    const float2 Cv = mapC(t), Bv = mapB(t);
-                    R = cxcfma(a[t + 1], R, make_float2(Cv.x * dyp[t], -Cv.y * dyp[t]));   // H_t
-                    [[maybe_unused]] const float2 xprev = (t > 0) ? x[t - 1] : xin;
-                    dCacc[k][t].x = __builtin_fmaf(dyp[t], x[t].x, dCacc[k][t].x);        // dypre conj(x)
-                    dCacc[k][t].y = __builtin_fmaf(-dyp[t], x[t].y, dCacc[k][t].y);
-                    ypre[t] = __builtin_fmaf(Cv.x, x[t].x, __builtin_fmaf(-Cv.y, x[t].y, ypre[t]));   // Re(C x)
-                    const float2 hb = cxmulc(R, Bv);                        // H conj(B)
-                    if constexpr (DISC == DISC_ZOH_S6) {
-                        pdu[t] += hb.x;                                      // sum_n Re(H conj(B)); scaled by Delta resp. u in the epilogue
-                        const float du_ = dl[t] * uv[t];
-                        dBacc[k][t].x = __builtin_fmaf(R.x, du_, dBacc[k][t].x);
-                        dBacc[k][t].y = __builtin_fmaf(R.y, du_, dBacc[k][t].y);
-                        // grad a conj(a) = H conj(a x_{l-1}), and a x_{l-1} = x_l - Delta u B
-                        const float2 ax = make_float2(__builtin_fmaf(-du_, Bv.x, x[t].x), __builtin_fmaf(-du_, Bv.y, x[t].y));
-                        const float2 q = cxmulc(R, ax);
-                        pdd[t] = __builtin_fmaf(q.x, cc.Ar, __builtin_fmaf(q.y, cc.Ai, pdd[t]));   // Re(q conj(A))
-                        dA_part.x = __builtin_fmaf(q.x, dl[t], dA_part.x);
-                        dA_part.y = __builtin_fmaf(q.y, dl[t], dA_part.y);
-                    } else if constexpr (DISC == DISC_DIRAC) {
-                        // g = 1: the S6 expressions with u in place of Delta u
-                        pdu[t] += hb.x;
-                        dBacc[k][t].x = __builtin_fmaf(R.x, uv[t], dBacc[k][t].x);
-                        dBacc[k][t].y = __builtin_fmaf(R.y, uv[t], dBacc[k][t].y);
-                        const float2 ax = make_float2(__builtin_fmaf(-uv[t], Bv.x, x[t].x), __builtin_fmaf(-uv[t], Bv.y, x[t].y));
-                        const float2 q = cxmulc(R, ax);                      // grad a conj(a)
-                        pdd[t] = __builtin_fmaf(q.x, cc.Ar, __builtin_fmaf(q.y, cc.Ai, pdd[t]));
-                        dA_part.x = __builtin_fmaf(q.x, dl[t], dA_part.x);
-                        dA_part.y = __builtin_fmaf(q.y, dl[t], dA_part.y);
+                    const float2 xprev = t > 0 ? x[t - 1] : xin;
+                    const float2 K = make_float2(__builtin_fmaf(Cv[t].x, dy[t], Gin.x), __builtin_fmaf(Cv[t].y, dy[t], Gin.y));
+                    Gin = cxmul(a[t], K);
+                    dC[s][t] = make_float2(__builtin_fmaf(dy[t], x[t].x, dC[s][t].x), __builtin_fmaf(dy[t], x[t].y, dC[s][t].y));
+                    if constexpr (HAS_Z) {
+                        acc(yp[t], Cv[t].x, x[t].x);
+                        yp[t] = __builtin_fmaf(-Cv[t].y, x[t].y, yp[t]);
+                    }
+                    if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) {
+                        // S6: g = Delta (du and dDelta share sum_n Re(K B), scaled in the epilogue); dirac: g = 1
+                        acc(pu[t], K.x, Bv[t].x);
+                        pu[t] = __builtin_fmaf(-K.y, Bv[t].y, pu[t]);
+                        dB[s][t] = make_float2(__builtin_fmaf(K.x, du[t], dB[s][t].x), __builtin_fmaf(K.y, du[t], dB[s][t].y));
+                        const float2 q = cxmul(Gin, xprev);              // grad a* a; da/dDelta = A a, da/dA = Delta a
+                        acc(pd[t], q.x, Av.x);
+                        pd[t] = __builtin_fmaf(-q.y, Av.y, pd[t]);
+                        dAp = make_float2(__builtin_fmaf(q.x, dl[t], dAp.x), __builtin_fmaf(q.y, dl[t], dAp.y));
                     } else {
-                        const float2 ga = cxmulc(R, xprev);                 // grad a
-                        const float2 gq = make_float2(hb.x * uv[t], hb.y * uv[t]);      // grad g
-                        pdu[t] += cxmulc(hb, gg[t]).x;                                     // Re(H conj(B) conj(g))
-                        const float2 rg = cxmulc(R, gg[t]);
-                        dBacc[k][t].x = __builtin_fmaf(rg.x, uv[t], dBacc[k][t].x);
-                        dBacc[k][t].y = __builtin_fmaf(rg.y, uv[t], dBacc[k][t].y);
+                        const float2 hb = cxmul(K, Bv[t]);
+                        const float2 gq = make_float2(hb.x * du[t], hb.y * du[t]);             // grad g*
+                        float2 g, d;                                                            // gain; dDelta is the real part of d
                         if constexpr (DISC == DISC_ZOH) {
-                            // da/dDelta = A a, da/dA = Delta a, dg/dDelta = a: with q = grad a conj(a),
-                            // dDelta += Re(q conj(A) + grad g conj(a)), dA += Delta q + grad g conj(dg/dA)
+                            // da/dDelta = A a, da/dA = Delta a, dg/dDelta = a
+                            const CCoef cc = make_ccoef(Av.x, Av.y);
                             float2 a_t, a_A, g_t, g_A;
-                            cdisc_partials<DISC>(dl[t], cc, a[t], gg[t], a_t, a_A, g_t, g_A);
-                            const float2 q = cxmulc(ga, a[t]);
-                            pdd[t] = __builtin_fmaf(q.x, cc.Ar, __builtin_fmaf(q.y, cc.Ai, pdd[t])) + cxmulc(gq, a[t]).x;
-                            const float2 s2 = cxmulc(gq, g_A);
-                            dA_part.x = __builtin_fmaf(q.x, dl[t], dA_part.x) + s2.x;
-                            dA_part.y = __builtin_fmaf(q.y, dl[t], dA_part.y) + s2.y;
+                            g = gg[t];
+                            cdisc_partials<DISC>(dl[t], cc, a[t], g, a_t, a_A, g_t, g_A);
+                            const float2 q = cxmul(Gin, xprev);
+                            d = make_float2(__builtin_fmaf(q.x, Av.x, __builtin_fmaf(-q.y, Av.y, __builtin_fmaf(gq.x, a[t].x, -gq.y * a[t].y))), 0.0f);
+                            const float2 e = cxfma(gq, g_A, make_float2(q.x * dl[t], q.y * dl[t]));
+                            dAp = make_float2(dAp.x + e.x, dAp.y + e.y);
                         } else {
-                            // bilinear: with q = 1 / (1 - Delta A / 2) all four partials are multiples of q^2:
-                            // dDelta += Re((grad a conj(A) + grad g) conj(q^2)),
-                            // dA += Delta (grad a + grad g Delta / 2) conj(q^2)
-                            const float r = (dl[t] != 0.0f) ? rcp_fast(dl[t]) : 0.0f;
-                            const float2 q = (dl[t] != 0.0f) ? make_float2(gg[t].x * r, gg[t].y * r) : make_float2(1.0f, 0.0f);
-                            const float2 q2 = cxmul(q, q);
-                            const float2 t1 = make_float2(__builtin_fmaf(ga.x, cc.Ar, __builtin_fmaf(ga.y, cc.Ai, gq.x)),
-                                                          __builtin_fmaf(ga.y, cc.Ar, __builtin_fmaf(-ga.x, cc.Ai, gq.y)));
-                            pdd[t] += cxmulc(t1, q2).x;
+                            // bilinear: with q = 1 / (1 - Delta A / 2) all four partials are multiples of q^2, and
+                            // a = (1 + Delta A / 2) q gives q = (a + 1) / 2 without a second reciprocal
+                            const float2 q = make_float2(__builtin_fmaf(a[t].x, 0.5f, 0.5f), 0.5f * a[t].y), q2 = cxmul(q, q);
+                            g = make_float2(dl[t] * q.x, dl[t] * q.y);
+                            const float2 ga = cxmul(K, xprev);                                  // grad a*
+                            const float2 t1 = cxfma(ga, Av, gq);
+                            d = make_float2(__builtin_fmaf(t1.x, q2.x, -t1.y * q2.y), 0.0f);
                             const float hd = 0.5f * dl[t];
                             const float2 t2 = make_float2(__builtin_fmaf(gq.x, hd, ga.x) * dl[t], __builtin_fmaf(gq.y, hd, ga.y) * dl[t]);
-                            const float2 s = cxmulc(t2, q2);
-                            dA_part.x += s.x;
-                            dA_part.y += s.y;
+                            dAp = cxfma(t2, q2, dAp);
                         }
+                        acc(pu[t], hb.x, g.x);
+                        pu[t] = __builtin_fmaf(-hb.y, g.y, pu[t]);
+                        pd[t] = s == 0 ? d.x : pd[t] + d.x;
+                        const float2 kg = cxmul(K, g);
+                        dB[s][t] = make_float2(__builtin_fmaf(kg.x, du[t], dB[s][t].x), __builtin_fmaf(kg.y, du[t], dB[s][t].y));
                     }
+                    // computed here: left to itself the compiler moves the products of one state down to the sums of the
+                    // next one's, and spills what it then has to keep
+                    if constexpr (HAS_Z) asm volatile("" : "+v"(yp[t]));
+                    asm volatile("" : "+v"(dC[s][t].x), "+v"(dC[s][t].y), "+v"(dB[s][t].x), "+v"(dB[s][t].y), "+v"(pu[t]), "+v"(pd[t]),
+                                      "+v"(dAp.x), "+v"(dAp.y));
                 }
-                dAr4[k] = dA_part.x; dAi4[k] = dA_part.y;
-                __builtin_amdgcn_sched_barrier(0);   // keep the states apart: interleaving them costs more registers than there are
-            }
-            // the per-lane sums of dA: four real values (two states) per joint reduction; lanes 0-3 and 32-35 own them
-            if constexpr (NK % 2 == 0) {
-#pragma unroll
-                for (int k2 = 0; k2 < NK; k2 += 2) {
-                    const float v4[4] = {dAr4[k2], dAr4[k2 + 1], dAi4[k2], dAi4[k2 + 1]};
-                    const float v = half_sum4(v4, lane);       // lane % 4 = 0,1,2,3 holds value 0,2,1,3
-                    if ((lane & 0x1C) == 0)
-                        lds_add(&sdA[lane >> 5][((g * N + w * NK + k2 + ((lane >> 1) & 1)) << 1) + (lane & 1)], v);
-                }
-            } else {
-                const float vr = half_sum(dAr4[0]), vi = half_sum(dAi4[0]);
-                if ((lane & 31) == 0) { lds_add(&sdA[lane >> 5][(g * N + w) << 1], vr); lds_add(&sdA[lane >> 5][((g * N + w) << 1) + 1], vi); }
-            }
-#pragma unroll
-            for (int q = 0; q < TQ; ++q) {
-                float *base = &sPart[(w * 3) * TILE + (q * 64 + lane) * 4];
-                *reinterpret_cast<float4 *>(base) = make_float4(ypre[4 * q], ypre[4 * q + 1], ypre[4 * q + 2], ypre[4 * q + 3]);
-                *reinterpret_cast<float4 *>(base + TILE) = make_float4(pdu[4 * q], pdu[4 * q + 1], pdu[4 * q + 2], pdu[4 * q + 3]);
-                *reinterpret_cast<float4 *>(base + 2 * TILE) = make_float4(pdd[4 * q], pdd[4 * q + 1], pdd[4 * q + 2], pdd[4 * q + 3]);
-            }
-            __syncthreads();
-
-            // ---- epilogue: the epilogue threads share the tile in flat order
-            if (epi_thread) {
-                float o_du[TPW], o_dd[TPW], o_dz[TPW];
-                float dD_part = 0.0f, db_part = 0.0f;
-                // every LDS value of the epilogue is read up front, in one round trip (left alone, the compiler moves
-                // the reads that only feed the stores into the stores' own branch, one round trip after the other)
-                float e_in[TPW][5], e_part[TPW][W][3];
-#pragma unroll
-                for (int i = 0; i < TPW; ++i) {
-                    const int fs = fslot(f0e + i);
-#pragma unroll
-                    for (int j = 0; j < 5; ++j) e_in[i][j] = in[j * TILE + fs];
-#pragma unroll
-                    for (int ww = 0; ww < W; ++ww)
-#pragma unroll
-                        for (int j = 0; j < 3; ++j) e_part[i][ww][j] = sPart[(ww * 3 + j) * TILE + fs];
-                }
+                dA[s] = dAp;
+            };
+            const bool first = li == 0, last = li == 15;
+            if constexpr (PAIR) {
+                float2 a[2][T], x[2][T], gg[T], P[2], S[2], Q[2], xin[2], Gin[2];
+                fold(0, a[0], x[0], gg, P[0], S[0], Q[0]);
                 __builtin_amdgcn_sched_barrier(0);
+                fold(1, a[1], x[1], gg, P[1], S[1], Q[1]);
+                // row 0 takes both pieces of state 0, row 1 those of state 1
+                const float2 xc = *(first ? &sAC[buf][1][c][n0 + row] : &sZero), hc = *(last ? &sH[at + row] : &sZero);
+                swap_rows(P[0], P[1]); swap_rows(S[0], S[1]); swap_rows(Q[0], Q[1]);
+                const float2 out = piece_scans(P[0], S[0], Q[0], P[1], S[1], Q[1], xc, hc, xin[0], xin[1], Gin[0], Gin[1]);
+                swap_rows(xin[0], xin[1]); swap_rows(Gin[0], Gin[1]);
+                if (own && first) sH[at + row] = out;            // carried to the earlier tile
+                __builtin_amdgcn_sched_barrier(0);
+                replay(0, a[0], x[0], gg, xin[0], Gin[0]);
+                __builtin_amdgcn_sched_barrier(0);
+                replay(1, a[1], x[1], gg, xin[1], Gin[1]);
+            } else {
 #pragma unroll
-                for (int i = 0; i < TPW; ++i) {
-                    const float e_u = e_in[i][1], e_dyp = e_in[i][2];
-                    float yp = Dsk * e_u, s_du = 0.0f, s_dd = 0.0f;
-#pragma unroll
-                    for (int ww = 0; ww < W; ++ww) {
-                        yp += e_part[i][ww][0];
-                        s_du += e_part[i][ww][1];
-                        s_dd += e_part[i][ww][2];
-                    }
-                    if constexpr (DISC == DISC_ZOH_S6) {
-                        // the wavefronts' sums are sum_n Re(H conj(B)): dDelta += u times it, du = Delta times it
-                        s_dd = __builtin_fmaf(e_u, s_du, s_dd);
-                        s_du *= e_in[i][0];
-                    }
-                    o_du[i] = __builtin_fmaf(e_dyp, Dsk, s_du);
-                    o_dd[i] = s_dd * e_in[i][3];
-                    o_dz[i] = yp * e_in[i][4];
-                    dD_part = __builtin_fmaf(e_dyp, e_u, dD_part);
-                    db_part += (f0e + i < rem) ? o_dd[i] : 0.0f;
-                    asm volatile("" : "+v"(o_du[i]), "+v"(o_dd[i]), "+v"(o_dz[i]));   // computed here, not inside the stores' branch
-                }
-                store_few<IO, TPW>(reinterpret_cast<IO *>(p.du) + bs * p.du_sb + d * p.du_sd + toff + l0, f0e, rem, vec, o_du);
-                store_few<IO, TPW>(reinterpret_cast<IO *>(p.ddelta) + bs * p.dd_sb + d * p.dd_sd + toff + l0, f0e, rem, vec, o_dd);
-                if (p.dz) store_few<IO, TPW>(reinterpret_cast<IO *>(p.dz) + bs * p.dz_sb + d * p.dz_sd + toff + l0, f0e, rem, vec, o_dz);
-                const float vD = half_sum(dD_part), vb = half_sum(db_part);
-                if ((lane & 31) == 0) {
-                    lds_add(&sdD[((lane >> 5) * W + w) * kMaxGc + g], vD);
-                    lds_add(&sdb[((lane >> 5) * W + w) * kMaxGc + g], vb);
+                for (int s = 0; s < NS; ++s) {
+                    float2 a[T], x[T], gg[T], P, S, Q, xE, xO, gE, gO;
+                    fold(s, a, x, gg, P, S, Q);
+                    // (both rows hold the same)
+                    const float2 xc = *(first ? &sAC[buf][1][c][n0 + s] : &sZero), hc = *(last ? &sH[at + s] : &sZero);
+                    float2 P1 = P, S1 = S, Q1 = Q;
+                    swap_rows(P, P1); swap_rows(S, S1); swap_rows(Q, Q1);
+                    const float2 out = piece_scans(P, S, Q, P1, S1, Q1, xc, hc, xE, xO, gE, gO);
+                    if (own && first && row == 0) sH[at + s] = out;
+                    const float2 xin = make_float2(row ? xO.x : xE.x, row ? xO.y : xE.y), Gin = make_float2(row ? gO.x : gE.x, row ? gO.y : gE.y);
+                    replay(s, a, x, gg, xin, Gin);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
-            // the next channel's prologue fills the other half of sIn (the prefetch that feeds it was issued before
-            // the main pass)
-            if (pro_thread && g + 1 < Gact) prologue(g + 1);
-        }
-
-        // ---- add this tile's dBm/dCm sums (over the G channels) to global memory, transposed through LDS so that
-        // consecutive threads hit consecutive addresses; FL lanes (FL * T time steps) at a time
-        // A lane's two states of a step are one 16-byte chunk of that step's row; lanes are T * N pairs apart, which
-        // would put all of them on the same banks, so the chunk index is XORed with the lane's low bits (eight
-        // consecutive lanes then cover all banks; a reader's consecutive floats stay a permutation of whole chunks
-        // within one 8-chunk block).  A thread reads all its values in one batch before it issues its atomics.
-        float2 *fbB = reinterpret_cast<float2 *>(sPart), *fbC = fbB + FL * T * N;
-        constexpr int CPL = T * N / 2;                                   // 16-byte chunks per lane
-        constexpr bool SWZ = NK == 2 && CPL >= 8;
-        for (int j = 0; j < 64 / FL; ++j) {
-            __syncthreads();
-            if (lane / FL == j) {
-                // (addresses formed here and now: hoisted out of the tile loop they would cost the channel loop registers)
-                int lr = lane % FL;
-                asm volatile("" : "+v"(lr));
+            // dA over the 16 lanes of a row.  With two states two exchange steps leave each lane of a quad with the quad's sum of
+            // ONE of the four values (lane % 4 = 0, 1, 2, 3: value 0, 2, 1, 3), two rotations sum the quads
+            float *sum = reinterpret_cast<float *>(&sdA[at]);
+            if constexpr (NS == 2) {
+                const float v4[4] = {dA[0].x, dA[0].y, dA[1].x, dA[1].y};
+                const bool b0 = ln & 1, b1 = ln & 2;
+                float kA = b0 ? v4[2] : v4[0], kB = b0 ? v4[3] : v4[1];
+                kA += dpp<0xB1>(0.0f, b0 ? v4[0] : v4[2]);           // quad_perm [1,0,3,2]
+                kB += dpp<0xB1>(0.0f, b0 ? v4[1] : v4[3]);
+                float v = b1 ? kB : kA;
+                v += dpp<0x4E>(0.0f, b1 ? kA : kB);                  // quad_perm [2,3,0,1]
+                v += dpp<0x124>(0.0f, v);                            // row_ror:4
+                v += dpp<0x128>(0.0f, v);                            // row_ror:8
+                if (own && li < 4) lds_add(sum + ((ln & 1) << 1) + ((ln >> 1) & 1), v);
+            } else {
 #pragma unroll
-                for (int t = 0; t < T; ++t) {
-                    if constexpr (SWZ) {
-                        const int c4 = ((lr * T + t) * (N / 2) + w) ^ (lr & 7);
-                        *reinterpret_cast<float4 *>(&fbB[c4 * 2]) = make_float4(dBacc[0][t].x, dBacc[0][t].y, dBacc[1][t].x, dBacc[1][t].y);
-                        *reinterpret_cast<float4 *>(&fbC[c4 * 2]) = make_float4(dCacc[0][t].x, dCacc[0][t].y, dCacc[1][t].x, dCacc[1][t].y);
-                    } else {
-#pragma unroll
-                        for (int k = 0; k < NK; ++k) {
-                            fbB[(lr * T + t) * N + w * NK + k] = dBacc[k][t];
-                            fbC[(lr * T + t) * N + w * NK + k] = dCacc[k][t];
+                for (int j = 0; j < 2; ++j) {
+                    float v = j ? dA[0].y : dA[0].x;
+                    v += dpp<0xB1>(0.0f, v);
+                    v += dpp<0x4E>(0.0f, v);
+                    v += dpp<0x124>(0.0f, v);
+                    v += dpp<0x128>(0.0f, v);
+                    if (own && li == 0) lds_add(sum + j, v);
+                }
+            }
+        };
+        if constexpr (OWN) {
+            __syncthreads();                             // (one wavefront: orders the LDS accesses only)
+            for (int g = 0; g < Gact; g += CP) {
+                const unsigned t0 = fresh(tid);
+                const int c = t0 >> 5, l4 = (t0 & 31) * 4;
+                float u[T], dl[T], dy[T], yp[T], pu[T], pd[T];
+                step_inputs(g + c_own, t0, u, dl, dy);
+                csteps_write<T>(sIn[0][c][0], l4, u);
+                csteps_write<T>(sIn[0][c][1], l4, n_sg);
+                if constexpr (HAS_Z) csteps_write<T>(sIn[0][c][2], l4, n_zf);
+                if (t0 < 2 * CP * N) (&sAC[0][0][0][0])[t0] = r_ac;
+                fetch(t0);
+                __syncthreads();
+                states(g, 0, t0, dl, u, dy, yp, pu, pd);
+                csteps_read<T>(sIn[0][c][0], l4, u);
+                csteps_read<T>(sIn[0][c][1], l4, e_sg);
+                if constexpr (HAS_Z) csteps_read<T>(sIn[0][c][2], l4, e_zf);
+                finish(g, t0, dl, u, dy, yp, pu, pd);
+                __syncthreads();
+            }
+        } else {
+            // Between two barriers a wavefront finishes the pair before (its partial sums are complete), runs the main part
+            // of this pair and prepares the next one.  There is one set of partial sums: before a wavefront writes its own it
+            // sees to it that those who read the pair before are through, which they have been for nearly a whole pass
+            // (they count themselves in sDone on their way, and wait for nobody before that).
+            auto main_part = [&](const int g, const int buf) {
+                const unsigned ln = fresh(lane), c = ln >> 5;
+                const int l4 = (ln & 31) * 4;
+                float dl[T], du[T], dy[T], yp[T], pu[T], pd[T];
+                csteps_read<T>(sIn[buf][c][0], l4, dl);
+                csteps_read<T>(sIn[buf][c][1], l4, du);
+                csteps_read<T>(sIn[buf][c][2], l4, dy);
+                states(g, buf, ln, dl, du, dy, yp, pu, pd);
+                if constexpr (NB == 2) {
+                    asm volatile("" ::: "memory");
+                    while (__hip_atomic_load(&sDone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < done) {}
+                    asm volatile("" ::: "memory");
+                }
+                if constexpr (HAS_Z) csteps_write<T>(sPart[c][w][0], l4, yp);
+                csteps_write<T>(sPart[c][w][1], l4, pu);
+                csteps_write<T>(sPart[c][w][2], l4, pd);
+            };
+            auto next_inputs = [&](const int g, const int buf) {          // (past the last pair: unused)
+                if (!pro) return;
+                const unsigned t0 = fresh(tid);
+                prologue(g + c_own, t0, buf);
+                fetch(t0);
+            };
+            next_inputs(0, 0);
+            if constexpr (NB == 2) {
+                int g = 0, buf = 0;
+                for (; g < Gact; g += CP, buf ^= 1) {
+                    __syncthreads();
+                    if (g > 0) {
+                        if (epi) {
+                            epilogue(g - CP, buf ^ 1);
+                            asm volatile("" ::: "memory");
+                            if (lane == 0) (void)__hip_atomic_fetch_add(&sDone, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                         }
+                        done += SPLIT ? W / 2 : W;
                     }
+                    rotate();
+                    main_part(g, buf);
+                    next_inputs(g + CP, buf ^ 1);
                 }
-            }
-            __syncthreads();
-            const int step0 = j * FL * T;                                // within the tile
-            float *gB = reinterpret_cast<float *>(p.dBm + bc0 + (l0 + step0) * N);
-            float *gC = reinterpret_cast<float *>(p.dCm + bc0 + (l0 + step0) * N);
-            const float *lB = reinterpret_cast<const float *>(fbB), *lC = reinterpret_cast<const float *>(fbC);
-            constexpr int TOTAL = FL * T * N * 2;                        // floats per array and round
-            constexpr int PER = (TOTAL + NT - 1) / NT;
-            float vB[PER], vC[PER];
-            int tf = tid;
-            asm volatile("" : "+v"(tf));
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                const int idx = tf + i * NT;
-                const int at = SWZ ? ((((idx >> 2) ^ (((idx >> 2) / CPL) & 7)) << 2) | (idx & 3)) : idx;
-                const bool in = TOTAL % NT == 0 || idx < TOTAL;
-                vB[i] = in ? lB[at] : 0.0f; vC[i] = in ? lC[at] : 0.0f;
-            }
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                const int idx = tf + i * NT;
-                if ((TOTAL % NT == 0 || idx < TOTAL) && step0 + idx / (2 * N) < rem) {
-                    unsafeAtomicAdd(gB + (unsigned)idx, vB[i]);
-                    unsafeAtomicAdd(gC + (unsigned)idx, vC[i]);
+                __syncthreads();
+                if (epi) epilogue(g - CP, buf ^ 1);
+            } else {
+                for (int g = 0; g < Gact; g += CP) {
+                    __syncthreads();
+                    rotate();
+                    main_part(g, 0);
+                    __syncthreads();
+                    epilogue(g, 0);
+                    next_inputs(g + CP, 0);
                 }
             }
         }
-        __syncthreads();
-    }
 
+        // ---- the tile's sums of dBm and dCm over this workgroup's channels
+        // (the two halves hold different channels: summed by a swap that leaves the lower half with steps 0-3 of a lane, the
+        // upper half with steps 4-7)
+        const unsigned t0 = fresh(tid), q0 = ((t0 & 15) * 2 + (t0 >> 4 & 1)) * 2 + (t0 >> 5 & 1);      // four steps from step 4 q0 on
+        auto halves = [&](float v, float v4) {
+            const auto r = __builtin_amdgcn_permlane32_swap((unsigned)f2i(v), (unsigned)f2i(v4), false, false);
+            return make_float2(i2f((int)r[0]), i2f((int)r[1]));
+        };
+        auto sums = [&](const float2 (&o)[T], int j) {                   // the sums' real (j = 0) and imaginary parts: conjugated back
+            float v[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float2 h = j ? halves(o[t].y, o[t + 4].y) : halves(o[t].x, o[t + 4].x);
+                v[t] = j ? -h.x - h.y : h.x + h.y;
+            }
+            return make_float4(v[0], v[1], v[2], v[3]);
+        };
+        if (p.part) {
+            // to this workgroup's own slot of the workspace; the sum over workgroups and the transposition to [L,N] are those of
+            // the real backward pass with twice the states (k_ss_bwd_maps), so the slot is laid out as its kernel does
+            float *pt = p.part + (((slot0 + tile_first + tile) * gridDim.x + blockIdx.x) * 4 * N + 2 * n0) * TILE + ((q0 & 1) << 7) + ((q0 >> 1) << 2);
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    *reinterpret_cast<float4 *>(pt + (2 * s + j) * TILE) = sums(dB[s], j);
+                    *reinterpret_cast<float4 *>(pt + (2 * N + 2 * s + j) * TILE) = sums(dC[s], j);
+                }
+        } else {
+            // without a workspace: float atomics, on consecutive addresses (the sums change their order in the maps' place; four
+            // steps are a piece, whose place in a plane of the part is permuted against conflicts)
+            float *bB = reinterpret_cast<float *>(sB), *bC = reinterpret_cast<float *>(sC);
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int e = (n0 + s) * 2 + j, at = e * TILE + (q0 ^ (e & 15)) * 4;
+                    *reinterpret_cast<float4 *>(bB + at) = sums(dB[s], j);
+                    *reinterpret_cast<float4 *>(bC + at) = sums(dC[s], j);
+                }
+            __syncthreads();
+            float *gB = reinterpret_cast<float *>(p.dBm + bc0 + l0 * N), *gC = reinterpret_cast<float *>(p.dCm + bc0 + l0 * N);
+#pragma unroll 1
+            for (int i = t0; i < rem * 2 * N; i += NT) {
+                const int e = i % (2 * N), l = i / (2 * N), at = e * TILE + ((l >> 2) ^ (e & 15)) * 4 + (l & 3);
+                unsafeAtomicAdd(gB + i, bB[at]);
+                unsafeAtomicAdd(gC + i, bC[at]);
+            }
+        }
+    }
+    __syncthreads();
     // ---- per-channel results of this workgroup
     for (int i = tid; i < Gact * N; i += NT) {
-        const int g = i / N, n = i % N;
-        float *dst = reinterpret_cast<float *>(p.dA + (int64_t)(d0 + g) * N + n);
-        unsafeAtomicAdd(dst, sdA[0][2 * (g * N + n)] + sdA[1][2 * (g * N + n)]);
-        unsafeAtomicAdd(dst + 1, sdA[0][2 * (g * N + n) + 1] + sdA[1][2 * (g * N + n) + 1]);
-        if (p.dx0 && chunk == 0) p.dx0[((int64_t)b * p.D + d0 + g) * N + n] = sH[g * N + n];
+        float *dst = reinterpret_cast<float *>(p.dA + (int64_t)d0 * N + i);
+        unsafeAtomicAdd(dst, sdA[i].x);
+        unsafeAtomicAdd(dst + 1, -sdA[i].y);
+        if (p.dx0 && chunk == 0) p.dx0[((int64_t)b * p.D + d0) * N + i] = make_float2(sH[i].x, -sH[i].y);
     }
     for (int g = tid; g < Gact; g += NT) {
-        float sD = 0.0f, sb = 0.0f;
-#pragma unroll
-        for (int ww = 0; ww < 2 * W; ++ww) { sD += sdD[ww * kMaxGc + g]; sb += sdb[ww * kMaxGc + g]; }
-        if (p.dD) unsafeAtomicAdd(p.dD + d0 + g, sD);
-        if (p.dbias) unsafeAtomicAdd(p.dbias + d0 + g, sb);
+        if (p.dD) unsafeAtomicAdd(p.dD + d0 + g, sdD[g]);
+        if (p.dbias) unsafeAtomicAdd(p.dbias + d0 + g, sdb[g]);
     }
 }
 
 // ---------------------------------------------------------------- launchers
-// channels per workgroup: aim at one workgroup per CU (256), as many channels each as fit: the staging of the maps
-// and the flush of dBm/dCm are paid once per (workgroup, tile).  Measured on B=8, D=1536, N=16, L=2048: 1.69 ms with
-// 256 workgroups, 1.76 ms with 512, 1.90 ms with 1024.
-int cbwd_channels_per_group(int B, int D, int, bool balanced) {
-    // packed sequences of unknown lengths: four times as many workgroups, so that the short ones fill in beside the long
-    int64_t G = ((int64_t)B * D) / (balanced ? 256 : 1024);
-    if (balanced) {
-        // never a few workgroups more than a whole number of rounds of 256 (see bwd_channels_per_group)
-        int64_t rounds = 1;
-        while ((int64_t)B * ((D + kMaxGc - 1) / kMaxGc) > rounds * 256 && rounds < 64) ++rounds;
-        const int64_t nb = rounds * 256 / B;
-        if (nb >= 1) G = (D + nb - 1) / nb;
-    }
-    if (G < 8) G = 8;
-    if (G > kMaxGc) G = kMaxGc;
-    if (G > D) G = D;
-    const int64_t groups = (D + G - 1) / G;
-    G = (D + groups - 1) / groups;                     // even split
-    return (int)G;
-}
-
-// launch shape incl. the chunked path for few rows and long sequences (selective_bwd_carry.hip): the chip holds one
-// 512-thread workgroup per CU for N = 16, two smaller ones below
-BwdPlan cbwd_plan(int rowsg, int dpg, int N, int64_t L, int mode, bool balanced) {
-    const int G = cbwd_channels_per_group(rowsg, dpg, N, balanced);
-    return plan_time_chunks(rowsg, dpg, L, balanced ? mode : 1, G, N >= 16 ? 256 : 512, kMaxGc);
-}
-
-template <typename IO, int N, int NK, int DISC>
+template <typename IO, int N, int DISC>
 static hipError_t launch_cbwd_n(const CBwdParams &p, hipStream_t s) {
-    const int gmin = p.wcap > 0 ? p.gmin : p.G;                       // fewest channels a workgroup may take
-    dim3 grid(p.bcg * ((p.dpg + gmin - 1) / gmin), p.B, p.nchunks > 1 ? p.nchunks : 1);
-    hipLaunchKernelGGL((k_ss_cbwd<IO, N, NK, 4, DISC>), grid, dim3((N / NK) * 64), 0, s, p);
+    const dim3 grid(cbwd_grid_x(p), p.B, p.nchunks > 1 ? p.nchunks : 1), block(CBwdGeom<N>::NT);
+    if (p.z) hipLaunchKernelGGL((k_ss_cbwd<IO, N, DISC, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((k_ss_cbwd<IO, N, DISC, false>), grid, block, 0, s, p);
+    if (p.part) {
+        BwdParams m{};
+        m.B = p.B; m.N = 2 * N; m.L = p.L; m.G = p.G; m.bcg = p.bcg; m.dpg = p.dpg; m.cu = p.cu; m.nslots = p.nslots;
+        m.dBm = reinterpret_cast<float *>(p.dBm); m.dCm = reinterpret_cast<float *>(p.dCm);
+        m.wcap = p.wcap; m.gmin = p.gmin; m.part = p.part; m.part_tiles = p.part_tiles;
+        return launch_bwd_maps(m, (int)grid.x, s);
+    }
     return hipGetLastError();
 }
 
 template <typename IO, int DISC>
 static hipError_t launch_cbwd_disc(const CBwdParams &p, hipStream_t s) {
     switch (p.N) {
-        case 1: return launch_cbwd_n<IO, 1, 1, DISC>(p, s);
-        case 2: return launch_cbwd_n<IO, 2, 2, DISC>(p, s);
-        // two states per wavefront: with four, the complex sums of dBm/dCm alone take 64 registers and the
-        // compiler spills to scratch memory (measured 1.9x slower on the Mamba-block shape)
-        case 4: return launch_cbwd_n<IO, 4, 2, DISC>(p, s);
-        case 8: return launch_cbwd_n<IO, 8, 2, DISC>(p, s);
-        case 16: return launch_cbwd_n<IO, 16, 2, DISC>(p, s);
+        case 1: return launch_cbwd_n<IO, 1, DISC>(p, s);
+        case 2: return launch_cbwd_n<IO, 2, DISC>(p, s);
+        case 4: return launch_cbwd_n<IO, 4, DISC>(p, s);
+        case 8: return launch_cbwd_n<IO, 8, DISC>(p, s);
+        case 16: return launch_cbwd_n<IO, 16, DISC>(p, s);
     }
     return hipErrorInvalidValue;
 }
@@ -597,8 +815,59 @@ static hipError_t launch_cbwd_io(const CBwdParams &p, int disc, hipStream_t s) {
     return hipErrorInvalidValue;
 }
 
+// float32 and bfloat16 are compiled side by side: selective_cplx_bwd_f32.hip includes this file for the former.
+hipError_t launch_ss_cbwd_f32(const CBwdParams &p, int disc, hipStream_t s);
+#ifdef LRNNX_CBWD_F32
+hipError_t launch_ss_cbwd_f32(const CBwdParams &p, int disc, hipStream_t s) { return launch_cbwd_io<float>(p, disc, s); }
+#else
 hipError_t launch_ss_cbwd(const CBwdParams &p, int io_dtype, int disc, hipStream_t s) {
-    return io_dtype == 1 ? launch_cbwd_io<bf16_t>(p, disc, s) : launch_cbwd_io<float>(p, disc, s);
+    return io_dtype == 1 ? launch_cbwd_io<bf16_t>(p, disc, s) : launch_ss_cbwd_f32(p, disc, s);
 }
+
+// Workgroups the chip holds at once: two wavefronts per SIMD are what the registers allow.
+int cbwd_places(int N) { return 2048 / (N >= 2 ? N / 2 : 1); }
+
+// channels per workgroup: as many as fit when every place of the chip has one, since the staging of the maps and the flush
+// of dBm/dCm are paid once per (workgroup, tile)
+int cbwd_channels_per_group(int B, int D, int N, bool balanced) {
+    const int64_t full = cbwd_places(N);
+    // packed sequences of unknown lengths: four times as many workgroups, so that the short ones fill in beside the long
+    int64_t G = ((int64_t)B * D) / (balanced ? full : 4 * full);
+    if (balanced) {
+        // never a few workgroups more than a whole number of rounds (see channels_for in selective_bwd.hip)
+        int64_t rounds = 1;
+        while ((int64_t)B * ((D + kMaxGc - 1) / kMaxGc) > rounds * full && rounds < 64) ++rounds;
+        const int64_t nb = rounds * full / B;
+        if (nb >= 1) G = (D + nb - 1) / nb;
+    }
+    if (G < 8) G = 8;
+    if (G > kMaxGc) G = kMaxGc;
+    if (G > D) G = D;
+    const int64_t groups = (D + G - 1) / G;
+    G = (D + groups - 1) / groups;                     // even split
+    return (int)(G + 1) / 2 * 2;                       // (walked in pairs)
+}
+
+// Whether the tile sums of dBm and dCm, which take `bytes`, go through the workspace and a second launch instead of float atomics.
+// Many small workgroups meet at the same addresses (2 x 771 rows, L = 1531, N = 16, bf16: 181 us with atomics, 162 through
+// the workspace; 4 x 1024 rows in 4 groups, L = 1000: 218 and 205); rows of one tile are done before a second launch could start
+// (64 x 512, L = 100, N = 4: 90 and 97; 4 x 1024, L = 256, N = 8: 50 and 55), and so are small calls altogether (512 rows, L = 512,
+// N = 4: 45 and 48).  With one or two states there are more workgroups, and their atomics cost more.
+bool cbwd_sums_pay(int N, int64_t tiles, bool packed, size_t bytes) {
+    return bytes > ((size_t)4 << 20) && (packed || tiles > 1 || N < 4);
+}
+int cbwd_grid_x(const CBwdParams &p) {
+    const int gmin = p.wcap > 0 ? p.gmin : p.G;                       // fewest channels a workgroup may take
+    return p.bcg * ((p.dpg + gmin - 1) / gmin);
+}
+
+// launch shape incl. the chunked path for few rows and long sequences (selective_bwd_carry.hip)
+BwdPlan cbwd_plan(int rowsg, int dpg, int N, int64_t L, int mode, bool balanced) {
+    const int G = cbwd_channels_per_group(rowsg, dpg, N, balanced);
+    BwdPlan pl = plan_time_chunks(rowsg, dpg, L, balanced ? mode : 1, G, cbwd_places(N), kMaxGc);
+    pl.G = (pl.G + 1) / 2 * 2;
+    return pl;
+}
+#endif
 
 }  // namespace lrnnx
