@@ -34,11 +34,10 @@ int fwd_chunks(int64_t B, int64_t D, int64_t L, bool forced) {
     return (int)n;
 }
 
-// the complex forward kernel: 8 channels per workgroup, tiles of 512 steps for both I/O types
-constexpr int kCfwdTile = 512;
-int cfwd_chunks(int64_t wgs, int64_t L, bool forced) {
-    const int64_t ntiles = cdiv(L, kCfwdTile);
-    int64_t n = cdiv(forced ? 8 * kNumCU : 2 * kNumCU, wgs);
+// The same for the complex forward scan.
+int cfwd_chunks(int64_t B, int64_t bcg, int64_t dpg, int64_t L, bool forced) {
+    const int64_t ntiles = cdiv(L, cfwd_tile_steps());
+    int64_t n = cdiv(8 * kNumCU, B * bcg * cdiv(dpg, cfwd_channels_per_workgroup()));
     if (forced && n < 2) n = 2;
     if (n > ntiles) n = ntiles;
     return n < 1 ? 1 : (int)n;
@@ -249,9 +248,8 @@ int lrnnx_selective_scan_fwd_complex_chunks(int64_t B, int64_t D, int64_t N, int
     const int bcg = bc_groups > 1 ? bc_groups : 1;
     if (B < 1 || D < 1 || L < 1 || B > 65535 || D > INT32_MAX || D % bcg || !supported_n_complex((int)N)) return 0;
     if (path < LRNNX_PATH_AUTO || path > LRNNX_PATH_CHUNK_CARRY) return 0;
-    const int64_t wgs = B * bcg * cdiv(D / bcg, 8);
-    if (path == LRNNX_PATH_CHUNK_CARRY) return cfwd_chunks(wgs, L, true);
-    if (path == LRNNX_PATH_AUTO && wgs <= kNumCU / 2 && cdiv(L, kCfwdTile) >= 4) return cfwd_chunks(wgs, L, false);
+    if (path == LRNNX_PATH_CHUNK_CARRY) return cfwd_chunks(B, bcg, D / bcg, L, true);
+    if (path == LRNNX_PATH_AUTO && cfwd_chunks_pay(B, bcg, D / bcg, N, L)) return cfwd_chunks(B, bcg, D / bcg, L, false);
     return 1;
 }
 
@@ -279,7 +277,7 @@ size_t lrnnx_workspace_bytes(int which, int64_t B, int64_t D, int64_t N, int64_t
         if (which == LRNNX_WS_BWD_SUMS) return bwd_sums_bytes(bwd_plan, 1, B, D, N, L, bcg, packed != 0) + 512;
         if (which == LRNNX_WS_FWD) return packed ? 0 : (size_t)2 * B * D * fwd_chunks(B, D, L, true) * N * es;
         if (which == LRNNX_WS_FWD_COMPLEX)
-            return packed ? 0 : (size_t)2 * B * D * cfwd_chunks(B * bcg * cdiv(D / bcg, 8), L, true) * N * es;
+            return packed ? 0 : (size_t)2 * B * D * cfwd_chunks(B, bcg, D / bcg, L, true) * N * es;
         // backward: the checkpoints of the recompute sweep (not LRNNX_WS_BWD_CARRY: the caller has the forward's), then
         // the chunk aggregates, or for a packed batch the launch order
         size_t ck = 0;
@@ -424,9 +422,8 @@ int lrnnx_selective_scan_fwd_complex(const lrnnx_ss_fwd_complex_args *a) {
             (!a->y || row_vec_ok(a->y, p.y_sb, p.y_sd, es)) && (!a->z || row_vec_ok(a->z, p.z_sb, p.z_sd, es));
     hipStream_t s = reinterpret_cast<hipStream_t>(a->stream);
 
-    // chunk-carry path: asked for, or (automatic) few rows and a sequence of four tiles or more
-    const int64_t ntiles = cdiv(a->L, kCfwdTile);
-    const int64_t wgs = (int64_t)a->B * bcg * cdiv(a->D / bcg, 8);
+    // chunk-carry path: asked for, or where it is faster
+    const int64_t ntiles = cdiv(a->L, cfwd_tile_steps());
     int nch = cu ? 1 : lrnnx_selective_scan_fwd_complex_chunks(a->B, a->D, a->N, a->L, bcg, path);
     if (nch > 1 && (!ws || ws_bytes < (size_t)2 * a->B * a->D * nch * a->N * sizeof(float2))) {
         if (path == LRNNX_PATH_CHUNK_CARRY) return LRNNX_ERR_WORKSPACE;

@@ -290,6 +290,9 @@ hipError_t launch_fill(const FillList &z, hipStream_t s);
 
 // Tile geometry the host needs for grids, workspaces and the choice of path (each constant lives beside its kernel).
 int fwd_channels_per_workgroup();            // of the 16-lane shape, which the chunk-carry forward path launches
+int cfwd_channels_per_workgroup();           // the same of the complex forward kernel
+int cfwd_tile_steps();
+bool cfwd_chunks_pay(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L);
 bool fwd_chunks_pay(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L, bool f32);
 int lti_chunk_group();                       // chunks (wavefronts) of one workgroup of the two-launch LTI path
 int lti_onepass_anchor();                    // every how many groups the single-launch LTI scan publishes a true state
