@@ -177,6 +177,25 @@ __device__ __forceinline__ void bwd_step_inputs(float s, float dy, float z, bool
     if (has_z) gate_bwd(z, dyp, zf);
 }
 
+// ---------------------------------------------------------------- issue priority
+// Two wavefronts of a SIMD issue plain fp32 instructions side by side (2.5 cycles of 2.4 GHz each), and one wavefront issues
+// them beside a transcendental, a row swap or a DPP operand of the other, which take the ALU 4 to 8 cycles.  But this lasts
+// only while the wavefront with the slow instruction goes first: at equal priority one exponential in 64 multiply-adds makes
+// it 3.4 cycles an instruction, one in eight 5.1, one DPP operand in eight 4.9.  So a kernel raises its priority where such
+// instructions are dense (slow_part), lowers it for plain arithmetic (fast_part), and raises it further where a workgroup
+// is about to meet at a barrier (edge_part).  A loop like the backward pass's (18 exponentials, 46 DPP operands, 244 plain):
+// 4.1 cycles an instruction as it stands with two wavefronts a SIMD, 4.2 with the priorities the wrong way round, 2.6
+// with these; 4.0 and 2.9 with three wavefronts.  The whole kernels keep part of that: see there.
+template <int P>
+__device__ __forceinline__ void issue_priority() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(P);
+    __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ void slow_part() { issue_priority<1>(); }
+__device__ __forceinline__ void fast_part() { issue_priority<0>(); }
+__device__ __forceinline__ void edge_part() { issue_priority<2>(); }
+
 // ---------------------------------------------------------------- wavefront scans over affine pairs
 // One Hillis-Steele step on the pair held in (P,S): the pair of the lane named by the DPP
 // control is composed in from the earlier side.  Both updates are single VALU instructions

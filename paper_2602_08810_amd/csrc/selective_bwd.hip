@@ -17,11 +17,13 @@
 // states in registers and over wavefronts through LDS: after a barrier every thread finishes a few consecutive steps
 // of one channel (epilogue) and prepares the same steps of the next pair of channels (prologue).
 //
-// What bounds it: vector-ALU issue.  With exponentials and DPP instructions in the stream a SIMD issues one vector
-// instruction every four cycles, whatever its kind and however many wavefronts it holds (an exponential takes two such
-// slots), so the time is the number of instructions: 22.6 slots per state update in the main part (15 multiply-adds
-// and products, 3 for the exponential and its argument, 3.6 for the two scans and the fold's product) and about 5 for
-// prologue, epilogue and the work per tile.  Time on 64 lanes with 4 steps each and all four states of a wavefront
+// What bounds it: vector-ALU issue and, with two wavefronts a SIMD, the waits of a wavefront that the other one does not
+// fill (a quarter of its time, mostly for LDS after the one barrier of a pass).  22.6 slots of four cycles per state update
+// in the main part (15 multiply-adds and products, 3 for the exponential and its argument, 3.6 for the two scans and the
+// fold's product) and about 5 for prologue, epilogue and the work per tile.  The parts of a pass run at the issue priorities
+// of scan_common.hpp, prologue and epilogue at the highest, since a whole workgroup waits for the last at its barrier:
+// 369 -> 338 us (both parts at one priority: 351), B=16, D=2560, L=4096 2149 -> 1840.  (Before that the two wavefronts of a
+// SIMD took turns at a raised priority, a pass each.)  Time on 64 lanes with 4 steps each and all four states of a wavefront
 // scanned together took 34.8.  Mamba-block shape (B=8, D=1536, N=16, L=2048, bf16): 440 -> 358 us + 25 us for the
 // sums of dBm and dCm; B=16, D=2560, L=4096: 2630 -> 2190 us.  Also tried: four channels per wavefront on rows of 16
 // lanes with 16 steps each (19.7 slots, but twice the LDS traffic and one workgroup per compute unit: 560 us), halves
@@ -156,12 +158,6 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
     __shared__ float sdD[kBwdMaxG], sdb[kBwdMaxG];
     __shared__ float sDskip[kBwdMaxG], sBias[kBwdMaxG];
 
-    // Two workgroups share a compute unit, so each SIMD holds one wavefront of each.  The issue arbiter prefers the
-    // older wavefront, the older workgroup finishes earlier and the younger one then runs alone, badly hiding its
-    // latencies.  With four wavefronts per workgroup the two wavefronts of a SIMD therefore take turns at the higher issue
-    // priority, one pass each (told apart by the lowest bit of the hardware wavefront slot).
-    constexpr bool ALT_PRIO = W == 4;
-    [[maybe_unused]] const unsigned hw_slot = ALT_PRIO ? (__builtin_amdgcn_s_getreg(6148) & 1u) : 0u;   // HW_ID.WAVE_ID, bit 0
     const int tid = threadIdx.x;
     const int lane = tid & 63, li = lane & 31, half = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -454,6 +450,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
                     const ACoef ac = make_acoef<DISC>(Ak[s]);
+                    slow_part();
                     // the checkpointed state enters through the half's first lane, the carried adjoint through its last
                     float xin = i2f(f2i(ck[s]) & (int)first_lane), Gin = i2f(f2i(hc[s]) & (int)last_lane);
                     float a[T], x[T], gg[T];
@@ -476,6 +473,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                     else P = exp2_fast(sum_dl * ac.A2);
                     half_scans(P, S, Q, xin, Gin);
                     if (own && (ln & 31) == 0) sH[at + s] = Q;       // carried to the earlier tile
+                    fast_part();
                     // replay of the states (earliest step first) and of the adjoint (last step first), side by side: two chains
                     // whose instructions fill each other's result latencies.  zoh and bilinear, which need more registers and
                     // have more instructions a step to fill them with, take the adjoint step by step below instead (side by
@@ -547,6 +545,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                     }
                     dA[s] = dAp;
                 }
+                slow_part();
                 // dA: over the 16 lanes of a row.  With four states two exchange steps leave each lane of a quad with the
                 // quad's sum of ONE state (lane % 4 = 0, 1, 2, 3: state 0, 2, 1, 3), two rotations sum the quads
                 if constexpr (NS == 4) {
@@ -572,11 +571,6 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 }
         };
         __syncthreads();                                 // the tables (first tile) are in place; the tile before is done
-        auto take_turn = [&](int g) {
-            if constexpr (ALT_PRIO) {
-                if (((unsigned)(g / CP) & 1u) == hw_slot) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
-            }
-        };
         if constexpr (OWN) {
             for (int g = 0; g < Gact; g += CP) {
                 const unsigned t0 = fresh(tid);
@@ -601,6 +595,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 lds_steps_read<T>(sIn[buf][c][1], l4, du);
                 lds_steps_read<T>(sIn[buf][c][2], l4, dy);
                 states(g, buf, ln, dl, du, dy, yp, pu, pd);
+                edge_part();
                 if constexpr (HAS_Z) lds_steps_write<T>(sPart[buf][c][w][0], l4, yp);
                 lds_steps_write<T>(sPart[buf][c][w][1], l4, pu);
                 lds_steps_write<T>(sPart[buf][c][w][2], l4, pd);
@@ -616,7 +611,6 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 // part of this pair and prepares the next one: nobody waits in between.  (Two barriers per pair cost 4 %.)
                 int g = 0, buf = 0;
                 for (; g < Gact; g += CP, buf ^= 1) {
-                    take_turn(g);
                     __syncthreads();
                     if (g > 0) epilogue(g - CP, buf ^ 1);
                     rotate();
@@ -627,7 +621,6 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 epilogue(g - CP, buf ^ 1);
             } else {
                 for (int g = 0; g < Gact; g += CP) {
-                    take_turn(g);
                     __syncthreads();
                     rotate();
                     main_part(g, 0);

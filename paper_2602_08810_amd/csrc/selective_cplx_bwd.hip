@@ -23,10 +23,11 @@
 // sit in LDS as fp32 pairs, and what is summed over states (ypre, du, dDelta) goes through LDS once per pair of channels.
 //
 // What bounds it: vector-ALU issue, 65 instructions per state update (57.6 of them in the main part, among them 18 folds and
-// replays with two multiply-adds a component, 9 for the multiplier, 6 for the scans), 81 % of the issue slots in use; the rest is
+// replays with two multiply-adds a component, 9 for the multiplier, 6 for the scans), the rest is
 // lost where a wavefront waits for LDS or at the one barrier of a pass and the other of its SIMD cannot fill in alone.
 // B=8, D=1536, N=16, L=2048, bf16: 1505 us with time on 64 lanes of 4 steps and a scan of 64 lanes for each state (116
-// instructions an update), now 935; B=4, D=2560, L=2048: call 1288 us, now 811; N = 4: 686, now 265.
+// instructions an update), then 935, and with its parts at the priorities of scan_common.hpp 736.  B=4, D=2560, L=2048: call
+// 1288 us, then 811 before the priorities; N = 4: 686 and 265.
 #include "kernels.hpp"
 #include "scan_common.hpp"
 #include "cplx_common.hpp"
@@ -490,6 +491,8 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
                     if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) x[t] = make_float2(du[t] * Bv[t].x, du[t] * Bv[t].y);
                     else x[t] = cxmul(make_float2(gg[t].x * du[t], gg[t].y * du[t]), Bv[t]);
                 }
+                if constexpr (DISC != DISC_BILINEAR) P = cexp_dt(sum_dl, cc.A2r, cc.Arev);       // product of the T multipliers
+                fast_part();
                 S = x[0];
 #pragma unroll
                 for (int t = 1; t < T; ++t) S = cxfma(a[t], S, x[t]);
@@ -499,7 +502,6 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
                     Q = cxmul(a[t], make_float2(__builtin_fmaf(Cv[t].x, dy[t], Q.x), __builtin_fmaf(Cv[t].y, dy[t], Q.y)));
                 if constexpr (DISC == DISC_BILINEAR)
                     P = cxmul(cxmul(cxmul(a[0], a[1]), cxmul(a[2], a[3])), cxmul(cxmul(a[4], a[5]), cxmul(a[6], a[7])));
-                else P = cexp_dt(sum_dl, cc.A2r, cc.Arev);       // product of the T multipliers
             };
             float2 dA[NS];
             // the states (earliest step first), then the adjoint (last step first) with all that is summed over it
@@ -577,19 +579,22 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
             const bool first = li == 0, last = li == 15;
             if constexpr (PAIR) {
                 float2 a[2][T], x[2][T], gg[T], P[2], S[2], Q[2], xin[2], Gin[2];
+                slow_part();
                 fold(0, a[0], x[0], gg, P[0], S[0], Q[0]);
-                __builtin_amdgcn_sched_barrier(0);
+                slow_part();
                 fold(1, a[1], x[1], gg, P[1], S[1], Q[1]);
                 // row 0 takes both pieces of state 0, row 1 those of state 1
                 const float2 xc = *(first ? &sAC[buf][1][c][n0 + row] : &sZero), hc = *(last ? &sH[at + row] : &sZero);
+                slow_part();
                 swap_rows(P[0], P[1]); swap_rows(S[0], S[1]); swap_rows(Q[0], Q[1]);
                 const float2 out = piece_scans(P[0], S[0], Q[0], P[1], S[1], Q[1], xc, hc, xin[0], xin[1], Gin[0], Gin[1]);
                 swap_rows(xin[0], xin[1]); swap_rows(Gin[0], Gin[1]);
                 if (own && first) sH[at + row] = out;            // carried to the earlier tile
-                __builtin_amdgcn_sched_barrier(0);
+                fast_part();
                 replay(0, a[0], x[0], gg, xin[0], Gin[0]);
                 __builtin_amdgcn_sched_barrier(0);
                 replay(1, a[1], x[1], gg, xin[1], Gin[1]);
+                slow_part();
             } else {
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
@@ -665,11 +670,13 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
                 csteps_read<T>(sIn[buf][c][1], l4, du);
                 csteps_read<T>(sIn[buf][c][2], l4, dy);
                 states(g, buf, ln, dl, du, dy, yp, pu, pd);
+                fast_part();
                 if constexpr (NB == 2) {
                     asm volatile("" ::: "memory");
                     while (__hip_atomic_load(&sDone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < done) {}
                     asm volatile("" ::: "memory");
                 }
+                edge_part();
                 if constexpr (HAS_Z) csteps_write<T>(sPart[c][w][0], l4, yp);
                 csteps_write<T>(sPart[c][w][1], l4, pu);
                 csteps_write<T>(sPart[c][w][2], l4, pd);

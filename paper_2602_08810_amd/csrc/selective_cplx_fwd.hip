@@ -10,6 +10,9 @@
 // steps into one affine pair, the channel's lanes take the prefix over the pairs with DPP operands, and the lane replays its
 // steps from the state that enters it, accumulating y.  The state after the tile waits in LDS.
 //
+// What bounds it: vector-ALU issue.  Multipliers, folds, scan and replay run at the priorities of scan_common.hpp: B=8, D=1536,
+// N=16, L=2048, bf16 315 -> 258 us (multipliers, folds and scan as one part: 278).
+//
 // The same kernel serves the three launches of the chunk-carry path for few long rows (blockIdx.z = chunk), as in the real
 // forward: MODE_AGG returns each chunk's pair, k_ss_ccarry chains them, MODE_APPLY reruns each chunk from its true carry-in.
 #include "kernels.hpp"
@@ -287,7 +290,7 @@ __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) vo
                     float2 xin = xn, a[T], x[T], P, S;
                     An = lA[n + 1]; xn = lX[n + 1];      // (after the last n: not used)
                     read(lB + n * GE::ROW, std::integral_constant<int, T>{}, x);
-                    __builtin_amdgcn_sched_barrier(0);
+                    slow_part();
 #pragma unroll
                     for (int t = 0; t < T; ++t) {
                         float2 g;
@@ -297,6 +300,8 @@ __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) vo
                         // (four steps at a time: all at once, the parts of the multipliers would take four registers a step)
                         if (T > 8 && t % 4 == 3) __builtin_amdgcn_sched_barrier(0);
                     }
+                    if constexpr (DISC != DISC_BILINEAR) P = cexp_dt(sum_dl, cc.A2r, cc.Arev);     // product of the T multipliers
+                    fast_part();
                     S = cxfma(a[0], xin, x[0]);
 #pragma unroll
                     for (int t = 1; t < T; ++t) S = cxfma(a[t], S, x[t]);
@@ -304,13 +309,14 @@ __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) vo
                         P = a[0];
 #pragma unroll
                         for (int t = 1; t < T; ++t) P = cxmul(P, a[t]);
-                    } else P = cexp_dt(sum_dl, cc.A2r, cc.Arev);     // product of the T multipliers
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                     float2 Ct[2][4];                     // Cm four steps at a time, one such ahead
                     const float *lC = lB + (NS + n) * GE::ROW;
                     if constexpr (WANT_Y) read(lC, kFew, Ct[0]);
-                    __builtin_amdgcn_sched_barrier(0);
+                    slow_part();
                     cchannel_scan<LPC>(P, S, xin);
+                    fast_part();
                     if constexpr (TILE != kCkptInterval) {
                         const int64_t ll = l0 + li * T;
                         if (p.ckpt && li % ((int)kCkptInterval / T) == 0 && live && ll < L) {
@@ -336,6 +342,7 @@ __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) vo
                         if constexpr (!WANT_Y && LPC == 16) sP[ch][h * NS + n] = cxmul(sP[ch][h * NS + n], P);
                     }
                 }
+                edge_part();
                 if constexpr (!EARLY) {
                     if (h + 1 == NH) fetch_z();
                     fetch_next();

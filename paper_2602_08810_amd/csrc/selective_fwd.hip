@@ -10,8 +10,9 @@
 // with DPP moves, and the lane replays its steps from the carried-in state, accumulating y = sum_n C x on the fly.  The
 // state after the tile is the last lane's; it waits in LDS for the next tile of the same row.
 //
-// What bounds it: vector-ALU issue, one instruction per SIMD every four cycles whatever its kind (an exponential takes
-// two of these slots); with three wavefronts a SIMD the ALU is busy all the time.  Per state update: 7 slots for the
+// What bounds it: vector-ALU issue; with three wavefronts a SIMD the ALU is busy all the time.  Plain fp32 instructions of
+// two wavefronts issue side by side if the parts of a state run at the priorities of scan_common.hpp (120 -> 109 us on the
+// shape below; 2048 rows, L = 65536: 642 -> 585).  Per state update: 7 slots for the
 // multiplier (a product and an exponential), the input, the fold, the replay and the projection, and 1/T of the rest:
 // 13 to 16 for the prefix, its start and its end, and of 26 a step (softplus, gate, conversions) shared by the N states.
 // Hence 16 steps per lane, one LDS address for all of Bm and Cm, and tiles known to be whole without any check.
@@ -308,7 +309,7 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
                     }
                     __builtin_amdgcn_sched_barrier(0);
                     if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) next_n();
-                    __builtin_amdgcn_sched_barrier(0);
+                    slow_part();
 #pragma unroll
                     for (int t = 0; t < T; ++t) {
                         float g;
@@ -325,6 +326,7 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
                         for (int t = 1; t < T; ++t) P *= a[t];
                     } else P = exp2_fast(sum_dl * ac.A2);            // product of the T multipliers
                     channel_scan<LPC, AGG>(P, S, xin);
+                    fast_part();
                     if constexpr (CKPT && TILE != kCkptInterval) {
                         const int64_t ll = l0 + li * T;
                         if (li % ((int)kCkptInterval / T) == 0 && live && ll < L) {
