@@ -22,7 +22,9 @@
 // in the main part (15 multiply-adds and products, 3 for the exponential and its argument, 3.6 for the two scans and the
 // fold's product) and about 5 for prologue, epilogue and the work per tile.  The parts of a pass run at the issue priorities
 // of scan_common.hpp, prologue and epilogue at the highest, since a whole workgroup waits for the last at its barrier:
-// 369 -> 338 us (both parts at one priority: 351), B=16, D=2560, L=4096 2149 -> 1840.  (Before that the two wavefronts of a
+// 369 -> 338 us (both parts at one priority: 351), B=16, D=2560, L=4096 2149 -> 1840.  Of those 338 us the main part takes 241,
+// the prologue 45, the epilogue 40, the barrier 14; with conflict-free LDS accesses in prologue and epilogue, the epilogue's
+// reads under way together and 9 instructions less: 325 and 1805.  (Before that the two wavefronts of a
 // SIMD took turns at a raised priority, a pass each.)  Time on 64 lanes with 4 steps each and all four states of a wavefront
 // scanned together took 34.8.  Mamba-block shape (B=8, D=1536, N=16, L=2048, bf16): 440 -> 358 us + 25 us for the
 // sums of dBm and dCm; B=16, D=2560, L=4096: 2630 -> 2190 us.  Also tried: four channels per wavefront on rows of 16
@@ -65,9 +67,10 @@ __device__ __forceinline__ void half_scans(float P, float &S, float &Q, float &x
 }
 
 // CNT consecutive steps of a tile of 256 in LDS: laid out [step % 8 / 4][step / 8][step % 4], so that a lane's 8 steps
-// are two conflict-free 16-byte accesses, the second half rotated by half the banks, so that consecutive threads of
-// the prologue and epilogue (a few steps each) touch every bank once as well.  f is a multiple of CNT.
-__device__ __forceinline__ int step_slot(int f) { return ((f & 4) << 5) + (((f >> 3) << 2) ^ ((f & 4) << 3)) + (f & 3); }
+// are two conflict-free 16-byte accesses, the second half rotated by 16 floats, so that consecutive threads of the prologue
+// and epilogue (a few steps each) are free of conflicts as well: 8-byte accesses of 16 lanes go out together and must fall
+// into 32 different banks (rotated by 32 floats, every one of them took twice its time).  f is a multiple of CNT.
+__device__ __forceinline__ int step_slot(int f) { return ((f & 4) << 5) + (((f >> 3) << 2) ^ ((f & 4) << 2)) + (f & 3); }
 template <int CNT>
 __device__ __forceinline__ void lds_steps_read(const float *plane, int slot, float *out) {
     const float *p = plane + slot;
@@ -76,7 +79,7 @@ __device__ __forceinline__ void lds_steps_read(const float *plane, int slot, flo
     else {
 #pragma unroll
         for (int q = 0; q < CNT / 4; ++q) {
-            const float4 v = *reinterpret_cast<const float4 *>(plane + (q ? (slot ^ 32) + 128 : slot));
+            const float4 v = *reinterpret_cast<const float4 *>(plane + (q ? (slot ^ 16) + 128 : slot));
             out[4 * q] = v.x; out[4 * q + 1] = v.y; out[4 * q + 2] = v.z; out[4 * q + 3] = v.w;
         }
     }
@@ -89,7 +92,7 @@ __device__ __forceinline__ void lds_steps_write(float *plane, int slot, const fl
     else {
 #pragma unroll
         for (int q = 0; q < CNT / 4; ++q)
-            *reinterpret_cast<float4 *>(plane + (q ? (slot ^ 32) + 128 : slot)) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+            *reinterpret_cast<float4 *>(plane + (q ? (slot ^ 16) + 128 : slot)) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
     }
 }
 
@@ -337,11 +340,12 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 n_sg[i] = p.softplus ? sg : 1.0f;
                 if constexpr (HAS_Z) gate_bwd(z[i], dy[i], n_zf[i]);
             }
-            if (!FULL || ch >= Gact) {                   // steps past the end: Delta = 0 (a = 1), no input, no gradient
+            if (__builtin_expect(!FULL || ch >= Gact, !FULL)) {      // steps past the end: Delta = 0 (a = 1), no input, no gradient
                 const int f0 = (t0 % NTC) * TPT;
 #pragma unroll
                 for (int i = 0; i < TPT; ++i)
                     if (f0 + i >= rem || ch >= Gact) { dl[i] = 0.0f; u[i] = 0.0f; dy[i] = 0.0f; }
+                asm volatile("");                        // (a branch that is hardly ever taken, not six selects in every pass)
             }
         };
         auto prologue = [&](int ch, unsigned t0, int slot, int buf) {
@@ -358,10 +362,9 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         };
         // ---- epilogue: du, ddelta, dz of this thread's steps from the sums over states
         auto finish = [&](const int g, unsigned t0, unsigned f0, const float (&e_dl)[TPT], const float (&e_u)[TPT], const float (&e_dy)[TPT],
-                          const float (&s_yp)[TPT], const float (&s_du)[TPT], const float (&s_dd)[TPT]) {
+                          const float (&s_yp)[TPT], const float (&s_du)[TPT], const float (&s_dd)[TPT], const float Dsk) {
             const int ch = g + c_own;
             const bool live = ch < Gact;
-            const float Dsk = sDskip[live ? ch : Gact - 1];
             float o_u[TPT], o_d[TPT], o_z[TPT];
             float dD_part = 0.0f, db_part = 0.0f;
 #pragma unroll
@@ -406,27 +409,26 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         auto epilogue = [&](const int g, const int buf) {
             const unsigned t0 = fresh(tid), f0 = (t0 % NTC) * TPT;
             const int slot = step_slot((int)f0);
-            float e_in[3][TPT], s_yp[TPT], s_du[TPT], s_dd[TPT];
+            float e_in[3][TPT], s_yp[TPT], s_du[TPT], s_dd[TPT], v[W][3][TPT];
+#pragma unroll
+            for (int ww = 0; ww < W; ++ww)
+#pragma unroll
+                for (int j = HAS_Z ? 0 : 1; j < 3; ++j) lds_steps_read<TPT>(sPart[buf][c_own][ww][j], slot, v[ww][j]);
 #pragma unroll
             for (int j = 0; j < 3; ++j) lds_steps_read<TPT>(sIn[buf][c_own][j], slot, e_in[j]);
+            const float Dsk = sDskip[g + c_own < Gact ? g + c_own : Gact - 1];
+            // all reads before the first use: left to itself the compiler waits for each wavefront's sums before it reads the next
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 0; i < TPT; ++i) { s_yp[i] = 0.0f; s_du[i] = 0.0f; s_dd[i] = 0.0f; }
+            for (int i = 0; i < TPT; ++i) {
+                s_yp[i] = HAS_Z ? v[0][0][i] : 0.0f; s_du[i] = v[0][1][i]; s_dd[i] = v[0][2][i];
 #pragma unroll
-            for (int ww = 0; ww < W; ++ww) {
-                float v[TPT];
-                if constexpr (HAS_Z) {
-                    lds_steps_read<TPT>(sPart[buf][c_own][ww][0], slot, v);
-#pragma unroll
-                    for (int i = 0; i < TPT; ++i) s_yp[i] = ww ? s_yp[i] + v[i] : v[i];
+                for (int ww = 1; ww < W; ++ww) {
+                    if constexpr (HAS_Z) s_yp[i] += v[ww][0][i];
+                    s_du[i] += v[ww][1][i]; s_dd[i] += v[ww][2][i];
                 }
-                lds_steps_read<TPT>(sPart[buf][c_own][ww][1], slot, v);
-#pragma unroll
-                for (int i = 0; i < TPT; ++i) s_du[i] = ww ? s_du[i] + v[i] : v[i];
-                lds_steps_read<TPT>(sPart[buf][c_own][ww][2], slot, v);
-#pragma unroll
-                for (int i = 0; i < TPT; ++i) s_dd[i] = ww ? s_dd[i] + v[i] : v[i];
             }
-            finish(g, t0, f0, e_in[0], e_in[1], e_in[2], s_yp, s_du, s_dd);
+            finish(g, t0, f0, e_in[0], e_in[1], e_in[2], s_yp, s_du, s_dd, Dsk);
         };
         // ---- main: this lane's 8 steps of its channel, one state after the other
         auto states = [&](const int g, const int buf, const unsigned ln, float (&dl)[T], float (&du)[T], const float (&dy)[T],
@@ -583,7 +585,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 for (int t = 0; t < T; ++t) du[t] = u[t];
                 __syncthreads();                         // (one wavefront: orders the LDS accesses only)
                 states(g, 0, t0, dl, du, dy, yp, pu, pd);
-                finish(g, t0, (t0 % NTC) * TPT, dl, u, dy, yp, pu, pd);
+                finish(g, t0, (t0 % NTC) * TPT, dl, u, dy, yp, pu, pd, sDskip[g + c_own < Gact ? g + c_own : Gact - 1]);
                 __syncthreads();
             }
         } else {
@@ -596,9 +598,11 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 lds_steps_read<T>(sIn[buf][c][2], l4, dy);
                 states(g, buf, ln, dl, du, dy, yp, pu, pd);
                 edge_part();
-                if constexpr (HAS_Z) lds_steps_write<T>(sPart[buf][c][w][0], l4, yp);
-                lds_steps_write<T>(sPart[buf][c][w][1], l4, pu);
-                lds_steps_write<T>(sPart[buf][c][w][2], l4, pd);
+                float *part = &sPart[buf][0][w][0][0] + (0u - c & (unsigned)(sizeof(sPart[0][0]) / sizeof(float)));
+                constexpr int PL = sizeof(sPart[0][0][0][0]) / sizeof(float);
+                if constexpr (HAS_Z) lds_steps_write<T>(part, l4, yp);
+                lds_steps_write<T>(part + PL, l4, pu);
+                lds_steps_write<T>(part + 2 * PL, l4, pd);
             };
             auto next_inputs = [&](const int g, const int buf) {          // (past the last pair: unused)
                 const unsigned t0 = fresh(tid);
