@@ -26,7 +26,8 @@
 // replays with two multiply-adds a component, 9 for the multiplier, 6 for the scans), the rest is
 // lost where a wavefront waits for LDS or at the one barrier of a pass and the other of its SIMD cannot fill in alone.
 // B=8, D=1536, N=16, L=2048, bf16: 1505 us with time on 64 lanes of 4 steps and a scan of 64 lanes for each state (116
-// instructions an update), then 935, and with its parts at the priorities of scan_common.hpp 736.  B=4, D=2560, L=2048: call
+// instructions an update), then 935, with its parts at the priorities of scan_common.hpp 736,
+// and without bank conflicts in prologue and epilogue 678.  B=4, D=2560, L=2048: call
 // 1288 us, then 811 before the priorities; N = 4: 686 and 265.
 #include "kernels.hpp"
 #include "scan_common.hpp"
@@ -57,10 +58,12 @@ template <int N> struct CBwdGeom {
 };
 
 // The lane of a half that owns piece q of the tile (8 steps each), and the place of step f in a plane of 256 floats in LDS:
-// [step % 8 / 4][lane][step % 4], the second half rotated by half the banks (see step_slot in selective_bwd.hip).
+// [step % 8 / 4][lane][step % 4], the second half rotated by 16 floats and the lanes of the odd row by 8, so that a lane's 8
+// steps and the few steps of consecutive threads are both free of bank conflicts (see step_slot in selective_bwd.hip).
 __device__ __forceinline__ int piece_lane(int q) { return ((q & 1) << 4) + (q >> 1); }
+__device__ __forceinline__ int lane_slot(int li) { return (li << 2) ^ ((li & 16) >> 1); }
 __device__ __forceinline__ int cstep_slot(int f) {
-    return ((f & 4) << 5) + ((piece_lane(f >> 3) << 2) ^ ((f & 4) << 3)) + (f & 3);
+    return ((f & 4) << 5) + (lane_slot(piece_lane(f >> 3)) ^ ((f & 4) << 2)) + (f & 3);
 }
 template <int CNT>
 __device__ __forceinline__ void csteps_read(const float *plane, int slot, float *out) {
@@ -68,7 +71,7 @@ __device__ __forceinline__ void csteps_read(const float *plane, int slot, float 
     else {
 #pragma unroll
         for (int q = 0; q < CNT / 4; ++q) {
-            const float4 v = *reinterpret_cast<const float4 *>(plane + (q ? (slot ^ 32) + 128 : slot));
+            const float4 v = *reinterpret_cast<const float4 *>(plane + (q ? (slot ^ 16) + 128 : slot));
             out[4 * q] = v.x; out[4 * q + 1] = v.y; out[4 * q + 2] = v.z; out[4 * q + 3] = v.w;
         }
     }
@@ -79,7 +82,7 @@ __device__ __forceinline__ void csteps_write(float *plane, int slot, const float
     else {
 #pragma unroll
         for (int q = 0; q < CNT / 4; ++q)
-            *reinterpret_cast<float4 *>(plane + (q ? (slot ^ 32) + 128 : slot)) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+            *reinterpret_cast<float4 *>(plane + (q ? (slot ^ 16) + 128 : slot)) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
     }
 }
 
@@ -641,7 +644,7 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
             __syncthreads();                             // (one wavefront: orders the LDS accesses only)
             for (int g = 0; g < Gact; g += CP) {
                 const unsigned t0 = fresh(tid);
-                const int c = t0 >> 5, l4 = (t0 & 31) * 4;
+                const int c = t0 >> 5, l4 = lane_slot(t0 & 31);
                 float u[T], dl[T], dy[T], yp[T], pu[T], pd[T];
                 step_inputs(g + c_own, t0, u, dl, dy);
                 csteps_write<T>(sIn[0][c][0], l4, u);
@@ -664,7 +667,7 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
             // (they count themselves in sDone on their way, and wait for nobody before that).
             auto main_part = [&](const int g, const int buf) {
                 const unsigned ln = fresh(lane), c = ln >> 5;
-                const int l4 = (ln & 31) * 4;
+                const int l4 = lane_slot(ln & 31);
                 float dl[T], du[T], dy[T], yp[T], pu[T], pd[T];
                 csteps_read<T>(sIn[buf][c][0], l4, dl);
                 csteps_read<T>(sIn[buf][c][1], l4, du);
