@@ -11,7 +11,7 @@
 // Mapping.  A workgroup of W = N/4 wavefronts works on one tile of 256 steps at a time, last tile first, and on two
 // channels at a time: the halves of a wavefront are the two channels, and lane i of a half owns T = 8 consecutive steps
 // of the tile.  A wavefront holds four states, one after the other in the same registers, so a prefix over the tile is
-// a scan of 32 lanes shared by 8 steps.  The workgroup loops over G channels; a lane keeps its columns of Bm and Cm (4
+// a scan of 32 lanes shared by 8 steps (with N = 16 two at a time, whose scans over 16 lanes are one: see bwd_pairs).  The workgroup loops over G channels; a lane keeps its columns of Bm and Cm (4
 // states x 8 steps) and the running sums of dBm and dCm over channels in registers, so the reduction over channels costs
 // no traffic inside the loop.  What is summed over states (ypre for dz, du, dDelta) is added over the wavefront's
 // states in registers and over wavefronts through LDS: after a barrier every thread finishes a few consecutive steps
@@ -24,7 +24,7 @@
 // of scan_common.hpp, prologue and epilogue at the highest, since a whole workgroup waits for the last at its barrier:
 // 369 -> 338 us (both parts at one priority: 351), B=16, D=2560, L=4096 2149 -> 1840.  Of those 338 us the main part takes 241,
 // the prologue 45, the epilogue 40, the barrier 14; with conflict-free LDS accesses in prologue and epilogue, the epilogue's
-// reads under way together and 9 instructions less: 325 and 1805.  (Before that the two wavefronts of a
+// reads under way together and 9 instructions less: 325 and 1805; with states in pairs 318 and 1715.  (Before that the two wavefronts of a
 // SIMD took turns at a raised priority, a pass each.)  Time on 64 lanes with 4 steps each and all four states of a wavefront
 // scanned together took 34.8.  Mamba-block shape (B=8, D=1536, N=16, L=2048, bf16): 440 -> 358 us + 25 us for the
 // sums of dBm and dCm; B=16, D=2560, L=4096: 2630 -> 2190 us.  Also tried: four channels per wavefront on rows of 16
@@ -66,11 +66,62 @@ __device__ __forceinline__ void half_scans(float P, float &S, float &Q, float &x
         : "+v"(S), "+v"(Q), "+v"(xin), "+v"(Gin), "=&v"(Qn) : "v"(P), "v"(Pr));
 }
 
-// CNT consecutive steps of a tile of 256 in LDS: laid out [step % 8 / 4][step / 8][step % 4], so that a lane's 8 steps
-// are two conflict-free 16-byte accesses, the second half rotated by 16 floats, so that consecutive threads of the prologue
-// and epilogue (a few steps each) are free of conflicts as well: 8-byte accesses of 16 lanes go out together and must fall
-// into 32 different banks (rotated by 32 floats, every one of them took twice its time).  f is a multiple of CNT.
-__device__ __forceinline__ int step_slot(int f) { return ((f & 4) << 5) + (((f >> 3) << 2) ^ ((f & 4) << 2)) + (f & 3); }
+// rows of two registers: on return a holds the even rows of both (a's first), b the odd rows; its own inverse
+__device__ __forceinline__ void swap_rows(float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)f2i(a), (unsigned)f2i(b), false, false);
+    a = i2f((int)r[0]); b = i2f((int)r[1]);
+}
+
+// Both scans over the 16 lanes of each row: S becomes the inclusive prefix (lane 0 first) and Q the inclusive suffix (lane
+// 15 first) of the pairs (P, S) and (P, Q), x the prefix of the lane before (lane 0 keeps what it came with) and g the suffix
+// of the lane after (lane 15 keeps it).
+__device__ __forceinline__ void row_scans(float P, float &S, float &Q, float &x, float &g) {
+    float Pr = P;
+    asm("s_nop 1\n\t"
+        LRNNX_FR_STATE(0, 1, 2, 3, "row_shr:1" LRNNX_ALLROWS, "row_shl:1" LRNNX_ALLROWS)
+        LRNNX_FR_STATE(0, 1, 2, 3, "row_shr:2" LRNNX_ALLROWS, "row_shl:2" LRNNX_ALLROWS)
+        LRNNX_FR_STATE(0, 1, 2, 3, "row_shr:4" LRNNX_ALLROWS, "row_shl:4" LRNNX_ALLROWS)
+        "v_fmac_f32_dpp %0, %0, %1 row_shr:8" LRNNX_ALLROWS "\n\t"
+        "v_fmac_f32_dpp %2, %2, %3 row_shl:8" LRNNX_ALLROWS "\n\t"
+        "s_nop 0\n\t"
+        "v_mov_b32_dpp %4, %0 row_shr:1" LRNNX_ALLROWS "\n\t"
+        "v_mov_b32_dpp %5, %2 row_shl:1" LRNNX_ALLROWS
+        : "+v"(S), "+v"(P), "+v"(Q), "+v"(Pr), "+v"(x), "+v"(g));
+}
+
+// Both scans of two states over the tile, after their lanes' folds (P, S, Q: multiplier, end state from zero and adjoint handed on
+// from zero; one register for each state).  The rows of a half hold alternate pieces of eight steps, so a row swap gives row 0
+// both pieces of the first state and row 1 both of the second, and one scan over 16 lanes serves the two.  xc is the state that
+// enters the tile (lane 0 of the row of that state, zero elsewhere), hc the adjoint that enters it from the later side (lane 15).
+// On return xin and Gin are what enters each lane's piece of each state; the result is the adjoint that leaves the tile on the
+// earlier side (lane 0 of each row).
+__device__ __forceinline__ float pair_scans(float P0, float P1, float S0, float S1, float Q0, float Q1, float xc, float hc,
+                                            float &xin0, float &xin1, float &Gin0, float &Gin1) {
+    swap_rows(P0, P1); swap_rows(S0, S1); swap_rows(Q0, Q1);             // now 0: the earlier piece, 1: the later one
+    const float P = P0 * P1;
+    float S = __builtin_fmaf(P1, S0, S1), Q = __builtin_fmaf(P0, Q1, Q0);
+    S = __builtin_fmaf(P, xc, S);
+    Q = __builtin_fmaf(P, hc, Q);
+    row_scans(P, S, Q, xc, hc);
+    xin0 = xc; xin1 = __builtin_fmaf(P0, xc, S0);
+    Gin1 = hc; Gin0 = __builtin_fmaf(P1, hc, Q1);
+    swap_rows(xin0, xin1); swap_rows(Gin0, Gin1);
+    return Q;
+}
+
+// the eight steps of the tile that lane li of a half holds; PAIR: its two rows of 16 lanes hold alternate pieces
+template <bool PAIR> __device__ __forceinline__ int piece_of(int li) { return PAIR ? ((li & 15) << 1) | (li >> 4 & 1) : li; }
+
+// CNT consecutive steps of a tile of 256 in LDS: laid out [step % 8 / 4][lane that holds the 8 steps][step % 4], so that a
+// lane's 8 steps are two conflict-free 16-byte accesses, the second half rotated by 16 floats (and with PAIR the lanes of odd
+// rows by 8), so that consecutive threads of the prologue and epilogue (a few steps each) are free of conflicts as well: 8-byte
+// accesses of 16 lanes go out together and must fall into 32 different banks (rotated by 32 floats, every one of them took
+// twice its time).  f is a multiple of CNT.
+template <bool PAIR> __device__ __forceinline__ int lane_slot(int li) { return (li << 2) ^ (PAIR ? (li & 16) >> 1 : 0); }
+template <bool PAIR> __device__ __forceinline__ int step_slot(int f) {
+    const int g = f >> 3, li = PAIR ? (g >> 1) | ((g & 1) << 4) : g;
+    return ((f & 4) << 5) + (lane_slot<PAIR>(li) ^ ((f & 4) << 2)) + (f & 3);
+}
 template <int CNT>
 __device__ __forceinline__ void lds_steps_read(const float *plane, int slot, float *out) {
     const float *p = plane + slot;
@@ -128,6 +179,12 @@ template <int N> struct BwdGeom {
     static constexpr int NB = W >= 4 ? 2 : 1;        // buffers
 };
 
+// Whether a wavefront takes two states at a time, one scan over 16 lanes for both (pair_scans): 5.4 vector instructions a
+// state update for folds' ends and scans instead of 6.9, but both states' multipliers and inputs are held at once.  It pays for
+// many states, whose tiles are long in work: N = 16, B=16, D=2560, L=4096, bf16 1805 -> 1721 us, L=2048 of D=1536 325 -> 315,
+// N = 32 0.98 to 1.02; N = 8 5 to 20 % slower; the exact zero-order hold (gains beside the multipliers) 17 to 43 %, bilinear 2 %.
+template <int N, int DISC> constexpr bool bwd_pairs() { return N == 16 && (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC); }
+
 // `sequence bounds of batch entry b`: packed variable-length mode (cu != nullptr): batch entry b is the sequence of
 // steps cu[b] .. cu[b+1]-1 of ONE packed time axis of Lp steps.  The bounds are clamped to the packed axis, so no
 // content of cu can send an access out of the buffers.
@@ -153,6 +210,8 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
 
     constexpr bool OWN = GE::OWN;
     constexpr int NB = GE::NB;
+    constexpr bool PAIR = bwd_pairs<N, DISC>();
+    static_assert(!PAIR || (!OWN && NS % 2 == 0), "whole pairs of states, steps through LDS");
     __shared__ __attribute__((aligned(16))) float sIn[NB][CP][3][OWN ? 4 : TILE];       // delta, u, dypre of a pair of channels
     __shared__ __attribute__((aligned(16))) float sPart[NB][CP][W][3][OWN ? 4 : TILE];  // per wavefront: ypre, du, ddelta partials
     __shared__ __attribute__((aligned(16))) float sH[kBwdMaxG * N];   // a_{l0} H_{l0} carried to the earlier tile, per (channel, n)
@@ -225,7 +284,8 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
     // The addresses that follow from the thread's number are formed where they are needed: hoisted out of the loops by the
     // compiler they would sit in registers all through the main pass, which has none to spare.
     auto fresh = [](unsigned v) { asm volatile("" : "+v"(v)); return v; };
-    const unsigned first_lane = li == 0 ? ~0u : 0u, last_lane = li == 31 ? ~0u : 0u;
+    constexpr int LAST = PAIR ? 15 : 31;             // of the lanes that are scanned together
+    const unsigned first_lane = (li & LAST) == 0 ? ~0u : 0u, last_lane = (li & LAST) == LAST ? ~0u : 0u;
 
     // One tile.  FULL: all of its steps are valid and every row takes vector accesses, nothing to check per element (a
     // taken branch costs a wavefront about a hundred cycles).
@@ -241,7 +301,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
             const IO *BmT = Bm + l0 * N, *CmT = Cm + l0 * N;
 #pragma unroll
             for (int t = 0; t < T; ++t) {
-                const int step = li * T + t;
+                const int step = piece_of<PAIR>(li) * T + t;
                 const int row = step < rem ? step : rem - 1;
                 load_few_raw<IO, NS>(BmT + (unsigned)(row * N + n0), 0, NS, true, rB[t]);
                 load_few_raw<IO, NS>(CmT + (unsigned)(row * N + n0), 0, NS, true, rC[t]);
@@ -305,7 +365,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
             float tb[NS], tc[NS];
             unpack_few<IO, NS>(rB[t], tb);
             unpack_few<IO, NS>(rC[t], tc);
-            const bool ok = li * T + t < rem;
+            const bool ok = piece_of<PAIR>(li) * T + t < rem;
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 Bv[s][t] = ok ? tb[s] : 0.0f; Cv[s][t] = ok ? tc[s] : 0.0f;
@@ -408,7 +468,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         };
         auto epilogue = [&](const int g, const int buf) {
             const unsigned t0 = fresh(tid), f0 = (t0 % NTC) * TPT;
-            const int slot = step_slot((int)f0);
+            const int slot = step_slot<PAIR>((int)f0);
             float e_in[3][TPT], s_yp[TPT], s_du[TPT], s_dd[TPT], v[W][3][TPT];
 #pragma unroll
             for (int ww = 0; ww < W; ++ww)
@@ -437,10 +497,12 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 const int ch = g + (int)c < Gact ? g + (int)c : g;             // (the half past the last channel repeats the first, unused)
                 const bool own = g + (int)c < Gact;
                 const int at = ch * N + n0;
-                float Ak[NS], ck[NS], hc[NS];
+                float Ak[NS], ck[PAIR ? 1 : NS], hc[PAIR ? 1 : NS];
                 lds_few<NS>(&sAC[buf][0][c][n0], Ak);
-                lds_few<NS>(&sAC[buf][1][c][n0], ck);
-                lds_few<NS>(&sH[at], hc);
+                if constexpr (!PAIR) {
+                    lds_few<NS>(&sAC[buf][1][c][n0], ck);
+                    lds_few<NS>(&sH[at], hc);
+                }
                 if constexpr (DISC == DISC_ZOH_S6) {
 #pragma unroll
                     for (int t = 0; t < T; ++t) du[t] *= dl[t];      // S6 only ever needs Delta*u; the others keep u
@@ -449,6 +511,62 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
 #pragma unroll
                 for (int t = 1; t < T; ++t) sum_dl += dl[t];
                 float dA[NS];
+                if constexpr (PAIR) {
+                    const int row = ln >> 4 & 1;                     // of the half, and the state of a pair that it scans
+#pragma unroll
+                    for (int s = 0; s < NS; s += 2) {
+                        float a[2][T], x[2][T], P[2], S[2], Q[2], xin[2], Gin[2];
+                        slow_part();
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            // the lane's folds, as below but from zero: what enters the tile joins the scan
+                            const ACoef ac = make_acoef<DISC>(Ak[s + j]);
+#pragma unroll
+                            for (int t = 0; t < T; ++t) {
+                                float g;
+                                disc_ag<DISC>(dl[t], ac, a[j][t], g);
+                                x[j][t] = du[t] * Bv[s + j][t];
+                            }
+                            S[j] = x[j][0]; Q[j] = a[j][T - 1] * (Cv[s + j][T - 1] * dy[T - 1]);
+#pragma unroll
+                            for (int t = 1; t < T; ++t) S[j] = __builtin_fmaf(a[j][t], S[j], x[j][t]);
+#pragma unroll
+                            for (int t = T - 2; t >= 0; --t) Q[j] = a[j][t] * __builtin_fmaf(Cv[s + j][t], dy[t], Q[j]);
+                            P[j] = exp2_fast(sum_dl * ac.A2);
+                        }
+                        const float xc = i2f(f2i(sAC[buf][1][c][n0 + s + row]) & (int)first_lane);
+                        const float hc2 = i2f(f2i(sH[at + s + row]) & (int)last_lane);
+                        const float out = pair_scans(P[0], P[1], S[0], S[1], Q[0], Q[1], xc, hc2, xin[0], xin[1], Gin[0], Gin[1]);
+                        if (own && (ln & 15) == 0) sH[at + s + row] = out;       // carried to the earlier tile
+                        fast_part();
+                        // replay of both states side by side (earliest step first), then of both adjoints (last step first): two
+                        // chains whose instructions fill each other's result latencies
+                        float xp[2] = {xin[0], xin[1]}, dAp[2] = {0.0f, 0.0f};
+#pragma unroll
+                        for (int t = 0; t < T; ++t)
+#pragma unroll
+                            for (int j = 0; j < 2; ++j) { xp[j] = __builtin_fmaf(a[j][t], xp[j], x[j][t]); x[j][t] = xp[j]; }
+#pragma unroll
+                        for (int t = T - 1; t >= 0; --t)
+#pragma unroll
+                            for (int j = 0; j < 2; ++j) {
+                                auto acc = [&](float &sum, float m1, float m2) { sum = (s + j == 0) ? m1 * m2 : __builtin_fmaf(m1, m2, sum); };
+                                const float H = __builtin_fmaf(Cv[s + j][t], dy[t], Gin[j]);
+                                Gin[j] = a[j][t] * H;
+                                dC[s + j][t] = __builtin_fmaf(dy[t], x[j][t], dC[s + j][t]);
+                                if constexpr (HAS_Z) acc(yp[t], Cv[s + j][t], x[j][t]);
+                                acc(pu[t], H, Bv[s + j][t]);         // (S6 and dirac: see below)
+                                dB[s + j][t] = __builtin_fmaf(H, du[t], dB[s + j][t]);
+                                const float q = Gin[j] * (t > 0 ? x[j][t - 1] : xin[j]);
+                                acc(pd[t], q, Ak[s + j]);
+                                dAp[j] = __builtin_fmaf(q, dl[t], dAp[j]);
+                                // (computed here, as below)
+                                if constexpr (HAS_Z) asm volatile("" : "+v"(yp[t]));
+                                asm volatile("" : "+v"(dC[s + j][t]), "+v"(dB[s + j][t]), "+v"(pu[t]), "+v"(pd[t]), "+v"(dAp[j]));
+                            }
+                        dA[s] = dAp[0]; dA[s + 1] = dAp[1];
+                    }
+                } else
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
                     const ACoef ac = make_acoef<DISC>(Ak[s]);
@@ -591,7 +709,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         } else {
             auto main_part = [&](const int g, const int buf) {
                 const unsigned ln = fresh(lane), c = ln >> 5;
-                const int l4 = (ln & 31) * 4;
+                const int l4 = lane_slot<PAIR>(ln & 31);
                 float dl[T], du[T], dy[T], yp[T], pu[T], pd[T];
                 lds_steps_read<T>(sIn[buf][c][0], l4, dl);
                 lds_steps_read<T>(sIn[buf][c][1], l4, du);
@@ -606,7 +724,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
             };
             auto next_inputs = [&](const int g, const int buf) {          // (past the last pair: unused)
                 const unsigned t0 = fresh(tid);
-                prologue(g + c_own, t0, step_slot((int)((t0 % NTC) * TPT)), buf);
+                prologue(g + c_own, t0, step_slot<PAIR>((int)((t0 % NTC) * TPT)), buf);
                 fetch(t0);
             };
             next_inputs(0, 0);
@@ -651,7 +769,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         if constexpr (PART) {
             // to this workgroup's own slot of the workspace, as 16-byte pieces in the order the lanes hold them (the sum
             // over workgroups and the transposition to [L,N] are k_ss_bwd_maps's)
-            float *pt = p.part + (((slot0 + tile_first + tile) * gridDim.x + blockIdx.x) * 2 * N + n0) * TILE + lane * 4;
+            float *pt = p.part + (((slot0 + tile_first + tile) * gridDim.x + blockIdx.x) * 2 * N + n0) * TILE + (half * 32 + piece_of<PAIR>(li)) * 4;
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 *reinterpret_cast<float4 *>(pt + s * TILE) = make_float4(oB[s][0], oB[s][1], oB[s][2], oB[s][3]);
@@ -660,7 +778,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         } else {
             // without a workspace: float atomics, on consecutive addresses (the sums change their order in LDS: lanes that add
             // 8 steps apart take a transaction each, 8 times as long)
-            const unsigned t0 = fresh(tid), st0 = (t0 & 31) * T + (t0 >> 5 & 1) * 4;
+            const unsigned t0 = fresh(tid), st0 = piece_of<PAIR>(t0 & 31) * T + (t0 >> 5 & 1) * 4;
             if constexpr (OWN) {
                 float *gB = p.dBm + bc0 + l0 * N, *gC = p.dCm + bc0 + l0 * N;
 #pragma unroll
