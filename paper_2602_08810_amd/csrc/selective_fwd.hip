@@ -12,7 +12,7 @@
 //
 // What bounds it: vector-ALU issue; with three wavefronts a SIMD the ALU is busy all the time.  Plain fp32 instructions of
 // two wavefronts issue side by side if the parts of a state run at the priorities of scan_common.hpp (120 -> 109 us on the
-// shape below; 2048 rows, L = 65536: 642 -> 585).  Per state update: 7 slots for the
+// shape below; 2048 rows, L = 65536: 642 -> 585, and with two states at a time 564).  Per state update: 7 slots for the
 // multiplier (a product and an exponential), the input, the fold, the replay and the projection, and 1/T of the rest:
 // 13 to 16 for the prefix, its start and its end, and of 26 a step (softplus, gate, conversions) shared by the N states.
 // Hence 16 steps per lane, one LDS address for all of Bm and Cm, and tiles known to be whole without any check.
@@ -62,6 +62,27 @@ __device__ __forceinline__ void channel_scan(float &P, float &S, float &xin) {
 #undef LRNNX_PS
 #undef LRNNX_S
 }
+// The same for two states, whose instructions are each other's wait states.
+template <int LPC, bool KEEP_P>
+__device__ __forceinline__ void channel_scan2(float (&P)[2], float (&S)[2], float (&xin)[2]) {
+    static_assert(LPC == 16 || (LPC == 64 && !KEEP_P), "lanes of a channel");
+#define LRNNX_S2(CTRL) "v_fmac_f32_dpp %0, %0, %1 " CTRL "\n\tv_fmac_f32_dpp %3, %3, %4 " CTRL "\n\ts_nop 0\n\t"
+#define LRNNX_PS2(CTRL) LRNNX_F_STATE(0, 1, CTRL) LRNNX_F_STATE(3, 4, CTRL)
+#define LRNNX_SCAN2(LAST, CTRL)                                                                                          \
+    asm("s_nop 1\n\t" LRNNX_PS2("row_shr:1" LRNNX_ALLROWS) LRNNX_PS2("row_shr:2" LRNNX_ALLROWS)                          \
+        LRNNX_PS2("row_shr:4" LRNNX_ALLROWS) LAST "v_mov_b32_dpp %2, %0 " CTRL "\n\tv_mov_b32_dpp %5, %3 " CTRL          \
+        : "+v"(S[0]), "+v"(P[0]), "+v"(xin[0]), "+v"(S[1]), "+v"(P[1]), "+v"(xin[1]))
+    if constexpr (LPC == 16) {
+        if constexpr (KEEP_P) LRNNX_SCAN2(LRNNX_PS2("row_shr:8" LRNNX_ALLROWS), "row_shr:1" LRNNX_ALLROWS);
+        else LRNNX_SCAN2(LRNNX_S2("row_shr:8" LRNNX_ALLROWS), "row_shr:1" LRNNX_ALLROWS);
+    } else {
+        LRNNX_SCAN2(LRNNX_PS2("row_shr:8" LRNNX_ALLROWS) LRNNX_PS2("row_bcast:15 row_mask:0xa bank_mask:0xf")
+                    LRNNX_S2("row_bcast:31 row_mask:0xc bank_mask:0xf"), "wave_shr:1" LRNNX_ALLROWS);
+    }
+#undef LRNNX_SCAN2
+#undef LRNNX_PS2
+#undef LRNNX_S2
+}
 
 template <int LPC, int T> struct FwdGeom {
     static constexpr int W = LPC * T / 64 < 8 ? LPC * T / 64 : 8;      // wavefronts of a workgroup
@@ -84,6 +105,12 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
     constexpr bool EARLY = sizeof(IO) == 2 ? LPC > 16 || N <= 8 : LPC > 16 && N <= 8;
     constexpr bool LATE_Z = sizeof(IO) == 4 && T == 16 && LPC == 16;
     constexpr bool AGG = !WANT_Y && !CKPT;           // the aggregate launch of the chunk-carry path
+    // Two states at a time: their chains (folds, scan, replay) fill each other's latencies, which counts where few wavefronts share a
+    // SIMD: 2048 rows, L = 65536, N = 16, bf16 577 -> 564 us, 64 rows of 16384 steps 21.5 -> 20.5, states alone (B=16, D=2560,
+    // L=4096) 432 -> 407.  Not where it takes the registers of a wavefront (16 lanes with outputs: 110 -> 124 us, 30 spilled), with
+    // few states (N = 8: up to 6 % longer), and in float32 with 8 steps (2 % longer).
+    constexpr bool PAIR = NS == 16 && (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) &&
+                          (!WANT_Y || (LPC == 64 && !(T == 8 && sizeof(IO) == 4)));
     static_assert(TILE % kCkptInterval == 0 && RPT * NT == TILE, "tile shape");
     __shared__ __attribute__((aligned(16))) float sBC[WANT_Y ? 2 * NS : NS + 1][GE::ROW];   // Bm, Cm
     __shared__ __attribute__((aligned(16))) float sA[CH + 1][N], sX[CH + 2][N];    // A; the state entering the next tile, and zeros
@@ -290,43 +317,7 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
                 };
                 const float *lB = &sBC[0][li * 4], *lA = &sA[ch][h * NS];
                 const float *lX = &sX[li == 0 ? ch : CH][h * NS];    // the carried state enters through the channel's first lane
-                float Bt[T], Ct[T], An = lA[0], xn = lX[0];
-                read(lB, Bt);
-#pragma unroll 1
-                for (int n = 0; n < NS; ++n) {
-                    const ACoef ac = make_acoef<DISC>(An);
-                    float xin = xn;
-                    auto next_n = [&]() {                // (after the last n: one row further, not used)
-                        An = lA[n + 1]; xn = lX[n + 1]; read(lB + (n + 1) * GE::ROW, Bt);
-                    };
-                    float a[T], x[T], P, S;
-                    if constexpr (WANT_Y) read(lB + (NS + n) * GE::ROW, Ct);
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int t = 0; t < T; ++t) {
-                        if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) x[t] = du[t] * Bt[t];
-                        else x[t] = Bt[t];
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                    if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) next_n();
-                    slow_part();
-#pragma unroll
-                    for (int t = 0; t < T; ++t) {
-                        float g;
-                        disc_ag<DISC>(dl[t], ac, a[t], g);
-                        if constexpr (DISC != DISC_ZOH_S6 && DISC != DISC_DIRAC) x[t] *= g * du[t];
-                    }
-                    if constexpr (DISC != DISC_ZOH_S6 && DISC != DISC_DIRAC) next_n();
-                    S = __builtin_fmaf(a[0], xin, x[0]);
-#pragma unroll
-                    for (int t = 1; t < T; ++t) S = __builtin_fmaf(a[t], S, x[t]);
-                    if constexpr (DISC == DISC_BILINEAR) {
-                        P = a[0];
-#pragma unroll
-                        for (int t = 1; t < T; ++t) P *= a[t];
-                    } else P = exp2_fast(sum_dl * ac.A2);            // product of the T multipliers
-                    channel_scan<LPC, AGG>(P, S, xin);
-                    fast_part();
+                auto checkpoint = [&](int n, float xin) {            // the state entering this lane's first step
                     if constexpr (CKPT && TILE != kCkptInterval) {
                         const int64_t ll = l0 + li * T;
                         if (li % ((int)kCkptInterval / T) == 0 && live && ll < L) {
@@ -334,16 +325,117 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
                             p.ckpt[(r * nck + ck_first + ll / kCkptInterval) * N + h * NS + n] = xin;
                         }
                     }
-                    if constexpr (WANT_Y) {
+                };
+                auto leave = [&](int n, float x, float P) {
+                    if (li == LPC - 1) {                 // the channel's last lane ends on the tile's last step
+                        sX[ch][h * NS + n] = x;
+                        if constexpr (AGG) sP[ch][h * NS + n] *= P;
+                    }
+                };
+                if constexpr (PAIR) {
+                    float An[2] = {lA[0], lA[1]}, xn[2] = {lX[0], lX[1]};
+#pragma unroll 1
+                    for (int n = 0; n < NS; n += 2) {
+                        // Bm's reads are under way while the multipliers are formed, Cm's (four steps at a time, one such
+                        // ahead) during the scan; A and the carried state one pair ahead
+                        const ACoef ac[2] = {make_acoef<DISC>(An[0]), make_acoef<DISC>(An[1])};
+                        float xin[2] = {xn[0], xn[1]}, a[2][T], x[2][T], P[2], S[2];
+                        read(lB + n * GE::ROW, x[0]);
+                        read(lB + (n + 1) * GE::ROW, x[1]);
+                        An[0] = lA[n + 2]; An[1] = lA[n + 3]; xn[0] = lX[n + 2]; xn[1] = lX[n + 3];    // (after the last: not used)
+                        slow_part();
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            float g;
+#pragma unroll
+                            for (int t = 0; t < T; ++t) disc_ag<DISC>(dl[t], ac[j], a[j][t], g);
+                            P[j] = exp2_fast(sum_dl * ac[j].A2);         // product of the T multipliers
+                        }
+                        fast_part();
+#pragma unroll
+                        for (int t = 0; t < T; ++t)
+#pragma unroll
+                            for (int j = 0; j < 2; ++j) {
+                                x[j][t] *= du[t];
+                                S[j] = __builtin_fmaf(a[j][t], t ? S[j] : xin[j], x[j][t]);
+                            }
+                        float Ct[2][2][4];
+                        const float *lC = lB + (NS + n) * GE::ROW;
+                        auto read_C = [&](int q) {
+#pragma unroll
+                            for (int j = 0; j < 2; ++j) {
+                                const float4 f = *reinterpret_cast<const float4 *>(lC + j * GE::ROW + q * GE::Q);
+                                float *c = Ct[q % 2][j];
+                                c[0] = f.x; c[1] = f.y; c[2] = f.z; c[3] = f.w;
+                            }
+                        };
+                        if constexpr (WANT_Y) read_C(0);
+                        slow_part();
+                        channel_scan2<LPC, AGG>(P, S, xin);
+                        fast_part();
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) checkpoint(n + j, xin[j]);
+                        if constexpr (WANT_Y) {
+#pragma unroll
+                            for (int t = 0; t < T; ++t) {
+                                if (t % 4 == 0 && t + 4 < T) read_C(t / 4 + 1);
+#pragma unroll
+                                for (int j = 0; j < 2; ++j) {
+                                    xin[j] = __builtin_fmaf(a[j][t], xin[j], x[j][t]);
+                                    yv[t] = __builtin_fmaf(Ct[t / 4 % 2][j][t % 4], xin[j], yv[t]);
+                                }
+                            }
+                        }
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) leave(n + j, WANT_Y ? xin[j] : S[j], P[j]);
+                    }
+                } else {
+                    float Bt[T], Ct[T], An = lA[0], xn = lX[0];
+                    read(lB, Bt);
+#pragma unroll 1
+                    for (int n = 0; n < NS; ++n) {
+                        const ACoef ac = make_acoef<DISC>(An);
+                        float xin = xn;
+                        auto next_n = [&]() {                // (after the last n: one row further, not used)
+                            An = lA[n + 1]; xn = lX[n + 1]; read(lB + (n + 1) * GE::ROW, Bt);
+                        };
+                        float a[T], x[T], P, S;
+                        if constexpr (WANT_Y) read(lB + (NS + n) * GE::ROW, Ct);
+                        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                         for (int t = 0; t < T; ++t) {
-                            xin = __builtin_fmaf(a[t], xin, x[t]);
-                            yv[t] = __builtin_fmaf(Ct[t], xin, yv[t]);
+                            if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) x[t] = du[t] * Bt[t];
+                            else x[t] = Bt[t];
                         }
-                    }
-                    if (li == LPC - 1) {                 // the channel's last lane ends on the tile's last step
-                        sX[ch][h * NS + n] = WANT_Y ? xin : S;
-                        if constexpr (AGG) sP[ch][h * NS + n] *= P;
+                        __builtin_amdgcn_sched_barrier(0);
+                        if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) next_n();
+                        slow_part();
+#pragma unroll
+                        for (int t = 0; t < T; ++t) {
+                            float g;
+                            disc_ag<DISC>(dl[t], ac, a[t], g);
+                            if constexpr (DISC != DISC_ZOH_S6 && DISC != DISC_DIRAC) x[t] *= g * du[t];
+                        }
+                        if constexpr (DISC != DISC_ZOH_S6 && DISC != DISC_DIRAC) next_n();
+                        S = __builtin_fmaf(a[0], xin, x[0]);
+#pragma unroll
+                        for (int t = 1; t < T; ++t) S = __builtin_fmaf(a[t], S, x[t]);
+                        if constexpr (DISC == DISC_BILINEAR) {
+                            P = a[0];
+#pragma unroll
+                            for (int t = 1; t < T; ++t) P *= a[t];
+                        } else P = exp2_fast(sum_dl * ac.A2);            // product of the T multipliers
+                        channel_scan<LPC, AGG>(P, S, xin);
+                        fast_part();
+                        checkpoint(n, xin);
+                        if constexpr (WANT_Y) {
+#pragma unroll
+                            for (int t = 0; t < T; ++t) {
+                                xin = __builtin_fmaf(a[t], xin, x[t]);
+                                yv[t] = __builtin_fmaf(Ct[t], xin, yv[t]);
+                            }
+                        }
+                        leave(n, WANT_Y ? xin : S, P);
                     }
                 }
                 if (LATE_Z && h + 1 == NH) fetch_z();
