@@ -31,12 +31,46 @@ __device__ __forceinline__ float2 cfma(float2 a, float2 b, float2 c) {   // a*b 
 constexpr int kSpinLimit = 1 << 22;          // polls before a waiting wavefront gives up
 constexpr int kAnchor = 16;                  // every 16th group publishes its true end state
 
-// element of a wave-uniform row at a lane's 32-bit byte offset (scalar base + vector offset addressing)
-__device__ __forceinline__ const float2 &at(const float2 *row, unsigned byte_off) {
-    return *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(row) + byte_off);
+// Elements of a wave-uniform row at a lane's 32-bit byte offset (scalar base + vector offset addressing), for the
+// tensors that are streamed through once.  NT: a non-temporal access, which leaves the caches to others.
+typedef float stream_f2 __attribute__((ext_vector_type(2)));
+template <bool NT>
+__device__ __forceinline__ float2 load_at(const float2 *row, unsigned byte_off) {
+    const stream_f2 *q = reinterpret_cast<const stream_f2 *>(reinterpret_cast<const char *>(row) + byte_off);
+    const stream_f2 t = NT ? __builtin_nontemporal_load(q) : *q;
+    return make_float2(t.x, t.y);
 }
-__device__ __forceinline__ float2 &at(float2 *row, unsigned byte_off) {
-    return *reinterpret_cast<float2 *>(reinterpret_cast<char *>(row) + byte_off);
+template <bool NT>
+__device__ __forceinline__ float load_at(const float *row, unsigned byte_off) {
+    const float *q = reinterpret_cast<const float *>(reinterpret_cast<const char *>(row) + byte_off);
+    return NT ? __builtin_nontemporal_load(q) : *q;
+}
+template <bool NT>
+__device__ __forceinline__ void store_at(float2 *row, unsigned byte_off, float2 v) {
+    stream_f2 *q = reinterpret_cast<stream_f2 *>(reinterpret_cast<char *>(row) + byte_off);
+    const stream_f2 t = {v.x, v.y};
+    if (NT) __builtin_nontemporal_store(t, q); else *q = t;
+}
+template <bool NT>
+__device__ __forceinline__ void store_at(float *row, unsigned byte_off, float v) {
+    float *q = reinterpret_cast<float *>(reinterpret_cast<char *>(row) + byte_off);
+    if (NT) __builtin_nontemporal_store(v, q); else *q = v;
+}
+
+// Where the streams go past the caches (a forward call and its adjoint, us, before and after):
+// - What an adjoint writes is not read again in the call: its stores are always non-temporal.  LTI, P = 1024, 8 x 8192 steps
+//   498 -> 485; 4 x 4096 steps, P = 256 43.2 -> 41.2; real coefficients, P = 1024, 8 x 2048 steps 127.5 -> 118.5.  The forward's
+//   states are read next by the adjoint, and its stores stay ordinary (non-temporal: 127 -> 133).
+// - What an adjoint reads is read once, if the rows of P values are whole cache lines: then its loads are
+//   non-temporal too (485 -> 458, 118.5 -> 116).  Rows that are not share their lines with the neighbouring
+//   workgroup's (P = 1000 real, 8 x 4096 steps: 277 and 292 with such loads).
+// - The forward's loads likewise, but only from 384 MiB of traffic on, one and a half times the 256 MiB of Infinity Cache: there
+//   458 -> 440 (complex coefficients, P = 1024, 8 x 4096: 397 -> 378); with less the inputs are often still in it (real
+//   coefficients, 8 x 2048 steps: 116 and 120).
+constexpr int64_t kCacheLine = 128;
+constexpr int64_t kStreamPastCaches = 384ll << 20;
+inline bool whole_lines(int64_t row_bytes, const void *a, const void *b, const void *c) {
+    return ((row_bytes | (int64_t)(intptr_t)a | (int64_t)(intptr_t)b | (int64_t)(intptr_t)c) & (kCacheLine - 1)) == 0;
 }
 
 // A published slot is an 8-byte complex value written by one relaxed atomic store at agent scope; kNotReady

@@ -33,21 +33,13 @@ template <> struct Elem<true> {
     static __device__ __forceinline__ T conj(T a) { return make_float2(a.x, -a.y); }
 };
 
-template <typename E>
-__device__ __forceinline__ const E &el(const E *row, unsigned byte_off) {
-    return *reinterpret_cast<const E *>(reinterpret_cast<const char *>(row) + byte_off);
-}
-template <typename E>
-__device__ __forceinline__ E &el(E *row, unsigned byte_off) {
-    return *reinterpret_cast<E *>(reinterpret_cast<char *>(row) + byte_off);
-}
-
 // ANCH: every ANCH-th group publishes its true end state; a group looks back over at most ANCH-1 aggregates.
 // BWD = false: the scan.  BWD = true: its adjoint, the same chain over reversed time (scan position j is time
 // k = L-1-j): g_k = gx_k + conj(a_{k+1}) g_{k+1}, read through p.b = gx and written through p.x = db; the coefficient
 // of a position is therefore the NEXT time step's a, conjugated.  Each step also loads the saved state before it
 // and writes da_k = conj(x_{k-1}) g_k; the last position writes dx0 = conj(a_0) g_0 through p.x_last.
-template <bool CPLX, int CS, int GW, int ANCH, bool BWD>
+// NTL: non-temporal loads of the streamed inputs; the adjoint's stores are always so (see chain.hpp).
+template <bool CPLX, int CS, int GW, int ANCH, bool BWD, bool NTL>
 __global__ __launch_bounds__(GW * 64) void k_diag_scan(const DiagParams p) {
     using EL = Elem<CPLX>;
     using E = typename EL::T;
@@ -77,14 +69,14 @@ __global__ __launch_bounds__(GW * 64) void k_diag_scan(const DiagParams p) {
     if (full && (!BWD || k0 > 0)) {
         if (okp) {
 #pragma unroll
-            for (int i = 0; i < CS; ++i) { a[i] = el(arow + i * tstep, boff); bv[i] = el(brow + i * tstep, boff); }
+            for (int i = 0; i < CS; ++i) { a[i] = load_at<NTL>(arow + i * tstep, boff); bv[i] = load_at<NTL>(brow + i * tstep, boff); }
         }
     } else if (okp) {
 #pragma unroll
         for (int i = 0; i < CS; ++i)
             if (k0 + i < p.L) {
-                if (!BWD || k0 + i > 0) a[i] = el(arow + i * tstep, boff);
-                bv[i] = el(brow + i * tstep, boff);
+                if (!BWD || k0 + i > 0) a[i] = load_at<NTL>(arow + i * tstep, boff);
+                bv[i] = load_at<NTL>(brow + i * tstep, boff);
             }
     }
     E xprev[BWD ? CS : 1];
@@ -96,13 +88,13 @@ __global__ __launch_bounds__(GW * 64) void k_diag_scan(const DiagParams p) {
         if (k0 + CS < p.L) {
             if (okp) {
 #pragma unroll
-                for (int i = 0; i < CS; ++i) xprev[i] = el(xrow + i * tstep, boff);
+                for (int i = 0; i < CS; ++i) xprev[i] = load_at<NTL>(xrow + i * tstep, boff);
             }
         } else if (okp) {
 #pragma unroll
             for (int i = 0; i < CS; ++i) {
                 const int64_t k = p.L - 1 - (k0 + i);
-                if (k > 0) xprev[i] = el(xrow + i * tstep, boff);
+                if (k > 0) xprev[i] = load_at<NTL>(xrow + i * tstep, boff);
                 else if (k == 0 && p.x0) xprev[i] = reinterpret_cast<const E *>(p.x0)[(int64_t)b * P + pp];
             }
         }
@@ -188,8 +180,8 @@ __global__ __launch_bounds__(GW * 64) void k_diag_scan(const DiagParams p) {
 #pragma unroll
             for (int i = 0; i < CS; ++i) {
                 x = EL::fma(a[i], x, bv[i]);
-                el(xrow_out + i * tstep, boff) = x;
-                if constexpr (BWD) el(darow + i * tstep, boff) = EL::mul(EL::conj(xprev[i]), x);
+                store_at<BWD>(xrow_out + i * tstep, boff, x);
+                if constexpr (BWD) store_at<BWD>(darow + i * tstep, boff, EL::mul(EL::conj(xprev[i]), x));
             }
         }
         xl = x;
@@ -198,8 +190,8 @@ __global__ __launch_bounds__(GW * 64) void k_diag_scan(const DiagParams p) {
         for (int i = 0; i < CS; ++i) {
             x = EL::fma(a[i], x, bv[i]);
             if (k0 + i < p.L) {
-                el(xrow_out + i * tstep, boff) = x;
-                if constexpr (BWD) el(darow + i * tstep, boff) = EL::mul(EL::conj(xprev[i]), x);
+                store_at<BWD>(xrow_out + i * tstep, boff, x);
+                if constexpr (BWD) store_at<BWD>(darow + i * tstep, boff, EL::mul(EL::conj(xprev[i]), x));
                 xl = x;
             }
         }
@@ -229,25 +221,28 @@ int diag_scan_min_group_steps(int is_complex) { return kDsCS * (is_complex ? kDs
 int diag_scan_anchor(int is_complex) { return is_complex ? kDsCplxAnchor : kAnchor; }
 int diag_scan_bwd_group_steps(int is_complex) { return (is_complex ? kDsBwdCplxCS : kDsCS) * kDsBwdGW; }
 
-hipError_t launch_diag_scan(const DiagParams &p, hipStream_t s) {
+template <bool CPLX, int CS, int GW, int ANCH, bool BWD>
+static void launch_diag(const DiagParams &p, bool nt, hipStream_t s) {
     const int npslab = (p.P + 63) / 64;
     dim3 grid((unsigned)(npslab * p.B), p.ngroups);
-    if (p.is_complex)
-        hipLaunchKernelGGL((k_diag_scan<true, kDsCS, kDsCplxGW, kDsCplxAnchor, false>), grid, dim3(kDsCplxGW * 64), 0, s, p);
-    else if (ds_gw(p.B, p.P, 0) == kDsGWSmall)
-        hipLaunchKernelGGL((k_diag_scan<false, kDsCS, kDsGWSmall, kAnchor, false>), grid, dim3(kDsGWSmall * 64), 0, s, p);
-    else
-        hipLaunchKernelGGL((k_diag_scan<false, kDsCS, kDsGWLarge, kAnchor, false>), grid, dim3(kDsGWLarge * 64), 0, s, p);
+    if (nt) hipLaunchKernelGGL((k_diag_scan<CPLX, CS, GW, ANCH, BWD, true>), grid, dim3(GW * 64), 0, s, p);
+    else hipLaunchKernelGGL((k_diag_scan<CPLX, CS, GW, ANCH, BWD, false>), grid, dim3(GW * 64), 0, s, p);
+}
+
+static int64_t row_bytes(const DiagParams &p) { return (int64_t)p.P * (p.is_complex ? 8 : 4); }
+
+hipError_t launch_diag_scan(const DiagParams &p, hipStream_t s) {
+    const bool nt = whole_lines(row_bytes(p), p.a, p.b, p.x) && 3 * row_bytes(p) * p.B * p.L >= kStreamPastCaches;
+    if (p.is_complex) launch_diag<true, kDsCS, kDsCplxGW, kDsCplxAnchor, false>(p, nt, s);
+    else if (ds_gw(p.B, p.P, 0) == kDsGWSmall) launch_diag<false, kDsCS, kDsGWSmall, kAnchor, false>(p, nt, s);
+    else launch_diag<false, kDsCS, kDsGWLarge, kAnchor, false>(p, nt, s);
     return hipGetLastError();
 }
 
 hipError_t launch_diag_scan_bwd(const DiagParams &p, hipStream_t s) {
-    const int npslab = (p.P + 63) / 64;
-    dim3 grid((unsigned)(npslab * p.B), p.ngroups);
-    if (p.is_complex)
-        hipLaunchKernelGGL((k_diag_scan<true, kDsBwdCplxCS, kDsBwdGW, kDsCplxAnchor, true>), grid, dim3(kDsBwdGW * 64), 0, s, p);
-    else
-        hipLaunchKernelGGL((k_diag_scan<false, kDsCS, kDsBwdGW, kAnchor, true>), grid, dim3(kDsBwdGW * 64), 0, s, p);
+    const bool nt = whole_lines(row_bytes(p), p.a, p.b, p.xs) && whole_lines(0, p.x, p.da, nullptr);
+    if (p.is_complex) launch_diag<true, kDsBwdCplxCS, kDsBwdGW, kDsCplxAnchor, true>(p, nt, s);
+    else launch_diag<false, kDsCS, kDsBwdGW, kAnchor, true>(p, nt, s);
     return hipGetLastError();
 }
 

@@ -97,7 +97,8 @@ constexpr int kOneBwdCS = 32, kOneBwdGW = 4;      // the adjoint also holds the 
 // writing dv = g through p.x; each wavefront also loads the saved forward state before each of its steps and
 // accumulates dlambda += conj(x_{k-1}) g_k, reduced over the workgroup in LDS and added to p.dlambda with one
 // atomic pair per lane.  The scan position j maps to time k = j (forward) or k = L-1-j (adjoint).
-template <int CS, int kOneGW, bool BWD>
+// NTL: non-temporal loads of v (gx) and of the saved states; the adjoint's stores are always so (see chain.hpp).
+template <int CS, int kOneGW, bool BWD, bool NTL>
 __global__ __launch_bounds__(kOneGW * 64) void k_lti_onepass(const LtiParams p) {
     __shared__ float2 sS[kOneGW][64];
     __shared__ float2 sCarry[64];
@@ -128,12 +129,12 @@ __global__ __launch_bounds__(kOneGW * 64) void k_lti_onepass(const LtiParams p) 
     if (full) {
         if (okp) {
 #pragma unroll
-            for (int i = 0; i < CS; ++i) v[i] = at(vrow + i * tstep, boff);
+            for (int i = 0; i < CS; ++i) v[i] = load_at<NTL>(vrow + i * tstep, boff);
         }
     } else if (okp) {
 #pragma unroll
         for (int i = 0; i < CS; ++i)
-            if (k0 + i < p.L) v[i] = at(vrow + i * tstep, boff);
+            if (k0 + i < p.L) v[i] = load_at<NTL>(vrow + i * tstep, boff);
     }
     float2 xprev[BWD ? CS : 1];
     if constexpr (BWD) {
@@ -144,13 +145,13 @@ __global__ __launch_bounds__(kOneGW * 64) void k_lti_onepass(const LtiParams p) 
         if (k0 + CS < p.L) {                                   // every k of this chunk is at least 1
             if (okp) {
 #pragma unroll
-                for (int i = 0; i < CS; ++i) xprev[i] = at(xrow + i * tstep, boff);
+                for (int i = 0; i < CS; ++i) xprev[i] = load_at<NTL>(xrow + i * tstep, boff);
             }
         } else if (okp) {
 #pragma unroll
             for (int i = 0; i < CS; ++i) {
                 const int64_t k = p.L - 1 - (k0 + i);
-                if (k > 0) xprev[i] = at(xrow + i * tstep, boff);
+                if (k > 0) xprev[i] = load_at<NTL>(xrow + i * tstep, boff);
                 else if (k == 0 && p.x0) xprev[i] = p.x0[(int64_t)b * P + pp];
             }
         }
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(kOneGW * 64) void k_lti_onepass(const LtiParams p) 
 #pragma unroll
             for (int i = 0; i < CS; ++i) {
                 x = cfma(lam, x, v[i]);
-                at(xrow_out + i * tstep, boff) = x;
+                store_at<BWD>(xrow_out + i * tstep, boff, x);
                 if constexpr (BWD) dlam_term(i);
             }
         }
@@ -229,7 +230,7 @@ __global__ __launch_bounds__(kOneGW * 64) void k_lti_onepass(const LtiParams p) 
         for (int i = 0; i < CS; ++i) {
             x = cfma(lam, x, v[i]);
             if (k0 + i < p.L) {
-                at(xrow_out + i * tstep, boff) = x;
+                store_at<BWD>(xrow_out + i * tstep, boff, x);
                 if constexpr (BWD) dlam_term(i);
                 xl = x;
             }
@@ -259,20 +260,25 @@ int lti_onepass_bwd_group_steps() { return kOneBwdCS * kOneBwdGW; }
 int lti_onepass_anchor() { return kAnchor; }
 int lti_chunk_group() { return kLtiWaves; }
 
-hipError_t launch_lti_onepass(const LtiParams &p, hipStream_t s) {
+template <int GW, bool BWD>
+static void launch_onepass(const LtiParams &p, bool nt, hipStream_t s) {
+    constexpr int CS = BWD ? kOneBwdCS : kOneCS;
     const int npslab = (p.P + 63) / 64;
     dim3 grid((unsigned)(npslab * p.B), p.ngroups);
-    if (onepass_gw(p.B, p.P) == kOneGWSmall)
-        hipLaunchKernelGGL((k_lti_onepass<kOneCS, kOneGWSmall, false>), grid, dim3(kOneGWSmall * 64), 0, s, p);
-    else
-        hipLaunchKernelGGL((k_lti_onepass<kOneCS, kOneGWLarge, false>), grid, dim3(kOneGWLarge * 64), 0, s, p);
+    if (nt) hipLaunchKernelGGL((k_lti_onepass<CS, GW, BWD, true>), grid, dim3(GW * 64), 0, s, p);
+    else hipLaunchKernelGGL((k_lti_onepass<CS, GW, BWD, false>), grid, dim3(GW * 64), 0, s, p);
+}
+
+hipError_t launch_lti_onepass(const LtiParams &p, hipStream_t s) {
+    const int64_t row = (int64_t)p.P * sizeof(float2);
+    const bool nt = whole_lines(row, p.v, p.x, nullptr) && 2 * row * p.B * p.L >= kStreamPastCaches;
+    if (onepass_gw(p.B, p.P) == kOneGWSmall) launch_onepass<kOneGWSmall, false>(p, nt, s);
+    else launch_onepass<kOneGWLarge, false>(p, nt, s);
     return hipGetLastError();
 }
 
 hipError_t launch_lti_onepass_bwd(const LtiParams &p, hipStream_t s) {
-    const int npslab = (p.P + 63) / 64;
-    dim3 grid((unsigned)(npslab * p.B), p.ngroups);
-    hipLaunchKernelGGL((k_lti_onepass<kOneBwdCS, kOneBwdGW, true>), grid, dim3(kOneBwdGW * 64), 0, s, p);
+    launch_onepass<kOneBwdGW, true>(p, whole_lines((int64_t)p.P * sizeof(float2), p.v, p.xs, p.x), s);
     return hipGetLastError();
 }
 
