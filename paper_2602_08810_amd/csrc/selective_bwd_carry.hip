@@ -157,6 +157,179 @@ __global__ __launch_bounds__(512, 2) void k_ss_bwd_agg(const BwdParams p) {
     }
 }
 
+// The same where a = e^{Delta A} (every scheme but the bilinear one): then prod_{l0 <= j <= l} a_j is e^{A s_l} with
+// s_l = sum_{l0 <= j <= l} Delta_j, which does not depend on the state, and
+//     P = e^{A s_{l1}},   Q = sum_l e^{A s_l} Cm_l dypre_l
+// needs one scan of Delta per tile, no scan per state and no order among the steps: a lane adds up its own for all
+// tiles of the chunk (N sums in registers), and the lanes' sums meet once at the end.  Five issue slots a state
+// update instead of twelve.  s_l has a relative error of some 2^-23, so a weight e^{-x} one of x 2^-23: less than the product
+// of its steps' exponentials carries.  The next tile's loads are under way during a tile's states.  Kernel times, bf16, gated,
+// before and after: 768 rows of 16384 steps, N = 16, 58 -> 46 us (of 31 us of issue and 14 of memory), N = 32 103 -> 72;
+// 2048 rows 131 -> 99; 64 rows of 8192 14.6 -> 10.6.
+template <typename IO, int N>
+__global__ __launch_bounds__(512, 4) void k_ss_bwd_agg_exp(const BwdParams p) {
+    constexpr int T = 8, W = 8;
+    constexpr int TQ = T / 4;
+    constexpr int QS = 256 + 32 / TQ;                  // as in k_ss_bwd_agg
+    constexpr int PLANE = TQ * QS;
+    constexpr int TILE = 64 * T;
+    static_assert(TILE == W * 64, "a thread stages one step of Cm");
+    __shared__ __attribute__((aligned(16))) float sC[N * PLANE];
+
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = blockIdx.y;
+    const int chunk = blockIdx.z + 1;                  // chunk 0 hands its adjoint to nobody: its pair is not needed
+    const int blk_per_grp = (p.dpg + W - 1) / W;
+    const int grp = blockIdx.x / blk_per_grp;
+    const int d_in = (blockIdx.x % blk_per_grp) * W + w;
+    const bool active = d_in < p.dpg;
+    const int d = grp * p.dpg + (active ? d_in : p.dpg - 1);
+    int64_t s0, Lc, bs;
+    chunk_span(p.cu, b, p.L, chunk, p.nchunks, p.tiles_per_chunk * kBwdTileSteps, s0, Lc, bs);
+    const int64_t ntiles = (Lc + TILE - 1) / TILE;     // none for a packed sequence that ends before this chunk: the pair stays (1, 0)
+    const bool vec = p.vec != 0;
+    const bool window = vec && Lc >= T;                // the last steps of the chunk: see tail_window
+    const bool has_z = p.z != nullptr;
+
+    const IO *drow = reinterpret_cast<const IO *>(p.delta) + bs * p.dl_sb + d * p.dl_sd + s0;
+    const IO *gyrow = reinterpret_cast<const IO *>(p.dy) + bs * p.dy_sb + d * p.dy_sd + s0;
+    const IO *zrow = has_z ? reinterpret_cast<const IO *>(p.z) + bs * p.z_sb + d * p.z_sd + s0 : nullptr;
+    const IO *Cm = reinterpret_cast<const IO *>(p.Cm) + ((bs * p.bcg + grp) * p.L + s0) * N;
+
+    const float bias = p.bias ? p.bias[d] : 0.0f;
+    float A2[N], acc[N], before = 0.0f;                // before: sum of Delta over the tiles before this one
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        A2[n] = p.A[(int64_t)d * N + n] * kLog2e;
+        // in vector registers: an instruction with a scalar operand takes the ALU almost twice as long
+        if constexpr (N <= 16) asm volatile("" : "+v"(A2[n]));
+        acc[n] = 0.0f;
+    }
+
+    // The next tile's loads are under way during this one's states.  FEW: Cm's too; 32 states do not have the registers.
+    constexpr bool FEW = N <= 16;
+    constexpr int NC = FEW ? N : N / 2;
+    const int q = threadIdx.x;                         // the step of a tile whose Cm this thread stages
+    RawFew<IO, T> r_dl, r_dy, r_z;
+    RawFew<IO, NC> r_C;
+    auto fetch_map = [&](int64_t tile, int n0) {       // (past the chunk: its last step again, dropped below)
+        const int64_t l = tile * TILE + q;
+        load_few_raw<IO, NC>(Cm + (l < Lc ? l : Lc - 1) * N + n0, 0, NC, true, r_C);
+    };
+    auto fetch = [&](int64_t tile) {
+        const int64_t l0 = tile * TILE;
+        const int n = Lc - l0 < TILE ? (int)(Lc - l0) : TILE, o = window ? tail_window<T>(lane * T, n) : lane * T;
+        auto one = [&](const IO *row, RawFew<IO, T> &raw) {
+            if (window) load_few_raw<IO, T>(row + l0 + o, 0, T, true, raw);
+            else load_few_raw<IO, T>(row + l0, o, n, false, raw);
+        };
+        one(drow, r_dl);
+        one(gyrow, r_dy);
+        if (has_z) one(zrow, r_z);
+        if constexpr (FEW) fetch_map(tile, 0);
+    };
+    if (ntiles > 0) fetch(0);
+
+    for (int64_t tile = 0; tile < ntiles; ++tile) {
+        const int64_t l0 = tile * TILE;
+        const int rem = Lc - l0 < TILE ? (int)(Lc - l0) : TILE;
+        const int r = lane * T, o = window ? tail_window<T>(r, rem) : r;
+        __syncthreads();
+#pragma unroll
+        for (int n0 = 0; n0 < N; n0 += NC) {           // fp32, layout [n][t/4][lane][t%4]; steps past the chunk are zero
+            float cv[NC];
+            const int off = ((q % T) / 4) * QS + (q / T) * 4 + (q % 4);
+            if constexpr (!FEW) fetch_map(tile, n0);
+            unpack_few<IO, NC>(r_C, cv);
+#pragma unroll
+            for (int n = 0; n < NC; ++n) sC[(n0 + n) * PLANE + off] = q < rem ? cv[n] : 0.0f;
+        }
+        __syncthreads();
+
+        // ---- this lane's T steps: s_l and the gradient reaching ypre
+        float cum[T], dyp[T], zv[T];
+        if (window) {
+            tail_shift<IO, T>(r_dl, r - o);
+            tail_shift<IO, T>(r_dy, r - o);
+            if (has_z) tail_shift<IO, T>(r_z, r - o);
+        }
+        unpack_few<IO, T>(r_dl, cum);
+        unpack_few<IO, T>(r_dy, dyp);
+        if (has_z) unpack_few<IO, T>(r_z, zv);
+        // (the two uniform branches around the steps, not inside: step by step their chains waited for each other)
+        slow_part();
+#pragma unroll
+        for (int t = 0; t < T; ++t) cum[t] += bias;
+        if (p.softplus) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) cum[t] = softplus<sizeof(IO) == 4>(cum[t]);
+        }
+        if (has_z) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) dyp[t] *= zv[t] * sigmoid_fast(zv[t]);
+        }
+        float sum = 0.0f;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {                  // steps past the end: Delta = 0 and no source term
+            sum += (r + t < rem) ? cum[t] : 0.0f;
+            dyp[t] = (r + t < rem) ? dyp[t] : 0.0f;
+            cum[t] = sum;
+        }
+        if (tile + 1 < ntiles) fetch(tile + 1);
+        float upto = sum;                              // inclusive prefix over the lanes
+        upto += dpp<0x111>(0.0f, upto);                // row_shr:1, 2, 4, 8
+        upto += dpp<0x112>(0.0f, upto);
+        upto += dpp<0x114>(0.0f, upto);
+        upto += dpp<0x118>(0.0f, upto);
+        upto += dpp<DPP_ROW_BCAST15, 0xA>(0.0f, upto);
+        upto += dpp<DPP_ROW_BCAST31, 0xC>(0.0f, upto);
+        const float start = before + dpp<DPP_WAVE_SHR1>(0.0f, upto);
+        before += readlane(upto, 63);
+#pragma unroll
+        for (int t = 0; t < T; ++t) cum[t] += start;
+        if (!active) continue;
+
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            float4 c[TQ];                              // read while the exponentials are formed
+#pragma unroll
+            for (int k = 0; k < TQ; ++k) c[k] = *reinterpret_cast<const float4 *>(&sC[n * PLANE + k * QS + lane * 4]);
+            float e[T];
+            slow_part();
+#pragma unroll
+            for (int t = 0; t < T; ++t) e[t] = exp2_fast(cum[t] * A2[n]);
+            fast_part();
+            float odd = 0.0f;                          // two chains of sums
+#pragma unroll
+            for (int t = 0; t < T; t += 2) {
+                acc[n] = __builtin_fmaf(e[t], reinterpret_cast<const float *>(&c[t / 4])[t % 4] * dyp[t], acc[n]);
+                const float v = reinterpret_cast<const float *>(&c[t / 4])[t % 4 + 1] * dyp[t + 1];
+                odd = t ? __builtin_fmaf(e[t + 1], v, odd) : e[t + 1] * v;
+            }
+            acc[n] += odd;
+        }
+    }
+
+    float Q = 0.0f;                                    // lane n: the sum of state n
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        float v = acc[n];
+        v += dpp<0x111>(0.0f, v);
+        v += dpp<0x112>(0.0f, v);
+        v += dpp<0x114>(0.0f, v);
+        v += dpp<0x118>(0.0f, v);
+        v += dpp<DPP_ROW_BCAST15, 0xA>(0.0f, v);
+        v += dpp<DPP_ROW_BCAST31, 0xC>(0.0f, v);
+        Q = writelane(Q, readlane(v, 63), n);
+    }
+    if (active && lane < N) {
+        const int64_t j = (((int64_t)b * p.D + d) * p.nchunks + chunk) * N + lane;
+        p.ws_P[j] = exp2_fast(before * (p.A[(int64_t)d * N + lane] * kLog2e));
+        p.ws_Q[j] = Q;
+    }
+}
+
 // Chains the chunk aggregates of one (b,d,n) from the last chunk to the first: the adjoint entering chunk c from
 // the later side is Q_{c+1} + P_{c+1} (that entering chunk c+1), zero for the last chunk.  ws_Q[c] is replaced by it.
 __global__ void k_ss_bwd_carry(const BwdParams p) {
@@ -342,7 +515,11 @@ hipError_t launch_seq_order(const int64_t *cu, int B, int64_t L, int *order, hip
 template <typename IO, int N, int DISC>
 static hipError_t launch_agg_n(const BwdParams &p, hipStream_t s) {
     dim3 grid(p.bcg * ((p.dpg + 7) / 8), p.B, p.nchunks - 1);
-    hipLaunchKernelGGL((k_ss_bwd_agg<IO, N, DISC>), grid, dim3(512), 0, s, p);
+    // Up to four states in float32 are bound by memory, and the kernel of few registers has more loads under way: 2048 rows of
+    // 16384 steps, N = 4, 74 and 84 us (N = 8: 93 and 76)
+    constexpr bool SCAN = DISC == DISC_BILINEAR || (sizeof(IO) == 4 && N <= 4);
+    if constexpr (SCAN) hipLaunchKernelGGL((k_ss_bwd_agg<IO, N, DISC>), grid, dim3(512), 0, s, p);
+    else hipLaunchKernelGGL((k_ss_bwd_agg_exp<IO, N>), grid, dim3(512), 0, s, p);
     return hipGetLastError();
 }
 template <typename IO, int DISC>
