@@ -877,13 +877,15 @@ __global__ __launch_bounds__(256) void k_ss_bwd_maps(const BwdParams p, int gx) 
     // this thread's four steps: of lane li of the piece (8 steps each), the first or the second four
     const int li = el % LP, q = (el / LP) & 1, n = el / (2 * LP);
     float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    auto add = [&](const float4 v) { a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w; };
+    auto add = [&](const auto v) { a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w; };
     if (KS > 1 || tid < NE) {
         const int at = (n0 + n) * kBwdTileSteps + q * 128 + (piece * LP + li) * 4;
         const float *src = p.part + ((slot * gx + (int64_t)grp * nblk) * 2 + blockIdx.y) * PT + at;
         const int k0 = nblk * ks / KS, k1 = nblk * (ks + 1) / KS;
+        // read once and never again: non-temporal (packed batch of 24 sequences, 16384 steps, D = 1536: training step 572 -> 565 us)
+        typedef float f4 __attribute__((ext_vector_type(4)));
 #pragma unroll 8
-        for (int k = k0; k < k1; ++k) add(*reinterpret_cast<const float4 *>(src + (int64_t)k * 2 * PT));
+        for (int k = k0; k < k1; ++k) add(__builtin_nontemporal_load(reinterpret_cast<const f4 *>(src + (int64_t)k * 2 * PT)));
         if constexpr (KS > 1) sK[ks * NE + el] = a;
     }
     if constexpr (KS > 1) {
