@@ -523,7 +523,6 @@ int lrnnx_selective_scan_bwd_complex(const lrnnx_ss_bwd_complex_args *a) {
         p.hc = p.ws_Q;
         used += (size_t)2 * a->B * a->D * p.nchunks * a->N * sizeof(float2);
         if (launch_ss_cbwd_agg(p, a->io_dtype, a->disc, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
-        if (launch_ss_cbwd_carry(p, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
     }
     // packed batches: longest sequences first, if the workspace has room for the order (as in the real backward)
     if (cu && pl.nchunks == 1 && a->B > 1 && a->B <= kMaxOrdered && a->workspace &&
@@ -550,7 +549,7 @@ int lrnnx_selective_scan_bwd_complex(const lrnnx_ss_bwd_complex_args *a) {
     z.ptr[2] = reinterpret_cast<float *>(a->dA); z.count[2] = (int64_t)a->D * a->N * 2;
     z.ptr[3] = a->dD; z.count[3] = a->D;
     z.ptr[4] = a->dbias; z.count[4] = a->D;
-    if (launch_fill(z, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
+    if ((p.nchunks > 1 ? launch_ss_cbwd_carry(p, z, s) : launch_fill(z, s)) != hipSuccess) return LRNNX_ERR_LAUNCH;
     return launch_ss_cbwd(p, a->io_dtype, a->disc, s) == hipSuccess ? LRNNX_OK : LRNNX_ERR_LAUNCH;
 }
 
@@ -643,7 +642,6 @@ int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
         p.ws_Q = p.ws_P + (size_t)a->B * a->D * p.nchunks * a->N;
         p.hc = p.ws_Q;
         if (launch_ss_bwd_agg(p, a->io_dtype, a->disc, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
-        if (launch_ss_bwd_carry(p, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
     }
     // packed batches: longest sequences first, if the workspace has room for the order (B ints, after the checkpoints
     // of the recompute sweep if there are any)
@@ -672,7 +670,8 @@ int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
     z.ptr[2] = a->dA; z.count[2] = (int64_t)a->D * a->N;
     z.ptr[3] = a->dD; z.count[3] = a->D;
     z.ptr[4] = a->dbias; z.count[4] = a->D;
-    if (launch_fill(z, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
+    // (with chunks of time the kernel that chains them clears them along the way)
+    if ((p.nchunks > 1 ? launch_ss_bwd_carry(p, z, s) : launch_fill(z, s)) != hipSuccess) return LRNNX_ERR_LAUNCH;
     return launch_ss_bwd(p, a->io_dtype, a->disc, s) == hipSuccess ? LRNNX_OK : LRNNX_ERR_LAUNCH;
 }
 

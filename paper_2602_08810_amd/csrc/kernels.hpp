@@ -192,6 +192,19 @@ struct CStepParams {
     const float *Dskip, *bias;
 };
 
+// Device words to clear or set on the stream: by a launch of their own (launch_fill) or along with another kernel.
+struct FillList {
+    static constexpr int kMax = 5;
+    float *ptr[kMax];
+    int64_t count[kMax];     // 32-bit words
+    uint32_t bits[kMax];     // the word written (0 = 0.0f)
+};
+inline int64_t fill_words_most(const FillList &z) {
+    int64_t most = 0;
+    for (int k = 0; k < FillList::kMax; ++k) if (z.ptr[k] && z.count[k] > most) most = z.count[k];
+    return most;
+}
+
 // Each launcher returns hipSuccess or the launch error; it validates nothing.
 hipError_t launch_ss_step(const StepParams &p, int io_dtype, int disc, hipStream_t s);
 hipError_t launch_ss_cstep(const CStepParams &p, int io_dtype, int disc, hipStream_t s);
@@ -207,7 +220,7 @@ int cbwd_places(int N);                      // workgroups of the complex backwa
 hipError_t launch_ss_bwd(const BwdParams &p, int io_dtype, int disc, hipStream_t s);
 hipError_t launch_bwd_maps(const BwdParams &p, int grid_x, hipStream_t s);   // sums the tiles of p.part, of p.N states, over the channel blocks
 hipError_t launch_ss_bwd_agg(const BwdParams &p, int io_dtype, int disc, hipStream_t s);   // chunk aggregates -> ws_P, ws_Q
-hipError_t launch_ss_bwd_carry(const BwdParams &p, hipStream_t s);                         // ws_Q -> carries, in place
+hipError_t launch_ss_bwd_carry(const BwdParams &p, const FillList &z, hipStream_t s);      // ws_Q -> carries, in place; z filled
 // Launch shape of the backward pass: channels per workgroup, and (chunks > 1) the chunked path's cut of the time axis
 struct BwdPlan { int G, nchunks; int64_t tiles_per_chunk; };
 // rowsg = B * (number of Bm/Cm groups), dpg = channels per group; mode 0: automatic, 1: single pass, 2: chunked asked for
@@ -215,7 +228,7 @@ BwdPlan bwd_plan(int rowsg, int dpg, int N, int64_t L, int mode, bool balanced);
 BwdPlan cbwd_plan(int rowsg, int dpg, int N, int64_t L, int mode, bool balanced);          // the complex-A backward
 hipError_t launch_ss_ccarry(const CFwdParams &p, hipStream_t s);
 hipError_t launch_ss_cbwd_agg(const CBwdParams &p, int io_dtype, int disc, hipStream_t s);
-hipError_t launch_ss_cbwd_carry(const CBwdParams &p, hipStream_t s);
+hipError_t launch_ss_cbwd_carry(const CBwdParams &p, const FillList &z, hipStream_t s);
 
 // Few rows and a long sequence: one workgroup per row group would leave most of the chip idle, so the time axis is cut
 // into chunks that run side by side.  Measured with the real kernel on one batch entry of 512-2048 channels and
@@ -280,12 +293,6 @@ int diag_scan_anchor(int is_complex);
 hipError_t launch_diag_scan_bwd(const DiagParams &p, hipStream_t s);
 int diag_scan_bwd_group_steps(int is_complex);
 int lti_onepass_bwd_group_steps();
-struct FillList {
-    static constexpr int kMax = 5;
-    float *ptr[kMax];
-    int64_t count[kMax];     // 32-bit words
-    uint32_t bits[kMax];     // the word written (0 = 0.0f)
-};
 hipError_t launch_fill(const FillList &z, hipStream_t s);
 
 // Tile geometry the host needs for grids, workspaces and the choice of path (each constant lives beside its kernel).

@@ -10,6 +10,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "kernels.hpp"
 
 namespace lrnnx {
 
@@ -226,6 +227,18 @@ __device__ __forceinline__ void wave_scan_fwd(float &P, float &S) {
     "v_mul_f32_dpp %" #p ", %" #p ", %" #p " " CF "\n\t"
 #define LRNNX_FR_STATE(s, p, r, q, CF, CR) LRNNX_F_STATE(s, p, CF) LRNNX_F_STATE(r, q, CR)
 #define LRNNX_ALLROWS " row_mask:0xf bank_mask:0xf"
+
+// ---------------------------------------------------------------- words cleared on the stream
+// thread i of `stride` threads
+__device__ __forceinline__ void fill_words(const FillList &z, int64_t i, int64_t stride) {
+#pragma unroll
+    for (int k = 0; k < FillList::kMax; ++k) {
+        uint32_t *ptr = reinterpret_cast<uint32_t *>(z.ptr[k]);
+        if (!ptr) continue;
+        const uint32_t word = z.bits[k];
+        for (int64_t j = i; j < z.count[k]; j += stride) ptr[j] = word;
+    }
+}
 
 // ---------------------------------------------------------------- I/O element access
 template <typename IO> struct io_traits;

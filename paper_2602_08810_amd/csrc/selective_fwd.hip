@@ -686,14 +686,7 @@ __global__ __launch_bounds__(256) void k_ss_carry(const FwdParams p) {
 // Fills up to five buffers of 32-bit words, each with its own word, in one launch (a fill kernel rather than
 // hipMemsetAsync, so that a caller may capture the library call in a HIP graph).
 __global__ void k_fill(const FillList z) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-#pragma unroll
-    for (int k = 0; k < FillList::kMax; ++k) {
-        uint32_t *ptr = reinterpret_cast<uint32_t *>(z.ptr[k]);
-        if (!ptr) continue;
-        const uint32_t word = z.bits[k];
-        for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < z.count[k]; i += stride) ptr[i] = word;
-    }
+    fill_words(z, blockIdx.x * (int64_t)blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
 }
 
 hipError_t launch_ss_carry(const FwdParams &p, hipStream_t s) {
@@ -703,8 +696,7 @@ hipError_t launch_ss_carry(const FwdParams &p, hipStream_t s) {
 }
 
 hipError_t launch_fill(const FillList &z, hipStream_t s) {
-    int64_t most = 0;
-    for (int k = 0; k < FillList::kMax; ++k) if (z.ptr[k] && z.count[k] > most) most = z.count[k];
+    const int64_t most = fill_words_most(z);
     if (most <= 0) return hipSuccess;
     int64_t blocks = (most + 255) / 256;
     if (blocks > 2048) blocks = 2048;
