@@ -58,8 +58,10 @@ __device__ __forceinline__ void store_at(float *row, unsigned byte_off, float v)
 }
 
 // Where the streams go past the caches (a forward call and its adjoint, us, before and after):
-// - What an adjoint writes is not read again in the call: its stores are always non-temporal.  LTI, P = 1024, 8 x 8192 steps
-//   498 -> 485; 4 x 4096 steps, P = 256 43.2 -> 41.2; real coefficients, P = 1024, 8 x 2048 steps 127.5 -> 118.5.  The forward's
+// - What an adjoint writes is not read again in the call: its stores are non-temporal.  LTI, P = 1024, 8 x 8192 steps
+//   498 -> 485; 4 x 4096 steps, P = 256 43.2 -> 41.2; real coefficients, P = 1024, 8 x 2048 steps 127.5 -> 118.5.  Rows of real
+//   values that are not whole lines share too many of them between workgroups (P = 129, 16 x 8001 steps 158 -> 170, P = 777 254 -> 270): ordinary
+//   there; 8-byte values gain all the same (P = 1237, 3 x 4000 235 -> 226).  The forward's
 //   states are read next by the adjoint, and its stores stay ordinary (non-temporal: 127 -> 133).
 // - What an adjoint reads is read once, if the rows of P values are whole cache lines: then its loads are
 //   non-temporal too (485 -> 458, 118.5 -> 116).  Rows that are not share their lines with the neighbouring

@@ -38,11 +38,12 @@ template <> struct Elem<true> {
 // k = L-1-j): g_k = gx_k + conj(a_{k+1}) g_{k+1}, read through p.b = gx and written through p.x = db; the coefficient
 // of a position is therefore the NEXT time step's a, conjugated.  Each step also loads the saved state before it
 // and writes da_k = conj(x_{k-1}) g_k; the last position writes dx0 = conj(a_0) g_0 through p.x_last.
-// NTL: non-temporal loads of the streamed inputs; the adjoint's stores are always so (see chain.hpp).
+// NTL: non-temporal loads of the streamed inputs; for the adjoint's stores see NTS (and chain.hpp).
 template <bool CPLX, int CS, int GW, int ANCH, bool BWD, bool NTL>
 __global__ __launch_bounds__(GW * 64) void k_diag_scan(const DiagParams p) {
     using EL = Elem<CPLX>;
     using E = typename EL::T;
+    constexpr bool NTS = BWD && (CPLX || NTL);                 // (with real values the rows have to be whole lines)
     constexpr int NS = CPLX ? 2 : 1;                           // 8-byte slots per published aggregate
     __shared__ E sA[GW][64], sS[GW][64], sCarry[64];
     const int lane = threadIdx.x & 63;
@@ -180,8 +181,8 @@ __global__ __launch_bounds__(GW * 64) void k_diag_scan(const DiagParams p) {
 #pragma unroll
             for (int i = 0; i < CS; ++i) {
                 x = EL::fma(a[i], x, bv[i]);
-                store_at<BWD>(xrow_out + i * tstep, boff, x);
-                if constexpr (BWD) store_at<BWD>(darow + i * tstep, boff, EL::mul(EL::conj(xprev[i]), x));
+                store_at<NTS>(xrow_out + i * tstep, boff, x);
+                if constexpr (BWD) store_at<NTS>(darow + i * tstep, boff, EL::mul(EL::conj(xprev[i]), x));
             }
         }
         xl = x;
@@ -190,8 +191,8 @@ __global__ __launch_bounds__(GW * 64) void k_diag_scan(const DiagParams p) {
         for (int i = 0; i < CS; ++i) {
             x = EL::fma(a[i], x, bv[i]);
             if (k0 + i < p.L) {
-                store_at<BWD>(xrow_out + i * tstep, boff, x);
-                if constexpr (BWD) store_at<BWD>(darow + i * tstep, boff, EL::mul(EL::conj(xprev[i]), x));
+                store_at<NTS>(xrow_out + i * tstep, boff, x);
+                if constexpr (BWD) store_at<NTS>(darow + i * tstep, boff, EL::mul(EL::conj(xprev[i]), x));
                 xl = x;
             }
         }
