@@ -163,7 +163,7 @@ __global__ __launch_bounds__(512, 2) void k_ss_bwd_agg(const BwdParams p) {
 // needs one scan of Delta per tile, no scan per state and no order among the steps: a lane adds up its own for all
 // tiles of the chunk (N sums in registers), and the lanes' sums meet once at the end.  Five issue slots a state
 // update instead of twelve.  s_l has a relative error of some 2^-23, so a weight e^{-x} one of x 2^-23: less than the product
-// of its steps' exponentials carries.  The next tile's loads are under way during a tile's states.  Kernel times, bf16, gated,
+// of its steps' exponentials carries (float32, L = 16384, small Delta, chunked, against 64 bits: dA 1.9e-6 -> 6.4e-7, dDelta 4.8e-7 -> 2.6e-7).  The next tile's loads are under way during a tile's states.  Kernel times, bf16, gated,
 // before and after: 768 rows of 16384 steps, N = 16, 58 -> 46 us (of 31 us of issue and 14 of memory), N = 32 103 -> 72;
 // 2048 rows 131 -> 99; 64 rows of 8192 14.6 -> 10.6.
 template <typename IO, int N>

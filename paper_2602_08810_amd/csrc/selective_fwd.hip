@@ -17,9 +17,9 @@
 // 13 to 16 for the prefix, its start and its end, and of 26 a step (softplus, gate, conversions) shared by the N states.
 // Hence 16 steps per lane, one LDS address for all of Bm and Cm, and tiles known to be whole without any check.
 // The next tile's inputs are fetched before the state loop where the registers allow, else after it.
-// Mamba-block training shape (B = 8, D = 1536, N = 16, L = 2048, bf16, with gate and checkpoints): 109 us when launched from a
-// graph, 122 us between the events of the benchmark, which an earlier kernel of 64 lanes, 8 steps and 13 slots an update
-// took 143 us by; B = 16, D = 2560, L = 4096 without gate: 640 us, before 823.
+// Mamba-block training shape (B = 8, D = 1536, N = 16, L = 2048, bf16, with gate and checkpoints): 97 to 103 us, 102
+// between the events of the benchmark; before the priorities 109 from a graph and 122, and an earlier kernel of 64 lanes, 8 steps and
+// 13 slots an update 143; B = 16, D = 2560, L = 4096 without gate: 608 to 632 us, before 640 and 823.
 // See fwd_shape() for the choice of LPC and T.
 //
 // The same kernel serves the three launches of the chunk-carry path for long L / few
@@ -503,7 +503,7 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
 //             L = 1024, N = 4, float32: 124 us, 16 lanes 147)
 //   64 x 8:   a few thousand rows (4096 rows, L = 2048, N = 16, float32: 50 us; 16 lanes 74, 64 x 4 72)
 //   64 x 16:  one workgroup a compute unit (its tile takes the LDS), so at most 2048 rows, but fewer instructions
-//             than 64 x 8 (2048 rows, L = 65536: 645 to 670 us; 64 x 8: 730)
+//             than 64 x 8 (2048 rows, L = 65536, before priorities and pairs: 645 to 670 us; 64 x 8: 730)
 // Over that grid the choice is 1 % slower than the best of the four and the chunked path.
 enum class FwdShape { l16, l64x4, l64x8, l64x16 };
 struct FwdCost { int tile, state, wg, wg_state; };
