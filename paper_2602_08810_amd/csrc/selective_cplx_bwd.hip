@@ -151,8 +151,10 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
     constexpr int W = GE::W, NS = GE::NS, NT = GE::NT, CP = GE::CP, TPT = GE::TPT, NTC = GE::NTC, NA = GE::NA, NB = GE::NB;
     constexpr bool OWN = GE::OWN, SPLIT = GE::SPLIT;
     constexpr int T = 8, TILE = kBwdTileSteps;
-    // two states side by side; the exact zero-order hold takes one after the other, since it also keeps the gains
-    constexpr bool PAIR = NS == 2 && DISC != DISC_ZOH;
+    // Two states side by side; the exact zero-order hold takes one after the other, since it also keeps the gains, and so does the
+    // bilinear scheme with N = 2 in float32, which spills 61 registers with both and 36 with one (8 x 1536 rows, L = 2048: 386 and 315 us;
+    // bfloat16: 251 and 256)
+    constexpr bool PAIR = NS == 2 && DISC != DISC_ZOH && !(DISC == DISC_BILINEAR && N == 2 && sizeof(IO) == 4);
     static_assert(TILE == kCkptInterval && TILE == 32 * T, "a tile is one checkpoint interval and one half-wavefront");
 
     __shared__ __attribute__((aligned(16))) float sIn[NB][CP][GE::IN][TILE];
@@ -482,15 +484,21 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
             };
             // the lane's steps as one affine pair each way: S the end state from zero, Q = a_0 (c_0 + a_1 (c_1 + ...)) the
             // adjoint handed on, both with multiplier P
-            auto fold = [&](int s, float2 (&a)[T], float2 (&x)[T], float2 (&gg)[T], float2 &P, float2 &S, float2 &Q) {
+            // (bilinear: hd holds q, from which multiplier and gain follow, see cbilinear_q)
+            auto mult = [](float2 h) { if constexpr (DISC == DISC_BILINEAR) return cbilinear_a(h); else return h; };
+            auto fold = [&](int s, float2 (&hd)[T], float2 (&x)[T], float2 (&gg)[T], float2 &P, float2 &S, float2 &Q) {
                 const float2 Av = sAC[buf][0][c][n0 + s];
                 const CCoef cc = make_ccoef(Av.x, Av.y);
-                float2 Bv[T], Cv[T];
+                float2 Bv[T], Cv[T], a[T];
                 maps(sB, s, Bv);
                 maps(sC, s, Cv);
 #pragma unroll
                 for (int t = 0; t < T; ++t) {
-                    cdisc_ag<DISC>(dl[t], cc, a[t], gg[t]);
+                    if constexpr (DISC == DISC_BILINEAR) {
+                        hd[t] = cbilinear_q(dl[t], cc);
+                        gg[t] = make_float2(dl[t] * hd[t].x, dl[t] * hd[t].y);
+                    } else cdisc_ag<DISC>(dl[t], cc, hd[t], gg[t]);
+                    a[t] = mult(hd[t]);
                     if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) x[t] = make_float2(du[t] * Bv[t].x, du[t] * Bv[t].y);
                     else x[t] = cxmul(make_float2(gg[t].x * du[t], gg[t].y * du[t]), Bv[t]);
                 }
@@ -505,10 +513,14 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
                     Q = cxmul(a[t], make_float2(__builtin_fmaf(Cv[t].x, dy[t], Q.x), __builtin_fmaf(Cv[t].y, dy[t], Q.y)));
                 if constexpr (DISC == DISC_BILINEAR)
                     P = cxmul(cxmul(cxmul(a[0], a[1]), cxmul(a[2], a[3])), cxmul(cxmul(a[4], a[5]), cxmul(a[6], a[7])));
+                if constexpr (DISC == DISC_BILINEAR) {   // (there are no registers to keep the multipliers beside q)
+#pragma unroll
+                    for (int t = 0; t < T; ++t) asm volatile("" : "+v"(hd[t].x), "+v"(hd[t].y));
+                }
             };
             float2 dA[NS];
             // the states (earliest step first), then the adjoint (last step first) with all that is summed over it
-            auto replay = [&](int s, const float2 (&a)[T], float2 (&x)[T], const float2 (&gg)[T], const float2 xin, float2 Gin) {
+            auto replay = [&](int s, const float2 (&hd)[T], float2 (&x)[T], const float2 (&gg)[T], const float2 xin, float2 Gin) {
                 const float2 Av = sAC[buf][0][c][n0 + s];
                 float2 Bv[T], Cv[T];
                 maps(sC, s, Cv);
@@ -516,7 +528,7 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
                 {
                     float2 xp = xin;
 #pragma unroll
-                    for (int t = 0; t < T; ++t) { xp = cxfma(a[t], xp, x[t]); x[t] = xp; }
+                    for (int t = 0; t < T; ++t) { xp = cxfma(mult(hd[t]), xp, x[t]); x[t] = xp; }
                 }
                 float2 dAp = make_float2(0.0f, 0.0f);
                 auto acc = [&](float &sum, float m1, float m2) { sum = (s == 0) ? m1 * m2 : __builtin_fmaf(m1, m2, sum); };
@@ -524,7 +536,11 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
                 for (int t = T - 1; t >= 0; --t) {
                     const float2 xprev = t > 0 ? x[t - 1] : xin;
                     const float2 K = make_float2(__builtin_fmaf(Cv[t].x, dy[t], Gin.x), __builtin_fmaf(Cv[t].y, dy[t], Gin.y));
-                    Gin = cxmul(a[t], K);
+                    [[maybe_unused]] float2 qK;                          // bilinear: q K; a K = 2 q K - K
+                    if constexpr (DISC == DISC_BILINEAR) {
+                        qK = cxmul(hd[t], K);
+                        Gin = make_float2(__builtin_fmaf(2.0f, qK.x, -K.x), __builtin_fmaf(2.0f, qK.y, -K.y));
+                    } else Gin = cxmul(hd[t], K);
                     dC[s][t] = make_float2(__builtin_fmaf(dy[t], x[t].x, dC[s][t].x), __builtin_fmaf(dy[t], x[t].y, dC[s][t].y));
                     if constexpr (HAS_Z) {
                         acc(yp[t], Cv[t].x, x[t].x);
@@ -539,37 +555,40 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
                         acc(pd[t], q.x, Av.x);
                         pd[t] = __builtin_fmaf(-q.y, Av.y, pd[t]);
                         dAp = make_float2(__builtin_fmaf(q.x, dl[t], dAp.x), __builtin_fmaf(q.y, dl[t], dAp.y));
-                    } else {
+                    } else if constexpr (DISC == DISC_ZOH) {
+                        // da/dDelta = A a, da/dA = Delta a, dg/dDelta = a
                         const float2 hb = cxmul(K, Bv[t]);
                         const float2 gq = make_float2(hb.x * du[t], hb.y * du[t]);             // grad g*
-                        float2 g, d;                                                            // gain; dDelta is the real part of d
-                        if constexpr (DISC == DISC_ZOH) {
-                            // da/dDelta = A a, da/dA = Delta a, dg/dDelta = a
-                            const CCoef cc = make_ccoef(Av.x, Av.y);
-                            float2 a_t, a_A, g_t, g_A;
-                            g = gg[t];
-                            cdisc_partials<DISC>(dl[t], cc, a[t], g, a_t, a_A, g_t, g_A);
-                            const float2 q = cxmul(Gin, xprev);
-                            d = make_float2(__builtin_fmaf(q.x, Av.x, __builtin_fmaf(-q.y, Av.y, __builtin_fmaf(gq.x, a[t].x, -gq.y * a[t].y))), 0.0f);
-                            const float2 e = cxfma(gq, g_A, make_float2(q.x * dl[t], q.y * dl[t]));
-                            dAp = make_float2(dAp.x + e.x, dAp.y + e.y);
-                        } else {
-                            // bilinear: with q = 1 / (1 - Delta A / 2) all four partials are multiples of q^2, and
-                            // a = (1 + Delta A / 2) q gives q = (a + 1) / 2 without a second reciprocal
-                            const float2 q = make_float2(__builtin_fmaf(a[t].x, 0.5f, 0.5f), 0.5f * a[t].y), q2 = cxmul(q, q);
-                            g = make_float2(dl[t] * q.x, dl[t] * q.y);
-                            const float2 ga = cxmul(K, xprev);                                  // grad a*
-                            const float2 t1 = cxfma(ga, Av, gq);
-                            d = make_float2(__builtin_fmaf(t1.x, q2.x, -t1.y * q2.y), 0.0f);
-                            const float hd = 0.5f * dl[t];
-                            const float2 t2 = make_float2(__builtin_fmaf(gq.x, hd, ga.x) * dl[t], __builtin_fmaf(gq.y, hd, ga.y) * dl[t]);
-                            dAp = cxfma(t2, q2, dAp);
-                        }
+                        const CCoef cc = make_ccoef(Av.x, Av.y);
+                        float2 a_t, a_A, g_t, g_A;
+                        const float2 a = hd[t], g = gg[t];
+                        cdisc_partials<DISC>(dl[t], cc, a, g, a_t, a_A, g_t, g_A);
+                        const float2 q = cxmul(Gin, xprev);
+                        const float d = __builtin_fmaf(q.x, Av.x, __builtin_fmaf(-q.y, Av.y, __builtin_fmaf(gq.x, a.x, -gq.y * a.y)));
+                        const float2 e = cxfma(gq, g_A, make_float2(q.x * dl[t], q.y * dl[t]));
+                        dAp = make_float2(dAp.x + e.x, dAp.y + e.y);
                         acc(pu[t], hb.x, g.x);
                         pu[t] = __builtin_fmaf(-hb.y, g.y, pu[t]);
-                        pd[t] = s == 0 ? d.x : pd[t] + d.x;
+                        pd[t] = s == 0 ? d : pd[t] + d;
                         const float2 kg = cxmul(K, g);
                         dB[s][t] = make_float2(__builtin_fmaf(kg.x, du[t], dB[s][t].x), __builtin_fmaf(kg.y, du[t], dB[s][t].y));
+                    } else {
+                        // bilinear: g = Delta q, and all four partials are multiples of q^2: da/dDelta = A q^2, da/dA = Delta q^2,
+                        // dg/dDelta = q^2, dg/dA = Delta^2 q^2 / 2.  One factor q sits in q K (twelve instructions less than q^2 apart:
+                        // 8 x 1536 rows, L = 2048, bf16, N = 16 945 -> 895 us, N = 4 306 -> 291).
+                        const float2 q = hd[t], qB = cxmul(qK, Bv[t]), ga = cxmul(qK, xprev);
+                        const float2 gq = make_float2(qB.x * du[t], qB.y * du[t]);
+                        float dt = dl[t];
+                        if constexpr (N == 2) asm volatile("" : "+v"(dt));       // (its products are not kept for the other state: no registers)
+                        const float gd = dt * du[t];
+                        acc(pu[t], dt, qB.x);
+                        dB[s][t] = make_float2(__builtin_fmaf(qK.x, gd, dB[s][t].x), __builtin_fmaf(qK.y, gd, dB[s][t].y));
+                        const float2 t1 = cxfma(ga, Av, gq);
+                        acc(pd[t], t1.x, q.x);
+                        pd[t] = __builtin_fmaf(-t1.y, q.y, pd[t]);
+                        const float h = 0.5f * dt;
+                        const float2 t2 = make_float2(__builtin_fmaf(gq.x, h, ga.x) * dt, __builtin_fmaf(gq.y, h, ga.y) * dt);
+                        dAp = cxfma(t2, q, dAp);
                     }
                     // computed here: left to itself the compiler moves the products of one state down to the sums of the
                     // next one's, and spills what it then has to keep

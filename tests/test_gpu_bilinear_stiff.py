@@ -1,0 +1,51 @@
+"""GPU parity of the bilinear scheme's backward pass with stiff poles (|Delta A| of 10^5, float32) against the fp64 oracle.
+
+There the multiplier a = 2 q - 1, q = 1 / (1 - Delta A / 2), is close to -1, and whatever is taken from the rounded a instead of
+from q (the gain Delta q, the partials, which are multiples of q^2) has a relative error of up to |Delta A| 2^-26 = 1.5e-3.
+Tolerance: state and adjoint take three roundings of 2^-24 each a step, over at most L steps and both in a gradient:
+6 L 2^-24 to first order, and L 2^-24 for the sums over states and channels."""
+import numpy as np
+import pytest
+
+from paper_2602_08810_amd import workloads
+from _util import dev, host, rel_err
+
+pytestmark = pytest.mark.gpu
+L = 64
+TOL = 7 * L * 2.0 ** -24
+
+
+@pytest.fixture(scope="module")
+def api():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2602_08810_amd import api as _api
+    _api.lib()
+    return _api
+
+
+def _stiff(p, rng):
+    """Step sizes of 0.5 to 1.5 as they are, and poles of 0.7e5 to 2e5."""
+    p["delta"] = rng.uniform(0.5, 1.5, p["delta"].shape).astype(np.float32)
+    p["delta_bias"] = None
+    return -rng.uniform(0.7e5, 2e5, p["A"].shape)
+
+
+@pytest.mark.parametrize("N", [1, 2, 16])
+@pytest.mark.parametrize("gate", [False, True])
+def test_complex(api, oracle, N, gate):
+    import torch
+    rng = np.random.Generator(np.random.PCG64(N + 31 * gate))
+    p = workloads.make_selective_complex(B=2, D=6, N=N, L=L, io="f32", gate=gate, seed=N)
+    p["A"] = (_stiff(p, rng) + 1j * rng.uniform(-2e5, 2e5, p["A"].shape)).astype(np.complex64)
+    dy = rng.standard_normal(p["u"].shape, dtype=np.float32)
+    cplx = lambda a: np.ascontiguousarray(a).view(np.complex64)[..., 0]
+    t = {k: dev(p[k]) for k in ("u", "delta", "A", "Dskip", "delta_bias", "z")}
+    g = api.lrnnx_selective_scan_bwd_complex(**t, Bm=dev(cplx(p["Bm"])), Cm=dev(cplx(p["Cm"])), dy=dev(dy), disc="bilinear",
+                                             delta_softplus=False)
+    r = oracle.selective_scan_bwd_complex(p["u"], p["delta"], p["A"], cplx(p["Bm"]), cplx(p["Cm"]), dy, Dskip=p["Dskip"], z=p["z"],
+                                          disc="bilinear", delta_softplus=False)
+    parts = lambda a: np.stack([a.real, a.imag])
+    errs = {k: rel_err(host(g[k]), r[k]) for k in ("du", "ddelta", "dz", "dD") if r[k] is not None}
+    errs.update({k: rel_err(parts(host(g[k])), parts(r[k])) for k in ("dA", "dBm", "dCm")})
+    assert max(errs.values()) <= TOL, errs
