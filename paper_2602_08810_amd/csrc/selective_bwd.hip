@@ -574,11 +574,16 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                     // the checkpointed state enters through the half's first lane, the carried adjoint through its last
                     float xin = i2f(f2i(ck[s]) & (int)first_lane), Gin = i2f(f2i(hc[s]) & (int)last_lane);
                     float a[T], x[T], gg[T];
+                    [[maybe_unused]] float q[T];                     // bilinear, see bilinear_q
 #pragma unroll
                     for (int t = 0; t < T; ++t) {
                         // (an own copy for each state: multiples and powers of Delta are not kept in registers for the next)
                         if constexpr (DISC == DISC_ZOH || DISC == DISC_BILINEAR) asm volatile("" : "+v"(dl[t]));
-                        disc_ag<DISC>(dl[t], ac, a[t], gg[t]);
+                        if constexpr (DISC == DISC_BILINEAR) {
+                            q[t] = bilinear_q(dl[t], ac);
+                            a[t] = bilinear_a(q[t]);
+                            gg[t] = dl[t] * q[t];
+                        } else disc_ag<DISC>(dl[t], ac, a[t], gg[t]);
                         if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) x[t] = du[t] * Bv[s][t];
                         else x[t] = gg[t] * du[t] * Bv[s][t];
                     }
@@ -591,6 +596,10 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                     for (int t = T - 1; t >= 0; --t) Q = a[t] * __builtin_fmaf(Cv[s][t], dy[t], Q);
                     if constexpr (DISC == DISC_BILINEAR) P = ((a[0] * a[1]) * (a[2] * a[3])) * ((a[4] * a[5]) * (a[6] * a[7]));
                     else P = exp2_fast(sum_dl * ac.A2);
+                    if constexpr (DISC == DISC_BILINEAR) {           // (there are no registers to keep the multipliers beside q)
+#pragma unroll
+                        for (int t = 0; t < T; ++t) asm volatile("" : "+v"(q[t]));
+                    }
                     half_scans(P, S, Q, xin, Gin);
                     if (own && (ln & 31) == 0) sH[at + s] = Q;       // carried to the earlier tile
                     fast_part();
@@ -606,6 +615,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                         for (int t = 0; t < T; ++t) {
                             const int r = T - 1 - t;
                             if constexpr (!APART) R[r] = __builtin_fmaf(Cv[s][r], dy[r], Gin);                 // H_r
+                            if constexpr (DISC == DISC_BILINEAR) a[t] = bilinear_a(q[t]);
                             xp = __builtin_fmaf(a[t], xp, x[t]); x[t] = xp;
                             if constexpr (!APART) {
                                 Gin = a[r] * R[r];                                       // a_r H_r
@@ -621,7 +631,10 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                         if constexpr (APART) {
                             asm volatile("" : "+v"(dl[t]));
                             R[t] = __builtin_fmaf(Cv[s][t], dy[t], Gin);
-                            Gin = a[t] * R[t];
+                            if constexpr (DISC == DISC_BILINEAR) {
+                                G[t] = q[t] * R[t];
+                                Gin = __builtin_fmaf(2.0f, G[t], -R[t]);         // a R
+                            } else Gin = a[t] * R[t];
                         }
                         dC[s][t] = __builtin_fmaf(dy[t], x[t], dC[s][t]);
                         if constexpr (HAS_Z) acc(yp[t], Cv[s][t], x[t]);
@@ -646,17 +659,13 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                             else pd[t] = __builtin_fmaf(q, ac.A, __builtin_fmaf(dg, a[t], pd[t]));
                             dAp = __builtin_fmaf(q, dl[t], __builtin_fmaf(dg, g_A, dAp));
                         } else {
-                            // bilinear: with q = 1 / (1 - Delta A / 2) all four partials are multiples of q^2, and
-                            // a = (1 + Delta A / 2) q gives q = (a + 1) / 2 without a second reciprocal
-                            const float q = __builtin_fmaf(a[t], 0.5f, 0.5f);
-                            const float q2 = q * q, gt = dl[t] * q;
-                            const float da = R[t] * xprev;
-                            const float hb = R[t] * Bv[s][t];
-                            const float dg = hb * du[t];
-                            acc(pu[t], hb, gt);
-                            dB[s][t] = __builtin_fmaf(R[t] * gt, du[t], dB[s][t]);
-                            acc(pd[t], __builtin_fmaf(da, ac.A, dg), q2);                                    // A q^2 da + q^2 dg
-                            dAp = __builtin_fmaf(__builtin_fmaf(0.5f * dl[t], dg, da) * dl[t], q2, dAp);     // Delta q^2 da + Delta^2 q^2 dg / 2
+                            // bilinear: g = Delta q, and all four partials are multiples of q^2: da/dDelta = A q^2, da/dA = Delta q^2,
+                            // dg/dDelta = q^2, dg/dA = Delta^2 q^2 / 2.  One factor q sits in G = q R.
+                            const float qB = G[t] * Bv[s][t], da = G[t] * xprev, dg = qB * du[t];
+                            acc(pu[t], qB, dl[t]);
+                            dB[s][t] = __builtin_fmaf(G[t] * dl[t], du[t], dB[s][t]);
+                            acc(pd[t], __builtin_fmaf(da, ac.A, dg), q[t]);
+                            dAp = __builtin_fmaf(__builtin_fmaf(0.5f * dl[t], dg, da) * dl[t], q[t], dAp);
                         }
                         // computed here: left to itself the compiler moves the products of one state down to the sums of the
                         // next one's, and spills what it then has to keep
