@@ -108,7 +108,8 @@ __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) vo
     // packed time axis of p.L steps; I/O rows have no batch stride, the maps are [G, p.L, N].  The bounds are
     // clamped to the packed axis, so no content of cu can send an access out of the buffers.
     int64_t L = p.L, toff = 0;
-    unsigned bs = b;
+    constexpr bool BRIEF = LPC == 64 && T == 4;      // see row()
+    std::conditional_t<BRIEF, unsigned, int64_t> bs = b;
     if (p.cu) {
         int64_t o = p.cu[b], e = p.cu[b + 1];
         o = o < 0 ? 0 : (o > p.L ? p.L : o);
@@ -122,19 +123,21 @@ __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) vo
     const int mode = p.mode;
 
     // Rows and lanes are worked out again where they are used: an opaque copy of the thread's number keeps the compiler
-    // from holding a register for each address throughout.  With 64 lanes a channel the address is the wavefront's: its number is
-    // copied likewise, and channel and batch entry multiply the strides unsigned.  Calls of many short rows are bound by these
-    // scalar instructions, which the SIMDs of a compute unit share (N = 1, float32: 4 x 1024 rows of 64 steps 7.0 -> 6.5 us,
-    // 8 x 1536 of 256 13.3 -> 12.4).
+    // from holding a register for each address throughout.  Calls of many short rows are bound by scalar instructions, which the
+    // SIMDs of a compute unit share: the shape for them (64 lanes of 4 steps, whose rows are the wavefront's) forms the addresses of a
+    // tile that is not whole where they are used, and multiplies the strides unsigned (N = 1, float32: 4 x 1024 rows of 64 steps 7.0 ->
+    // 6.7 us, 8 x 1536 of 256 13.3 -> 12.5; whole tiles of long rows, their addresses formed anew, and the longer tiles take up to
+    // 6 % longer with it).
     auto fresh = [&]() { unsigned t = tid; asm volatile("" : "+v"(t)); return t; };
-    auto row = [&](const void *base, int64_t sb, int64_t sd, int64_t l) {
+    using channel_t = std::conditional_t<BRIEF, unsigned, int>;
+    auto row = [&](const void *base, int64_t sb, int64_t sd, int64_t l, auto FULL) {
         int wv = w;
-        if constexpr (LPC == 64) asm volatile("" : "+s"(wv));
+        if constexpr (BRIEF && !FULL) asm volatile("" : "+s"(wv));
         int c = din0 + wv * CPW + (fresh() & 63) / LPC;
         c = c < p.dpg ? c : p.dpg - 1;
-        return reinterpret_cast<const IO *>(base) + ((int64_t)bs * sb + (int64_t)(unsigned)(grp * p.dpg + c) * sd + toff + l);
+        return reinterpret_cast<const IO *>(base) + ((int64_t)bs * sb + (int64_t)(channel_t)(grp * p.dpg + c) * sd + toff + l);
     };
-    const int64_t bc0 = (((int64_t)bs * (unsigned)p.bcg + (unsigned)grp) * p.L + toff) * N;       // first complex element of the maps of this sequence
+    const int64_t bc0 = (((int64_t)bs * p.bcg + grp) * p.L + toff) * N;       // first complex element of the maps of this sequence
     const CW *Bm = reinterpret_cast<const CW *>(p.Bm) + bc0;
     const CW *Cm = reinterpret_cast<const CW *>(p.Cm) + bc0;
     const float Dsk = p.Dskip ? p.Dskip[d] : 0.0f;
@@ -165,7 +168,7 @@ __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) vo
     CW r_B[NS], r_C[WANT_Y ? NS : 1];
     auto fetch_rows = [&](int64_t tile, auto FULL) {
         const int64_t l0 = tile * TILE;
-        const IO *u = row(p.u, p.u_sb, p.u_sd, l0), *dl = row(p.delta, p.dl_sb, p.dl_sd, l0);
+        const IO *u = row(p.u, p.u_sb, p.u_sd, l0, FULL), *dl = row(p.delta, p.dl_sb, p.dl_sd, l0, FULL);
         const int r = (fresh() % LPC) * T;
         if constexpr (FULL) {
             load_few_raw<IO, T>(u + r, 0, T, true, r_u);
@@ -202,7 +205,7 @@ __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) vo
         auto fetch_z = [&]() {
             if constexpr (WANT_Y) {
                 if (!p.z) return;
-                const IO *z = row(p.z, p.z_sb, p.z_sd, l0);
+                const IO *z = row(p.z, p.z_sb, p.z_sd, l0, FULL);
                 const int r = (fresh() % LPC) * T;
                 if constexpr (FULL) load_few_raw<IO, T>(z + r, 0, T, true, r_z);
                 else if (window) load_few_raw<IO, T>(z + tail_window<T>(r, rem), 0, T, true, r_z);
@@ -368,7 +371,7 @@ __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) vo
                     for (int t = 0; t < T; ++t) yv[t] *= zv[t] * sigmoid_fast(zv[t]);
                 }
                 if (live) {
-                    IO *y = const_cast<IO *>(row(p.y, p.y_sb, p.y_sd, l0));
+                    IO *y = const_cast<IO *>(row(p.y, p.y_sb, p.y_sd, l0, FULL));
                     const int r = (fresh() % LPC) * T;
                     if constexpr (T == 4) store_few<IO, T>(y, r, rem, FULL || vec, yv);
                     else if constexpr (FULL) store_seg<IO, T>(y + r, 0, T, true, yv);
