@@ -410,32 +410,41 @@ __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) vo
 // ---------------------------------------------------------------- launchers
 // The shape of a single pass, by the time each would take, as in the real forward pass (see fwd_shape in selective_fwd.hip): a
 // tile costs its fixed part and a part for each state, and the same for each workgroup that shares the compute unit.  The
-// costs (in 10 ns) are fitted to 16 to 40960 rows of 64 to 32768 steps with N = 1 to 16.
-//   16 lanes: the fewest instructions; needs about 8000 rows (8 x 1536, L = 2048, N = 16, bf16: 310 us; 64 x 8: 355, 64 x 4: 450)
-//   64 x 4:   the shortest tile and the quickest, for few rows (256 rows, L = 512, N = 16, bf16: 18 us; 64 x 8: 21, 16 lanes: 30)
-//   64 x 8:   in between (2 x 771 rows, L = 2048, N = 16, bf16: 73 us; 64 x 4: 95, 16 lanes: 113)
-// Over that grid the choice is 0.3 % slower than the best of the three and the chunk-carry path, at most 1.3 times (64 rows, L = 512,
-// N = 1: 8.3 us and 6.5).
+// costs (in 10 ns) are fitted to 850 calls of each type: 16 to 40960 rows, 64 to 32768 steps, N = 1 to 16, all schemes.
+//   16 lanes: the fewest instructions; needs about 8000 rows (8 x 1536, L = 2048, N = 16, bf16: 265 us; 64 x 8: 315, 64 x 4: 405)
+//   64 x 4:   the shortest tile and the quickest, for few rows (768 rows, L = 512, N = 16, bf16: 18 us)
+//   64 x 8:   in between (2 x 771 rows, L = 8192, N = 16, bf16: 241 us; 64 x 4: 314)
+// Over them the choice (with the chunk-carry path) is 0.3 % slower than the best, at most 1.18 times; with costs of an earlier form of the
+// kernels, before their issue priorities, it was 1.3 % in float32 and 0.8 % in bfloat16, at most 1.6 times (3 x 1000 rows of 32768
+// steps, N = 1, float32: 532 us in chunks, 327 in a single pass).
+// A packed batch, whose lengths only the device knows, is priced by their mean, with half a tile more for the end of each sequence
+// and fractions of a round, since its workgroups differ; its long sequences run on alone, hence costs of their own.  Over 250 batches
+// of 2 to 96 sequences for each type 1.4 %, at most 1.28 times (with the batch's costs 6 %, at most 2.2: 6 sequences of 32768 steps in
+// all, D = 1068, N = 1, bf16 207 us and 120).
 enum class CFwdShape { l16, l64x4, l64x8 };
 struct CFwdCost { int tile, state, wg, wg_state; };
-static constexpr CFwdCost kCFwdCost[2][3] = {{{27, 39, 245, 56}, {51, 20, 47, 26}, {0, 23, 203, 83}},          // float32
-                                             {{59, 31, 133, 62}, {54, 18, 35, 26}, {16, 23, 155, 79}}};        // bfloat16
-static int64_t cfwd_cost(const CFwdCost &c, int64_t N, int64_t tiles, int64_t wgs) {
-    const int64_t share = (wgs + kNumCU - 1) / kNumCU;   // workgroups of a compute unit
-    return tiles * (c.tile + c.state * N + share * (c.wg + c.wg_state * N));
+static constexpr CFwdCost kCFwdCost[2][3] = {{{64, 45, 239, 38}, {32, 12, 44, 24}, {48, 14, 219, 67}},         // float32
+                                             {{4, 99, 167, 12}, {42, 26, 32, 22}, {32, 35, 152, 67}}};         // bfloat16
+static constexpr CFwdCost kCFwdPackedCost[2][3] = {{{233, 117, 241, 50}, {97, 58, 54, 22}, {90, 96, 246, 67}},
+                                                   {{373, 109, 138, 54}, {130, 58, 40, 22}, {47, 131, 249, 57}}};
+// share: workgroups of a compute unit
+static double cfwd_cost(const CFwdCost &c, int64_t N, double tiles, double share) {
+    return tiles * ((double)(c.tile + c.state * N) + share * (double)(c.wg + c.wg_state * N));
 }
-static int64_t cfwd_time(int64_t maps, int64_t dpg, int64_t N, int64_t L, bool f32, CFwdShape shape) {
+static double cfwd_time(int64_t maps, int64_t dpg, int64_t N, int64_t L, bool f32, CFwdShape shape, int64_t packed = 0) {
     static constexpr int steps[3] = {256, 256, 512}, channels[3] = {16, 4, 8};
     const int i = (int)shape;
-    return cfwd_cost(kCFwdCost[f32 ? 0 : 1][i], N, (L + steps[i] - 1) / steps[i], maps * ((dpg + channels[i] - 1) / channels[i]));
+    const int64_t wgs = maps * ((dpg + channels[i] - 1) / channels[i]);
+    if (!packed) return cfwd_cost(kCFwdCost[f32 ? 0 : 1][i], N, (double)((L + steps[i] - 1) / steps[i]), (double)((wgs + kNumCU - 1) / kNumCU));
+    const double tiles = (double)L / (double)(packed * steps[i]) + 0.5, share = (double)wgs / kNumCU;
+    return cfwd_cost(kCFwdPackedCost[f32 ? 0 : 1][i], N, tiles < 1.0 ? 1.0 : tiles, share < 1.0 ? 1.0 : share);
 }
-// (of a packed batch, whose lengths only the device knows, by their mean)
 static CFwdShape cfwd_shape(const CFwdParams &p, bool f32) {
     CFwdShape best = CFwdShape::l16;
-    int64_t least = INT64_MAX;
+    double least = 0.0;
     for (const CFwdShape shape : {CFwdShape::l16, CFwdShape::l64x4, CFwdShape::l64x8}) {
-        const int64_t t = cfwd_time((int64_t)p.B * p.bcg, p.dpg, p.N, p.cu ? (p.L + p.B - 1) / p.B : p.L, f32, shape);
-        if (t < least) { least = t; best = shape; }
+        const double t = cfwd_time((int64_t)p.B * p.bcg, p.dpg, p.N, p.L, f32, shape, p.cu ? p.B : 0);
+        if (shape == CFwdShape::l16 || t < least) { least = t; best = shape; }
     }
     return best;
 }
@@ -496,16 +505,16 @@ int cfwd_tile_steps() { return CFwdGeom<16, 16>::TILE; }
 
 // Whether the chunk-carry path is faster than the best single pass, by 3 % at least since it takes scratch (costs fitted as above,
 // with bfloat16 I/O for both types: the query of the number of chunks does not know the type; the first two are those of
-// the three launches).  N = 16, bf16: 16 rows of 8192 steps 47 us, 234 in a single pass; 768 rows of 32768 steps 560, 925.
+// the three launches).  N = 16, bf16: 16 rows of 8192 steps 47 us, 234 in a single pass; 768 rows of 32768 steps 487 and 930.
 bool cfwd_chunks_pay(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L) {
-    static constexpr CFwdCost cost = {1003, 45, 180, 119};
+    static constexpr CFwdCost cost = {859, 105, 350, 104};
     const int64_t tiles = (L + cfwd_tile_steps() - 1) / cfwd_tile_steps();
     if (tiles < 2) return false;
-    const int64_t channels = cfwd_channels_per_workgroup();
-    const int64_t chunked = cfwd_cost(cost, N, 1, B * bcg * ((dpg + channels - 1) / channels) * tiles);
-    constexpr int64_t launch = 220;
+    const int64_t channels = cfwd_channels_per_workgroup(), wgs = B * bcg * ((dpg + channels - 1) / channels) * tiles;
+    const double chunked = cfwd_cost(cost, N, 1.0, (double)((wgs + kNumCU - 1) / kNumCU));
+    constexpr double launch = 220;
     for (const CFwdShape shape : {CFwdShape::l16, CFwdShape::l64x4, CFwdShape::l64x8})
-        if (cfwd_time(B * bcg, dpg, N, L, false, shape) + launch <= chunked + chunked * 3 / 100) return false;
+        if (cfwd_time(B * bcg, dpg, N, L, false, shape) + launch <= 1.03 * chunked) return false;
     return true;
 }
 

@@ -296,3 +296,15 @@ def test_host_side_validation_of_the_complex_calls(lib):
     # packed mode sizes the recompute workspace by D * (L / interval + B) * N float pairs
     need = 8 * (100 // int(lib.lrnnx_ckpt_interval()) + 2) * 16 * 8
     assert bwd(ckpt=0, cu_seqlens=fake, workspace=fake, workspace_bytes=need - 1) == 3
+
+
+def test_complex_forward_plan(lib):
+    """Where the complex forward scan cuts the time axis: where a single pass of few rows would leave the chip idle, not with 2 x 771 rows
+    of few states or 3 x 1000 rows (of 32768 steps, N = 1: 300 to 530 us in chunks, 213 to 327 without)."""
+    chunks = lib.lrnnx_selective_scan_fwd_complex_chunks
+    chunks.argtypes = [ctypes.c_int64] * 4 + [ctypes.c_int] * 2
+    assert chunks(1, 16, 16, 8192, 1, 0) == 32 and chunks(1, 768, 16, 32768, 1, 0) > 1
+    assert all(chunks(3, 1000, n, 32768, 1, 0) == 1 for n in (1, 2, 4, 8, 16))
+    assert all(chunks(2, 771, n, 32768, 1, 0) == 1 for n in (1, 2, 4)) and chunks(2, 771, 16, 32768, 1, 0) > 1
+    assert chunks(8, 1536, 16, 32768, 1, 0) == 1 and chunks(1, 16, 16, 200, 1, 0) == 1
+    assert chunks(3, 1000, 1, 32768, 1, 2) > 1                        # asked for
