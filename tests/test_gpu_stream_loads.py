@@ -1,6 +1,7 @@
 """GPU: loads that go past the caches return what ordinary ones do.  Large forward calls take them from a size on, so two
 halves of the batch, each below it, must give the same bits; adjoints take them where every row is whole cache lines, so
-the same tensors one element further in memory must."""
+the same tensors one element further in memory must.  (An adjoint's stores are non-temporal whatever the rows, but for real values:
+there the two calls differ in loads and stores, elsewhere in the loads.)"""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -47,10 +48,11 @@ def test_forward_past_the_caches(api, kind, L):
 
 
 @pytest.mark.parametrize("kind", ["lti", "real", "complex"])
-@pytest.mark.parametrize("B,P,L", [(2, 32, 129), (1, 64, 4097), (3, 160, 700), (1, 48, 100)])
+@pytest.mark.parametrize("B,P,L", [(2, 32, 129), (1, 64, 4097), (3, 160, 700), (1, 96, 100)])
 def test_adjoint_of_whole_lines(api, kind, B, P, L):
     import torch
     v, gx = (_rand((B, L, P), kind != "real", s) for s in (1, 2))
+    assert P * v.element_size() % 128 == 0 and v.data_ptr() % 128 == 0 and gx.data_ptr() % 128 == 0, "whole lines"
     if kind == "lti":
         lam = 0.99 * torch.exp(1j * _rand((P,), False, 3))
         x = api.lrnnx_lti_diag_scan(lam, v)
