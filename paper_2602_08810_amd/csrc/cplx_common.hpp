@@ -127,69 +127,19 @@ __device__ __forceinline__ float2 cxfma(float2 a, float2 b, float2 c) {   // a *
     return make_float2(__builtin_fmaf(a.x, b.x, __builtin_fmaf(-a.y, b.y, c.x)),
                        __builtin_fmaf(a.x, b.y, __builtin_fmaf(a.y, b.x, c.y)));
 }
-__device__ __forceinline__ float2 cxcfma(float2 a, float2 b, float2 c) {  // conj(a) * b + c
-    return make_float2(__builtin_fmaf(a.x, b.x, __builtin_fmaf(a.y, b.y, c.x)),
-                       __builtin_fmaf(a.x, b.y, __builtin_fmaf(-a.y, b.x, c.y)));
-}
 
-// Partials (da/ddt, da/dA, dg/ddt, dg/dA) of one step given its a and g; a and g are holomorphic in A.
-template <int DISC>
-__device__ __forceinline__ void cdisc_partials(float dt, const CCoef &c, float2 a, float2 g,
-                                               float2 &a_t, float2 &a_A, float2 &g_t, float2 &g_A) {
-    const float2 Ac = make_float2(c.Ar, c.Ai);
-    if constexpr (DISC == DISC_BILINEAR) {
-        const float2 q = make_float2(__builtin_fmaf(a.x, 0.5f, 0.5f), 0.5f * a.y);   // 1 / (1 - dt A / 2) = (a + 1) / 2
-        const float2 q2 = cxmul(q, q);
-        a_t = cxmul(Ac, q2);
-        a_A = make_float2(dt * q2.x, dt * q2.y);
-        g_t = q2;
-        const float h = 0.5f * dt * dt;
-        g_A = make_float2(h * q2.x, h * q2.y);
-    } else {
-        a_t = cxmul(Ac, a);
-        a_A = make_float2(dt * a.x, dt * a.y);
-        if constexpr (DISC == DISC_ZOH_S6) { g_t = make_float2(1.0f, 0.0f); g_A = make_float2(0.0f, 0.0f); }
-        else if constexpr (DISC == DISC_DIRAC) { g_t = make_float2(0.0f, 0.0f); g_A = make_float2(0.0f, 0.0f); }
-        else {
-            g_t = a;
-            // (dt A a - (a - 1)) / A^2 = (dt a - g) / A; for small z = dt A: dt^2 (1/2 + z/3 + z^2/8 + z^3/30)
-            const float2 z = make_float2(dt * c.Ar, dt * c.Ai);
-            float2 s = make_float2(0.125f + z.x * 0.033333335f, z.y * 0.033333335f);
-            s = cxmul(s, z); s.x += 0.33333334f;
-            s = cxmul(s, z); s.x += 0.5f;
-            const float d2 = dt * dt;
-            const float2 big = cxmul(make_float2(__builtin_fmaf(dt, a.x, -g.x), __builtin_fmaf(dt, a.y, -g.y)),
-                                     make_float2(c.iAr, c.iAi));
-            const bool small = z.x * z.x + z.y * z.y < 0.015625f;
-            g_A = make_float2(small ? d2 * s.x : big.x, small ? d2 * s.y : big.y);
-        }
-    }
-}
-
-// Both scans of the backward pass: inclusive prefix of (P,S) over the lanes (lane 0 first) and inclusive suffix of
-// (Pr,Sr) (lane 63 first); the two are independent and their steps alternate.
-__device__ __forceinline__ void cwave_scan_fwd_rev(float2 &P, float2 &S, float2 &Pr, float2 &Sr, int lane) {
-    cpair_step<0x111, 0xF>(P, S);  cpair_step<0x101, 0xF>(Pr, Sr);      // row_shr / row_shl : 1
-    cpair_step<0x112, 0xF>(P, S);  cpair_step<0x102, 0xF>(Pr, Sr);
-    cpair_step<0x114, 0xF>(P, S);  cpair_step<0x104, 0xF>(Pr, Sr);
-    cpair_step<0x118, 0xF>(P, S);  cpair_step<0x108, 0xF>(Pr, Sr);
-    const int src = ((lane & 0x30) + 16) & 63;                          // first lane of the next row
-    float2 Pp = make_float2(bpermute(src, Pr.x), bpermute(src, Pr.y));
-    float2 Sp = make_float2(bpermute(src, Sr.x), bpermute(src, Sr.y));
-    cpair_step<DPP_ROW_BCAST15, 0xA>(P, S);
-    cpair_step<DPP_ROW_BCAST31, 0xC>(P, S);
-    {   // rows 0 and 2 take the suffix held by the first lane of the next row
-        const bool take = ((lane >> 4) & 1) == 0;
-        Pp = take ? Pp : make_float2(1.0f, 0.0f); Sp = take ? Sp : make_float2(0.0f, 0.0f);
-        Sr = cxfma(Pr, Sp, Sr); Pr = cxmul(Pr, Pp);
-    }
-    {   // rows 0 and 1 take the suffix held by lane 32
-        float2 Pq = make_float2(bpermute(32, Pr.x), bpermute(32, Pr.y));
-        float2 Sq = make_float2(bpermute(32, Sr.x), bpermute(32, Sr.y));
-        const bool take = lane < 32;
-        Pq = take ? Pq : make_float2(1.0f, 0.0f); Sq = take ? Sq : make_float2(0.0f, 0.0f);
-        Sr = cxfma(Pr, Sq, Sr); Pr = cxmul(Pr, Pq);
-    }
+// dg/dA of one step of the exact zero-order hold, given its a and g (holomorphic in A; the other partials are written out where they
+// are used): (dt A a - (a - 1)) / A^2 = (dt a - g) / A; for small z = dt A: dt^2 (1/2 + z/3 + z^2/8 + z^3/30)
+__device__ __forceinline__ float2 czoh_gain_dA(float dt, const CCoef &c, float2 a, float2 g) {
+    const float2 z = make_float2(dt * c.Ar, dt * c.Ai);
+    float2 s = make_float2(0.125f + z.x * 0.033333335f, z.y * 0.033333335f);
+    s = cxmul(s, z); s.x += 0.33333334f;
+    s = cxmul(s, z); s.x += 0.5f;
+    const float d2 = dt * dt;
+    const float2 big = cxmul(make_float2(__builtin_fmaf(dt, a.x, -g.x), __builtin_fmaf(dt, a.y, -g.y)),
+                             make_float2(c.iAr, c.iAi));
+    const bool small = z.x * z.x + z.y * z.y < 0.015625f;
+    return make_float2(small ? d2 * s.x : big.x, small ? d2 * s.y : big.y);
 }
 
 }  // namespace lrnnx

@@ -28,7 +28,7 @@ template <int CTRL, int ROW_MASK = 0xF>
 __device__ __forceinline__ float dpp(float old, float src) {
     return i2f(__builtin_amdgcn_update_dpp(f2i(old), f2i(src), CTRL, ROW_MASK, 0xF, false));
 }
-constexpr int DPP_WAVE_SHL1 = 0x130, DPP_WAVE_SHR1 = 0x138;
+constexpr int DPP_WAVE_SHR1 = 0x138;
 constexpr int DPP_ROW_BCAST15 = 0x142, DPP_ROW_BCAST31 = 0x143;
 
 __device__ __forceinline__ float readlane(float x, int lane) { return i2f(__builtin_amdgcn_readlane(f2i(x), lane)); }
@@ -39,12 +39,11 @@ extern "C" __device__ int lrnnx_llvm_writelane_i32(int value, int lane, int old)
 __device__ __forceinline__ float writelane(float old, float v, int lane) {
     return i2f(lrnnx_llvm_writelane_i32(f2i(v), lane, f2i(old)));
 }
-__device__ __forceinline__ float bpermute(int src_lane, float x) { return i2f(__builtin_amdgcn_ds_bpermute(src_lane << 2, f2i(x))); }
-// v[lane] + v[lane ^ 16]: the row-pair swap of gfx950 exchanges the odd rows of one copy with the even rows of the
-// other, all in the vector ALU (a swizzle through the LDS crossbar would cost a round trip of a hundred cycles)
-__device__ __forceinline__ float sum_xor16(float v) {
-    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)f2i(v), (unsigned)f2i(v), false, false);
-    return i2f((int)r[0]) + i2f((int)r[1]);
+// Rows of two registers: on return a holds the even rows of both (a's first), b the odd rows; its own inverse.  All in the vector ALU (a
+// swizzle through the LDS crossbar would cost a round trip of a hundred cycles).
+__device__ __forceinline__ void swap_rows(float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)f2i(a), (unsigned)f2i(b), false, false);
+    a = i2f((int)r[0]); b = i2f((int)r[1]);
 }
 // LDS accumulate without a returned value: the wavefront does not wait for it
 __device__ __forceinline__ void lds_add(float *p, float v) {
@@ -137,30 +136,17 @@ __device__ __forceinline__ void disc_ag(float dt, const ACoef &c, float &a, floa
     }
 }
 
-// Partials (da/ddt, da/dA, dg/ddt, dg/dA) given a, g of the same step.
-template <int DISC>
-__device__ __forceinline__ void disc_partials(float dt, const ACoef &c, float a, float g,
-                                              float &a_t, float &a_A, float &g_t, float &g_A) {
-    if constexpr (DISC == DISC_BILINEAR) {
-        const float q = __builtin_fmaf(a, 0.5f, 0.5f);               // 1 / (1 - dt A / 2) = (a + 1) / 2
-        const float q2 = q * q;
-        a_t = c.A * q2; a_A = dt * q2; g_t = q2; g_A = 0.5f * dt * dt * q2;
-    } else {
-        a_t = c.A * a; a_A = dt * a;
-        if constexpr (DISC == DISC_ZOH_S6) { g_t = 1.0f; g_A = 0.0f; }
-        else if constexpr (DISC == DISC_DIRAC) { g_t = 0.0f; g_A = 0.0f; }
-        else {
-            g_t = a;
-            // (dt A a - (a - 1)) / A^2 = (dt a - g) / A = dt^2 (1/2 + x/3 + x^2/8 + x^3/30 + ...), x = dt A.  A
-            // rounding error e in a reaches the difference dt a - g as e / A, i.e. 2 eps / x^2 relative to it: the
-            // closed form is used from |x| = 1/8 on (1e-5), the series below (first omitted term x^4/144 < 4e-6)
-            const float x = dt * c.A;
-            float small = dt * dt * __builtin_fmaf(x, __builtin_fmaf(x, __builtin_fmaf(x, 0.033333335f, 0.125f), 0.33333334f), 0.5f);
-            float closed = __builtin_fmaf(dt, a, -g) * c.rA;
-            asm("" : "+v"(small), "+v"(closed));     // (no branches, as in zoh_gain)
-            g_A = fabsf(x) < 0.125f ? small : closed;
-        }
-    }
+// dg/dA of one step of the exact zero-order hold, given its a and g.  (The other partials of this scheme, da/ddt = A a, da/dA = dt a and
+// dg/ddt = a, and all of the other schemes' are written out where they are used.)
+// (dt A a - (a - 1)) / A^2 = (dt a - g) / A = dt^2 (1/2 + x/3 + x^2/8 + x^3/30 + ...), x = dt A.  A rounding error e in a reaches
+// the difference dt a - g as e / A, i.e. 2 eps / x^2 relative to it: the closed form is used from |x| = 1/8 on (1e-5), the series
+// below (first omitted term x^4/144 < 4e-6).
+__device__ __forceinline__ float zoh_gain_dA(float dt, const ACoef &c, float a, float g) {
+    const float x = dt * c.A;
+    float small = dt * dt * __builtin_fmaf(x, __builtin_fmaf(x, __builtin_fmaf(x, 0.033333335f, 0.125f), 0.33333334f), 0.5f);
+    float closed = __builtin_fmaf(dt, a, -g) * c.rA;
+    asm("" : "+v"(small), "+v"(closed));         // (no branches, as in zoh_gain)
+    return fabsf(x) < 0.125f ? small : closed;
 }
 
 // ---------------------------------------------------------------- per-step inputs of the backward pass
@@ -183,14 +169,14 @@ __device__ __forceinline__ void bwd_step_inputs(float s, float dy, float z, bool
 }
 
 // ---------------------------------------------------------------- issue priority
-// Two wavefronts of a SIMD issue plain fp32 instructions side by side (2.5 cycles of 2.4 GHz each), and one wavefront issues
-// them beside a transcendental, a row swap or a DPP operand of the other, which take the ALU 4 to 8 cycles.  But this lasts
-// only while the wavefront with the slow instruction goes first: at equal priority one exponential in 64 multiply-adds makes
-// it 3.4 cycles an instruction, one in eight 5.1, one DPP operand in eight 4.9.  So a kernel raises its priority where such
-// instructions are dense (slow_part), lowers it for plain arithmetic (fast_part), and raises it further where a workgroup
-// is about to meet at a barrier (edge_part).  A loop like the backward pass's (18 exponentials, 46 DPP operands, 244 plain):
-// 4.1 cycles an instruction as it stands with two wavefronts a SIMD, 4.2 with the priorities the wrong way round, 2.6
-// with these; 4.0 and 2.9 with three wavefronts.  The whole kernels keep part of that: see there.
+// Two wavefronts of a SIMD issue plain fp32 instructions side by side (2.8 to 3 cycles of 2.4 GHz an instruction), and one wavefront issues
+// them beside a transcendental, a row swap or a DPP operand of the other, which take the ALU 4.5 to 8.5 cycles.  But this lasts
+// only while the wavefront with the slow instruction goes first, and only where slow instructions are dense: one exponential in
+// 64 multiply-adds 3.0 cycles an instruction, one in eight 5.5, one DPP operand in eight 4.9, whatever the priorities.  So a kernel
+// keeps such instructions together and raises its priority over them (slow_part), lowers it for plain arithmetic (fast_part), and raises
+// it further where a workgroup is about to meet at a barrier (edge_part).  A loop like the backward pass's (18 exponentials and 46 DPP
+// operands, then 244 plain): 4.0 cycles an instruction with two wavefronts a SIMD at equal priorities, 4.25 with the priorities the wrong
+// way round, 3.1 with these; 3.8, 4.4 and 3.05 with three (valu_probe.hip).  The whole kernels keep part of that: see there.
 template <int P>
 __device__ __forceinline__ void issue_priority() {
     __builtin_amdgcn_sched_barrier(0);

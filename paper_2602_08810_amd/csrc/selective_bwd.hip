@@ -66,12 +66,6 @@ __device__ __forceinline__ void half_scans(float P, float &S, float &Q, float &x
         : "+v"(S), "+v"(Q), "+v"(xin), "+v"(Gin), "=&v"(Qn) : "v"(P), "v"(Pr));
 }
 
-// rows of two registers: on return a holds the even rows of both (a's first), b the odd rows; its own inverse
-__device__ __forceinline__ void swap_rows(float &a, float &b) {
-    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)f2i(a), (unsigned)f2i(b), false, false);
-    a = i2f((int)r[0]); b = i2f((int)r[1]);
-}
-
 // Both scans over the 16 lanes of each row: S becomes the inclusive prefix (lane 0 first) and Q the inclusive suffix (lane
 // 15 first) of the pairs (P, S) and (P, Q), x the prefix of the lane before (lane 0 keeps what it came with) and g the suffix
 // of the lane after (lane 15 keeps it).
@@ -651,8 +645,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                             dAp = __builtin_fmaf(q, dl[t], dAp);
                         } else if constexpr (DISC == DISC_ZOH) {
                             // da/dDelta = A a, da/dA = Delta a, dg/dDelta = a: the common factor a is taken out
-                            float a_t, a_A, g_t, g_A;
-                            disc_partials<DISC>(dl[t], ac, a[t], gg[t], a_t, a_A, g_t, g_A);
+                            const float g_A = zoh_gain_dA(dl[t], ac, a[t], gg[t]);
                             const float hb = R[t] * Bv[s][t];
                             const float dg = hb * du[t];
                             const float q = Gin * xprev;

@@ -120,11 +120,6 @@ __device__ __forceinline__ void crow_scans(float2 P, float2 &S, float2 &Q, float
 #undef LRNNX_ROW
 }
 
-// rows of two registers: on return a holds the even rows of both (a's first), b the odd rows
-__device__ __forceinline__ void swap_rows(float &a, float &b) {
-    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)f2i(a), (unsigned)f2i(b), false, false);
-    a = i2f((int)r[0]); b = i2f((int)r[1]);
-}
 __device__ __forceinline__ void swap_rows(float2 &a, float2 &b) { swap_rows(a.x, b.x); swap_rows(a.y, b.y); }
 
 // Both scans of a state over the tile, in a row of lanes that holds its even pieces (E) and its odd ones (O): xc is the
@@ -560,9 +555,7 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
                         const float2 hb = cxmul(K, Bv[t]);
                         const float2 gq = make_float2(hb.x * du[t], hb.y * du[t]);             // grad g*
                         const CCoef cc = make_ccoef(Av.x, Av.y);
-                        float2 a_t, a_A, g_t, g_A;
-                        const float2 a = hd[t], g = gg[t];
-                        cdisc_partials<DISC>(dl[t], cc, a, g, a_t, a_A, g_t, g_A);
+                        const float2 a = hd[t], g = gg[t], g_A = czoh_gain_dA(dl[t], cc, a, g);
                         const float2 q = cxmul(Gin, xprev);
                         const float d = __builtin_fmaf(q.x, Av.x, __builtin_fmaf(-q.y, Av.y, __builtin_fmaf(gq.x, a.x, -gq.y * a.y)));
                         const float2 e = cxfma(gq, g_A, make_float2(q.x * dl[t], q.y * dl[t]));
