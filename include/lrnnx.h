@@ -186,8 +186,9 @@ int lrnnx_selective_scan_fwd_complex(const lrnnx_ss_fwd_complex_args *args);
  * (lrnnx_workspace_bytes(LRNNX_WS_BWD_COMPLEX, B, D, N, L, io_dtype), which also covers the chunked path's
  * aggregates and up to 512 MiB of partial sums of dBm and dCm; with `ckpt` given its first part, the checkpoints, is not
  * needed).  A workspace without room for those sums is accepted: dBm and dCm are then accumulated with atomics.
- * dA, dBm, dCm, dD, dbias are OVERWRITTEN (cleared on the stream, then accumulated with atomics where they do not go
- * through the workspace: their last bits may then differ from run to run).
+ * dA, dBm, dCm, dD, dbias are OVERWRITTEN (cleared on the stream, then accumulated: dBm and dCm in a fixed order if they go
+ * through the workspace, else, and dA, dD and dbias always, with atomics, within a workgroup too: their last bits may differ
+ * from run to run).
  * Optional (NULL allowed): Dskip, delta_bias, z, x0, ckpt, dD, dbias, dz, dx0.  dD requires Dskip, dbias requires
  * delta_bias, dz requires z.  Alignment: Bm, Cm, dBm, dCm 16 bytes; A, x0, ckpt, dA, dx0 8 bytes.              */
 typedef struct lrnnx_ss_bwd_complex_args {

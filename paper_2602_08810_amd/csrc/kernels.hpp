@@ -237,8 +237,8 @@ hipError_t launch_ss_cbwd_carry(const CBwdParams &p, const FillList &z, hipStrea
 // and flush of dBm/dCm are paid per workgroup and tile: G = 8 -> 64 is 25 % faster at equal workgroup count).  So:
 // the largest G <= maxG for which some chunk count fills the chip without exceeding it; baseG is the single pass's G.
 // `roomy`: the tile sums of the single pass fit their scratch.  If not, and its workgroups take few channels, chunks of more
-// channels are the better plan (B * D = 4096, N = 16, bf16: L = 8192 670 us, chunked 584, L = 16384 1311 and 1148, and a
-// sixteenth of the sums; L = 4096, where they still fit: 342 and 367).
+// channels are the better plan (B * D = 4096, N = 16, bf16: L = 8192 592 us, chunked 505, L = 16384 1207 and 898, and a
+// sixteenth of the sums; L = 4096, where they still fit: 311 and 326).
 inline BwdPlan plan_time_chunks(int rowsg, int dpg, int64_t L, int mode, int baseG, int64_t full, int maxG, bool roomy = true) {
     BwdPlan pl;
     pl.G = baseG;

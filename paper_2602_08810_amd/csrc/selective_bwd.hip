@@ -11,25 +11,23 @@
 // Mapping.  A workgroup of W = N/4 wavefronts works on one tile of 256 steps at a time, last tile first, and on two
 // channels at a time: the halves of a wavefront are the two channels, and lane i of a half owns T = 8 consecutive steps
 // of the tile.  A wavefront holds four states, one after the other in the same registers, so a prefix over the tile is
-// a scan of 32 lanes shared by 8 steps (with N = 16 two at a time, whose scans over 16 lanes are one: see bwd_pairs).  The workgroup loops over G channels; a lane keeps its columns of Bm and Cm (4
-// states x 8 steps) and the running sums of dBm and dCm over channels in registers, so the reduction over channels costs
+// a scan of 32 lanes shared by 8 steps (with N = 16 two at a time, whose scans over 16 lanes are one: see bwd_pairs).  The
+// workgroup loops over G channels; a lane keeps its columns of Bm and Cm (4 states x 8 steps) and the running sums of dBm and dCm over channels in registers, so the reduction over channels costs
 // no traffic inside the loop.  What is summed over states (ypre for dz, du, dDelta) is added over the wavefront's
 // states in registers and over wavefronts through LDS: after a barrier every thread finishes a few consecutive steps
 // of one channel (epilogue) and prepares the same steps of the next pair of channels (prologue).
 //
 // What bounds it: vector-ALU issue and, with two wavefronts a SIMD, the waits of a wavefront that the other one does not
-// fill (a quarter of its time, mostly for LDS after the one barrier of a pass).  22.6 slots of four cycles per state update
-// in the main part (15 multiply-adds and products, 3 for the exponential and its argument, 3.6 for the two scans and the
-// fold's product) and about 5 for prologue, epilogue and the work per tile.  The parts of a pass run at the issue priorities
-// of scan_common.hpp, prologue and epilogue at the highest, since a whole workgroup waits for the last at its barrier:
-// 369 -> 338 us (both parts at one priority: 351), B=16, D=2560, L=4096 2149 -> 1840.  Of those 338 us the main part takes 241,
-// the prologue 45, the epilogue 40, the barrier 14; with conflict-free LDS accesses in prologue and epilogue, the epilogue's
-// reads under way together and 9 instructions less: 325 and 1805; with states in pairs 318 and 1715.  (Before that the two wavefronts of a
-// SIMD took turns at a raised priority, a pass each.)  Time on 64 lanes with 4 steps each and all four states of a wavefront
-// scanned together took 34.8.  Mamba-block shape (B=8, D=1536, N=16, L=2048, bf16): 440 -> 358 us + 25 us for the
-// sums of dBm and dCm; B=16, D=2560, L=4096: 2630 -> 2190 us.  Also tried: four channels per wavefront on rows of 16
-// lanes with 16 steps each (19.7 slots, but twice the LDS traffic and one workgroup per compute unit: 560 us), halves
-// holding different states at three wavefronts per SIMD (25.4 slots and a swap-and-add per sum: 431 us).
+// fill (a sixth of its time, for LDS and at the one barrier of a pass).  With N = 16, 25.9 vector instructions per state update, or 27.8
+// issue slots if an exponential counts as two: 17 instructions of arithmetic, 5.4 for folds' ends and scans, the rest prologue, epilogue
+// and the work per tile.  B=8, D=1536, N=16, L=2048, bf16: 283 to 297 us, 4.0 to 4.2 cycles a slot, and 25 us for the sums of dBm and dCm;
+// B=16, D=2560, L=4096 1700.  What brought it there, in us on the former shape: time on 32 lanes of 8 steps instead of 64 of 4
+// with all four states of a wavefront scanned together 440 -> 358; parts of a pass at the issue priorities of scan_common.hpp, prologue and
+// epilogue at the highest, since a whole workgroup waits for the last at its barrier, 369 -> 338 (both parts at one priority
+// 351); LDS accesses of prologue and epilogue without bank conflicts, the epilogue's reads under way together 325; two states at
+// a time 318; nothing spilled 8 less.  Also tried: four channels per wavefront on rows of 16 lanes with 16 steps each (twice the LDS
+// traffic and one workgroup per compute unit: 560 us), halves holding different states at three wavefronts per SIMD (a
+// swap-and-add per sum: 431 us).
 #include "kernels.hpp"
 #include "scan_common.hpp"
 #include <type_traits>
@@ -176,7 +174,8 @@ template <int N> struct BwdGeom {
 // Whether a wavefront takes two states at a time, one scan over 16 lanes for both (pair_scans): 5.4 vector instructions a
 // state update for folds' ends and scans instead of 6.9, but both states' multipliers and inputs are held at once.  It pays for
 // many states, whose tiles are long in work: N = 16, B=16, D=2560, L=4096, bf16 1805 -> 1721 us, L=2048 of D=1536 325 -> 315,
-// N = 32 0.98 to 1.02; N = 8 5 to 20 % slower; the exact zero-order hold (gains beside the multipliers) 17 to 43 %, bilinear 2 %.
+// N = 32 0.98 to 1.02; N = 8 5 to 20 % slower; the exact zero-order hold (gains beside the multipliers) 17 to 43 %, bilinear 2 % (all of it
+// while the row addresses of the maps were spilled beside).
 template <int N, int DISC> constexpr bool bwd_pairs() { return N == 16 && (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC); }
 
 // `sequence bounds of batch entry b`: packed variable-length mode (cu != nullptr): batch entry b is the sequence of

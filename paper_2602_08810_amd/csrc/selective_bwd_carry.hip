@@ -162,9 +162,11 @@ __global__ __launch_bounds__(512, 2) void k_ss_bwd_agg(const BwdParams p) {
 //     P = e^{A s_{l1}},   Q = sum_l e^{A s_l} Cm_l dypre_l
 // needs one scan of Delta per tile, no scan per state and no order among the steps: a lane adds up its own for all
 // tiles of the chunk (N sums in registers), and the lanes' sums meet once at the end.  Five issue slots a state
-// update instead of twelve.  s_l has a relative error of some 2^-23, so a weight e^{-x} one of x 2^-23: less than the product
-// of its steps' exponentials carries (float32, L = 16384, small Delta, chunked, against 64 bits: dA 1.9e-6 -> 6.4e-7, dDelta 4.8e-7 -> 2.6e-7).  The next tile's loads are under way during a tile's states.  Kernel times, bf16, gated,
-// before and after: 768 rows of 16384 steps, N = 16, 58 -> 46 us (of 31 us of issue and 14 of memory), N = 32 103 -> 72;
+// update instead of twelve.  An s_l is added up in some 15 roundings and one more for each tile of the chunk before it, each of at most
+// 2^-24 of the sum of |Delta| (Delta of either sign, without softplus, may cancel), so the exponent of a weight is off by at most
+// (15 + tiles) 2^-24 |A| sum |Delta|.  Measured on one shape (float32, 8 rows of 16384 steps, N = 16, small Delta, chunks of one tile, against
+// 64 bits; with the product of the steps' exponentials before): dA 1.9e-6 -> 6.4e-7, dDelta 4.8e-7 -> 2.6e-7.  The next tile's
+// loads are under way during a tile's states.  Kernel times, bf16, gated, before and after: 768 rows of 16384 steps, N = 16, 58 -> 46 us (of 31 us of issue and 14 of memory), N = 32 103 -> 72;
 // 2048 rows 131 -> 99; 64 rows of 8192 14.6 -> 10.6.
 template <typename IO, int N>
 __global__ __launch_bounds__(512, 4) void k_ss_bwd_agg_exp(const BwdParams p) {
@@ -366,7 +368,9 @@ __global__ void k_ss_bwd_carry(const BwdParams p, const FillList z) {
 // H_l = dypre_l conj(Cm_l) + conj(a_{l+1}) H_{l+1}: the pair of a chunk is P = prod conj(a_j),
 // Q = sum_l (prod_{l0 <= j <= l} conj(a_j)) dypre_l conj(Cm_l).  Only the tile's total is needed, so the lanes take the
 // tile's time slots in reverse order (lane 63 the earliest): the composition "earlier o later" then runs towards
-// higher lanes and is the forward scan, all DPP steps; lane 63 ends up with the tile's pair.
+// higher lanes and is the forward scan, all DPP steps; lane 63 ends up with the tile's pair.  (The sum of exponentials of the real
+// kernel has not been built here: its phases Im(A) s_l would grow over the whole chunk, where this one's start anew with each lane's
+// eight steps.)
 template <typename IO, int N, int DISC>
 __global__ __launch_bounds__(512, 2) void k_ss_cbwd_agg(const CBwdParams p) {
     using CW = typename cword<IO>::type;

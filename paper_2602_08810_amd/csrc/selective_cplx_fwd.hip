@@ -411,9 +411,9 @@ __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) vo
 // The shape of a single pass, by the time each would take, as in the real forward pass (see fwd_shape in selective_fwd.hip): a
 // tile costs its fixed part and a part for each state, and the same for each workgroup that shares the compute unit.  The
 // costs (in 10 ns) are fitted to 850 calls of each type: 16 to 40960 rows, 64 to 32768 steps, N = 1 to 16, all schemes.
-//   16 lanes: the fewest instructions; needs about 8000 rows (8 x 1536, L = 2048, N = 16, bf16: 265 us; 64 x 8: 315, 64 x 4: 405)
-//   64 x 4:   the shortest tile and the quickest, for few rows (768 rows, L = 512, N = 16, bf16: 18 us)
-//   64 x 8:   in between (2 x 771 rows, L = 8192, N = 16, bf16: 241 us; 64 x 4: 314)
+//   16 lanes: the fewest instructions; needs about 8000 rows (8 x 1536, L = 2048, N = 16, bf16: 250 us; 64 x 8: 296, 64 x 4: 389)
+//   64 x 4:   the shortest tile and the quickest, for few rows (256 rows, L = 512, N = 16, bf16: 17.6 us, 16 lanes 34)
+//   64 x 8:   in between (2 x 771 rows, L = 8192, N = 16, bf16: 247 us; 64 x 4: 333, 16 lanes 509)
 // Over them the choice (with the chunk-carry path) is 0.3 % slower than the best, at most 1.18 times; with costs of an earlier form of the
 // kernels, before their issue priorities, it was 1.3 % in float32 and 0.8 % in bfloat16, at most 1.6 times (3 x 1000 rows of 32768
 // steps, N = 1, float32: 532 us in chunks, 327 in a single pass).
@@ -505,7 +505,7 @@ int cfwd_tile_steps() { return CFwdGeom<16, 16>::TILE; }
 
 // Whether the chunk-carry path is faster than the best single pass, by 3 % at least since it takes scratch (costs fitted as above,
 // with bfloat16 I/O for both types: the query of the number of chunks does not know the type; the first two are those of
-// the three launches).  N = 16, bf16: 16 rows of 8192 steps 47 us, 234 in a single pass; 768 rows of 32768 steps 487 and 930.
+// the three launches).  N = 16, bf16: 16 rows of 8192 steps 36 us, 227 in a single pass; 768 rows of 32768 steps 460 and 919.
 bool cfwd_chunks_pay(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L) {
     static constexpr CFwdCost cost = {859, 105, 350, 104};
     const int64_t tiles = (L + cfwd_tile_steps() - 1) / cfwd_tile_steps();

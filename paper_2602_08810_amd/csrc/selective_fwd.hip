@@ -12,7 +12,7 @@
 //
 // What bounds it: vector-ALU issue; with three wavefronts a SIMD the ALU is busy all the time.  Plain fp32 instructions of
 // two wavefronts issue side by side if the parts of a state run at the priorities of scan_common.hpp (120 -> 109 us on the
-// shape below; 2048 rows, L = 65536: 642 -> 585, and with two states at a time 564).  Per state update: 7 slots for the
+// shape below; 2048 rows, L = 65536: 642 -> 585, and with two states at a time 562).  Per state update: 7 slots for the
 // multiplier (a product and an exponential), the input, the fold, the replay and the projection, and 1/T of the rest:
 // 13 to 16 for the prefix, its start and its end, and of 26 a step (softplus, gate, conversions) shared by the N states.
 // Hence 16 steps per lane, one LDS address for all of Bm and Cm, and tiles known to be whole without any check.
@@ -497,14 +497,16 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
 // barriers, the latency of a wavefront that is alone on its SIMD), and the same for each workgroup that shares the compute
 // unit; the costs (in 10 ns) are fitted to 16 to 40960 rows of 64 to 65536 steps with N = 1 to 32.
 //   16 lanes: the fewest instructions; needs about 8000 rows for three workgroups a compute unit
-//             (8 x 1536 rows, L = 2048, N = 16, bf16: 109 us; 64 x 8: 125, 64 x 16: 144)
-//   64 x 4:   the shortest tile and the quickest, for rows of up to 256 steps (256 rows, L = 256, N = 16, float32: 6.4 us,
-//             64 x 8 10.7, 16 lanes 10.3) and with few states, where memory is the bound, for many rows (16 x 2560 rows,
-//             L = 1024, N = 4, float32: 124 us, 16 lanes 147)
-//   64 x 8:   a few thousand rows (4096 rows, L = 2048, N = 16, float32: 50 us; 16 lanes 74, 64 x 4 72)
+//             (8 x 1536 rows, L = 2048, N = 16, bf16: 97 us; 64 x 8: 104, 64 x 16: 121, 64 x 4: 133)
+//   64 x 4:   the shortest tile and the quickest, for rows of up to 256 steps (256 rows, L = 256, N = 16, float32: 6.2 us,
+//             64 x 8 10.0, 16 lanes 10.7) and with few states, where memory is the bound, for many rows (16 x 2560 rows,
+//             L = 2048, N = 4, float32: 247 us, 16 lanes 274)
+//   64 x 8:   a few thousand rows (4096 rows, L = 2048, N = 16, float32: 46 us; 16 lanes 73, 64 x 4 65)
 //   64 x 16:  one workgroup a compute unit (its tile takes the LDS), so at most 2048 rows, but fewer instructions
-//             than 64 x 8 (2048 rows, L = 65536, before priorities and pairs: 645 to 670 us; 64 x 8: 730)
-// Over that grid the choice is 1 % slower than the best of the four and the chunked path.
+//             than 64 x 8 (768 rows, L = 32768, N = 16, bf16: 284 us; 64 x 8: 328)
+// The costs were fitted before the issue priorities and the pairs of states changed the shapes unequally.  With the present kernels the
+// choice is 1.8 % (float32) and 0.7 % (bfloat16) slower than the best of the four and the chunked path over 729 calls of each type, at
+// most 1.30 times: N = 1 on 16 to 1500 rows of 1531 steps takes 64 x 16, 11.4 us for the 8.8 of 64 x 4.
 enum class FwdShape { l16, l64x4, l64x8, l64x16 };
 struct FwdCost { int tile, state, wg, wg_state; };
 static constexpr FwdCost kFwdCost[2][4] = {{{0, 20, 249, 17}, {22, 12, 52, 8}, {0, 6, 183, 27}, {0, 0, 215, 65}},          // float32
@@ -540,7 +542,9 @@ static FwdShape fwd_shape(const FwdParams &p, bool f32) {
 // (24 sequences of 8192 steps in all, 1536 channels, N = 4: 70 us, 64 x 4: 58) except on very many rows of short sequences (24
 // of 85 steps, 2560 channels: 50, 58).  Long sequences take the longer tiles: 64 x 8 (5 of 3056 steps
 // on average, 1724 channels: 173 us, 64 x 4: 188), very few rows of very long ones 64 x 16 (2 sequences of up to
-// 23848 steps, 363 channels: 152 us, 64 x 4: 186).
+// 23848 steps, 363 channels: 152 us, 64 x 4: 186).  (Figures of the kernels before their issue priorities.  With the present ones the choice is
+// 1.8 % slower than the best in float32 and 2.8 % in bfloat16 over 236 batches of each type, at most 1.32 times: 24 sequences of
+// 341 steps on average, 512 channels, N = 32, float32 82 us, 16 lanes 62.)
 static FwdShape packed_shape(const FwdParams &p, bool f32) {
     const int64_t rows = (int64_t)p.B * p.D, mean = p.L / p.B;
     const bool brief = mean <= 256;
@@ -617,8 +621,8 @@ int fwd_tile_steps() { return FwdGeom<16, 16>::TILE; }
 
 // Whether the chunk-carry path is faster than the best single pass, by 3 % at least since it takes scratch: it walks the sequence
 // twice and launches three times, but on a full chip (costs fitted as above; the first two are those of the three launches).
-// N = 16, bf16: 512 rows of 2048 steps 21 us against 23, 1024 rows of 2048 28 against 24; 16 rows of 65536 steps 22
-// against 640.
+// N = 16, bf16: 512 rows of 2048 steps 21.1 us against 21.7, 1024 rows of 2048 25.6 against 22.6; 16 rows of 65536 steps 21
+// against 557.
 bool fwd_chunks_pay(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L, bool f32) {
     static constexpr FwdCost cost[2] = {{771, 41, 405, 30}, {865, 32, 188, 33}};
     const int64_t tiles = (L + fwd_tile_steps() - 1) / fwd_tile_steps();
