@@ -372,6 +372,7 @@ __device__ __forceinline__ void store_few(IO *row, IDX l, IDX L, bool vec, const
 // data is needed (unpacking is a separate step and nothing waits on the load until then).
 template <typename IO, int CNT>
 struct RawFew {
+    static constexpr int COUNT = CNT;
     static constexpr int WORDS = (CNT * (16 / io_traits<IO>::EPC) + 3) / 4;
     uint32_t w[WORDS];
 };

@@ -109,10 +109,14 @@ template <bool PAIR> __device__ __forceinline__ int piece_of(int li) { return PA
 // rows by 8), so that consecutive threads of the prologue and epilogue (a few steps each) are free of conflicts as well: 8-byte
 // accesses of 16 lanes go out together and must fall into 32 different banks (rotated by 32 floats, every one of them took
 // twice its time).  f is a multiple of CNT.
-template <bool PAIR> __device__ __forceinline__ int lane_slot(int li) { return (li << 2) ^ (PAIR ? (li & 16) >> 1 : 0); }
-template <bool PAIR> __device__ __forceinline__ int step_slot(int f) {
-    const int g = f >> 3, li = PAIR ? (g >> 1) | ((g & 1) << 4) : g;
-    return ((f & 4) << 5) + (lane_slot<PAIR>(li) ^ ((f & 4) << 2)) + (f & 3);
+// A short tile (T = 4 or 2 steps a lane) takes the first 128 or 64 floats, [lane][step % T].
+template <bool PAIR, int T> __device__ __forceinline__ int lane_slot(int li) {
+    return T == 2 ? li << 1 : (li << 2) ^ (PAIR ? (li & 16) >> 1 : 0);
+}
+template <bool PAIR, int T> __device__ __forceinline__ int step_slot(int f) {
+    const int g = f / T, li = PAIR ? (g >> 1) | ((g & 1) << 4) : g;
+    if constexpr (T < 8) return lane_slot<PAIR, T>(li) + f % T;
+    else return ((f & 4) << 5) + (lane_slot<PAIR, T>(li) ^ ((f & 4) << 2)) + (f & 3);
 }
 template <int CNT>
 __device__ __forceinline__ void lds_steps_read(const float *plane, int slot, float *out) {
@@ -197,9 +201,9 @@ __device__ __forceinline__ int channels_of(const BwdParams &p, int64_t ntiles) {
 template <typename IO, int N, int DISC, bool HAS_Z, bool PART>
 __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p) {
     using GE = BwdGeom<N>;
-    constexpr int W = GE::W, NS = GE::NS, NT = GE::NT, CP = GE::CP, TPT = GE::TPT, NTC = GE::NTC;
-    constexpr int T = 8, TILE = kBwdTileSteps;
-    static_assert(TILE == kCkptInterval && TILE == 32 * T, "a tile is one checkpoint interval and one half-wavefront");
+    constexpr int W = GE::W, NS = GE::NS, NT = GE::NT, CP = GE::CP;
+    constexpr int TILE = kBwdTileSteps;
+    static_assert(TILE == kCkptInterval && TILE == 32 * 8, "a tile is one checkpoint interval and one half-wavefront");
 
     constexpr bool OWN = GE::OWN;
     constexpr int NB = GE::NB;
@@ -271,9 +275,6 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
     const IO *Bm = reinterpret_cast<const IO *>(p.Bm) + bc0;
     const IO *Cm = reinterpret_cast<const IO *>(p.Cm) + bc0;
 
-    // this thread's channel of a pair and its steps in prologue / epilogue
-    int c_own = tid / NTC;
-    if constexpr (NTC >= 64) c_own = __builtin_amdgcn_readfirstlane(c_own);
     // The addresses that follow from the thread's number are formed where they are needed: hoisted out of the loops by the
     // compiler they would sit in registers all through the main pass, which has none to spare: it spilled them, and a reload waits
     // for every access before it, at the head of a tile for the atomics of the one before (6 packed sequences of 32768 steps, 1536
@@ -283,9 +284,22 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
     const unsigned first_lane = (li & LAST) == 0 ? ~0u : 0u, last_lane = (li & LAST) == LAST ? ~0u : 0u;
 
     // One tile.  FULL: all of its steps are valid and every row takes vector accesses, nothing to check per element (a
-    // taken branch costs a wavefront about a hundred cycles).
-    auto do_tile = [&](int64_t tile, auto full) {
+    // taken branch costs a wavefront about a hundred cycles).  A sequence's last tile, if it has at most 128 or 64 steps, takes
+    // T = 4 or 2 of them a lane instead of 8: half or a quarter of the work per step and state; the scans, the barriers and the
+    // maps' loads stay.  Training steps of packed batches, with the forward pass's short tiles: 87 sequences of 67 steps, 538 channels, N = 8, float32
+    // 162 -> 122 us, 74 of 119, 204 channels, N = 16, bf16 132 -> 111; whole tiles and longer tails as before.
+    auto do_tile = [&](int64_t tile, auto full, auto per_lane) {
         constexpr bool FULL = decltype(full)::value;
+        constexpr int T = decltype(per_lane)::value;
+        // prologue and epilogue: steps of a thread, threads that share a channel there, and this thread's channel of a pair (with short
+        // tiles some wavefronts may have none)
+        constexpr int TPT = GE::TPT * T / 8 > 0 ? GE::TPT * T / 8 : 1, NTC = 32 * T / TPT;
+        constexpr bool ALL = CP * NTC == NT;
+        static_assert(T == 8 || NTC >= 64, "a wavefront's steps are those of one channel");
+        int c_own = tid / NTC;
+        if constexpr (NTC >= 64) c_own = __builtin_amdgcn_readfirstlane(c_own);
+        const bool busy = ALL || c_own < CP;
+        if constexpr (!ALL) c_own = busy ? c_own : CP - 1;
         const int64_t l0 = tile * TILE;
         const int rem = FULL ? TILE : ((L - l0 < TILE) ? (int)(L - l0) : TILE);      // valid steps of this tile (at least one)
 
@@ -326,7 +340,8 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         const bool window = TPT > 1 && vec && L >= TPT;              // the last steps of the sequence: see tail_window
         auto fetch = [&](unsigned t0) {
             const unsigned f0 = (t0 % NTC) * TPT;
-            if (FULL) {
+            if (!busy) {
+            } else if (FULL) {
                 load_at<IO, TPT>(n_u, f0, r_u);
                 load_at<IO, TPT>(n_dl, f0, r_dl);
                 load_at<IO, TPT>(n_dy, f0, r_dy);
@@ -405,11 +420,13 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
             }
         };
         auto prologue = [&](int ch, unsigned t0, int slot, int buf) {
-            float u[TPT], dl[TPT], dy[TPT];
-            step_inputs(ch, t0, u, dl, dy);
-            lds_steps_write<TPT>(sIn[buf][c_own][0], slot, dl);
-            lds_steps_write<TPT>(sIn[buf][c_own][1], slot, u);
-            lds_steps_write<TPT>(sIn[buf][c_own][2], slot, dy);
+            if (busy) {
+                float u[TPT], dl[TPT], dy[TPT];
+                step_inputs(ch, t0, u, dl, dy);
+                lds_steps_write<TPT>(sIn[buf][c_own][0], slot, dl);
+                lds_steps_write<TPT>(sIn[buf][c_own][1], slot, u);
+                lds_steps_write<TPT>(sIn[buf][c_own][2], slot, dy);
+            }
             if (t0 < 2 * CP * N) (&sAC[buf][0][0][0])[t0] = r_ac;
         };
         auto rotate = [&]() {
@@ -463,8 +480,9 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
             if constexpr (HAS_Z) { if (o_dz) o_dz += CP * p.dz_sd; }
         };
         auto epilogue = [&](const int g, const int buf) {
+            if (!busy) return;
             const unsigned t0 = fresh(tid), f0 = (t0 % NTC) * TPT;
-            const int slot = step_slot<PAIR>((int)f0);
+            const int slot = step_slot<PAIR, T>((int)f0);
             float e_in[3][TPT], s_yp[TPT], s_du[TPT], s_dd[TPT], v[W][3][TPT];
 #pragma unroll
             for (int ww = 0; ww < W; ++ww)
@@ -590,8 +608,11 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                     for (int t = 1; t < T; ++t) S = __builtin_fmaf(a[t], S, x[t]);
 #pragma unroll
                     for (int t = T - 1; t >= 0; --t) Q = a[t] * __builtin_fmaf(Cv[s][t], dy[t], Q);
-                    if constexpr (DISC == DISC_BILINEAR) P = ((a[0] * a[1]) * (a[2] * a[3])) * ((a[4] * a[5]) * (a[6] * a[7]));
-                    else P = exp2_fast(sum_dl * ac.A2);
+                    if constexpr (DISC == DISC_BILINEAR) {
+                        if constexpr (T == 8) P = ((a[0] * a[1]) * (a[2] * a[3])) * ((a[4] * a[5]) * (a[6] * a[7]));
+                        else if constexpr (T == 4) P = (a[0] * a[1]) * (a[2] * a[3]);
+                        else P = a[0] * a[1];
+                    } else P = exp2_fast(sum_dl * ac.A2);
                     if constexpr (DISC == DISC_BILINEAR) {           // (there are no registers to keep the multipliers beside q)
 #pragma unroll
                         for (int t = 0; t < T; ++t) asm volatile("" : "+v"(q[t]));
@@ -713,7 +734,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         } else {
             auto main_part = [&](const int g, const int buf) {
                 const unsigned ln = fresh(lane), c = ln >> 5;
-                const int l4 = lane_slot<PAIR>(ln & 31);
+                const int l4 = lane_slot<PAIR, T>(ln & 31);
                 float dl[T], du[T], dy[T], yp[T], pu[T], pd[T];
                 lds_steps_read<T>(sIn[buf][c][0], l4, dl);
                 lds_steps_read<T>(sIn[buf][c][1], l4, du);
@@ -728,7 +749,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
             };
             auto next_inputs = [&](const int g, const int buf) {          // (past the last pair: unused)
                 const unsigned t0 = fresh(tid);
-                prologue(g + c_own, t0, step_slot<PAIR>((int)((t0 % NTC) * TPT)), buf);
+                prologue(g + c_own, t0, step_slot<PAIR, T>((int)((t0 % NTC) * TPT)), buf);
                 fetch(t0);
             };
             next_inputs(0, 0);
@@ -758,35 +779,40 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         }
 
         // ---- the tile's sums of dBm and dCm over this workgroup's channels
-        // (the two halves hold different channels: summed by a swap that leaves the lower half with steps 0-3 of a lane, the
-        // upper half with steps 4-7)
-        float oB[NS][4], oC[NS][4];
+        // (the two halves hold different channels: summed by a swap that leaves the lower half with the first half of a lane's
+        // steps, the upper half with the others)
+        constexpr int TH = T / 2;
+        float oB[NS][TH], oC[NS][TH];
+        auto put = [](float *m, const float (&v)[TH]) {
+            if constexpr (TH == 4) *reinterpret_cast<float4 *>(m) = make_float4(v[0], v[1], v[2], v[3]);
+            else if constexpr (TH == 2) *reinterpret_cast<float2 *>(m) = make_float2(v[0], v[1]);
+            else m[0] = v[0];
+        };
 #pragma unroll
         for (int s = 0; s < NS; ++s)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const auto r = __builtin_amdgcn_permlane32_swap((unsigned)f2i(dB[s][t]), (unsigned)f2i(dB[s][t + 4]), false, false);
-                const auto q = __builtin_amdgcn_permlane32_swap((unsigned)f2i(dC[s][t]), (unsigned)f2i(dC[s][t + 4]), false, false);
+            for (int t = 0; t < TH; ++t) {
+                const auto r = __builtin_amdgcn_permlane32_swap((unsigned)f2i(dB[s][t]), (unsigned)f2i(dB[s][t + TH]), false, false);
+                const auto q = __builtin_amdgcn_permlane32_swap((unsigned)f2i(dC[s][t]), (unsigned)f2i(dC[s][t + TH]), false, false);
                 oB[s][t] = i2f((int)r[0]) + i2f((int)r[1]);
                 oC[s][t] = i2f((int)q[0]) + i2f((int)q[1]);
             }
         if constexpr (PART) {
             // to this workgroup's own slot of the workspace, as 16-byte pieces in the order the lanes hold them (the sum
             // over workgroups and the transposition to [L,N] are k_ss_bwd_maps's)
-            float *pt = p.part + (((slot0 + tile_first + tile) * gridDim.x + blockIdx.x) * 2 * N + n0) * TILE + (half * 32 + piece_of<PAIR>(li)) * 4;
+            const int r = piece_of<PAIR>(li) * T + half * TH;            // [step % 8 / 4][step / 8][step % 4], for any T
+            const int at = T == 8 ? (half * 32 + piece_of<PAIR>(li)) * 4 : ((r & 4) << 5) + (r >> 3 << 2) + (r & 3);
+            float *pt = p.part + (((slot0 + tile_first + tile) * gridDim.x + blockIdx.x) * 2 * N + n0) * TILE + at;
 #pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                *reinterpret_cast<float4 *>(pt + s * TILE) = make_float4(oB[s][0], oB[s][1], oB[s][2], oB[s][3]);
-                *reinterpret_cast<float4 *>(pt + (N + s) * TILE) = make_float4(oC[s][0], oC[s][1], oC[s][2], oC[s][3]);
-            }
+            for (int s = 0; s < NS; ++s) { put(pt + s * TILE, oB[s]); put(pt + (N + s) * TILE, oC[s]); }
         } else {
             // without a workspace: float atomics, on consecutive addresses (the sums change their order in LDS: lanes that add
             // 8 steps apart take a transaction each, 8 times as long)
-            const unsigned t0 = fresh(tid), st0 = piece_of<PAIR>(t0 & 31) * T + (t0 >> 5 & 1) * 4;
+            const unsigned t0 = fresh(tid), st0 = piece_of<PAIR>(t0 & 31) * T + (t0 >> 5 & 1) * TH;
             if constexpr (OWN) {
                 float *gB = p.dBm + bc0 + l0 * N, *gC = p.dCm + bc0 + l0 * N;
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
+                for (int t = 0; t < TH; ++t)
                     if ((int)st0 + t < rem) {
 #pragma unroll
                         for (int s = 0; s < NS; ++s) {
@@ -797,11 +823,10 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
             } else {
                 static_assert(OWN || N <= NB * CP * W * 3, "one map's sums in the partial sums' place");
                 float *buf = &sPart[0][0][0][0][0];
-                auto flush = [&](float (&o)[NS][4], float *g) {
+                auto flush = [&](float (&o)[NS][TH], float *g) {
                     __syncthreads();
 #pragma unroll
-                    for (int s = 0; s < NS; ++s)
-                        *reinterpret_cast<float4 *>(buf + (n0 + s) * TILE + st0) = make_float4(o[s][0], o[s][1], o[s][2], o[s][3]);
+                    for (int s = 0; s < NS; ++s) put(buf + (n0 + s) * TILE + st0, o[s]);
                     __syncthreads();
 #pragma unroll 1
                     for (int i = t0; i < rem * N; i += NT) unsafeAtomicAdd(g + bc0 + l0 * N + i, buf[(i % N) * TILE + i / N]);
@@ -812,8 +837,18 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         }
     };
     const int whole = vec ? (int)(L / TILE) : 0;         // tiles known to be whole
-    for (int64_t tile = ntiles - 1; tile >= 0; --tile) {
-        if (tile < whole) do_tile(tile, std::true_type{}); else do_tile(tile, std::false_type{});
+    int64_t tile = ntiles - 1;
+    if constexpr (!OWN) {
+        const int64_t left = L - tile * TILE;        // steps of the last tile
+        if (tile >= 0 && left <= 128) {
+            if (left <= 64) do_tile(tile, std::false_type{}, std::integral_constant<int, 2>{});
+            else do_tile(tile, std::false_type{}, std::integral_constant<int, 4>{});
+            --tile;
+        }
+    }
+    for (; tile >= 0; --tile) {
+        constexpr std::integral_constant<int, 8> eight{};
+        if (tile < whole) do_tile(tile, std::true_type{}, eight); else do_tile(tile, std::false_type{}, eight);
     }
     __syncthreads();
     // ---- per-channel results of this workgroup

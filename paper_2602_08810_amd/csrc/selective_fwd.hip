@@ -96,21 +96,25 @@ template <int LPC, int T> struct FwdGeom {
 // Workgroups that share a compute unit: three of four wavefronts with 16 lanes per channel (168 registers, three wavefronts a
 // SIMD); with 64 lanes four of four wavefronts (4 steps) or two of eight (8 steps: 75 KB of LDS each), at 128 registers four a
 // SIMD; one of eight with 16 steps, whose staged tile takes more than half of the LDS.
-template <typename IO, int N, int DISC, bool WANT_Y, bool CKPT, int LPC, int T>
-__global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 3 : 2) : 4)) void k_ss_fwd(const FwdParams p) {
-    using GE = FwdGeom<LPC, T>;
+template <typename IO, int N, int DISC, bool WANT_Y, bool CKPT, int LPC, int TM>
+__global__ __launch_bounds__((FwdGeom<LPC, TM>::W * 64), (TM == 16 ? (LPC == 16 ? 3 : 2) : 4)) void k_ss_fwd(const FwdParams p) {
+    using GE = FwdGeom<LPC, TM>;
     constexpr int W = GE::W, CPW = GE::CPW, CH = GE::CH, TILE = GE::TILE, NT = W * 64;
     constexpr int RPT = TILE / NT;                   // rows of the maps a thread stages
     constexpr int NS = N > 16 ? 16 : N, NH = N / NS; // states staged at a time, and how often
     constexpr bool EARLY = sizeof(IO) == 2 ? LPC > 16 || N <= 8 : LPC > 16 && N <= 8;
-    constexpr bool LATE_Z = sizeof(IO) == 4 && T == 16 && LPC == 16;
+    constexpr bool LATE_Z = sizeof(IO) == 4 && TM == 16 && LPC == 16;
     constexpr bool AGG = !WANT_Y && !CKPT;           // the aggregate launch of the chunk-carry path
+    // A sequence's last tile with half of its steps or fewer takes a half or a quarter of them a lane (11 x 1059 rows of 339 steps,
+    // N = 16, bf16: call 35.9 -> 28.8 us).  With 16 lanes a channel only: a tile of 64 lanes of 4 steps has nothing to halve, and
+    // the shapes with longer tiles are for long rows, which have one such tile.
+    constexpr bool SHORT = LPC == 16;
     // Two states at a time: their chains (folds, scan, replay) fill each other's latencies, which counts where few wavefronts share a
     // SIMD: 2048 rows, L = 65536, N = 16, bf16 577 -> 564 us, 64 rows of 16384 steps 21.5 -> 20.5, states alone (B=16, D=2560,
     // L=4096) 432 -> 407.  Not where it takes the registers of a wavefront (16 lanes with outputs: 110 -> 124 us, 30 spilled), with
     // few states (N = 8: up to 6 % longer), and in float32 with 8 steps (2 % longer).
     constexpr bool PAIR = NS == 16 && (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) &&
-                          (!WANT_Y || (LPC == 64 && !(T == 8 && sizeof(IO) == 4)));
+                          (!WANT_Y || (LPC == 64 && !(TM == 8 && sizeof(IO) == 4)));
     static_assert(TILE % kCkptInterval == 0 && RPT * NT == TILE, "tile shape");
     __shared__ __attribute__((aligned(16))) float sBC[WANT_Y ? 2 * NS : NS + 1][GE::ROW];   // Bm, Cm
     __shared__ __attribute__((aligned(16))) float sA[CH + 1][N], sX[CH + 2][N];    // A; the state entering the next tile, and zeros
@@ -176,17 +180,18 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
     }
     if (lane < N) sX[CH][lane] = 0.0f;               // (every wavefront: the same value)
 
-    // A staged row of Bm or Cm: step 4 q + i of lane l (of T) at q Q + 4 l + i.  The reads, 16 bytes from each lane,
-    // are contiguous over the lanes and all share one address; Q leaves a gap of 256 / T so that the 64 consecutive steps
+    // A staged row of Bm or Cm: step 4 q + i of lane l (of TM) at q Q + 4 l + i.  The reads, 16 bytes from each lane,
+    // are contiguous over the lanes and all share one address; Q leaves a gap of 256 / TM so that the 64 consecutive steps
     // which a wavefront stages at once fall into 64 banks.
     // ---- the inputs of a tile, raw.  Those of a whole tile (FULL: nothing to check per element) are fetched ahead, once
     // the state loop of the tile before is done, and used after its epilogue.
     // the last steps of the sequence: see tail_window (64 x 16 is for long rows, which have one such tile: left out there,
     // where the mere presence of that code cost the main loop 2 %)
-    const bool window = GE::TILE <= 512 && vec && L >= T;
-    RawFew<IO, T> r_u, r_dl;
+    const bool window = GE::TILE <= 512 && vec && L >= TM;
+    RawFew<IO, TM> r_u, r_dl;
     RawFew<IO, NS> r_B[RPT], r_C[WANT_Y ? RPT : 1];
-    auto fetch_rows = [&](int64_t tile, auto FULL) {
+    auto fetch_rows = [&](int64_t tile, auto FULL, auto &r_u, auto &r_dl) {
+        constexpr int T = std::remove_reference_t<decltype(r_u)>::COUNT;
         const int64_t l0 = tile * TILE;
         const IO *u = row(p.u, p.u_sb, p.u_sd, l0), *dl = row(p.delta, p.dl_sb, p.dl_sd, l0);
         const int r = (fresh() % LPC) * T;
@@ -224,7 +229,13 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
 #pragma unroll
         for (int k = 0; k < RPT; ++k) { forget(r_B[k]); if constexpr (WANT_Y) forget(r_C[k]); }
     };
-    auto do_tile = [&](int64_t tile, auto FULL, bool ahead) {
+    // STEPS: steps of a lane, fewer in a short tile (the last one of a sequence), whose rows are fetched here
+    auto do_tile = [&](int64_t tile, auto FULL, auto STEPS, bool ahead) {
+        constexpr int T = STEPS;
+        RawFew<IO, T> t_u, t_dl;
+        auto &q_u = [&]() -> auto & { if constexpr (T == TM) return r_u; else return t_u; }();
+        auto &q_dl = [&]() -> auto & { if constexpr (T == TM) return r_dl; else return t_dl; }();
+        if constexpr (T != TM) { if (busy) fetch_rows(tile, FULL, t_u, t_dl); }
         const int64_t l0 = tile * TILE;
         const int rem = FULL ? TILE : (L - l0 < TILE ? (int)(L - l0) : TILE);
         float dl[T], du[T], yv[T], sum_dl = 0.0f;    // du: Delta*u for S6, u for the other schemes
@@ -246,6 +257,7 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
 #pragma unroll
             for (int k = 0; k < RPT; ++k) {
                 const unsigned r = fresh() + k * NT, q = (r % T) / 4;
+                if (T != TM && r >= LPC * T) break;
                 const unsigned off = q * GE::Q + (r / T) * 4 + (r % 4);
                 float v[NS];
                 unpack_few<IO, NS>(r_B[k], v);
@@ -270,11 +282,11 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
                 // ---- this lane's steps of Delta, Delta u and D u
                 if (!FULL && window) {
                     const int r = (fresh() % LPC) * T, by = r - tail_window<T>(r, rem);
-                    tail_shift<IO, T>(r_u, by);
-                    tail_shift<IO, T>(r_dl, by);
+                    tail_shift<IO, T>(q_u, by);
+                    tail_shift<IO, T>(q_dl, by);
                 }
-                unpack_few<IO, T>(r_u, du);
-                unpack_few<IO, T>(r_dl, dl);
+                unpack_few<IO, T>(q_u, du);
+                unpack_few<IO, T>(q_dl, dl);
 #pragma unroll
                 for (int t = 0; t < T; ++t) asm volatile("" : "+v"(du[t]), "+v"(dl[t]));
                 if constexpr (!LATE_Z) fetch_z();
@@ -301,7 +313,7 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
                 if (h + 1 < NH) { fetch_maps(tile, h + 1, FULL); return; }
                 if (FULL && ahead) {
                     fetch_maps(tile + 1, 0, FULL);
-                    if constexpr (ROWS) fetch_rows(tile + 1, FULL);
+                    if constexpr (ROWS && T == TM) fetch_rows(tile + 1, FULL, r_u, r_dl);
                 } else { forget_maps(); forget(r_u); forget(r_dl); }
             };
             if (busy) {
@@ -457,7 +469,7 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
                 if (live) {
                     IO *y = const_cast<IO *>(row(p.y, p.y_sb, p.y_sd, l0));
                     const int r = (fresh() % LPC) * T;
-                    if constexpr (T == 4) store_few<IO, T>(y, r, rem, FULL || vec, yv);
+                    if constexpr (T < 8) store_few<IO, T>(y, r, rem, FULL || vec, yv);
                     else if constexpr (FULL) store_seg<IO, T>(y + r, 0, T, true, yv);
                     else store_seg<IO, T>(y, r, rem, vec, yv);
                 }
@@ -468,13 +480,18 @@ __global__ __launch_bounds__((FwdGeom<LPC, T>::W * 64), (T == 16 ? (LPC == 16 ? 
     int64_t tile = tile0;
     if (tile < tilef) {
         fetch_maps(tile, 0, std::true_type{});
-        if (busy) fetch_rows(tile, std::true_type{});
-        for (; tile < tilef; ++tile) do_tile(tile, std::true_type{}, tile + 1 < tilef);
+        if (busy) fetch_rows(tile, std::true_type{}, r_u, r_dl);
+        for (; tile < tilef; ++tile) do_tile(tile, std::true_type{}, std::integral_constant<int, TM>{}, tile + 1 < tilef);
     }
     for (; tile < tile1; ++tile) {                   // the rest of the sequence (all of it without vector access)
         fetch_maps(tile, 0, std::false_type{});
-        if (busy) fetch_rows(tile, std::false_type{});
-        do_tile(tile, std::false_type{}, false);
+        if constexpr (SHORT) {
+            const int64_t left = L - tile * TILE;
+            if (left <= TILE / 4) { do_tile(tile, std::false_type{}, std::integral_constant<int, SHORT ? TM / 4 : TM>{}, false); continue; }
+            if (left <= TILE / 2) { do_tile(tile, std::false_type{}, std::integral_constant<int, SHORT ? TM / 2 : TM>{}, false); continue; }
+        }
+        if (busy) fetch_rows(tile, std::false_type{}, r_u, r_dl);
+        do_tile(tile, std::false_type{}, std::integral_constant<int, TM>{}, false);
     }
 
     // every wavefront wrote the end states of its own channels
