@@ -175,7 +175,7 @@ void set_bwd_shape(BwdParams &p, const lrnnx_ss_bwd_args *a, const BwdPlan &pl) 
     p.nchunks = pl.nchunks;
     p.tiles_per_chunk = pl.tiles_per_chunk;
     if (!a->cu_seqlens || pl.nchunks > 1) return;
-    bwd_packed_shape(a->B, a->D, a->L, a->max_seqlen, bwd_channels_per_group(a->B * p.bcg, p.dpg, a->N, a->L, true),
+    bwd_packed_shape(a->B, a->D, p.dpg, a->L, a->max_seqlen, bwd_channels_per_group(a->B * p.bcg, p.dpg, a->N, a->L, true),
                      bwd_places(a->N), &p.G, &p.wcap, &p.gmin);
     // tile sums a little over their scratch: up to half as many channels again, if that makes them fit (see kBwdSumsCap)
     int &least = p.wcap > 0 ? p.gmin : p.G;
@@ -515,7 +515,7 @@ int lrnnx_selective_scan_bwd_complex(const lrnnx_ss_bwd_complex_args *a) {
     p.tiles_per_chunk = pl.tiles_per_chunk;
     size_t used = carry_off;                       // bytes of the workspace taken so far
     if (cu && pl.nchunks == 1)
-        bwd_packed_shape(a->B, a->D, a->L, a->max_seqlen, cbwd_channels_per_group(a->B * bcg, a->D / bcg, a->N, true),
+        bwd_packed_shape(a->B, a->D, p.dpg, a->L, a->max_seqlen, cbwd_channels_per_group(a->B * bcg, a->D / bcg, a->N, true),
                          cbwd_places(a->N), &p.G, &p.wcap, &p.gmin);
     if (pl.nchunks > 1) {
         p.ws_P = reinterpret_cast<float2 *>(static_cast<char *>(a->workspace) + carry_off);

@@ -130,7 +130,7 @@ constexpr size_t kBwdSumsCap = (size_t)512 << 20;
 // known, nothing changes): *G comes in as the channels per workgroup of a batch of unknown lengths and may be raised
 // to Gbal, those of a batch [B,D,L] of equal lengths; else cap and fewest channels as in BwdParams.  `places` =
 // workgroups the chip holds at once.
-void bwd_packed_shape(int B, int D, int64_t L, int64_t max_seqlen, int Gbal, int places, int *G, int *wcap, int *gmin);
+void bwd_packed_shape(int B, int D, int dpg, int64_t L, int64_t max_seqlen, int Gbal, int places, int *G, int *wcap, int *gmin);
 constexpr int kMaxOrdered = 256;     // packed batches of more sequences than this are not reordered
 hipError_t launch_seq_order(const int64_t *cu, int B, int64_t L, int *order, hipStream_t s);
 
