@@ -3,7 +3,8 @@
 Every function here has the name of the C entry point it calls (include/lrnnx.h) and
 does nothing but check tensor dtypes/devices, allocate the outputs and the workspace
 with torch, fill the args struct with data pointers, strides and the current HIP
-stream, and call into the library.  There is no CPU or PyTorch fallback: if the
+stream, and call into the library.  Calls in their usual form take the same steps in
+csrc/binding.cpp.  There is no CPU or PyTorch fallback: if the
 library has not been built, importing the entry points raises.
 """
 from __future__ import annotations
@@ -17,6 +18,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblrnnx.so")
+BINDING_PATH = os.path.join(_HERE, "_binding.so")
 
 F32, BF16, C64 = 0, 1, 2
 DISC = {"zoh_s6": 0, "zoh": 1, "bilinear": 2, "dirac": 3}
@@ -119,9 +121,8 @@ class LtiStepArgs(ctypes.Structure):
 
 def _packer(cls):
     """Packs the values of an argument struct's fields in order (0, not None, stands for NULL).  One call of 0.6 us, where 34
-    attributes set one by one take 3.7.  Small calls are bound by this file: with the checks of the usual forms taken first
-    and the stream asked for by one native call, the forward call of 16 rows of 256 steps takes 15.3 us instead of 21.6, a
-    generated token of 64 x 1536 channels 11.0 instead of 15.1."""
+    attributes set one by one take 3.7: the general path of the forward call of 16 rows of 256 steps takes 15.3 us, of a generated
+    token of 64 x 1536 channels 11.0 (csrc/binding.cpp: 6.6 and 5.0)."""
     code = {_vp: "Q", _i32: "i", _i64: "q", _sz: "Q"}
     p = struct.Struct("=" + "".join(code[t] for _, t in cls._fields_))
     assert p.size == ctypes.sizeof(cls), f"{cls.__name__}: padded"
@@ -132,15 +133,16 @@ _pack_fwd, _pack_bwd, _pack_step = _packer(FwdArgs), _packer(BwdArgs), _packer(S
 _FWD_SIZE, _BWD_SIZE, _STEP_SIZE = ctypes.sizeof(FwdArgs), ctypes.sizeof(BwdArgs), ctypes.sizeof(StepArgs)
 
 _lib = None
+_native = None                                    # entry points that csrc/binding.cpp takes in their usual form
 _packed = {}                                      # the entry points that are called with a packed struct
 
 
 def lib():
     """The loaded C library.  Raises if it was not built (no fallback exists)."""
-    global _lib
+    global _lib, _native
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise RuntimeError(f"{LIB_PATH} is missing: run `python -m paper_2602_08810_amd.build` "
+        if not os.path.exists(LIB_PATH) or not os.path.exists(BINDING_PATH):
+            raise RuntimeError(f"{LIB_PATH} or {BINDING_PATH} is missing: run `python -m paper_2602_08810_amd.build` "
                                "(the scan has no CPU or PyTorch fallback)")
         L = ctypes.CDLL(LIB_PATH)
         L.lrnnx_selective_scan_fwd.argtypes = [ctypes.POINTER(FwdArgs)]
@@ -183,7 +185,13 @@ def lib():
             _packed[n] = of_bytes((n, L))
         n = "lrnnx_selective_scan_bwd_workspace_bytes"
         _packed[n] = size_of_bytes((n, L))
+        from . import _binding
+        _binding.bind(_check, L.lrnnx_ckpt_interval(), tuple(ctypes.cast(getattr(L, "lrnnx_" + n), _vp).value for n in (
+            "selective_scan_fwd", "selective_scan_bwd", "selective_scan_bwd_workspace_bytes", "selective_scan_fwd_complex",
+            "selective_scan_bwd_complex", "selective_step", "selective_step_complex", "lti_diag_scan", "lti_diag_scan_bwd",
+            "diag_scan", "diag_scan_bwd", "workspace_bytes")))
         _lib = L
+        _native = _binding
     return _lib
 
 
@@ -313,6 +321,21 @@ def _device_checked(fn):
     return wrapper
 
 
+def _native_first(fn):
+    """Calls in their usual form are taken by csrc/binding.cpp, without the checks and the marshalling below; everything
+    else (None: nothing done) goes the general way, which is `__wrapped__`."""
+    name = fn.__name__
+
+    @functools.wraps(fn)
+    def wrapper(*args, **kwargs):
+        if _native is not None:
+            res = getattr(_native, name)(args, kwargs)
+            if res is not None:
+                return res
+        return fn(*args, **kwargs)
+    return wrapper
+
+
 def lrnnx_ckpt_interval() -> int:
     return int(lib().lrnnx_ckpt_interval())
 
@@ -344,6 +367,7 @@ def _bc_groups(Bm, Cm, io, Bsz, D, L, N):
     return G
 
 
+@_native_first
 @_device_checked
 def lrnnx_selective_scan_fwd(u, delta, A, Bm, Cm, Dskip=None, delta_bias=None, z=None, x0=None,
                              disc="zoh_s6", delta_softplus=True, path="auto",
@@ -402,6 +426,7 @@ def lrnnx_selective_scan_fwd(u, delta, A, Bm, Cm, Dskip=None, delta_bias=None, z
     return res[0] if len(res) == 1 else res
 
 
+@_native_first
 @_device_checked
 def lrnnx_selective_scan_fwd_complex(u, delta, A, Bm, Cm, Dskip=None, delta_bias=None, z=None, x0=None,
                                      disc="zoh_s6", delta_softplus=True, return_last_state=False, out=None,
@@ -496,6 +521,7 @@ def _check_complex_maps(A, Bm, Cm, io, Bsz, D, L):
     return N, G
 
 
+@_native_first
 @_device_checked
 def lrnnx_selective_scan_bwd_complex(u, delta, A, Bm, Cm, dy, Dskip=None, delta_bias=None, z=None, x0=None,
                                      ckpt=None, disc="zoh_s6", delta_softplus=True, want_dx0=False, outs=None,
@@ -588,6 +614,7 @@ def lrnnx_selective_scan_bwd_complex(u, delta, A, Bm, Cm, dy, Dskip=None, delta_
     return outs
 
 
+@_native_first
 @_device_checked
 def lrnnx_selective_scan_bwd(u, delta, A, Bm, Cm, dy, Dskip=None, delta_bias=None, z=None, x0=None,
                              ckpt=None, disc="zoh_s6", delta_softplus=True, want_dx0=False,
@@ -665,6 +692,7 @@ def lrnnx_selective_scan_bwd(u, delta, A, Bm, Cm, dy, Dskip=None, delta_bias=Non
     return outs
 
 
+@_native_first
 @_device_checked
 def lrnnx_lti_diag_scan(lam, v, x0=None, return_last_state=False, out=None, workspace=None, path="auto",
                         chain_status=None):
@@ -727,6 +755,7 @@ def lrnnx_lti_diag_scan_static(lam, v, out, x0=None, x_last_out=None):
     return out
 
 
+@_native_first
 @_device_checked
 def lrnnx_lti_diag_scan_bwd(lam, x, gx, x0=None, want_dx0=True, out=None, workspace=None, chain_status=None):
     """(dv [B,L,P], dlam [P], dx0 [B,P] or None) from the saved states x and the incoming gradient gx;
@@ -761,6 +790,7 @@ def lrnnx_lti_diag_scan_bwd(lam, x, gx, x0=None, want_dx0=True, out=None, worksp
     return dv, dlam, dx0
 
 
+@_native_first
 @_device_checked
 def lrnnx_diag_scan(a, b, x0=None, return_last_state=False, out=None, workspace=None, chain_status=None):
     """x [B,L,P] of x_k = a_k * x_{k-1} + b_k for float32 or complex64 a, b; see lrnnx_diag_scan_args."""
@@ -794,6 +824,7 @@ def lrnnx_diag_scan(a, b, x0=None, return_last_state=False, out=None, workspace=
     return (x, x_last) if return_last_state else x
 
 
+@_native_first
 @_device_checked
 def lrnnx_diag_scan_bwd(a, x, gx, x0=None, want_dx0=True, workspace=None, chain_status=None):
     """(da, db [B,L,P], dx0 [B,P] or None) from the forward call's a, saved states x and the incoming gradient gx;
@@ -835,6 +866,7 @@ def _bd(t, name, io):
     return t.data_ptr(), *t.stride()
 
 
+@_native_first
 @_device_checked
 def lrnnx_selective_step(x, u, delta, A, Bm, Cm, Dskip=None, delta_bias=None, z=None,
                          disc="zoh_s6", delta_softplus=True, out=None):
@@ -867,6 +899,7 @@ def lrnnx_selective_step(x, u, delta, A, Bm, Cm, Dskip=None, delta_bias=None, z=
     return y
 
 
+@_native_first
 @_device_checked
 def lrnnx_selective_step_complex(x, u, delta, A, Bm, Cm, Dskip=None, delta_bias=None, z=None,
                                  disc="zoh_s6", delta_softplus=True, out=None):
