@@ -22,7 +22,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "liblrnnx.so")
 BINDING = os.path.join(HERE, "_binding.so")
 PROBE = os.path.join(HERE, "valu_probe")
-SOURCES = ["selective_fwd.hip", "selective_fwd_f32.hip", "selective_bwd.hip", "selective_bwd_f32.hip", "api.hip", "selective_bwd_carry.hip", "selective_cplx_fwd.hip", "selective_cplx_fwd_f32.hip", "selective_cplx_bwd.hip", "selective_cplx_bwd_f32.hip", "lti_scan.hip", "diag_scan.hip", "step.hip"]
+SOURCES = ["selective_fwd.hip", "selective_fwd_f32.hip", "selective_bwd.hip", "selective_bwd_f32.hip", "api.hip", "selective_bwd_carry.hip", "selective_cplx_fwd.hip", "selective_cplx_fwd_f32.hip", "selective_cplx_bwd.hip", "selective_cplx_bwd_f32.hip", "lti_scan.hip", "diag_scan.hip", "column_scan.hip", "step.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

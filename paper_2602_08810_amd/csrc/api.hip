@@ -675,11 +675,15 @@ int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
     return launch_ss_bwd(p, a->io_dtype, a->disc, s) == hipSuccess ? LRNNX_OK : LRNNX_ERR_LAUNCH;
 }
 
-// the single-launch path on a chain workspace of at least lti_onepass_bytes(B, P, L) bytes (checked by the callers)
+// the single-launch paths, the chained one on a workspace of at least lti_onepass_bytes(B, P, L) bytes (checked by the callers)
 static int lti_onepass_run(const lrnnx_lti_args *a, void *ws, hipStream_t s) {
     const int64_t ng = cdiv(a->L, lti_onepass_group_steps(a->B, a->P));
     const int64_t wgx = (int64_t)a->B * cdiv(a->P, 64);
     if (ng > 65535 || wgx > 0x7fffffff) return LRNNX_ERR_UNSUPPORTED;
+    if (const int shape = column_shape(true, a->B, a->P, a->L)) {
+        const ColumnParams c = {a->B, a->P, a->L, a->lambda, a->v, a->x0, a->x, a->x_last};
+        return launch_column_scan(true, shape, c, s) == hipSuccess ? LRNNX_OK : LRNNX_ERR_LAUNCH;
+    }
     LtiParams p{};
     p.B = a->B; p.P = a->P; p.L = a->L;
     p.lambda = reinterpret_cast<const float2 *>(a->lambda);
@@ -822,6 +826,10 @@ int lrnnx_diag_scan(const lrnnx_diag_scan_args *a) {
         (reinterpret_cast<uintptr_t>(a->workspace) & 7u))
         return LRNNX_ERR_WORKSPACE;
     hipStream_t s = reinterpret_cast<hipStream_t>(a->stream);
+    if (const int shape = cplx ? 0 : column_shape(false, a->B, a->P, a->L)) {
+        const ColumnParams c = {a->B, a->P, a->L, a->a, a->b, a->x0, a->x, a->x_last};
+        return launch_column_scan(false, shape, c, s) == hipSuccess ? LRNNX_OK : LRNNX_ERR_LAUNCH;
+    }
     DiagParams p{};
     p.B = a->B; p.P = a->P; p.L = a->L;
     p.is_complex = cplx; p.ngroups = (int)ng;

@@ -1,0 +1,213 @@
+// Scans over time with one workgroup to a block of columns, for gfx950: the LTI recurrence x_k = lambda x_{k-1} + v_k and the real
+// recurrence with caller-supplied coefficients x_k = a_k x_{k-1} + b_k (Eq. 2 of the paper, Sec. 2.2.1 and 2.2.2).
+//
+// The arrays are [B,L,P] with P contiguous.  A workgroup takes COLS neighbouring columns of one batch entry and walks the
+// whole time axis in tiles, the next tile's loads under way during this one's steps.  Nothing is exchanged between
+// workgroups: no workspace, no launch that arms one (4.7 us), no waiting on a chain.  Of a wavefront's 64 lanes COLS lie along the
+// columns and J = 64 / COLS along time; a lane owns T consecutive steps, a wavefront J T and a tile W J T.  Lanes fold their steps
+// to affine pairs, a prefix over the J pieces stays in the wavefront, and the wavefronts' pairs meet in LDS, where every lane chains
+// them onto the carry that it keeps.
+//
+// What bounds it: memory, or with few tiles' work a workgroup the latency of a tile (1 to 3 us).  Against the chained scans with the launch that
+// arms their slots (us): 2 x 102 columns of 280 steps, LTI 8.5 -> 4.9, 7 x 455 of 1966 27.6 -> 25.8, 4 x 256 of 4096 18.5 -> 16.5; real
+// coefficients 16 x 30 of 467 7.0 -> 4.6, 8 x 1024 of 2048 35.7 -> 33.9.  16 steps a lane spill (56 us on the
+// 8 x 1024 columns), and with one set of registers refilled during the replay less is under way (36).
+#include "kernels.hpp"
+#include "chain.hpp"
+#include "elem.hpp"
+#include <cmath>
+#include <type_traits>
+
+namespace lrnnx {
+
+template <bool LTI, int COLS, int T, int W>
+__global__ __launch_bounds__(W * 64, 4) void k_column_scan(const ColumnParams p) {
+    using EL = Elem<LTI>;                                      // complex poles, real coefficients
+    using E = typename EL::T;
+    constexpr int J = 64 / COLS, SPAN = J * T, TILE = W * SPAN;
+    // The pairs of caller-supplied coefficients are formed and chained in double precision: 8 steps a lane pass through more of them than the
+    // chained scan's 32, and in single precision the states' error (2-norm, against 64 bits) was 4.3e-8 where that scan's is 4.0e-8.
+    using ED = std::conditional_t<LTI, EL, Elem<false, double>>;
+    using D = typename ED::T;
+    __shared__ D sS[2][W][COLS], sA[2][LTI ? 1 : W][COLS];
+
+    const int lane = threadIdx.x & 63, c = lane % COLS, j = lane / COLS;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // blocks that share cache lines go to one XCD (workgroup i runs on XCD i % 8)
+    const int nblk = (p.P + COLS - 1) / COLS;
+    const unsigned id = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (id >= (unsigned)nblk * (unsigned)p.B) return;          // (the whole workgroup)
+    const int b = id / nblk, col = (id % nblk) * COLS + c;
+    const bool okp = col < p.P;
+    const int64_t P = p.P, pc = okp ? col : p.P - 1;           // (lanes past the last column repeat it and store nothing)
+    // An element's address: a row that all lanes share (in scalar registers) and the lane's offset in bytes, 32 bits: see column_fits
+    const unsigned off = ((unsigned)(j * T) * (unsigned)p.P + (unsigned)pc) * (unsigned)sizeof(E);
+    const int64_t row0 = ((int64_t)b * p.L + w * SPAN) * P;    // of the wavefront's first step
+    const int first = (w * J + j) * T;                         // the lane's first position within a tile
+
+    // Powers of lambda: T 2^i steps, the lane's pieces before it, a wavefront.  Squared in double precision, rounded once (see cpow).
+    E lam = EL::one(), lam_w = EL::one(), lam_j = EL::one(), lam_d[7] = {};
+    if constexpr (LTI) {
+        lam = reinterpret_cast<const E *>(p.a)[pc];
+        double2 q = make_double2(lam.x, lam.y), r = make_double2(1.0, 0.0);
+        auto times = [](double2 x, double2 y) { return make_double2(x.x * y.x - x.y * y.y, x.x * y.y + x.y * y.x); };
+#pragma unroll
+        for (int e = 1; e < T; e *= 2) q = times(q, q);
+#pragma unroll
+        for (int d = 1, i = 0; d < J; d *= 2, ++i) {
+            lam_d[i] = make_float2((float)q.x, (float)q.y);
+            const double2 t = times(r, q);
+            if (j & d) r = t;
+            q = times(q, q);
+        }
+        lam_w = make_float2((float)q.x, (float)q.y);
+        lam_j = make_float2((float)r.x, (float)r.y);
+    }
+    D carry = p.x0 ? ED::from(reinterpret_cast<const E *>(p.x0)[(int64_t)b * P + pc]) : ED::zero();
+
+    struct Steps { E v[T], a[LTI ? 1 : T]; };
+    // Steps past the end of the sequence are read from its last row (no branch for each) and become the identity map in `run`.
+    auto fetch = [&](int64_t tile, Steps &s) {
+        const E *vr = reinterpret_cast<const E *>(p.b) + row0 + tile * TILE * P;
+        const E *ar = LTI ? nullptr : reinterpret_cast<const E *>(p.a) + row0 + tile * TILE * P;
+        if ((tile + 1) * TILE <= p.L) {
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                s.v[i] = load_at<false>(vr + i * P, off);
+                if constexpr (!LTI) s.a[i] = load_at<false>(ar + i * P, off);
+            }
+        } else {
+            const int64_t left = p.L - 1 - tile * TILE - first;          // of the lane's steps' rows, the last that there is
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                const int64_t at = ((int64_t)b * p.L + tile * TILE + first + (i < left ? i : left)) * P + pc;
+                s.v[i] = reinterpret_cast<const E *>(p.b)[at];
+                if constexpr (!LTI) s.a[i] = reinterpret_cast<const E *>(p.a)[at];
+            }
+        }
+    };
+    auto run = [&](int64_t tile, Steps &s, const int buf) {
+        const int64_t rem = p.L - tile * TILE;
+        if (rem < TILE) {
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                s.v[i] = EL::pick(first + i < rem, s.v[i], EL::zero());
+                if constexpr (!LTI) s.a[i] = EL::pick(first + i < rem, s.a[i], EL::one());
+            }
+        }
+        auto coef = [&](int i) { if constexpr (LTI) return lam; else return s.a[i]; };
+        // ---- fold of the lane's steps, prefix over the wavefront's pieces
+        D A = ED::one(), S = ED::zero();
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            S = ED::fma(ED::from(coef(i)), S, ED::from(s.v[i]));
+            if constexpr (!LTI) A = ED::mul(ED::from(s.a[i]), A);
+        }
+#pragma unroll
+        for (int d = 1, n = 0; d < J; d *= 2, ++n) {
+            const D Sp = ED::up(S, d * COLS);
+            if constexpr (LTI) { if (j >= d) S = ED::fma(lam_d[n], Sp, S); }
+            else {
+                const D Ap = ED::up(A, d * COLS);
+                if (j >= d) { S = ED::fma(A, Sp, S); A = ED::mul(A, Ap); }
+            }
+        }
+        if (j == J - 1) { sS[buf][w][c] = S; if constexpr (!LTI) sA[buf][w][c] = A; }
+        D Se = ED::zero(), Ae = ED::one();                     // of the pieces before this lane's
+        if constexpr (J > 1) {
+            Se = ED::pick(j > 0, ED::up(S, COLS), Se);
+            if constexpr (!LTI) Ae = ED::pick(j > 0, ED::up(A, COLS), Ae);
+        }
+        __syncthreads();                                       // (two buffers: the one of the tile before may still be read)
+        // ---- the wavefronts' pairs onto the carry
+        D enter = carry;
+#pragma unroll
+        for (int ww = 0; ww < W; ++ww) {
+            if (ww == w) enter = carry;
+            if constexpr (LTI) carry = ED::fma(lam_w, carry, sS[buf][ww][c]);
+            else carry = ED::fma(sA[buf][ww][c], carry, sS[buf][ww][c]);
+        }
+        E x;
+        if constexpr (LTI) x = EL::fma(lam_j, enter, Se);
+        else x = EL::from(ED::fma(Ae, enter, Se));
+        // ---- replay
+        E *xr = reinterpret_cast<E *>(p.x) + row0 + tile * TILE * P;
+        if (rem >= TILE) {
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                x = EL::fma(coef(i), x, s.v[i]);
+                if (okp) store_at<false>(xr + i * P, off, x);
+            }
+            if (rem == TILE && p.x_last && okp && first == TILE - T) reinterpret_cast<E *>(p.x_last)[(int64_t)b * P + pc] = x;
+        } else {
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                x = EL::fma(coef(i), x, s.v[i]);
+                if (okp && first + i < rem) store_at<false>(xr + i * P, off, x);
+                if (okp && first + i == rem - 1 && p.x_last) reinterpret_cast<E *>(p.x_last)[(int64_t)b * P + pc] = x;
+            }
+        }
+    };
+
+    const int64_t ntiles = (p.L + TILE - 1) / TILE;
+    Steps s0, s1;
+    fetch(0, s0);
+    for (int64_t tile = 0; tile < ntiles; tile += 2) {
+        if (tile + 1 < ntiles) fetch(tile + 1, s1);
+        run(tile, s0, 0);
+        if (tile + 1 >= ntiles) break;
+        if (tile + 2 < ntiles) fetch(tile + 2, s0);
+        run(tile + 1, s1, 1);
+    }
+}
+
+// ---------------------------------------------------------------- which scan, which shape
+// The estimated time of a call (us): a start, and of the rest a part for its steps one after the other and one for its bytes, which overlap:
+// c0 + hypot(c1 * steps, c2 * MB), c2 for rows that are whole cache lines or not.  `steps` counts tiles, times the rounds in which the workgroups
+// fit the chip, or for the chained scans thousands of time steps; the bytes of a column scan take longer, by the root of what a last round of one
+// workgroup a compute unit lacks.  Rows that are not whole lines vary more with their length, and a column scan is taken there from an
+// estimate a tenth below the other's.  Fitted over 240 shapes of 16 to 2048 columns, 64 to 16384 steps, 1 to 32 batch entries and 0.1 to 1100 MB: the
+// choice is 1.33 (LTI) and 1.10 times (real) as fast as the chained scans alone (geometric mean), at worst 1.07 and 1.11 times as long.
+struct ColumnCost { int cols, waves; double c0, c1, c2[2]; };           // c2: whole lines, others
+constexpr int kColumnT = 8;
+constexpr double kChainedCost[2][4] = {{7.5, 1.39, 0.151, 0.21}, {6.2, 0.9, 0.163, 0.229}};
+// LTI, real: 32-byte pieces of a row for few columns, 16 columns in half as large a workgroup for short sequences, whole lines of real values
+// for many columns
+constexpr ColumnCost kColumnCost[2][3] = {{{4, 8, 3.5, 1.45, {0.182, 0.209}}, {16, 4, 3.0, 0.9, {0.16, 0.185}}, {0, 0, 0, 0, {0, 0}}},
+                                          {{8, 8, 3.1, 1.55, {0.194, 0.223}}, {16, 4, 2.75, 1.18, {0.167, 0.165}}, {32, 8, 3.27, 1.32, {0.138, 0.15}}}};
+
+int column_shape(bool lti, int B, int P, int64_t L) {
+    const int64_t es = lti ? 8 : 4, arrays = lti ? 2 : 3;
+    const int part = P * es % kCacheLine == 0 ? 0 : 1;
+    const double mb = (double)arrays * es * B * P * (double)L * 1e-6;
+    const double *k = kChainedCost[lti ? 0 : 1];
+    double least = k[0] + std::hypot(k[1] * (double)L * 1e-3, k[2 + part] * mb);
+    int shape = 0;
+    for (int i = 0; i < 3; ++i) {
+        const ColumnCost &c = kColumnCost[lti ? 0 : 1][i];
+        if (!c.cols) continue;
+        const int64_t wgs = (int64_t)B * ((P + c.cols - 1) / c.cols), tile = (int64_t)c.waves * kColumnT * 64 / c.cols;
+        // a lane's offset in 32 bits, and a grid's threads in 32 bits
+        if (64 / c.cols * kColumnT * (int64_t)P * es >= (1ll << 31) || wgs > (1ll << 22)) continue;
+        const int64_t places = (c.waves == 8 ? 2 : 4) * kNumCU, rounds = (wgs + places - 1) / places;
+        const double full = std::sqrt((double)((wgs + kNumCU - 1) / kNumCU * kNumCU) / (double)wgs);
+        const double t = (c.c0 + std::hypot(c.c1 * (double)((L + tile - 1) / tile * rounds), c.c2[part] * mb * full)) / (part ? 0.9 : 1.0);
+        if (t < least) { least = t; shape = i + 1; }
+    }
+    return shape;
+}
+
+template <bool LTI, int COLS, int W> static void launch(const ColumnParams &p, hipStream_t s) {
+    const unsigned wgs = (unsigned)p.B * ((p.P + COLS - 1) / COLS);
+    hipLaunchKernelGGL((k_column_scan<LTI, COLS, kColumnT, W>), dim3((wgs + 7) / 8 * 8), dim3(W * 64), 0, s, p);
+}
+
+hipError_t launch_column_scan(bool lti, int shape, const ColumnParams &p, hipStream_t s) {
+    if (lti) { if (shape == 1) launch<true, 4, 8>(p, s); else launch<true, 16, 4>(p, s); }
+    else if (shape == 1) launch<false, 8, 8>(p, s);
+    else if (shape == 2) launch<false, 16, 4>(p, s);
+    else launch<false, 32, 8>(p, s);
+    return hipGetLastError();
+}
+
+}  // namespace lrnnx

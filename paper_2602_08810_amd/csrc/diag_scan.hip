@@ -10,28 +10,9 @@
 // pair as two.  HBM-bound: 3 elements per step (a and b read once, x written once).
 #include "kernels.hpp"
 #include "chain.hpp"
+#include "elem.hpp"
 
 namespace lrnnx {
-
-template <bool CPLX> struct Elem;
-template <> struct Elem<false> {
-    using T = float;
-    static __device__ __forceinline__ T zero() { return 0.0f; }
-    static __device__ __forceinline__ T one() { return 1.0f; }
-    static __device__ __forceinline__ T mul(T a, T b) { return a * b; }
-    static __device__ __forceinline__ T fma(T a, T x, T b) { return __builtin_fmaf(a, x, b); }
-    static __device__ __forceinline__ T nan() { return __builtin_nanf(""); }
-    static __device__ __forceinline__ T conj(T a) { return a; }
-};
-template <> struct Elem<true> {
-    using T = float2;
-    static __device__ __forceinline__ T zero() { return make_float2(0.0f, 0.0f); }
-    static __device__ __forceinline__ T one() { return make_float2(1.0f, 0.0f); }
-    static __device__ __forceinline__ T mul(T a, T b) { return cmul(a, b); }
-    static __device__ __forceinline__ T fma(T a, T x, T b) { return cfma(a, x, b); }
-    static __device__ __forceinline__ T nan() { return make_float2(__builtin_nanf(""), __builtin_nanf("")); }
-    static __device__ __forceinline__ T conj(T a) { return make_float2(a.x, -a.y); }
-};
 
 // ANCH: every ANCH-th group publishes its true end state; a group looks back over at most ANCH-1 aggregates.
 // BWD = false: the scan.  BWD = true: its adjoint, the same chain over reversed time (scan position j is time

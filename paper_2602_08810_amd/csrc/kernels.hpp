@@ -169,6 +169,14 @@ struct DiagParams {
     void *da;                // [B,L,P] out
 };
 
+// forward scans with one workgroup to a block of columns
+struct ColumnParams {
+    int B, P;
+    int64_t L;
+    const void *a, *b, *x0;  // lambda [P] (float2) or a [B,L,P] (float); v or b [B,L,P]; [B,P] or null
+    void *x, *x_last;
+};
+
 struct StepParams {
     int B, D, N;
     int softplus;
@@ -291,6 +299,9 @@ int diag_scan_group_steps(int64_t B, int64_t P, int is_complex);
 int diag_scan_min_group_steps(int is_complex);
 int diag_scan_anchor(int is_complex);
 hipError_t launch_diag_scan_bwd(const DiagParams &p, hipStream_t s);
+// a shape of the column scan (from 1) where it is estimated to be faster than the chained one, else 0
+int column_shape(bool lti, int B, int P, int64_t L);
+hipError_t launch_column_scan(bool lti, int shape, const ColumnParams &p, hipStream_t s);
 int diag_scan_bwd_group_steps(int is_complex);
 int lti_onepass_bwd_group_steps();
 hipError_t launch_fill(const FillList &z, hipStream_t s);
