@@ -262,7 +262,7 @@ typedef struct lrnnx_ss_bwd_args {
                                     only when max_seqlen is given. */
     const int64_t *cu_seqlens;   /* as in the forward call (then dBm, dCm are [G,L,N]), or NULL.  In packed mode the
                                     workspace also holds B ints that let the launch start the longest sequences first
-                                    (batches of up to 256 sequences), which shortens its tail; a workspace without
+                                    (batches of 65 to 256 sequences; fewer need none), which shortens its tail; a workspace without
                                     room for them is accepted and the launch keeps the caller's order. */
     int64_t max_seqlen;          /* packed mode: the longest sequence of the batch (steps) if the caller knows it,
                                     else 0.  A hint for the launch shape only, never for addressing: with it the

@@ -191,7 +191,7 @@ size_t bwd_ckpt_bytes(const lrnnx_ss_bwd_args *a) {
     return (size_t)rows * a->N * sizeof(float);
 }
 size_t bwd_order_bytes(const lrnnx_ss_bwd_args *a, int nchunks) {
-    return a->cu_seqlens && nchunks == 1 && a->B > 1 && a->B <= kMaxOrdered ? sizeof(int) * (size_t)a->B : 0;
+    return a->cu_seqlens && nchunks == 1 && a->B > kMaxRanked && a->B <= kMaxOrdered ? sizeof(int) * (size_t)a->B : 0;
 }
 
 // The real and the complex backward entry points take the same per-row tensors (same field names in both argument
@@ -524,8 +524,10 @@ int lrnnx_selective_scan_bwd_complex(const lrnnx_ss_bwd_complex_args *a) {
         used += (size_t)2 * a->B * a->D * p.nchunks * a->N * sizeof(float2);
         if (launch_ss_cbwd_agg(p, a->io_dtype, a->disc, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
     }
-    // packed batches: longest sequences first, if the workspace has room for the order (as in the real backward)
-    if (cu && pl.nchunks == 1 && a->B > 1 && a->B <= kMaxOrdered && a->workspace &&
+    // packed batches: longest sequences first; more than the workgroups rank themselves if the workspace has room for the order (as
+    // in the real backward)
+    p.ranked = cu && pl.nchunks == 1 && a->B > 1 && a->B <= kMaxRanked;
+    if (cu && pl.nchunks == 1 && a->B > kMaxRanked && a->B <= kMaxOrdered && a->workspace &&
         a->workspace_bytes >= carry_off + sizeof(int) * (size_t)a->B) {
         int *order = reinterpret_cast<int *>(static_cast<char *>(a->workspace) + carry_off);
         if (launch_seq_order(cu, a->B, a->L, order, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
@@ -643,8 +645,9 @@ int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
         p.hc = p.ws_Q;
         if (launch_ss_bwd_agg(p, a->io_dtype, a->disc, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
     }
-    // packed batches: longest sequences first, if the workspace has room for the order (B ints, after the checkpoints
-    // of the recompute sweep if there are any)
+    // packed batches: longest sequences first; more than the workgroups rank themselves if the workspace has room for the order (B
+    // ints, after the checkpoints of the recompute sweep if there are any)
+    p.ranked = cu && pl.nchunks == 1 && a->B > 1 && a->B <= kMaxRanked;
     const size_t order_bytes = bwd_order_bytes(a, pl.nchunks);
     if (order_bytes && a->workspace && a->workspace_bytes >= carry_off + order_bytes) {
         int *order = reinterpret_cast<int *>(static_cast<char *>(a->workspace) + carry_off);

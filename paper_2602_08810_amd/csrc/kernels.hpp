@@ -17,6 +17,7 @@ struct FwdParams {
     int bcg, dpg;            // number of Bm/Cm groups and channels per group (D = bcg * dpg)
     const int64_t *cu;       // packed variable-length mode: [B+1] sequence boundaries on the packed axis of L steps
     int64_t nslots;          // packed mode: checkpoint slots per channel
+    bool ranked;             // packed mode: blockIdx.y counts from the longest sequence down (see seq_span)
     int nchunks;
     int64_t tiles_per_chunk;
     const void *u, *delta, *z;
@@ -36,6 +37,7 @@ struct CFwdParams {
     int bcg, dpg;            // number of Bm/Cm groups and channels per group (D = bcg * dpg)
     const int64_t *cu;       // packed variable-length mode: [B+1] sequence boundaries on the packed axis of L steps
     int64_t nslots;          // packed mode: checkpoint slots per channel
+    bool ranked;             // as in FwdParams
     const void *u, *delta, *z;
     void *y;
     int64_t u_sb, u_sd, dl_sb, dl_sd, z_sb, z_sd, y_sb, y_sd;
@@ -76,6 +78,7 @@ struct CBwdParams {
     float2 *ws_P, *ws_Q;
     const float2 *hc;
     const int *order;        // packed mode: sequences in the order the launch should start them, or null
+    bool ranked;             // as in BwdParams
     int wcap, gmin;          // packed mode with a known longest sequence: as in BwdParams
     float *part;             // workspace of the tile sums of dBm and dCm, as in BwdParams (two floats a state), or null
     int64_t part_tiles;
@@ -103,8 +106,10 @@ struct BwdParams {
     int64_t tiles_per_chunk;
     float *ws_P, *ws_Q;
     const float *hc;
-    // packed mode: sequences in the order the launch should start them (longest first), or null for 0, 1, 2, ...
+    // packed mode, longest sequences first: more than 64 in an order that a launch of its own has formed, or null; up to 64 are ranked by
+    // the workgroups themselves
     const int *order;
+    bool ranked;
     // packed mode with a known longest sequence: cap on the channel-tiles (channels x 256-step tiles) one workgroup
     // walks, and the fewest channels a workgroup may take (the grid is sized for that; 0: no cap, always G).  A
     // workgroup of a long sequence then takes wcap / tiles channels, between gmin and G, and the workgroups of the
@@ -131,6 +136,13 @@ constexpr size_t kBwdSumsCap = (size_t)512 << 20;
 // to Gbal, those of a batch [B,D,L] of equal lengths; else cap and fewest channels as in BwdParams.  `places` =
 // workgroups the chip holds at once.
 void bwd_packed_shape(int B, int D, int dpg, int64_t L, int64_t max_seqlen, int Gbal, int places, int *G, int *wcap, int *gmin);
+constexpr int kMaxRanked = 64;       // sequences that a workgroup ranks itself (one a lane)
+// Whether a forward launch of `wgs` workgroups with 16 lanes a channel, three of which a compute unit holds, ranks its sequences.  Where all run at
+// once their order changes nothing, and a workgroup with little work would pay for it: 60 sequences of 68 steps, 331 channels, N = 4,
+// float32, 64 lanes a channel, took 30 us instead of 21; 60 of 67, 1000 channels, N = 8, 16 lanes, 48 -> 41 with it and the short tiles.
+inline bool ranked_sequences(const int64_t *cu, int B, int N, int64_t wgs) {
+    return cu && N >= 8 && B > 1 && B <= kMaxRanked && wgs > 3 * kNumCU;
+}
 constexpr int kMaxOrdered = 256;     // packed batches of more sequences than this are not reordered
 hipError_t launch_seq_order(const int64_t *cu, int B, int64_t L, int *order, hipStream_t s);
 

@@ -182,15 +182,6 @@ template <int N> struct BwdGeom {
 // while the row addresses of the maps were spilled beside).
 template <int N, int DISC> constexpr bool bwd_pairs() { return N == 16 && (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC); }
 
-// `sequence bounds of batch entry b`: packed variable-length mode (cu != nullptr): batch entry b is the sequence of
-// steps cu[b] .. cu[b+1]-1 of ONE packed time axis of Lp steps.  The bounds are clamped to the packed axis, so no
-// content of cu can send an access out of the buffers.
-__device__ __forceinline__ void seq_bounds(const int64_t *cu, int b, int64_t Lp, int64_t &toff, int64_t &L) {
-    int64_t o = cu[b], e = cu[b + 1];
-    o = o < 0 ? 0 : (o > Lp ? Lp : o);
-    e = e < o ? o : (e > Lp ? Lp : e);
-    toff = o; L = e - o;
-}
 // channels per workgroup for a sequence of ntiles tiles: fewer than G in a packed batch with a work cap
 __device__ __forceinline__ int channels_of(const BwdParams &p, int64_t ntiles) {
     if (p.wcap <= 0) return p.G;
@@ -221,11 +212,12 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
     const int lane = tid & 63, li = lane & 31, half = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n0 = w * NS;                           // this wavefront's first state
-    // packed batches: workgroups start in launch order, so the longest sequences go first and the short ones fill the
-    // end of the launch instead of a long one running on alone
-    const int b = p.order ? p.order[blockIdx.y] : blockIdx.y;
+    int b = blockIdx.y;
     int64_t L = p.L, toff = 0, bs = b;
-    if (p.cu) { seq_bounds(p.cu, b, p.L, toff, L); bs = 0; }
+    if (p.cu) {
+        const SeqSpan q = seq_span(p.cu, p.B, p.L, b, p.ranked, p.order);           // the longest sequences start first
+        b = q.b; toff = q.toff; L = q.L; bs = 0;
+    }
     const int64_t slot0 = p.cu ? toff / TILE + b : (int64_t)b * p.part_tiles;    // first tile of this entry among all tiles
     // Chunked launch: this workgroup walks chunk blockIdx.z of its rows only, i.e. the steps toff .. toff + L - 1 of
     // the time axis, starting from that chunk's carried adjoint.  Chunks are counted from the start of the sequence;
@@ -899,7 +891,8 @@ __global__ __launch_bounds__(256) void k_ss_bwd_maps(const BwdParams p, int gx) 
             if (o / kBwdTileSteps + mid <= slot) lo = mid; else hi = mid - 1;
         }
         b = lo;
-        seq_bounds(p.cu, lo, p.L, toff, L);
+        const SeqSpan q = seq_span(p.cu, p.B, p.L, lo, false);
+        toff = q.toff; L = q.L;
         tile = slot - (toff / kBwdTileSteps + b);
     } else {
         b = slot / p.part_tiles;

@@ -166,16 +166,13 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n0 = w * NS;                           // this wavefront's first state
-    const int b = p.order ? p.order[blockIdx.y] : blockIdx.y;   // packed batches: the longest sequences start first
-    // Packed variable-length mode (p.cu != nullptr): batch entry b is the sequence of steps cu[b] .. cu[b+1]-1 of ONE
-    // packed time axis of p.L steps; I/O rows have no batch stride, the maps and their gradients are [G, p.L, N].
-    // The bounds are clamped to the packed axis, so no content of cu can send an access out of the buffers.
+    int b = blockIdx.y;
+    // packed variable-length mode (p.cu != nullptr, see seq_span): I/O rows have no batch stride, the maps and their gradients are
+    // [G, p.L, N]
     int64_t L = p.L, toff = 0, bs = b;
     if (p.cu) {
-        int64_t o = p.cu[b], e = p.cu[b + 1];
-        o = o < 0 ? 0 : (o > p.L ? p.L : o);
-        e = e < o ? o : (e > p.L ? p.L : e);
-        toff = o; L = e - o; bs = 0;
+        const SeqSpan q = seq_span(p.cu, p.B, p.L, b, p.ranked, p.order);           // the longest sequences start first
+        b = q.b; toff = q.toff; L = q.L; bs = 0;
     }
     // Chunked launch: this workgroup walks chunk blockIdx.z of its rows only, i.e. the steps toff .. toff + L - 1 of
     // the time axis, starting from that chunk's carried adjoint.  Chunks are counted from the start of the sequence;

@@ -92,7 +92,7 @@ __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) vo
     const int tid = threadIdx.x;
     const int lane = tid & 63, li = lane % LPC;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int b = blockIdx.y;
+    int b = blockIdx.y;
     // a workgroup takes CH consecutive channels of ONE Bm/Cm group (it stages that group's maps in LDS)
     const int blk_per_grp = (p.dpg + CH - 1) / CH;
     const int grp = blockIdx.x / blk_per_grp;
@@ -104,17 +104,13 @@ __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) vo
     const int d0 = grp * p.dpg + din0;
     const int d = grp * p.dpg + (live ? din0 + ch : p.dpg - 1);
     const int chunk = blockIdx.z;
-    // Packed variable-length mode (p.cu != nullptr): batch entry b is the sequence of steps cu[b] .. cu[b+1]-1 of ONE
-    // packed time axis of p.L steps; I/O rows have no batch stride, the maps are [G, p.L, N].  The bounds are
-    // clamped to the packed axis, so no content of cu can send an access out of the buffers.
+    // packed variable-length mode (p.cu != nullptr, see seq_span): I/O rows have no batch stride, the maps are [G, p.L, N]
     int64_t L = p.L, toff = 0;
     constexpr bool BRIEF = LPC == 64 && T == 4;      // see row()
     std::conditional_t<BRIEF, unsigned, int64_t> bs = b;
     if (p.cu) {
-        int64_t o = p.cu[b], e = p.cu[b + 1];
-        o = o < 0 ? 0 : (o > p.L ? p.L : o);
-        e = e < o ? o : (e > p.L ? p.L : e);
-        toff = o; L = e - o; bs = 0;
+        const SeqSpan q = seq_span_fwd<LPC == 16>(p.cu, p.B, p.L, b, p.ranked);
+        b = q.b; toff = q.toff; L = q.L; bs = 0;
     }
     const int64_t ntiles = (L + TILE - 1) / TILE;
     const int64_t tile0 = (int64_t)chunk * p.tiles_per_chunk;
@@ -456,6 +452,8 @@ static hipError_t launch_cfwd_lanes(CFwdParams p, hipStream_t s) {
     if (p.nchunks == 1) p.tiles_per_chunk = (p.L + GE::TILE - 1) / GE::TILE;
     // the aggregate launch skips the last chunk: nobody needs its pair
     const dim3 grid(p.bcg * ((p.dpg + GE::CH - 1) / GE::CH), p.B, p.mode == MODE_AGG ? p.nchunks - 1 : p.nchunks), block(GE::W * 64);
+    // packed batches of more workgroups than the chip holds: longest sequences first
+    p.ranked = LPC == 16 && ranked_sequences(p.cu, p.B, N, (int64_t)grid.x * grid.y);
     if (p.mode != MODE_AGG && p.y) hipLaunchKernelGGL((k_ss_cfwd<IO, N, DISC, true, LPC, T>), grid, block, 0, s, p);
     else hipLaunchKernelGGL((k_ss_cfwd<IO, N, DISC, false, LPC, T>), grid, block, 0, s, p);
     return hipGetLastError();

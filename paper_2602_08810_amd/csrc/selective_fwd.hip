@@ -123,7 +123,7 @@ __global__ __launch_bounds__((FwdGeom<LPC, TM>::W * 64), (TM == 16 ? (LPC == 16 
     const int tid = threadIdx.x;
     const int lane = tid & 63, li = lane % LPC;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int b = blockIdx.y;
+    int b = blockIdx.y;
     // a workgroup takes CH consecutive channels of ONE Bm/Cm group (it stages that group's maps in LDS)
     const int blk_per_grp = (p.dpg + CH - 1) / CH;
     const int grp = blockIdx.x / blk_per_grp;
@@ -134,15 +134,11 @@ __global__ __launch_bounds__((FwdGeom<LPC, TM>::W * 64), (TM == 16 ? (LPC == 16 
     const int d0 = grp * p.dpg + din0;
     const int d = grp * p.dpg + (live ? din0 + ch : p.dpg - 1);
     const int chunk = blockIdx.z;
-    // Packed variable-length mode (p.cu != nullptr): batch entry b is the sequence of steps cu[b] .. cu[b+1]-1 of ONE
-    // packed time axis of p.L steps; I/O rows have no batch stride, the maps are [G, p.L, N].  The bounds are
-    // clamped to the packed axis, so no content of cu can send an access out of the buffers.
+    // packed variable-length mode (p.cu != nullptr, see seq_span): I/O rows have no batch stride, the maps are [G, p.L, N]
     int64_t L = p.L, toff = 0, bs = b;
     if (p.cu) {
-        int64_t o = p.cu[b], e = p.cu[b + 1];
-        o = o < 0 ? 0 : (o > p.L ? p.L : o);
-        e = e < o ? o : (e > p.L ? p.L : e);
-        toff = o; L = e - o; bs = 0;
+        const SeqSpan q = seq_span_fwd<LPC == 16>(p.cu, p.B, p.L, b, p.ranked);
+        b = q.b; toff = q.toff; L = q.L; bs = 0;
     }
     const int64_t ntiles = (L + TILE - 1) / TILE;
     const int64_t tile0 = (int64_t)chunk * p.tiles_per_chunk;
@@ -577,6 +573,8 @@ static hipError_t launch_fwd_lanes(FwdParams p, hipStream_t s) {
     // tiles_per_chunk counts tiles of 256 steps; a single pass is one chunk whatever the tile
     if (p.nchunks == 1) p.tiles_per_chunk = (p.L + GE::TILE - 1) / GE::TILE;
     dim3 grid(p.bcg * ((p.dpg + GE::CH - 1) / GE::CH), p.B, p.mode == MODE_AGG ? p.nchunks - 1 : p.nchunks);
+    // packed batches of more workgroups than the chip holds: longest sequences first
+    p.ranked = LPC == 16 && ranked_sequences(p.cu, p.B, N, (int64_t)grid.x * grid.y);
     const bool want_y = (p.mode == MODE_FULL || p.mode == MODE_APPLY);
     const dim3 block(GE::W * 64);
     if (want_y && p.ckpt) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, true, true, LPC, T>), grid, block, 0, s, p);
