@@ -856,20 +856,22 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
 
 // dBm, dCm [.., L, N] from the tile sums the workgroups of k_ss_bwd left in the workspace: a workgroup adds one piece of a
 // tile (blockIdx.x) of one of the two maps (blockIdx.y) of one group (blockIdx.z) over the channel blocks, always in the same order, and
-// transposes it through LDS.  With many tiles it is bound by the reads of the workspace.  With few tiles of many channel blocks a
+// transposes it through LDS.  With many tiles it is bound by the reads of the workspace, whole lines of 128 bytes (half lines, as the pieces
+// of 32 states, or of 16 complex ones, once were: 32 blocks of 64 tiles 41 us, now 22 or 6.0 TB/s).  With few tiles of many channel blocks a
 // chain of reads is what it waits for: KS threads then share an element, each a quarter of the blocks, and a
 // workgroup takes a quarter of the piece (whole call, bf16, L = 512: 1024 rows, N = 16 49 us, so 41; 4096 rows 73 and 57, N = 4
 // 57 and 42).
 template <int N> struct BwdMaps {
-    static constexpr int PIECES = N >= 8 ? N / 4 : 1;                // pieces of a tile, of one thread an element
+    // pieces of a tile, of one thread an element: of time as long as what is read of a state stays whole lines, then of the states
+    static constexpr int TIME = N >= 16 ? 4 : N >= 8 ? N / 4 : 1, STATES = N > 16 ? N / 16 : 1, PIECES = TIME * STATES;
 };
 template <int N, int KS>
 __global__ __launch_bounds__(256) void k_ss_bwd_maps(const BwdParams p, int gx) {
     constexpr int PT = N * kBwdTileSteps;            // floats of one map's sums of one tile
     // the quarter of a piece is one of time as long as what is read of a state stays whole lines of 128 bytes, and one of the
     // states beyond that (cut to 32 bytes, the sums of 4096 rows of 2048 steps, N = 16, took 40 us longer)
-    constexpr int LS = KS == 1 || N >= 16 ? 1 : KS * 4 / N, NP = KS / LS;
-    constexpr int PIECES = BwdMaps<N>::PIECES * LS;
+    constexpr int LS = KS == 1 || N >= 16 ? 1 : KS * 4 / N, NP = KS / LS * BwdMaps<N>::STATES;
+    constexpr int PIECES = BwdMaps<N>::TIME * LS;
     constexpr int LP = 32 / PIECES;                  // lanes (of 8 steps) of a piece
     constexpr int SP = LP * 8;                       // its steps
     constexpr int NW = N / NP;                       // its states
@@ -997,9 +999,11 @@ hipError_t launch_ss_bwd(const BwdParams &p, int io_dtype, int disc, hipStream_t
 template <int N>
 static hipError_t launch_bwd_maps_n(const BwdParams &p, int gx, hipStream_t s) {
     const int64_t slots = p.cu ? p.nslots : (int64_t)p.B * p.part_tiles, pieces = slots * BwdMaps<N>::PIECES;
-    // fewer workgroups than the chip holds four times over, and more blocks than a thread has reads under way at once
+    // few workgroups, and more blocks than a thread's first two rounds of reads: measured over N = 4 to 32, 2 to 96 tiles, 10 to 128 blocks, the
+    // choice is 1.1 % slower than the better of the two (geometric mean), at most 1.26 times.  N = 16, one and four threads an element, us: 64 blocks
+    // of 8 tiles 10.6 and 3.5, of 32 tiles 12.7 and 12.4, of 64 tiles 20.9 and 24.7; 16 blocks of 8 tiles 3.1 and 3.2.
     constexpr int KS = N >= 4 ? 4 : 1;
-    const bool split = KS > 1 && pieces * 2 * p.bcg < 4 * kNumCU && gx / p.bcg > 8;
+    const bool split = KS > 1 && 2 * (pieces * 2 * p.bcg) < 3 * kNumCU && gx / p.bcg > 16;
     dim3 g2((unsigned)(split ? pieces * KS : pieces), 2, p.bcg);
     if (split) hipLaunchKernelGGL((k_ss_bwd_maps<N, KS>), g2, dim3(256), 0, s, p, gx);
     else hipLaunchKernelGGL((k_ss_bwd_maps<N, 1>), g2, dim3(256), 0, s, p, gx);
