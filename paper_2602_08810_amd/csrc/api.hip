@@ -194,6 +194,17 @@ size_t bwd_order_bytes(const lrnnx_ss_bwd_args *a, int nchunks) {
     return a->cu_seqlens && nchunks == 1 && a->B > kMaxRanked && a->B <= kMaxOrdered ? sizeof(int) * (size_t)a->B : 0;
 }
 
+// every row's offset b * stride_b + d * stride_d, and both products, within 31 bits
+template <typename Args> int step_rows_narrow(const Args *a) {
+    auto fits = [&](int64_t sb, int64_t sd) {
+        const __int128 most = (__int128)1 << 31, nb = a->B - 1, nd = a->D - 1;
+        const __int128 ob = nb * (sb < 0 ? -(__int128)sb : sb), od = nd * (sd < 0 ? -(__int128)sd : sd);
+        return ob + od < most && (sb < 0 ? -(__int128)sb : sb) < most && (sd < 0 ? -(__int128)sd : sd) < most;
+    };
+    return fits(a->u_stride_b, a->u_stride_d) && fits(a->delta_stride_b, a->delta_stride_d) && fits(a->y_stride_b, a->y_stride_d) &&
+           (!a->z || fits(a->z_stride_b, a->z_stride_d));
+}
+
 // The real and the complex backward entry points take the same per-row tensors (same field names in both argument
 // structs and both parameter blocks): checks and marshalling are written once.
 template <typename Args>
@@ -886,7 +897,7 @@ int lrnnx_selective_step(const lrnnx_ss_step_args *a) {
     if (!aligned16(a->x) || !aligned16(a->A) || !aligned16(a->Bm) || !aligned16(a->Cm)) return LRNNX_ERR_INVALID_ARG;
     StepParams p{};
     p.B = a->B; p.D = a->D; p.N = a->N; p.softplus = a->delta_softplus ? 1 : 0;
-    p.bcg = bcg; p.dpg = a->D / bcg;
+    p.bcg = bcg; p.narrow = step_rows_narrow(a); p.by_D = Divider((unsigned)a->D); p.by_dpg = Divider((unsigned)(a->D / bcg));
     p.x = a->x; p.u = a->u; p.delta = a->delta; p.z = a->z; p.Bm = a->Bm; p.Cm = a->Cm; p.y = a->y;
     p.u_sb = a->u_stride_b; p.u_sd = a->u_stride_d; p.dl_sb = a->delta_stride_b; p.dl_sd = a->delta_stride_d;
     p.z_sb = a->z_stride_b; p.z_sd = a->z_stride_d; p.y_sb = a->y_stride_b; p.y_sd = a->y_stride_d;
@@ -908,7 +919,7 @@ int lrnnx_selective_step_complex(const lrnnx_ss_step_complex_args *a) {
     if (!aligned16(a->x) || !aligned16(a->A) || !aligned16(a->Bm) || !aligned16(a->Cm)) return LRNNX_ERR_INVALID_ARG;
     CStepParams p{};
     p.B = a->B; p.D = a->D; p.N = a->N; p.softplus = a->delta_softplus ? 1 : 0;
-    p.bcg = bcg; p.dpg = a->D / bcg;
+    p.bcg = bcg; p.narrow = step_rows_narrow(a); p.by_D = Divider((unsigned)a->D); p.by_dpg = Divider((unsigned)(a->D / bcg));
     p.x = reinterpret_cast<float2 *>(a->x); p.u = a->u; p.delta = a->delta; p.z = a->z; p.Bm = a->Bm; p.Cm = a->Cm; p.y = a->y;
     p.u_sb = a->u_stride_b; p.u_sd = a->u_stride_d; p.dl_sb = a->delta_stride_b; p.dl_sd = a->delta_stride_d;
     p.z_sb = a->z_stride_b; p.z_sd = a->z_stride_d; p.y_sb = a->y_stride_b; p.y_sd = a->y_stride_d;

@@ -189,10 +189,28 @@ struct ColumnParams {
     void *x, *x_last;
 };
 
+// Division of a 32-bit number by one that the host knows, in five instructions (Granlund and Montgomery 1994: a multiplication and two shifts)
+struct Divider {
+    unsigned m = 0, s1 = 0, s2 = 0;
+    Divider() = default;
+    explicit Divider(unsigned d) {             // d >= 1
+        unsigned l = 0;
+        while (l < 32 && (1ull << l) < d) ++l;
+        m = (unsigned)(((1ull << 32) * ((1ull << l) - d)) / d + 1);
+        s1 = l < 1 ? l : 1; s2 = l < 1 ? 0 : l - 1;
+    }
+    __host__ __device__ unsigned operator()(unsigned n) const {
+        const unsigned t = (unsigned)(((uint64_t)m * n) >> 32);
+        return (t + ((n - t) >> s1)) >> s2;
+    }
+};
+
 struct StepParams {
     int B, D, N;
     int softplus;
-    int bcg, dpg;                              // number of Bm/Cm groups and channels per group
+    int bcg;                                   // number of Bm/Cm groups
+    int narrow;                                // the rows' offsets (elements) fit 31 bits
+    Divider by_D, by_dpg;                      // channels, channels per group
     float *x;                                  // [B,D,N] in/out
     const void *u, *delta, *z, *Bm, *Cm;       // u, delta, z: [B,D] with strides; Bm, Cm: [B,N]
     void *y;
@@ -203,7 +221,9 @@ struct StepParams {
 struct CStepParams {
     int B, D, N;
     int softplus;
-    int bcg, dpg;                              // number of Bm/Cm groups and channels per group
+    int bcg;                                   // number of Bm/Cm groups
+    int narrow;                                // the rows' offsets (elements) fit 31 bits
+    Divider by_D, by_dpg;                      // channels, channels per group
     float2 *x;                                 // [B,D,N] complex, in/out
     const void *u, *delta, *z, *Bm, *Cm;       // u, delta, z: [B,D] with strides; Bm, Cm: [B,N] complex in the I/O type
     void *y;
