@@ -1003,7 +1003,10 @@ static hipError_t launch_bwd_maps_n(const BwdParams &p, int gx, hipStream_t s) {
     // choice is 1.1 % slower than the better of the two (geometric mean), at most 1.26 times.  N = 16, one and four threads an element, us: 64 blocks
     // of 8 tiles 10.6 and 3.5, of 32 tiles 12.7 and 12.4, of 64 tiles 20.9 and 24.7; 16 blocks of 8 tiles 3.1 and 3.2.
     constexpr int KS = N >= 4 ? 4 : 1;
-    const bool split = KS > 1 && 2 * (pieces * 2 * p.bcg) < 3 * kNumCU && gx / p.bcg > 16;
+    // A packed batch has slots without a tile, whose workgroups end at once and leave uneven numbers on the CUs: up to three a CU four threads are the
+    // faster (N = 16, D = 1536, one and four, us: 8 x 2048 steps 29.1 and 25.7, 24 of 16384 in all 27.2 and 26.8); with 32 states not.
+    const int64_t wgs = pieces * 2 * p.bcg;
+    const bool split = KS > 1 && gx / p.bcg > 16 && (2 * wgs < 3 * kNumCU || (p.cu && N <= 16 && wgs < 3 * kNumCU));
     dim3 g2((unsigned)(split ? pieces * KS : pieces), 2, p.bcg);
     if (split) hipLaunchKernelGGL((k_ss_bwd_maps<N, KS>), g2, dim3(256), 0, s, p, gx);
     else hipLaunchKernelGGL((k_ss_bwd_maps<N, 1>), g2, dim3(256), 0, s, p, gx);
