@@ -175,8 +175,7 @@ void set_bwd_shape(BwdParams &p, const lrnnx_ss_bwd_args *a, const BwdPlan &pl) 
     p.nchunks = pl.nchunks;
     p.tiles_per_chunk = pl.tiles_per_chunk;
     if (!a->cu_seqlens || pl.nchunks > 1) return;
-    bwd_packed_shape(a->B, a->D, p.dpg, a->L, a->max_seqlen, bwd_channels_per_group(a->B * p.bcg, p.dpg, a->N, a->L, true),
-                     bwd_places(a->N), &p.G, &p.wcap, &p.gmin);
+    bwd_packed_shape(a->B, a->D, p.bcg, a->N, a->L, a->max_seqlen, &p.G, &p.wcap, &p.gmin);
     // tile sums a little over their scratch: up to half as many channels again, if that makes them fit (see kBwdSumsCap)
     int &least = p.wcap > 0 ? p.gmin : p.G;
     const int planned = least, most = planned + planned / 2 < kBwdMaxG ? planned + planned / 2 : kBwdMaxG;
@@ -525,9 +524,7 @@ int lrnnx_selective_scan_bwd_complex(const lrnnx_ss_bwd_complex_args *a) {
     p.nchunks = pl.nchunks;
     p.tiles_per_chunk = pl.tiles_per_chunk;
     size_t used = carry_off;                       // bytes of the workspace taken so far
-    if (cu && pl.nchunks == 1)
-        bwd_packed_shape(a->B, a->D, p.dpg, a->L, a->max_seqlen, cbwd_channels_per_group(a->B * bcg, a->D / bcg, a->N, true),
-                         cbwd_places(a->N), &p.G, &p.wcap, &p.gmin);
+    if (cu && pl.nchunks == 1) cbwd_packed_shape(a->B, a->D, bcg, a->N, a->L, a->max_seqlen, &p.G, &p.wcap, &p.gmin);
     if (pl.nchunks > 1) {
         p.ws_P = reinterpret_cast<float2 *>(static_cast<char *>(a->workspace) + carry_off);
         p.ws_Q = p.ws_P + (size_t)a->B * a->D * p.nchunks * a->N;

@@ -131,11 +131,15 @@ constexpr int kBwdMinG = 4, kBwdMaxG = 128;   // channels of a workgroup (the mo
 // chunks of the time axis instead (plan_time_chunks), and a packed launch that needs a little more than this takes up to
 // half as many channels again (24 sequences, 32768 steps, 128 channels, N = 32: 400 us, with atomics 759).
 constexpr size_t kBwdSumsCap = (size_t)512 << 20;
-// launch shape of a packed batch of B sequences on L steps, D channels, whose longest has max_seqlen steps (0: not
-// known, nothing changes): *G comes in as the channels per workgroup of a batch of unknown lengths and may be raised
-// to Gbal, those of a batch [B,D,L] of equal lengths; else cap and fewest channels as in BwdParams.  `places` =
-// workgroups the chip holds at once.
-void bwd_packed_shape(int B, int D, int dpg, int64_t L, int64_t max_seqlen, int Gbal, int places, int *G, int *wcap, int *gmin);
+constexpr int kMaxGc = 64;           // the most channels of a workgroup of the complex pass: it sizes that kernel's tables in LDS
+// launch shape of a packed batch of B sequences on L steps, D channels in bcg groups, whose longest has max_seqlen steps (0: not
+// known, nothing changes): *G comes in as the channels per workgroup of a batch of unknown lengths and may be raised, never
+// past what the kernel's tables hold; else cap and fewest channels as in BwdParams.  Real and complex.
+void bwd_packed_shape(int B, int D, int bcg, int N, int64_t L, int64_t max_seqlen, int *G, int *wcap, int *gmin);
+void cbwd_packed_shape(int B, int D, int bcg, int N, int64_t L, int64_t max_seqlen, int *G, int *wcap, int *gmin);
+// What the two have in common.  Gbal: channels per workgroup of a batch [B,D,L] of equal lengths, `most`: those that the kernel's
+// tables hold, `places`: workgroups the chip holds at once.
+void packed_shape(int B, int D, int dpg, int64_t L, int64_t max_seqlen, int Gbal, int most, int places, int *G, int *wcap, int *gmin);
 constexpr int kMaxRanked = 64;       // sequences that a workgroup ranks itself (one a lane)
 // Whether a forward launch of `wgs` workgroups with 16 lanes a channel, three of which a compute unit holds, ranks its sequences.  Where all run at
 // once their order changes nothing, and a workgroup with little work would pay for it: 60 sequences of 68 steps, 331 channels, N = 4,

@@ -993,6 +993,7 @@ hipError_t launch_ss_bwd_f32(const BwdParams &p, int disc, hipStream_t s);
 hipError_t launch_ss_bwd_f32(const BwdParams &p, int disc, hipStream_t s) { return launch_bwd_io<float>(p, disc, s); }
 #else
 hipError_t launch_ss_bwd(const BwdParams &p, int io_dtype, int disc, hipStream_t s) {
+    if (p.G > kBwdMaxG) return hipErrorInvalidValue;       // (more channels than the tables in LDS hold)
     return io_dtype == 1 ? launch_bwd_io<bf16_t>(p, disc, s) : launch_ss_bwd_f32(p, disc, s);
 }
 
@@ -1055,7 +1056,7 @@ int bwd_channels_per_group(int B, int D, int N, int64_t, bool balanced) {
     return whole_passes(channels_for(B, D, bwd_places(N), balanced));
 }
 
-void bwd_packed_shape(int B, int D, int dpg, int64_t L, int64_t max_seqlen, int Gbal, int places, int *G, int *wcap, int *gmin) {
+void packed_shape(int B, int D, int dpg, int64_t L, int64_t max_seqlen, int Gbal, int most, int places, int *G, int *wcap, int *gmin) {
     *wcap = 0; *gmin = *G;
     if (max_seqlen <= 0) return;
     // what each place of the chip gets at perfect balance, in channel-tiles: D channels x the tiles of all sequences
@@ -1071,16 +1072,19 @@ void bwd_packed_shape(int B, int D, int dpg, int64_t L, int64_t max_seqlen, int 
     // many: as long as the longest sequence's workgroups are a fifth below a place's share and there are two workgroups for each
     // place, more channels each cost no balance, and the tile sums and what is paid per tile and workgroup become less (24 sequences,
     // 16384 steps, 1536 channels, N = 16, bf16: 18 -> 26 channels, training step 531 -> 512 us).
-    const int64_t most = (int64_t)B * D / (2 * places);
-    const int64_t wide = 0.8 * fit < (double)most ? (int64_t)(0.8 * fit) : most;
+    const int64_t two = (int64_t)B * D / (2 * places);
+    const int64_t wide = 0.8 * fit < (double)two ? (int64_t)(0.8 * fit) : two;
     if (fit >= (double)*G && wide > *G) {
-        const int64_t g = wide < kBwdMaxG ? wide : kBwdMaxG, blocks = (dpg + g - 1) / g;
+        const int64_t g = wide < most ? wide : most, blocks = (dpg + g - 1) / g;
         const int even = (int)((dpg + blocks - 1) / blocks + 1) & ~1;
         if (even > *G) *G = *gmin = even;
     }
     if (fit >= (double)*G || *G <= kBwdMinG) return;    // the longest sequence is no longer than a fair share: no cap
     *wcap = cap < 1.0 ? 1 : (cap > 1e9 ? 1000000000 : (int)cap);
     *gmin = fit < (double)kBwdMinG ? kBwdMinG : (int)fit & ~1;
+}
+void bwd_packed_shape(int B, int D, int bcg, int N, int64_t L, int64_t max_seqlen, int *G, int *wcap, int *gmin) {
+    packed_shape(B, D, D / bcg, L, max_seqlen, bwd_channels_per_group(B * bcg, D / bcg, N, L, true), kBwdMaxG, bwd_places(N), G, wcap, gmin);
 }
 
 // launch shape incl. the chunked path for few rows and long sequences (selective_bwd_carry.hip)

@@ -36,8 +36,6 @@
 
 namespace lrnnx {
 
-constexpr int kMaxGc = 64;
-
 // Geometry of a workgroup for N states.
 template <int N> struct CBwdGeom {
     static constexpr int NS = N >= 2 ? 2 : 1;        // states of a wavefront
@@ -840,6 +838,7 @@ hipError_t launch_ss_cbwd_f32(const CBwdParams &p, int disc, hipStream_t s);
 hipError_t launch_ss_cbwd_f32(const CBwdParams &p, int disc, hipStream_t s) { return launch_cbwd_io<float>(p, disc, s); }
 #else
 hipError_t launch_ss_cbwd(const CBwdParams &p, int io_dtype, int disc, hipStream_t s) {
+    if (p.G > kMaxGc) return hipErrorInvalidValue;         // (more channels than the tables in LDS hold)
     return io_dtype == 1 ? launch_cbwd_io<bf16_t>(p, disc, s) : launch_ss_cbwd_f32(p, disc, s);
 }
 
@@ -865,6 +864,9 @@ int cbwd_channels_per_group(int B, int D, int N, bool balanced) {
     const int64_t groups = (D + G - 1) / G;
     G = (D + groups - 1) / groups;                     // even split
     return (int)(G + 1) / 2 * 2;                       // (walked in pairs)
+}
+void cbwd_packed_shape(int B, int D, int bcg, int N, int64_t L, int64_t max_seqlen, int *G, int *wcap, int *gmin) {
+    packed_shape(B, D, D / bcg, L, max_seqlen, cbwd_channels_per_group(B * bcg, D / bcg, N, true), kMaxGc, cbwd_places(N), G, wcap, gmin);
 }
 
 // Whether the tile sums of dBm and dCm, which take `bytes`, go through the workspace and a second launch instead of float atomics.

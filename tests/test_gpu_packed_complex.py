@@ -111,6 +111,13 @@ def test_packed_complex_one_long_sequence_with_max_seqlen(api, oracle, hint):
     _check(api, oracle, 256, 16, lengths, "bf16", seed=42, max_seqlen=hint)
 
 
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+def test_packed_complex_as_many_channels_as_a_workgroup_holds(api, oracle, io):
+    """32 short sequences of 2048 channels: the balance alone would take 128 channels a workgroup, the kernel's tables hold 64."""
+    lengths = tuple((37 * i) % 229 + 1 for i in range(31)) + (256,)
+    _check(api, oracle, 2048, 16, lengths, io, seed=43, max_seqlen=256)
+
+
 @pytest.mark.parametrize("hint", [None, 5000, 1000])
 def test_packed_complex_backward_in_chunks(api, oracle, hint):
     """The chunked backward on a packed batch, chunks planned for the longest length the caller names, for the whole
