@@ -17,7 +17,6 @@ struct FwdParams {
     int bcg, dpg;            // number of Bm/Cm groups and channels per group (D = bcg * dpg)
     const int64_t *cu;       // packed variable-length mode: [B+1] sequence boundaries on the packed axis of L steps
     int64_t nslots;          // packed mode: checkpoint slots per channel
-    bool ranked;             // packed mode: blockIdx.y counts from the longest sequence down (see seq_span)
     int nchunks;
     int64_t tiles_per_chunk;
     const void *u, *delta, *z;
@@ -37,7 +36,6 @@ struct CFwdParams {
     int bcg, dpg;            // number of Bm/Cm groups and channels per group (D = bcg * dpg)
     const int64_t *cu;       // packed variable-length mode: [B+1] sequence boundaries on the packed axis of L steps
     int64_t nslots;          // packed mode: checkpoint slots per channel
-    bool ranked;             // as in FwdParams
     const void *u, *delta, *z;
     void *y;
     int64_t u_sb, u_sd, dl_sb, dl_sd, z_sb, z_sd, y_sb, y_sd;

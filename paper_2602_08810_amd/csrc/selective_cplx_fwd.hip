@@ -76,7 +76,8 @@ template <int LPC, int T> struct CFwdGeom {
 };
 
 // Wavefronts that share a SIMD: three with 16 lanes per channel (168 registers), four with 64.
-template <typename IO, int N, int DISC, bool WANT_Y, int LPC, int T>
+// RANKED: a packed batch whose workgroups rank the sequences (ranked_sequences)
+template <typename IO, int N, int DISC, bool WANT_Y, int LPC, int T, bool RANKED>
 __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) void k_ss_cfwd(const CFwdParams p) {
     using CW = typename cword<IO>::type;
     using GE = CFwdGeom<LPC, T>;
@@ -109,7 +110,7 @@ __global__ __launch_bounds__((CFwdGeom<LPC, T>::W * 64), (LPC == 16 ? 3 : 4)) vo
     constexpr bool BRIEF = LPC == 64 && T == 4;      // see row()
     std::conditional_t<BRIEF, unsigned, int64_t> bs = b;
     if (p.cu) {
-        const SeqSpan q = seq_span_fwd<LPC == 16>(p.cu, p.B, p.L, b, p.ranked);
+        const SeqSpan q = seq_span_fwd<RANKED>(p.cu, p.B, p.L, b);
         b = q.b; toff = q.toff; L = q.L; bs = 0;
     }
     const int64_t ntiles = (L + TILE - 1) / TILE;
@@ -452,11 +453,15 @@ static hipError_t launch_cfwd_lanes(CFwdParams p, hipStream_t s) {
     if (p.nchunks == 1) p.tiles_per_chunk = (p.L + GE::TILE - 1) / GE::TILE;
     // the aggregate launch skips the last chunk: nobody needs its pair
     const dim3 grid(p.bcg * ((p.dpg + GE::CH - 1) / GE::CH), p.B, p.mode == MODE_AGG ? p.nchunks - 1 : p.nchunks), block(GE::W * 64);
+    auto launch = [&](auto RANKED) {
+        if (p.mode != MODE_AGG && p.y) hipLaunchKernelGGL((k_ss_cfwd<IO, N, DISC, true, LPC, T, RANKED>), grid, block, 0, s, p);
+        else hipLaunchKernelGGL((k_ss_cfwd<IO, N, DISC, false, LPC, T, RANKED>), grid, block, 0, s, p);
+        return hipGetLastError();
+    };
     // packed batches of more workgroups than the chip holds: longest sequences first
-    p.ranked = LPC == 16 && ranked_sequences(p.cu, p.B, N, (int64_t)grid.x * grid.y);
-    if (p.mode != MODE_AGG && p.y) hipLaunchKernelGGL((k_ss_cfwd<IO, N, DISC, true, LPC, T>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((k_ss_cfwd<IO, N, DISC, false, LPC, T>), grid, block, 0, s, p);
-    return hipGetLastError();
+    if constexpr (LPC == 16 && N >= 8)
+        if (ranked_sequences(p.cu, p.B, N, (int64_t)grid.x * grid.y)) return launch(std::true_type{});
+    return launch(std::false_type{});
 }
 template <typename IO, int N, int DISC>
 static hipError_t launch_cfwd_n(const CFwdParams &p, hipStream_t s) {

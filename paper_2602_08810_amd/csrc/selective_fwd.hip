@@ -96,7 +96,8 @@ template <int LPC, int T> struct FwdGeom {
 // Workgroups that share a compute unit: three of four wavefronts with 16 lanes per channel (168 registers, three wavefronts a
 // SIMD); with 64 lanes four of four wavefronts (4 steps) or two of eight (8 steps: 75 KB of LDS each), at 128 registers four a
 // SIMD; one of eight with 16 steps, whose staged tile takes more than half of the LDS.
-template <typename IO, int N, int DISC, bool WANT_Y, bool CKPT, int LPC, int TM>
+// RANKED: a packed batch whose workgroups rank the sequences (ranked_sequences)
+template <typename IO, int N, int DISC, bool WANT_Y, bool CKPT, int LPC, int TM, bool RANKED>
 __global__ __launch_bounds__((FwdGeom<LPC, TM>::W * 64), (TM == 16 ? (LPC == 16 ? 3 : 2) : 4)) void k_ss_fwd(const FwdParams p) {
     using GE = FwdGeom<LPC, TM>;
     constexpr int W = GE::W, CPW = GE::CPW, CH = GE::CH, TILE = GE::TILE, NT = W * 64;
@@ -137,7 +138,7 @@ __global__ __launch_bounds__((FwdGeom<LPC, TM>::W * 64), (TM == 16 ? (LPC == 16 
     // packed variable-length mode (p.cu != nullptr, see seq_span): I/O rows have no batch stride, the maps are [G, p.L, N]
     int64_t L = p.L, toff = 0, bs = b;
     if (p.cu) {
-        const SeqSpan q = seq_span_fwd<LPC == 16>(p.cu, p.B, p.L, b, p.ranked);
+        const SeqSpan q = seq_span_fwd<RANKED>(p.cu, p.B, p.L, b);
         b = q.b; toff = q.toff; L = q.L; bs = 0;
     }
     const int64_t ntiles = (L + TILE - 1) / TILE;
@@ -573,16 +574,20 @@ static hipError_t launch_fwd_lanes(FwdParams p, hipStream_t s) {
     // tiles_per_chunk counts tiles of 256 steps; a single pass is one chunk whatever the tile
     if (p.nchunks == 1) p.tiles_per_chunk = (p.L + GE::TILE - 1) / GE::TILE;
     dim3 grid(p.bcg * ((p.dpg + GE::CH - 1) / GE::CH), p.B, p.mode == MODE_AGG ? p.nchunks - 1 : p.nchunks);
-    // packed batches of more workgroups than the chip holds: longest sequences first
-    p.ranked = LPC == 16 && ranked_sequences(p.cu, p.B, N, (int64_t)grid.x * grid.y);
     const bool want_y = (p.mode == MODE_FULL || p.mode == MODE_APPLY);
     const dim3 block(GE::W * 64);
-    if (want_y && p.ckpt) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, true, true, LPC, T>), grid, block, 0, s, p);
-    else if (want_y) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, true, false, LPC, T>), grid, block, 0, s, p);
-    else if (p.ckpt) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, false, true, LPC, T>), grid, block, 0, s, p);
-    else if constexpr (LPC == 16) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, false, false, LPC, T>), grid, block, 0, s, p);
-    else return hipErrorInvalidValue;                    // the chunk-carry path takes 16 lanes per channel
-    return hipGetLastError();
+    auto launch = [&](auto RANKED) {
+        if (want_y && p.ckpt) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, true, true, LPC, T, RANKED>), grid, block, 0, s, p);
+        else if (want_y) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, true, false, LPC, T, RANKED>), grid, block, 0, s, p);
+        else if (p.ckpt) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, false, true, LPC, T, RANKED>), grid, block, 0, s, p);
+        else if constexpr (LPC == 16 && !RANKED) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, false, false, LPC, T, RANKED>), grid, block, 0, s, p);
+        else return hipErrorInvalidValue;                // the chunk-carry path takes 16 lanes per channel, and no packed batches
+        return hipGetLastError();
+    };
+    // packed batches of more workgroups than the chip holds: longest sequences first
+    if constexpr (LPC == 16 && N >= 8)
+        if (ranked_sequences(p.cu, p.B, N, (int64_t)grid.x * grid.y)) return launch(std::true_type{});
+    return launch(std::false_type{});
 }
 
 template <typename IO, int N, int DISC>
