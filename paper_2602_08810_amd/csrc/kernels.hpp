@@ -136,8 +136,8 @@ constexpr int kMaxGc = 64;           // the most channels of a workgroup of the 
 void bwd_packed_shape(int B, int D, int bcg, int N, int64_t L, int64_t max_seqlen, int *G, int *wcap, int *gmin);
 void cbwd_packed_shape(int B, int D, int bcg, int N, int64_t L, int64_t max_seqlen, int *G, int *wcap, int *gmin);
 // What the two have in common.  Gbal: channels per workgroup of a batch [B,D,L] of equal lengths, `most`: those that the kernel's
-// tables hold, `places`: workgroups the chip holds at once.
-void packed_shape(int B, int D, int dpg, int64_t L, int64_t max_seqlen, int Gbal, int most, int places, int *G, int *wcap, int *gmin);
+// tables hold, `places`: workgroups the chip holds at once, `gain`: by how much more channels a batch of unequal lengths is worth another shape.
+void packed_shape(int B, int D, int dpg, int64_t L, int64_t max_seqlen, int Gbal, int most, double gain, int places, int *G, int *wcap, int *gmin);
 constexpr int kMaxRanked = 64;       // sequences that a workgroup ranks itself (one a lane)
 // Whether a forward launch of `wgs` workgroups with 16 lanes a channel, three of which a compute unit holds, ranks its sequences.  Where all run at
 // once their order changes nothing, and a workgroup with little work would pay for it: 60 sequences of 68 steps, 331 channels, N = 4,

@@ -1004,8 +1004,9 @@ static hipError_t launch_bwd_maps_n(const BwdParams &p, int gx, hipStream_t s) {
     // choice is 1.1 % slower than the better of the two (geometric mean), at most 1.26 times.  N = 16, one and four threads an element, us: 64 blocks
     // of 8 tiles 10.6 and 3.5, of 32 tiles 12.7 and 12.4, of 64 tiles 20.9 and 24.7; 16 blocks of 8 tiles 3.1 and 3.2.
     constexpr int KS = N >= 4 ? 4 : 1;
-    // A packed batch has slots without a tile, whose workgroups end at once and leave uneven numbers on the CUs: up to three a CU four threads are the
-    // faster (N = 16, D = 1536, one and four, us: 8 x 2048 steps 29.1 and 25.7, 24 of 16384 in all 27.2 and 26.8); with 32 states not.
+    // A packed batch has slots without a tile, whose workgroups end at once and leave uneven numbers on the CUs: up to three a CU four threads can be the
+    // faster (N = 16, D = 1536, one and four, us: 8 x 2048 steps 29.1 and 25.7, 24 of 16384 in all 27.2 and 26.8), with 32 states they are not.  Over 107
+    // packed backward calls in that range (N = 4 to 16, real and complex, 256 to 4096 channels) the two are even: 1.000, 0.967 to 1.029.
     const int64_t wgs = pieces * 2 * p.bcg;
     const bool split = KS > 1 && gx / p.bcg > 16 && (2 * wgs < 3 * kNumCU || (p.cu && N <= 16 && wgs < 3 * kNumCU));
     dim3 g2((unsigned)(split ? pieces * KS : pieces), 2, p.bcg);
@@ -1056,7 +1057,7 @@ int bwd_channels_per_group(int B, int D, int N, int64_t, bool balanced) {
     return whole_passes(channels_for(B, D, bwd_places(N), balanced));
 }
 
-void packed_shape(int B, int D, int dpg, int64_t L, int64_t max_seqlen, int Gbal, int most, int places, int *G, int *wcap, int *gmin) {
+void packed_shape(int B, int D, int dpg, int64_t L, int64_t max_seqlen, int Gbal, int most, double gain, int places, int *G, int *wcap, int *gmin) {
     *wcap = 0; *gmin = *G;
     if (max_seqlen <= 0) return;
     // what each place of the chip gets at perfect balance, in channel-tiles: D channels x the tiles of all sequences
@@ -1071,20 +1072,24 @@ void packed_shape(int B, int D, int dpg, int64_t L, int64_t max_seqlen, int Gbal
     // Otherwise the workgroups start longest first, and what evens the launch out is that the last ones are short, not that there are
     // many: as long as the longest sequence's workgroups are a fifth below a place's share and there are two workgroups for each
     // place, more channels each cost no balance, and the tile sums and what is paid per tile and workgroup become less (24 sequences,
-    // 16384 steps, 1536 channels, N = 16, bf16: 18 -> 26 channels, training step 531 -> 512 us).
+    // 16384 steps, 1536 channels, N = 16, bf16: 18 -> 26 channels, training step 531 -> 512 us).  Backward calls that this widens, bf16, 3 to 96
+    // sequences of 4096 to 32768 steps in all, 256 to 4096 channels, lengths from nearly equal to log-normal with sigma 1.2, time after / before: real
+    // pass, 130 calls with N = 16 and 32, 0.915 (geometric mean; 0.58 to 1.12); with fewer states the launch is as wide already.
+    // Complex pass, 90 calls with N = 4 to 16, 0.976 (0.82 to 1.15), and a third more channels or nothing (`gain`) 0.976 with half of the losses
+    // above 5 %; the real pass loses with such a bound (0.922).
     const int64_t two = (int64_t)B * D / (2 * places);
     const int64_t wide = 0.8 * fit < (double)two ? (int64_t)(0.8 * fit) : two;
     if (fit >= (double)*G && wide > *G) {
         const int64_t g = wide < most ? wide : most, blocks = (dpg + g - 1) / g;
         const int even = (int)((dpg + blocks - 1) / blocks + 1) & ~1;
-        if (even > *G) *G = *gmin = even;
+        if (even > *G && even >= gain * *G) *G = *gmin = even;
     }
     if (fit >= (double)*G || *G <= kBwdMinG) return;    // the longest sequence is no longer than a fair share: no cap
     *wcap = cap < 1.0 ? 1 : (cap > 1e9 ? 1000000000 : (int)cap);
     *gmin = fit < (double)kBwdMinG ? kBwdMinG : (int)fit & ~1;
 }
 void bwd_packed_shape(int B, int D, int bcg, int N, int64_t L, int64_t max_seqlen, int *G, int *wcap, int *gmin) {
-    packed_shape(B, D, D / bcg, L, max_seqlen, bwd_channels_per_group(B * bcg, D / bcg, N, L, true), kBwdMaxG, bwd_places(N), G, wcap, gmin);
+    packed_shape(B, D, D / bcg, L, max_seqlen, bwd_channels_per_group(B * bcg, D / bcg, N, L, true), kBwdMaxG, 1.0, bwd_places(N), G, wcap, gmin);
 }
 
 // launch shape incl. the chunked path for few rows and long sequences (selective_bwd_carry.hip)

@@ -866,7 +866,7 @@ int cbwd_channels_per_group(int B, int D, int N, bool balanced) {
     return (int)(G + 1) / 2 * 2;                       // (walked in pairs)
 }
 void cbwd_packed_shape(int B, int D, int bcg, int N, int64_t L, int64_t max_seqlen, int *G, int *wcap, int *gmin) {
-    packed_shape(B, D, D / bcg, L, max_seqlen, cbwd_channels_per_group(B * bcg, D / bcg, N, true), kMaxGc, cbwd_places(N), G, wcap, gmin);
+    packed_shape(B, D, D / bcg, L, max_seqlen, cbwd_channels_per_group(B * bcg, D / bcg, N, true), kMaxGc, 1.3, cbwd_places(N), G, wcap, gmin);
 }
 
 // Whether the tile sums of dBm and dCm, which take `bytes`, go through the workspace and a second launch instead of float atomics.

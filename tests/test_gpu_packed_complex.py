@@ -118,6 +118,11 @@ def test_packed_complex_as_many_channels_as_a_workgroup_holds(api, oracle, io):
     _check(api, oracle, 2048, 16, lengths, io, seed=43, max_seqlen=256)
 
 
+def test_packed_complex_more_channels_with_max_seqlen(api, oracle):
+    """63 sequences of up to 131 steps: 16 channels a workgroup with the longest length known, 8 without."""
+    _check(api, oracle, 256, 8, tuple((37 * i) % 131 + 1 for i in range(63)), "bf16", seed=44, max_seqlen=131)
+
+
 @pytest.mark.parametrize("hint", [None, 5000, 1000])
 def test_packed_complex_backward_in_chunks(api, oracle, hint):
     """The chunked backward on a packed batch, chunks planned for the longest length the caller names, for the whole
