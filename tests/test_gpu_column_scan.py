@@ -34,12 +34,7 @@ def _reference(a, b, x0):
     return out
 
 
-# columns of a workgroup x steps of its tile: LTI 4 x 1024 and 16 x 128, real 8 x 512, 16 x 128 and 32 x 128 (complex: the chained scan)
-@pytest.mark.parametrize("kind", ["lti", "real", "complex"])
-@pytest.mark.parametrize("B,P,L", [(1, 1, 1), (2, 3, 7), (1, 4, 8), (3, 5, 9), (2, 15, 127), (1, 16, 128), (2, 17, 129), (8, 208, 92), (5, 31, 511),
-                                   (2, 8, 512), (3, 9, 513), (1, 7, 1023), (2, 4, 1024), (1, 6, 1025), (2, 13, 2050), (40, 70, 130),
-                                   (8, 1024, 2048), (4, 256, 4096)])
-def test_edges(api, kind, B, P, L):
+def _check(api, kind, B, P, L):
     g = torch.Generator(device="cuda").manual_seed(B * 1000003 + P * 1009 + L)
     rand = lambda *s: torch.rand(s, generator=g, device="cuda")
     randn = lambda *s: torch.randn(s, generator=g, device="cuda")
@@ -56,6 +51,23 @@ def test_edges(api, kind, B, P, L):
         own = b.clone()
         assert scan(a, own, x0=x0, out=own) is own       # in place
         assert torch.equal(own, x)
+
+
+# around whole tiles and blocks of columns; the longer ones of real coefficients, and complex ones, take the chained scan
+@pytest.mark.parametrize("kind", ["lti", "real", "complex"])
+@pytest.mark.parametrize("B,P,L", [(1, 1, 1), (2, 3, 7), (1, 4, 8), (3, 5, 9), (2, 15, 127), (1, 16, 128), (2, 17, 129), (8, 208, 92), (5, 31, 511),
+                                   (2, 8, 512), (3, 9, 513), (1, 7, 1023), (2, 4, 1024), (1, 6, 1025), (2, 13, 2050), (40, 70, 130),
+                                   (8, 1024, 2048), (4, 256, 4096)])
+def test_edges(api, kind, B, P, L):
+    _check(api, kind, B, P, L)
+
+
+# three tiles or more in every shape, the last one short, the last block of columns not full
+@pytest.mark.parametrize("kind,shape,B,P,L", [("lti", 1, 1, 67, 3075), ("lti", 2, 4, 999, 700), ("real", 1, 1, 1999, 1025), ("real", 1, 2, 2001, 1537),
+                                              ("real", 2, 8, 699, 389), ("real", 3, 16, 1009, 300)])
+def test_shapes(api, kind, shape, B, P, L):
+    assert _shape(api, kind, B, P, L) == shape
+    _check(api, kind, B, P, L)
 
 
 # |coefficient| > 1: the powers over a lane's pieces, a wavefront and a tile grow past float32's range (and double's) where the states, of an
