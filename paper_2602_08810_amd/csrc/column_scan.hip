@@ -31,7 +31,8 @@ __global__ __launch_bounds__(W * 64, 4) void k_column_scan(const ColumnParams p)
     // chained scan's 32, and in single precision the states' error (2-norm, against 64 bits) was 4.3e-8 where that scan's is 4.0e-8.
     // Products of many coefficients can leave the range of the states, which may be zero or tiny where they do (a lane's pieces begin
     // up to 120 steps after the wavefront's first).  Powers of lambda beyond single precision are taken in double as well, and what is beyond
-    // that (any state but zero is infinite then) never meets a zero: a power is kept finite, a product of coefficients not applied to it.
+    // that (any state but zero is infinite then) never meets a zero, a state's or a coefficient's that ends what came before: a power is kept finite,
+    // a product of coefficients not applied to it.
     using ED = Elem<LTI, double>;
     using D = typename ED::T;
     using ES = std::conditional_t<LTI, EL, ED>;                // end states of pieces
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(W * 64, 4) void k_column_scan(const ColumnParams p)
 #pragma unroll
         for (int i = 0; i < 7; ++i) lam_d[i] = EC::from(pow_d[i]);
         C carry = EC::from(x0);
-        // a pair applied to a state
+        // a pair applied to a state, or with S = 0 to an earlier product
         auto apply = [](C A, C x, C S) {
             if constexpr (!LTI) {
                 const int lo = __double2loint(A), hi = __double2hiint(A);
@@ -140,7 +141,7 @@ __global__ __launch_bounds__(W * 64, 4) void k_column_scan(const ColumnParams p)
                 if constexpr (LTI) { if (j >= d) S = ES::from(apply(lam_d[n], EC::from(Sp), EC::from(S))); }
                 else {
                     const D Ap = ED::up(A, d * COLS);
-                    if (j >= d) { S = apply(A, Sp, S); A = ED::mul(A, Ap); }
+                    if (j >= d) { S = apply(A, Sp, S); A = apply(A, Ap, ED::zero()); }
                 }
             }
             if (j == J - 1) { sS[buf][w][c] = S; if constexpr (!LTI) sA[buf][w][c] = A; }

@@ -99,3 +99,18 @@ def test_growing_states_are_finite_as_long_as_they_are(api, kind, shape, B, P, L
         assert np.abs(want).max() < 3e38
         x = scan(a_, b_, x0=x0).cpu().numpy()
         assert (np.abs(x - want) <= 3 * 2.0 ** -24 * (n + 16) * np.abs(want)).all(), (first, value)
+
+
+# a coefficient of zero ends what came before, however large the products of those after it (beyond double's range from 16 steps on)
+@pytest.mark.parametrize("shape,B,P,L", [(1, 1, 64, 700), (2, 1, 64, 32), (2, 1, 16, 127), (2, 8, 700, 700), (3, 4, 2000, 1100)])
+@pytest.mark.parametrize("at", [0.0, 0.2, 0.6])
+def test_zero_before_large_coefficients(api, shape, B, P, L, at):
+    assert _shape(api, "real", B, P, L) == shape
+    at = int(at * L)
+    a, b = torch.full((B, L, P), 1e20, device="cuda"), torch.zeros(B, L, P, device="cuda")
+    a[:, :at], a[:, at] = 0.999, 0.0
+    b[:, -1] = 1.0
+    x0 = torch.ones(B, P, device="cuda")
+    x = api.lrnnx_diag_scan(a, b, x0=x0).cpu().numpy()
+    want = _reference(a, b, x0)
+    assert (np.abs(x - want) <= 2.0 ** -24 * (at + 16) * np.abs(want)).all()
