@@ -212,7 +212,8 @@ __global__ __launch_bounds__(W * 64, 4) void k_column_scan(const ColumnParams p)
 // fit the chip, or for the chained scans thousands of time steps; the bytes of a column scan take longer, by the root of what a last round of one
 // workgroup a compute unit lacks.  Rows that are not whole lines vary more with their length, and a column scan is taken there from an
 // estimate a tenth below the other's.  Fitted over 240 shapes of 16 to 2048 columns, 64 to 16384 steps, 1 to 32 batch entries and 0.1 to 1100 MB: the
-// choice is 1.33 (LTI) and 1.10 times (real) as fast as the chained scans alone (geometric mean), at worst 1.07 and 1.11 times as long.
+// choice is 1.33 (LTI) and 1.10 times (real) as fast as the chained scans alone (geometric mean), at worst 1.07 and 1.11 times as long.  (The costs are those of
+// the kernel with twice the code, see above; the calls that take a column scan are now 0.83 (LTI, 40 calls) and 0.79 (real, 28) of that, from a graph.)
 struct ColumnCost { int cols, waves; double c0, c1, c2[2]; };           // c2: whole lines, others
 constexpr int kColumnT = 8;
 constexpr double kChainedCost[2][4] = {{7.5, 1.39, 0.151, 0.21}, {6.2, 0.9, 0.163, 0.229}};
