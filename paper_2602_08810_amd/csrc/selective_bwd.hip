@@ -101,22 +101,48 @@ __device__ __forceinline__ float pair_scans(float P0, float P1, float S0, float 
     return Q;
 }
 
+// Sums over the 16 lanes of each row, several at a time: a step that folds halves of a row (or of its halves) writes half of the lanes of one
+// register from one sum and the other half from another (bank_mask: groups of four lanes), so that no value has to be selected.
+// Four sums: on return lane i of a row holds sum i / 4.
+__device__ __forceinline__ float row_sums4(float a, float b, float c, float d) {
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3" : "+v"(a), "+v"(b));
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc" : "+v"(a), "+v"(b) : "v"(c), "v"(d));
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_ror:12 row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %0, %1, %1 row_ror:4 row_mask:0xf bank_mask:0xa" : "+v"(a) : "v"(b));
+    a += dpp<0xB1>(0.0f, a);                         // quad_perm [1,0,3,2]
+    return a + dpp<0x4E>(0.0f, a);                   // quad_perm [2,3,0,1]
+}
+// Two sums: lanes 0 to 7 of a row hold the first, 8 to 15 the second.
+__device__ __forceinline__ float row_sums2(float a, float b) {
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xc" : "+v"(a) : "v"(b));
+    a += dpp<0x141>(0.0f, a);                        // row_half_mirror
+    a += dpp<0xB1>(0.0f, a);                         // quad_perm [1,0,3,2]
+    return a + dpp<0x4E>(0.0f, a);                   // quad_perm [2,3,0,1]
+}
+
 // the eight steps of the tile that lane li of a half holds; PAIR: its two rows of 16 lanes hold alternate pieces
 template <bool PAIR> __device__ __forceinline__ int piece_of(int li) { return PAIR ? ((li & 15) << 1) | (li >> 4 & 1) : li; }
 
-// CNT consecutive steps of a tile of 256 in LDS: laid out [step % 8 / 4][lane that holds the 8 steps][step % 4], so that a
-// lane's 8 steps are two conflict-free 16-byte accesses, the second half rotated by 16 floats (and with PAIR the lanes of odd
-// rows by 8), so that consecutive threads of the prologue and epilogue (a few steps each) are free of conflicts as well: 8-byte
-// accesses of 16 lanes go out together and must fall into 32 different banks (rotated by 32 floats, every one of them took
-// twice its time).  f is a multiple of CNT.
+// CNT consecutive steps of a tile of 256 in LDS.  Step f of a whole tile sits at float f with its bits 2 and 3 turned by bits 5 and 6: a
+// lane's 8 steps are two 16-byte accesses (the second at the first's place ^ 4), those of 8 lanes, which go out together, fall into 32 different
+// banks whether the lanes hold consecutive pieces of the tile or alternate ones, and so do the few steps of consecutive threads of the prologue
+// and epilogue, whose place is a shift, a mask and an exclusive or of the thread's number.  f is a multiple of CNT.
 // A short tile (T = 4 or 2 steps a lane) takes the first 128 or 64 floats, [lane][step % T].
 template <bool PAIR, int T> __device__ __forceinline__ int lane_slot(int li) {
-    return T == 2 ? li << 1 : (li << 2) ^ (PAIR ? (li & 16) >> 1 : 0);
+    if constexpr (T == 8) { const int p = piece_of<PAIR>(li); return p << 3 ^ (p & 12); }
+    else return T == 2 ? li << 1 : (li << 2) ^ (PAIR ? (li & 16) >> 1 : 0);
 }
 template <bool PAIR, int T> __device__ __forceinline__ int step_slot(int f) {
+    if constexpr (T == 8) return f ^ (f >> 3 & 12);
     const int g = f / T, li = PAIR ? (g >> 1) | ((g & 1) << 4) : g;
-    if constexpr (T < 8) return lane_slot<PAIR, T>(li) + f % T;
-    else return ((f & 4) << 5) + (lane_slot<PAIR, T>(li) ^ ((f & 4) << 2)) + (f & 3);
+    return lane_slot<PAIR, T>(li) + f % T;
 }
 template <int CNT>
 __device__ __forceinline__ void lds_steps_read(const float *plane, int slot, float *out) {
@@ -126,7 +152,7 @@ __device__ __forceinline__ void lds_steps_read(const float *plane, int slot, flo
     else {
 #pragma unroll
         for (int q = 0; q < CNT / 4; ++q) {
-            const float4 v = *reinterpret_cast<const float4 *>(plane + (q ? (slot ^ 16) + 128 : slot));
+            const float4 v = *reinterpret_cast<const float4 *>(plane + (q ? slot ^ 4 : slot));
             out[4 * q] = v.x; out[4 * q + 1] = v.y; out[4 * q + 2] = v.z; out[4 * q + 3] = v.w;
         }
     }
@@ -139,7 +165,7 @@ __device__ __forceinline__ void lds_steps_write(float *plane, int slot, const fl
     else {
 #pragma unroll
         for (int q = 0; q < CNT / 4; ++q)
-            *reinterpret_cast<float4 *>(plane + (q ? (slot ^ 16) + 128 : slot)) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+            *reinterpret_cast<float4 *>(plane + (q ? slot ^ 4 : slot)) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
     }
 }
 
@@ -200,13 +226,14 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
     constexpr int NB = GE::NB;
     constexpr bool PAIR = bwd_pairs<N, DISC>();
     static_assert(!PAIR || (!OWN && NS % 2 == 0), "whole pairs of states, steps through LDS");
-    __shared__ __attribute__((aligned(16))) float sIn[NB][CP][3][OWN ? 4 : TILE];       // delta, u, dypre of a pair of channels
-    __shared__ __attribute__((aligned(16))) float sPart[NB][CP][W][3][OWN ? 4 : TILE];  // per wavefront: ypre, du, ddelta partials
+    // What the wavefronts exchange of a pair of channels, a block for each buffer, so that one address reaches all of it: planes of CP x
+    // TILE steps (delta, u, dypre; then ypre, du, ddelta partials of each wavefront), then A and the state entering the tile [2][CP][N].
+    constexpr int PL = OWN ? 0 : CP * TILE, AC = (3 + 3 * W) * PL, BUF = AC + 2 * CP * N;
+    __shared__ __attribute__((aligned(16))) float sPair[NB * BUF];
     __shared__ __attribute__((aligned(16))) float sH[kBwdMaxG * N];   // a_{l0} H_{l0} carried to the earlier tile, per (channel, n)
-    __shared__ __attribute__((aligned(16))) float sAC[NB][2][CP][N];   // A and the state entering the tile, of a pair
     __shared__ float sdA[kBwdMaxG * N];
-    __shared__ float sdD[kBwdMaxG], sdb[kBwdMaxG];
-    __shared__ float sDskip[kBwdMaxG], sBias[kBwdMaxG];
+    __shared__ float sdDb[2][kBwdMaxG];
+    __shared__ float sDskip[kBwdMaxG], sBias[kBwdMaxG + CP];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, li = lane & 31, half = lane >> 5;
@@ -252,15 +279,18 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
     const float *ckrow = p.ckpt + (((p.cu ? (int64_t)d0 : (int64_t)b * p.D + d0) * nck) + ck0) * N;
     const bool vec = p.vec != 0;
 
-    for (int i = tid; i < Gact * N; i += NT) {
+    // (an odd last channel has a partner in its pass, whose steps are empty and whose results go nowhere: its places in the tables exist,
+    // G being even, and hold zeros)
+    const int Gpair = (Gact + 1) & ~1;
+    for (int i = tid; i < Gpair * N; i += NT) {
         float h = 0.0f;
-        if (p.nchunks > 1) h = p.hc[(((int64_t)b * p.D + d0 + i / N) * p.nchunks + chunk) * N + i % N];
+        if (p.nchunks > 1 && i < Gact * N) h = p.hc[(((int64_t)b * p.D + d0 + i / N) * p.nchunks + chunk) * N + i % N];
         sH[i] = h; sdA[i] = 0.0f;
     }
-    for (int i = tid; i < Gact; i += NT) {
-        sdD[i] = 0.0f; sdb[i] = 0.0f;
-        sDskip[i] = p.Dskip ? p.Dskip[d0 + i] : 0.0f;
-        sBias[i] = p.bias ? p.bias[d0 + i] : 0.0f;
+    for (int i = tid; i < Gpair; i += NT) {
+        sdDb[0][i] = 0.0f; sdDb[1][i] = 0.0f;
+        sDskip[i] = p.Dskip && i < Gact ? p.Dskip[d0 + i] : 0.0f;
+        sBias[i] = p.bias && i < Gact ? p.bias[d0 + i] : 0.0f;
     }
 
     const int64_t bc0 = ((p.cu ? (int64_t)grp : (int64_t)b * p.bcg + grp) * p.L + toff) * N;   // first element of the maps of this sequence
@@ -282,6 +312,12 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
     // 162 -> 122 us, 74 of 119, 204 channels, N = 16, bf16 132 -> 111; whole tiles and longer tails as before.
     auto do_tile = [&](int64_t tile, auto full, auto per_lane) {
         constexpr bool FULL = decltype(full)::value;
+        // The launch's parameters, read again here: what the tiles need of them would otherwise be held in scalar registers, or for lack of
+        // those in lanes of vector registers, all through the kernel, once for each kind of tile (125 scalars spilled, so 54).
+        typedef const __attribute__((address_space(4))) BwdParams KernArgs;          // (the kernel's only argument)
+        KernArgs *args = (KernArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(args));
+        KernArgs &q = *args;
         constexpr int T = decltype(per_lane)::value;
         // prologue and epilogue: steps of a thread, threads that share a channel there, and this thread's channel of a pair (with short
         // tiles some wavefronts may have none)
@@ -316,19 +352,25 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         const int64_t tl = toff + l0;
         const int c_first = c_own < Gact ? c_own : Gact - 1;
         const int64_t dch = d0 + c_first;
-        const IO *n_u = reinterpret_cast<const IO *>(p.u) + bs * p.u_sb + dch * p.u_sd + tl;
-        const IO *n_dl = reinterpret_cast<const IO *>(p.delta) + bs * p.dl_sb + dch * p.dl_sd + tl;
-        const IO *n_dy = reinterpret_cast<const IO *>(p.dy) + bs * p.dy_sb + dch * p.dy_sd + tl;
-        const IO *n_z = HAS_Z ? reinterpret_cast<const IO *>(p.z) + bs * p.z_sb + dch * p.z_sd + tl : n_dy;
-        const int64_t z_sd = HAS_Z ? p.z_sd : p.dy_sd;
-        IO *o_du = reinterpret_cast<IO *>(p.du) + bs * p.du_sb + dch * p.du_sd + tl;
-        IO *o_dd = reinterpret_cast<IO *>(p.ddelta) + bs * p.dd_sb + dch * p.dd_sd + tl;
-        IO *o_dz = HAS_Z && p.dz ? reinterpret_cast<IO *>(p.dz) + bs * p.dz_sb + dch * p.dz_sd + tl : nullptr;
+        const IO *n_u = reinterpret_cast<const IO *>(q.u) + bs * q.u_sb + dch * q.u_sd + tl;
+        const IO *n_dl = reinterpret_cast<const IO *>(q.delta) + bs * q.dl_sb + dch * q.dl_sd + tl;
+        const IO *n_dy = reinterpret_cast<const IO *>(q.dy) + bs * q.dy_sb + dch * q.dy_sd + tl;
+        const IO *n_z = HAS_Z ? reinterpret_cast<const IO *>(q.z) + bs * q.z_sb + dch * q.z_sd + tl : n_dy;
+        const int64_t z_sd = HAS_Z ? q.z_sd : q.dy_sd;
+        IO *o_du = reinterpret_cast<IO *>(q.du) + bs * q.du_sb + dch * q.du_sd + tl;
+        IO *o_dd = reinterpret_cast<IO *>(q.ddelta) + bs * q.dd_sb + dch * q.dd_sd + tl;
+        const bool want_dz = HAS_Z && q.dz;
+        IO *o_dz = reinterpret_cast<IO *>(q.dz) + bs * q.dz_sb + dch * q.dz_sd + tl;
         int n_g = 0;                                                 // first channel of the pair of the next fetch
-        // A and the checkpointed state of the pair: one value each for the first 2 * CP * N threads
-        const float *n_A = p.A + (int64_t)d0 * N, *n_ck = ckrow + tile * N;
-        const unsigned ck_sd = (unsigned)(nck * N);                  // floats between the checkpoints of two channels
+        // A and the checkpointed state of the pair, [CP][N] each: the first wavefront fetches the former, the second the latter (lanes past
+        // their number again what the others do); a workgroup of one wavefront has a thread for each value
+        const bool has_ac = OWN ? tid < 2 * CP * N : w < 2, is_ck = OWN ? tid >= CP * N : w != 0;
+        const float *n_ac = is_ck ? ckrow + tile * N : q.A + (int64_t)d0 * N;
+        const unsigned ac_sd = is_ck ? (unsigned)(nck * N) : N;      // floats between two channels
         float r_ac = 0.0f;
+        auto put_ac = [&](unsigned t0, int buf) {
+            if (has_ac) (sPair + buf + AC + (OWN ? 0 : w * CP * N))[OWN ? t0 : t0 & (CP * N - 1)] = r_ac;
+        };
         const bool window = TPT > 1 && vec && L >= TPT;              // the last steps of the sequence: see tail_window
         auto fetch = [&](unsigned t0) {
             const unsigned f0 = (t0 % NTC) * TPT;
@@ -350,14 +392,14 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 load_few_raw<IO, TPT>(n_dy, (int)f0, rem, vec, r_dy);
                 if constexpr (HAS_Z) load_few_raw<IO, TPT>(n_z, (int)f0, rem, vec, r_z);
             }
-            if (t0 < 2 * CP * N) {
-                const bool second = (t0 / N) % CP && n_g + 1 < Gact;     // else the first channel of the pair again
-                const float *q = t0 < CP * N ? n_A : n_ck;
-                r_ac = q[t0 % N + (second ? (t0 < CP * N ? (unsigned)N : ck_sd) : 0u)];
+            if (has_ac) {
+                const unsigned second = n_g + 1 < Gact ? ac_sd : 0u;     // (no second channel: the first again)
+                const unsigned at = (t0 % N + (0u - (t0 / N % CP) & second)) * 4u;
+                r_ac = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(n_ac) + at);
             }
             n_g += CP;
-            if (n_g < Gact) { n_A += CP * N; n_ck += (int64_t)CP * ck_sd; }
-            if (n_g + c_own < Gact) { n_u += CP * p.u_sd; n_dl += CP * p.dl_sd; n_dy += CP * p.dy_sd; n_z += CP * z_sd; }
+            if (n_g < Gact) n_ac += (int64_t)CP * ac_sd;
+            if (n_g + c_own < Gact) { n_u += CP * q.u_sd; n_dl += CP * q.dl_sd; n_dy += CP * q.dy_sd; n_z += CP * z_sd; }
         };
         fetch(fresh(tid));
 
@@ -376,12 +418,10 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
             }
         }
 
-        // kept in registers from a pair's prologue to its epilogue: d softplus / ds and the factor that turns ypre
-        // into dz (n_*: of the pair after)
-        float e_sg[TPT], e_zf[TPT], n_sg[TPT], n_zf[TPT];
+        // kept in registers from a pair's prologue to its epilogue: d softplus / ds and the factor that turns ypre into dz
+        struct Kept { float sg[TPT], zf[TPT]; } even, odd;
         // ---- prologue of the pair whose inputs have been fetched: each thread prepares TPT steps of its channel
-        auto step_inputs = [&](int ch, unsigned t0, float (&u)[TPT], float (&dl)[TPT], float (&dy)[TPT]) {
-            const float bias = sBias[ch < Gact ? ch : Gact - 1];
+        auto step_inputs = [&](int ch, float bias, unsigned t0, Kept &k, float (&u)[TPT], float (&dl)[TPT], float (&dy)[TPT]) {
             float z[TPT];
             if (!FULL && window) {
                 const int f0 = (int)((t0 % NTC) * TPT), by = f0 - tail_window<TPT>(f0, rem);
@@ -399,9 +439,9 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 const float v = dl[i] + bias;
                 float sp, sg;
                 softplus_sigmoid<sizeof(IO) == 4>(v, sp, sg);
-                dl[i] = p.softplus ? sp : v;
-                n_sg[i] = p.softplus ? sg : 1.0f;
-                if constexpr (HAS_Z) gate_bwd(z[i], dy[i], n_zf[i]);
+                dl[i] = q.softplus ? sp : v;
+                k.sg[i] = q.softplus ? sg : 1.0f;
+                if constexpr (HAS_Z) gate_bwd(z[i], dy[i], k.zf[i]);
             }
             if (__builtin_expect(!FULL || ch >= Gact, !FULL)) {      // steps past the end: Delta = 0 (a = 1), no input, no gradient
                 const int f0 = (t0 % NTC) * TPT;
@@ -411,27 +451,30 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 asm volatile("");                        // (a branch that is hardly ever taken, not six selects in every pass)
             }
         };
-        auto prologue = [&](int ch, unsigned t0, int slot, int buf) {
+        // where this thread's steps of its channel are in a plane
+        auto thread_slot = [&](unsigned t0) {
+            // (a whole tile: the thread's number holds the channel above the step)
+            if constexpr (T == 8 && ALL) return step_slot<PAIR, T>((int)(t0 * TPT));
+            else return step_slot<PAIR, T>((int)((t0 % NTC) * TPT)) + c_own * TILE;
+        };
+        auto prologue = [&](int ch, float bias, unsigned t0, Kept &k, int buf) {
             if (busy) {
                 float u[TPT], dl[TPT], dy[TPT];
-                step_inputs(ch, t0, u, dl, dy);
-                lds_steps_write<TPT>(sIn[buf][c_own][0], slot, dl);
-                lds_steps_write<TPT>(sIn[buf][c_own][1], slot, u);
-                lds_steps_write<TPT>(sIn[buf][c_own][2], slot, dy);
+                step_inputs(ch, bias, t0, k, u, dl, dy);
+                float *in = sPair + buf + (unsigned)thread_slot(t0);
+                lds_steps_write<TPT>(in, 0, dl);
+                lds_steps_write<TPT>(in + PL, 0, u);
+                lds_steps_write<TPT>(in + 2 * PL, 0, dy);
             }
-            if (t0 < 2 * CP * N) (&sAC[buf][0][0][0])[t0] = r_ac;
-        };
-        auto rotate = [&]() {
-#pragma unroll
-            for (int i = 0; i < TPT; ++i) { e_sg[i] = n_sg[i]; if constexpr (HAS_Z) e_zf[i] = n_zf[i]; }
+            put_ac(t0, buf);
         };
         // ---- epilogue: du, ddelta, dz of this thread's steps from the sums over states
-        auto finish = [&](const int g, unsigned t0, unsigned f0, const float (&e_dl)[TPT], const float (&e_u)[TPT], const float (&e_dy)[TPT],
+        auto finish = [&](const int g, const Kept &k, unsigned t0, unsigned f0, const float (&e_dl)[TPT], const float (&e_u)[TPT], const float (&e_dy)[TPT],
                           const float (&s_yp)[TPT], const float (&s_du)[TPT], const float (&s_dd)[TPT], const float Dsk) {
             const int ch = g + c_own;
             const bool live = ch < Gact;
             float o_u[TPT], o_d[TPT], o_z[TPT];
-            float dD_part = 0.0f, db_part = 0.0f;
+            float dD_part, db_part;
 #pragma unroll
             for (int i = 0; i < TPT; ++i) {
                 const float ed = e_dl[i], eu = e_u[i], ey = e_dy[i];
@@ -442,47 +485,41 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                     su *= ed;
                 }
                 o_u[i] = __builtin_fmaf(ey, Dsk, su);
-                o_d[i] = sd * e_sg[i];
-                if constexpr (HAS_Z) o_z[i] = __builtin_fmaf(Dsk, eu, s_yp[i]) * e_zf[i];
-                dD_part = __builtin_fmaf(ey, eu, dD_part);
-                db_part += (FULL || (int)f0 + i < rem) ? o_d[i] : 0.0f;
+                o_d[i] = sd * k.sg[i];
+                if constexpr (HAS_Z) o_z[i] = __builtin_fmaf(Dsk, eu, s_yp[i]) * k.zf[i];
+                const float db = (FULL || (int)f0 + i < rem) ? o_d[i] : 0.0f;
+                dD_part = i ? __builtin_fmaf(ey, eu, dD_part) : ey * eu;
+                db_part = i ? db_part + db : db;
             }
             if (live) {
                 if (FULL) {
                     store_at<IO, TPT>(o_du, f0, o_u);
                     store_at<IO, TPT>(o_dd, f0, o_d);
-                    if constexpr (HAS_Z) { if (o_dz) store_at<IO, TPT>(o_dz, f0, o_z); }
+                    if constexpr (HAS_Z) { if (want_dz) store_at<IO, TPT>(o_dz, f0, o_z); }
                 } else {
                     store_few<IO, TPT>(o_du, (int)f0, rem, vec, o_u);
                     store_few<IO, TPT>(o_dd, (int)f0, rem, vec, o_d);
-                    if constexpr (HAS_Z) { if (o_dz) store_few<IO, TPT>(o_dz, (int)f0, rem, vec, o_z); }
+                    if constexpr (HAS_Z) { if (want_dz) store_few<IO, TPT>(o_dz, (int)f0, rem, vec, o_z); }
                 }
             }
-            {
-                // joint reduction of the two per-lane sums over a row of lanes, as for dA
-                const bool odd = t0 & 1;
-                float v = odd ? db_part : dD_part;
-                v += dpp<0xB1>(0.0f, odd ? dD_part : db_part);           // quad_perm [1,0,3,2]
-                v += dpp<0x4E>(0.0f, v);                                  // quad_perm [2,3,0,1]
-                v += dpp<0x124>(0.0f, v);                                 // row_ror:4
-                v += dpp<0x128>(0.0f, v);                                 // row_ror:8
-                if ((t0 & 15) < 2 && live) lds_add(&(odd ? sdb : sdD)[ch], v);
-            }
-            o_du += CP * p.du_sd; o_dd += CP * p.dd_sd;
-            if constexpr (HAS_Z) { if (o_dz) o_dz += CP * p.dz_sd; }
+            const float sum = row_sums2(dD_part, db_part);
+            if (__builtin_amdgcn_inverse_ballot_w64(0x0101010101010101)) lds_add(&sdDb[0][0] + ch + (t0 & 8) * (kBwdMaxG / 8), sum);
+            o_du += CP * q.du_sd; o_dd += CP * q.dd_sd;
+            if constexpr (HAS_Z) o_dz += CP * q.dz_sd;
         };
-        auto epilogue = [&](const int g, const int buf) {
+        auto epilogue = [&](const int g, const Kept &k, const int buf, auto read_next) {
             if (!busy) return;
             const unsigned t0 = fresh(tid), f0 = (t0 % NTC) * TPT;
-            const int slot = step_slot<PAIR, T>((int)f0);
+            const float *at = sPair + buf + (unsigned)thread_slot(t0);
             float e_in[3][TPT], s_yp[TPT], s_du[TPT], s_dd[TPT], v[W][3][TPT];
 #pragma unroll
             for (int ww = 0; ww < W; ++ww)
 #pragma unroll
-                for (int j = HAS_Z ? 0 : 1; j < 3; ++j) lds_steps_read<TPT>(sPart[buf][c_own][ww][j], slot, v[ww][j]);
+                for (int j = HAS_Z ? 0 : 1; j < 3; ++j) lds_steps_read<TPT>(at + (3 + 3 * ww + j) * PL, 0, v[ww][j]);
 #pragma unroll
-            for (int j = 0; j < 3; ++j) lds_steps_read<TPT>(sIn[buf][c_own][j], slot, e_in[j]);
-            const float Dsk = sDskip[g + c_own < Gact ? g + c_own : Gact - 1];
+            for (int j = 0; j < 3; ++j) lds_steps_read<TPT>(at + j * PL, 0, e_in[j]);
+            const float Dsk = sDskip[g + c_own];
+            read_next();
             // all reads before the first use: left to itself the compiler waits for each wavefront's sums before it reads the next
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -494,20 +531,20 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                     s_du[i] += v[ww][1][i]; s_dd[i] += v[ww][2][i];
                 }
             }
-            finish(g, t0, f0, e_in[0], e_in[1], e_in[2], s_yp, s_du, s_dd, Dsk);
+            finish(g, k, t0, f0, e_in[0], e_in[1], e_in[2], s_yp, s_du, s_dd, Dsk);
         };
         // ---- main: this lane's 8 steps of its channel, one state after the other
         auto states = [&](const int g, const int buf, const unsigned ln, float (&dl)[T], float (&du)[T], const float (&dy)[T],
                           float (&yp)[T], float (&pu)[T], float (&pd)[T]) {
-                const unsigned c = ln >> 5;
-                const int ch = g + (int)c < Gact ? g + (int)c : g;             // (the half past the last channel repeats the first, unused)
-                const bool own = g + (int)c < Gact;
-                const int at = ch * N + n0;
+                // this lane's channel in the tables of A and the state entering the tile, and in those of the adjoint and dA
+                const unsigned cN = (ln & 32) * N >> 5;
+                const float *ac = sPair + buf + AC + n0 + cN;
+                float *at = sH + g * N + n0 + cN;
                 float Ak[NS], ck[PAIR ? 1 : NS], hc[PAIR ? 1 : NS];
-                lds_few<NS>(&sAC[buf][0][c][n0], Ak);
+                lds_few<NS>(ac, Ak);
                 if constexpr (!PAIR) {
-                    lds_few<NS>(&sAC[buf][1][c][n0], ck);
-                    lds_few<NS>(&sH[at], hc);
+                    lds_few<NS>(ac + CP * N, ck);
+                    lds_few<NS>(at, hc);
                 }
                 if constexpr (DISC == DISC_ZOH_S6) {
 #pragma unroll
@@ -518,7 +555,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 for (int t = 1; t < T; ++t) sum_dl += dl[t];
                 float dA[NS];
                 if constexpr (PAIR) {
-                    const int row = ln >> 4 & 1;                     // of the half, and the state of a pair that it scans
+                    const unsigned row = ln >> 4 & 1;                // of the half, and the state of a pair that it scans
 #pragma unroll
                     for (int s = 0; s < NS; s += 2) {
                         float a[2][T], x[2][T], P[2], S[2], Q[2], xin[2], Gin[2];
@@ -526,11 +563,11 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
 #pragma unroll
                         for (int j = 0; j < 2; ++j) {
                             // the lane's folds, as below but from zero: what enters the tile joins the scan
-                            const ACoef ac = make_acoef<DISC>(Ak[s + j]);
+                            const ACoef co = make_acoef<DISC>(Ak[s + j]);
 #pragma unroll
                             for (int t = 0; t < T; ++t) {
                                 float g;
-                                disc_ag<DISC>(dl[t], ac, a[j][t], g);
+                                disc_ag<DISC>(dl[t], co, a[j][t], g);
                                 x[j][t] = du[t] * Bv[s + j][t];
                             }
                             S[j] = x[j][0]; Q[j] = a[j][T - 1] * (Cv[s + j][T - 1] * dy[T - 1]);
@@ -538,12 +575,12 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                             for (int t = 1; t < T; ++t) S[j] = __builtin_fmaf(a[j][t], S[j], x[j][t]);
 #pragma unroll
                             for (int t = T - 2; t >= 0; --t) Q[j] = a[j][t] * __builtin_fmaf(Cv[s + j][t], dy[t], Q[j]);
-                            P[j] = exp2_fast(sum_dl * ac.A2);
+                            P[j] = exp2_fast(sum_dl * co.A2);
                         }
-                        const float xc = i2f(f2i(sAC[buf][1][c][n0 + s + row]) & (int)first_lane);
-                        const float hc2 = i2f(f2i(sH[at + s + row]) & (int)last_lane);
+                        const float xc = i2f(f2i((ac + row)[CP * N + s]) & (int)first_lane);
+                        const float hc2 = i2f(f2i((at + row)[s]) & (int)last_lane);
                         const float out = pair_scans(P[0], P[1], S[0], S[1], Q[0], Q[1], xc, hc2, xin[0], xin[1], Gin[0], Gin[1]);
-                        if (own && (ln & 15) == 0) sH[at + s + row] = out;       // carried to the earlier tile
+                        if (first_lane) (at + row)[s] = out;             // carried to the earlier tile
                         fast_part();
                         // replay of both states side by side (earliest step first), then of both adjoints (last step first): two
                         // chains whose instructions fill each other's result latencies
@@ -575,7 +612,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 } else
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
-                    const ACoef ac = make_acoef<DISC>(Ak[s]);
+                    const ACoef co = make_acoef<DISC>(Ak[s]);
                     slow_part();
                     // the checkpointed state enters through the half's first lane, the carried adjoint through its last
                     float xin = i2f(f2i(ck[s]) & (int)first_lane), Gin = i2f(f2i(hc[s]) & (int)last_lane);
@@ -586,10 +623,10 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                         // (an own copy for each state: multiples and powers of Delta are not kept in registers for the next)
                         if constexpr (DISC == DISC_ZOH || DISC == DISC_BILINEAR) asm volatile("" : "+v"(dl[t]));
                         if constexpr (DISC == DISC_BILINEAR) {
-                            q[t] = bilinear_q(dl[t], ac);
+                            q[t] = bilinear_q(dl[t], co);
                             a[t] = bilinear_a(q[t]);
                             gg[t] = dl[t] * q[t];
-                        } else disc_ag<DISC>(dl[t], ac, a[t], gg[t]);
+                        } else disc_ag<DISC>(dl[t], co, a[t], gg[t]);
                         if constexpr (DISC == DISC_ZOH_S6 || DISC == DISC_DIRAC) x[t] = du[t] * Bv[s][t];
                         else x[t] = gg[t] * du[t] * Bv[s][t];
                     }
@@ -604,13 +641,13 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                         if constexpr (T == 8) P = ((a[0] * a[1]) * (a[2] * a[3])) * ((a[4] * a[5]) * (a[6] * a[7]));
                         else if constexpr (T == 4) P = (a[0] * a[1]) * (a[2] * a[3]);
                         else P = a[0] * a[1];
-                    } else P = exp2_fast(sum_dl * ac.A2);
+                    } else P = exp2_fast(sum_dl * co.A2);
                     if constexpr (DISC == DISC_BILINEAR) {           // (there are no registers to keep the multipliers beside q)
 #pragma unroll
                         for (int t = 0; t < T; ++t) asm volatile("" : "+v"(q[t]));
                     }
                     half_scans(P, S, Q, xin, Gin);
-                    if (own && (ln & 31) == 0) sH[at + s] = Q;       // carried to the earlier tile
+                    if (first_lane) at[s] = Q;                       // carried to the earlier tile
                     fast_part();
                     // replay of the states (earliest step first) and of the adjoint (last step first), side by side: two chains
                     // whose instructions fill each other's result latencies.  zoh and bilinear, which need more registers and
@@ -653,18 +690,18 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                             acc(pu[t], R[t], Bv[s][t]);
                             dB[s][t] = __builtin_fmaf(R[t], du[t], dB[s][t]);
                             const float q = G[t] * xprev;
-                            acc(pd[t], q, ac.A);
+                            acc(pd[t], q, co.A);
                             dAp = __builtin_fmaf(q, dl[t], dAp);
                         } else if constexpr (DISC == DISC_ZOH) {
                             // da/dDelta = A a, da/dA = Delta a, dg/dDelta = a: the common factor a is taken out
-                            const float g_A = zoh_gain_dA(dl[t], ac, a[t], gg[t]);
+                            const float g_A = zoh_gain_dA(dl[t], co, a[t], gg[t]);
                             const float hb = R[t] * Bv[s][t];
                             const float dg = hb * du[t];
                             const float q = Gin * xprev;
                             acc(pu[t], hb, gg[t]);
                             dB[s][t] = __builtin_fmaf(R[t] * gg[t], du[t], dB[s][t]);
-                            if (s == 0) pd[t] = __builtin_fmaf(q, ac.A, dg * a[t]);
-                            else pd[t] = __builtin_fmaf(q, ac.A, __builtin_fmaf(dg, a[t], pd[t]));
+                            if (s == 0) pd[t] = __builtin_fmaf(q, co.A, dg * a[t]);
+                            else pd[t] = __builtin_fmaf(q, co.A, __builtin_fmaf(dg, a[t], pd[t]));
                             dAp = __builtin_fmaf(q, dl[t], __builtin_fmaf(dg, g_A, dAp));
                         } else {
                             // bilinear: g = Delta q, and all four partials are multiples of q^2: da/dDelta = A q^2, da/dA = Delta q^2,
@@ -672,7 +709,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                             const float qB = G[t] * Bv[s][t], da = G[t] * xprev, dg = qB * du[t];
                             acc(pu[t], qB, dl[t]);
                             dB[s][t] = __builtin_fmaf(G[t] * dl[t], du[t], dB[s][t]);
-                            acc(pd[t], __builtin_fmaf(da, ac.A, dg), q[t]);
+                            acc(pd[t], __builtin_fmaf(da, co.A, dg), q[t]);
                             dAp = __builtin_fmaf(__builtin_fmaf(0.5f * dl[t], dg, da) * dl[t], q[t], dAp);
                         }
                         // computed here: left to itself the compiler moves the products of one state down to the sums of the
@@ -683,18 +720,11 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                     dA[s] = dAp;
                 }
                 slow_part();
-                // dA: over the 16 lanes of a row.  With four states two exchange steps leave each lane of a quad with the
-                // quad's sum of ONE state (lane % 4 = 0, 1, 2, 3: state 0, 2, 1, 3), two rotations sum the quads
+                // dA: over the 16 lanes of a row
+                float *sum = sdA + g * N + n0 + cN;
                 if constexpr (NS == 4) {
-                    const bool b0 = ln & 1, b1 = ln & 2;
-                    float kA = b0 ? dA[2] : dA[0], kB = b0 ? dA[3] : dA[1];
-                    kA += dpp<0xB1>(0.0f, b0 ? dA[0] : dA[2]);           // quad_perm [1,0,3,2]
-                    kB += dpp<0xB1>(0.0f, b0 ? dA[1] : dA[3]);
-                    float v = b1 ? kB : kA;
-                    v += dpp<0x4E>(0.0f, b1 ? kA : kB);                  // quad_perm [2,3,0,1]
-                    v += dpp<0x124>(0.0f, v);                            // row_ror:4
-                    v += dpp<0x128>(0.0f, v);                            // row_ror:8
-                    if (own && (ln & 15) < 4) lds_add(&sdA[at + ((ln & 1) << 1) + ((ln >> 1) & 1)], v);
+                    const float v = row_sums4(dA[0], dA[1], dA[2], dA[3]);
+                    if (__builtin_amdgcn_inverse_ballot_w64(0x1111111111111111)) lds_add(sum + (ln >> 2 & 3), v);
                 } else {
 #pragma unroll
                     for (int s = 0; s < NS; ++s) {
@@ -703,7 +733,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                         v += dpp<0x4E>(0.0f, v);
                         v += dpp<0x124>(0.0f, v);
                         v += dpp<0x128>(0.0f, v);
-                        if (own && (ln & 15) == 0) lds_add(&sdA[at + s], v);
+                        if ((ln & 15) == 0) lds_add(sum + s, v);
                     }
                 }
         };
@@ -712,60 +742,93 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
             for (int g = 0; g < Gact; g += CP) {
                 const unsigned t0 = fresh(tid);
                 float u[T], dl[T], dy[T], du[T], yp[T], pu[T], pd[T];
-                step_inputs(g + c_own, t0, u, dl, dy);
-                rotate();
-                if (t0 < 2 * CP * N) (&sAC[0][0][0][0])[t0] = r_ac;
+                step_inputs(g + c_own, sBias[g + c_own], t0, even, u, dl, dy);
+                put_ac(t0, 0);
                 fetch(t0);
 #pragma unroll
                 for (int t = 0; t < T; ++t) du[t] = u[t];
                 __syncthreads();                         // (one wavefront: orders the LDS accesses only)
                 states(g, 0, t0, dl, du, dy, yp, pu, pd);
-                finish(g, t0, (t0 % NTC) * TPT, dl, u, dy, yp, pu, pd, sDskip[g + c_own < Gact ? g + c_own : Gact - 1]);
+                finish(g, even, t0, (t0 % NTC) * TPT, dl, u, dy, yp, pu, pd, sDskip[g + c_own < Gact ? g + c_own : Gact - 1]);
                 __syncthreads();
             }
         } else {
+            // A pass's steps are read from LDS behind the epilogue's reads and ahead of its arithmetic, and the next pair's biases ahead of
+            // the stores of the partial sums: what is read is there when it is needed (277.7 -> 271.6 us on the training shape above).
+            float dl[T], du[T], dy[T], bias;
+            auto lane_at = [&](unsigned ln) { return (unsigned)lane_slot<PAIR, T>(ln & 31) + (ln & 32) * (TILE / 32); };
+            unsigned l4 = 0;                             // where this lane's steps are in a plane
+            auto main_read = [&](const int buf) {
+                l4 = lane_at(fresh(lane));
+                lds_steps_read<T>(sPair + buf, l4, dl);
+                lds_steps_read<T>(sPair + buf + PL, l4, du);
+                lds_steps_read<T>(sPair + buf + 2 * PL, l4, dy);
+            };
             auto main_part = [&](const int g, const int buf) {
-                const unsigned ln = fresh(lane), c = ln >> 5;
-                const int l4 = lane_slot<PAIR, T>(ln & 31);
-                float dl[T], du[T], dy[T], yp[T], pu[T], pd[T];
-                lds_steps_read<T>(sIn[buf][c][0], l4, dl);
-                lds_steps_read<T>(sIn[buf][c][1], l4, du);
-                lds_steps_read<T>(sIn[buf][c][2], l4, dy);
+                const unsigned ln = fresh(lane);
+                float yp[T], pu[T], pd[T];
                 states(g, buf, ln, dl, du, dy, yp, pu, pd);
                 edge_part();
-                float *part = &sPart[buf][0][w][0][0] + (0u - c & (unsigned)(sizeof(sPart[0][0]) / sizeof(float)));
-                constexpr int PL = sizeof(sPart[0][0][0][0]) / sizeof(float);
+                bias = sBias[g + CP + c_own];                // (past the last pair: not used)
+                float *part = sPair + buf + (3 + 3 * w) * PL;
                 if constexpr (HAS_Z) lds_steps_write<T>(part, l4, yp);
                 lds_steps_write<T>(part + PL, l4, pu);
                 lds_steps_write<T>(part + 2 * PL, l4, pd);
             };
-            auto next_inputs = [&](const int g, const int buf) {          // (past the last pair: unused)
+            auto next_inputs = [&](const int g, Kept &k, const int buf) {          // (past the last pair: unused)
                 const unsigned t0 = fresh(tid);
-                prologue(g + c_own, t0, step_slot<PAIR, T>((int)((t0 % NTC) * TPT)), buf);
+                prologue(g + c_own, bias, t0, k, buf);
                 fetch(t0);
             };
-            next_inputs(0, 0);
+            constexpr auto nothing = [] {};
+            bias = sBias[c_own];
+            next_inputs(0, even, 0);
             if constexpr (NB == 2) {
                 // Between two barriers a wavefront finishes the pair before (its partial sums are complete), runs the main
-                // part of this pair and prepares the next one: nobody waits in between.  (Two barriers per pair cost 4 %.)
-                int g = 0, buf = 0;
-                for (; g < Gact; g += CP, buf ^= 1) {
+                // part of this pair and prepares the next one: nobody waits in between.  (Two barriers per pair cost 4 %.)  Written out for the
+                // two buffers: with the buffer in a variable the kept values are copied and addresses formed in every pass.
+                auto pass = [&](const int g, Kept &kept, const int buf, Kept &other, const int next) {
                     __syncthreads();
-                    if (g > 0) epilogue(g - CP, buf ^ 1);
-                    rotate();
+                    if (g > 0) epilogue(g - CP, other, next, [&] { main_read(buf); }); else main_read(buf);
                     main_part(g, buf);
-                    next_inputs(g + CP, buf ^ 1);
+                    next_inputs(g + CP, other, next);
+                };
+                int g = 0;
+                if constexpr (FULL) {
+                    for (; g + CP < Gact; g += 2 * CP) {
+                        pass(g, even, 0, odd, BUF);
+                        pass(g + CP, odd, BUF, even, 0);
+                    }
+                    if (g < Gact) {
+                        pass(g, even, 0, odd, BUF);
+                        __syncthreads();
+                        epilogue(g, even, 0, nothing);
+                    } else {
+                        __syncthreads();
+                        epilogue(g - CP, odd, BUF, nothing);
+                    }
+                } else {
+                    int buf = 0;
+                    for (; g < Gact; g += CP, buf = BUF - buf) {
+                        __syncthreads();
+                        if (g > 0) epilogue(g - CP, odd, BUF - buf, nothing);
+                        odd = even;
+                        main_read(buf);
+                        main_part(g, buf);
+                        next_inputs(g + CP, even, BUF - buf);
+                    }
+                    __syncthreads();
+                    epilogue(g - CP, odd, BUF - buf, nothing);
                 }
-                __syncthreads();
-                epilogue(g - CP, buf ^ 1);
             } else {
                 for (int g = 0; g < Gact; g += CP) {
                     __syncthreads();
-                    rotate();
+                    odd = even;
+                    main_read(0);
                     main_part(g, 0);
                     __syncthreads();
-                    epilogue(g, 0);
-                    next_inputs(g + CP, 0);
+                    epilogue(g, odd, 0, nothing);
+                    next_inputs(g + CP, even, 0);
                 }
             }
         }
@@ -794,7 +857,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
             // over workgroups and the transposition to [L,N] are k_ss_bwd_maps's)
             const int r = piece_of<PAIR>(li) * T + half * TH;            // [step % 8 / 4][step / 8][step % 4], for any T
             const int at = T == 8 ? (half * 32 + piece_of<PAIR>(li)) * 4 : ((r & 4) << 5) + (r >> 3 << 2) + (r & 3);
-            float *pt = p.part + (((slot0 + tile_first + tile) * gridDim.x + blockIdx.x) * 2 * N + n0) * TILE + at;
+            float *pt = q.part + (((slot0 + tile_first + tile) * gridDim.x + blockIdx.x) * 2 * N + n0) * TILE + at;
 #pragma unroll
             for (int s = 0; s < NS; ++s) { put(pt + s * TILE, oB[s]); put(pt + (N + s) * TILE, oC[s]); }
         } else {
@@ -802,7 +865,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
             // 8 steps apart take a transaction each, 8 times as long)
             const unsigned t0 = fresh(tid), st0 = piece_of<PAIR>(t0 & 31) * T + (t0 >> 5 & 1) * TH;
             if constexpr (OWN) {
-                float *gB = p.dBm + bc0 + l0 * N, *gC = p.dCm + bc0 + l0 * N;
+                float *gB = q.dBm + bc0 + l0 * N, *gC = q.dCm + bc0 + l0 * N;
 #pragma unroll
                 for (int t = 0; t < TH; ++t)
                     if ((int)st0 + t < rem) {
@@ -813,8 +876,8 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                         }
                     }
             } else {
-                static_assert(OWN || N <= NB * CP * W * 3, "one map's sums in the partial sums' place");
-                float *buf = &sPart[0][0][0][0][0];
+                static_assert(OWN || N * TILE <= NB * BUF, "one map's sums in the pairs' place");
+                float *buf = sPair;
                 auto flush = [&](float (&o)[NS][TH], float *g) {
                     __syncthreads();
 #pragma unroll
@@ -823,8 +886,8 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
 #pragma unroll 1
                     for (int i = t0; i < rem * N; i += NT) unsafeAtomicAdd(g + bc0 + l0 * N + i, buf[(i % N) * TILE + i / N]);
                 };
-                flush(oB, p.dBm);
-                flush(oC, p.dCm);
+                flush(oB, q.dBm);
+                flush(oC, q.dCm);
             }
         }
     };
@@ -849,8 +912,8 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         if (p.dx0 && chunk == 0) p.dx0[((int64_t)b * p.D + d0) * N + i] = sH[i];
     }
     for (int g = tid; g < Gact; g += NT) {
-        if (p.dD) unsafeAtomicAdd(p.dD + d0 + g, sdD[g]);
-        if (p.dbias) unsafeAtomicAdd(p.dbias + d0 + g, sdb[g]);
+        if (p.dD) unsafeAtomicAdd(p.dD + d0 + g, sdDb[0][g]);
+        if (p.dbias) unsafeAtomicAdd(p.dbias + d0 + g, sdDb[1][g]);
     }
 }
 
@@ -948,6 +1011,7 @@ __global__ __launch_bounds__(256) void k_ss_bwd_maps(const BwdParams p, int gx) 
         for (int i = tid; i < rows * N; i += 256) out[i] = sT[(i / N) * (N + 1) + i % N];
     }
 }
+
 
 // ---------------------------------------------------------------- launchers
 // HAS_Z (gated) is a template parameter: without it the kernel does not rebuild ypre = sum_n C x for dz.  So is whether the
