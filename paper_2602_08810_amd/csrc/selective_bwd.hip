@@ -757,7 +757,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
             // the stores of the partial sums: what is read is there when it is needed (277.7 -> 271.6 us on the training shape above).
             float dl[T], du[T], dy[T], bias;
             auto lane_at = [&](unsigned ln) { return (unsigned)lane_slot<PAIR, T>(ln & 31) + (ln & 32) * (TILE / 32); };
-            unsigned l4 = 0;                             // where this lane's steps are in a plane
+            unsigned l4 = 0;                             // where this lane's steps are in a plane (float32: formed again, a register less)
             auto main_read = [&](const int buf) {
                 l4 = lane_at(fresh(lane));
                 lds_steps_read<T>(sPair + buf, l4, dl);
@@ -769,6 +769,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 float yp[T], pu[T], pd[T];
                 states(g, buf, ln, dl, du, dy, yp, pu, pd);
                 edge_part();
+                if constexpr (sizeof(IO) == 4) l4 = lane_at(fresh(ln));
                 bias = sBias[g + CP + c_own];                // (past the last pair: not used)
                 float *part = sPair + buf + (3 + 3 * w) * PL;
                 if constexpr (HAS_Z) lds_steps_write<T>(part, l4, yp);
