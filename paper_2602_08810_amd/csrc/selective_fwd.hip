@@ -84,8 +84,9 @@ __device__ __forceinline__ void channel_scan2(float (&P)[2], float (&S)[2], floa
 #undef LRNNX_S2
 }
 
-template <int LPC, int T> struct FwdGeom {
-    static constexpr int W = LPC * T / 64 < 8 ? LPC * T / 64 : 8;      // wavefronts of a workgroup
+// WG: wavefronts of a workgroup where a shape has more than one number of them (0: the usual one)
+template <int LPC, int T, int WG = 0> struct FwdGeom {
+    static constexpr int W = WG ? WG : LPC * T / 64 < 8 ? LPC * T / 64 : 8;      // wavefronts of a workgroup
     static constexpr int CPW = 64 / LPC;             // channels of a wavefront
     static constexpr int CH = W * CPW;               // channels of a workgroup
     static constexpr int TILE = LPC * T;
@@ -97,11 +98,11 @@ template <int LPC, int T> struct FwdGeom {
 // SIMD); with 64 lanes four of four wavefronts (4 steps) or two of eight (8 steps: 75 KB of LDS each), at 128 registers four a
 // SIMD; one of eight with 16 steps, whose staged tile takes more than half of the LDS.
 // RANKED: a packed batch whose workgroups rank the sequences (ranked_sequences)
-template <typename IO, int N, int DISC, bool WANT_Y, bool CKPT, int LPC, int TM, bool RANKED>
-__global__ __launch_bounds__((FwdGeom<LPC, TM>::W * 64), (TM == 16 ? (LPC == 16 ? 3 : 2) : 4)) void k_ss_fwd(const FwdParams p) {
-    using GE = FwdGeom<LPC, TM>;
-    constexpr int W = GE::W, CPW = GE::CPW, CH = GE::CH, TILE = GE::TILE, NT = W * 64;
-    constexpr int RPT = TILE / NT;                   // rows of the maps a thread stages
+template <typename IO, int N, int DISC, bool WANT_Y, bool CKPT, int LPC, int TM, bool RANKED, int WG = 0>
+__global__ __launch_bounds__((FwdGeom<LPC, TM, WG>::W * 64), (TM == 16 ? (LPC == 16 ? 3 : 2) : WG ? 3 : 4)) void k_ss_fwd(const FwdParams p) {
+    using GE = FwdGeom<LPC, TM, WG>;
+    constexpr int W = GE::W, CPW = GE::CPW, CH = GE::CH, TILE = GE::TILE, NT = W * 64 < TILE ? W * 64 : TILE;
+    constexpr int RPT = TILE / NT;                   // rows of the maps a thread stages (the first NT threads do)
     constexpr int NS = N > 16 ? 16 : N, NH = N / NS; // states staged at a time, and how often
     constexpr bool EARLY = sizeof(IO) == 2 ? LPC > 16 || N <= 8 : LPC > 16 && N <= 8;
     constexpr bool LATE_Z = sizeof(IO) == 4 && TM == 16 && LPC == 16;
@@ -176,6 +177,7 @@ __global__ __launch_bounds__((FwdGeom<LPC, TM>::W * 64), (TM == 16 ? (LPC == 16 
         if constexpr (AGG) sP[c][n] = 1.0f;
     }
     if (lane < N) sX[CH][lane] = 0.0f;               // (every wavefront: the same value)
+    const bool stages = NT == W * 64 || w < NT / 64;
 
     // A staged row of Bm or Cm: step 4 q + i of lane l (of TM) at q Q + 4 l + i.  The reads, 16 bytes from each lane,
     // are contiguous over the lanes and all share one address; Q leaves a gap of 256 / TM so that the 64 consecutive steps
@@ -209,6 +211,7 @@ __global__ __launch_bounds__((FwdGeom<LPC, TM>::W * 64), (TM == 16 ? (LPC == 16 
     };
     auto fetch_maps = [&](int64_t tile, int h, auto FULL) {
         const int64_t l0 = tile * TILE;
+        if (!stages) return;
 #pragma unroll
         for (int k = 0; k < RPT; ++k) {
             int64_t l = l0 + (int)(fresh() + k * NT);
@@ -254,7 +257,7 @@ __global__ __launch_bounds__((FwdGeom<LPC, TM>::W * 64), (TM == 16 ? (LPC == 16 
 #pragma unroll
             for (int k = 0; k < RPT; ++k) {
                 const unsigned r = fresh() + k * NT, q = (r % T) / 4;
-                if (T != TM && r >= LPC * T) break;
+                if ((T != TM && r >= LPC * T) || !stages) break;
                 const unsigned off = q * GE::Q + (r / T) * 4 + (r % 4);
                 float v[NS];
                 unpack_few<IO, NS>(r_B[k], v);
@@ -516,30 +519,36 @@ __global__ __launch_bounds__((FwdGeom<LPC, TM>::W * 64), (TM == 16 ? (LPC == 16 
 //             64 x 8 10.0, 16 lanes 10.7) and with few states, where memory is the bound, for many rows (16 x 2560 rows,
 //             L = 2048, N = 4, float32: 247 us, 16 lanes 274)
 //   64 x 8:   a few thousand rows (4096 rows, L = 2048, N = 16, float32: 46 us; 16 lanes 73, 64 x 4 65)
+//   64 x 8, twelve wavefronts: where workgroups of eight channels would be a little more than one a compute unit, which is as long as two, and
+//             those of twelve are not (2049 to 3072 rows; one workgroup a compute unit, three wavefronts a SIMD instead of four; 2313 rows,
+//             L = 1531, N = 16, float32: 36.3 -> 30.2 us, bf16 32.4 -> 26.9; 3000 rows, L = 4096: 83.0 -> 72.1, 72.4 -> 62.6; with nine or
+//             ten wavefronts the same, with thirteen to sixteen, four on a SIMD, what eight take)
 //   64 x 16:  one workgroup a compute unit (its tile takes the LDS), so at most 2048 rows, but fewer instructions
 //             than 64 x 8 (768 rows, L = 32768, N = 16, bf16: 284 us; 64 x 8: 328)
 // The costs were fitted before the issue priorities and the pairs of states changed the shapes unequally.  With the present kernels the
 // choice is 1.8 % (float32) and 0.7 % (bfloat16) slower than the best of the four and the chunked path over 729 calls of each type, at
 // most 1.30 times: N = 1 on 16 to 1500 rows of 1531 steps takes 64 x 16, 11.4 us for the 8.8 of 64 x 4.
-enum class FwdShape { l16, l64x4, l64x8, l64x16 };
+enum class FwdShape { l16, l64x4, l64x8, l64x16, l64x8w12 };
 struct FwdCost { int tile, state, wg, wg_state; };
-static constexpr FwdCost kFwdCost[2][4] = {{{0, 20, 249, 17}, {22, 12, 52, 8}, {0, 6, 183, 27}, {0, 0, 215, 65}},          // float32
-                                           {{19, 16, 136, 17}, {40, 9, 31, 7}, {0, 8, 132, 24}, {0, 0, 170, 53}}};         // bfloat16
+static constexpr FwdCost kFwdCost[2][5] = {{{0, 20, 249, 17}, {22, 12, 52, 8}, {0, 6, 183, 27}, {0, 0, 215, 65}, {0, 6, 296, 44}},          // float32
+                                           {{19, 16, 136, 17}, {40, 9, 31, 7}, {0, 8, 132, 24}, {0, 0, 170, 53}, {0, 8, 214, 39}}};         // bfloat16
+static constexpr FwdShape kFwdShapes[5] = {FwdShape::l16, FwdShape::l64x4, FwdShape::l64x8, FwdShape::l64x16, FwdShape::l64x8w12};
 static int64_t fwd_cost(const FwdCost &c, int64_t N, int64_t tiles, int64_t wgs) {
     const int64_t share = (wgs + kNumCU - 1) / kNumCU;   // workgroups of a compute unit
     return tiles * (c.tile + c.state * N + share * (c.wg + c.wg_state * N));
 }
 static int64_t fwd_time(int64_t maps, int64_t dpg, int64_t N, int64_t L, bool f32, FwdShape shape) {
-    static constexpr int steps[4] = {256, 256, 512, 1024}, channels[4] = {16, 4, 8, 8};
+    static constexpr int steps[5] = {256, 256, 512, 1024, 512}, channels[5] = {16, 4, 8, 8, 12};
     const int i = (int)shape;
     const int64_t wgs = maps * ((dpg + channels[i] - 1) / channels[i]);
     if (shape == FwdShape::l64x16 && wgs > kNumCU) return INT64_MAX;
+    if (shape == FwdShape::l64x8w12 && (wgs > kNumCU || N < 8 || maps * ((dpg + 7) / 8) <= kNumCU)) return INT64_MAX;
     return fwd_cost(kFwdCost[f32 ? 0 : 1][i], N, (L + steps[i] - 1) / steps[i], wgs);
 }
 static FwdShape fwd_shape(const FwdParams &p, bool f32) {
     FwdShape best = FwdShape::l16;
     int64_t least = INT64_MAX;
-    for (const FwdShape shape : {FwdShape::l16, FwdShape::l64x4, FwdShape::l64x8, FwdShape::l64x16}) {
+    for (const FwdShape shape : kFwdShapes) {
         const int64_t t = fwd_time((int64_t)p.B * p.bcg, p.dpg, p.N, p.L, f32, shape);
         if (t < least) { least = t; best = shape; }
     }
@@ -568,19 +577,19 @@ static FwdShape packed_shape(const FwdParams &p, bool f32) {
     return rows >= 2048 && mean >= 2048 ? FwdShape::l64x8 : FwdShape::l64x4;
 }
 
-template <typename IO, int N, int DISC, int LPC, int T>
+template <typename IO, int N, int DISC, int LPC, int T, int WG = 0>
 static hipError_t launch_fwd_lanes(FwdParams p, hipStream_t s) {
-    using GE = FwdGeom<LPC, T>;
+    using GE = FwdGeom<LPC, T, WG>;
     // tiles_per_chunk counts tiles of 256 steps; a single pass is one chunk whatever the tile
     if (p.nchunks == 1) p.tiles_per_chunk = (p.L + GE::TILE - 1) / GE::TILE;
     dim3 grid(p.bcg * ((p.dpg + GE::CH - 1) / GE::CH), p.B, p.mode == MODE_AGG ? p.nchunks - 1 : p.nchunks);
     const bool want_y = (p.mode == MODE_FULL || p.mode == MODE_APPLY);
     const dim3 block(GE::W * 64);
     auto launch = [&](auto RANKED) {
-        if (want_y && p.ckpt) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, true, true, LPC, T, RANKED>), grid, block, 0, s, p);
-        else if (want_y) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, true, false, LPC, T, RANKED>), grid, block, 0, s, p);
-        else if (p.ckpt) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, false, true, LPC, T, RANKED>), grid, block, 0, s, p);
-        else if constexpr (LPC == 16 && !RANKED) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, false, false, LPC, T, RANKED>), grid, block, 0, s, p);
+        if (want_y && p.ckpt) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, true, true, LPC, T, RANKED, WG>), grid, block, 0, s, p);
+        else if (want_y) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, true, false, LPC, T, RANKED, WG>), grid, block, 0, s, p);
+        else if (p.ckpt) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, false, true, LPC, T, RANKED, WG>), grid, block, 0, s, p);
+        else if constexpr (LPC == 16 && !RANKED) hipLaunchKernelGGL((k_ss_fwd<IO, N, DISC, false, false, LPC, T, RANKED, WG>), grid, block, 0, s, p);
         else return hipErrorInvalidValue;                // the chunk-carry path takes 16 lanes per channel, and no packed batches
         return hipGetLastError();
     };
@@ -598,6 +607,9 @@ static hipError_t launch_fwd_n(const FwdParams &p, hipStream_t s) {
         case FwdShape::l64x4: return launch_fwd_lanes<IO, N, DISC, 64, 4>(p, s);
         case FwdShape::l64x8: return launch_fwd_lanes<IO, N, DISC, 64, 8>(p, s);
         case FwdShape::l64x16: return launch_fwd_lanes<IO, N, DISC, 64, 16>(p, s);
+        case FwdShape::l64x8w12:
+            if constexpr (N >= 8) return launch_fwd_lanes<IO, N, DISC, 64, 8, 12>(p, s);
+            break;
         default: break;
     }
     return launch_fwd_lanes<IO, N, DISC, 16, 16>(p, s);
@@ -650,7 +662,7 @@ bool fwd_chunks_pay(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L, b
     const int64_t channels = fwd_channels_per_workgroup();
     const int64_t chunked = fwd_cost(cost[f32 ? 0 : 1], N, 1, B * bcg * ((dpg + channels - 1) / channels) * tiles);
     constexpr int64_t launch = 220;
-    for (const FwdShape shape : {FwdShape::l16, FwdShape::l64x4, FwdShape::l64x8, FwdShape::l64x16}) {
+    for (const FwdShape shape : kFwdShapes) {
         const int64_t t = fwd_time(B * bcg, dpg, N, L, f32, shape);
         if (t != INT64_MAX && t + launch <= chunked + chunked * 3 / 100) return false;
     }
