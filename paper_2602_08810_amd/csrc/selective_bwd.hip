@@ -331,20 +331,51 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
         const int64_t l0 = tile * TILE;
         const int rem = FULL ? TILE : ((L - l0 < TILE) ? (int)(L - l0) : TILE);      // valid steps of this tile (at least one)
 
-        // ---- this lane's columns of Bm and Cm: every row is loaded without a branch (past the end of the tile the last
-        // valid row is read again and then discarded), so that all loads of a lane are in flight together
-        RawFew<IO, NS> rB[T], rC[T];
+        // ---- the rows of Bm and Cm: all without a branch (past the end of the tile the last valid row is read again and then discarded), so that all
+        // loads of a lane are in flight together.  From four wavefronts on they are read as they lie, 16 bytes a lane, and each lane takes its
+        // columns from LDS, where the rows of eight steps have a gap of 16 bytes against bank conflicts.  Loaded by column each access met 32
+        // cache lines, and those of eight wavefronts held up what came behind them (B=8, D=1536, N=16, L=2048, bf16: 274 -> 269.5 us).
+        constexpr bool STAGED = NB == 2;
+        constexpr int RB = N * (int)sizeof(IO), ROWS = 32 * T, CHUNKS = RB / 16, CPT = STAGED ? (ROWS * CHUNKS + NT - 1) / NT : 1;       // bytes of a row, its chunks, chunks of a thread
+        RawFew<IO, STAGED ? 16 / (int)sizeof(IO) : NS> rB[STAGED ? CPT : T], rC[STAGED ? CPT : T];
         {
             const IO *BmT = Bm + l0 * N, *CmT = Cm + l0 * N;
-            const int first = piece_of<PAIR>((int)(fresh(tid) & 31)) * T;
+            const unsigned t0 = fresh(tid);
+            if constexpr (STAGED) {
 #pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const int step = first + t;
-                const int row = step < rem ? step : rem - 1;
-                load_few_raw<IO, NS>(BmT + (unsigned)(row * N + n0), 0, NS, true, rB[t]);
-                load_few_raw<IO, NS>(CmT + (unsigned)(row * N + n0), 0, NS, true, rC[t]);
+                for (int k = 0; k < CPT; ++k) {
+                    const unsigned i = t0 + k * NT;
+                    int row = i / CHUNKS;
+                    if (!FULL || ROWS * CHUNKS % NT) row = row < rem ? row : rem - 1;
+                    const unsigned at = row * N + i % CHUNKS * (16 / (int)sizeof(IO));
+                    load_at<IO, 16 / (int)sizeof(IO)>(BmT, at, rB[k]);
+                    load_at<IO, 16 / (int)sizeof(IO)>(CmT, at, rC[k]);
+                }
+            } else {
+                const int first = piece_of<PAIR>((int)(t0 & 31)) * T;
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const int step = first + t;
+                    const int row = step < rem ? step : rem - 1;
+                    load_few_raw<IO, NS>(BmT + (unsigned)(row * N + n0), 0, NS, true, rB[t]);
+                    load_few_raw<IO, NS>(CmT + (unsigned)(row * N + n0), 0, NS, true, rC[t]);
+                }
             }
         }
+        // (in the places of partial sums, of the first buffer and of the second; the first pair's inputs lie before those)
+        char *mB = reinterpret_cast<char *>(sPair + 3 * PL), *mC = reinterpret_cast<char *>(sPair + (3 * PL + (NB - 1) * BUF));
+        auto row_at = [](unsigned row) { return row * RB + row / 8 * 16; };
+        static_assert(!STAGED || 256 * RB + 32 * 16 <= 3 * W * PL * (int)sizeof(float), "a map in the partial sums' place");
+        auto stage_maps = [&]() {
+            const unsigned t0 = fresh(tid);
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) {
+                const unsigned i = t0 + k * NT, at = row_at(i / CHUNKS) + i % CHUNKS * 16;
+                if (ROWS * CHUNKS % NT && i >= ROWS * CHUNKS) break;
+                *reinterpret_cast<uint4 *>(mB + at) = make_uint4(rB[k].w[0], rB[k].w[1], rB[k].w[2], rB[k].w[3]);
+                *reinterpret_cast<uint4 *>(mC + at) = make_uint4(rC[k].w[0], rC[k].w[1], rC[k].w[2], rC[k].w[3]);
+            }
+        };
 
         // ---- per-step inputs of a pair of channels are fetched one pair ahead.  Row pointers: this thread's channel of
         // the pair the next fetch reads and the next epilogue writes (past the last channel they stay on a valid one).
@@ -405,18 +436,28 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
 
         // ---- Bm, Cm columns and the sums of dBm, dCm over channels stay in registers
         float Bv[NS][T], Cv[NS][T], dB[NS][T], dC[NS][T];
+        auto take_maps = [&]() {
+            const int first = piece_of<PAIR>((int)(fresh(tid) & 31)) * T;
 #pragma unroll
-        for (int t = 0; t < T; ++t) {
-            float tb[NS], tc[NS];
-            unpack_few<IO, NS>(rB[t], tb);
-            unpack_few<IO, NS>(rC[t], tc);
-            const bool ok = piece_of<PAIR>(li) * T + t < rem;
+            for (int t = 0; t < T; ++t) {
+                float tb[NS], tc[NS];
+                if constexpr (STAGED) {
+                    const unsigned at = row_at(first + t) + n0 * (unsigned)sizeof(IO);
+                    load_row<IO, NS>(reinterpret_cast<const IO *>(mB + at), tb);
+                    load_row<IO, NS>(reinterpret_cast<const IO *>(mC + at), tc);
+                } else {
+                    unpack_few<IO, NS>(rB[t], tb);
+                    unpack_few<IO, NS>(rC[t], tc);
+                }
+                const bool ok = FULL || first + t < rem;
 #pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                Bv[s][t] = ok ? tb[s] : 0.0f; Cv[s][t] = ok ? tc[s] : 0.0f;
-                dB[s][t] = 0.0f; dC[s][t] = 0.0f;
+                for (int s = 0; s < NS; ++s) {
+                    Bv[s][t] = ok ? tb[s] : 0.0f; Cv[s][t] = ok ? tc[s] : 0.0f;
+                    dB[s][t] = 0.0f; dC[s][t] = 0.0f;
+                }
             }
-        }
+        };
+        if constexpr (!STAGED) take_maps();
 
         // kept in registers from a pair's prologue to its epilogue: d softplus / ds and the factor that turns ypre into dz
         struct Kept { float sg[TPT], zf[TPT]; } even, odd;
@@ -738,6 +779,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
                 }
         };
         __syncthreads();                                 // the tables (first tile) are in place; the tile before is done
+        if constexpr (STAGED) stage_maps();
         if constexpr (OWN) {
             for (int g = 0; g < Gact; g += CP) {
                 const unsigned t0 = fresh(tid);
@@ -784,6 +826,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p)
             constexpr auto nothing = [] {};
             bias = sBias[c_own];
             next_inputs(0, even, 0);
+            if constexpr (STAGED) { __syncthreads(); take_maps(); }
             if constexpr (NB == 2) {
                 // Between two barriers a wavefront finishes the pair before (its partial sums are complete), runs the main
                 // part of this pair and prepares the next one: nobody waits in between.  (Two barriers per pair cost 4 %.)  Written out for the
