@@ -237,7 +237,8 @@ int lrnnx_selective_scan_bwd_complex(const lrnnx_ss_bwd_complex_args *args);
  * delta_bias, z and x0.  The state is recomputed tile by tile from checkpoints and
  * never stored per step (Sec. 3).  `ckpt` is the array a forward call wrote for the
  * same inputs; if NULL the library first runs a state-only forward sweep into
- * `workspace`.  lrnnx_workspace_bytes(LRNNX_WS_BWD, ...) covers that sweep and the chunk aggregates of the
+ * `workspace`, cut into chunks like a forward call with few long rows if the workspace has room for their
+ * aggregates.  lrnnx_workspace_bytes(LRNNX_WS_BWD, ...) covers that sweep and the chunk aggregates of the
  * chunked path (`path`); with `ckpt` given, LRNNX_WS_BWD_CARRY bytes are enough for the latter, and with a
  * workspace too small for it (or none) the call runs as a single pass.
  * Outputs du, ddelta, dz: io_dtype, written once each.  dA[D,N], dBm, dCm[B,L,N],

@@ -116,6 +116,15 @@ size_t cbwd_carry_bytes(int64_t B, int64_t D, int64_t N, int64_t L) {    // the 
     return nch > 1 ? (size_t)2 * B * D * nch * N * sizeof(float2) : 0;
 }
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
+// Chunks of the time axis of the recompute sweep of a real backward call (1: none), and the bytes of their aggregates, which lie behind the
+// checkpoints, where the backward pass puts its own afterwards.  By the rule of the forward pass: the sweep is that pass without its outputs,
+// and as one chain a row it was what a call with few long rows waited for.  Whole calls, one chain and in chunks (us; bf16, N = 16, one
+// batch entry): 16 channels, 65536 steps 468 and 92; 64, 16384 175 and 87; 256, 4096 103 and 86; 768, 16384 308 and 276; N = 4, 64
+// channels, 65536 steps 242 and 93.  Where the rule keeps one chain, nothing changes.
+int sweep_chunks(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L, bool f32) {
+    return fwd_chunks_pay(B, bcg, dpg, N, L, f32) ? fwd_chunks(B, bcg * dpg, L, false) : 1;
+}
+size_t sweep_bytes(int64_t B, int64_t D, int64_t N, int chunks) { return chunks > 1 ? (size_t)2 * B * D * chunks * N * sizeof(float) : 0; }
 
 // Launch plan of a backward call.  A batch [B,D,L] is planned as it is.  Of a packed batch the host knows the number of
 // sequences and the length of the time axis, and max_seqlen if the caller gave it (else 0): the single pass is planned
@@ -295,7 +304,13 @@ size_t lrnnx_workspace_bytes(int which, int64_t B, int64_t D, int64_t N, int64_t
             ck = align256((size_t)(packed ? D * lrnnx_packed_ckpt_slots(L, B) : B * D * cdiv(L, kCkptInterval)) * N * es);
         const size_t carry = cplx ? cbwd_carry_bytes(B * bcg, D / bcg, N, L) : bwd_carry_bytes(B * bcg, D / bcg, N, L);
         const size_t order = packed ? sizeof(int) * (size_t)B : 0;
-        const size_t base = ck + (carry > order ? carry : order);
+        size_t base = carry > order ? carry : order;
+        if (which == LRNNX_WS_BWD && !packed)            // (of either type)
+            for (const bool f32 : {false, true}) {
+                const size_t sweep = sweep_bytes(B, D, N, sweep_chunks(B, bcg, D / bcg, N, L, f32));
+                if (base < sweep) base = sweep;
+            }
+        base += ck;
         if (!cplx) return base;
         const size_t sums = bwd_sums_bytes(cbwd_plan, 2, B, D, N, L, bcg, packed != 0);
         return cbwd_sums_pay((int)N, cdiv(L, kBwdTileSteps), packed != 0, sums) ? base + sums + 512 : base;
@@ -573,15 +588,20 @@ size_t lrnnx_selective_scan_bwd_workspace_bytes(const lrnnx_ss_bwd_args *a) {
     const BwdPlan pl = plan_bwd(p, a, bcg);
     set_bwd_shape(p, a, pl);
     size_t n = a->ckpt ? 0 : align256(bwd_ckpt_bytes(a));
+    auto with_sweep = [&, ck = n](size_t n) {
+        if (a->ckpt || a->cu_seqlens || a->path == LRNNX_PATH_SINGLE_PASS) return n;
+        const size_t sweep = ck + sweep_bytes(a->B, a->D, a->N, sweep_chunks(a->B, bcg, a->D / bcg, a->N, a->L, a->io_dtype == LRNNX_F32));
+        return n < sweep ? sweep : n;
+    };
     if (pl.nchunks > 1) n += (size_t)2 * a->B * a->D * pl.nchunks * a->N * sizeof(float);
     n += bwd_order_bytes(a, pl.nchunks);
     // A batch of one tile and many blocks of channels: a workgroup adds to dBm and dCm once, and atomics are done before a second
     // launch could start (L = 256, bf16: 1024 rows, N = 16 27 us, with the workspace 32, N = 4 19 and 20; 4096 rows 44 and
     // 49, 27 and 29).  Few blocks of many states take as long either way or longer (256 rows, N = 32: 33 and 32 us), and
     // with N <= 2 the additions collide within a wavefront (4096 rows, N = 1: 37 and 27).
-    if (!a->cu_seqlens && a->L <= kBwdTileSteps && a->N >= 4 && bwd_grid_x(p) >= (a->N > 8 ? 2 * a->N : 16) * bcg) return n;
+    if (!a->cu_seqlens && a->L <= kBwdTileSteps && a->N >= 4 && bwd_grid_x(p) >= (a->N > 8 ? 2 * a->N : 16) * bcg) return with_sweep(n);
     const size_t sums = bwd_part_bytes(a->N, bwd_tile_slots(a), bwd_grid_x(p));
-    return sums <= kBwdSumsCap ? n + 256 + sums : n;          // (256: the sums start on such a boundary)
+    return with_sweep(sums <= kBwdSumsCap ? n + 256 + sums : n);          // (256: the sums start on such a boundary)
 }
 
 int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
@@ -636,6 +656,19 @@ int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
         f.ckpt = reinterpret_cast<float *>(a->workspace);
         f.vec = row_vec_ok(a->u, f.u_sb, f.u_sd, es) && row_vec_ok(a->delta, f.dl_sb, f.dl_sd, es);
         f.mode = MODE_CKPT_ONLY; f.nchunks = 1; f.tiles_per_chunk = cdiv(a->L, fwd_tile_steps());
+        // few long rows: in chunks of the time axis, like the forward pass, if the workspace has room for their aggregates
+        const int nch = cu || path == LRNNX_PATH_SINGLE_PASS ? 1 : sweep_chunks(a->B, bcg, f.dpg, a->N, a->L, a->io_dtype == LRNNX_F32);
+        if (nch > 1 && a->workspace_bytes >= carry_off && sweep_bytes(a->B, a->D, a->N, nch) <= a->workspace_bytes - carry_off) {
+            f.tiles_per_chunk = cdiv(f.tiles_per_chunk, nch);
+            f.nchunks = (int)cdiv(cdiv(a->L, fwd_tile_steps()), f.tiles_per_chunk);          // no empty trailing chunk
+            f.ws_P = reinterpret_cast<float *>(static_cast<char *>(a->workspace) + carry_off);
+            f.ws_S = f.ws_P + (size_t)a->B * a->D * f.nchunks * a->N;
+            FwdParams fa = f;
+            fa.mode = MODE_AGG; fa.ckpt = nullptr;
+            if (launch_ss_fwd(fa, a->io_dtype, a->disc, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
+            if (launch_ss_carry(f, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
+            f.mode = MODE_CKPT_APPLY;
+        }
         if (launch_ss_fwd(f, a->io_dtype, a->disc, s) != hipSuccess) return LRNNX_ERR_LAUNCH;
         ckpt = f.ckpt;
     }

@@ -8,7 +8,7 @@ constexpr int kNumCU = 256;              // MI355X
 
 constexpr int64_t kCkptInterval = 256;   // steps between state checkpoints (public: lrnnx_ckpt_interval)
 
-enum : int { MODE_FULL = 0, MODE_AGG = 1, MODE_APPLY = 2, MODE_CKPT_ONLY = 3 };
+enum : int { MODE_FULL = 0, MODE_AGG = 1, MODE_APPLY = 2, MODE_CKPT_ONLY = 3, MODE_CKPT_APPLY = 4 };
 
 struct FwdParams {
     int B, D, N;
