@@ -65,15 +65,30 @@ __device__ __forceinline__ void store_at(float *row, unsigned byte_off, float v)
 //   states are read next by the adjoint, and its stores stay ordinary (non-temporal: 127 -> 133).
 // - What an adjoint reads is read once, if the rows of P values are whole cache lines: then its loads are
 //   non-temporal too (485 -> 458, 118.5 -> 116).  Rows that are not share their lines with the neighbouring
-//   workgroup's (P = 1000 real, 8 x 4096 steps: 277 and 292 with such loads).
+//   workgroup's (P = 1000 real, 8 x 4096 steps: 234 and 242 with such loads; P = 777, 1 x 13476 84 and 98); 8-byte values share fewer and
+//   gain from 256 MiB of loads on, the size of the Infinity Cache (LTI, P = 600, 16 x 2000 steps 154 -> 147; with less P = 333, 2 x 9000 63 and 70).
 // - The forward's loads likewise, but only from 384 MiB of traffic on, one and a half times the 256 MiB of Infinity Cache: there
 //   458 -> 440 (complex coefficients, P = 1024, 8 x 4096: 397 -> 378); with less the inputs are often still in it (real
-//   coefficients, 8 x 2048 steps: 116 and 120).
+//   coefficients, 8 x 2048 steps: 116 and 120).  Rows of 8-byte values that are not whole lines, both rules together: LTI, P = 1001,
+//   8 x 8192 568 -> 545; complex coefficients, P = 1000, 8 x 4096 401 -> 386, P = 1237, 3 x 4000 206 -> 199.
 constexpr int64_t kCacheLine = 128;
-constexpr int64_t kStreamPastCaches = 384ll << 20;
+constexpr int64_t kStreamPastCaches = 384ll << 20, kPastInfinityCache = 256ll << 20;
 inline bool whole_lines(int64_t row_bytes, const void *a, const void *b, const void *c) {
     return ((row_bytes | (int64_t)(intptr_t)a | (int64_t)(intptr_t)b | (int64_t)(intptr_t)c) & (kCacheLine - 1)) == 0;
 }
+
+// The slab a workgroup takes: workgroup j of the n of one group of steps.  Consecutive workgroups run on the 8 dies in turn, each with an L2
+// of its own; with `deal` the slabs go out so that each die gets a run of neighbours, which share the cache lines at their borders: read
+// from memory once then, and the two parts of a line written meet in one L2.
+__device__ __forceinline__ int slab_of(unsigned j, unsigned n, int deal) {
+    const unsigned c = j & 7;
+    return (int)(deal ? c * (n >> 3) + (c < (n & 7) ? c : (n & 7)) + (j >> 3) : j);
+}
+// Where dealing pays (a forward call and its adjoint, us, in turn and dealt): rows that are not whole lines (LTI, P = 1001, 8 x 8192 steps 632
+// and 568, P = 207, 20 x 1265 56 and 50; real coefficients, P = 129, 16 x 8001 158 and 130, P = 1000, 8 x 4096 257 and 234; complex, P = 1001,
+// 8 x 2048 254 and 233), and many slabs also where they share nothing (P = 1024, 8 x 2048: real 106.6 and 102.8, complex 212 and 203).  Few
+// slabs of whole lines are as fast or faster in turn (LTI, P = 1024, 1 x 16384: 124 and 127; P = 256, 4 x 4096 40.0 and 40.5).
+inline int deal_slabs(bool whole, unsigned n) { return !whole || n >= 64; }
 
 // A published slot is an 8-byte complex value written by one relaxed atomic store at agent scope; kNotReady
 // (all ones, a NaN pattern that arithmetic does not produce from other inputs) marks an empty slot, and a

@@ -30,7 +30,8 @@ __global__ __launch_bounds__(GW * 64) void k_diag_scan(const DiagParams p) {
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int npslab = (p.P + 63) / 64;
-    const int pslab = blockIdx.x % npslab, b = blockIdx.x / npslab;
+    const int slab = slab_of(blockIdx.x, gridDim.x, p.deal);
+    const int pslab = slab % npslab, b = slab / npslab;
     const int g = blockIdx.y;
     const int pp = pslab * 64 + lane;
     const unsigned boff = (unsigned)pp * (unsigned)sizeof(E);
@@ -204,9 +205,10 @@ int diag_scan_anchor(int is_complex) { return is_complex ? kDsCplxAnchor : kAnch
 int diag_scan_bwd_group_steps(int is_complex) { return (is_complex ? kDsBwdCplxCS : kDsCS) * kDsBwdGW; }
 
 template <bool CPLX, int CS, int GW, int ANCH, bool BWD>
-static void launch_diag(const DiagParams &p, bool nt, hipStream_t s) {
+static void launch_diag(DiagParams p, bool whole, bool nt, hipStream_t s) {
     const int npslab = (p.P + 63) / 64;
     dim3 grid((unsigned)(npslab * p.B), p.ngroups);
+    p.deal = deal_slabs(whole, grid.x);
     if (nt) hipLaunchKernelGGL((k_diag_scan<CPLX, CS, GW, ANCH, BWD, true>), grid, dim3(GW * 64), 0, s, p);
     else hipLaunchKernelGGL((k_diag_scan<CPLX, CS, GW, ANCH, BWD, false>), grid, dim3(GW * 64), 0, s, p);
 }
@@ -214,17 +216,19 @@ static void launch_diag(const DiagParams &p, bool nt, hipStream_t s) {
 static int64_t row_bytes(const DiagParams &p) { return (int64_t)p.P * (p.is_complex ? 8 : 4); }
 
 hipError_t launch_diag_scan(const DiagParams &p, hipStream_t s) {
-    const bool nt = whole_lines(row_bytes(p), p.a, p.b, p.x) && 3 * row_bytes(p) * p.B * p.L >= kStreamPastCaches;
-    if (p.is_complex) launch_diag<true, kDsCS, kDsCplxGW, kDsCplxAnchor, false>(p, nt, s);
-    else if (ds_gw(p.B, p.P, 0) == kDsGWSmall) launch_diag<false, kDsCS, kDsGWSmall, kAnchor, false>(p, nt, s);
-    else launch_diag<false, kDsCS, kDsGWLarge, kAnchor, false>(p, nt, s);
+    const bool whole = whole_lines(row_bytes(p), p.a, p.b, p.x);
+    const bool nt = (whole || p.is_complex) && 3 * row_bytes(p) * p.B * p.L >= kStreamPastCaches;
+    if (p.is_complex) launch_diag<true, kDsCS, kDsCplxGW, kDsCplxAnchor, false>(p, whole, nt, s);
+    else if (ds_gw(p.B, p.P, 0) == kDsGWSmall) launch_diag<false, kDsCS, kDsGWSmall, kAnchor, false>(p, whole, nt, s);
+    else launch_diag<false, kDsCS, kDsGWLarge, kAnchor, false>(p, whole, nt, s);
     return hipGetLastError();
 }
 
 hipError_t launch_diag_scan_bwd(const DiagParams &p, hipStream_t s) {
-    const bool nt = whole_lines(row_bytes(p), p.a, p.b, p.xs) && whole_lines(0, p.x, p.da, nullptr);
-    if (p.is_complex) launch_diag<true, kDsBwdCplxCS, kDsBwdGW, kDsCplxAnchor, true>(p, nt, s);
-    else launch_diag<false, kDsCS, kDsBwdGW, kAnchor, true>(p, nt, s);
+    const bool whole = whole_lines(row_bytes(p), p.a, p.b, p.xs) && whole_lines(0, p.x, p.da, nullptr);
+    const bool nt = whole || (p.is_complex && 3 * row_bytes(p) * p.B * p.L >= kPastInfinityCache);
+    if (p.is_complex) launch_diag<true, kDsBwdCplxCS, kDsBwdGW, kDsCplxAnchor, true>(p, whole, nt, s);
+    else launch_diag<false, kDsCS, kDsBwdGW, kAnchor, true>(p, whole, nt, s);
     return hipGetLastError();
 }
 

@@ -152,6 +152,7 @@ struct LtiParams {
     int B, P;
     int64_t L;
     int nchunks, ngroups;    // chunks, and groups of 4 consecutive chunks
+    int deal;                // single pass: the order of the slabs (set by the launcher)
     int64_t chunk;           // time steps per chunk
     const float2 *lambda, *v, *x0;
     float2 *x, *x_last;
@@ -172,6 +173,7 @@ struct DiagParams {
     int B, P;
     int64_t L;
     int is_complex, ngroups;
+    int deal;                // the order of the slabs (set by the launcher)
     const void *a, *b, *x0;  // [B,L,P], [B,L,P], [B,P] of float or float2
     void *x, *x_last;
     float2 *ws_T;            // [B,ngroups,slots,P] group aggregates (slots: 1 real = (A,S); 2 complex = A, S)

@@ -105,7 +105,8 @@ __global__ __launch_bounds__(kOneGW * 64) void k_lti_onepass(const LtiParams p) 
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int npslab = (p.P + 63) / 64;
-    const int pslab = blockIdx.x % npslab, b = blockIdx.x / npslab;
+    const int slab = slab_of(blockIdx.x, gridDim.x, p.deal);
+    const int pslab = slab % npslab, b = slab / npslab;
     const int g = blockIdx.y;
     const int pp = pslab * 64 + lane;
     const unsigned boff = (unsigned)pp * 8u;                   // the lane's byte offset within a row of P values
@@ -261,24 +262,28 @@ int lti_onepass_anchor() { return kAnchor; }
 int lti_chunk_group() { return kLtiWaves; }
 
 template <int GW, bool BWD>
-static void launch_onepass(const LtiParams &p, bool nt, hipStream_t s) {
+static void launch_onepass(LtiParams p, bool whole, bool nt, hipStream_t s) {
     constexpr int CS = BWD ? kOneBwdCS : kOneCS;
     const int npslab = (p.P + 63) / 64;
     dim3 grid((unsigned)(npslab * p.B), p.ngroups);
+    p.deal = deal_slabs(whole, grid.x);
     if (nt) hipLaunchKernelGGL((k_lti_onepass<CS, GW, BWD, true>), grid, dim3(GW * 64), 0, s, p);
     else hipLaunchKernelGGL((k_lti_onepass<CS, GW, BWD, false>), grid, dim3(GW * 64), 0, s, p);
 }
 
 hipError_t launch_lti_onepass(const LtiParams &p, hipStream_t s) {
     const int64_t row = (int64_t)p.P * sizeof(float2);
-    const bool nt = whole_lines(row, p.v, p.x, nullptr) && 2 * row * p.B * p.L >= kStreamPastCaches;
-    if (onepass_gw(p.B, p.P) == kOneGWSmall) launch_onepass<kOneGWSmall, false>(p, nt, s);
-    else launch_onepass<kOneGWLarge, false>(p, nt, s);
+    const bool whole = whole_lines(row, p.v, p.x, nullptr);
+    const bool nt = 2 * row * p.B * p.L >= kStreamPastCaches;
+    if (onepass_gw(p.B, p.P) == kOneGWSmall) launch_onepass<kOneGWSmall, false>(p, whole, nt, s);
+    else launch_onepass<kOneGWLarge, false>(p, whole, nt, s);
     return hipGetLastError();
 }
 
 hipError_t launch_lti_onepass_bwd(const LtiParams &p, hipStream_t s) {
-    launch_onepass<kOneBwdGW, true>(p, whole_lines((int64_t)p.P * sizeof(float2), p.v, p.xs, p.x), s);
+    const int64_t row = (int64_t)p.P * sizeof(float2);
+    const bool whole = whole_lines(row, p.v, p.xs, p.x);
+    launch_onepass<kOneBwdGW, true>(p, whole, whole || 2 * row * p.B * p.L >= kPastInfinityCache, s);
     return hipGetLastError();
 }
 
