@@ -215,8 +215,11 @@ __device__ __forceinline__ int channels_of(const BwdParams &p, int64_t ntiles) {
     return fit < p.gmin ? p.gmin : (fit < p.G ? (int)fit & ~1 : p.G);      // (channels are walked in pairs)
 }
 
+// Two wavefronts a SIMD, also where the registers would let in a third (few states without a gate): single-wavefront workgroups then crowd
+// some SIMDs and leave others to one (N = 4, bf16, 140 rows of 42166 steps 58 and 66 us with up to three; with the forward pass,
+// 6144 rows of 2048 steps 111 and 117, N = 1 67 and 70).
 template <typename IO, int N, int DISC, bool HAS_Z, bool PART>
-__global__ __launch_bounds__(BwdGeom<N>::NT, 2) void k_ss_bwd(const BwdParams p) {
+__global__ __launch_bounds__(BwdGeom<N>::NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_ss_bwd(const BwdParams p) {
     using GE = BwdGeom<N>;
     constexpr int W = GE::W, NS = GE::NS, NT = GE::NT, CP = GE::CP;
     constexpr int TILE = kBwdTileSteps;
