@@ -68,6 +68,16 @@ __device__ __forceinline__ float2 cbilinear_q(float dt, const CCoef &c) {
 }
 __device__ __forceinline__ float2 cbilinear_a(float2 q) { return make_float2(__builtin_fmaf(2.0f, q.x, -1.0f), 2.0f * q.y); }
 
+// c0 + c1 z + .. + c4 z^4 with real coefficients, z = (zr, zi), s = |z|^2: by z^2 = 2 zr z - s, nine instructions; Horner's rule in complex
+// arithmetic took twelve to fourteen for one power less.  In the exact zero-order hold this and sums without intermediate results are 5 % of the
+// whole training step (8 x 768 rows of 2048 steps, N = 16, bf16 1185 -> 1121 us), and the largest relative error of the two series up to
+// |z| = 1/8 is 1.5e-7 where it was 3.6e-6.
+__device__ __forceinline__ float2 creal_quartic(float zr, float zi, float s, float c0, float c1, float c2, float c3, float c4) {
+    const float r = zr + zr, b3 = __builtin_fmaf(r, c4, c3), b2 = __builtin_fmaf(r, b3, __builtin_fmaf(-s, c4, c2)),
+                b1 = __builtin_fmaf(r, b2, __builtin_fmaf(-s, b3, c1));
+    return make_float2(__builtin_fmaf(zr, b1, __builtin_fmaf(-s, b2, c0)), zi * b1);
+}
+
 // multiplier a and input gain g of one step (schemes of Sec. 3, complex arithmetic)
 template <int DISC>
 __device__ __forceinline__ void cdisc_ag(float dt, const CCoef &c, float2 &a, float2 &g) {
@@ -81,16 +91,13 @@ __device__ __forceinline__ void cdisc_ag(float dt, const CCoef &c, float2 &a, fl
         else if constexpr (DISC == DISC_DIRAC) g = make_float2(1.0f, 0.0f);
         else {                                                              // exact ZOH: (a - 1) / A
             const float zr = dt * c.Ar, zi = dt * c.Ai;
-            // small |z|: dt (1 + z/2 + z^2/6 + z^3/24), Horner in complex arithmetic
-            float pr = 1.0f + zr * 0.25f, pi = zi * 0.25f;                  // 1 + z/4
-            float tr = pr * zr - pi * zi, ti = pr * zi + pi * zr;           // z (1 + z/4)
-            pr = 1.0f + tr * 0.33333334f; pi = ti * 0.33333334f;            // 1 + z/3 (1 + z/4)
-            tr = pr * zr - pi * zi; ti = pr * zi + pi * zr;
-            pr = 1.0f + tr * 0.5f; pi = ti * 0.5f;                          // 1 + z/2 (1 + z/3 (1 + z/4))
-            const float sr = dt * pr, si = dt * pi;
+            // small |z|: dt (1 + z/2 + z^2/6 + z^3/24 + z^4/120)
+            const float s2 = __builtin_fmaf(zr, zr, zi * zi);
+            const float2 ser = creal_quartic(zr, zi, s2, 1.0f, 0.5f, 0.16666667f, 0.041666668f, 0.0083333338f);
+            const float sr = dt * ser.x, si = dt * ser.y;
             const float mr = a.x - 1.0f, mi = a.y;
             const float dr = mr * c.iAr - mi * c.iAi, di = mr * c.iAi + mi * c.iAr;
-            const bool small = zr * zr + zi * zi < 0.015625f;
+            const bool small = s2 < 0.015625f;
             g = make_float2(small ? sr : dr, small ? si : di);
         }
     }
@@ -129,16 +136,14 @@ __device__ __forceinline__ float2 cxfma(float2 a, float2 b, float2 c) {   // a *
 }
 
 // dg/dA of one step of the exact zero-order hold, given its a and g (holomorphic in A; the other partials are written out where they
-// are used): (dt A a - (a - 1)) / A^2 = (dt a - g) / A; for small z = dt A: dt^2 (1/2 + z/3 + z^2/8 + z^3/30)
+// are used): (dt A a - (a - 1)) / A^2 = (dt a - g) / A; for small z = dt A: dt^2 (1/2 + z/3 + z^2/8 + z^3/30 + z^4/144)
 __device__ __forceinline__ float2 czoh_gain_dA(float dt, const CCoef &c, float2 a, float2 g) {
-    const float2 z = make_float2(dt * c.Ar, dt * c.Ai);
-    float2 s = make_float2(0.125f + z.x * 0.033333335f, z.y * 0.033333335f);
-    s = cxmul(s, z); s.x += 0.33333334f;
-    s = cxmul(s, z); s.x += 0.5f;
+    const float zr = dt * c.Ar, zi = dt * c.Ai, s2 = __builtin_fmaf(zr, zr, zi * zi);
+    const float2 s = creal_quartic(zr, zi, s2, 0.5f, 0.33333334f, 0.125f, 0.033333335f, 0.0069444445f);
     const float d2 = dt * dt;
     const float2 big = cxmul(make_float2(__builtin_fmaf(dt, a.x, -g.x), __builtin_fmaf(dt, a.y, -g.y)),
                              make_float2(c.iAr, c.iAi));
-    const bool small = z.x * z.x + z.y * z.y < 0.015625f;
+    const bool small = s2 < 0.015625f;
     return make_float2(small ? d2 * s.x : big.x, small ? d2 * s.y : big.y);
 }
 

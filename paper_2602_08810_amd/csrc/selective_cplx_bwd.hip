@@ -552,12 +552,12 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
                         const CCoef cc = make_ccoef(Av.x, Av.y);
                         const float2 a = hd[t], g = gg[t], g_A = czoh_gain_dA(dl[t], cc, a, g);
                         const float2 q = cxmul(Gin, xprev);
-                        const float d = __builtin_fmaf(q.x, Av.x, __builtin_fmaf(-q.y, Av.y, __builtin_fmaf(gq.x, a.x, -gq.y * a.y)));
-                        const float2 e = cxfma(gq, g_A, make_float2(q.x * dl[t], q.y * dl[t]));
-                        dAp = make_float2(dAp.x + e.x, dAp.y + e.y);
+                        acc(pd[t], q.x, Av.x);
+                        pd[t] = __builtin_fmaf(-q.y, Av.y, pd[t]);
+                        pd[t] = __builtin_fmaf(gq.x, a.x, __builtin_fmaf(-gq.y, a.y, pd[t]));
+                        dAp = cxfma(gq, g_A, make_float2(__builtin_fmaf(q.x, dl[t], dAp.x), __builtin_fmaf(q.y, dl[t], dAp.y)));
                         acc(pu[t], hb.x, g.x);
                         pu[t] = __builtin_fmaf(-hb.y, g.y, pu[t]);
-                        pd[t] = s == 0 ? d : pd[t] + d;
                         const float2 kg = cxmul(K, g);
                         dB[s][t] = make_float2(__builtin_fmaf(kg.x, du[t], dB[s][t].x), __builtin_fmaf(kg.y, du[t], dB[s][t].y));
                     } else {
