@@ -243,7 +243,7 @@ int lrnnx_selective_scan_bwd_complex(const lrnnx_ss_bwd_complex_args *args);
  * workspace too small for it (or none) the call runs as a single pass.
  * Outputs du, ddelta, dz: io_dtype, written once each.  dA[D,N], dBm, dCm[B,L,N],
  * dD[D], dbias[D]: float, OVERWRITTEN (the library clears them on the stream, then
- * accumulates with atomics: their last bits may differ from run to run).
+ * accumulates with atomics, or, with room in the workspace, adds up partial sums: their last bits may differ from run to run).
  * dx0[B,D,N] float.  Optional (NULL allowed): Dskip, delta_bias, z, x0, ckpt, dD,
  * dbias, dz, dx0.  dD requires Dskip, dbias requires delta_bias, dz requires z.    */
 typedef struct lrnnx_ss_bwd_args {
@@ -505,9 +505,9 @@ typedef enum { LRNNX_WS_FWD = 0, LRNNX_WS_BWD = 1, LRNNX_WS_LTI = 2, LRNNX_WS_LT
                LRNNX_WS_BWD_CARRY = 7,  /* the chunk aggregates of lrnnx_selective_scan_bwd alone (ckpt supplied) */
                LRNNX_WS_FWD_COMPLEX = 8,
                LRNNX_WS_BWD_SUMS = 9    /* optional, in addition to LRNNX_WS_BWD or LRNNX_WS_BWD_CARRY: partial sums of dBm
-                                         * and dCm, at most 512 MiB.  With room for all of them they are added up by a
-                                         * second launch, in a fixed order; else by float atomics, which is the slower way
-                                         * for launches that need no more than that */
+                                         * and dCm, and of dA, dD and dbias over few batch entries, at most 512 MiB.  With
+                                         * room for all of them they are added up by a second launch, in a fixed order; else
+                                         * by float atomics, which is the slower way for launches that need no more than that */
              } lrnnx_ws_kind;
 
 /* Bytes of device scratch the call may need (the largest over its paths).  bc_groups as in the call's struct (0 or 1:

@@ -54,6 +54,17 @@ struct CFwdParams {
 };
 
 // backward of the same
+// Where a backward workgroup leaves its channels' sums of dA, dD and dbias.  sb < 0: added with float atomics to the call's own arrays, which
+// a launch has cleared before.  sb >= 0: stored, at b * sb floats behind these pointers; a channel of a batch entry then has one
+// workgroup, and the launch that adds up the tile sums of dBm and dCm adds up the batch entries as well, its workgroups from `first`
+// on (sb > 0), or there is one batch entry and these are the call's arrays (sb = 0).
+struct RowSums {
+    float *A, *D, *b;
+    int64_t sb;
+    unsigned first;
+};
+constexpr int kRowSumsMaxB = 32;     // batch entries that a thread adds up
+
 struct CBwdParams {
     int B, D, N;
     int64_t L;
@@ -80,6 +91,7 @@ struct CBwdParams {
     int wcap, gmin;          // packed mode with a known longest sequence: as in BwdParams
     float *part;             // workspace of the tile sums of dBm and dCm, as in BwdParams (two floats a state), or null
     int64_t part_tiles;
+    RowSums rows;
 };
 
 struct BwdParams {
@@ -118,6 +130,7 @@ struct BwdParams {
     // (a packed batch counts its tiles like its checkpoint slots).
     float *part;
     int64_t part_tiles;
+    RowSums rows;
 };
 constexpr int kBwdTileSteps = 256;
 constexpr int kBwdMinG = 4, kBwdMaxG = 128;   // channels of a workgroup (the most: it sizes the tables in LDS)

@@ -954,13 +954,20 @@ __global__ __launch_bounds__(BwdGeom<N>::NT) __attribute__((amdgpu_waves_per_eu(
     }
     __syncthreads();
     // ---- per-channel results of this workgroup
+    const bool own = PART && p.rows.sb >= 0;         // see RowSums
+    float *oA = p.dA, *oD = p.dD, *ob = p.dbias;
+    if (own) {
+        const int64_t at = b * p.rows.sb;
+        oA = p.rows.A + at; oD = oD ? p.rows.D + at : oD; ob = ob ? p.rows.b + at : ob;
+    }
+    auto leave = [&](float *at, float v) { if (own) *at = v; else unsafeAtomicAdd(at, v); };
     for (int i = tid; i < Gact * N; i += NT) {
-        unsafeAtomicAdd(p.dA + (int64_t)d0 * N + i, sdA[i]);
+        leave(oA + (int64_t)d0 * N + i, sdA[i]);
         if (p.dx0 && chunk == 0) p.dx0[((int64_t)b * p.D + d0) * N + i] = sH[i];
     }
     for (int g = tid; g < Gact; g += NT) {
-        if (p.dD) unsafeAtomicAdd(p.dD + d0 + g, sdDb[0][g]);
-        if (p.dbias) unsafeAtomicAdd(p.dbias + d0 + g, sdDb[1][g]);
+        if (oD) leave(oD + d0 + g, sdDb[0][g]);
+        if (ob) leave(ob + d0 + g, sdDb[1][g]);
     }
 }
 
@@ -989,6 +996,17 @@ __global__ __launch_bounds__(256) void k_ss_bwd_maps(const BwdParams p, int gx) 
     static_assert(LP * PIECES == 32 && (KS == 1 ? NE <= 256 : NE == 64 && KS == 4), "a thread for each element, a wavefront for each share of the blocks");
     __shared__ float sT[SP * (NW + 1)];
     __shared__ float4 sK[KS > 1 ? KS * NE : 1];
+    if (p.rows.sb > 0 && blockIdx.x >= p.rows.first) {       // dA, dD, dbias from what the workgroups left for each batch entry
+        const int64_t nA = (int64_t)p.D * N, e = (int64_t)(blockIdx.x - p.rows.first) * 256 + threadIdx.x;
+        if (blockIdx.y || blockIdx.z || e >= nA + 2 * p.D) return;
+        float *out = e < nA ? p.dA + e : e < nA + p.D ? (p.dD ? p.dD + (e - nA) : nullptr) : (p.dbias ? p.dbias + (e - nA - p.D) : nullptr);
+        if (!out) return;
+        float sum = 0.0f;
+#pragma unroll 8
+        for (int b = 0; b < p.B; ++b) sum += p.rows.A[b * p.rows.sb + e];
+        *out = sum;
+        return;
+    }
     const int n0 = (blockIdx.x % NP) * NW;
     const int piece = (blockIdx.x / NP) % PIECES;
     const int64_t slot = blockIdx.x / (NP * PIECES);
@@ -1121,8 +1139,11 @@ static hipError_t launch_bwd_maps_n(const BwdParams &p, int gx, hipStream_t s) {
     const int64_t wgs = pieces * 2 * p.bcg;
     const bool split = KS > 1 && gx / p.bcg > 16 && (2 * wgs < 3 * kNumCU || (p.cu && N <= 16 && wgs < 3 * kNumCU));
     dim3 g2((unsigned)(split ? pieces * KS : pieces), 2, p.bcg);
-    if (split) hipLaunchKernelGGL((k_ss_bwd_maps<N, KS>), g2, dim3(256), 0, s, p, gx);
-    else hipLaunchKernelGGL((k_ss_bwd_maps<N, 1>), g2, dim3(256), 0, s, p, gx);
+    BwdParams q = p;
+    q.rows.first = g2.x;
+    if (p.rows.sb > 0) g2.x += (unsigned)(((int64_t)p.D * (N + 2) + 255) / 256);
+    if (split) hipLaunchKernelGGL((k_ss_bwd_maps<N, KS>), g2, dim3(256), 0, s, q, gx);
+    else hipLaunchKernelGGL((k_ss_bwd_maps<N, 1>), g2, dim3(256), 0, s, q, gx);
     return hipGetLastError();
 }
 hipError_t launch_bwd_maps(const BwdParams &p, int gx, hipStream_t s) {

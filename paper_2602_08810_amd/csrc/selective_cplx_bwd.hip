@@ -781,15 +781,27 @@ __global__ __launch_bounds__(CBwdGeom<N>::NT, 2) void k_ss_cbwd(const CBwdParams
     }
     __syncthreads();
     // ---- per-channel results of this workgroup
+    // (the parameters read again: held in scalar registers all through the kernel they would push others out)
+    typedef const __attribute__((address_space(4))) CBwdParams KernArgs;
+    KernArgs *args = (KernArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    KernArgs &q = *args;
+    const bool own = q.rows.sb >= 0;                 // see RowSums
+    float *oA = reinterpret_cast<float *>(q.dA), *oD = q.dD, *ob = q.dbias;
+    if (own) {
+        const int64_t at = b * q.rows.sb;
+        oA = q.rows.A + at; oD = oD ? q.rows.D + at : oD; ob = ob ? q.rows.b + at : ob;
+    }
+    auto leave = [&](float *at, float v) { if (own) *at = v; else unsafeAtomicAdd(at, v); };
     for (int i = tid; i < Gact * N; i += NT) {
-        float *dst = reinterpret_cast<float *>(p.dA + (int64_t)d0 * N + i);
-        unsafeAtomicAdd(dst, sdA[i].x);
-        unsafeAtomicAdd(dst + 1, -sdA[i].y);
-        if (p.dx0 && chunk == 0) p.dx0[((int64_t)b * p.D + d0) * N + i] = make_float2(sH[i].x, -sH[i].y);
+        float *dst = oA + 2 * ((int64_t)d0 * N + i);
+        leave(dst, sdA[i].x);
+        leave(dst + 1, -sdA[i].y);
+        if (q.dx0 && chunk == 0) q.dx0[((int64_t)b * q.D + d0) * N + i] = make_float2(sH[i].x, -sH[i].y);
     }
     for (int g = tid; g < Gact; g += NT) {
-        if (p.dD) unsafeAtomicAdd(p.dD + d0 + g, sdD[g]);
-        if (p.dbias) unsafeAtomicAdd(p.dbias + d0 + g, sdb[g]);
+        if (oD) leave(oD + d0 + g, sdD[g]);
+        if (ob) leave(ob + d0 + g, sdb[g]);
     }
 }
 
@@ -801,9 +813,10 @@ static hipError_t launch_cbwd_n(const CBwdParams &p, hipStream_t s) {
     else hipLaunchKernelGGL((k_ss_cbwd<IO, N, DISC, false>), grid, block, 0, s, p);
     if (p.part) {
         BwdParams m{};
-        m.B = p.B; m.N = 2 * N; m.L = p.L; m.G = p.G; m.bcg = p.bcg; m.dpg = p.dpg; m.cu = p.cu; m.nslots = p.nslots;
+        m.B = p.B; m.D = p.D; m.N = 2 * N; m.L = p.L; m.G = p.G; m.bcg = p.bcg; m.dpg = p.dpg; m.cu = p.cu; m.nslots = p.nslots;
         m.dBm = reinterpret_cast<float *>(p.dBm); m.dCm = reinterpret_cast<float *>(p.dCm);
         m.wcap = p.wcap; m.gmin = p.gmin; m.part = p.part; m.part_tiles = p.part_tiles;
+        m.rows = p.rows; m.dA = reinterpret_cast<float *>(p.dA); m.dD = p.dD; m.dbias = p.dbias;
         return launch_bwd_maps(m, (int)grid.x, s);
     }
     return hipGetLastError();

@@ -1,0 +1,55 @@
+"""GPU parity of dA, dD and dbias where the workgroups of a backward call store their sums and a later launch adds up the batch entries: one
+entry, two, as many as a thread adds up and one more; with room for them in the workspace and, a word short, with atomics; real and complex."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_2602_08810_amd import workloads
+from _util import dev, host, rel_err, sel_inputs_dev
+
+pytestmark = pytest.mark.gpu
+TOL_F32 = 1e-4                                              # sums in float32, whatever the type of the inputs
+
+
+@pytest.mark.parametrize("B,D,N,L,G,skip", [(1, 37, 16, 300, 1, True), (2, 33, 4, 700, 1, True), (2, 1030, 16, 520, 2, False),
+                                            (32, 5, 8, 257, 1, True), (33, 5, 8, 257, 1, True), (5, 130, 32, 300, 1, True), (3, 40, 1, 600, 2, False)])
+def test_real(oracle, B, D, N, L, G, skip):
+    import torch
+    from paper_2602_08810_amd import api
+    p = workloads.make_selective(B=B, D=D, N=N, L=L, io="f32", gate=True, with_dy=True, seed=B + D, bc_groups=G)
+    if not skip:
+        p["Dskip"] = None
+    t, dy = sel_inputs_dev(p, "f32"), dev(p["dy"], "f32")
+    _, ckpt = api.lrnnx_selective_scan_fwd(**t, return_ckpt=True)
+    r = oracle.selective_scan_bwd(p["u"], p["delta"], p["A"], p["Bm"], p["Cm"], p["dy"], Dskip=p["Dskip"], delta_bias=p["delta_bias"], z=p["z"])
+    a = api.BwdArgs()
+    a.struct_size = ctypes.sizeof(api.BwdArgs)
+    a.B, a.D, a.N, a.L, a.bc_groups, a.path, a.ckpt = B, D, N, L, G, api.PATH["single_pass"], 0x1000
+    need = int(api.lib().lrnnx_selective_scan_bwd_workspace_bytes(ctypes.byref(a)))
+    for room in (need, need - 4):
+        ws = torch.full((room,), 0xff, dtype=torch.uint8, device="cuda")       # (NaN in whatever is read before it is written)
+        g = [api.lrnnx_selective_scan_bwd(**t, dy=dy, ckpt=ckpt, path="single_pass", workspace=ws) for _ in range(2)]
+        errs = {k: rel_err(host(g[0][k]), r[k]) for k in ("dA", "dBm", "dCm", "dD", "dbias", "du") if r[k] is not None}
+        assert "dA" in errs and all(e <= TOL_F32 for e in errs.values()), (room, errs)
+        if room == need and B <= 32:                        # always the same order (dD and dbias meet in LDS within a workgroup, in any)
+            assert torch.equal(g[0]["dA"], g[1]["dA"])
+
+
+@pytest.mark.parametrize("B,D,N,L", [(1, 700, 16, 600), (2, 900, 8, 1030), (3, 1200, 2, 700)])
+def test_complex(oracle, B, D, N, L):
+    import torch
+    from paper_2602_08810_amd import api
+    p = workloads.make_selective_complex(B=B, D=D, N=N, L=L, io="f32", gate=True, seed=B + D)
+    rng = np.random.Generator(np.random.PCG64(D))
+    dy = rng.standard_normal((B, D, L), dtype=np.float32)
+    maps = {k: torch.view_as_complex(torch.from_numpy(np.ascontiguousarray(p[k])).cuda()) for k in ("Bm", "Cm")}
+    t = dict(u=dev(p["u"], "f32"), delta=dev(p["delta"], "f32"), A=torch.from_numpy(p["A"]).cuda(), Dskip=dev(p["Dskip"]),
+             delta_bias=dev(p["delta_bias"]), z=dev(p["z"], "f32"), **maps)
+    _, ckpt = api.lrnnx_selective_scan_fwd_complex(**t, return_ckpt=True)
+    g = api.lrnnx_selective_scan_bwd_complex(**t, dy=dev(dy, "f32"), ckpt=ckpt, path="single_pass")
+    c = {k: p[k][..., 0].astype(np.float64) + 1j * p[k][..., 1] for k in ("Bm", "Cm")}
+    r = oracle.selective_scan_bwd_complex(p["u"], p["delta"], p["A"], c["Bm"], c["Cm"], dy, Dskip=p["Dskip"], delta_bias=p["delta_bias"], z=p["z"])
+    for k in ("dA", "dD", "dbias", "dBm"):
+        got, ref = np.asarray(host(g[k]) if not g[k].is_complex() else g[k].cpu().numpy()), np.asarray(r[k])
+        assert float(np.abs(got - ref).max() / np.abs(ref).max()) <= TOL_F32, k
