@@ -171,7 +171,7 @@ __global__ __launch_bounds__((FwdGeom<LPC, TM, WG>::W * 64), (TM == 16 ? (LPC ==
         const int64_t r = (int64_t)b * p.D + dc;
         sA[c][n] = p.A[(int64_t)dc * N + n];
         float x = 0.0f;
-        if (mode == MODE_APPLY || mode == MODE_CKPT_APPLY) x = p.ws_S[(r * p.nchunks + chunk) * N + n];
+        if (mode == (WANT_Y ? MODE_APPLY : MODE_CKPT_APPLY)) x = p.ws_S[(r * p.nchunks + chunk) * N + n];
         else if (mode != MODE_AGG && p.x0) x = p.x0[r * N + n];
         sX[c][n] = x;
         if constexpr (AGG) sP[c][n] = 1.0f;
