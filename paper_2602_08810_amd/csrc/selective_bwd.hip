@@ -18,16 +18,21 @@
 // of one channel (epilogue) and prepares the same steps of the next pair of channels (prologue).
 //
 // What bounds it: vector-ALU issue and, with two wavefronts a SIMD, the waits of a wavefront that the other one does not
-// fill (a sixth of its time, for LDS and at the one barrier of a pass).  With N = 16, 25.9 vector instructions per state update, or 27.8
+// fill (a seventh of its time, for LDS and at the one barrier of a pass).  With N = 16, 24.3 vector instructions per state update, or 26.1
 // issue slots if an exponential counts as two: 17 instructions of arithmetic, 5.4 for folds' ends and scans, the rest prologue, epilogue
-// and the work per tile.  B=8, D=1536, N=16, L=2048, bf16: 283 to 297 us, 4.0 to 4.2 cycles a slot, and 25 us for the sums of dBm and dCm;
-// B=16, D=2560, L=4096 1700.  What brought it there, in us on the former shape: time on 32 lanes of 8 steps instead of 64 of 4
+// and the work per tile.  B=8, D=1536, N=16, L=2048, bf16: 261 to 275 us, 3.9 to 4.1 cycles a slot, and 23 us for the sums of dBm and dCm;
+// B=16, D=2560, L=4096 1600 to 1627.  What brought it there, in us on the former shape: time on 32 lanes of 8 steps instead of 64 of 4
 // with all four states of a wavefront scanned together 440 -> 358; parts of a pass at the issue priorities of scan_common.hpp, prologue and
 // epilogue at the highest, since a whole workgroup waits for the last at its barrier, 369 -> 338 (both parts at one priority
 // 351); LDS accesses of prologue and epilogue without bank conflicts, the epilogue's reads under way together 325; two states at
-// a time 318; nothing spilled 8 less.  Also tried: four channels per wavefront on rows of 16 lanes with 16 steps each (twice the LDS
+// a time 318; nothing spilled 8 less.  Then, back to back: the steps' places in LDS by a shift, a mask and an exclusive or, one address for
+// all planes of a pair, sums over rows by masked lanes, both buffers' passes written out 287 -> 278; the reads of the main part behind the
+// epilogue's 272; the maps through LDS 269; no launch that clears dA, dD and dbias, see RowSums.  Where the main loop falls in memory
+// is 1.5 % (1592 to 1650 us on the latter shape with the same instructions, padded by 0 to 12 words).
+// Also tried: four channels per wavefront on rows of 16 lanes with 16 steps each (twice the LDS
 // traffic and one workgroup per compute unit: 560 us), halves holding different states at three wavefronts per SIMD (a
-// swap-and-add per sum: 431 us).
+// swap-and-add per sum: 431 us); the next tile's first steps and maps under way in the last pass of this one (274 and 275 us; with the
+// registers for it spilled 315); the epilogue before the main part (292); the two workgroups of a compute unit set off apart (no gain).
 #include "kernels.hpp"
 #include "scan_common.hpp"
 #include <type_traits>
