@@ -151,20 +151,20 @@ void fit_chunks(BwdPlan &pl, size_t nfit) {
 }
 
 // Sums of dA, dD and dbias for each batch entry (`floats` of a channel's dA, D channels), behind the tile sums of dBm and dCm: they save the launch that
-// clears the three arrays and the atomics.  Bytes; 0 where a channel has several workgroups (chunks of time), for a packed batch, which has dBm
-// and dCm cleared in any case, for one batch entry, which needs none, and for more than a thread should add up.  Training steps, bf16, N = 16, us:
+// clears the three arrays and the atomics (and for a packed batch dBm and dCm: that launch clears their rows outside every sequence).  Bytes; 0 where a
+// channel has several workgroups (chunks of time), for one batch entry, which needs none, and for more than a thread should add up.  Training steps, bf16, N = 16, us:
 // one entry of 512 rows, 512 steps 43.6 and 37.7; 2 x 256, 512 42.3 and 36.8; 32 x 64, 500 51.2 and 46.3; 8 x 1536, 2048 396 and 392.
-size_t row_sums_bytes(int64_t B, int64_t D, int64_t floats, int nchunks, bool packed) {
-    return !packed && nchunks <= 1 && B > 1 && B <= kRowSumsMaxB ? (size_t)B * D * (floats + 2) * sizeof(float) : 0;
+size_t row_sums_bytes(int64_t B, int64_t D, int64_t floats, int nchunks) {
+    return nchunks <= 1 && B > 1 && B <= kRowSumsMaxB ? (size_t)B * D * (floats + 2) * sizeof(float) : 0;
 }
 // where they go, given the place behind the tile sums (null: those are added with atomics) and the end of the workspace
-RowSums row_sums(const float *part, size_t part_bytes, uintptr_t end, int64_t B, int64_t D, int64_t floats, int nchunks, bool packed, float *dA,
+RowSums row_sums(const float *part, size_t part_bytes, uintptr_t end, int64_t B, int64_t D, int64_t floats, int nchunks, float *dA,
                  float *dD, float *dbias) {
     const RowSums none = {nullptr, nullptr, nullptr, -1, 0};
-    if (!part || packed || nchunks > 1) return none;
+    if (!part || nchunks > 1) return none;
     if (B == 1) return {dA, dD, dbias, 0, 0};
     const uintptr_t at = reinterpret_cast<uintptr_t>(part) + part_bytes;
-    const size_t bytes = row_sums_bytes(B, D, floats, nchunks, packed);
+    const size_t bytes = row_sums_bytes(B, D, floats, nchunks);
     if (!bytes || at > end || bytes > end - at) return none;
     float *f = reinterpret_cast<float *>(at);
     return {f, f + D * floats, f + D * (floats + 1), D * (floats + 2), 0};
@@ -180,8 +180,8 @@ size_t bwd_sums_bytes(Plan plan, int floats, int64_t B, int64_t D, int64_t N, in
     auto widest = [&](int64_t G) {
         size_t n = bwd_part_bytes((int)N * floats, packed ? lrnnx_packed_ckpt_slots(L, B) : B * cdiv(L, kBwdTileSteps), bcg * cdiv(dpg, G));
         if (n > kBwdSumsCap) return;
-        const size_t rows = row_sums_bytes(B, D, N * floats, 1, packed);
-        if (rows <= kBwdSumsCap - n) n += rows;
+        const size_t rows = row_sums_bytes(B, D, N * floats, 1);
+        n = rows < kBwdSumsCap - n ? n + rows : kBwdSumsCap;
         if (n > most) most = n;
     };
     if (packed)
@@ -587,7 +587,7 @@ int lrnnx_selective_scan_bwd_complex(const lrnnx_ss_bwd_complex_args *a) {
     const size_t part_need = bwd_part_bytes(2 * a->N, cu ? nslots : a->B * p.part_tiles, cbwd_grid_x(p));
     if (cbwd_sums_pay(a->N, p.part_tiles, cu != nullptr, part_need) && a->workspace && part <= end && part_need <= end - part)
         p.part = reinterpret_cast<float *>(part);
-    p.rows = row_sums(p.part, part_need, end, a->B, a->D, 2 * a->N, p.nchunks, cu != nullptr, reinterpret_cast<float *>(a->dA), a->dD, a->dbias);
+    p.rows = row_sums(p.part, part_need, end, a->B, a->D, 2 * a->N, p.nchunks, reinterpret_cast<float *>(a->dA), a->dD, a->dbias);
 
     const int64_t nbc = (cu ? 1 : (int64_t)a->B) * bcg * a->L * a->N * 2;   // floats; packed mode: one time axis for all sequences
     FillList z{};
@@ -626,7 +626,7 @@ size_t lrnnx_selective_scan_bwd_workspace_bytes(const lrnnx_ss_bwd_args *a) {
     if (!a->cu_seqlens && a->L <= kBwdTileSteps && a->N >= 4 && bwd_grid_x(p) >= (a->N > 8 ? 2 * a->N : 16) * bcg) return with_sweep(n);
     const size_t sums = bwd_part_bytes(a->N, bwd_tile_slots(a), bwd_grid_x(p));
     if (sums > kBwdSumsCap) return with_sweep(n);
-    const size_t rows = row_sums_bytes(a->B, a->D, a->N, pl.nchunks, a->cu_seqlens != nullptr);
+    const size_t rows = row_sums_bytes(a->B, a->D, a->N, pl.nchunks);
     return with_sweep(n + 256 + sums + (rows <= kBwdSumsCap - sums ? rows : 0));        // (256: the sums start on such a boundary)
 }
 
@@ -728,7 +728,7 @@ int lrnnx_selective_scan_bwd(const lrnnx_ss_bwd_args *a) {
     const uintptr_t end = reinterpret_cast<uintptr_t>(a->workspace) + a->workspace_bytes;
     const size_t part_need = bwd_part_bytes(a->N, bwd_tile_slots(a), bwd_grid_x(p));
     if (a->workspace && part <= end && part_need <= end - part) p.part = reinterpret_cast<float *>(part);
-    p.rows = row_sums(p.part, part_need, end, a->B, a->D, a->N, p.nchunks, cu != nullptr, a->dA, a->dD, a->dbias);
+    p.rows = row_sums(p.part, part_need, end, a->B, a->D, a->N, p.nchunks, a->dA, a->dD, a->dbias);
 
     // reduced outputs that are accumulated with atomics: clear them on the stream first, if there are any (dBm and dCm of a packed
     // batch in any case: rows outside every sequence are zero)

@@ -56,8 +56,8 @@ struct CFwdParams {
 // backward of the same
 // Where a backward workgroup leaves its channels' sums of dA, dD and dbias.  sb < 0: added with float atomics to the call's own arrays, which
 // a launch has cleared before.  sb >= 0: stored, at b * sb floats behind these pointers; a channel of a batch entry then has one
-// workgroup, and the launch that adds up the tile sums of dBm and dCm adds up the batch entries as well, its workgroups from `first`
-// on (sb > 0), or there is one batch entry and these are the call's arrays (sb = 0).
+// workgroup, and the launch that adds up the tile sums of dBm and dCm, in its workgroups from `first` on, clears what a packed batch leaves out
+// of those and adds up the batch entries (sb > 0), or there is one batch entry and these are the call's arrays (sb = 0).
 struct RowSums {
     float *A, *D, *b;
     int64_t sb;

@@ -983,6 +983,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT) __attribute__((amdgpu_waves_per_eu(
 // chain of reads is what it waits for: KS threads then share an element, each a quarter of the blocks, and a
 // workgroup takes a quarter of the piece (whole call, bf16, L = 512: 1024 rows, N = 16 49 us, so 41; 4096 rows 73 and 57, N = 4
 // 57 and 42).
+constexpr unsigned kClearWgs = 16;                  // workgroups that look after rows outside every sequence (few, if any)
 template <int N> struct BwdMaps {
     // pieces of a tile, of one thread an element: of time as long as what is read of a state stays whole lines, then of the states
     static constexpr int TIME = N >= 16 ? 4 : N >= 8 ? N / 4 : 1, STATES = N > 16 ? N / 16 : 1, PIECES = TIME * STATES;
@@ -1001,8 +1002,19 @@ __global__ __launch_bounds__(256) void k_ss_bwd_maps(const BwdParams p, int gx) 
     static_assert(LP * PIECES == 32 && (KS == 1 ? NE <= 256 : NE == 64 && KS == 4), "a thread for each element, a wavefront for each share of the blocks");
     __shared__ float sT[SP * (NW + 1)];
     __shared__ float4 sK[KS > 1 ? KS * NE : 1];
-    if (p.rows.sb > 0 && blockIdx.x >= p.rows.first) {       // dA, dD, dbias from what the workgroups left for each batch entry
-        const int64_t nA = (int64_t)p.D * N, e = (int64_t)(blockIdx.x - p.rows.first) * 256 + threadIdx.x;
+    if (blockIdx.x >= p.rows.first) {
+        const int64_t nA = (int64_t)p.D * N;
+        const unsigned nz = p.cu ? kClearWgs : 0, at = blockIdx.x - p.rows.first;
+        if (at < nz) {                               // a packed batch: the rows of this map outside every sequence are zero
+            const auto clip = [&](int64_t o) { return o < 0 ? 0 : o > p.L ? p.L : o; };
+            const int64_t head = clip(p.cu[0]), end = clip(p.cu[p.B]), rows = head + p.L - (end < head ? head : end);
+            float *out = (blockIdx.y ? p.dCm : p.dBm) + (int64_t)blockIdx.z * p.L * N;
+            for (int64_t i = at * 256 + threadIdx.x; i < rows * N; i += (int64_t)nz * 256)
+                out[i < head * N ? i : p.L * N - rows * N + i] = 0.0f;
+            return;
+        }
+        // dA, dD, dbias from what the workgroups left for each batch entry
+        const int64_t e = (int64_t)(at - nz) * 256 + threadIdx.x;
         if (blockIdx.y || blockIdx.z || e >= nA + 2 * p.D) return;
         float *out = e < nA ? p.dA + e : e < nA + p.D ? (p.dD ? p.dD + (e - nA) : nullptr) : (p.dbias ? p.dbias + (e - nA - p.D) : nullptr);
         if (!out) return;
@@ -1146,6 +1158,7 @@ static hipError_t launch_bwd_maps_n(const BwdParams &p, int gx, hipStream_t s) {
     dim3 g2((unsigned)(split ? pieces * KS : pieces), 2, p.bcg);
     BwdParams q = p;
     q.rows.first = g2.x;
+    if (p.rows.sb >= 0 && p.cu) g2.x += kClearWgs;
     if (p.rows.sb > 0) g2.x += (unsigned)(((int64_t)p.D * (N + 2) + 255) / 256);
     if (split) hipLaunchKernelGGL((k_ss_bwd_maps<N, KS>), g2, dim3(256), 0, s, q, gx);
     else hipLaunchKernelGGL((k_ss_bwd_maps<N, 1>), g2, dim3(256), 0, s, q, gx);

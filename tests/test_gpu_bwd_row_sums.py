@@ -53,3 +53,30 @@ def test_complex(oracle, B, D, N, L):
     for k in ("dA", "dD", "dbias", "dBm"):
         got, ref = np.asarray(host(g[k]) if not g[k].is_complex() else g[k].cpu().numpy()), np.asarray(r[k])
         assert float(np.abs(got - ref).max() / np.abs(ref).max()) <= TOL_F32, k
+
+
+@pytest.mark.parametrize("N,D,cu,L", [(16, 70, [3, 300, 300, 901], 1000), (4, 33, [0, 700], 900), (8, 40, [17] + list(range(40, 1040, 31)), 1100),
+                                      (1, 30, [0, 5, 513, 800], 800)])
+def test_packed(oracle, N, D, cu, L):
+    """Also the rows of dBm and dCm outside every sequence, which the same launch clears."""
+    import torch
+    from paper_2602_08810_amd import api
+    p = workloads.make_selective(B=1, D=D, N=N, L=L, io="f32", gate=True, with_dy=True, seed=N + D)
+    t = {k: (v if k in ("A", "Dskip", "delta_bias") or v is None else v[0]) for k, v in sel_inputs_dev(p, "f32").items()}
+    cud = torch.tensor(cu, dtype=torch.int64, device="cuda")
+    t.pop("x0", None)
+    q = {k: p[k][0] for k in ("u", "delta", "Bm", "Cm", "dy", "z")}
+    r = oracle.selective_scan_bwd_packed(q["u"], q["delta"], p["A"], q["Bm"], q["Cm"], q["dy"], np.asarray(cu), Dskip=p["Dskip"],
+                                         delta_bias=p["delta_bias"], z=q["z"])
+    a = api.BwdArgs()
+    a.struct_size = ctypes.sizeof(api.BwdArgs)
+    a.B, a.D, a.N, a.L, a.cu_seqlens = len(cu) - 1, D, N, L, 0x1000
+    need = int(api.lib().lrnnx_selective_scan_bwd_workspace_bytes(ctypes.byref(a)))
+    inside = np.zeros(L, dtype=bool)
+    inside[cu[0]:cu[-1]] = True
+    for room in (need, need - 4):
+        ws = torch.full((room,), 0xff, dtype=torch.uint8, device="cuda")
+        g = api.lrnnx_selective_scan_bwd(**t, dy=dev(q["dy"], "f32"), cu_seqlens=cud, workspace=ws)
+        for k in ("dA", "dBm", "dCm", "dD", "dbias"):
+            assert rel_err(host(g[k]), r[k]) <= TOL_F32, (room, k)
+        assert not host(g["dBm"])[~inside].any() and not host(g["dCm"])[~inside].any()
