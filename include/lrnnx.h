@@ -96,7 +96,9 @@ int64_t lrnnx_packed_ckpt_slots(int64_t L, int64_t B);
  * ONE time axis of L steps, sequence b being steps cu_seqlens[b] .. cu_seqlens[b+1]-1 (each starts from x0[b] or 0,
  * nothing crosses a boundary; steps outside every sequence are not touched).  u, delta, z, y are then [D,L] (the
  * batch strides are ignored), Bm and Cm [G,L,N], x0 and x_last [B,D,N], and ckpt is
- * [D, lrnnx_packed_ckpt_slots(L,B), N].  Boundaries are clamped to [0,L] on the device; the single-pass path
+ * [D, lrnnx_packed_ckpt_slots(L,B), N].  Boundaries are clamped to [0,L] on the device, and not checked to
+ * ascend: a sequence that ends before it starts is empty, but no two may share a step, nor a slot of ckpt (sequence b has
+ * those from cu_seqlens[b] / interval + b on).  The single-pass path
  * is used (LRNNX_PATH_CHUNK_CARRY is refused).  Sequences may start anywhere: rows are read and written with vector
  * accesses at element alignment.
  * workspace is needed only by LRNNX_PATH_CHUNK_CARRY (AUTO falls back to the single

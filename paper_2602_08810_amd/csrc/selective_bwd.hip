@@ -976,6 +976,17 @@ __global__ __launch_bounds__(BwdGeom<N>::NT) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
+// a boundary as a step of the axis, and the sequence whose tiles start last at or before a slot: sequence b's start at cu[b] / 256 + b
+__device__ __forceinline__ int64_t axis_step(int64_t o, int64_t Lp) { return o < 0 ? 0 : (o > Lp ? Lp : o); }
+__device__ __forceinline__ int seq_of_slot(const int64_t *cu, int B, int64_t Lp, int64_t slot) {
+    int lo = 0, hi = B - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (axis_step(cu[mid], Lp) / kBwdTileSteps + mid <= slot) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+
 // dBm, dCm [.., L, N] from the tile sums the workgroups of k_ss_bwd left in the workspace: a workgroup adds one piece of a
 // tile (blockIdx.x) of one of the two maps (blockIdx.y) of one group (blockIdx.z) over the channel blocks, always in the same order, and
 // transposes it through LDS.  With many tiles it is bound by the reads of the workspace, whole lines of 128 bytes (half lines, as the pieces
@@ -1006,9 +1017,25 @@ __global__ __launch_bounds__(256) void k_ss_bwd_maps(const BwdParams p, int gx) 
         const int64_t nA = (int64_t)p.D * N;
         const unsigned nz = p.cu ? kClearWgs : 0, at = blockIdx.x - p.rows.first;
         if (at < nz) {                               // a packed batch: the rows of this map outside every sequence are zero
-            const auto clip = [&](int64_t o) { return o < 0 ? 0 : o > p.L ? p.L : o; };
-            const int64_t head = clip(p.cu[0]), end = clip(p.cu[p.B]), rows = head + p.L - (end < head ? head : end);
             float *out = (blockIdx.y ? p.dCm : p.dBm) + (int64_t)blockIdx.z * p.L * N;
+            const int s = threadIdx.x & 63;
+            static_assert(kRowSumsMaxB <= 64, "a lane for each sequence");
+            if (__builtin_amdgcn_ballot_w64(s < p.B && axis_step(p.cu[s], p.L) > axis_step(p.cu[s + 1], p.L))) {
+                // Boundaries that descend somewhere are not refused.  What they leave out may lie anywhere, and what is before the first or
+                // after the last may be some sequence's: row by row those that no other workgroup of this launch writes.
+                for (int64_t r = at * 256 + threadIdx.x; r < p.L; r += (int64_t)nz * 256) {
+                    bool written = false;
+                    for (int b = 0; b < p.B; ++b) {
+                        const SeqSpan q = seq_span_fwd<false>(p.cu, p.B, p.L, b);
+                        const int64_t in = r - q.toff;
+                        written |= in >= 0 && in < q.L && seq_of_slot(p.cu, p.B, p.L, (q.toff / kBwdTileSteps + b) + in / kBwdTileSteps) == b;
+                    }
+                    if (!written)
+                        for (int n = 0; n < N; ++n) out[r * N + n] = 0.0f;
+                }
+                return;
+            }
+            const int64_t head = axis_step(p.cu[0], p.L), rows = head + p.L - axis_step(p.cu[p.B], p.L);
             for (int64_t i = at * 256 + threadIdx.x; i < rows * N; i += (int64_t)nz * 256)
                 out[i < head * N ? i : p.L * N - rows * N + i] = 0.0f;
             return;
@@ -1029,16 +1056,8 @@ __global__ __launch_bounds__(256) void k_ss_bwd_maps(const BwdParams p, int gx) 
     const int64_t slot = blockIdx.x / (NP * PIECES);
     int64_t b, tile, toff = 0, L = p.L;
     if (p.cu) {
-        // the sequence whose tiles start last at or before this slot: sequence b's start at cu[b] / 256 + b
-        int lo = 0, hi = p.B - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            int64_t o = p.cu[mid];
-            o = o < 0 ? 0 : (o > p.L ? p.L : o);
-            if (o / kBwdTileSteps + mid <= slot) lo = mid; else hi = mid - 1;
-        }
-        b = lo;
-        const SeqSpan q = seq_span(p.cu, p.B, p.L, lo, false);
+        b = seq_of_slot(p.cu, p.B, p.L, slot);
+        const SeqSpan q = seq_span(p.cu, p.B, p.L, (int)b, false);
         toff = q.toff; L = q.L;
         tile = slot - (toff / kBwdTileSteps + b);
     } else {
