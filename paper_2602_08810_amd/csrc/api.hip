@@ -160,14 +160,14 @@ size_t row_sums_bytes(int64_t B, int64_t D, int64_t floats, int nchunks) {
 // where they go, given the place behind the tile sums (null: those are added with atomics) and the end of the workspace
 RowSums row_sums(const float *part, size_t part_bytes, uintptr_t end, int64_t B, int64_t D, int64_t floats, int nchunks, float *dA,
                  float *dD, float *dbias) {
-    const RowSums none = {nullptr, nullptr, nullptr, -1, 0};
+    const RowSums none = {nullptr, nullptr, nullptr, -1, 0, 0};
     if (!part || nchunks > 1) return none;
-    if (B == 1) return {dA, dD, dbias, 0, 0};
+    if (B == 1) return {dA, dD, dbias, 0, 0, 0};
     const uintptr_t at = reinterpret_cast<uintptr_t>(part) + part_bytes;
     const size_t bytes = row_sums_bytes(B, D, floats, nchunks);
     if (!bytes || at > end || bytes > end - at) return none;
     float *f = reinterpret_cast<float *>(at);
-    return {f, f + D * floats, f + D * (floats + 1), D * (floats + 2), 0};
+    return {f, f + D * floats, f + D * (floats + 1), D * (floats + 2), 0, 0};
 }
 
 // Scratch for the tile sums of dBm and dCm of a backward call, real (LRNNX_WS_BWD_SUMS) or complex (`plan` is its bwd_plan resp.

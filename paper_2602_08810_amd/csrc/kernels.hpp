@@ -57,11 +57,11 @@ struct CFwdParams {
 // Where a backward workgroup leaves its channels' sums of dA, dD and dbias.  sb < 0: added with float atomics to the call's own arrays, which
 // a launch has cleared before.  sb >= 0: stored, at b * sb floats behind these pointers; a channel of a batch entry then has one
 // workgroup, and the launch that adds up the tile sums of dBm and dCm, in its workgroups from `first` on, clears what a packed batch leaves out
-// of those and adds up the batch entries (sb > 0), or there is one batch entry and these are the call's arrays (sb = 0).
+// of those (`clear` workgroups a map) and adds up the batch entries (sb > 0), or there is one batch entry and these are the call's arrays (sb = 0).
 struct RowSums {
     float *A, *D, *b;
     int64_t sb;
-    unsigned first;
+    unsigned first, clear;      // set by the launcher
 };
 constexpr int kRowSumsMaxB = 32;     // batch entries that a thread adds up
 
@@ -368,5 +368,6 @@ int bwd_channels_per_group(int B, int D, int N, int64_t L, bool balanced);
 int bwd_places(int N);                       // workgroups of the backward kernel the chip holds at once
 int bwd_grid_x(const BwdParams &p);
 size_t bwd_part_bytes(int N, int64_t tile_slots, int64_t grid_x);
+unsigned bwd_clear_wgs(int64_t L, int floats);
 
 }  // namespace lrnnx

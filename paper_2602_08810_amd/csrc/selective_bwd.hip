@@ -994,7 +994,6 @@ __device__ __forceinline__ int seq_of_slot(const int64_t *cu, int B, int64_t Lp,
 // chain of reads is what it waits for: KS threads then share an element, each a quarter of the blocks, and a
 // workgroup takes a quarter of the piece (whole call, bf16, L = 512: 1024 rows, N = 16 49 us, so 41; 4096 rows 73 and 57, N = 4
 // 57 and 42).
-constexpr unsigned kClearWgs = 16;                  // workgroups that look after rows outside every sequence (few, if any)
 template <int N> struct BwdMaps {
     // pieces of a tile, of one thread an element: of time as long as what is read of a state stays whole lines, then of the states
     static constexpr int TIME = N >= 16 ? 4 : N >= 8 ? N / 4 : 1, STATES = N > 16 ? N / 16 : 1, PIECES = TIME * STATES;
@@ -1015,7 +1014,7 @@ __global__ __launch_bounds__(256) void k_ss_bwd_maps(const BwdParams p, int gx) 
     __shared__ float4 sK[KS > 1 ? KS * NE : 1];
     if (blockIdx.x >= p.rows.first) {
         const int64_t nA = (int64_t)p.D * N;
-        const unsigned nz = p.cu ? kClearWgs : 0, at = blockIdx.x - p.rows.first;
+        const unsigned nz = p.rows.clear, at = blockIdx.x - p.rows.first;
         if (at < nz) {                               // a packed batch: the rows of this map outside every sequence are zero
             float *out = (blockIdx.y ? p.dCm : p.dBm) + (int64_t)blockIdx.z * p.L * N;
             const int s = threadIdx.x & 63;
@@ -1162,6 +1161,15 @@ hipError_t launch_ss_bwd(const BwdParams &p, int io_dtype, int disc, hipStream_t
     return io_dtype == 1 ? launch_bwd_io<bf16_t>(p, disc, s) : launch_ss_bwd_f32(p, disc, s);
 }
 
+// Workgroups that look after the rows of one map (`floats` a row) outside every sequence of a packed batch.  The host knows the length of the axis,
+// not how much of it is unused: a workgroup for every 8192 floats of the map, and up to 512 of them.  Backward calls, bf16, us, with 16 workgroups and with
+// these: 4 sequences, 2048 steps in all, 64 channels, N = 16, on an axis of 65536 steps 37.3 and 29.9, of 262144 70.3 and 36.9; 16 sequences, 4096 steps,
+// 128 channels, N = 4, of 524288 37.7 and 22.6; with no step unused as before (27.6; 8 x 512 channels, 8192 steps 74.4).
+unsigned bwd_clear_wgs(int64_t L, int floats) {
+    const int64_t wgs = L * floats / 8192;
+    return wgs < 16 ? 16 : wgs > 512 ? 512 : (unsigned)wgs;
+}
+
 template <int N>
 static hipError_t launch_bwd_maps_n(const BwdParams &p, int gx, hipStream_t s) {
     const int64_t slots = p.cu ? p.nslots : (int64_t)p.B * p.part_tiles, pieces = slots * BwdMaps<N>::PIECES;
@@ -1177,7 +1185,8 @@ static hipError_t launch_bwd_maps_n(const BwdParams &p, int gx, hipStream_t s) {
     dim3 g2((unsigned)(split ? pieces * KS : pieces), 2, p.bcg);
     BwdParams q = p;
     q.rows.first = g2.x;
-    if (p.rows.sb >= 0 && p.cu) g2.x += kClearWgs;
+    q.rows.clear = p.rows.sb >= 0 && p.cu ? bwd_clear_wgs(p.L, N) : 0;
+    g2.x += q.rows.clear;
     if (p.rows.sb > 0) g2.x += (unsigned)(((int64_t)p.D * (N + 2) + 255) / 256);
     if (split) hipLaunchKernelGGL((k_ss_bwd_maps<N, KS>), g2, dim3(256), 0, s, q, gx);
     else hipLaunchKernelGGL((k_ss_bwd_maps<N, 1>), g2, dim3(256), 0, s, q, gx);

@@ -46,3 +46,29 @@ def test_descending(oracle, N, D, L, cu, spans, workspace):
         assert np.isnan(got[:, ~inside]).all(), k                 # steps outside every sequence are not touched
         if spans:
             assert rel_err(got[:, inside], ref[k][:, inside]) <= TOL_F32, k
+
+
+@pytest.mark.parametrize("N,L,cu", [(16, 70001, [500, 1100, 1300]), (32, 140003, [139000, 139500, 140003]), (1, 150001, [0, 10, 400])])
+def test_long_axis_of_few_steps(oracle, N, L, cu):
+    """Most of the axis unused: more workgroups clear it, the most there are in the second case."""
+    import torch
+    from paper_2602_08810_amd import api
+    D, o, e = 6, cu[0], cu[-1]
+    p = workloads.make_selective(B=1, D=D, N=N, L=e - o, io="f32", gate=True, with_dy=True, seed=N)
+    t = {k: (v if k in ("A", "Dskip", "delta_bias") or v is None else v[0]) for k, v in sel_inputs_dev(p, "f32").items()}
+    t.pop("x0", None)
+
+    def spread(x, time):                                    # on the long axis, NaN around
+        out = torch.full([L if i == time else n for i, n in enumerate(x.shape)], float("nan"), device="cuda")
+        out.narrow(time, o, e - o).copy_(x)
+        return out
+    t = {k: (v if k in ("A", "Dskip", "delta_bias") else spread(v, 0 if k in ("Bm", "Cm") else 1)) for k, v in t.items()}
+    g = api.lrnnx_selective_scan_bwd(**t, dy=spread(dev(p["dy"][0], "f32"), 1), cu_seqlens=torch.tensor(cu, device="cuda"), outs=poisoned(D, N, L))
+    r = oracle.selective_scan_bwd_packed(*(p[k][0] for k in ("u", "delta")), p["A"], *(p[k][0] for k in ("Bm", "Cm", "dy")), np.array(cu) - o,
+                                         Dskip=p["Dskip"], delta_bias=p["delta_bias"], z=p["z"][0])
+    for k in ("dBm", "dCm"):
+        got, ref = host(g[k]), np.zeros((L, N))
+        ref[o:e] = np.asarray(r[k]).reshape(e - o, N)
+        assert rel_err(got, ref) <= TOL_F32, k
+    for k in ("dA", "dD", "dbias"):
+        assert rel_err(host(g[k]), r[k]) <= TOL_F32, k
