@@ -117,12 +117,12 @@ size_t cbwd_carry_bytes(int64_t B, int64_t D, int64_t N, int64_t L) {    // the 
 }
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 // Chunks of the time axis of the recompute sweep of a real backward call (1: none), and the bytes of their aggregates, which lie behind the
-// checkpoints, where the backward pass puts its own afterwards.  By the rule of the forward pass: the sweep is that pass without its outputs,
-// and as one chain a row it was what a call with few long rows waited for.  Whole calls, one chain and in chunks (us; bf16, N = 16, one
+// checkpoints, where the backward pass puts its own afterwards.  As one chain a row the sweep was what a call with few long rows waited
+// for.  Whole calls, one chain and in chunks (us; bf16, N = 16, one
 // batch entry): 16 channels, 65536 steps 468 and 92; 64, 16384 175 and 87; 256, 4096 103 and 86; 768, 16384 308 and 276; N = 4, 64
-// channels, 65536 steps 242 and 93.  Where the rule keeps one chain, nothing changes.
+// channels, 65536 steps 242 and 93.  (The sweep of a complex call is one chain a row.)
 int sweep_chunks(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L, bool f32) {
-    return fwd_chunks_pay(B, bcg, dpg, N, L, f32) ? fwd_chunks(B, bcg * dpg, L, false) : 1;
+    return sweep_chunks_pay(B, bcg, dpg, N, L, f32) ? fwd_chunks(B, bcg * dpg, L, false) : 1;
 }
 size_t sweep_bytes(int64_t B, int64_t D, int64_t N, int chunks) { return chunks > 1 ? (size_t)2 * B * D * chunks * N * sizeof(float) : 0; }
 

@@ -361,6 +361,7 @@ int cfwd_channels_per_workgroup();           // the same of the complex forward 
 int cfwd_tile_steps();
 bool cfwd_chunks_pay(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L);
 bool fwd_chunks_pay(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L, bool f32);
+bool sweep_chunks_pay(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L, bool f32);
 int lti_chunk_group();                       // chunks (wavefronts) of one workgroup of the two-launch LTI path
 int lti_onepass_anchor();                    // every how many groups the single-launch LTI scan publishes a true state
 int fwd_tile_steps();                        // time steps one workgroup of the 16-lane shape covers per tile

@@ -669,6 +669,21 @@ bool fwd_chunks_pay(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L, b
     return true;
 }
 
+// The same for the sweep that a backward call without checkpoints makes, of states alone, whose second pass saves nothing over the aggregates but the
+// launches stay: costs of its own, of one chain a row (64 x 16) and of the three launches.  Sweeps on 256 workgroups of eight channels and less
+// (with more, one chain was faster in every call measured).  870 sweeps of 16 to 3000 rows of 512 to 65536 steps, N = 1 to 32, both types: chunks
+// are taken in one that is slower so (1.04 times); by the rule above in 30, up to 1.22 times (us, one chain and in chunks, bf16: 1024 rows of 4096
+// steps, N = 32 50.6 and 61.6; 512 of 2048, N = 16 15.8 and 17.9).  700 drawn ones, all schemes, odd lengths, groups: in 5, up to 1.08 (20, 1.27).
+bool sweep_chunks_pay(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L, bool f32) {
+    static constexpr FwdCost chain[2] = {{312, 0, 173, 38}, {302, 1, 122, 33}}, chunks[2] = {{785, 30, 238, 25}, {858, 24, 121, 28}};
+    const int64_t tiles = (L + fwd_tile_steps() - 1) / fwd_tile_steps(), channels = fwd_channels_per_workgroup(), maps = B * bcg;
+    if (tiles < 2 || maps * ((dpg + 7) / 8) > kNumCU) return false;
+    const FwdCost &c = chain[f32 ? 0 : 1];
+    const int64_t one = c.tile + c.state * N + (L + 1023) / 1024 * (c.wg + c.wg_state * N);
+    const int64_t chunked = fwd_cost(chunks[f32 ? 0 : 1], N, 1, maps * ((dpg + channels - 1) / channels) * tiles);
+    return chunked + chunked * 6 / 100 < one;
+}
+
 // Chains the chunk aggregates of one (b,d,n): carry-in of chunk c+1 = P_c * carry-in of chunk c + S_c.
 // ws_S[c] is replaced by the carry-in of chunk c.  A workgroup takes 16 such chains and up to 256 chunks at a time: 16 threads
 // of a chain fold up to 16 consecutive pairs each, all read at once, and replay them from the state that the threads before
