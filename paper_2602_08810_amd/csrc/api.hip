@@ -125,6 +125,11 @@ int sweep_chunks(int64_t B, int64_t bcg, int64_t dpg, int64_t N, int64_t L, bool
     return sweep_chunks_pay(B, bcg, dpg, N, L, f32) ? fwd_chunks(B, bcg * dpg, L, false) : 1;
 }
 size_t sweep_bytes(int64_t B, int64_t D, int64_t N, int chunks) { return chunks > 1 ? (size_t)2 * B * D * chunks * N * sizeof(float) : 0; }
+// (neither size query goes by the type of the rows)
+size_t sweep_bytes_of_either(int64_t B, int64_t D, int64_t N, int64_t L, int64_t bcg) {
+    const size_t bf16 = sweep_bytes(B, D, N, sweep_chunks(B, bcg, D / bcg, N, L, false)), f32 = sweep_bytes(B, D, N, sweep_chunks(B, bcg, D / bcg, N, L, true));
+    return bf16 > f32 ? bf16 : f32;
+}
 
 // Launch plan of a backward call.  A batch [B,D,L] is planned as it is.  Of a packed batch the host knows the number of
 // sequences and the length of the time axis, and max_seqlen if the caller gave it (else 0): the single pass is planned
@@ -328,11 +333,10 @@ size_t lrnnx_workspace_bytes(int which, int64_t B, int64_t D, int64_t N, int64_t
         const size_t carry = cplx ? cbwd_carry_bytes(B * bcg, D / bcg, N, L) : bwd_carry_bytes(B * bcg, D / bcg, N, L);
         const size_t order = packed ? sizeof(int) * (size_t)B : 0;
         size_t base = carry > order ? carry : order;
-        if (which == LRNNX_WS_BWD && !packed)            // (of either type)
-            for (const bool f32 : {false, true}) {
-                const size_t sweep = sweep_bytes(B, D, N, sweep_chunks(B, bcg, D / bcg, N, L, f32));
-                if (base < sweep) base = sweep;
-            }
+        if (which == LRNNX_WS_BWD && !packed) {
+            const size_t sweep = sweep_bytes_of_either(B, D, N, L, bcg);
+            if (base < sweep) base = sweep;
+        }
         base += ck;
         if (!cplx) return base;
         const size_t sums = bwd_sums_bytes(cbwd_plan, 2, B, D, N, L, bcg, packed != 0);
@@ -614,7 +618,7 @@ size_t lrnnx_selective_scan_bwd_workspace_bytes(const lrnnx_ss_bwd_args *a) {
     size_t n = a->ckpt ? 0 : align256(bwd_ckpt_bytes(a));
     auto with_sweep = [&, ck = n](size_t n) {
         if (a->ckpt || a->cu_seqlens || a->path == LRNNX_PATH_SINGLE_PASS) return n;
-        const size_t sweep = ck + sweep_bytes(a->B, a->D, a->N, sweep_chunks(a->B, bcg, a->D / bcg, a->N, a->L, a->io_dtype == LRNNX_F32));
+        const size_t sweep = ck + sweep_bytes_of_either(a->B, a->D, a->N, a->L, bcg);
         return n < sweep ? sweep : n;
     };
     if (pl.nchunks > 1) n += (size_t)2 * a->B * a->D * pl.nchunks * a->N * sizeof(float);
