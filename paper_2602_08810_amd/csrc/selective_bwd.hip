@@ -344,7 +344,7 @@ __global__ __launch_bounds__(BwdGeom<N>::NT) __attribute__((amdgpu_waves_per_eu(
         // columns from LDS, where the rows of eight steps have a gap of 16 bytes against bank conflicts.  Loaded by column each access met 32
         // cache lines, and those of eight wavefronts held up what came behind them (B=8, D=1536, N=16, L=2048, bf16: 274 -> 269.5 us).
         constexpr bool STAGED = NB == 2;
-        constexpr int RB = N * (int)sizeof(IO), ROWS = 32 * T, CHUNKS = RB / 16, CPT = STAGED ? (ROWS * CHUNKS + NT - 1) / NT : 1;       // bytes of a row, its chunks, chunks of a thread
+        constexpr int RB = N * (int)sizeof(IO), ROWS = 32 * T, CHUNKS = STAGED ? RB / 16 : 1, CPT = STAGED ? (ROWS * CHUNKS + NT - 1) / NT : 1;       // bytes of a row, its chunks, chunks of a thread
         RawFew<IO, STAGED ? 16 / (int)sizeof(IO) : NS> rB[STAGED ? CPT : T], rC[STAGED ? CPT : T];
         {
             const IO *BmT = Bm + l0 * N, *CmT = Cm + l0 * N;
