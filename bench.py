@@ -200,7 +200,8 @@ def main():
     fwd_bytes = _selective_bytes(B, D, N, L, 2, True, False) + ckpt.numel() * 4
     bwd_bytes = _selective_bytes(B, D, N, L, 2, True, True) + ckpt.numel() * 4
     traffic, traffic_note = measured_traffic()
-    roofline = {"bound": "hbm", "kernel": "k_ss_bwd<bf16,N=16> (config 2 backward)",
+    # "bound" names the roof that achieved and peak are given against; what limits the kernel is the other one
+    roofline = {"bound": "hbm", "limited_by": "vector-ALU issue (roofline_alu)", "kernel": "k_ss_bwd<bf16,N=16> (config 2 backward)",
                 "achieved": bwd_bytes / bwd_t / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": bwd_bytes / bwd_t / 1e9 / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": traffic_note,
                 "algorithmic_bytes": bwd_bytes, "avg_launch_us": bwd_t * 1e6,

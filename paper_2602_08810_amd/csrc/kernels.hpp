@@ -8,6 +8,8 @@ constexpr int kNumCU = 256;              // MI355X
 
 constexpr int64_t kCkptInterval = 256;   // steps between state checkpoints (public: lrnnx_ckpt_interval)
 
+// passes of the forward kernels: whole rows; in chunks of time the chunks' aggregates, then outputs from their carry-ins; states alone (the sweep of a
+// backward call without checkpoints), whole rows and in chunks from their carry-ins
 enum : int { MODE_FULL = 0, MODE_AGG = 1, MODE_APPLY = 2, MODE_CKPT_ONLY = 3, MODE_CKPT_APPLY = 4 };
 
 struct FwdParams {

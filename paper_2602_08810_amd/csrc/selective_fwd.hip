@@ -96,7 +96,7 @@ template <int LPC, int T, int WG = 0> struct FwdGeom {
 
 // Workgroups that share a compute unit: three of four wavefronts with 16 lanes per channel (168 registers, three wavefronts a
 // SIMD); with 64 lanes four of four wavefronts (4 steps) or two of eight (8 steps: 75 KB of LDS each), at 128 registers four a
-// SIMD; one of eight with 16 steps, whose staged tile takes more than half of the LDS.
+// SIMD; one of twelve (8 steps, three wavefronts a SIMD); one of eight with 16 steps, whose staged tile takes more than half of the LDS.
 // RANKED: a packed batch whose workgroups rank the sequences (ranked_sequences)
 template <typename IO, int N, int DISC, bool WANT_Y, bool CKPT, int LPC, int TM, bool RANKED, int WG = 0>
 __global__ __launch_bounds__((FwdGeom<LPC, TM, WG>::W * 64), (TM == 16 ? (LPC == 16 ? 3 : 2) : WG ? 3 : 4)) void k_ss_fwd(const FwdParams p) {
