@@ -522,11 +522,16 @@ __global__ __launch_bounds__((FwdGeom<LPC, TM, WG>::W * 64), (TM == 16 ? (LPC ==
 //   64 x 8, twelve wavefronts: where workgroups of eight channels would be a little more than one a compute unit, which is as long as two, and
 //             those of twelve are not (2049 to 3072 rows; one workgroup a compute unit, three wavefronts a SIMD instead of four; 2313 rows,
 //             L = 1531, N = 16, float32: 36.3 -> 30.2 us, bf16 32.4 -> 26.9; 3000 rows, L = 4096: 83.0 -> 72.1, 72.4 -> 62.6; with nine or
-//             ten wavefronts the same, with thirteen to sixteen, four on a SIMD, what eight take)
+//             ten wavefronts the same, with thirteen to sixteen, four on a SIMD, what eight take).  Of these rows not few tiles of 512 steps the last of which is at
+//             most half full: 64 x 4 leaves that half out (2600 rows, L = 768, N = 16, float32: 20.1 us, twelve wavefronts 23.1, eight 26.7); nor, with
+//             eight states or for states alone, for a 257th workgroup of one to four channels, which costs the one beside it little (2049 rows,
+//             L = 5000, N = 8, float32: 53.3 us with eight wavefronts, 57.8).  3024 calls of 2049 to 3072 rows, 256 to 12000 steps, N = 8 to 32, both
+//             types: 0.918 of the time without this shape (geometric mean), 11 slower by more than 2 %, at most 1.06 times (without those conditions 0.931, 524
+//             and 1.28); 756 passes over states alone: 0.918, 3 and 1.02 (0.932, 136 and 1.21)
 //   64 x 16:  one workgroup a compute unit (its tile takes the LDS), so at most 2048 rows, but fewer instructions
 //             than 64 x 8 (768 rows, L = 32768, N = 16, bf16: 284 us; 64 x 8: 328)
 // The costs were fitted before the issue priorities and the pairs of states changed the shapes unequally.  With the present kernels the
-// choice is 1.8 % (float32) and 0.7 % (bfloat16) slower than the best of the four and the chunked path over 729 calls of each type, at
+// choice is 1.8 % (float32) and 0.7 % (bfloat16) slower than the best of the first four and the chunked path over 729 calls of each type (before there was a fifth), at
 // most 1.30 times: N = 1 on 16 to 1500 rows of 1531 steps takes 64 x 16, 11.4 us for the 8.8 of 64 x 4.
 enum class FwdShape { l16, l64x4, l64x8, l64x16, l64x8w12 };
 struct FwdCost { int tile, state, wg, wg_state; };
@@ -545,11 +550,19 @@ static int64_t fwd_time(int64_t maps, int64_t dpg, int64_t N, int64_t L, bool f3
     if (shape == FwdShape::l64x8w12 && (wgs > kNumCU || N < 8 || maps * ((dpg + 7) / 8) <= kNumCU)) return INT64_MAX;
     return fwd_cost(kFwdCost[f32 ? 0 : 1][i], N, (L + steps[i] - 1) / steps[i], wgs);
 }
-static FwdShape fwd_shape(const FwdParams &p, bool f32) {
+// `outputs`: else the pass writes states alone.  `few`: up to there 64 x 4 is the faster where the last tile of 512 is at most half full (its time over that of
+// twelve wavefronts, geometric means: float32 N = 8 0.82 at 768 steps, 0.94 at 2304, 1.00 at 3073; N = 16 0.85, 0.97 at 1280, 1.03 at 1537; N = 32 0.89, 0.97,
+// 1.03; bf16 N = 8 0.84, 0.92 at 1280, 0.97 at 1792, 1.02 at 2049; N = 16 0.86, 0.96, 1.03 at 1537; N = 32 0.92, 1.02; states alone 0.86 to 0.99 at 768).
+static FwdShape fwd_shape(int64_t maps, int64_t dpg, int64_t N, int64_t L, bool f32, bool outputs) {
+    const bool twelve = fwd_time(maps, dpg, N, L, f32, FwdShape::l64x8w12) != INT64_MAX;
+    const bool one_more = twelve && (N == 8 || !outputs) && maps * ((dpg + 7) / 8) == kNumCU + 1 && (dpg + 7) % 8 < 4;
+    const int64_t few = !outputs ? (N > 8 ? 768 : 1280) : f32 ? (N > 8 ? 1280 : one_more ? 1792 : 3328) : N > 16 ? 768 : N > 8 ? 1280 : 1792;
+    const bool half = twelve && (L + 511) % 512 < 256 && L <= few;
     FwdShape best = FwdShape::l16;
     int64_t least = INT64_MAX;
     for (const FwdShape shape : kFwdShapes) {
-        const int64_t t = fwd_time((int64_t)p.B * p.bcg, p.dpg, p.N, p.L, f32, shape);
+        if (half && (shape == FwdShape::l64x8 || shape == FwdShape::l64x8w12)) continue;
+        const int64_t t = fwd_time(maps, one_more && shape == FwdShape::l64x8 ? 8 * kNumCU : dpg, N, L, f32, shape);       // (then maps is 1)
         if (t < least) { least = t; best = shape; }
     }
     return best;
@@ -603,7 +616,7 @@ template <typename IO, int N, int DISC>
 static hipError_t launch_fwd_n(const FwdParams &p, hipStream_t s) {
     // the aggregate launch skips the last chunk: nobody needs its pair
     if (p.mode == MODE_AGG && p.nchunks < 2) return hipSuccess;
-    switch (p.cu ? packed_shape(p, sizeof(IO) == 4) : p.nchunks == 1 ? fwd_shape(p, sizeof(IO) == 4) : FwdShape::l16) {
+    switch (p.cu ? packed_shape(p, sizeof(IO) == 4) : p.nchunks == 1 ? fwd_shape((int64_t)p.B * p.bcg, p.dpg, p.N, p.L, sizeof(IO) == 4, p.mode == MODE_FULL) : FwdShape::l16) {
         case FwdShape::l64x4: return launch_fwd_lanes<IO, N, DISC, 64, 4>(p, s);
         case FwdShape::l64x8: return launch_fwd_lanes<IO, N, DISC, 64, 8>(p, s);
         case FwdShape::l64x16: return launch_fwd_lanes<IO, N, DISC, 64, 16>(p, s);
@@ -648,6 +661,8 @@ hipError_t launch_ss_fwd(const FwdParams &p, int io_dtype, int disc, hipStream_t
     return io_dtype == 1 ? launch_fwd_io<bf16_t>(p, disc, s) : launch_ss_fwd_f32(p, disc, s);
 }
 
+// the shape of a single pass over a batch, as a number (for tests of the choice)
+int fwd_shape_number(int64_t maps, int64_t dpg, int64_t N, int64_t L, bool f32, bool outputs) { return (int)fwd_shape(maps, dpg, N, L, f32, outputs); }
 int fwd_channels_per_workgroup() { return FwdGeom<16, 16>::CH; }
 int fwd_tile_steps() { return FwdGeom<16, 16>::TILE; }
 
