@@ -86,7 +86,8 @@ __device__ __forceinline__ int slab_of(unsigned j, unsigned n, int deal) {
 }
 // Where dealing pays (a forward call and its adjoint, us, in turn and dealt): rows that are not whole lines (LTI, P = 1001, 8 x 8192 steps 632
 // and 568, P = 207, 20 x 1265 56 and 50; real coefficients, P = 129, 16 x 8001 158 and 130, P = 1000, 8 x 4096 257 and 234; complex, P = 1001,
-// 8 x 2048 254 and 233), and many slabs also where they share nothing (P = 1024, 8 x 2048: real 106.6 and 102.8, complex 212 and 203).  Few
+// 8 x 2048 254 and 233), and many slabs also where they share nothing (P = 1024: real, 8 x 2048 110.0 and 109.5, 8 x 8192 403 and 376; complex, 8 x 2048
+// 207 and 201; LTI, 8 x 8192 439.5 and 433).  Few
 // slabs of whole lines are as fast or faster in turn (LTI, P = 1024, 1 x 16384: 124 and 127; P = 256, 4 x 4096 40.0 and 40.5).
 inline int deal_slabs(bool whole, unsigned n) { return !whole || n >= 64; }
 
